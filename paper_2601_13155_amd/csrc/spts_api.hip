@@ -49,7 +49,7 @@ Workspace carve(const spts_model_desc& m, const Limits& L) {
     w.z = take(Np * (size_t)L.max_r * b);
     size_t inner = (size_t)(m.Dff > L.max_dlow ? m.Dff : L.max_dlow);
     w.big = take(Np * inner * b);
-    w.misc = take(4096);
+    w.misc = take(ARGMAX_SCRATCH_BYTES);
     w.seg = take(3 * (size_t)(SPTS_MAX_BATCH + 1) * sizeof(int64_t));   // segment descriptors of a batched call
     w.topk = take(TOPK_MULTI_SCRATCH_BYTES);                             // tables of the chip-wide TopK
     w.total = off;
@@ -614,7 +614,7 @@ int spts_greedy_token(spts_ctx* c, const void* x, const void* gamma_f, const voi
     // separate norm: over a table of this size the plain kernel streams faster than the fused one
     SPTS_HIP(c, launch_rmsnorm(x, gamma_f, m.rms_eps, xn, 1, m.D, c->bf16, c->stream));
     SPTS_HIP(c, launch_gemv(g, c->bf16, c->stream));
-    SPTS_HIP(c, launch_argmax_row(logits, V, token_out, table, m.D, x_next, c->bf16, c->stream));
+    SPTS_HIP(c, launch_argmax_rows(logits, V, 1, token_out, table, m.D, x_next, c->bf16, c->p<void>(c->off.misc), c->stream));
     return SPTS_OK;
 }
 
@@ -694,13 +694,10 @@ int spts_greedy_token_batched(spts_ctx* c, const void* x, const void* gamma_f, c
     void* xn = c->p<void>(c->off.xn);
     GemvArgs g{}; g.mode = GEMV_F32; g.x = xn; g.K = m.D; g.W[0] = table; g.R[0] = V; g.y[0] = logits;
     if (!gemv_supported(g, c->bf16)) return SPTS_ESHAPE;
-    const size_t eb = c->bf16 ? 2 : 4;
     PHASE(c, PH_DEC_HEAD);
     SPTS_HIP(c, launch_rmsnorm(x, gamma_f, m.rms_eps, xn, batch, m.D, c->bf16, c->stream));
     SPTS_HIP(c, launch_gemv_nb(g, batch, c->bf16, c->stream));
-    for (int b = 0; b < batch; ++b)
-        SPTS_HIP(c, launch_argmax_row(logits + (size_t)b * V, V, token_out + b, table, m.D,
-                                      x_next ? (char*)x_next + (size_t)b * m.D * eb : nullptr, c->bf16, c->stream));
+    SPTS_HIP(c, launch_argmax_rows(logits, V, batch, token_out, table, m.D, x_next, c->bf16, c->p<void>(c->off.misc), c->stream));
     return SPTS_OK;
 }
 

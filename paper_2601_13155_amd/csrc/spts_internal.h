@@ -271,8 +271,11 @@ hipError_t launch_decode_rope_append_batched(const float* q32, const float* k32,
 // out [n, H, d]: attention of sequence b's query over its count[b] + 1 cached pairs
 hipError_t launch_decode_attn_batched(const void* q, const DecodeBatch& db, int H, int Hkv, int d, float* part, size_t part_floats,
                                       void* out, bool bf16, hipStream_t s);
-// token = argmax(logits [V]) with ties to the lowest id; x_next [D] = table[token, :] (skipped when NULL)
-hipError_t launch_argmax_row(const float* logits, int V, int32_t* token, const void* table, int D, void* x_next, bool bf16,
-                             hipStream_t s);
+// token[b] = argmax(logits[b, 0..V)) with ties to the lowest id; x_next[b, 0..D) = table[token[b], :] (skipped when NULL), for
+// nrows <= DECODE_MAX_BATCH rows; V % 4 == 0; scratch: ARGMAX_SCRATCH_BYTES of device memory
+constexpr int ARGMAX_PARTS = 32;
+constexpr size_t ARGMAX_SCRATCH_BYTES = 4096;
+hipError_t launch_argmax_rows(const float* logits, int V, int nrows, int32_t* token, const void* table, int D, void* x_next, bool bf16,
+                              void* scratch, hipStream_t s);
 
 }  // namespace spts

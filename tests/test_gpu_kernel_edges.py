@@ -1,0 +1,44 @@
+"""Kernels at the sizes where their tiles, groups and splits begin and end, against the CPU oracle (through the C ABI)."""
+import numpy as np
+import pytest
+
+from paper_2601_13155_amd import runtime, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+# ------------------------------------------------------------------------------------------ greedy head
+@pytest.mark.parametrize("V", [16, 1008, 1024 * 32, 1024 * 32 + 16, 128256])   # (batched calls take multiples of 16)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_argmax_picks_the_lowest_id_of_equal_logits(torch, dtype, V):
+    """Logits are whole numbers here (one non-zero state element, integer table): ties are exact and lie in different shares of
+    the row; a row of all-equal logits gives id 0."""
+    D, nb = 64, 3
+    shape = synth.ModelShape(D=D, H=1, Hkv=1, d=64, Dff=64, dtype=dtype, rms_eps=0.0)
+    ctx = runtime.make_context(shape, 16, 1, 1, 64)
+    rng = np.random.default_rng(V)
+    table = np.zeros((V, D), dtype=np.float32)
+    table[:, :2] = rng.integers(-3, 3, (V, 2))
+    best = sorted(rng.integers(0, V, 5).tolist())
+    table[best, 0] = 4.0                      # row 0 of the batch: tie between these ids
+    table[V - 1, 1] = 5.0                     # row 1: the very last id
+    x = np.zeros((nb, D), dtype=np.float32)
+    x[0, 0] = x[1, 1] = x[2, 5] = 1.0         # rows 2: every logit is zero
+    td = runtime.to_device(table, dtype)
+    xd, gd = runtime.to_device(x, dtype), runtime.to_device(np.ones(D, dtype=np.float32), dtype)
+    tok = torch.full((nb,), -1, dtype=torch.int32, device="cuda")
+    logits = torch.zeros((nb, V), dtype=torch.float32, device="cuda")
+    nxt = torch.zeros_like(xd)
+    ctx.spts_greedy_token_batched(xd, gd, td, V, nb, tok, logits, nxt)
+    assert tok.cpu().tolist() == [best[0], V - 1, 0]
+    assert torch.equal(nxt, td[tok.long()])
+    one = torch.full((4,), -1, dtype=torch.int32, device="cuda")
+    ctx.spts_greedy_token(xd[0], gd, td, V, one, logits[0], None)
+    assert int(one[0]) == best[0]
