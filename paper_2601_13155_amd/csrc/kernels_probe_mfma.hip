@@ -13,6 +13,9 @@
 // (32*RB rows per wavefront); K tiles of 64 keys go through LDS (swizzled, shared by the 4
 // wavefronts).  Pass 1 computes S^T = K Q^T (one probe row per lane column: row max in-lane),
 // pass 2 computes S = Q K^T (one key per lane column: the sum over rows is in-lane).
+// Up to 512 rows per kv head are one workgroup's; more (7 query heads per kv head x 128 probe rows = 896, say) are dealt to
+// row groups of 512 (grid z), each of which streams K for itself and leaves its own part[group][g][n].  (They used to take the
+// fp32 kernels: a layer of 8192 tokens with 896 probe rows per kv head, 64.4 -> 2.03 ms.)
 #include "spts_internal.h"
 
 namespace spts {
@@ -44,6 +47,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
     __shared__ float sRed[NWV][PKV];
 
     const int chunk = blockIdx.x, g = blockIdx.y;
+    const int row_base = (int)blockIdx.z * (32 * RB * NWV);   // first probe row of this row group
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     const int grp = a.H / a.Hkv;
@@ -58,7 +62,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
     const bf16_t* Q = (const bf16_t*)a.qp;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        int rr = wave * 32 * RB + rb * 32 + l32;
+        int rr = row_base + wave * 32 * RB + rb * 32 + l32;
         int rc = rr < R ? rr : R - 1;
         int p = rc / grp, hg = rc % grp;
         vis_last[rb] = rr < R ? (int)(a.N - a.P + p) : -1;
@@ -90,7 +94,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int rr = wave * 32 * RB + rb * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
+                const int rr = row_base + wave * 32 * RB + rb * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
                 const float2 st = *reinterpret_cast<const float2*>(stats + ((int64_t)g * Rp + rr) * 2);
                 coff[rb][r] = st.y > 0.f ? __builtin_amdgcn_logf(st.y) - st.x : -INFINITY;
                 const uint32_t enc = rr < R ? (uint32_t)(rr / grp + 1) : 0u;
@@ -203,7 +207,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
                     float tot = sRed[0][tid];
 #pragma unroll
                     for (int wv = 1; wv < NWV; ++wv) tot += sRed[wv][tid];   // fixed order
-                    a.partial[(int64_t)g * Np + key] = tot;
+                    a.partial[((int64_t)blockIdx.z * a.Hkv + g) * Np + key] = tot;
                 }
             }
         }
@@ -214,7 +218,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             float l = l_run[rb] + __shfl_xor(l_run[rb], 32);
-            int rr = wave * 32 * RB + rb * 32 + l32;
+            int rr = row_base + wave * 32 * RB + rb * 32 + l32;
             if (lh == 0) {
                 float* o = stats_part + (((int64_t)chunk * a.Hkv + g) * Rp + rr) * 2;
                 o[0] = m_run[rb];
@@ -251,24 +255,30 @@ __global__ void __launch_bounds__(256) probe_combine_kernel(const float* __restr
     }
 }
 
-__global__ void probe_final_kernel(const float* __restrict__ part, float* __restrict__ S, int64_t N, int64_t Np, int Hkv,
+__global__ void probe_final_kernel(const float* __restrict__ part, float* __restrict__ S, int64_t N, int64_t Np, int nparts,
                                    float inv_rows) {
     int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= N) return;
     float acc = 0.f;
-    for (int g = 0; g < Hkv; ++g) acc += part[(int64_t)g * Np + n];
+    for (int g = 0; g < nparts; ++g) acc += part[(int64_t)g * Np + n];   // (row group, kv head) in order
     S[n] = acc * inv_rows;
 }
 
-static inline int probe_rp(int P, int H, int Hkv) { int R = P * (H / Hkv); return (R + 127) / 128 * 128; }
+// probe rows per kv head, padded to whole wavefronts' shares: a multiple of 128 up to 512, of 512 (row groups) beyond
+constexpr int PROBE_GROUP_ROWS = 512;
+static inline int probe_rp(int P, int H, int Hkv) {
+    const int R = P * (H / Hkv), Rp = (R + 127) / 128 * 128;
+    return Rp <= PROBE_GROUP_ROWS ? Rp : (Rp + PROBE_GROUP_ROWS - 1) / PROBE_GROUP_ROWS * PROBE_GROUP_ROWS;
+}
+static inline int probe_groups(int Rp) { return (Rp + PROBE_GROUP_ROWS - 1) / PROBE_GROUP_ROWS; }
 
 size_t probe_scratch_floats(int64_t N, int P, int H, int Hkv) {
     // generic path: stats [P*H, 2].  Matrix-core path: stats_part [nchunks][Hkv][Rp][2] + stats [Hkv][Rp][2]
-    // + part [Hkv][Np]
+    // + part [groups][Hkv][Np]
     int64_t Np = (N + 255) / 256 * 256;
     int64_t nchunks = (N + CHUNK - 1) / CHUNK;
     int64_t Rp = probe_rp(P, H, Hkv);
-    const size_t windowed = (size_t)(2 * (int64_t)P * H + 64) + (size_t)(nchunks * Hkv * Rp * 2 + Hkv * Rp * 2 + Hkv * Np + 256);
+    const size_t windowed = (size_t)(2 * (int64_t)P * H + 64) + (size_t)(nchunks * Hkv * Rp * 2 + Hkv * Rp * 2 + probe_groups((int)Rp) * Hkv * Np + 256);
     const size_t single = probe_p1_scratch_floats(N, H);   // the single-row probe uses the same region from its start
     return windowed > single ? windowed : single;
 }
@@ -276,7 +286,7 @@ size_t probe_scratch_floats(int64_t N, int P, int H, int Hkv) {
 bool probe_mfma_supported(const ProbeArgs& a) {
     if (a.d != 128 && a.d != 64) return false;
     if (a.N <= 0 || a.P <= 0 || a.H % a.Hkv != 0) return false;
-    if (probe_rp(a.P, a.H, a.Hkv) > 512) return false;
+    if (a.P >= 65535) return false;   // window rows are kept in 16 bits (pass 2)
     auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     return al(a.qp) && al(a.k);
 }
@@ -293,11 +303,12 @@ static hipError_t launch_probe_t(const ProbeArgs& a, int Rp, hipStream_t s) {
     b.partial = part;
     const float want = attention_mfma_q_scale(D);
     const float qmul = (a.q_scale != 0.f) ? want / a.q_scale : want;   // exactly 1 when the producer applied `want`
-    dim3 grid(nchunks, a.Hkv), block(256), pblock(64 * NWV);
+    const int groups = probe_groups(Rp);
+    dim3 grid(nchunks, a.Hkv, groups), block(256), pblock(64 * NWV);
     probe_mfma_kernel<D, RB, 1, NWV><<<grid, pblock, 0, s>>>(b, Rp, Np, qmul, stats_part, nullptr);
     probe_combine_kernel<<<dim3((a.Hkv * Rp + 3) / 4), block, 0, s>>>(stats_part, stats, nchunks, a.Hkv, Rp, R);
     probe_mfma_kernel<D, RB, 2, NWV><<<grid, pblock, 0, s>>>(b, Rp, Np, qmul, nullptr, stats);
-    probe_final_kernel<<<dim3((unsigned)((a.N + 255) / 256)), block, 0, s>>>(part, a.S, a.N, Np, a.Hkv, 1.0f / (float)(a.P * a.H));
+    probe_final_kernel<<<dim3((unsigned)((a.N + 255) / 256)), block, 0, s>>>(part, a.S, a.N, Np, groups * a.Hkv, 1.0f / (float)(a.P * a.H));
     return hipGetLastError();
 }
 
@@ -308,7 +319,7 @@ hipError_t launch_probe_mfma(const ProbeArgs& a, hipStream_t s) {
         if (rb == 1) return launch_probe_t<128, 1>(a, Rp, s);
         if (rb == 2) return launch_probe_t<128, 2>(a, Rp, s);
         if (rb == 3) return launch_probe_t<128, 3>(a, Rp, s);
-        return launch_probe_t<128, 2, 8>(a, Rp, s);   // 512 rows: 8 wavefronts x 64 rows keep two wavefronts per SIMD
+        return launch_probe_t<128, 2, 8>(a, Rp, s);   // 512 rows (per group): 8 wavefronts x 64 rows keep two wavefronts per SIMD
     }
     if (rb == 1) return launch_probe_t<64, 1>(a, Rp, s);
     if (rb == 2) return launch_probe_t<64, 2>(a, Rp, s);

@@ -2,7 +2,9 @@
 import numpy as np
 import pytest
 
+from oracle import spts_oracle as orc
 from paper_2601_13155_amd import runtime, synth
+from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
 
@@ -12,6 +14,29 @@ def torch():
     import torch
     assert torch.cuda.is_available()
     return torch
+
+
+def _mk(shape, N, r, seed):
+    return (synth.make_layer(seed, 0, shape, r), synth.hidden_states(seed, N, shape.D, shape.dtype),
+            (synth.positions(N) * 2 + 1).astype(np.int32))
+
+
+# ------------------------------------------------------------------------------------------ probe row groups
+# more than 512 probe rows per kv head: 513..1024 rows are two row groups (525: the second nearly empty), 1040 are three
+@pytest.mark.parametrize("H_,Hkv,d,P,N", [(7, 1, 128, 75, 600), (14, 2, 128, 128, 1111), (7, 1, 64, 74, 74), (16, 2, 64, 130, 513)],
+                         ids=["525rows", "896rows", "518rows_all_probe", "1040rows"])
+def test_probe_row_groups(torch, H_, Hkv, d, P, N):
+    shape = synth.ModelShape(D=512, H=H_, Hkv=Hkv, d=d, Dff=256, dtype="bf16")
+    w, x, pos = _mk(shape, N, 16, 7)
+    ctx = runtime.make_context(shape, N, P, 16, shape.Dff)
+    dw = runtime.upload_layer(w, shape, 16)
+    kd = torch.zeros((N, Hkv, d), dtype=torch.bfloat16, device="cuda")
+    sd = torch.zeros(N, dtype=torch.float32, device="cuda")
+    ctx.spts_probe_attn(runtime.to_device(x, "bf16"), torch.from_numpy(pos).cuda(), N, dw, P, kd, sd)
+    _, S = orc.probe_attn(x, pos, w, H.oracle_model(shape), P, H.rnd_for("bf16"))
+    s = sd.cpu().numpy()
+    assert H.score_rel_err(s, S) <= H.TOL["bf16"]["score"]
+    assert abs(float(s.astype(np.float64).sum()) - 1.0) < 1e-3
 
 
 # ------------------------------------------------------------------------------------------ greedy head
