@@ -1,161 +1,297 @@
-// Shape-agnostic causal GQA attention and PAP probe scoring with fp32 arithmetic.  These serve the
-// fp32 configuration and head dimensions / dtypes the matrix-core kernels do not take.
+// Causal GQA attention and PAP probe scoring with fp32 arithmetic, any even head dimension up to 256: the fp32 configuration
+// and the head dimensions / types the bf16 matrix-core kernels do not take.
+//
+// All products run on the fp32 matrix instruction v_mfma_f32_32x32x2_f32 (fp32 products and sums; bf16 inputs are widened).
+// What bounds these kernels at the fp32 configuration's sizes (256-2048 rows, d = 64) is the latency of dependent loads, so
+// operand fragments come straight from global memory, a lane's whole row piece at once (element j of a lane's 4-element
+// piece is the operand of product j: which k an instruction multiplies is free as long as both operands agree), and the
+// wavefronts of a workgroup split the keys (attention, statistics) or the probe rows (scores) and meet in LDS.
+// Measured at N = 512, 4 heads, d = 64: attention of 256 queries 50 -> 35 us against one wavefront per query row; probe of 32
+// rows 1001 -> 22 us (two launches) against one lane per candidate that walked all P * H rows.
 #include "spts_internal.h"
 
 namespace spts {
 
-constexpr int MAX_D = 256;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// wavefronts per workgroup: eight, four where a row's pieces need more than 256 registers
+template <int D> constexpr int f32_waves() { return D <= 64 ? 8 : 4; }
+constexpr float LOG2E = 1.4426950408889634f;
+
+// elements c .. c+3 of a row of d elements as fp32, zeros past its end; d4: d % 4 == 0 (the piece is then one aligned load)
+__device__ inline f32x4 load4(const float* row, int c, int d, bool d4) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (d4) { if (c < d) v = *reinterpret_cast<const f32x4*>(row + c); return v; }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) if (c + e < d) v[e] = row[c + e];
+    return v;
+}
+__device__ inline f32x4 load4(const bf16_t* row, int c, int d, bool d4) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (d4) {
+        if (c < d) {
+            const u32x2 w = *reinterpret_cast<const u32x2*>(row + c);
+            v = f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16), __uint_as_float(w[1] & 0xffff0000u)};
+        }
+        return v;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) if (c + e < d) v[e] = bf16_to_f32(row[c + e]);
+    return v;
+}
+
+// acc += a b^T over the 32-row operands whose row pieces (8 s + 4 lh ..) are in fa / fb
+template <int NS>
+__device__ inline f32x16 mma_rows(const f32x4 (&fa)[NS], const f32x4 (&fb)[NS]) {
+    f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NS; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[t][j], fb[t][j], s, 0, 0, 0);
+    return s;
+}
+// row (or key) inside a 32-block that accumulator register r of lane half lh holds
+__device__ inline int acc_row(int r, int lh) { return 8 * (r >> 2) + 4 * lh + (r & 3); }
 
 // ---------------------------------------------------------------- attention
-// One wavefront per (query row, head).  Keys are visited in chunks of 64 (one key per lane for the
-// logits, one output column group per lane for the value sum) with an online softmax.
-template <typename T>
-__global__ void __launch_bounds__(64) attention_generic_kernel(AttnArgs a) {
-    __shared__ float qs[MAX_D];
-    __shared__ float ps[64];
-    const int64_t i = blockIdx.x;
-    const int h = blockIdx.y;
-    const int g = h / (a.H / a.Hkv);
-    const int lane = threadIdx.x;
-    const int d = a.d;
-    const T* q = (const T*)a.q + (i * a.H + h) * (int64_t)d;
-    const T* K = (const T*)a.k;
-    const T* V = (const T*)a.v;
-    const float scale = 1.0f / sqrtf((float)d) / (a.q_scale != 0.f ? a.q_scale : 1.0f);   // q may arrive pre-scaled
-    for (int j = lane; j < d; j += 64) qs[j] = to_f32(q[j]);
-    __syncthreads();
-    const int qp = a.qpos[i];
-
-    float m = -INFINITY, l = 0.f;
-    float acc[MAX_D / 64] = {};
-    for (int64_t j0 = 0; j0 < a.Mk; j0 += 64) {
-        if (a.kpos[j0] > qp) break;  // ascending positions: nothing visible from here on
-        int64_t j = j0 + lane;
-        float logit = -INFINITY;
-        if (j < a.Mk && a.kpos[j] <= qp) {
-            const T* kr = K + (j * a.Hkv + g) * (int64_t)d;
-            float s = 0.f;
-            for (int c = 0; c < d; ++c) s = fmaf(qs[c], to_f32(kr[c]), s);
-            logit = s * scale;
-        }
-        float cm = logit;
-        for (int off = 32; off > 0; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off));
-        float m_new = fmaxf(m, cm);  // finite: the chunk's first key is visible
-        float p = (logit == -INFINITY) ? 0.f : expf(logit - m_new);
-        float csum = p;
-        for (int off = 32; off > 0; off >>= 1) csum += __shfl_xor(csum, off);
-        float alpha = (m == -INFINITY) ? 0.f : expf(m - m_new);
-        l = l * alpha + csum;
-        m = m_new;
-        ps[lane] = p;
-        __syncthreads();
-        int64_t nk = a.Mk - j0 < 64 ? a.Mk - j0 : 64;
+// Workgroup = 32 queries of one head.  A wavefront takes every GW-th block of 32 keys: S^T = K Q^T (one query per lane column:
+// the softmax is in-lane), online softmax, O^T += V^T P^T with the probabilities as they left the first product.  D: head
+// dimension rounded up to 32 / 64 / 128 / 256.
+template <typename T, int D>
+__global__ void __launch_bounds__(64 * f32_waves<D>()) attention_f32_kernel(AttnArgs a) {
+    constexpr int NS = D / 8, DB = D / 32, GW = f32_waves<D>();
+    __shared__ float sm[GW][32], sl[GW][32];
+    __shared__ __attribute__((aligned(16))) float so[32][D + 4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int h = blockIdx.y, g = h / (a.H / a.Hkv), d = a.d;
+    const int64_t q0 = (int64_t)(gridDim.x - 1 - blockIdx.x) * 32;   // longest causal ranges first
+    const bool d4 = d % 4 == 0;
+    const float scale = LOG2E / sqrtf((float)d) / (a.q_scale != 0.f ? a.q_scale : 1.0f);   // q may arrive pre-scaled
+    const int64_t qi = q0 + l32 < a.Mq ? q0 + l32 : a.Mq - 1;
+    const int qp = a.qpos[qi];
+    const int qp_last = a.qpos[(q0 + 32 < a.Mq ? q0 + 32 : a.Mq) - 1];
+    const T* K = (const T*)a.k + (int64_t)g * d;
+    const T* V = (const T*)a.v + (int64_t)g * d;
+    const int64_t rstride = (int64_t)a.Hkv * d;
+    f32x4 qf[NS];
+    {
+        const T* qr = (const T*)a.q + (qi * a.H + h) * (int64_t)d;
 #pragma unroll
-        for (int t = 0; t < MAX_D / 64; ++t) {
-            int c = lane + 64 * t;
-            if (c < d) {
-                float s = acc[t] * alpha;
-                for (int64_t jj = 0; jj < nk; ++jj) s = fmaf(ps[jj], to_f32(V[((j0 + jj) * a.Hkv + g) * (int64_t)d + c]), s);
-                acc[t] = s;
+        for (int t = 0; t < NS; ++t) qf[t] = load4(qr, 8 * t + 4 * lh, d, d4);
+    }
+    float m = -INFINITY, l = 0.f;
+    f32x16 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+
+    for (int64_t j0 = wave * 32; j0 < a.Mk; j0 += 32 * GW) {
+        if (a.kpos[j0] > qp_last) break;   // ascending positions: nothing visible from here on
+        const int64_t jk = j0 + l32 < a.Mk ? j0 + l32 : a.Mk - 1;
+        f32x4 kf[NS];
+#pragma unroll
+        for (int t = 0; t < NS; ++t) kf[t] = load4(K + jk * rstride, 8 * t + 4 * lh, d, d4);
+        int kp[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int64_t j = j0 + acc_row(r, lh);
+            kp[r] = a.kpos[j < a.Mk ? j : a.Mk - 1];
+        }
+        const f32x16 s = mma_rows<NS>(kf, qf);
+        float p[16], mx = m;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            p[r] = j0 + acc_row(r, lh) < a.Mk && kp[r] <= qp ? s[r] * scale : -INFINITY;
+            mx = fmaxf(mx, p[r]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mu = mx == -INFINITY ? 0.f : mx;   // none of the query's keys seen yet
+        const float alpha = __builtin_amdgcn_exp2f(m - mu);
+        m = mx;
+        l *= alpha;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { p[r] = __builtin_amdgcn_exp2f(p[r] - mu); l += p[r]; }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const int c = db * 32 + l32;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                int64_t j = j0 + acc_row(r, lh);
+                if (j >= a.Mk) j = a.Mk - 1;   // its probability is zero
+                const float vv = c < d ? to_f32(V[j * rstride + c]) : 0.f;
+                if (r == 0)
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) o[db][t] *= alpha;
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv, p[r], o[db], 0, 0, 0);
             }
         }
+    }
+    l += __shfl_xor(l, 32);
+    if (lh == 0) { sm[wave][l32] = m; sl[wave][l32] = l; }
+    __syncthreads();
+    float mg = -INFINITY, lg = 0.f;
+#pragma unroll
+    for (int w = 0; w < GW; ++w) mg = fmaxf(mg, sm[w][l32]);
+    const float mu = mg == -INFINITY ? 0.f : mg;
+#pragma unroll
+    for (int w = 0; w < GW; ++w) lg += sl[w][l32] * __builtin_amdgcn_exp2f(sm[w][l32] - mu);
+    const float f = __builtin_amdgcn_exp2f(m - mu) * (lg > 0.f ? 1.0f / lg : 0.f);
+    for (int w = 0; w < GW; ++w) {   // one wavefront after the other: a fixed order of the sums
+        if (wave == w) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f32x4* dst = reinterpret_cast<f32x4*>(&so[l32][db * 32 + 8 * q + 4 * lh]);
+                    const f32x4 v = {o[db][4 * q] * f, o[db][4 * q + 1] * f, o[db][4 * q + 2] * f, o[db][4 * q + 3] * f};
+                    *dst = w == 0 ? v : *dst + v;
+                }
+        }
         __syncthreads();
     }
-    T* o = (T*)a.out + (i * a.H + h) * (int64_t)d;
-    float inv = l > 0.f ? 1.0f / l : 0.f;
-#pragma unroll
-    for (int t = 0; t < MAX_D / 64; ++t) {
-        int c = lane + 64 * t;
-        if (c < d) o[c] = from_f32<T>(acc[t] * inv);
+    for (int t = tid; t < 32 * d; t += 64 * GW) {
+        const int r = t / d, c = t - r * d;
+        if (q0 + r < a.Mq) ((T*)a.out)[((q0 + r) * a.H + h) * (int64_t)d + c] = from_f32<T>(so[r][c]);
     }
+}
+
+template <typename T>
+static void launch_attention_f32_t(const AttnArgs& a, hipStream_t s) {
+    const dim3 grid((unsigned)((a.Mq + 31) / 32), (unsigned)a.H);
+    if (a.d <= 32) attention_f32_kernel<T, 32><<<grid, dim3(64 * f32_waves<32>()), 0, s>>>(a);
+    else if (a.d <= 64) attention_f32_kernel<T, 64><<<grid, dim3(64 * f32_waves<64>()), 0, s>>>(a);
+    else if (a.d <= 128) attention_f32_kernel<T, 128><<<grid, dim3(64 * f32_waves<128>()), 0, s>>>(a);
+    else attention_f32_kernel<T, 256><<<grid, dim3(64 * f32_waves<256>()), 0, s>>>(a);
 }
 
 hipError_t launch_attention_generic(const AttnArgs& a, bool bf16, hipStream_t s) {
     if (a.Mq == 0) return hipSuccess;
-    dim3 grid((unsigned)a.Mq, (unsigned)a.H), block(64);
-    if (bf16) attention_generic_kernel<bf16_t><<<grid, block, 0, s>>>(a);
-    else attention_generic_kernel<float><<<grid, block, 0, s>>>(a);
+    if (a.d > 256) return hipErrorInvalidValue;
+    if (bf16) launch_attention_f32_t<bf16_t>(a, s); else launch_attention_f32_t<float>(a, s);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- probe (Eq. (mha_importance))
-// Pass 1: one workgroup per probe row (p, h): max and sum of exp over the visible candidates.
-template <typename T>
-__global__ void __launch_bounds__(256) probe_stats_generic_kernel(ProbeArgs a) {
-    __shared__ float qs[MAX_D];
-    __shared__ float red[4];
-    const int p = blockIdx.x / a.H, h = blockIdx.x % a.H;
-    const int g = h / (a.H / a.Hkv);
-    const int d = a.d;
-    const T* q = (const T*)a.qp + ((int64_t)p * a.H + h) * d;
-    const T* K = (const T*)a.k;
-    const float scale = 1.0f / sqrtf((float)d) / (a.q_scale != 0.f ? a.q_scale : 1.0f);   // q may arrive pre-scaled
-    for (int j = threadIdx.x; j < d; j += 256) qs[j] = to_f32(q[j]);
-    __syncthreads();
-    const int64_t nvis = a.N - a.P + p + 1;  // candidates 0 .. N-P+p
-    float m = -INFINITY;
-    for (int64_t n = threadIdx.x; n < nvis; n += 256) {
-        const T* kr = K + (n * a.Hkv + g) * (int64_t)d;
-        float s = 0.f;
-        for (int c = 0; c < d; ++c) s = fmaf(qs[c], to_f32(kr[c]), s);
-        m = fmaxf(m, s * scale);
+// Probe row rr = p * grp + hg of kv head g <-> qp[p, g * grp + hg, :]; window row p sees candidates 0 .. N - P + p.
+// Pass 1: a workgroup takes 32 probe rows of one kv head and all candidates (its wavefronts every GW-th block of 32), leaving
+// the rows' maximum (log2 units) and 1 / sum of exponentials.
+template <typename T, int D>
+__global__ void __launch_bounds__(64 * f32_waves<D>()) probe_stats_f32_kernel(ProbeArgs a) {
+    constexpr int NS = D / 8, GW = f32_waves<D>();
+    __shared__ float sm[GW][32], sl[GW][32];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int grp = a.H / a.Hkv, g = blockIdx.y, R = a.P * grp, d = a.d;
+    const int rr = blockIdx.x * 32 + l32, rc = rr < R ? rr : R - 1;
+    const bool d4 = d % 4 == 0;
+    const float scale = LOG2E / sqrtf((float)d) / (a.q_scale != 0.f ? a.q_scale : 1.0f);
+    const int64_t last = a.N - a.P + rc / grp;   // last candidate the lane's row sees
+    const int64_t rstride = (int64_t)a.Hkv * d;
+    f32x4 qf[NS];
+    {
+        const T* qr = (const T*)a.qp + ((int64_t)(rc / grp) * a.H + g * grp + rc % grp) * d;
+#pragma unroll
+        for (int t = 0; t < NS; ++t) qf[t] = load4(qr, 8 * t + 4 * lh, d, d4);
     }
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    __syncthreads();
-    float l = 0.f;
-    for (int64_t n = threadIdx.x; n < nvis; n += 256) {
-        const T* kr = K + (n * a.Hkv + g) * (int64_t)d;
-        float s = 0.f;
-        for (int c = 0; c < d; ++c) s = fmaf(qs[c], to_f32(kr[c]), s);
-        l += expf(s * scale - m);
+    float m = -INFINITY, l = 0.f;
+    for (int64_t n0 = wave * 32; n0 < a.N; n0 += 32 * GW) {
+        const int64_t nk = n0 + l32 < a.N ? n0 + l32 : a.N - 1;
+        const T* kr = (const T*)a.k + nk * rstride + (int64_t)g * d;
+        f32x4 kf[NS];
+#pragma unroll
+        for (int t = 0; t < NS; ++t) kf[t] = load4(kr, 8 * t + 4 * lh, d, d4);
+        const f32x16 s = mma_rows<NS>(kf, qf);
+        float v[16], mx = m;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { v[r] = n0 + acc_row(r, lh) <= last ? s[r] * scale : -INFINITY; mx = fmaxf(mx, v[r]); }
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mu = mx == -INFINITY ? 0.f : mx;
+        l *= __builtin_amdgcn_exp2f(m - mu);
+        m = mx;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) l += __builtin_amdgcn_exp2f(v[r] - mu);
     }
-    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = l;
+    l += __shfl_xor(l, 32);
+    if (lh == 0) { sm[wave][l32] = m; sl[wave][l32] = l; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        a.stats[2 * blockIdx.x] = m;
-        a.stats[2 * blockIdx.x + 1] = red[0] + red[1] + red[2] + red[3];
+    if (threadIdx.x < 32 && rr < R) {
+        float mg = -INFINITY, lg = 0.f;
+#pragma unroll
+        for (int w = 0; w < GW; ++w) mg = fmaxf(mg, sm[w][l32]);
+#pragma unroll
+        for (int w = 0; w < GW; ++w) lg += sl[w][l32] * __builtin_amdgcn_exp2f(sm[w][l32] - mg);   // a row sees at least one candidate
+        float* st = a.stats + ((int64_t)g * R + rr) * 2;
+        st[0] = mg;
+        st[1] = 1.0f / lg;
     }
 }
 
-// Pass 2: one lane per candidate, rows visited in a fixed order (deterministic sum).
-template <typename T>
-__global__ void __launch_bounds__(256) probe_accum_generic_kernel(ProbeArgs a) {
-    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= a.N) return;
-    const int d = a.d;
-    const T* K = (const T*)a.k;
-    const T* Q = (const T*)a.qp;
-    const float scale = 1.0f / sqrtf((float)d) / (a.q_scale != 0.f ? a.q_scale : 1.0f);   // q may arrive pre-scaled
-    const int grp = a.H / a.Hkv;
+// Pass 2: a workgroup takes 32 candidates, its wavefronts every GW-th (kv head, 32 probe rows): S = Q K^T (one candidate per lane
+// column: the sum over rows is in-lane), fixed order of all sums.
+template <typename T, int D>
+__global__ void __launch_bounds__(64 * f32_waves<D>()) probe_scores_f32_kernel(ProbeArgs a) {
+    constexpr int NS = D / 8, GW = f32_waves<D>();
+    __shared__ float ss[GW][32];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int grp = a.H / a.Hkv, R = a.P * grp, nrb = (R + 31) / 32, d = a.d;
+    const bool d4 = d % 4 == 0;
+    const float scale = LOG2E / sqrtf((float)d) / (a.q_scale != 0.f ? a.q_scale : 1.0f);
+    const int64_t n = (int64_t)blockIdx.x * 32 + l32, nc = n < a.N ? n : a.N - 1;
     float acc = 0.f;
-    for (int p = 0; p < a.P; ++p) {
-        if (n > a.N - a.P + p) continue;
-        for (int h = 0; h < a.H; ++h) {
-            const T* kr = K + (n * a.Hkv + h / grp) * (int64_t)d;
-            const T* q = Q + ((int64_t)p * a.H + h) * d;
-            float s = 0.f;
-            for (int c = 0; c < d; ++c) s = fmaf(to_f32(q[c]), to_f32(kr[c]), s);
-            float m = a.stats[2 * (p * a.H + h)], l = a.stats[2 * (p * a.H + h) + 1];
-            acc += expf(s * scale - m) / l;
+    for (int item = wave; item < a.Hkv * nrb; item += GW) {
+        const int g = item / nrb, r0 = (item % nrb) * 32;
+        const int rc = r0 + l32 < R ? r0 + l32 : R - 1;
+        const T* qr = (const T*)a.qp + ((int64_t)(rc / grp) * a.H + g * grp + rc % grp) * d;
+        const T* kr = (const T*)a.k + (nc * a.Hkv + g) * (int64_t)d;
+        f32x4 qf[NS], kf[NS];
+#pragma unroll
+        for (int t = 0; t < NS; ++t) { qf[t] = load4(qr, 8 * t + 4 * lh, d, d4); kf[t] = load4(kr, 8 * t + 4 * lh, d, d4); }
+        float2 st[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int rr = r0 + acc_row(r, lh);
+            st[r] = rr < R ? *reinterpret_cast<const float2*>(a.stats + ((int64_t)g * R + rr) * 2) : make_float2(0.f, 0.f);
+        }
+        const f32x16 s = mma_rows<NS>(qf, kf);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int rr = r0 + acc_row(r, lh);
+            if (rr < R && n <= a.N - a.P + rr / grp) acc += __builtin_amdgcn_exp2f(s[r] * scale - st[r].x) * st[r].y;
         }
     }
-    a.S[n] = acc / (float)(a.P * a.H);
+    acc += __shfl_xor(acc, 32);
+    if (lh == 0) ss[wave][l32] = acc;
+    __syncthreads();
+    if (threadIdx.x < 32 && n < a.N) {
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < GW; ++w) t += ss[w][l32];
+        a.S[n] = t / (float)(a.P * a.H);
+    }
+}
+
+template <typename T, int D>
+static void launch_probe_f32_t(const ProbeArgs& a, hipStream_t s) {
+    const int R = a.P * (a.H / a.Hkv);
+    probe_stats_f32_kernel<T, D><<<dim3((unsigned)((R + 31) / 32), (unsigned)a.Hkv), dim3(64 * f32_waves<D>()), 0, s>>>(a);
+    probe_scores_f32_kernel<T, D><<<dim3((unsigned)((a.N + 31) / 32)), dim3(64 * f32_waves<D>()), 0, s>>>(a);
+}
+template <typename T>
+static void launch_probe_f32_d(const ProbeArgs& a, hipStream_t s) {
+    if (a.d <= 32) launch_probe_f32_t<T, 32>(a, s);
+    else if (a.d <= 64) launch_probe_f32_t<T, 64>(a, s);
+    else if (a.d <= 128) launch_probe_f32_t<T, 128>(a, s);
+    else launch_probe_f32_t<T, 256>(a, s);
 }
 
 hipError_t launch_probe_generic(const ProbeArgs& a, bool bf16, hipStream_t s) {
     if (a.N == 0) return hipSuccess;
-    dim3 g1((unsigned)(a.P * a.H)), g2((unsigned)((a.N + 255) / 256)), b(256);
-    if (bf16) {
-        probe_stats_generic_kernel<bf16_t><<<g1, b, 0, s>>>(a);
-        probe_accum_generic_kernel<bf16_t><<<g2, b, 0, s>>>(a);
-    } else {
-        probe_stats_generic_kernel<float><<<g1, b, 0, s>>>(a);
-        probe_accum_generic_kernel<float><<<g2, b, 0, s>>>(a);
-    }
+    if (a.d > 256) return hipErrorInvalidValue;
+    if (bf16) launch_probe_f32_d<bf16_t>(a, s); else launch_probe_f32_d<float>(a, s);
     return hipGetLastError();
 }
 

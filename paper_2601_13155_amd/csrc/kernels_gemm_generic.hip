@@ -1,9 +1,142 @@
-// Shape-agnostic C = A * B^T (A [M,K] rows optionally gathered, B [N,K]) with fp32 accumulation and
-// the SPTS epilogues.  Serves the fp32 configuration and any shape the matrix-core kernel does not
-// take (dimensions that are not tile multiples).  64x64 output tile, 256 threads, 4x4 per thread.
+// C = A * B^T (A [M,K] rows optionally gathered, B [N,K]) with fp32 accumulation and the SPTS epilogues for whatever the
+// 256-wide matrix-core kernel does not take: fp32, and bf16 with dimensions that are not tile multiples.
+//
+//  * gemm_tile32_kernel (rows of whole 16-byte chunks): 32x32 output tile per workgroup, the four wavefronts split K and
+//    meet in LDS.  fp32 runs on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: fp32 products and sums, 157 TFLOP/s,
+//    twice what the vector ALU has without packed instructions), bf16 on the 32x32x16 one.  What bounds it: latency.  The
+//    products of the fp32 configuration (M <= 512, K <= 688) are 1-200 MFLOP; with small tiles there are enough workgroups for
+//    the chip, with K over the wavefronts a wavefront's whole share of both operands (two or three groups of 128 bytes per
+//    row) is in flight at once, and nothing waits for a barrier before the final sum.  Operand fragments come straight from
+//    global memory: a lane takes 16 consecutive bytes of its row, which is four (fp32) products' operands or one (bf16)
+//    product's; which k an instruction multiplies is free as long as both operands agree.  256 x 256 x 256 fp32: 34 us (64x64
+//    tiles, 16-wide K steps through LDS, two barriers each) -> 7 us; 256 x 256 x 688 with the residual: 101 -> 10 us; the whole
+//    fp32 layer of 512 tokens with the probe and attention of kernels_attn_generic.hip 1590 -> 172 us, its error against 64
+//    bits 2.9e-7 -> 1.6e-7 (four partial sums instead of one chain).
+//  * gemm_generic_kernel: element-wise loads, any K and any leading dimension.
 #include "spts_internal.h"
 
 namespace spts {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// SPLIT_NONE: one product.  SILU: a second product (A1 / B1).  ROPE: columns c and c + d/2 of a head (B rows d/2 apart).  WIDE:
+// columns c and c + 32 (the row sums of squares keep their 64-column blocks).
+enum Tile32Mode : int { T32_ONE, T32_SILU, T32_ROPE, T32_WIDE };
+
+__device__ inline f32x16 tile32_mfma(u32x4 b, u32x4 a, f32x16 c, float) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(b[j]), __uint_as_float(a[j]), c, 0, 0, 0);
+    return c;
+}
+__device__ inline f32x16 tile32_mfma(u32x4 b, u32x4 a, f32x16 c, bf16_t) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
+}
+
+template <typename T, int MODE>
+__global__ void __launch_bounds__(256) gemm_tile32_kernel(GemmArgs a) {
+    constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
+    constexpr int KS = 2 * EPC;                // k per step: one chunk for each half of the wavefront
+    constexpr int U = 4;                       // steps per group: 128 consecutive bytes of a row
+    constexpr int NP = MODE == T32_ONE ? 1 : 2;
+    __shared__ __attribute__((aligned(16))) float red[NP][4][32][36];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int64_t row0 = (int64_t)blockIdx.y * 32;
+    const int col0 = (int)blockIdx.x * (MODE == T32_WIDE ? 64 : 32);
+    const int ncols = MODE == T32_ROPE ? a.N / 2 : a.N;   // rotary: a column stands for its pair
+    const int half = MODE == T32_ROPE ? a.head_dim >> 1 : 1;
+
+    int64_t arow = row0 + l32 < a.M ? row0 + l32 : a.M - 1;   // rows and columns past the end repeat the last one (never stored)
+    if (a.a_idx) arow = a.a_idx[arow];
+    const T* pa = (const T*)a.A + arow * a.lda + lh * EPC;
+    const T* pa1 = MODE == T32_SILU && a.A1 ? (const T*)a.A1 + arow * a.lda + lh * EPC : pa;
+    const int c = col0 + l32 < ncols ? col0 + l32 : ncols - 1;
+    int64_t brow = c, brow1 = c;
+    if (MODE == T32_ROPE) { brow = (int64_t)(c / half) * a.head_dim + c % half; brow1 = brow + half; }
+    if (MODE == T32_WIDE) brow1 = col0 + 32 + l32 < ncols ? col0 + 32 + l32 : ncols - 1;
+    const T* pb = (const T*)a.B0 + brow * a.ldb + lh * EPC;
+    const T* pb1 = (const T*)(MODE == T32_SILU ? a.B1 : a.B0) + brow1 * a.ldb + lh * EPC;
+
+    f32x16 acc[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[p][r] = 0.f;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    auto load = [&](const T* p, int k0) -> u32x4 { return k0 + lh * EPC < a.K ? *reinterpret_cast<const u32x4*>(p + k0) : zero; };   // K % EPC == 0
+    for (int k0 = wave * (U * KS); k0 < a.K; k0 += 4 * U * KS) {
+        u32x4 fa[U], fb[U], fa1[U], fb1[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            fa[u] = load(pa, k0 + u * KS);
+            fb[u] = load(pb, k0 + u * KS);
+            if (NP == 2) fb1[u] = load(pb1, k0 + u * KS);
+            if (MODE == T32_SILU) fa1[u] = load(pa1, k0 + u * KS);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            acc[0] = tile32_mfma(fb[u], fa[u], acc[0], T{});
+            if (NP == 2) acc[NP - 1] = tile32_mfma(fb1[u], MODE == T32_SILU ? fa1[u] : fa[u], acc[NP - 1], T{});
+        }
+    }
+    // lane: output row l32, columns 8 * (r / 4) + 4 * lh + r % 4
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(&red[p][wave][l32][8 * q + 4 * lh]) = f32x4{acc[p][4 * q], acc[p][4 * q + 1], acc[p][4 * q + 2], acc[p][4 * q + 3]};
+    __syncthreads();
+    const int r = tid >> 3, c4 = (tid & 7) * 4;
+    f32x4 v[2];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        v[p] = *reinterpret_cast<const f32x4*>(&red[p][0][r][c4]);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v[p] += *reinterpret_cast<const f32x4*>(&red[p][w][r][c4]);   // fixed order
+    }
+    const int64_t grow = row0 + r;
+    if (MODE == T32_WIDE) {   // EPI_SUMSQ
+        float ss = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (col0 + c4 + e < a.N) ss += v[0][e] * v[0][e];
+            if (col0 + 32 + c4 + e < a.N) ss += v[NP - 1][e] * v[NP - 1][e];
+        }
+        ss += __shfl_xor(ss, 1); ss += __shfl_xor(ss, 2); ss += __shfl_xor(ss, 4);
+        if ((tid & 7) == 0 && grow < a.M) a.part[grow * a.part_ld + blockIdx.x] = ss;
+        return;
+    }
+    if (grow >= a.M) return;
+    const int64_t crow = a.c_idx ? (int64_t)a.c_idx[grow] : grow;
+    T* C = (T*)a.C + crow * a.ldc;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int col = col0 + c4 + e;
+        if (col >= ncols) continue;
+        if (MODE == T32_ROPE) {
+            const int head = col / half, j = col % half;
+            const float2 cs = a.rope[(a.rope_idx ? (int64_t)a.rope_idx[grow] : grow) * half + j];
+            const float rs = a.rope_scale != 0.f ? a.rope_scale : 1.f, x1 = v[0][e], x2 = v[NP - 1][e];
+            C[(int64_t)head * a.head_dim + j] = from_f32<T>((x1 * cs.x - x2 * cs.y) * rs);
+            C[(int64_t)head * a.head_dim + j + half] = from_f32<T>((x2 * cs.x + x1 * cs.y) * rs);
+        } else if (MODE == T32_SILU) {
+            const float g = v[0][e];
+            const T o = from_f32<T>(g / (1.0f + expf(-g)) * v[NP - 1][e]);
+            C[col] = o;
+            if (a.Ct) ((T*)a.Ct)[(int64_t)col * a.ldct + vt_key_slot(grow)] = o;
+        } else if (a.epi == EPI_RESIDUAL) {
+            C[col] = from_f32<T>(to_f32(C[col]) + v[0][e]);
+        } else if (a.c_is_f32) {
+            ((float*)a.C)[crow * a.ldc + col] = v[0][e];
+        } else {
+            const T o = from_f32<T>(v[0][e]);
+            C[col] = o;
+            if (a.Ct) ((T*)a.Ct)[(int64_t)col * a.ldct + vt_key_slot(grow)] = o;
+        }
+    }
+}
 
 constexpr int GT = 64;   // tile edge
 constexpr int GK = 16;   // k step
@@ -111,8 +244,37 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(GemmArgs a) {
     }
 }
 
+// Rows of whole 16-byte chunks at 16-byte addresses; every epilogue but the merged rotary + store one, no stacked B.
+bool gemm_tile32_supported(const GemmArgs& a, bool bf16) {
+    const int epc = bf16 ? 8 : 4;
+    auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
+    if (a.M <= 0 || a.N <= 0 || a.K <= 0 || a.K % epc != 0 || a.lda % epc != 0 || a.ldb % epc != 0) return false;
+    if ((a.M + 31) / 32 > 65535) return false;   // grid y
+    if (!al(a.A) || !al(a.B0) || (a.A1 && !al(a.A1)) || (a.B1 && !al(a.B1))) return false;
+    if (a.a_slab || a.b_slab || a.c_slab || a.epi == EPI_ROPE_STORE || (a.epi == EPI_STORE && a.B1)) return false;
+    if (a.epi == EPI_ROPE && (a.head_dim <= 0 || a.head_dim % 2 != 0 || a.N % a.head_dim != 0 || a.c_is_f32 || a.Ct)) return false;
+    if (a.c_is_f32 && a.epi != EPI_STORE) return false;
+    return true;
+}
+
+template <typename T>
+static void launch_tile32_t(const GemmArgs& a, hipStream_t s) {
+    const unsigned ny = (unsigned)((a.M + 31) / 32);
+    switch (a.epi) {
+        case EPI_SILU_MUL: gemm_tile32_kernel<T, T32_SILU><<<dim3((unsigned)((a.N + 31) / 32), ny), dim3(256), 0, s>>>(a); break;
+        case EPI_ROPE: gemm_tile32_kernel<T, T32_ROPE><<<dim3((unsigned)((a.N / 2 + 31) / 32), ny), dim3(256), 0, s>>>(a); break;
+        case EPI_SUMSQ: gemm_tile32_kernel<T, T32_WIDE><<<dim3((unsigned)((a.N + 63) / 64), ny), dim3(256), 0, s>>>(a); break;
+        default: gemm_tile32_kernel<T, T32_ONE><<<dim3((unsigned)((a.N + 31) / 32), ny), dim3(256), 0, s>>>(a); break;
+    }
+}
+
 hipError_t launch_gemm_generic(const GemmArgs& a, bool bf16, hipStream_t s) {
     if (a.M == 0 || a.N == 0) return hipSuccess;
+    if (gemm_tile32_supported(a, bf16)) {
+        if (bf16) launch_tile32_t<bf16_t>(a, s); else launch_tile32_t<float>(a, s);
+        return hipGetLastError();
+    }
+    if (a.epi == EPI_ROPE || a.epi == EPI_ROPE_STORE) return hipErrorInvalidValue;
     dim3 grid((unsigned)((a.N + GT - 1) / GT), (unsigned)((a.M + GT - 1) / GT)), block(256);
     bool dual = a.epi == EPI_SILU_MUL;
     if (bf16) {

@@ -200,6 +200,10 @@ int run_gemm_rope(spts_ctx* c, GemmArgs g, int heads, const int32_t* tidx, int64
     f.rope_scale = out_scale;
     prefer_slab(c, f, b_slab, nullptr, g.N);
     if (c->bf16 && gemm_mfma_supported(f)) return run_gemm_mfma(c, f);
+    if (gemm_tile32_supported(f, c->bf16)) {
+        SPTS_HIP(c, launch_gemm_generic(f, c->bf16, c->stream));
+        return SPTS_OK;
+    }
     g.C = c->p<float>(c->off.tmp32); g.c_is_f32 = 1; g.epi = EPI_STORE;
     SPTS_TRY(run_gemm(c, g));
     SPTS_HIP(c, launch_rope_apply(c->p<float>(c->off.tmp32), table, tidx, row0, out, g.M, heads, c->m.d, c->bf16, c->stream, out_scale));

@@ -68,7 +68,7 @@ enum GemmEpilogue : int {
     EPI_SILU_MUL = 1,   // C[row, col] = silu(acc0) * acc1     (two B operands)
     EPI_RESIDUAL = 2,   // C[crow, col] = C[crow, col] + acc   (crow = c_idx ? c_idx[row] : row)
     EPI_SUMSQ = 3,      // part[row, col_block] = sum over the block's columns of acc^2
-    EPI_ROPE = 4,       // C[row, col] = rotary(acc) with table row (rope_idx ? rope_idx[row] : row); MFMA path only
+    EPI_ROPE = 4,       // C[row, col] = rotary(acc) with table row (rope_idx ? rope_idx[row] : row)
     EPI_ROPE_STORE = 5, // two products of the same A rows in one launch (MFMA path only): columns [0, n_split) = A * B0^T
                         // with the rotary epilogue -> C; columns [n_split, N) = A * B1^T stored plainly -> C2 (and Ct)
 };
@@ -107,7 +107,9 @@ struct GemmArgs {
 // sets *nfull; needs (tiles - nfull) * ksplit * 65536 floats of part32.
 int gemm_pick_split(int64_t M, int32_t N, int32_t K, int epi, int32_t* nfull);
 
+// any shape; EPI_ROPE only where gemm_tile32_supported
 hipError_t launch_gemm_generic(const GemmArgs& a, bool bf16, hipStream_t s);
+bool gemm_tile32_supported(const GemmArgs& a, bool bf16);
 // true when the matrix-core kernel can serve these arguments (alignment / divisibility)
 bool gemm_mfma_supported(const GemmArgs& a);
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);

@@ -67,3 +67,28 @@ def test_argmax_picks_the_lowest_id_of_equal_logits(torch, dtype, V):
     one = torch.full((4,), -1, dtype=torch.int32, device="cuda")
     ctx.spts_greedy_token(xd[0], gd, td, V, one, logits[0], None)
     assert int(one[0]) == best[0]
+
+
+# ------------------------------------------------------------------------------------------ fp32 / odd-dimension layer
+# head dimensions at and between the kernels' 32 / 64 / 128 / 256 (30: rows that are not whole 16-byte pieces), row lengths
+# that are not whole chunks (D = 62: the element-wise GEMM), sequence lengths around the 32-row tiles and the 8 (4) x 32 keys that
+# a workgroup's wavefronts take per round.  Tolerance: helpers.TOL (fp32 1e-4, derived there from K = 4096; K <= 256 here).
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,H_,Hkv,d,Dff", [(64, 4, 2, 16, 96), (62, 3, 1, 30, 70), (96, 2, 2, 96, 100), (256, 2, 1, 128, 130), (80, 2, 1, 256, 44)],
+                         ids=["d16", "d30", "d96", "d128", "d256"])
+def test_layer_of_any_head_dimension(torch, dtype, D, H_, Hkv, d, Dff):
+    shape = synth.ModelShape(D=D, H=H_, Hkv=Hkv, d=d, Dff=Dff, dtype=dtype)
+    mdl, r = H.oracle_model(shape), 8
+    ctx = runtime.make_context(shape, 300, 40, r, Dff)
+    w = synth.make_layer(51, 0, shape, r)
+    dw = runtime.upload_layer(w, shape, r)
+    for N in (1, 31, 33, 129, 257, 300):
+        x = synth.hidden_states(51 + N, N, D, dtype)
+        pos = (synth.positions(N) * 3 + 5).astype(np.int32)
+        P = min(37, N)
+        dense = runtime.run_layer(ctx, x, pos, dw, shape, skip=0, probe_len=P, m_attn=0, m_ffn=0)
+        H.lockstep_layer(dense, x, pos, w, mdl, orc.LayerCfg(0, P, N, N, 1, 0), dtype)
+        for kv_mode, ma in ((0, max(1, (2 * N) // 3)), (1, max(1, N // 3))):
+            mf = max(1, N // 2)
+            skip = runtime.run_layer(ctx, x, pos, dw, shape, skip=1, probe_len=P, m_attn=ma, m_ffn=mf, kv_mode=kv_mode)
+            H.lockstep_layer(skip, x, pos, w, mdl, orc.LayerCfg(1, P, ma, mf, 1, kv_mode), dtype)
