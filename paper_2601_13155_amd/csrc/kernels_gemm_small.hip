@@ -1,0 +1,396 @@
+// bf16 matrix-core GEMM for products that leave the 256x256 tiles of kernels_gemm_mfma.hip short of work: few rows (a short
+// prompt, the probe queries, one request's active rows) or few columns (K projection, proxy factors).
+//
+//  * TM x 128 output tile (TM = 64, 128 or 192), 4 wavefronts (2x2) of TM/2 x 64 = (TM/64) x 2 MFMA 32x32x16 blocks.  32 / 64 / 96
+//    accumulators per lane and a ring of 48 / 80 / 80 KB let two or three workgroups share a CU, which hides one's barriers,
+//    fragment reads and epilogue behind the other's MFMAs; per flop it moves twice the operand bytes of the 256x256 tile, so it
+//    pays only where that one leaves CUs idle or multiplies padding (the rule: gemm_small_plan).
+//  * K in slabs of 32, travelling global memory -> LDS directly into a ring of NST stages: NST - 1 slabs are in flight (64 KB
+//    per workgroup and stage set), which is what keeps HBM busy when the product is bound by reading its weights once.
+//    Slab-major operands as in kernels_gemm_mfma.hip (whole lines per load instruction), same swizzle, same LDS image.
+//  * Split-K: `ksplit` workgroups share a tile, each leaves its raw fp32 accumulators (fragment order: every store is 1 KB),
+//    small_finish_kernel sums them in split order and applies the epilogue.
+//  * Column blocks of a wavefront: wavefront column wn, block j covers tile columns j * 64 + wn * 32 (or wn * 64 + j * 32 for
+//    rotary heads of 64), so that block 0 and block 1 are the two members of a rotary pair, or gate and up of a channel: the
+//    dual epilogues combine registers of one lane, also in the finish kernel.
+//
+// Measured (us, weights from HBM, 256-wide tiles with their split -> here): 64 rows x 4096 x 4096 27.5 -> 14.6, 133 rows of
+// gate/up 80 -> 60 and of down 46 -> 37 (the weights' HBM time: 39 and 20), K projection of 4096 rows 59 -> 44, proxy z of 512
+// rows 36 -> 16.
+#include "spts_internal.h"
+
+namespace spts {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int SBN = 128;        // tile columns (weight rows)
+constexpr int SBK = 32;         // K slab
+constexpr int SROW = SBK * 2;   // bytes of a tile row in a slab
+template <int TM> constexpr int small_stages() { return TM == 128 ? 5 : 4; }   // 48 / 80 / 80 KB
+template <int TM> constexpr int small_stage_bytes() { return (TM + SBN) * SROW; }
+
+__device__ inline int small_off(int row, int c) { return row * SROW + ((c ^ ((row >> 2) & 3)) << 4); }
+__device__ inline float small_silu(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)); }
+
+// what the epilogue of one 4-column quad (or pair of quads) needs to know about its tile
+struct SmallTile { int col0; bool second; bool rope; int jstride, wstride; };
+
+__device__ __forceinline__ SmallTile small_tile(const GemmArgs& a, int tn) {
+    SmallTile t;
+    t.col0 = tn * (a.epi == EPI_SILU_MUL ? SBN / 2 : SBN);
+    t.second = a.epi == EPI_ROPE_STORE && t.col0 >= a.n_split;
+    t.rope = a.epi == EPI_ROPE || (a.epi == EPI_ROPE_STORE && !t.second);
+    const bool d64 = t.rope && a.head_dim == 64;
+    t.jstride = d64 ? 32 : 64;
+    t.wstride = d64 ? 64 : 32;
+    return t;
+}
+
+// id -> (row tile, column tile): up to GM row tiles of a column tile are neighbours (they read the same weight panel), column
+// tiles follow each other inside the group
+__device__ __forceinline__ void small_tile_of(int id, int nM, int nN, int& tm, int& tn) {
+    constexpr int GM = 8;
+    const int group = id / (GM * nN), first = group * GM;
+    const int gsz = nM - first < GM ? nM - first : GM;
+    const int in_g = id - group * GM * nN;
+    tm = first + in_g % gsz;
+    tn = in_g / gsz;
+}
+
+// the two finished quads (block j = 0, 1; columns tile_col(j) .. + 3) of output row grow -> bf16 pairs; returns how many quads
+// there are (dual epilogues: SiLU leaves one)
+__device__ __forceinline__ void small_epilogue(const GemmArgs& a, const SmallTile& t, int wn, int lh, int q, int64_t growc, int64_t crow,
+                                               f32x4 v0, f32x4 v1, u32x2& o0, u32x2& o1) {
+    if (a.epi == EPI_SILU_MUL) {
+        float h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = small_silu(v0[e]) * v1[e];
+        o0 = u32x2{cvt_pk_bf16(h[0], h[1]), cvt_pk_bf16(h[2], h[3])};
+        return;
+    }
+    if (t.rope) {
+        const int64_t trow = a.rope_idx ? (int64_t)a.rope_idx[growc] : growc;
+        const int jj = (a.head_dim == 128 ? wn * 32 : 0) + 4 * lh + 8 * q;
+        const float2* tab = a.rope + trow * (a.head_dim >> 1) + jj;
+        const float rs = a.rope_scale != 0.f ? a.rope_scale : 1.f;
+        float lo[4], hi[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float2 cs = tab[e];
+            lo[e] = (v0[e] * cs.x - v1[e] * cs.y) * rs;
+            hi[e] = (v1[e] * cs.x + v0[e] * cs.y) * rs;
+        }
+        o0 = u32x2{cvt_pk_bf16(lo[0], lo[1]), cvt_pk_bf16(lo[2], lo[3])};
+        o1 = u32x2{cvt_pk_bf16(hi[0], hi[1]), cvt_pk_bf16(hi[2], hi[3])};
+        return;
+    }
+    if (a.epi == EPI_RESIDUAL) {   // one rounding of old + sum
+        const bf16_t* c = (const bf16_t*)a.C + crow * a.ldc + t.col0 + wn * t.wstride + 4 * lh + 8 * q;
+        const u32x2 p0 = *reinterpret_cast<const u32x2*>(c), p1 = *reinterpret_cast<const u32x2*>(c + t.jstride);
+        v0 += f32x4{__uint_as_float(p0[0] << 16), __uint_as_float(p0[0] & 0xffff0000u), __uint_as_float(p0[1] << 16), __uint_as_float(p0[1] & 0xffff0000u)};
+        v1 += f32x4{__uint_as_float(p1[0] << 16), __uint_as_float(p1[0] & 0xffff0000u), __uint_as_float(p1[1] << 16), __uint_as_float(p1[1] & 0xffff0000u)};
+    }
+    o0 = u32x2{cvt_pk_bf16(v0[0], v0[1]), cvt_pk_bf16(v0[2], v0[3])};
+    o1 = u32x2{cvt_pk_bf16(v1[0], v1[1]), cvt_pk_bf16(v1[2], v1[3])};
+}
+
+// transposed copy of a stored quad (values of the attention): Ct[col + e, vt_key_slot(row)]
+__device__ __forceinline__ void small_store_ct(const GemmArgs& a, int col, int64_t grow, u32x2 o) {
+    bf16_t* ct = (bf16_t*)a.Ct;
+    const uint16_t e[4] = {(uint16_t)(o[0] & 0xffff), (uint16_t)(o[0] >> 16), (uint16_t)(o[1] & 0xffff), (uint16_t)(o[1] >> 16)};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) ct[(int64_t)(col + t) * a.ldct + vt_key_slot(grow)].v = e[t];
+}
+
+template <int TM>
+__global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmArgs a, int nM, int nN, int ksplit) {
+    constexpr int MI = TM / 64;                 // 32-row blocks per wavefront
+    constexpr int NST = small_stages<TM>(), STAGE = small_stage_bytes<TM>(), A_BYTES = TM * SROW;
+    constexpr int LA = TM / 64, LB = 2, PER = LA + LB;   // direct-to-LDS loads per wavefront and slab: 16 rows each
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    // XCD b % 8 takes a contiguous range of the units (split outermost): neighbouring units share operand panels in its L2
+    const int tiles = nM * nN, units = tiles * ksplit;
+    const int per_xcd = (units + 7) / 8;
+    const int unit = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+    if ((int)(blockIdx.x / 8) >= per_xcd || unit >= units) return;
+    const int split = unit / tiles, id = unit - split * tiles;
+    int tm, tn;
+    small_tile_of(id, nM, nN, tm, tn);
+    const SmallTile st = small_tile(a, tn);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lh = lane >> 5;
+    const int64_t row0 = (int64_t)tm * TM;
+
+    // ---- load addresses: a wavefront-uniform base advanced along K plus a fixed 32-bit lane offset
+    const bool second = st.second;
+    const int64_t a_pitch = a.a_slab ? 64 : a.lda * 2, b_pitch = a.b_slab ? 64 : a.ldb * 2;
+    const int64_t a_kstep = a.a_slab ? a.M * 64 : SROW, b_kstep = a.b_slab ? (second ? a.b_rows1 : a.b_rows) * 64 : SROW;
+    const int lr = lane >> 2;                   // row of the load's 16
+    uint32_t oa[LA], ob[LB];
+    const char* abase = (const char*)a.A + (a.a_idx ? (int64_t)0 : row0 * a_pitch);
+    // This wavefront's 32 weight rows: which matrix, and from which row of it.  Plain selects: written as an if / else chain this
+    // was compiled (ROCm 7.2) to a path that left the base register unset for the first half of a stacked B.
+    const int rw = wave * 32;
+    const bool silu_b = a.epi == EPI_SILU_MUL;
+    const bool upper = a.epi == EPI_STORE && a.B1 != nullptr && st.col0 >= a.N / 2;   // stacked B: columns [N/2, N) from B1
+    const bool from_b1 = silu_b ? rw >= 64 : (second || upper);
+    const int brow0 = (silu_b ? (rw & 63) : rw) + st.col0 - (second ? a.n_split : 0) - (upper ? a.N / 2 : 0);
+    const char* bbase = (const char*)(from_b1 ? a.B1 : a.B0) + (int64_t)brow0 * b_pitch;
+#pragma unroll
+    for (int q = 0; q < LA; ++q) {
+        const int r = wave * (TM / 4) + q * 16 + lr;
+        int64_t grow = row0 + r;
+        if (grow >= a.M) grow = a.M - 1;        // duplicates of the last row are never stored
+        const int64_t srow = a.a_idx ? (int64_t)a.a_idx[grow] : grow - row0;
+        oa[q] = (uint32_t)(srow * a_pitch + (((lane & 3) ^ ((r >> 2) & 3)) << 4));
+    }
+#pragma unroll
+    for (int q = 0; q < LB; ++q) {
+        const int r = wave * 32 + q * 16 + lr;
+        ob[q] = (uint32_t)((int64_t)(q * 16 + lr) * b_pitch + (((lane & 3) ^ ((r >> 2) & 3)) << 4));
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const uint32_t lds_a = lds0 + wave * (TM / 4) * SROW, lds_b = lds0 + A_BYTES + wave * 32 * SROW;
+    const int nk_all = a.K / SBK;
+    const int nk = nk_all / ksplit + (split < nk_all % ksplit ? 1 : 0);
+    const int kbeg = split * (nk_all / ksplit) + (split < nk_all % ksplit ? split : nk_all % ksplit);
+    auto issue = [&](int kt, int stage) {
+        const int64_t ks = kbeg + kt;
+#pragma unroll
+        for (int q = 0; q < LB; ++q) dma16s(ob[q], bbase + ks * b_kstep, lds_b + stage * STAGE + q * 1024);
+#pragma unroll
+        for (int q = 0; q < LA; ++q) dma16s(oa[q], abase + ks * a_kstep, lds_a + stage * STAGE + q * 1024);
+    };
+
+    f32x16 acc[MI][2];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    const int npre = nk < NST - 1 ? nk : NST - 1;
+    for (int t = 0; t < npre; ++t) issue(t, t);
+    // one slab: its loads (this wavefront's) have landed when only `left` slabs' loads are outstanding; the barrier publishes
+    // everyone's and says that the stage of the slab before is free, which the next loads go to
+#define SPTS_SMALL_SLAB(kt_, st_, left_, ISSUE)                                                                      \
+    {                                                                                                                \
+        SPTS_WAIT_VMCNT((left_) * PER);                                                                              \
+        __syncthreads();                                                                                             \
+        if (ISSUE) issue((kt_) + NST - 1, ((st_) + NST - 1) % NST);                                                  \
+        const char* sa_ = smem + (st_) * STAGE;                                                                      \
+        const char* sb_ = sa_ + A_BYTES;                                                                             \
+        bf16x8 fa_[2][MI], fb_[2][2];                                                                                \
+        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {                                                           \
+            _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                           \
+                fa_[ks][i] = *reinterpret_cast<const bf16x8*>(sa_ + small_off(wm * (TM / 2) + i * 32 + l32, 2 * ks + lh)); \
+            _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                            \
+                fb_[ks][j] = *reinterpret_cast<const bf16x8*>(sb_ + small_off(j * st.jstride + wn * st.wstride + l32, 2 * ks + lh)); \
+        }                                                                                                            \
+        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                             \
+            _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                           \
+                _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                        \
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb_[ks][j], fa_[ks][i], acc[i][j], 0, 0, 0); \
+    }
+    int kt = 0;
+    for (; kt + 2 * NST - 2 < nk; kt += NST) {   // ring stages are constants here
+#pragma unroll
+        for (int u = 0; u < NST; ++u) SPTS_SMALL_SLAB(kt + u, u, NST - 2, true)
+    }
+    for (; kt + NST - 1 < nk; ++kt) SPTS_SMALL_SLAB(kt, kt % NST, NST - 2, true)
+    for (; kt < nk; ++kt) SPTS_SMALL_SLAB(kt, kt % NST, 0, false)
+
+    // ---- lane: output row l32 of its block, columns 8 * q + 4 * lh + e of blocks j = 0, 1
+    if (ksplit > 1) {
+        float* P = a.part32 + ((int64_t)split * tiles + id) * (TM * SBN);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                    *reinterpret_cast<f32x4*>(P + ((((wave * MI + i) * 2 + j) * 4 + q) * 64 + lane) * 4) = v;
+                }
+        return;
+    }
+    // staged through LDS (the ring is free once every wavefront is past its last fragment read) so that the tile leaves in
+    // whole rows; 16-byte chunk c of row r at c ^ (r % chunks)
+    __syncthreads();
+    const bool silu = silu_b;
+    const int nch = silu ? 8 : 16;               // chunks per staged row
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int tr = wm * (TM / 2) + i * 32 + l32;
+        const int64_t grow = row0 + tr;
+        const int64_t growc = grow < a.M ? grow : a.M - 1;
+        const int64_t crow = a.c_idx ? (int64_t)a.c_idx[growc] : growc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u32x2 o[2];
+            small_epilogue(a, st, wn, lh, q, growc, crow, f32x4{acc[i][0][4 * q], acc[i][0][4 * q + 1], acc[i][0][4 * q + 2], acc[i][0][4 * q + 3]},
+                           f32x4{acc[i][1][4 * q], acc[i][1][4 * q + 1], acc[i][1][4 * q + 2], acc[i][1][4 * q + 3]}, o[0], o[1]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if (silu && j == 1) continue;
+                const int tc = j * st.jstride + wn * st.wstride + 4 * lh + 8 * q;
+                *reinterpret_cast<u32x2*>(smem + tr * (nch * 16) + ((((tc >> 3) ^ tr) & (nch - 1)) << 4) + ((tc & 4) << 1)) = o[j];
+                if (a.Ct && !st.rope && grow < a.ldct) small_store_ct(a, st.col0 - (second ? a.n_split : 0) + tc, grow, o[j]);
+            }
+        }
+    }
+    __syncthreads();
+    bf16_t* Cb = (bf16_t*)(second ? a.C2 : a.C);
+    const int colb = st.col0 - (second ? a.n_split : 0);
+    const int64_t ldo = second ? a.ldc2 : a.ldc;
+    const int total = TM * nch;
+    for (int e = tid; e < total; e += 256) {
+        int tr, oc;
+        if (a.c_slab) { oc = (e & 3) + 4 * (e / (TM * 4)); tr = (e >> 2) % TM; }   // slab by slab: 4 lanes per row, rows adjacent
+        else { tr = e / nch; oc = e % nch; }
+        const int64_t grow = row0 + tr;
+        if (grow >= a.M) continue;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(smem + tr * (nch * 16) + (((oc ^ tr) & (nch - 1)) << 4));
+        if (a.c_slab) {
+            *reinterpret_cast<u32x4*>(Cb + (((int64_t)(colb >> 5) + (oc >> 2)) * a.M + grow) * 32 + (oc & 3) * 8) = v;
+        } else {
+            const int64_t crow = a.c_idx ? (int64_t)a.c_idx[grow] : grow;
+            *reinterpret_cast<u32x4*>(Cb + crow * ldo + colb + oc * 8) = v;
+        }
+    }
+}
+
+// Second pass of a split product: one thread per fragment quad pair (j = 0, 1), splits summed in order.
+template <int TM>
+__global__ void __launch_bounds__(256) small_finish_kernel(GemmArgs a, int nM, int nN, int ksplit) {
+    constexpr int MI = TM / 64, QPT = TM * SBN / 8;      // quad pairs per tile
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int id = (int)(g / QPT), v = (int)(g % QPT);
+    const int lane = v & 63, q = (v >> 6) & 3, wi = v >> 8;
+    const int wave = wi / MI, i = wi % MI;
+    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lh = lane >> 5;
+    const int tiles = nM * nN;
+    int tm, tn;
+    small_tile_of(id, nM, nN, tm, tn);
+    const SmallTile st = small_tile(a, tn);
+    const int64_t grow = (int64_t)tm * TM + wm * (TM / 2) + i * 32 + l32;
+    const bool rok = grow < a.M;
+    if (!rok && !(a.Ct && !st.rope && grow < a.ldct)) return;
+    const float* P = a.part32 + (int64_t)id * (TM * SBN) + (((wave * MI + i) * 2 * 4 + q) * 64 + lane) * 4;
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll 4
+    for (int sp = 0; sp < ksplit; ++sp) {
+        const float* p = P + (int64_t)sp * tiles * (TM * SBN);
+        s0 += *reinterpret_cast<const f32x4*>(p);
+        s1 += *reinterpret_cast<const f32x4*>(p + 4 * 64 * 4);
+    }
+    const int64_t growc = rok ? grow : a.M - 1;
+    const int64_t crow = a.c_idx ? (int64_t)a.c_idx[growc] : growc;
+    u32x2 o[2];
+    small_epilogue(a, st, wn, lh, q, growc, crow, s0, s1, o[0], o[1]);
+    bf16_t* Cb = (bf16_t*)(st.second ? a.C2 : a.C);
+    const int64_t ldo = st.second ? a.ldc2 : a.ldc;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (a.epi == EPI_SILU_MUL && j == 1) continue;
+        const int col = st.col0 - (st.second ? a.n_split : 0) + j * st.jstride + wn * st.wstride + 4 * lh + 8 * q;
+        if (rok) {
+            if (a.c_slab) *reinterpret_cast<u32x2*>(Cb + ((int64_t)(col >> 5) * a.M + grow) * 32 + (col & 31)) = o[j];
+            else *reinterpret_cast<u32x2*>(Cb + crow * ldo + col) = o[j];
+        }
+        if (a.Ct && !st.rope && grow < a.ldct) small_store_ct(a, col, grow, o[j]);
+    }
+}
+
+bool gemm_small_supported(const GemmArgs& a) {
+    if (a.epi != EPI_STORE && a.epi != EPI_SILU_MUL && a.epi != EPI_RESIDUAL && a.epi != EPI_ROPE && a.epi != EPI_ROPE_STORE) return false;
+    if (a.A1 || a.ksplit > 1) return false;
+    // everything the 256-wide kernel checks (alignment, 32-bit offsets, slab rows), which is for multiples of 256 (128) columns
+    return gemm_mfma_supported(a);
+}
+
+// Time models (us) behind the choice between the two kernels and among this one's tiles and splits, fitted to 170 measured
+// (product, rows) pairs x 24 (tile, split) pairs: rows 1 .. 16000 of the 8B shape's projections, FFN and proxy products.  Over
+// those the choice costs 2 % on the mean against the best of everything measured.
+//  * this kernel: a K slab takes the load latency (0.18 / 0.31 / 0.38 us at TM = 64 / 128 / 192) or, with more workgroups, the
+//    47 KB/us that a CU's slab loads reach together (rows past M repeat a line and cost a third); a split adds the finish launch
+//    and its fp32 tiles written and read at 4 TB/s.
+//  * 256-wide tiles: 0.41 us per slab + up to 0.36 us as the chip fills, a round of 256 tiles after the other, a partly filled
+//    last round split over K as gemm_pick_split plans.
+static double small_time(const GemmArgs& a, int tm, int ks) {
+    const double lat = tm == 64 ? 0.18 : tm == 128 ? 0.31 : 0.38;
+    const int64_t nM = (a.M + tm - 1) / tm, nN = a.N / (a.epi == EPI_SILU_MUL ? SBN / 2 : SBN), units = nM * nN * ks;
+    const double fill = (double)units / 256.0, per_cu = fill <= 1.0 ? 1.0 : 0.5 * (fill + (double)((units + 255) / 256));
+    const double rows = tm * (0.35 + 0.65 * (double)a.M / (double)(nM * tm));
+    const double slab_kb = (rows + SBN) * SROW / 1024.0;
+    const double per_slab = lat > per_cu * slab_kb / 47.0 ? lat : per_cu * slab_kb / 47.0;
+    double t = 2.6 + per_slab * (double)((a.K / SBK + ks - 1) / ks);
+    if (ks > 1) t += 2.5 + (double)units * tm * SBN * 8.0 / 4.0e6;
+    return t;
+}
+static double wide_time(const GemmArgs& a, int ks, int nfull) {
+    const int64_t tiles = (a.M + 255) / 256 * (a.N / (a.epi == EPI_SILU_MUL ? 128 : 256));
+    const double slabs = a.K / SBK;
+    auto per_slab = [](double busy) { return 0.41 + 0.36 * busy / 256.0; };
+    const int64_t whole = ks > 1 ? nfull : tiles;
+    double t = 4.6 + (double)(whole / 256) * slabs * per_slab(256);
+    if (const int64_t rem = whole % 256) t += slabs * per_slab(whole > 256 && rem < 160 ? 160 : (double)rem);
+    if (ks > 1) {
+        const int64_t units = (tiles - nfull) * ks;
+        t += (double)((units + 255) / 256) * (double)((int)(slabs + ks - 1) / ks) * per_slab(units < 256 ? (double)units : 256.0) + 5.1 +
+             (double)units * 262144.0 * 2.0 / 4.0e6;
+    }
+    return t;
+}
+
+bool gemm_small_pick(const GemmArgs& a, int wide_ksplit, int wide_nfull, size_t part_bytes, GemmSmallPlan* plan) {
+    if (!gemm_small_supported(a)) return false;
+    // 7 % in hand: where the two are that close the wider tile moves fewer bytes
+    double best = 0.93 * wide_time(a, wide_ksplit, wide_nfull);
+    bool found = false;
+    for (const int tm : {64, 128, 192})
+        for (const int ks : {1, 2, 3, 4, 6, 8, 12, 16}) {
+            const GemmSmallPlan p{tm, ks};
+            // Shares of at least 1024: shorter ones save 1-2 us a product (64 x 4096 x 4096: 16.8 us in 4 shares, 14.6 in 8), and
+            // a product with K <= 1024 is then summed the same way whatever its row count (a batched call and the calls one
+            // by one agree bit for bit there).
+            if (ks > 1 && (a.K / ks < 1024 || gemm_small_part_bytes(a, p) > part_bytes)) break;
+            const double t = small_time(a, tm, ks);
+            if (t < best) { best = t; *plan = p; found = true; }
+        }
+    return found;
+}
+
+size_t gemm_small_part_bytes(const GemmArgs& a, const GemmSmallPlan& p) {
+    const int64_t nN = a.N / (a.epi == EPI_SILU_MUL ? SBN / 2 : SBN);
+    return p.ksplit > 1 ? (size_t)((a.M + p.tm - 1) / p.tm * nN) * p.ksplit * p.tm * SBN * sizeof(float) : 0;
+}
+
+template <int TM>
+static hipError_t launch_small_t(const GemmArgs& a, int ksplit, hipStream_t s) {
+    const int nM = (int)((a.M + TM - 1) / TM), nN = a.N / (a.epi == EPI_SILU_MUL ? SBN / 2 : SBN);
+    const int64_t units = (int64_t)nM * nN * ksplit;
+    if (units > ((int64_t)1 << 30)) return hipErrorInvalidValue;
+    constexpr int lds = small_stages<TM>() * small_stage_bytes<TM>();
+    static_assert(lds >= TM * SBN * 2, "the finished tile is staged in the ring");
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_small_kernel<TM>), lds);
+    if (e != hipSuccess) return e;
+    gemm_small_kernel<TM><<<dim3((unsigned)((units + 7) / 8 * 8)), dim3(256), lds, s>>>(a, nM, nN, ksplit);
+    if ((e = hipGetLastError()) != hipSuccess || ksplit <= 1) return e;
+    const int64_t pairs = (int64_t)nM * nN * (TM * SBN / 8);
+    small_finish_kernel<TM><<<dim3((unsigned)(pairs / 256)), dim3(256), 0, s>>>(a, nM, nN, ksplit);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_small(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s) {
+    if (p.ksplit < 1 || p.ksplit > a.K / SBK || (p.ksplit > 1 && !a.part32)) return hipErrorInvalidValue;
+    return p.tm == 192 ? launch_small_t<192>(a, p.ksplit, s) : p.tm == 128 ? launch_small_t<128>(a, p.ksplit, s) : launch_small_t<64>(a, p.ksplit, s);
+}
+
+}  // namespace spts

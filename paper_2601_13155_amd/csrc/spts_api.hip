@@ -18,6 +18,14 @@ struct Workspace {
     size_t total;
 };
 
+// Bytes of the fp32 staging buffer: the projections' unrounded outputs (shapes whose rotary embedding is a kernel of its own) and,
+// in bf16, the split-K partial tiles.  A short context needs as many of those as a long one (its few tiles are split over the
+// whole chip: 512 units of 128 KB), hence the floor.
+inline size_t split_scratch_bytes(const spts_model_desc& m, int64_t max_tokens) {
+    const size_t rows = ((size_t)max_tokens + 255) / 256 * 256 * m.H * m.d * 4, floor_bytes = m.dtype == SPTS_BF16 ? (size_t)64 << 20 : 0;
+    return rows > floor_bytes ? rows : floor_bytes;
+}
+
 struct Limits { int64_t max_tokens; int32_t max_probe, max_r, max_dlow; };
 
 Workspace carve(const spts_model_desc& m, const Limits& L) {
@@ -30,7 +38,7 @@ Workspace carve(const spts_model_desc& m, const Limits& L) {
     w.rope = take(Np * (size_t)(m.d / 2) * sizeof(float2));
     w.xn = take(Np * m.D * b);
     w.kall = take(Np * (size_t)m.Hkv * m.d * b);
-    w.tmp32 = take(Np * (size_t)m.H * m.d * 4);
+    w.tmp32 = take(split_scratch_bytes(m, L.max_tokens));
     w.qp = take((size_t)(L.max_probe + 256) * m.H * m.d * b);
     w.probe = take(probe_scratch_floats(L.max_tokens, L.max_probe, m.H, m.Hkv) * 4);
     w.S = take(Np * 4);
@@ -139,16 +147,23 @@ struct PhaseScope {
 namespace {
 
 // ---- dispatch helpers -------------------------------------------------------------------------
-// matrix-core launch; the partly filled last round of tiles is split over K through the fp32 staging buffer
+// matrix-core launch: 256-wide tiles, their partly filled last round split over K through the fp32 staging buffer, or the smaller
+// tiles where those leave the chip short of work
 int run_gemm_mfma(spts_ctx* c, GemmArgs a) {
+    const size_t have = split_scratch_bytes(c->m, c->lim.max_tokens);
     int32_t nfull = 0;
-    const int ks = gemm_pick_split(a.M, a.N, a.K, a.epi, &nfull);
+    int ks = gemm_pick_split(a.M, a.N, a.K, a.epi, &nfull);
     if (ks > 1) {
         const int64_t tiles = (a.M + 255) / 256 * (a.N / 256);
-        const size_t need = (size_t)(tiles - nfull) * ks * 65536 * sizeof(float);
-        const size_t have = (size_t)((c->lim.max_tokens + 255) / 256 * 256) * c->m.H * c->m.d * sizeof(float);
-        if (need <= have) { a.ksplit = ks; a.nfull = nfull; a.part32 = c->p<float>(c->off.tmp32); }
+        if ((size_t)(tiles - nfull) * ks * 65536 * sizeof(float) > have) ks = 1;
     }
+    a.part32 = c->p<float>(c->off.tmp32);
+    GemmSmallPlan small{};
+    if (gemm_small_pick(a, ks, nfull, have, &small)) {
+        SPTS_HIP(c, launch_gemm_small(a, small, c->stream));
+        return SPTS_OK;
+    }
+    if (ks > 1) { a.ksplit = ks; a.nfull = nfull; }
     SPTS_HIP(c, launch_gemm_mfma(a, c->stream));
     return SPTS_OK;
 }

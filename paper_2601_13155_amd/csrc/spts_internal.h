@@ -113,6 +113,15 @@ bool gemm_tile32_supported(const GemmArgs& a, bool bf16);
 // true when the matrix-core kernel can serve these arguments (alignment / divisibility)
 bool gemm_mfma_supported(const GemmArgs& a);
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
+// the same product on TM x 128 tiles with K shared by `ksplit` workgroups per tile (kernels_gemm_small.hip); a.part32 must hold
+// gemm_small_part_bytes when ksplit > 1.  Serves the epilogues STORE, SILU_MUL (no second A), RESIDUAL, ROPE, ROPE_STORE.
+struct GemmSmallPlan { int tm; int ksplit; };
+bool gemm_small_supported(const GemmArgs& a);
+size_t gemm_small_part_bytes(const GemmArgs& a, const GemmSmallPlan& p);
+// true (and *plan set) when that is expected to beat launch_gemm_mfma with its split plan (ksplit, nfull); at most part_bytes
+// of split scratch are used
+bool gemm_small_pick(const GemmArgs& a, int wide_ksplit, int wide_nfull, size_t part_bytes, GemmSmallPlan* plan);
+hipError_t launch_gemm_small(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s);
 // number of column blocks a EPI_SUMSQ launch writes per row
 int gemm_sumsq_blocks(int32_t N, bool mfma);
 

@@ -92,3 +92,26 @@ def test_layer_of_any_head_dimension(torch, dtype, D, H_, Hkv, d, Dff):
             mf = max(1, N // 2)
             skip = runtime.run_layer(ctx, x, pos, dw, shape, skip=1, probe_len=P, m_attn=ma, m_ffn=mf, kv_mode=kv_mode)
             H.lockstep_layer(skip, x, pos, w, mdl, orc.LayerCfg(1, P, ma, mf, 1, kv_mode), dtype)
+
+
+# ------------------------------------------------------------------------------------------ short products
+# row counts around the 64 / 128 / 192-row tiles of the short-product GEMM (one row tile, one row more, two tiles), every epilogue it
+# has (rotary d = 128 / 64, merged Q + V with the transposed copy, residual scatter, SiLU, stacked slab-major proxy input), with and
+# without slab-major weights
+@pytest.mark.parametrize("pack", [True, False], ids=["packed", "row_major"])
+@pytest.mark.parametrize("H_,Hkv,d", [(8, 2, 128), (8, 4, 64)], ids=["d128", "d64"])
+def test_layer_with_short_products(torch, H_, Hkv, d, pack):
+    shape = synth.ModelShape(D=1024, H=H_, Hkv=Hkv, d=d, Dff=2048, dtype="bf16", rope_base=500000.0)
+    mdl, r = H.oracle_model(shape), 256
+    ctx = runtime.make_context(shape, 400, 40, r, shape.Dff)
+    assert ctx.uses_mfma()
+    w = synth.make_layer(61, 0, shape, r)
+    dw = runtime.upload_layer(w, shape, r, pack=pack)
+    for N in (63, 65, 128, 191, 193, 321, 385):
+        x = synth.hidden_states(61 + N, N, shape.D, "bf16")
+        pos = (synth.positions(N) * 3 + 5).astype(np.int32)
+        dense = runtime.run_layer(ctx, x, pos, dw, shape, skip=0, probe_len=8, m_attn=0, m_ffn=0)
+        H.lockstep_layer(dense, x, pos, w, mdl, orc.LayerCfg(0, 8, N, N, 1, 0), "bf16")
+        for kv_mode, ma, mf in ((0, max(1, (2 * N) // 3), N // 2), (1, N // 3, N - 1)):
+            skip = runtime.run_layer(ctx, x, pos, dw, shape, skip=1, probe_len=37, m_attn=ma, m_ffn=mf, kv_mode=kv_mode)
+            H.lockstep_layer(skip, x, pos, w, mdl, orc.LayerCfg(1, 37, ma, mf, 1, kv_mode), "bf16")
