@@ -74,8 +74,9 @@ __device__ inline uint32_t pk2(float a, float b) { return cvt_pk_bf16(a, b); }
 
 // HPW heads of one kv-head group per workgroup (NW / HPW wavefronts x 32 queries each): they multiply the same K / V^T
 // tiles, so a tile that is loaded once serves HPW heads.
-template <int D, int HPW, int NW>
-__global__ void __launch_bounds__(NW * 64) attn_mfma_kernel(AttnArgs a, int nQ, int total, int xpg, float qmul) {
+// SEG: the query tiles of every sequence of a batch (seg.qtile counts them), each over its own rows of q, k, v and out.
+template <int D, int HPW, int NW, bool SEG>
+__global__ void __launch_bounds__(NW * 64) attn_mfma_kernel(AttnArgs a, int nQ, int total, int xpg, float qmul, AttnSegments seg) {
     using L = AttnLds<D>;
     constexpr int QB = 1;                // 32-query blocks per wavefront
     constexpr int WPH = NW / HPW;        // wavefronts per head
@@ -114,7 +115,24 @@ __global__ void __launch_bounds__(NW * 64) attn_mfma_kernel(AttnArgs a, int nQ, 
         g = id / (ngh * nQ);
         item = id % (ngh * nQ);
     }
-    const int qtile = nQ - 1 - item / ngh;
+    int qtile = nQ - 1 - item / ngh;
+    int64_t out_row0 = 0;                // first output row of this sequence
+    const int64_t out_rows = a.Mq;       // rows of the whole output (pitch of its slabs)
+    if (SEG) {
+        int lo = 0, hi = seg.n;          // last sequence whose first tile is at or before qtile
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (seg.qtile[mid] <= qtile) lo = mid; else hi = mid;
+        }
+        out_row0 = seg.off[lo];
+        a.Mq = a.Mk = seg.off[lo + 1] - out_row0;
+        qtile -= (int)seg.qtile[lo];
+        a.q = (const bf16_t*)a.q + out_row0 * a.H * D;
+        a.k = (const bf16_t*)a.k + out_row0 * a.Hkv * D;
+        a.vt = (const bf16_t*)a.vt + seg.vcol[lo];
+        a.qpos += out_row0;
+        a.kpos += out_row0;
+    }
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -406,7 +424,7 @@ __global__ void __launch_bounds__(NW * 64) attn_mfma_kernel(AttnArgs a, int nQ, 
                 const int64_t qi = q0w + r;
                 if (qi < a.Mq) {
                     const u32x4 v = *reinterpret_cast<const u32x4*>(stg + r * (D * 2) + ((((sl * 4 + c4) ^ r) & (NCH - 1)) << 4));
-                    *reinterpret_cast<u32x4*>(O + (((int64_t)h * DB + sl) * a.Mq + qi) * 32 + c4 * 8) = v;
+                    *reinterpret_cast<u32x4*>(O + (((int64_t)h * DB + sl) * out_rows + out_row0 + qi) * 32 + c4 * 8) = v;
                 }
             }
     } else {
@@ -419,7 +437,7 @@ __global__ void __launch_bounds__(NW * 64) attn_mfma_kernel(AttnArgs a, int nQ, 
             const int64_t qi = q0w + r;
             if (qi < a.Mq) {
                 const u32x4 v = *reinterpret_cast<const u32x4*>(stg + r * (D * 2) + (((c ^ r) & (NCH - 1)) << 4));
-                *reinterpret_cast<u32x4*>(O + (qi * a.H + h) * (int64_t)D + c * 8) = v;
+                *reinterpret_cast<u32x4*>(O + ((out_row0 + qi) * a.H + h) * (int64_t)D + c * 8) = v;
             }
         }
     }
@@ -436,10 +454,10 @@ bool attention_mfma_supported(const AttnArgs& a) {
     return al(a.q) && al(a.k) && al(a.vt) && al(a.out);
 }
 
-template <int D, int HPW, int NW>
-static hipError_t launch_attn_t(const AttnArgs& a, hipStream_t s) {
+template <int D, int HPW, int NW, bool SEG>
+static hipError_t launch_attn_t(const AttnArgs& a, const AttnSegments& seg, hipStream_t s) {
     constexpr int BQ = NW / HPW * 32;
-    const int nQ = (int)((a.Mq + BQ - 1) / BQ);
+    const int nQ = SEG ? (int)seg.tiles : (int)((a.Mq + BQ - 1) / BQ);
     const int grp = a.H / a.Hkv;
     const int ngh = grp / HPW;
     const int total = nQ * a.Hkv * ngh;
@@ -448,31 +466,45 @@ static hipError_t launch_attn_t(const AttnArgs& a, hipStream_t s) {
     const int grid = xpg > 1 ? 8 * ((nQ * ngh + xpg - 1) / xpg) : (total + 7) / 8 * 8;
     const size_t lds = (size_t)AttnLds<D>::STAGE * ATT_NST;
     {
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, HPW, NW>), (int)lds);
+        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, HPW, NW, SEG>), (int)lds);
         if (e != hipSuccess) return e;
     }
     const float want = attention_mfma_q_scale(D);
     const float qmul = (a.q_scale != 0.f) ? want / a.q_scale : want;   // exactly 1 when the producer applied `want`
-    attn_mfma_kernel<D, HPW, NW><<<dim3(grid), dim3(NW * 64), lds, s>>>(a, nQ, total, xpg, qmul);
+    attn_mfma_kernel<D, HPW, NW, SEG><<<dim3(grid), dim3(NW * 64), lds, s>>>(a, nQ, total, xpg, qmul, seg);
     return hipGetLastError();
 }
 
 #ifndef SPTS_ATT_HPW_MAX
 #define SPTS_ATT_HPW_MAX 4
 #endif
+// as many heads of a kv-head group per workgroup as divide the group (4, 2 or 1)
+static int heads_per_workgroup(int H, int Hkv) {
+    const int grp = H / Hkv;
+    return SPTS_ATT_HPW_MAX >= 4 && grp % 4 == 0 ? 4 : SPTS_ATT_HPW_MAX >= 2 && grp % 2 == 0 ? 2 : 1;
+}
 
-template <int D>
-static hipError_t launch_attn_d(const AttnArgs& a, hipStream_t s) {
-    // as many heads of a kv-head group per workgroup as divide the group (4, 2 or 1)
-    const int grp = a.H / a.Hkv;
-    if (SPTS_ATT_HPW_MAX >= 4 && grp % 4 == 0) return launch_attn_t<D, 4, 8>(a, s);
-    if (SPTS_ATT_HPW_MAX >= 2 && grp % 2 == 0) return launch_attn_t<D, 2, 8>(a, s);
-    return launch_attn_t<D, 1, 8>(a, s);
+template <int D, bool SEG>
+static hipError_t launch_attn_d(const AttnArgs& a, const AttnSegments& seg, hipStream_t s) {
+    switch (heads_per_workgroup(a.H, a.Hkv)) {
+        case 4: return launch_attn_t<D, 4, 8, SEG>(a, seg, s);
+        case 2: return launch_attn_t<D, 2, 8, SEG>(a, seg, s);
+        default: return launch_attn_t<D, 1, 8, SEG>(a, seg, s);
+    }
 }
 
 hipError_t launch_attention_mfma(const AttnArgs& a, hipStream_t s) {
-    if (a.d == 128) return launch_attn_d<128>(a, s);
-    return launch_attn_d<64>(a, s);
+    const AttnSegments none{nullptr, nullptr, nullptr, 0, 0};
+    if (a.d == 128) return launch_attn_d<128, false>(a, none, s);
+    return launch_attn_d<64, false>(a, none, s);
+}
+
+int attention_query_tile(int H, int Hkv) { return 8 / heads_per_workgroup(H, Hkv) * 32; }
+
+hipError_t launch_attention_mfma_batched(const AttnArgs& a, const AttnSegments& seg, hipStream_t s) {
+    if (seg.n < 1 || seg.tiles < 1 || seg.tiles * a.H > 0x7fffffff || a.qpos != a.kpos || a.Mq != a.Mk) return hipErrorInvalidValue;
+    if (a.d == 128) return launch_attn_d<128, true>(a, seg, s);
+    return launch_attn_d<64, true>(a, seg, s);
 }
 
 }  // namespace spts

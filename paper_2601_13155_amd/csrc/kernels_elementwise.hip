@@ -272,6 +272,34 @@ hipError_t launch_copy_bytes(const void* in, void* out, int64_t bytes, hipStream
     return hipGetLastError();
 }
 
+// blockIdx.y = sequence, blockIdx.z: 0 keys, 1 values (and the positions with the keys)
+template <typename V>
+__global__ void __launch_bounds__(256) fill_caches_kernel(CacheChunk c, const V* __restrict__ k, const V* __restrict__ v,
+                                                          const int32_t* __restrict__ pos, int64_t row_vec) {
+    const int b = blockIdx.y;
+    const int64_t n = c.rows[b] * row_vec, first = c.row0[b] * row_vec, stride = (int64_t)gridDim.x * 256;
+    const V* src = (blockIdx.z ? v : k) + first;
+    V* dst = (V*)(blockIdx.z ? c.v[b] : c.k[b]);
+    const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t i = t0; i < n; i += stride) dst[i] = src[i];
+    if (blockIdx.z == 0)
+        for (int64_t i = t0; i < c.rows[b]; i += stride) c.pos[b][i] = pos[c.row0[b] + i];
+}
+hipError_t launch_fill_caches(const CacheChunk& c, int n, const void* k, const void* v, const int32_t* pos, int64_t row_bytes, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    if (n > CacheChunk::CAP || row_bytes % 4 != 0) return hipErrorInvalidValue;
+    int64_t most = 0;
+    for (int b = 0; b < n; ++b) most = c.rows[b] > most ? c.rows[b] : most;
+    const bool wide = row_bytes % 16 == 0;
+    int64_t bx = cdiv(most * (row_bytes / (wide ? 16 : 4)), 1024);
+    if (bx < 1) bx = 1;
+    if (bx > 512) bx = 512;
+    const dim3 g((unsigned)bx, (unsigned)n, 2);
+    if (wide) fill_caches_kernel<u32x4><<<g, dim3(256), 0, s>>>(c, (const u32x4*)k, (const u32x4*)v, pos, row_bytes / 16);
+    else fill_caches_kernel<uint32_t><<<g, dim3(256), 0, s>>>(c, (const uint32_t*)k, (const uint32_t*)v, pos, row_bytes / 4);
+    return hipGetLastError();
+}
+
 __global__ void fill_i32_kernel(int32_t* p, int32_t v, int64_t n) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -424,6 +452,39 @@ hipError_t launch_transpose_pad(const void* v, void* vt, int64_t M, int C, int64
     dim3 g((unsigned)cdiv(ldvt, 32), (unsigned)cdiv(C, 32)), b(256);
     if (bf16) transpose_pad_kernel<bf16_t><<<g, b, 0, s>>>((const bf16_t*)v, (bf16_t*)vt, M, C, ldvt);
     else transpose_pad_kernel<float><<<g, b, 0, s>>>((const float*)v, (float*)vt, M, C, ldvt);
+    return hipGetLastError();
+}
+
+// The same for the sequences of a batch laid back to back: blockIdx.x takes 32 of the padded columns, which belong to one sequence.
+__global__ void __launch_bounds__(256) transpose_pad_batched_kernel(const bf16_t* __restrict__ v, bf16_t* __restrict__ vt, AttnSegments seg,
+                                                                    int C, int64_t ldvt) {
+    __shared__ bf16_t tile[32][33];
+    const int64_t col0 = (int64_t)blockIdx.x * 32;
+    int lo = 0, hi = seg.n;   // last sequence whose columns start at or before col0
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (seg.vcol[mid] <= col0) lo = mid; else hi = mid;
+    }
+    const int64_t row0 = seg.off[lo], M = seg.off[lo + 1] - row0, i0 = col0 - seg.vcol[lo];
+    const int c0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    for (int r = ty; r < 32; r += 8) {
+        const int64_t i = i0 + r;
+        const int c = c0 + tx;
+        bf16_t val{0};
+        if (i < M && c < C) val = v[(row0 + i) * C + c];
+        tile[r][tx] = val;
+    }
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) {
+        const int c = c0 + r;
+        if (c < C) vt[(int64_t)c * ldvt + vt_key_slot(col0 + tx)] = tile[tx][r];   // columns start at multiples of 64: slots stay in their group
+    }
+}
+hipError_t launch_transpose_pad_batched(const void* v, void* vt, const AttnSegments& seg, int64_t cols, int C, int64_t ldvt, hipStream_t s) {
+    static_assert(BATCH_VT_ALIGN % 32 == 0, "a block's columns belong to one sequence");
+    if (cols <= 0 || C <= 0) return hipSuccess;
+    if (cols % 32 != 0 || cols > ldvt) return hipErrorInvalidValue;
+    transpose_pad_batched_kernel<<<dim3((unsigned)(cols / 32), (unsigned)cdiv(C, 32)), dim3(256), 0, s>>>((const bf16_t*)v, (bf16_t*)vt, seg, C, ldvt);
     return hipGetLastError();
 }
 

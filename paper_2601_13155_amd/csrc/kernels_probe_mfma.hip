@@ -26,6 +26,17 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int PKV = 64;          // keys per tile
 constexpr int CHUNK_TILES = 4;   // tiles per workgroup
 constexpr int CHUNK = PKV * CHUNK_TILES;
+static_assert(CHUNK == PROBE_CHUNK, "the caller of the batched form counts chunks");
+
+// last b with pref[b] <= i (pref ascending, pref[0] = 0, i < pref[n])
+__device__ inline int segment_of(const int64_t* pref, int n, int64_t i) {
+    int lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (pref[mid] <= i) lo = mid; else hi = mid;
+    }
+    return lo;
+}
 
 template <int D> struct ProbeLds {
     static constexpr int CPRK = D / 8;
@@ -39,14 +50,26 @@ template <int D> struct ProbeLds {
 // where the rows fit (RB <= 2; left alone it used 270 registers for pass 2 and ran one).
 template <int D, int RB, int PASS, int NWV>
 __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((PASS == 2 && RB <= 2) ? 2 : 1, 8))) probe_mfma_kernel(ProbeArgs a, int Rp, int64_t Np, float qmul,
-                                                         float* __restrict__ stats_part, const float* __restrict__ stats) {
+                                                         float* __restrict__ stats_part, const float* __restrict__ stats, ProbeSegments seg) {
     using L = ProbeLds<D>;
     constexpr int KS = D / 16;
     __shared__ __attribute__((aligned(16))) char sK[2][L::K_BYTES];
     constexpr int NT = 64 * NWV;
     __shared__ float sRed[NWV][PKV];
 
-    const int chunk = blockIdx.x, g = blockIdx.y;
+    // one sequence, or the sequence of a batch that this chunk belongs to
+    int chunk = blockIdx.x;
+    const int g = blockIdx.y;
+    int64_t seq_row0 = 0;
+    const bf16_t* Q = (const bf16_t*)a.qp;
+    if (seg.n > 0) {
+        const int b = segment_of(seg.chunk, seg.n, blockIdx.x);
+        chunk = (int)(blockIdx.x - seg.chunk[b]);
+        seq_row0 = seg.off[b];
+        a.N = seg.off[b + 1] - seq_row0;
+        Q += (int64_t)b * a.P * a.H * D;
+        if (PASS == 2) stats += (int64_t)b * a.Hkv * Rp * 2;
+    }
     const int row_base = (int)blockIdx.z * (32 * RB * NWV);   // first probe row of this row group
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
@@ -59,7 +82,6 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
     // ---- probe-row fragments: row rr = p * grp + hg  <->  qp[p, g*grp + hg, :]
     bf16x8 qf[RB][KS];
     int vis_last[RB];   // last candidate index visible to the lane's row in block rb (pass 1 layout)
-    const bf16_t* Q = (const bf16_t*)a.qp;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         int rr = row_base + wave * 32 * RB + rb * 32 + l32;
@@ -105,7 +127,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
     constexpr int KCH = PKV * L::CPRK / NT;
     static_assert(KCH >= 1, "a key tile gives every thread at least one 16-byte chunk");
     const int kc = tid % L::CPRK, kr = tid / L::CPRK;
-    const bf16_t* Kg = (const bf16_t*)a.k;
+    const bf16_t* Kg = (const bf16_t*)a.k + seq_row0 * a.Hkv * (int64_t)D;
     u32x4 rk[KCH];
     auto load_tile = [&](int t) {
 #pragma unroll
@@ -207,7 +229,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
                     float tot = sRed[0][tid];
 #pragma unroll
                     for (int wv = 1; wv < NWV; ++wv) tot += sRed[wv][tid];   // fixed order
-                    a.partial[((int64_t)blockIdx.z * a.Hkv + g) * Np + key] = tot;
+                    a.partial[((int64_t)blockIdx.z * a.Hkv + g) * Np + seq_row0 + key] = tot;
                 }
             }
         }
@@ -220,7 +242,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
             float l = l_run[rb] + __shfl_xor(l_run[rb], 32);
             int rr = row_base + wave * 32 * RB + rb * 32 + l32;
             if (lh == 0) {
-                float* o = stats_part + (((int64_t)chunk * a.Hkv + g) * Rp + rr) * 2;
+                float* o = stats_part + (((int64_t)blockIdx.x * a.Hkv + g) * Rp + rr) * 2;
                 o[0] = m_run[rb];
                 o[1] = l;
             }
@@ -231,11 +253,17 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
 // stats[g][rr] = (M, 1/L) over the chunks; padded rows rr >= R get (huge, 0).  One wavefront per (g, rr):
 // lane c takes chunks c, c + 64, ...; maximum and sum are reduced over a fixed shuffle tree (deterministic).
 __global__ void __launch_bounds__(256) probe_combine_kernel(const float* __restrict__ stats_part, float* __restrict__ stats,
-                                                            int nchunks, int Hkv, int Rp, int R) {
+                                                            int nchunks, int Hkv, int Rp, int R, ProbeSegments seg) {
     const int lane = threadIdx.x & 63;
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= Hkv * Rp) return;
-    const int g = i / Rp, rr = i % Rp;
+    const int per_seq = Hkv * Rp, b = i / per_seq;
+    if (b >= (seg.n > 0 ? seg.n : 1)) return;
+    const int g = (i - b * per_seq) / Rp, rr = i % Rp;
+    if (seg.n > 0) {
+        const int64_t c0 = seg.chunk[b];
+        nchunks = (int)(seg.chunk[b + 1] - c0);
+        stats_part += c0 * per_seq * 2;
+    }
     if (rr >= R) {   // padded rows weigh nothing
         if (lane == 0) { stats[2 * i] = 1e30f; stats[2 * i + 1] = 0.f; }
         return;
@@ -291,40 +319,70 @@ bool probe_mfma_supported(const ProbeArgs& a) {
     return al(a.qp) && al(a.k);
 }
 
+// chunks, statistics rows and result rows of one sequence or of a batch
+struct ProbePlan { int64_t Np, chunks; int nseq; };
+static ProbePlan probe_plan(const ProbeArgs& a, const ProbeSegments& seg) {
+    return ProbePlan{(a.N + 255) / 256 * 256, seg.n > 0 ? seg.chunks : (a.N + CHUNK - 1) / CHUNK, seg.n > 0 ? seg.n : 1};
+}
+
 template <int D, int RB, int NWV = 4>
-static hipError_t launch_probe_t(const ProbeArgs& a, int Rp, hipStream_t s) {
-    const int64_t Np = (a.N + 255) / 256 * 256;
-    const int nchunks = (int)((a.N + CHUNK - 1) / CHUNK);
+static hipError_t launch_probe_t(const ProbeArgs& a, const ProbeSegments& seg, int Rp, hipStream_t s) {
+    const ProbePlan pl = probe_plan(a, seg);
+    const int nchunks = (int)pl.chunks;
     const int R = a.P * (a.H / a.Hkv);
     float* stats_part = a.partial;
     float* stats = stats_part + (size_t)nchunks * a.Hkv * Rp * 2;
-    float* part = stats + (size_t)a.Hkv * Rp * 2;
+    float* part = stats + (size_t)pl.nseq * a.Hkv * Rp * 2;
     ProbeArgs b = a;
     b.partial = part;
     const float want = attention_mfma_q_scale(D);
     const float qmul = (a.q_scale != 0.f) ? want / a.q_scale : want;   // exactly 1 when the producer applied `want`
     const int groups = probe_groups(Rp);
     dim3 grid(nchunks, a.Hkv, groups), block(256), pblock(64 * NWV);
-    probe_mfma_kernel<D, RB, 1, NWV><<<grid, pblock, 0, s>>>(b, Rp, Np, qmul, stats_part, nullptr);
-    probe_combine_kernel<<<dim3((a.Hkv * Rp + 3) / 4), block, 0, s>>>(stats_part, stats, nchunks, a.Hkv, Rp, R);
-    probe_mfma_kernel<D, RB, 2, NWV><<<grid, pblock, 0, s>>>(b, Rp, Np, qmul, nullptr, stats);
-    probe_final_kernel<<<dim3((unsigned)((a.N + 255) / 256)), block, 0, s>>>(part, a.S, a.N, Np, groups * a.Hkv, 1.0f / (float)(a.P * a.H));
+    probe_mfma_kernel<D, RB, 1, NWV><<<grid, pblock, 0, s>>>(b, Rp, pl.Np, qmul, stats_part, nullptr, seg);
+    probe_combine_kernel<<<dim3((unsigned)((pl.nseq * a.Hkv * Rp + 3) / 4)), block, 0, s>>>(stats_part, stats, nchunks, a.Hkv, Rp, R, seg);
+    probe_mfma_kernel<D, RB, 2, NWV><<<grid, pblock, 0, s>>>(b, Rp, pl.Np, qmul, nullptr, stats, seg);
+    probe_final_kernel<<<dim3((unsigned)((a.N + 255) / 256)), block, 0, s>>>(part, a.S, a.N, pl.Np, groups * a.Hkv, 1.0f / (float)(a.P * a.H));
     return hipGetLastError();
 }
 
-hipError_t launch_probe_mfma(const ProbeArgs& a, hipStream_t s) {
+static hipError_t launch_probe_any(const ProbeArgs& a, const ProbeSegments& seg, hipStream_t s) {
     const int Rp = probe_rp(a.P, a.H, a.Hkv);
     const int rb = Rp / 128;
     if (a.d == 128) {
-        if (rb == 1) return launch_probe_t<128, 1>(a, Rp, s);
-        if (rb == 2) return launch_probe_t<128, 2>(a, Rp, s);
-        if (rb == 3) return launch_probe_t<128, 3>(a, Rp, s);
-        return launch_probe_t<128, 2, 8>(a, Rp, s);   // 512 rows (per group): 8 wavefronts x 64 rows keep two wavefronts per SIMD
+        if (rb == 1) return launch_probe_t<128, 1>(a, seg, Rp, s);
+        if (rb == 2) return launch_probe_t<128, 2>(a, seg, Rp, s);
+        if (rb == 3) return launch_probe_t<128, 3>(a, seg, Rp, s);
+        return launch_probe_t<128, 2, 8>(a, seg, Rp, s);   // 512 rows (per group): 8 wavefronts x 64 rows keep two wavefronts per SIMD
     }
-    if (rb == 1) return launch_probe_t<64, 1>(a, Rp, s);
-    if (rb == 2) return launch_probe_t<64, 2>(a, Rp, s);
-    if (rb == 3) return launch_probe_t<64, 3>(a, Rp, s);
-    return launch_probe_t<64, 2, 8>(a, Rp, s);
+    if (rb == 1) return launch_probe_t<64, 1>(a, seg, Rp, s);
+    if (rb == 2) return launch_probe_t<64, 2>(a, seg, Rp, s);
+    if (rb == 3) return launch_probe_t<64, 3>(a, seg, Rp, s);
+    return launch_probe_t<64, 2, 8>(a, seg, Rp, s);
+}
+
+hipError_t launch_probe_mfma(const ProbeArgs& a, hipStream_t s) { return launch_probe_any(a, ProbeSegments{nullptr, nullptr, 0, 0}, s); }
+
+size_t probe_batch_scratch_floats(const ProbeArgs& a, const ProbeSegments& seg) {
+    const ProbePlan pl = probe_plan(a, seg);
+    const int Rp = probe_rp(a.P, a.H, a.Hkv);
+    return (size_t)(pl.chunks + pl.nseq) * a.Hkv * Rp * 2 + (size_t)probe_groups(Rp) * a.Hkv * pl.Np;
+}
+
+hipError_t launch_probe_mfma_batched(const ProbeArgs& a, const ProbeSegments& seg, hipStream_t s) {
+    if (seg.n < 1 || seg.chunks < 1 || seg.chunks > 0x7fffffff || (int64_t)seg.n * a.Hkv * probe_rp(a.P, a.H, a.Hkv) > 0x7fffffff) return hipErrorInvalidValue;
+    return launch_probe_any(a, seg, s);
+}
+
+__global__ void probe_rows_kernel(const int64_t* __restrict__ off, int P, int64_t total, int32_t* __restrict__ idx) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < total) idx[i] = (int32_t)(off[i / P + 1] - P + i % P);
+}
+hipError_t launch_probe_rows(const int64_t* off, int n, int P, int32_t* idx, hipStream_t s) {
+    const int64_t total = (int64_t)n * P;
+    if (total <= 0) return hipSuccess;
+    probe_rows_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(off, P, total, idx);
+    return hipGetLastError();
 }
 
 }  // namespace spts

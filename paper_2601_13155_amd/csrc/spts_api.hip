@@ -26,6 +26,10 @@ inline size_t split_scratch_bytes(const spts_model_desc& m, int64_t max_tokens) 
     return rows > floor_bytes ? rows : floor_bytes;
 }
 
+// key columns of the transposed value copy: padding of one sequence's end, and of 64 sequences' in a batch
+inline size_t vt_columns(int64_t max_tokens) { return ((size_t)max_tokens + 255) / 256 * 256 + 256 + 64 * BATCH_VT_ALIGN; }
+constexpr size_t SEG_ARRAYS = 8;   // a batched layer's descriptors: rows, budgets and list starts of both selections, probe chunks, V^T columns, query tiles
+
 struct Limits { int64_t max_tokens; int32_t max_probe, max_r, max_dlow; };
 
 Workspace carve(const spts_model_desc& m, const Limits& L) {
@@ -51,14 +55,14 @@ Workspace carve(const spts_model_desc& m, const Limits& L) {
     w.q = take(Np * (size_t)m.H * m.d * b);
     w.khat = take(Np * (size_t)m.Hkv * m.d * b);
     w.vhat = take(Np * (size_t)m.Hkv * m.d * b);
-    w.vt = take((size_t)m.Hkv * m.d * (Np + 256) * b);
+    w.vt = take((size_t)m.Hkv * m.d * vt_columns(L.max_tokens) * b);
     w.att = take(Np * (size_t)m.H * m.d * b);
     w.t = take(Np * (size_t)(2 * L.max_r) * b);
     w.z = take(Np * (size_t)L.max_r * b);
     size_t inner = (size_t)(m.Dff > L.max_dlow ? m.Dff : L.max_dlow);
     w.big = take(Np * inner * b);
     w.misc = take(ARGMAX_SCRATCH_BYTES);
-    w.seg = take(3 * (size_t)(SPTS_MAX_BATCH + 1) * sizeof(int64_t));   // segment descriptors of a batched call
+    w.seg = take(SEG_ARRAYS * (size_t)(SPTS_MAX_BATCH + 1) * sizeof(int64_t));   // segment descriptors of a batched call
     w.topk = take(TOPK_MULTI_SCRATCH_BYTES);                             // tables of the chip-wide TopK
     w.total = off;
     return w;
@@ -1004,21 +1008,26 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
     const auto& m = c->m;
     const int KV = m.Hkv * m.d, QD = m.H * m.d;
     const size_t eb = c->bf16 ? 2 : 4;
-    // host-side plan: per sequence its length, budgets and the start of its slice in the index lists
-    std::vector<int64_t> desc(3 * (size_t)(batch + 1));
-    int64_t* dOff = desc.data();                 // [batch+1] first row of each sequence
-    int64_t* dKa = dOff + (batch + 1);            // [batch]   attention budgets (then reused for the FFN)
-    int64_t* dOut = dKa + (batch + 1);            // [batch+1] first entry of each sequence in the index list
-    std::vector<int64_t> ma(batch), mf(batch), oa(batch + 1), of(batch + 1);
-    oa[0] = of[0] = 0;
+    // host-side plan, one array of batch + 1 numbers each: first rows, budgets and list starts of the two selections, and the
+    // starts of each sequence's probe chunks, V^T columns and query tiles
+    const size_t nb1 = (size_t)batch + 1;
+    std::vector<int64_t> desc(SEG_ARRAYS * nb1, 0);
+    int64_t *dOff = desc.data(), *ma = dOff + nb1, *oa = ma + nb1, *mf = oa + nb1, *of = mf + nb1, *dChunk = of + nb1, *dCol = dChunk + nb1, *dTile = dCol + nb1;
+    const int qt = attention_query_tile(m.H, m.Hkv);
+    int64_t max_len = 0;
     for (int b = 0; b < batch; ++b) {
         const int64_t nb = seq_offsets[b + 1] - seq_offsets[b];
         if (nb < 0) return SPTS_EINVAL;
         if (skip && (nb < probe_len || m_attn[b] < 0 || m_ffn[b] < 0)) return SPTS_EINVAL;   // every sequence holds its probe rows
         ma[b] = skip && m_attn[b] < nb ? m_attn[b] : nb;   // dense layer: every row is active
         mf[b] = skip && m_ffn[b] < nb ? m_ffn[b] : nb;
+        dOff[b] = seq_offsets[b];
         oa[b + 1] = oa[b] + ma[b];
         of[b + 1] = of[b] + mf[b];
+        dChunk[b + 1] = dChunk[b] + (nb + PROBE_CHUNK - 1) / PROBE_CHUNK;
+        dCol[b + 1] = dCol[b] + (ma[b] + BATCH_VT_ALIGN - 1) / BATCH_VT_ALIGN * BATCH_VT_ALIGN;
+        dTile[b + 1] = dTile[b] + (ma[b] + qt - 1) / qt;
+        max_len = std::max(max_len, nb);
         if (kv) {
             kv[b].count = 0;
             if (ma[b] > 0) {
@@ -1028,36 +1037,52 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
             }
         }
     }
+    dOff[batch] = N;
     const int64_t MaT = oa[batch], MfT = of[batch];
     hipStream_t st = c->stream;
     void* xn = c->p<void>(c->off.xn);
+    // the descriptors travel by value as kernel arguments: no staging copy of a host array that dies with this call.  The steps that
+    // stay inside a sequence find theirs from them: one launch per step whatever the batch (24 requests of 65 .. 1500 tokens,
+    // 8B shape: 24 x (projection + 4) probe launches 1000 -> 100 us, 24 x 2 attention launches 410 -> 68 us, the layer 3474 -> 2464).
     int64_t* seg = c->p<int64_t>(c->off.seg);
-    auto upload = [&](const std::vector<int64_t>& k, const std::vector<int64_t>& out) -> hipError_t {
-        for (int b = 0; b <= batch; ++b) { dOff[b] = seq_offsets[b]; dOut[b] = out[b]; if (b < batch) dKa[b] = k[b]; }
-        dKa[batch] = 0;
-        // the descriptors of the previous selection may still be read by work in flight: the small kernels that write the
-        // new ones (values passed by value as kernel arguments) are stream-ordered behind it
-        return launch_write_i64(desc.data(), (int64_t)desc.size(), seg, st);
-    };
-    const TopkSegments segs{seg, seg + (batch + 1), seg + 2 * (batch + 1)};
-    int64_t max_len = 0;
-    for (int b = 0; b < batch; ++b) max_len = std::max<int64_t>(max_len, seq_offsets[b + 1] - seq_offsets[b]);
+    SPTS_HIP(c, launch_write_i64(desc.data(), (int64_t)desc.size(), seg, st));
+    auto dev = [&](const int64_t* host) { return (const int64_t*)seg + (host - dOff); };
+    const TopkSegments seg_a{dev(dOff), dev(ma), dev(oa)}, seg_f{dev(dOff), dev(mf), dev(of)};
+    const float q_scale = query_store_scale(c);
 
     // ------------------------------------------------ attention block: PAP per sequence, projections over the batch
     float* S = s_mha ? s_mha : c->p<float>(c->off.S);
     void* kall = c->p<void>(c->off.kall);
     SPTS_TRY(probe_attn_impl(c, x, pos, N, w, 0, false, kall, nullptr));
-    for (int b = 0; skip && b < batch; ++b) {
-        const int64_t r0 = seq_offsets[b], nb = seq_offsets[b + 1] - r0;
-        SPTS_TRY(probe_scores_rows(c, r0, nb, w, probe_len, (const char*)kall + (size_t)r0 * KV * eb, S + r0));
+    if (skip) {
+        // the probe rows of all sequences in one projection (their queries lie where the active ones will) and one set of probe
+        // launches; shapes without the matrix-core probe take the sequences in turn
+        ProbeArgs pa{};
+        pa.qp = c->p<void>(c->off.q); pa.k = kall; pa.S = S; pa.partial = c->p<float>(c->off.tmp32); pa.q_scale = q_scale;
+        pa.N = N; pa.P = probe_len; pa.H = m.H; pa.Hkv = m.Hkv; pa.d = m.d;
+        const ProbeSegments ps{dev(dOff), dev(dChunk), batch, dChunk[batch]};
+        if (c->bf16 && probe_mfma_supported(pa) && probe_batch_scratch_floats(pa, ps) * sizeof(float) <= split_scratch_bytes(m, c->lim.max_tokens)) {
+            int32_t* rows = c->p<int32_t>(c->off.idxF);   // free until the FFN's selection
+            {
+                PHASE(c, PH_PROBE_Q);
+                SPTS_HIP(c, launch_probe_rows(dev(dOff), batch, probe_len, rows, st));
+                GemmArgs gq = gemm_args(xn, m.D, rows, w->Wq, m.D, nullptr, QD, (int64_t)batch * probe_len, QD, m.D);
+                gq.a_rows = N;
+                SPTS_TRY(run_gemm_rope(c, gq, m.H, rows, 0, c->p<void>(c->off.q), w->Wq_s, q_scale));
+            }
+            PHASE(c, PH_PROBE_ATTN);
+            SPTS_HIP(c, launch_probe_mfma_batched(pa, ps, st));
+        } else {
+            for (int b = 0; b < batch; ++b)
+                SPTS_TRY(probe_scores_rows(c, dOff[b], dOff[b + 1] - dOff[b], w, probe_len, (const char*)kall + (size_t)dOff[b] * KV * eb, S + dOff[b]));
+        }
     }
     // dense layer (the else-branches of Alg. 1): no selection, the "active rows" are the rows themselves
     int32_t* idxA = !skip ? nullptr : idx_attn ? idx_attn : c->p<int32_t>(c->off.idxA);
     if (skip) {
         PHASE(c, PH_TOPK);
-        SPTS_HIP(c, upload(ma, oa));
-        SPTS_HIP(c, launch_topk(S, max_len, 0, protect_last, idxA, batch, st, segs));
-        SPTS_HIP(c, launch_add_segment_base(idxA, segs.out_offsets, segs.offsets, batch, MaT, st));
+        SPTS_HIP(c, launch_topk(S, max_len, 0, protect_last, idxA, batch, st, seg_a));
+        SPTS_HIP(c, launch_add_segment_base(idxA, seg_a.out_offsets, seg_a.offsets, batch, MaT, st));
     }
     if (MaT > 0) {
         const int32_t* posA = pos;
@@ -1069,46 +1094,75 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
             posA = c->p<int32_t>(c->off.posA);
             khat = c->p<char>(c->off.khat);
         }
-        auto attn_args = [&](int b) {
-            AttnArgs aa{};
-            aa.q = c->p<char>(c->off.q) + (size_t)oa[b] * QD * eb;
-            aa.k = khat + (size_t)oa[b] * KV * eb; aa.v = vhat + (size_t)oa[b] * KV * eb;
-            aa.qpos = posA + oa[b]; aa.kpos = posA + oa[b];
-            aa.out = c->p<char>(c->off.att) + (size_t)oa[b] * QD * eb;
-            aa.Mq = ma[b]; aa.Mk = ma[b]; aa.H = m.H; aa.Hkv = m.Hkv; aa.d = m.d;
-            aa.ldvt = (ma[b] + 255) / 256 * 256; aa.vt = c->p<void>(c->off.vt);
-            return aa;
-        };
-        const float q_scale = query_store_scale(c);
+        // queries and values of the active rows: one launch where the matrix-core GEMM takes both
         GemmArgs gq = gemm_args(xn, m.D, idxA, w->Wq, m.D, nullptr, QD, MaT, QD, m.D);
         gq.a_rows = N;
-        { PHASE(c, PH_Q_PROJ); SPTS_TRY(run_gemm_rope(c, gq, m.H, idxA, 0, c->p<void>(c->off.q), w->Wq_s, q_scale)); }
-        GemmArgs gv = gemm_args(xn, m.D, idxA, w->Wv, m.D, vhat, KV, MaT, KV, m.D);
-        gv.a_rows = N;
-        prefer_slab(c, gv, w->Wv_s, nullptr, KV);
-        { PHASE(c, PH_V_PROJ); SPTS_TRY(run_gemm(c, gv)); }
-        for (int b = 0; b < batch; ++b) {
-            if (ma[b] == 0) continue;
-            AttnArgs aa = attn_args(b);
-            aa.q_scale = q_scale;
-            const bool amf = c->bf16 && attention_mfma_supported(aa);
-            PHASE(c, PH_ATTENTION);
-            if (amf) {
-                SPTS_HIP(c, launch_transpose_pad(aa.v, c->p<void>(c->off.vt), ma[b], KV, aa.ldvt, c->bf16, st));
-                SPTS_HIP(c, launch_attention_mfma(aa, st));
-            } else {
-                SPTS_HIP(c, launch_attention_generic(aa, c->bf16, st));
-            }
-            if (kv) {
-                SPTS_HIP(c, launch_copy_bytes(aa.k, kv[b].k, ma[b] * (int64_t)KV * eb, st));
-                SPTS_HIP(c, launch_copy_bytes(aa.v, kv[b].v, ma[b] * (int64_t)KV * eb, st));
-                SPTS_HIP(c, launch_copy_bytes(posA + oa[b], kv[b].pos, ma[b] * 4, st));
-                kv[b].count = ma[b];
-            }
+        GemmArgs f = gq;
+        f.epi = EPI_ROPE_STORE; f.N = QD + KV; f.n_split = QD; f.B1 = w->Wv;
+        f.C = c->p<void>(c->off.q); f.ldc = QD; f.C2 = vhat; f.ldc2 = KV;
+        f.rope = c->p<float2>(c->off.rope); f.rope_idx = idxA; f.head_dim = m.d; f.rope_scale = q_scale;
+        prefer_slab(c, f, w->Wq_s, w->Wv_s, QD, KV);
+        if (c->bf16 && gemm_mfma_supported(f)) {
+            PHASE(c, PH_QV_PROJ);
+            SPTS_TRY(run_gemm_mfma(c, f));
+        } else {
+            { PHASE(c, PH_Q_PROJ); SPTS_TRY(run_gemm_rope(c, gq, m.H, idxA, 0, c->p<void>(c->off.q), w->Wq_s, q_scale)); }
+            GemmArgs gv = gemm_args(xn, m.D, idxA, w->Wv, m.D, vhat, KV, MaT, KV, m.D);
+            gv.a_rows = N;
+            prefer_slab(c, gv, w->Wv_s, nullptr, KV);
+            PHASE(c, PH_V_PROJ);
+            SPTS_TRY(run_gemm(c, gv));
         }
         GemmArgs go = gemm_args(c->p<void>(c->off.att), QD, nullptr, w->Wo, QD, x, m.D, MaT, m.D, QD, EPI_RESIDUAL);
         go.c_idx = idxA;
         prefer_slab(c, go, w->Wo_s, nullptr, m.D);
+        // attention: the query tiles of all sequences in one launch, or the sequences in turn
+        AttnArgs all{};
+        all.q = c->p<void>(c->off.q); all.k = khat; all.v = vhat; all.qpos = posA; all.kpos = posA; all.out = c->p<void>(c->off.att);
+        all.Mq = MaT; all.Mk = MaT; all.H = m.H; all.Hkv = m.Hkv; all.d = m.d; all.q_scale = q_scale;
+        all.vt = c->p<void>(c->off.vt); all.ldvt = dCol[batch];
+        const AttnSegments as{dev(oa), dev(dCol), dev(dTile), batch, dTile[batch]};
+        if (c->bf16 && (size_t)dCol[batch] <= vt_columns(c->lim.max_tokens) && attention_mfma_supported(all)) {
+            GemmArgs t = go; t.a_slab = 1;
+            if (gemm_mfma_supported(t)) { go = t; all.out_slab = 1; }
+            PHASE(c, PH_ATTENTION);
+            SPTS_HIP(c, launch_transpose_pad_batched(vhat, c->p<void>(c->off.vt), as, dCol[batch], KV, all.ldvt, st));
+            SPTS_HIP(c, launch_attention_mfma_batched(all, as, st));
+        } else {
+            for (int b = 0; b < batch; ++b) {
+                if (ma[b] == 0) continue;
+                AttnArgs aa = all;
+                aa.q = c->p<char>(c->off.q) + (size_t)oa[b] * QD * eb;
+                aa.k = khat + (size_t)oa[b] * KV * eb; aa.v = vhat + (size_t)oa[b] * KV * eb;
+                aa.qpos = posA + oa[b]; aa.kpos = posA + oa[b];
+                aa.out = c->p<char>(c->off.att) + (size_t)oa[b] * QD * eb;
+                aa.Mq = ma[b]; aa.Mk = ma[b];
+                aa.ldvt = (ma[b] + 255) / 256 * 256;
+                PHASE(c, PH_ATTENTION);
+                if (c->bf16 && attention_mfma_supported(aa)) {
+                    SPTS_HIP(c, launch_transpose_pad(aa.v, c->p<void>(c->off.vt), ma[b], KV, aa.ldvt, c->bf16, st));
+                    SPTS_HIP(c, launch_attention_mfma(aa, st));
+                } else {
+                    SPTS_HIP(c, launch_attention_generic(aa, c->bf16, st));
+                }
+            }
+        }
+        if (kv) {
+            PHASE(c, PH_GATHER);
+            CacheChunk cc;
+            int in = 0;
+            for (int b = 0; b < batch; ++b) {
+                if (ma[b] > 0) {
+                    cc.k[in] = kv[b].k; cc.v[in] = kv[b].v; cc.pos[in] = kv[b].pos; cc.row0[in] = oa[b]; cc.rows[in] = ma[b];
+                    ++in;
+                    kv[b].count = ma[b];
+                }
+                if (in == CacheChunk::CAP || (b == batch - 1 && in > 0)) {
+                    SPTS_HIP(c, launch_fill_caches(cc, in, khat, vhat, posA, (int64_t)KV * eb, st));
+                    in = 0;
+                }
+            }
+        }
         { PHASE(c, PH_O_PROJ); SPTS_TRY(run_gemm(c, go)); }
     }
 
@@ -1120,9 +1174,8 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
     int32_t* idxF = !skip ? nullptr : idx_ffn ? idx_ffn : c->p<int32_t>(c->off.idxF);
     if (skip) {
         PHASE(c, PH_TOPK);
-        SPTS_HIP(c, upload(mf, of));
-        SPTS_HIP(c, launch_topk(SF, max_len, 0, protect_last, idxF, batch, st, segs));
-        SPTS_HIP(c, launch_add_segment_base(idxF, segs.out_offsets, segs.offsets, batch, MfT, st));
+        SPTS_HIP(c, launch_topk(SF, max_len, 0, protect_last, idxF, batch, st, seg_f));
+        SPTS_HIP(c, launch_add_segment_base(idxF, seg_f.out_offsets, seg_f.offsets, batch, MfT, st));
     }
     GemmArgs gh = gemm_args(xn, m.D, idxF, w->Wgate, m.D, c->p<void>(c->off.big), m.Dff, MfT, m.Dff, m.D, EPI_SILU_MUL);
     gh.a_rows = N;

@@ -156,6 +156,10 @@ hipError_t launch_gather_i32(const int32_t* in, const int32_t* idx, int32_t* out
 hipError_t launch_copy_bytes(const void* in, void* out, int64_t bytes, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_iota_i32(int32_t* p, int64_t n, hipStream_t s);
+// Per-sequence caches of a batch filled from rows laid back to back: sequence b's `rows[b]` rows from row0[b] on of k and v (row_bytes each,
+// a multiple of 4) and of pos go to its own buffers; up to CAP sequences travel as kernel arguments per launch
+struct CacheChunk { static constexpr int CAP = 48; void* k[CAP]; void* v[CAP]; int32_t* pos[CAP]; int64_t row0[CAP]; int64_t rows[CAP]; };
+hipError_t launch_fill_caches(const CacheChunk& c, int n, const void* k, const void* v, const int32_t* pos, int64_t row_bytes, hipStream_t s);
 // n host int64 values -> device array dst, in chunks passed by value as kernel arguments (no host staging buffer, no
 // synchronisation, safe under stream capture)
 struct I64Chunk { static constexpr int CAP = 256; int64_t v[CAP]; int32_t n; };
@@ -214,6 +218,15 @@ float attention_mfma_q_scale(int d);
 hipError_t launch_attention_generic(const AttnArgs& a, bool bf16, hipStream_t s);
 bool attention_mfma_supported(const AttnArgs& a);
 hipError_t launch_attention_mfma(const AttnArgs& a, hipStream_t s);
+// Every sequence of a batch in one launch (queries and keys of a sequence are the same rows): rows [off[b], off[b+1]) of q / k / v /
+// positions / out, V^T columns from vcol[b] (multiples of BATCH_VT_ALIGN), query tiles from qtile[b]; device arrays [n + 1].  a.Mq = a.Mk =
+// off[n], a.ldvt covers vcol[n]; qtile counts attention_query_tile(H, Hkv) queries a tile.
+struct AttnSegments { const int64_t* off; const int64_t* vcol; const int64_t* qtile; int n; int64_t tiles; };
+constexpr int BATCH_VT_ALIGN = 64;
+int attention_query_tile(int H, int Hkv);
+hipError_t launch_attention_mfma_batched(const AttnArgs& a, const AttnSegments& seg, hipStream_t s);
+// V^T of such a batch: vt[c, vcol[b] + vt_key_slot(i)] = v[off[b] + i, c], zeros from a sequence's end to the next one's columns
+hipError_t launch_transpose_pad_batched(const void* v, void* vt, const AttnSegments& seg, int64_t cols, int C, int64_t ldvt, hipStream_t s);
 
 // probe: qp [P, H, d], k [N, Hkv, d] -> S[N]; scratch floats: 2*P*H (+ Hkv*N for the MFMA path)
 struct ProbeArgs {
@@ -224,6 +237,14 @@ struct ProbeArgs {
 hipError_t launch_probe_generic(const ProbeArgs& a, bool bf16, hipStream_t s);
 bool probe_mfma_supported(const ProbeArgs& a);
 hipError_t launch_probe_mfma(const ProbeArgs& a, hipStream_t s);
+// Every sequence of a batch in the same four launches: rows [off[b], off[b+1]) of k and S, probe queries [n, P, H, d], chunks of
+// PROBE_CHUNK keys from chunk[b] (device arrays [n + 1]; `chunks` = chunk[n]); a.N = off[n]; a.partial: probe_batch_scratch_floats
+struct ProbeSegments { const int64_t* off; const int64_t* chunk; int n; int64_t chunks; };
+constexpr int PROBE_CHUNK = 256;
+size_t probe_batch_scratch_floats(const ProbeArgs& a, const ProbeSegments& seg);
+hipError_t launch_probe_mfma_batched(const ProbeArgs& a, const ProbeSegments& seg, hipStream_t s);
+// idx[b * P + p] = off[b + 1] - P + p: the probe rows of every sequence
+hipError_t launch_probe_rows(const int64_t* off, int n, int P, int32_t* idx, hipStream_t s);
 size_t probe_scratch_floats(int64_t N, int P, int H, int Hkv);
 // single probe row (P = 1): a scan of K with one query per head; scratch: probe_p1_scratch_floats(N, H) floats
 bool probe_p1_supported(const ProbeArgs& a);

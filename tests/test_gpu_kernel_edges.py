@@ -115,3 +115,51 @@ def test_layer_with_short_products(torch, H_, Hkv, d, pack):
         for kv_mode, ma, mf in ((0, max(1, (2 * N) // 3), N // 2), (1, N // 3, N - 1)):
             skip = runtime.run_layer(ctx, x, pos, dw, shape, skip=1, probe_len=37, m_attn=ma, m_ffn=mf, kv_mode=kv_mode)
             H.lockstep_layer(skip, x, pos, w, mdl, orc.LayerCfg(1, 37, ma, mf, 1, kv_mode), "bf16")
+
+
+# ------------------------------------------------------------------------------------------ batches in one launch per step
+@pytest.mark.parametrize("name,shape,P", [
+    ("d128_g4", synth.ModelShape(D=512, H=8, Hkv=2, d=128, Dff=1024, dtype="bf16", rope_base=500000.0), 8),
+    ("d64_g2_p1", synth.ModelShape(D=512, H=8, Hkv=4, d=64, Dff=1024, dtype="bf16"), 1),
+    ("d128_g7", synth.ModelShape(D=512, H=7, Hkv=1, d=128, Dff=1024, dtype="bf16"), 80),
+], ids=lambda v: v if isinstance(v, str) else None)
+def test_batch_with_sequences_around_chunks_and_tiles(torch, name, shape, P):
+    """50 sequences (more than one launch of the cache fill takes) whose lengths and budgets lie around the probe's 256-key chunks and
+    the attention's 64-key / 64 .. 256-query tiles, budgets of zero among them; skip and dense branch, every sequence
+    lock-step against the oracle, caches included."""
+    r, mdl = 64, H.oracle_model(shape)
+    rng = np.random.default_rng(3)
+    lens = [P, P + 1, 256, 257, 511] + [int(v) for v in rng.integers(P, 300, 45)]
+    w = synth.make_layer(71, 0, shape, r)
+    dw = runtime.upload_layer(w, shape, r)
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ctx = runtime.make_context(shape, int(offs[-1]), P, r, shape.Dff)
+    xs = [synth.hidden_states(200 + b, n, shape.D, "bf16") for b, n in enumerate(lens)]
+    ps = [(synth.positions(n) * 2 + b).astype(np.int32) for b, n in enumerate(lens)]
+    ma = [min(n, (63, 64, 65, 0, 256, 1)[b % 6]) for b, n in enumerate(lens)]
+    mf = [max(1, n // 2) for n in lens]
+    for skip in (1, 0):
+        a_n = ma if skip else lens
+        f_n = mf if skip else lens
+        xd = runtime.to_device(np.concatenate(xs), "bf16")
+        s = torch.zeros(int(offs[-1]), dtype=torch.float32, device="cuda")
+        ia = torch.full((sum(a_n) + 1,), -1, dtype=torch.int32, device="cuda")
+        iff = torch.full((sum(f_n) + 1,), -1, dtype=torch.int32, device="cuda")
+        caches = [runtime.KVCache(shape, n) for n in a_n]
+        kvs = [c.struct for c in caches]
+        ctx.spts_layer_prefill_batched(xd, torch.from_numpy(np.concatenate(ps)).cuda(), offs, dw, P, ma, mf, 1, kvs, s, ia, iff, skip=skip)
+        x_out, s_out, ia, iff = runtime.to_host(xd).astype(np.float64), s.cpu().numpy(), ia.cpu().numpy(), iff.cpu().numpy()
+        oa = of = 0
+        for b, n in enumerate(lens):
+            r0 = int(offs[b])
+            gpu = dict(x=x_out[r0:r0 + n], s_mha=s_out[r0:r0 + n], idx_attn=ia[oa:oa + a_n[b]] - r0, idx_ffn=iff[of:of + f_n[b]] - r0)
+            cfg = orc.LayerCfg(skip, P, a_n[b], f_n[b], 1, 0)
+            ref = H.lockstep_layer(gpu, xs[b], ps[b], w, mdl, cfg, "bf16")["ref"]
+            assert kvs[b].count == a_n[b]
+            if a_n[b]:
+                k, v, p = caches[b].host()
+                assert np.array_equal(p, ps[b][gpu["idx_attn"]] if skip else ps[b])
+                assert H.row_rel_err(k.reshape(a_n[b], -1), ref.k_cache.reshape(a_n[b], -1)) <= H.TOL["bf16"]["hidden"]
+                assert H.row_rel_err(v.reshape(a_n[b], -1), ref.v_cache.reshape(a_n[b], -1)) <= H.TOL["bf16"]["hidden"]
+            oa += a_n[b]
+            of += f_n[b]
