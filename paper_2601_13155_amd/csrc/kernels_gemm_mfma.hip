@@ -51,7 +51,7 @@
 //
 // Epilogues: plain store (+ optional transposed copy for V), rotary embedding (pairs (j, j+d/2) sit
 // in the same lane because an N block pair is d/2 apart), SiLU(gate)*up with gate and up columns
-// interleaved per wavefront, residual add into scattered rows, per-row partial sums of squares.
+// interleaved per wavefront (row-major, slab-major or channel-major), residual add into scattered rows, per-row partial sums of squares.
 #include "spts_internal.h"
 
 namespace spts {
@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     constexpr int MI = 16 / NW;                   // 32-row blocks per wavefront (4 or 2)
     constexpr int WROWS = 32 * MI;                // output rows per wavefront
     constexpr int LROWS = 256 / NW;               // operand tile rows each wavefront loads
-    constexpr bool DUAL = (EPI == EPI_SILU_MUL);
+    constexpr bool DUAL = (EPI == EPI_SILU_MUL || EPI == EPI_SILU_MUL_T);
     constexpr bool SEG = (EPI == EPI_ROPE_STORE);   // two products side by side: rotary columns, then stored columns
     constexpr bool CAN_SPLIT = (EPI == EPI_STORE || EPI == EPI_RESIDUAL || EPI == EPI_ROPE || SEG);
     constexpr int TILE_BYTES = S::TILE_BYTES;
@@ -410,6 +410,17 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
                     stage(tr, cb - col0 + 8 * q, o);
                 }
             }
+        } else if (EPI == EPI_SILU_MUL_T) {
+            // channel-major: staged channel c keeps the 16-byte chunk (8 rows) r at chunk position r ^ (c % 32), which spreads the
+            // 2-byte writes of a lane's four channels and the whole-channel reads over the banks
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int c = wn * 64 + j * 32 + 4 * lh + 8 * (r >> 2) + (r & 3);
+                    *reinterpret_cast<bf16_t*>(smem + c * 512 + ((((tr >> 3) ^ c) & 31) << 4) + ((tr & 7) << 1)) =
+                        f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
+                }
         } else if (EPI == EPI_SILU_MUL) {
             {
 #pragma unroll
@@ -485,6 +496,16 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     // ---- the staged tile leaves row by row: NCH consecutive lanes write one row's OUT_COLS columns as
     //      16-byte pieces (whole 128-byte lines), rows through the scatter list when there is one
     __syncthreads();
+    if (EPI == EPI_SILU_MUL_T) {
+        // a channel's 256 rows are 512 contiguous bytes (rows past M are stored too: ldc covers whole tiles)
+#pragma unroll 4
+        for (int e = tid; e < 128 * 32; e += NW * 64) {
+            const int c = e >> 5, ch = e & 31;
+            *reinterpret_cast<u32x4*>(Cb + (int64_t)(col0 + c) * a.ldc + row0 + ch * 8) =
+                *reinterpret_cast<const u32x4*>(smem + c * 512 + (((ch ^ c) & 31) << 4));
+        }
+        return;
+    }
     if ((EPI == EPI_SILU_MUL || EPI == EPI_STORE) && a.c_slab) {
         // slab-major output: slab sl of the tile is 256 rows x 64 bytes, contiguous over the rows; 4 lanes per row
         constexpr int RPS = NW * 64 / 4;         // rows per pass
@@ -522,14 +543,15 @@ static inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) 
 
 bool gemm_mfma_supported(const GemmArgs& a) {
     if (a.c_is_f32) return false;
-    const bool dual = a.epi == EPI_SILU_MUL;
+    const bool dual = a.epi == EPI_SILU_MUL || a.epi == EPI_SILU_MUL_T;
     const int ncols = dual ? 128 : 256;
+    if (a.epi == EPI_SILU_MUL_T && (a.A1 || a.c_idx || a.Ct || a.c_slab || a.ldc < (a.M + BM - 1) / BM * BM)) return false;
     if (a.M <= 0 || a.N <= 0 || a.N % ncols != 0) return false;
     if (a.K < 32 || a.K % 32 != 0) return false;
     if (a.lda % 8 != 0 || a.ldb % 8 != 0) return false;
     // slab-major operands: served by the 32-wide-slab instantiations; A not gathered
     const bool seg = a.epi == EPI_ROPE_STORE;
-    if ((a.a_slab || a.b_slab) && a.epi != EPI_SILU_MUL && a.epi != EPI_RESIDUAL && a.epi != EPI_STORE && a.epi != EPI_ROPE && !seg) return false;
+    if ((a.a_slab || a.b_slab) && !dual && a.epi != EPI_RESIDUAL && a.epi != EPI_STORE && a.epi != EPI_ROPE && !seg) return false;
     if (seg) {
         if (a.n_split <= 0 || a.n_split >= a.N || a.n_split % 256 != 0 || a.c_idx || a.c_slab) return false;
         if (!a.B1 || !al16(a.B1) || !a.C2 || !al16(a.C2) || a.ldc2 % 8 != 0) return false;
@@ -558,7 +580,7 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 
 template <int EPI, int BK, bool DUAL_A, int NW>
 static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
-    const int ncols = EPI == EPI_SILU_MUL ? 128 : 256;
+    const int ncols = EPI == EPI_SILU_MUL || EPI == EPI_SILU_MUL_T ? 128 : 256;
     const int nM = (int)((a.M + BM - 1) / BM), nN = a.N / ncols;
     const int tiles = nM * nN;
     const bool split = a.ksplit > 1;
@@ -700,6 +722,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
             if (a.A1) e = launch_t<EPI_SILU_MUL, 32, true, NW>(a, s);
             else e = launch_t<EPI_SILU_MUL, 32, false, NW>(a, s);   // 4 stages of 32 measured 2 % faster here than 2 of 64
             break;
+        case EPI_SILU_MUL_T: e = launch_t<EPI_SILU_MUL_T, 32, false, NW>(a, s); break;
         default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess || a.ksplit <= 1) return e;

@@ -796,9 +796,85 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_mean_kernel(const T* __rest
     }
 }
 
+// Rows of at most 64 * KPT values: one wavefront per row, the row read once into registers.  The key of the k-th largest |value|
+// (15 significant bits in bf16, 31 in fp32) is built from its top bit down: a bit stays set when at least k keys reach it.
+// Counting is one compare per key whose lane mask is summed on the scalar unit, so there are no histograms, no LDS and no
+// barrier, and the wavefronts of a SIMD hide each other's scalar work.  Bound: 15 compares per key on the vector unit (26 us
+// for 14336 rows of 4096) and one read of the row (20 us).  Measured there: 283 us with the workgroup-per-row kernel above
+// (two histogram passes over 1024-lane strides), 93 us here.
+template <typename T, int KPT>
+__global__ void __launch_bounds__(256) topk_mean_wave_kernel(const T* __restrict__ vals, int64_t ld, int64_t rows, int n, int k, int wide,
+                                                             float* __restrict__ out) {
+    constexpr int VN = 16 / (int)sizeof(T), BITS = sizeof(T) == 2 ? 15 : 31;
+    static_assert(KPT % VN == 0, "whole 16-byte loads");
+    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= rows) return;
+    const int lane = threadIdx.x & 63;
+    const T* row = vals + r * ld;
+    auto key_of = [](uint32_t raw) { return raw & (sizeof(T) == 2 ? 0x7fffu : 0x7fffffffu); };   // order of |v|; slots past n hold key 0
+    uint32_t key[KPT];
+    if (wide) {   // rows at 16-byte addresses
+#pragma unroll
+        for (int j = 0; j < KPT / VN; ++j) {
+            const int i0 = (j * 64 + lane) * VN;
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (i0 + VN <= n) v = *reinterpret_cast<const u32x4*>(row + i0);
+            else
+                for (int e = 0; e < VN; ++e)
+                    if (i0 + e < n) {
+                        const uint32_t raw = sizeof(T) == 2 ? (uint32_t)reinterpret_cast<const uint16_t*>(row)[i0 + e] : reinterpret_cast<const uint32_t*>(row)[i0 + e];
+                        if (sizeof(T) == 2) v[e >> 1] |= raw << (16 * (e & 1)); else v[e] = raw;
+                    }
+#pragma unroll
+            for (int e = 0; e < VN; ++e) key[j * VN + e] = key_of(sizeof(T) == 2 ? v[e >> 1] >> (16 * (e & 1)) : v[e]);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) {
+            const int i = j * 64 + lane;
+            key[j] = i < n ? key_of(sizeof(T) == 2 ? (uint32_t)reinterpret_cast<const uint16_t*>(row)[i] : reinterpret_cast<const uint32_t*>(row)[i]) : 0u;
+        }
+    }
+    uint32_t t = 0;
+    for (int b = BITS - 1; b >= 0; --b) {
+        const uint32_t cand = t | (1u << b);
+        int cnt = 0;
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) cnt += (int)__popcll(__ballot(key[j] >= cand));
+        if (cnt >= k) t = cand;
+    }
+    auto value = [](uint32_t q) { return __uint_as_float(sizeof(T) == 2 ? q << 16 : q); };
+    float s = 0.f;
+    int above = 0;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        above += (int)__popcll(__ballot(key[j] > t));
+        s += key[j] > t ? value(key[j]) : 0.f;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);   // fixed order
+    if (lane == 0) out[r] = (s + (float)(k - above) * value(t)) / (float)k;
+}
+
+template <typename T>
+static bool launch_topk_mean_wave(const T* vals, int64_t ld, int64_t rows, int64_t n, int64_t k, float* out, hipStream_t s) {
+    constexpr int MAXK = sizeof(T) == 2 ? 128 : 64;   // registers: two or more wavefronts per SIMD
+    if (n > 64 * MAXK || rows > (int64_t)1 << 32) return false;
+    const dim3 g((unsigned)((rows + 3) / 4)), b(256);
+    const int wide = (ld * (int)sizeof(T)) % 16 == 0 && (reinterpret_cast<uintptr_t>(vals) & 15u) == 0;
+    if (n <= 64 * 8) topk_mean_wave_kernel<T, 8><<<g, b, 0, s>>>(vals, ld, rows, (int)n, (int)k, wide, out);
+    else if (n <= 64 * 16) topk_mean_wave_kernel<T, 16><<<g, b, 0, s>>>(vals, ld, rows, (int)n, (int)k, wide, out);
+    else if (n <= 64 * 32) topk_mean_wave_kernel<T, 32><<<g, b, 0, s>>>(vals, ld, rows, (int)n, (int)k, wide, out);
+    else if (n <= 64 * 64) topk_mean_wave_kernel<T, 64><<<g, b, 0, s>>>(vals, ld, rows, (int)n, (int)k, wide, out);
+    else topk_mean_wave_kernel<T, MAXK><<<g, b, 0, s>>>(vals, ld, rows, (int)n, (int)k, wide, out);
+    return true;
+}
+
 hipError_t launch_topk_mean(const void* vals, int64_t ld, int64_t rows, int64_t n, int64_t k, float* out, bool bf16,
                             hipStream_t s) {
     if (rows <= 0 || n <= 0 || k <= 0) return hipSuccess;
+    if (bf16 ? launch_topk_mean_wave((const bf16_t*)vals, ld, rows, n, k, out, s) : launch_topk_mean_wave((const float*)vals, ld, rows, n, k, out, s))
+        return hipGetLastError();
     const dim3 g((unsigned)rows), b(TOPK_THREADS);
     if (bf16) topk_mean_kernel<bf16_t><<<g, b, 0, s>>>((const bf16_t*)vals, ld, n, k, out);
     else topk_mean_kernel<float><<<g, b, 0, s>>>((const float*)vals, ld, n, k, out);

@@ -71,6 +71,8 @@ enum GemmEpilogue : int {
     EPI_ROPE = 4,       // C[row, col] = rotary(acc) with table row (rope_idx ? rope_idx[row] : row)
     EPI_ROPE_STORE = 5, // two products of the same A rows in one launch (MFMA path only): columns [0, n_split) = A * B0^T
                         // with the rotary epilogue -> C; columns [n_split, N) = A * B1^T stored plainly -> C2 (and Ct)
+    EPI_SILU_MUL_T = 6, // EPI_SILU_MUL stored channel-major: C[col, row], ldc >= M rounded up to 256 (MFMA path only; the rows
+                        // between M and there are written with values of row M - 1)
 };
 
 struct GemmArgs {

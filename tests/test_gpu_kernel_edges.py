@@ -163,3 +163,21 @@ def test_batch_with_sequences_around_chunks_and_tiles(torch, name, shape, P):
                 assert H.row_rel_err(v.reshape(a_n[b], -1), ref.v_cache.reshape(a_n[b], -1)) <= H.TOL["bf16"]["hidden"]
             oa += a_n[b]
             of += f_n[b]
+
+
+# ------------------------------------------------------------------------------------------ channel scores
+# calibration lengths around the wavefront kernel's 64 x 8 .. 64 x 128 (fp32: 64 x 64) registers and the GEMM's 256-row tiles
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [1, 63, 255, 257, 512, 513, 1025, 2047, 2049, 4096, 4097, 8192, 8200])
+def test_channel_importance_lengths(torch, dtype, T):
+    shape = synth.ModelShape(D=64, H=1, Hkv=1, d=64, Dff=128, dtype=dtype)
+    w = synth.layer_weights(81, 0, shape)
+    dw = runtime.upload_layer(w, shape, 0, pack=False)
+    ctx = runtime.make_context(shape, T, 1, 1, shape.Dff)
+    x = synth.calibration_states(81, T, shape.D, dtype)
+    xd = runtime.to_device(x, dtype)
+    for k in sorted({1, max(1, T // 5), T}):
+        imp = torch.full((shape.Dff,), -1.0, dtype=torch.float32, device="cuda")
+        ctx.spts_channel_importance(xd, T, dw, k, imp)
+        ref = orc.channel_importance(x, w["Wgate"], w["Wup"], k, H.rnd_for(dtype))
+        assert np.max(np.abs(imp.cpu().numpy() - ref)) <= H.TOL[dtype]["score"] * np.max(np.abs(ref)), k
