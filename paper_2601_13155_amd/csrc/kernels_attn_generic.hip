@@ -6,7 +6,7 @@
 // operand fragments come straight from global memory, a lane's whole row piece at once (element j of a lane's 4-element
 // piece is the operand of product j: which k an instruction multiplies is free as long as both operands agree), and the
 // wavefronts of a workgroup split the keys (attention, statistics) or the probe rows (scores) and meet in LDS.
-// Measured at N = 512, 4 heads, d = 64: attention of 256 queries 50 -> 35 us against one wavefront per query row; probe of 32
+// Measured at N = 512, 4 heads, d = 64: attention of 256 queries 50 -> 24 us against one wavefront per query row; probe of 32
 // rows 1001 -> 22 us (two launches) against one lane per candidate that walked all P * H rows.
 #include "spts_internal.h"
 
@@ -19,25 +19,32 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int D> constexpr int f32_waves() { return D <= 64 ? 8 : 4; }
 constexpr float LOG2E = 1.4426950408889634f;
 
-// elements c .. c+3 of a row of d elements as fp32, zeros past its end; d4: d % 4 == 0 (the piece is then one aligned load)
+// elements c .. c+3 of a row of d elements as fp32, zeros past its end; d4: d % 4 == 0 (the piece is then one aligned load).  Loads
+// are unconditional from clamped places and the zeros selected afterwards: a load under a lane mask is a branch of its own, and a
+// row's loads then wait for one another (attention of 256 queries over 512 keys: 35 us with masked loads).
 __device__ inline f32x4 load4(const float* row, int c, int d, bool d4) {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (d4) { if (c < d) v = *reinterpret_cast<const f32x4*>(row + c); return v; }
+    f32x4 v;
+    if (d4) {
+        v = *reinterpret_cast<const f32x4*>(row + (c < d ? c : d - 4));
+    } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) if (c + e < d) v[e] = row[c + e];
+        for (int e = 0; e < 4; ++e) v[e] = row[c + e < d ? c + e : d - 1];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = c + e < d ? v[e] : 0.f;
     return v;
 }
 __device__ inline f32x4 load4(const bf16_t* row, int c, int d, bool d4) {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    f32x4 v;
     if (d4) {
-        if (c < d) {
-            const u32x2 w = *reinterpret_cast<const u32x2*>(row + c);
-            v = f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16), __uint_as_float(w[1] & 0xffff0000u)};
-        }
-        return v;
+        const u32x2 w = *reinterpret_cast<const u32x2*>(row + (c < d ? c : d - 4));
+        v = f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16), __uint_as_float(w[1] & 0xffff0000u)};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = bf16_to_f32(row[c + e < d ? c + e : d - 1]);
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) if (c + e < d) v[e] = bf16_to_f32(row[c + e]);
+    for (int e = 0; e < 4; ++e) v[e] = c + e < d ? v[e] : 0.f;
     return v;
 }
 
@@ -117,16 +124,17 @@ __global__ void __launch_bounds__(64 * f32_waves<D>()) attention_f32_kernel(Attn
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const int c = db * 32 + l32;
+            float vv[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 int64_t j = j0 + acc_row(r, lh);
                 if (j >= a.Mk) j = a.Mk - 1;   // its probability is zero
-                const float vv = c < d ? to_f32(V[j * rstride + c]) : 0.f;
-                if (r == 0)
-#pragma unroll
-                    for (int t = 0; t < 16; ++t) o[db][t] *= alpha;
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv, p[r], o[db], 0, 0, 0);
+                vv[r] = to_f32(V[j * rstride + (c < d ? c : d - 1)]);
             }
+#pragma unroll
+            for (int t = 0; t < 16; ++t) o[db][t] *= alpha;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(c < d ? vv[r] : 0.f, p[r], o[db], 0, 0, 0);
         }
     }
     l += __shfl_xor(l, 32);
@@ -254,7 +262,7 @@ __global__ void __launch_bounds__(64 * f32_waves<D>()) probe_scores_f32_kernel(P
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int rr = r0 + acc_row(r, lh);
-            st[r] = rr < R ? *reinterpret_cast<const float2*>(a.stats + ((int64_t)g * R + rr) * 2) : make_float2(0.f, 0.f);
+            st[r] = *reinterpret_cast<const float2*>(a.stats + ((int64_t)g * R + (rr < R ? rr : R - 1)) * 2);
         }
         const f32x16 s = mma_rows<NS>(qf, kf);
 #pragma unroll

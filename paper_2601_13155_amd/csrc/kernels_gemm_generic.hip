@@ -64,8 +64,15 @@ __global__ void __launch_bounds__(256) gemm_tile32_kernel(GemmArgs a) {
     for (int p = 0; p < NP; ++p)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[p][r] = 0.f;
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    auto load = [&](const T* p, int k0) -> u32x4 { return k0 + lh * EPC < a.K ? *reinterpret_cast<const u32x4*>(p + k0) : zero; };   // K % EPC == 0
+    // K % EPC == 0: a chunk is inside or outside as a whole.  Loads past K read the last chunk instead and count as zeros: a load
+    // under a lane mask is a branch of its own, and the group's loads would then wait for one another.
+    auto load = [&](const T* p, int k0) -> u32x4 {
+        const bool in = k0 + lh * EPC < a.K;
+        u32x4 v = *reinterpret_cast<const u32x4*>(p + (in ? k0 : a.K - EPC - lh * EPC));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = in ? v[e] : 0u;
+        return v;
+    };
     for (int k0 = wave * (U * KS); k0 < a.K; k0 += 4 * U * KS) {
         u32x4 fa[U], fb[U], fa1[U], fb1[U];
 #pragma unroll
