@@ -374,9 +374,7 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 constexpr int LONG_U = 4;                       // 16-byte loads in flight per lane
 constexpr int LONG_STEP = 64 * 4 * LONG_U;      // scores a wavefront takes per iteration
 
-__global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
-                                                                 int protect_last, int32_t* __restrict__ idx_out) {
-    extern __shared__ __attribute__((aligned(16))) char lsm[];
+__device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores, int64_t N, int64_t k, int protect_last, int32_t* __restrict__ idx_out, char* lsm) {
     int* h13 = reinterpret_cast<int*>(lsm);                                                     // [T13_BINS]
     uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);     // [TOPK_WAVES][T13_CW]
     int (*whist)[256] = reinterpret_cast<int (*)[256]>(lsm + T13_BINS * 4);                     // fallback only, same bytes
@@ -385,8 +383,6 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __
     __shared__ int64_t sh_need;
     __shared__ int wave_gt[TOPK_WAVES], wave_eq[TOPK_WAVES], wave_tot[TOPK_WAVES];
     __shared__ int sh_b12, sh_over;
-    scores += (int64_t)blockIdx.x * N;
-    idx_out += (int64_t)blockIdx.x * k;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)N;
     const int per_wave = ((n + TOPK_WAVES - 1) / TOPK_WAVES + LONG_STEP - 1) / LONG_STEP * LONG_STEP;
@@ -521,6 +517,253 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __
             }
             gt_before += tot_gt;
             eq_before += tot_eq;
+        }
+    }
+}
+
+__global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
+                                                                 int protect_last, int32_t* __restrict__ idx_out) {
+    extern __shared__ __attribute__((aligned(16))) char lsm[];
+    topk_long_rows(scores + (int64_t)blockIdx.x * N, N, k, protect_last, idx_out + (int64_t)blockIdx.x * k, lsm);
+}
+
+// The same rows read from memory once (32768 < N <= LONG1_MAX_N, N % 4 == 0).  A sample of 8192 scores spread over the row gives, through
+// the 8192-bin histogram and linear interpolation inside a bin, two keys that bracket the k-th largest with four standard
+// deviations of the sample's quantile on either side (about 4 % of the row lies between them).  One sweep over the row then
+// leaves, per score, a bit of the lane's own in LDS (above the bracket), and the keys inside the bracket, with their places, in the
+// wavefront's LDS region; counts tell whether the bracket holds the threshold.  The exact threshold is resolved among those keys,
+// the selected ones set their bits, and the index list is written from the bits: no score is read again.  Rows whose
+// bracket misses or overflows (heavily tied scores, scores that depend strongly on the position) take the three-sweep route of
+// topk_long_rows.
+// Bound: HBM for one read of the scores and the index list (68 us for 512 rows of 131072, k = 52428, at 5.5 TB/s) and about 25
+// vector instructions per score and wavefront.  Measured there: 199 us with three sweeps -> 153 us, of which about 45 are
+// the sample, the barriers and the passes over the bracket (the same for every length).
+constexpr int LONG1_MAX_N = 131072;                               // one bit per score: 16 KB
+constexpr int LONG1_WORDS = LONG1_MAX_N / TOPK_WAVES / 64 / 32;  // 32-score words per lane
+constexpr int LONG1_SAMPLES = 8192;
+struct topk_true { static constexpr bool value = true; };
+struct topk_false { static constexpr bool value = false; };
+
+// all 1024 lanes: the key at rank `rank` (1 = largest; clamped to 1 .. LONG1_SAMPLES by the caller) of the sampled histogram,
+// interpolated inside its 13-bit bin -> *sh_key; ends with a barrier
+__device__ inline void sample_key(const int* h13, int rank, int* wave_tot, uint32_t* sh_key) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int BPT = T13_BINS / TOPK_THREADS;
+    int c[BPT], tot = 0;
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) { c[q] = h13[T13_BINS - 1 - BPT * tid - q]; tot += c[q]; }
+    int incl = tot;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
+    }
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    int excl = incl - tot;
+    for (int w = 0; w < wave; ++w) excl += wave_tot[w];
+    if (excl < rank && rank <= excl + tot) {
+        int rem = rank - excl, q = 0;
+#pragma unroll
+        for (int t = 0; t < BPT - 1; ++t)
+            if (q == t && rem > c[t]) { rem -= c[t]; q = t + 1; }
+        int cq = c[0];
+#pragma unroll
+        for (int t = 1; t < BPT; ++t) cq = q == t ? c[t] : cq;
+        const uint32_t width = 1u << T13_LOW, lo = (uint32_t)(T13_BINS - 1 - BPT * tid - q) << T13_LOW;
+        const uint32_t down = (uint32_t)((float)width * ((float)rem - 0.5f) / (float)cq);   // the rem-th of cq keys from the bin's top
+        *sh_key = lo + (width - 1u - (down < width ? down : width - 1u));
+    }
+    __syncthreads();
+}
+
+__global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) topk_once_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
+                                                                 int protect_last, int32_t* __restrict__ idx_out) {
+    extern __shared__ __attribute__((aligned(16))) char lsm[];
+    int* h13 = reinterpret_cast<int*>(lsm);                                                   // [T13_BINS], the sample's
+    uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);   // [TOPK_WAVES][T13_CW]
+    __shared__ int hist[256];
+    __shared__ uint32_t sh_prefix, sh_lo, sh_hi;
+    __shared__ int64_t sh_need;
+    __shared__ int wave_gt[TOPK_WAVES], wave_in[TOPK_WAVES], wave_eq[TOPK_WAVES], wave_tot[TOPK_WAVES];
+    scores += (int64_t)blockIdx.x * N;
+    idx_out += (int64_t)blockIdx.x * k;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = (int)N;
+    // ---- bracket from the sample: two 16-byte pieces per lane, spread evenly
+    for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
+    __syncthreads();
+    {
+        const int quads = n / 4;
+        f32x4v v[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+            v[p] = *reinterpret_cast<const f32x4v*>(scores + 4 * (int64_t)((int64_t)(2 * tid + p) * quads / (LONG1_SAMPLES / 4)));
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) hist_add(h13, true, (int)(order_key(v[p][e]) >> T13_LOW));
+    }
+    __syncthreads();
+    const float frac = (float)k / (float)n, r = frac * LONG1_SAMPLES, dev = 4.f * sqrtf(r * (1.f - frac)) + 4.f;
+    const int r_hi = (int)(r - dev), r_lo = (int)(r + dev) + 1;
+    if (tid == 0) { sh_hi = 0xFFFFFFFFu; sh_lo = 0u; }
+    __syncthreads();
+    if (r_hi >= 1) sample_key(h13, r_hi, wave_tot, &sh_hi);                   // else nothing lies above the bracket
+    if (r_lo <= LONG1_SAMPLES) sample_key(h13, r_lo, wave_tot, &sh_lo);       // else it has no lower end
+    const uint32_t hi_key = sh_hi, lo_key = sh_lo < sh_hi ? sh_lo : sh_hi, width = hi_key - lo_key;
+
+    // ---- the one sweep: wavefront w owns a contiguous slice
+    const int per_wave = ((n + TOPK_WAVES - 1) / TOPK_WAVES + LONG_STEP - 1) / LONG_STEP * LONG_STEP;
+    const int lo = wave * per_wave;
+    const int hi = lo + per_wave < n ? lo + per_wave : n;   // n % 4 == 0, so a 16-byte load that starts below hi ends below it
+    const int last = protect_last ? n - 1 : -1;
+    // Bit 31 - (4 u + e) of word w: element e of the slice's load 8 w + u lies above the bracket (later: is selected).  The words lie
+    // where the sample's histogram was.  A key inside the bracket is kept as (key - lo_key) << 11 | (4 u + e) << 6 | lane; its word
+    // follows from the region's fill at the word's end.
+    uint32_t (*sel)[TOPK_THREADS] = reinterpret_cast<uint32_t (*)[TOPK_THREADS]>(lsm);
+    static_assert(LONG1_WORDS * TOPK_THREADS * 4 <= T13_BINS * 4, "the words fit the histogram's place");
+    const int words = (hi > lo ? hi - lo + 2 * LONG_STEP - 1 : 0) / (2 * LONG_STEP);   // of this wavefront
+    int cnt = 0, cgt = 0, word_end[LONG1_WORDS];
+#pragma unroll
+    for (int w = 0; w < LONG1_WORDS; ++w) {
+        if (w < words) {
+            uint32_t gw = 0;
+            // ALL: every score exists and none of them is the protected one
+            auto half_word = [&](int half, auto all_tag) {
+                constexpr bool ALL = decltype(all_tag)::value;
+                const int base = lo + (w * 2 + half) * LONG_STEP;
+                f32x4v v[LONG_U];
+#pragma unroll
+                for (int u = 0; u < LONG_U; ++u) {
+                    const int i0 = base + u * 256 + lane * 4;
+                    v[u] = *reinterpret_cast<const f32x4v*>(scores + (ALL || i0 < hi ? i0 : n - 4));   // past the slice: any place of the row
+                }
+#pragma unroll
+                for (int u = 0; u < LONG_U; ++u) {
+                    const int i0 = base + u * 256 + lane * 4;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        uint32_t key = order_key(v[u][e]);
+                        if (!ALL && i0 + e == last) key = 0xFFFFFFFFu;
+                        const uint32_t delta = key - lo_key;
+                        const bool in = (ALL || i0 < hi) && delta <= width;
+                        gw = (gw << 1) | ((ALL || i0 < hi) && key > hi_key ? 1u : 0u);
+                        const uint64_t m = __ballot(in);
+                        const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, cnt));
+                        if (in && at < T13_CW) cand[wave][at] = (delta << 11) | (uint32_t)((half * 16 + u * 4 + e) << 6) | (uint32_t)lane;
+                        cnt += (int)__popcll(m);
+                    }
+                }
+            };
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const int base = lo + (w * 2 + half) * LONG_STEP;
+                if (base + LONG_STEP <= hi && !(last >= base && last < base + LONG_STEP)) half_word(half, topk_true{});
+                else half_word(half, topk_false{});
+            }
+            sel[w][tid] = gw;
+            cgt += __popc(gw);
+        }
+        word_end[w] = cnt;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) cgt += __shfl_xor(cgt, off);
+    if (lane == 0) { wave_gt[wave] = cgt; wave_in[wave] = cnt; }
+    __syncthreads();
+    int above = 0, inside = 0;
+    bool fits = width < (1u << 21);
+#pragma unroll
+    for (int w = 0; w < TOPK_WAVES; ++w) { above += wave_gt[w]; inside += wave_in[w]; fits &= wave_in[w] <= T13_CW; }
+    if (!fits || (int64_t)above >= k || (int64_t)above + inside < k) {
+        __syncthreads();
+        topk_long_rows(scores, N, k, protect_last, idx_out, lsm);
+        return;
+    }
+    // ---- exact threshold among the keys of the bracket: 8 + 8 + 5 bits of their distance from its lower end
+    uint32_t prefix = 0;
+    int64_t need = k - above;
+    const int cnt64 = (cnt + 63) & ~63;
+#pragma unroll
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? 24 : pass == 1 ? 16 : 11;
+        const uint32_t hi_mask = pass == 0 ? 0u : pass == 1 ? 0xFF000000u : 0xFFFF0000u;
+        if (tid < 256) hist[tid] = 0;
+        __syncthreads();
+        for (int j = lane; j < cnt64; j += 64) {
+            const uint32_t c = j < cnt ? cand[wave][j] : 0u;
+            hist_add(hist, j < cnt && (c & hi_mask) == prefix, (int)((c >> shift) & (pass == 2 ? 0x1Fu : 0xFFu)));
+        }
+        __syncthreads();
+        if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh_prefix, &sh_need);
+        __syncthreads();
+        prefix = sh_prefix;
+        need = sh_need;
+    }
+    const uint32_t T = prefix >> 11;   // the threshold's distance from lo_key
+    const int need_eq = (int)need;
+    int g = 0, ne = 0;
+    for (int j = lane; j < cnt64; j += 64) {
+        const uint32_t c = j < cnt ? cand[wave][j] >> 11 : 0u;
+        g += (int)__popcll(__ballot(j < cnt && c > T));
+        ne += (int)__popcll(__ballot(j < cnt && c == T));
+    }
+    if (lane == 0) wave_eq[wave] = ne;
+    __syncthreads();
+    int eq_before = 0, eq_all = 0;
+#pragma unroll
+    for (int w = 0; w < TOPK_WAVES; ++w) { eq_before += w < wave ? wave_eq[w] : 0; eq_all += wave_eq[w]; }
+    // ---- the bracket's selected keys join the words.  Keys equal to the threshold go by index; they are ranked only where the
+    //      selection ends between them.
+    auto place = [&](uint32_t c, int j) {   // index order inside the wavefront: word, load, lane, element
+        int w = 0;
+#pragma unroll
+        for (int q = 0; q < LONG1_WORDS - 1; ++q) w += j >= word_end[q] ? 1 : 0;
+        const uint32_t ue = (c >> 6) & 31u;
+        return ((uint32_t)w << 11) | ((ue >> 2) << 8) | ((c & 63u) << 2) | (ue & 3u);
+    };
+    for (int j0 = 0; j0 < cnt64; j0 += 64) {
+        const int j = j0 + lane;
+        const uint32_t c = j < cnt ? cand[wave][j] : 0u;
+        const bool eq = j < cnt && (c >> 11) == T;
+        const uint32_t at = place(c, j);
+        bool take = j < cnt && (c >> 11) > T;
+        if (eq_all == need_eq) {
+            take |= eq;
+        } else if (__ballot(eq)) {
+            int rank = eq_before;
+            for (int q = 0; q < cnt; ++q) {
+                const uint32_t o = cand[wave][q];
+                if ((o >> 11) == T && place(o, q) < at) ++rank;
+            }
+            take |= eq && rank < need_eq;
+        }
+        if (take) atomicOr(&sel[at >> 11][wave * 64 + ((at >> 2) & 63u)], 1u << (31 - (((at >> 8) & 7u) * 4 + (at & 3u))));
+    }
+    const int eq_taken = need_eq - eq_before < 0 ? 0 : need_eq - eq_before < ne ? need_eq - eq_before : ne;
+    if (lane == 0) wave_in[wave] = cgt + g + eq_taken;   // selected scores of this slice
+    __syncthreads();
+    int out = 0;
+    for (int w = 0; w < wave; ++w) out += wave_in[w];
+
+    // ---- ordered index list from the words; index order inside a load is (lane, element e)
+    for (int w = 0; w < words; ++w) {
+        const uint32_t sw = sel[w][tid];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int i0 = lo + (w * 8 + q) * 256 + lane * 4;
+            int at = out;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint64_t m = __ballot((sw >> (31 - (q * 4 + e))) & 1u);
+                at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, at));
+                out += (int)__popcll(m);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool s_ = (sw >> (31 - (q * 4 + e))) & 1u;
+                if (s_) idx_out[at] = i0 + e;
+                at += s_ ? 1 : 0;
+            }
         }
     }
 }
@@ -900,9 +1143,16 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
         }
     }
     else if (!seg.offsets && N % 4 == 0 && N < ((int64_t)1 << 30)) {
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&topk_long_kernel), T13_LDS_BYTES);
-        if (e != hipSuccess) return e;
-        topk_long_kernel<<<g, b, T13_LDS_BYTES, s>>>(scores, N, k, protect_last, idx_out);
+        // the bracket needs sample ranks on both of its sides: budgets between 1/64 and 63/64 of the row
+        if (N <= LONG1_MAX_N && k * 64 >= N && (N - k) * 64 >= N) {
+            hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&topk_once_kernel), T13_LDS_BYTES);
+            if (e != hipSuccess) return e;
+            topk_once_kernel<<<g, b, T13_LDS_BYTES, s>>>(scores, N, k, protect_last, idx_out);
+        } else {
+            hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&topk_long_kernel), T13_LDS_BYTES);
+            if (e != hipSuccess) return e;
+            topk_long_kernel<<<g, b, T13_LDS_BYTES, s>>>(scores, N, k, protect_last, idx_out);
+        }
     }
     else topk_kernel<<<g, b, 0, s>>>(scores, N, k, protect_last, idx_out, seg);
     return hipGetLastError();

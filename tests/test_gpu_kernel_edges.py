@@ -181,3 +181,33 @@ def test_channel_importance_lengths(torch, dtype, T):
         ctx.spts_channel_importance(xd, T, dw, k, imp)
         ref = orc.channel_importance(x, w["Wgate"], w["Wup"], k, H.rnd_for(dtype))
         assert np.max(np.abs(imp.cpu().numpy() - ref)) <= H.TOL[dtype]["score"] * np.max(np.abs(ref)), k
+
+
+# ------------------------------------------------------------------------------------------ TopK of long rows of a batch
+@pytest.mark.parametrize("n", [32772, 65536, 100004, 131068, 131072, 131076])
+def test_long_row_topk_patterns(torch, n):
+    """Rows that the one-sweep kernel takes by its bracket (smooth, sorted, periodic), and rows that make the bracket miss or overflow
+    (equal scores, two values, a step at one place, values that the sample's positions never see); lengths around a wavefront's
+    slices and the kernel's longest row (one length beyond it)."""
+    rng = np.random.default_rng(n)
+    base = np.exp(0.5 * rng.standard_normal(n)).astype(np.float32) / n
+    unseen = base.copy()
+    quads = n // 4
+    seen = np.zeros(quads, bool)
+    seen[(np.arange(2048, dtype=np.int64) * quads) // 2048] = True
+    unseen[np.repeat(~seen, 4)[: n]] *= 7.0                       # the sample sees only the small ones
+    step = base.copy(); step[: n // 3] += 1.0
+    rows = {"smooth": base, "ascending": np.sort(base), "descending": np.sort(base)[::-1].copy(), "equal": np.full(n, 0.25, np.float32),
+            "two_values": np.where(np.arange(n) % 3 == 0, 0.5, 0.125).astype(np.float32), "step": step, "unseen": unseen,
+            "signed": rng.standard_normal(n).astype(np.float32), "octaves": np.exp(20 * rng.standard_normal(n)).astype(np.float32),
+            "zeros": np.where(rng.random(n) < 0.9, -0.0, base).astype(np.float32)}
+    s = np.stack(list(rows.values()))
+    sd = torch.from_numpy(s).cuda()
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    for k in (1, 2, 700, int(0.4 * n), n - 3, n):
+        for protect in (0, 1):
+            out = torch.full((len(rows), k), -7, dtype=torch.int32, device="cuda")
+            ctx.spts_select_topk_batched(sd, n, k, protect, len(rows), out)
+            got = out.cpu().numpy()
+            for b, name in enumerate(rows):
+                assert np.array_equal(got[b], orc.topk_select(s[b], k, protect)), (name, k, protect)
