@@ -4,9 +4,12 @@
 // FFN and the low-rank proxy.  Both operands are K-contiguous, so MFMA fragments are plain 16-byte
 // LDS reads with no transposition.
 //
-//  * 256x256 output tile per workgroup, 8 wavefronts (4x2), each owning 64x128 = 2x4 MFMA
-//    32x32x16 blocks: 128 fp32 accumulators per lane, 8 MFMAs per 6 fragment reads, two wavefronts
+//  * 256x256 output tile per workgroup, 8 wavefronts (4x2), each owning 64x128 = 4x8 MFMA
+//    16x16x32 blocks: 128 fp32 accumulators per lane, 32 MFMAs per 12 fragment reads, two wavefronts
 //    per SIMD so that one wavefront's LDS reads, waits and barriers hide behind the other's MFMAs.
+//    The same tile on 32x32x16 instructions (the same LDS traffic and rate on paper) is 5-10 % slower on large
+//    products: gate/up 3277 x 28672 x 4096 656 -> 593 us (1300 TFLOP/s), down 336 -> 324, Q+V 139 -> 128,
+//    O 123 -> 110.
 //  * K is consumed in slabs of 64 (32 when K is not a multiple of 64, or when a second A operand
 //    is staged).  Slabs travel global memory -> LDS directly (global_load_lds_dwordx4: no VGPR
 //    staging, no ds_write instructions) into a ring of 2 LDS stages of 64 KB (4 stages of 32 KB for
@@ -21,9 +24,9 @@
 //  * A direct-to-LDS load puts lane i's 16 bytes at base + 16*i, so the XOR swizzle that makes the
 //    16-lane b128 fragment reads bank-conflict free is applied on the global side: lane i fetches
 //    the chunk that belongs at position i.
-//  * Fragment reads of the next k-step are issued between the MFMAs of the current one
-//    (sched_group_barrier pins the interleaving); the barrier sits a few MFMAs into the second
-//    k-step so that the matrix pipe stays fed while wavefronts meet.
+//  * A slab of 32 is two steps, one per half of the wavefront's columns.  Fragment reads of the next step are issued
+//    between the MFMAs of the current one (sched_group_barrier pins the interleaving); the barrier sits a few MFMAs
+//    into the last step so that the matrix pipe stays fed while wavefronts meet.
 //  * Slab-major operands.  With row-major operands and slabs of 32 a load instruction takes 64 bytes of each of 16
 //    rows, so every 128-byte line is requested twice (by the loads of two consecutive slabs) and the kernel is bound
 //    by L2 requests (measured: whole-line loads of the same data are 8-9 % faster, per operand).  An operand stored
@@ -57,7 +60,6 @@
 namespace spts {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 256, BN = 256;
@@ -104,8 +106,8 @@ __device__ __forceinline__ void tile_of(int id, int nM, int nN, int& tm, int& tn
 template <int EPI, int BK, bool DUAL_A, int NW>
 __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, int nN, int nfull, int nunits) {
     using S = Slab<BK>;
-    constexpr int MI = 16 / NW;                   // 32-row blocks per wavefront (4 or 2)
-    constexpr int WROWS = 32 * MI;                // output rows per wavefront
+    constexpr int MI = 32 / NW;                   // 16-row blocks per wavefront (8 or 4)
+    constexpr int WROWS = 16 * MI;                // output rows per wavefront
     constexpr int LROWS = 256 / NW;               // operand tile rows each wavefront loads
     constexpr bool DUAL = (EPI == EPI_SILU_MUL || EPI == EPI_SILU_MUL_T);
     constexpr bool SEG = (EPI == EPI_ROPE_STORE);   // two products side by side: rotary columns, then stored columns
@@ -116,7 +118,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     constexpr int STAGE = TILE_BYTES * NOPS;
     constexpr int LPO = LROWS / S::ROWS_PER_LOAD; // loads per wavefront per operand tile
     constexpr int PER = LPO * NOPS;               // direct-to-LDS loads per wavefront per slab
-    constexpr int KSTEPS = BK / 16;
+    constexpr int STEPS = BK / 16;                // multiplication steps per slab: 32 of K times half of the wavefront's columns
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     // ---- work unit.  Workgroup b runs on XCD b % 8 as that XCD's (b / 8)-th workgroup.  Every XCD
@@ -144,7 +146,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, lh = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4;
     const int64_t row0 = (int64_t)tm * BM;
     constexpr int OUT_COLS = DUAL ? 128 : 256;   // output columns covered by one tile
     const int col0 = tn * OUT_COLS;
@@ -201,41 +203,50 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
 #define SPTS_DMA_SLAB(kt_)                                                                     \
     { _Pragma("unroll") for (int u_ = 0; u_ < PER; ++u_) SPTS_DMA_ONE(kt_, u_) }
 
-    f32x16 acc[MI][4];
+    f32x4 acc[MI][8];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 8; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-    // B tile row of this wavefront's N block j
-    auto brow = [&](int j) { return DUAL ? (j >> 1) * 128 + wn * 64 + (j & 1) * 32 : wn * 128 + j * 32; };
+    // B tile row of this wavefront's N block j (16 columns)
+    auto brow = [&](int j) { return DUAL ? (j >> 2) * 128 + wn * 64 + (j & 3) * 16 : wn * 128 + j * 16; };
 
-    bf16x8 af[2][MI], bfr[2][4], af1[2][DUAL_A ? MI : 1];
-#define SPTS_LOAD_FRAGS(buf, stage, ks)                                                                      \
+    // A fragment is 16 rows of 32 K elements.  Step st of a slab multiplies the A fragments of its 32-wide piece st / 2 by the B
+    // fragments of columns 64 * (st % 2) .. + 63 of the wavefront's.
+    bf16x8 af[2][MI], af1[DUAL_A ? MI : 1], bfr[2][4];
+#define SPTS_LOAD_A(buf, stage, ks)                                                                          \
     {                                                                                                        \
         const char* sA_ = smem + (stage) * STAGE;                                                            \
-        const char* sB_ = sA_ + TILE_BYTES;                                                                  \
-        const int c_ = (ks) * 2 + lh;                                                                        \
-        _Pragma("unroll") for (int i = 0; i < MI; ++i) {                                                     \
-            af[buf][i] = *reinterpret_cast<const bf16x8*>(sA_ + S::off(wm * WROWS + i * 32 + l32, c_));    \
-            if (DUAL_A)                                                                                      \
-                af1[buf][i] = *reinterpret_cast<const bf16x8*>(sB_ + TILE_BYTES + S::off(wm * WROWS + i * 32 + l32, c_)); \
-        }                                                                                                    \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                        \
-            bfr[buf][j] = *reinterpret_cast<const bf16x8*>(sB_ + S::off(brow(j) + l32, c_));               \
+        _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                       \
+            af[buf][i] = *reinterpret_cast<const bf16x8*>(sA_ + S::off(wm * WROWS + i * 16 + l16, (ks) * 4 + lq)); \
     }
-#define SPTS_MFMA(buf, i, j)                                                                                 \
+#define SPTS_LOAD_A1(stage, ks)                                                                              \
     {                                                                                                        \
-        if (DUAL_A && (j) >= 2)                                                                              \
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[buf][j], af1[buf][i], acc[i][j], 0, 0, 0); \
-        else                                                                                                 \
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[buf][j], af[buf][i], acc[i][j], 0, 0, 0);  \
+        const char* sA1_ = smem + (stage) * STAGE + 2 * TILE_BYTES;                                          \
+        _Pragma("unroll") for (int i = 0; i < (DUAL_A ? MI : 0); ++i)                                        \
+            af1[i] = *reinterpret_cast<const bf16x8*>(sA1_ + S::off(wm * WROWS + i * 16 + l16, (ks) * 4 + lq)); \
     }
-    constexpr int NREADS = (DUAL_A ? 2 * MI : MI) + 4;   // fragment reads per k-step
-    constexpr int NM = 4 * MI;                            // MFMAs per k-step
-    constexpr int HS = NM / 2;                            // MFMA slots per half k-step
+#define SPTS_LOAD_B(half, stage, ks)                                                                         \
+    {                                                                                                        \
+        const char* sB_ = smem + (stage) * STAGE + TILE_BYTES;                                               \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                        \
+            bfr[half][j] = *reinterpret_cast<const bf16x8*>(sB_ + S::off(brow((half) * 4 + j) + l16, (ks) * 4 + lq)); \
+    }
+    // MFMA m of a step
+#define SPTS_MFMA(abuf, half, m)                                                                             \
+    {                                                                                                        \
+        if (DUAL_A && (half) == 1)                                                                           \
+            acc[(m) / 4][(half) * 4 + (m) % 4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[half][(m) % 4], af1[DUAL_A ? (m) / 4 : 0], acc[(m) / 4][(half) * 4 + (m) % 4], 0, 0, 0); \
+        else                                                                                                 \
+            acc[(m) / 4][(half) * 4 + (m) % 4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[half][(m) % 4], af[abuf][(m) / 4], acc[(m) / 4][(half) * 4 + (m) % 4], 0, 0, 0); \
+    }
+    constexpr int NM = 4 * MI;                            // MFMAs per step
+    constexpr int HS = NM / 2;                            // MFMA slots per half step
+    constexpr int NR_ODD = DUAL_A ? MI + 4 : 4;           // fragment reads for a step of the second columns / of the first
+    constexpr int NR_EVEN = MI + 4;
 
     // K slabs of this workgroup: all of them, or the split's share (the first nk_all % ksplit splits
     // take one slab more)
@@ -249,62 +260,66 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
         if (npre == NST - 1) { SPTS_WAIT_VMCNT((NST - 2) * PER); } else { SPTS_WAIT_VMCNT(0); }   // slab 0 landed
     }
     __syncthreads();
-    SPTS_LOAD_FRAGS(0, 0, 0)
+    SPTS_LOAD_A(0, 0, 0)
+    SPTS_LOAD_B(0, 0, 0)
 
-    // One K slab = KSTEPS k-steps of 16 MFMAs per wavefront.  Every memory instruction sits in the
-    // shadow of an MFMA (an MFMA occupies the matrix pipe for 32 cycles while the wavefront may
+    // One K slab = STEPS steps of 16 MFMAs per wavefront.  Every memory instruction sits in the
+    // shadow of an MFMA (an MFMA occupies the matrix pipe for 16 cycles while the wavefront may
     // issue other work):
-    //   k-step s < KSTEPS-1: MFMA 1-8 are each followed by one fragment read of k-step s+1,
-    //                        MFMA 9-16 by one direct-to-LDS load of slab kt+NST-1 (ISSUE);
-    //   last k-step: 4 MFMAs, then wait for this wavefront's share of slab kt+1 and meet the
-    //                workgroup (slab kt+1 is published, stage kt%NST is free for the next iteration),
-    //                then 12 MFMAs, the first 8 each followed by a fragment read of slab kt+1.
-    // ISSUE / NEXT are literal constants at every expansion.
-    // HS MFMA slots, one fragment read after each (two after the first NREADS-HS of them)
-#define SPTS_INTERLEAVE_READS                                                                                \
-    _Pragma("unroll") for (int g_ = 0; g_ < NREADS - HS; ++g_) {                                             \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                   \
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                                   \
-    }                                                                                                        \
-    _Pragma("unroll") for (int g_ = NREADS - HS; g_ < HS; ++g_) {                                            \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                   \
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                   \
-    }
-#define SPTS_SLAB(kt_, ISSUE, NEXT, WAITN)                                                                   \
+    //   step s < STEPS-1: the first half's MFMAs are interleaved with the fragment reads of step s+1,
+    //                     the second half's with direct-to-LDS loads of slab kt+NST-1 (ISSUE);
+    //   last step: a quarter of the MFMAs, then wait for this wavefront's share of slab kt+1 and meet the
+    //              workgroup (slab kt+1 is published, stage kt%NST is free for the next iteration),
+    //              then the other MFMAs, interleaved with the first fragment reads of slab kt+1.
+    // ISSUE / NEXT / PAR (buffer of the slab's first A fragments) / COPY (hand the next slab its A fragments in buffer 0) are
+    // literal constants at every expansion.
+#define SPTS_SLAB(kt_, ISSUE, NEXT, WAITN, PAR, COPY)                                                        \
     {                                                                                                        \
         const int st_ = (kt_) % NST;                                                                         \
-        _Pragma("unroll") for (int ks = 0; ks + 1 < KSTEPS; ++ks) {                                          \
-            const int fb = ks & 1;                                                                           \
-            SPTS_LOAD_FRAGS(fb ^ 1, st_, ks + 1)                                                             \
-            _Pragma("unroll") for (int m_ = 0; m_ < HS; ++m_) SPTS_MFMA(fb, m_ / 4, m_ % 4)                  \
-            SPTS_INTERLEAVE_READS                                                                            \
+        _Pragma("unroll") for (int s_ = 0; s_ + 1 < STEPS; ++s_) {                                           \
+            const int ab_ = ((s_ >> 1) + (PAR)) & 1;                                                         \
+            if (s_ & 1) { SPTS_LOAD_A(ab_ ^ 1, st_, (s_ + 1) >> 1) SPTS_LOAD_B(0, st_, (s_ + 1) >> 1) }      \
+            else { SPTS_LOAD_B(1, st_, s_ >> 1) SPTS_LOAD_A1(st_, s_ >> 1) }                                 \
+            _Pragma("unroll") for (int m_ = 0; m_ < HS; ++m_) SPTS_MFMA(ab_, s_ & 1, m_)                     \
+            if (s_ & 1) {                                                                                    \
+                _Pragma("unroll") for (int g_ = 0; g_ < HS; ++g_) {                                          \
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
+                    __builtin_amdgcn_sched_group_barrier(0x100, (NR_EVEN + HS - 1) / HS, 0);                 \
+                }                                                                                            \
+            } else {                                                                                         \
+                _Pragma("unroll") for (int g_ = 0; g_ < HS; ++g_) {                                          \
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
+                    __builtin_amdgcn_sched_group_barrier(0x100, (NR_ODD + HS - 1) / HS, 0);                  \
+                }                                                                                            \
+            }                                                                                                \
             __builtin_amdgcn_sched_barrier(0);                                                               \
             _Pragma("unroll") for (int m_ = HS; m_ < NM; ++m_) {                                             \
-                SPTS_MFMA(fb, m_ / 4, m_ % 4)                                                                \
+                SPTS_MFMA(ab_, s_ & 1, m_)                                                                   \
                 if (ISSUE) {                                                                                 \
-                    const int u_ = ks * HS + m_ - HS;                                                        \
+                    const int u_ = s_ * HS + m_ - HS;                                                        \
                     __builtin_amdgcn_sched_barrier(0);                                                       \
                     if (u_ < PER) SPTS_DMA_ONE((kt_) + NST - 1, (u_ < PER ? u_ : 0))                         \
-                    if (KSTEPS == 2 && u_ + HS < PER) SPTS_DMA_ONE((kt_) + NST - 1, (u_ + HS < PER ? u_ + HS : 0)) \
                     __builtin_amdgcn_sched_barrier(0);                                                       \
                 }                                                                                            \
             }                                                                                                \
         }                                                                                                    \
         {                                                                                                    \
-            constexpr int fb = (KSTEPS - 1) & 1;                                                             \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j) SPTS_MFMA(fb, 0, j)                                \
+            const int ab_ = (((STEPS - 1) >> 1) + (PAR)) & 1;                                                \
+            _Pragma("unroll") for (int m_ = 0; m_ < NM / 4; ++m_) SPTS_MFMA(ab_, 1, m_)                      \
             if (NEXT) { SPTS_WAIT_VMCNT(WAITN); }                                                            \
             __syncthreads();                                                                                 \
-            if (NEXT) { SPTS_LOAD_FRAGS(fb ^ 1, ((kt_) + 1) % NST, 0) }                                      \
-            _Pragma("unroll") for (int i = 1; i < MI; ++i)                                                   \
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) SPTS_MFMA(fb, i, j)                            \
+            if (NEXT) { SPTS_LOAD_A(ab_ ^ 1, ((kt_) + 1) % NST, 0) SPTS_LOAD_B(0, ((kt_) + 1) % NST, 0) }    \
+            _Pragma("unroll") for (int m_ = NM / 4; m_ < NM; ++m_) SPTS_MFMA(ab_, 1, m_)                     \
             if (NEXT) {                                                                                      \
-                _Pragma("unroll") for (int g_ = 0; g_ < NM - 4; ++g_) {                                      \
+                _Pragma("unroll") for (int g_ = 0; g_ < NM - NM / 4; ++g_) {                                 \
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
-                    __builtin_amdgcn_sched_group_barrier(0x100, (NREADS + NM - 5) / (NM - 4), 0);            \
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                       \
                 }                                                                                            \
             }                                                                                                \
             __builtin_amdgcn_sched_barrier(0);                                                               \
+            if (NEXT && (COPY) && ab_ == 0) {                                                                \
+                _Pragma("unroll") for (int i = 0; i < MI; ++i) af[0][i] = af[1][i];                          \
+            }                                                                                                \
         }                                                                                                    \
     }
 
@@ -315,17 +330,17 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     if (SPTS_GEMM_UNROLL_RING && (NST & (NST - 1)) == 0) {
         int kb = 0;
         for (; kb * NST + 2 * NST - 2 < nk; ++kb) {
-            _Pragma("unroll") for (int u = 0; u < NST; ++u) SPTS_SLAB(kb * NST + u, true, true, (NST - 2) * PER)
+            _Pragma("unroll") for (int u = 0; u < NST; ++u) SPTS_SLAB(kb * NST + u, true, true, (NST - 2) * PER, STEPS == 2 ? (u & 1) : 0, false)
         }
         kt = kb * NST;
     }
-    for (; kt + NST - 1 < nk; ++kt) SPTS_SLAB(kt, true, true, (NST - 2) * PER)
+    for (; kt + NST - 1 < nk; ++kt) SPTS_SLAB(kt, true, true, (NST - 2) * PER, 0, true)
     // drain: nothing left to issue; wait for everything that is still in flight
-    for (; kt + 1 < nk; ++kt) SPTS_SLAB(kt, false, true, 0)
-    SPTS_SLAB(kt, false, false, 0)
+    for (; kt + 1 < nk; ++kt) SPTS_SLAB(kt, false, true, 0, 0, true)
+    SPTS_SLAB(kt, false, false, 0, 0, true)
 
-    // ---- epilogue.  acc[i][j][r]: row = row0 + wm*WROWS + i*32 + l32,
-    //      column (inside N block j) = 8*(r/4) + 4*lh + r%4  -> 4 consecutive columns per r/4.
+    // ---- epilogue.  acc[i][j][r]: row = row0 + wm*WROWS + i*16 + l16, column (inside the wavefront's share) =
+    //      16*j + 4*lq + r  -> 4 consecutive columns per block.
     bf16_t* Cb = (bf16_t*)a.C;
     if (partial) {
         // raw fp32 accumulators in fragment order: every store instruction of a wavefront writes 1 KB
@@ -333,12 +348,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    *reinterpret_cast<f32x4*>(P + ((((wave * MI + i) * 4 + j) * 4 + q) * 64 + lane) * 4) = v;
-                }
+            for (int j = 0; j < 8; ++j) *reinterpret_cast<f32x4*>(P + (((wave * MI + i) * 8 + j) * 64 + lane) * 4) = acc[i][j];
         return;
     }
     if (EPI == EPI_SUMSQ) {
@@ -346,12 +356,13 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
         for (int i = 0; i < MI; ++i) {
             float s = 0.f;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 8; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s += acc[i][j][r] * acc[i][j][r];
+                for (int r = 0; r < 4; ++r) s += acc[i][j][r] * acc[i][j][r];
+            s += __shfl_xor(s, 16);
             s += __shfl_xor(s, 32);
-            int64_t grow = row0 + wm * WROWS + i * 32 + l32;
-            if (lh == 0 && grow < a.M) a.part[grow * a.part_ld + tn * 2 + wn] = s;
+            int64_t grow = row0 + wm * WROWS + i * 16 + l16;
+            if (lq == 0 && grow < a.M) a.part[grow * a.part_ld + tn * 2 + wn] = s;
         }
         return;
     }
@@ -370,126 +381,87 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     };
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        const int tr = wm * WROWS + i * 32 + l32;
+        const int tr = wm * WROWS + i * 16 + l16;
         const int64_t grow = row0 + tr;
         const bool rok = grow < a.M;
         const int64_t growc = rok ? grow : a.M - 1;
         const int64_t crow = a.c_idx ? (int64_t)a.c_idx[growc] : growc;
         if (EPI == EPI_STORE || (SEG && second)) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int cb = col0 - colshift + wn * 128 + j * 32 + 4 * lh;   // column of this product's output
+            for (int j = 0; j < 8; ++j) {
+                const int cb = col0 - colshift + wn * 128 + j * 16 + 4 * lq;   // column of this product's output
+                uint2 o;
+                o.x = pack_bf16x2(acc[i][j][0], acc[i][j][1]);
+                o.y = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
+                stage(tr, cb - (col0 - colshift), o);
+                if (a.Ct && grow < a.ldct) {
+                    bf16_t* ct = (bf16_t*)a.Ct;
+                    const uint16_t e[4] = {(uint16_t)(o.x & 0xffff), (uint16_t)(o.x >> 16), (uint16_t)(o.y & 0xffff), (uint16_t)(o.y >> 16)};
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    uint2 o;
-                    o.x = pack_bf16x2(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
-                    o.y = pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                    stage(tr, cb - (col0 - colshift) + 8 * q, o);
-                    if (a.Ct && grow < a.ldct) {
-                        bf16_t* ct = (bf16_t*)a.Ct;
-                        const uint16_t e[4] = {(uint16_t)(o.x & 0xffff), (uint16_t)(o.x >> 16), (uint16_t)(o.y & 0xffff), (uint16_t)(o.y >> 16)};
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) ct[(int64_t)(cb + 8 * q + t) * a.ldct + vt_key_slot(grow)].v = e[t];
-                    }
+                    for (int t = 0; t < 4; ++t) ct[(int64_t)(cb + t) * a.ldct + vt_key_slot(grow)].v = e[t];
                 }
             }
         } else if (EPI == EPI_RESIDUAL) {
             // the old values are read in the fragment layout (rows past M read the last row; they are not
             // stored): one rounding of old + acc, as without the staging
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int cb = col0 + wn * 128 + j * 32 + 4 * lh;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint2 old = *reinterpret_cast<const uint2*>(Cb + crow * a.ldc + cb + 8 * q);
-                    float x0 = __uint_as_float(old.x << 16), x1 = __uint_as_float(old.x & 0xffff0000u);
-                    float x2 = __uint_as_float(old.y << 16), x3 = __uint_as_float(old.y & 0xffff0000u);
-                    uint2 o;
-                    o.x = pack_bf16x2(x0 + acc[i][j][4 * q], x1 + acc[i][j][4 * q + 1]);
-                    o.y = pack_bf16x2(x2 + acc[i][j][4 * q + 2], x3 + acc[i][j][4 * q + 3]);
-                    stage(tr, cb - col0 + 8 * q, o);
-                }
+            for (int j = 0; j < 8; ++j) {
+                const int cb = col0 + wn * 128 + j * 16 + 4 * lq;
+                const uint2 old = *reinterpret_cast<const uint2*>(Cb + crow * a.ldc + cb);
+                float x0 = __uint_as_float(old.x << 16), x1 = __uint_as_float(old.x & 0xffff0000u);
+                float x2 = __uint_as_float(old.y << 16), x3 = __uint_as_float(old.y & 0xffff0000u);
+                uint2 o;
+                o.x = pack_bf16x2(x0 + acc[i][j][0], x1 + acc[i][j][1]);
+                o.y = pack_bf16x2(x2 + acc[i][j][2], x3 + acc[i][j][3]);
+                stage(tr, cb - col0, o);
             }
         } else if (EPI == EPI_SILU_MUL_T) {
             // channel-major: staged channel c keeps the 16-byte chunk (8 rows) r at chunk position r ^ (c % 32), which spreads the
             // 2-byte writes of a lane's four channels and the whole-channel reads over the banks
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int c = wn * 64 + j * 32 + 4 * lh + 8 * (r >> 2) + (r & 3);
+                for (int r = 0; r < 4; ++r) {
+                    const int c = wn * 64 + j * 16 + 4 * lq + r;
                     *reinterpret_cast<bf16_t*>(smem + c * 512 + ((((tr >> 3) ^ c) & 31) << 4) + ((tr & 7) << 1)) =
-                        f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
+                        f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 4][r]);
                 }
         } else if (EPI == EPI_SILU_MUL) {
-            {
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int cb = col0 + wn * 64 + j * 32 + 4 * lh;
+            for (int j = 0; j < 4; ++j) {
+                float h[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float h0 = silu_f(acc[i][j][4 * q]) * acc[i][j + 2][4 * q];
-                        float h1 = silu_f(acc[i][j][4 * q + 1]) * acc[i][j + 2][4 * q + 1];
-                        float h2 = silu_f(acc[i][j][4 * q + 2]) * acc[i][j + 2][4 * q + 2];
-                        float h3 = silu_f(acc[i][j][4 * q + 3]) * acc[i][j + 2][4 * q + 3];
-                        uint2 o; o.x = pack_bf16x2(h0, h1); o.y = pack_bf16x2(h2, h3);
-                        stage(tr, cb - col0 + 8 * q, o);
-                    }
-                }
+                for (int t = 0; t < 4; ++t) h[t] = silu_f(acc[i][j][t]) * acc[i][j + 4][t];
+                uint2 o; o.x = pack_bf16x2(h[0], h[1]); o.y = pack_bf16x2(h[2], h[3]);
+                stage(tr, wn * 64 + j * 16 + 4 * lq, o);
             }
         } else if (EPI == EPI_ROPE || SEG) {
-            {
-                const int64_t trow = a.rope_idx ? (int64_t)a.rope_idx[growc] : growc;
-                const int half = a.head_dim >> 1;
-                const float2* tab = a.rope + trow * half;
-                const float rs = a.rope_scale != 0.f ? a.rope_scale : 1.f;
-                if (half == 64) {
-                    // wavefront = one head of 128 columns: blocks (0,2) and (1,3) are d/2 apart
+            const int64_t trow = a.rope_idx ? (int64_t)a.rope_idx[growc] : growc;
+            const int half = a.head_dim >> 1;
+            const float2* tab = a.rope + trow * half;
+            const float rs = a.rope_scale != 0.f ? a.rope_scale : 1.f;
+            // blocks j1 and j2 are d/2 columns apart; jj: the quad's first column inside the half head
+            auto rotate = [&](int j1, int j2, int jj) {
+                float lo[4], hi[4];
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const int jj = j * 32 + 4 * lh;
-                        const int cb = col0 + wn * 128 + jj;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            float lo[4], hi[4];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                float2 cs = tab[jj + 8 * q + t];
-                                float x1 = acc[i][j][4 * q + t], x2 = acc[i][j + 2][4 * q + t];
-                                lo[t] = (x1 * cs.x - x2 * cs.y) * rs;
-                                hi[t] = (x2 * cs.x + x1 * cs.y) * rs;
-                            }
-                            uint2 o1, o2;
-                            o1.x = pack_bf16x2(lo[0], lo[1]); o1.y = pack_bf16x2(lo[2], lo[3]);
-                            o2.x = pack_bf16x2(hi[0], hi[1]); o2.y = pack_bf16x2(hi[2], hi[3]);
-                            stage(tr, cb - col0 + 8 * q, o1);
-                            stage(tr, cb - col0 + 64 + 8 * q, o2);
-                        }
-                    }
-                } else {
-                    // d = 64: two heads per wavefront; blocks (0,1) and (2,3) are d/2 = 32 apart
-#pragma unroll
-                    for (int hh = 0; hh < 2; ++hh) {
-                        const int jj = 4 * lh;
-                        const int cb = col0 + wn * 128 + hh * 64 + jj;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            float lo[4], hi[4];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                float2 cs = tab[jj + 8 * q + t];
-                                float x1 = acc[i][2 * hh][4 * q + t], x2 = acc[i][2 * hh + 1][4 * q + t];
-                                lo[t] = (x1 * cs.x - x2 * cs.y) * rs;
-                                hi[t] = (x2 * cs.x + x1 * cs.y) * rs;
-                            }
-                            uint2 o1, o2;
-                            o1.x = pack_bf16x2(lo[0], lo[1]); o1.y = pack_bf16x2(lo[2], lo[3]);
-                            o2.x = pack_bf16x2(hi[0], hi[1]); o2.y = pack_bf16x2(hi[2], hi[3]);
-                            stage(tr, cb - col0 + 8 * q, o1);
-                            stage(tr, cb - col0 + 32 + 8 * q, o2);
-                        }
-                    }
+                for (int t = 0; t < 4; ++t) {
+                    float2 cs = tab[jj + t];
+                    float x1 = acc[i][j1][t], x2 = acc[i][j2][t];
+                    lo[t] = (x1 * cs.x - x2 * cs.y) * rs;
+                    hi[t] = (x2 * cs.x + x1 * cs.y) * rs;
                 }
+                uint2 o1, o2;
+                o1.x = pack_bf16x2(lo[0], lo[1]); o1.y = pack_bf16x2(lo[2], lo[3]);
+                o2.x = pack_bf16x2(hi[0], hi[1]); o2.y = pack_bf16x2(hi[2], hi[3]);
+                stage(tr, wn * 128 + j1 * 16 + 4 * lq, o1);
+                stage(tr, wn * 128 + j2 * 16 + 4 * lq, o2);
+            };
+            if (half == 64) {   // wavefront = one head of 128 columns
+#pragma unroll
+                for (int j = 0; j < 4; ++j) rotate(j, j + 4, j * 16 + 4 * lq);
+            } else {            // d = 64: two heads per wavefront
+#pragma unroll
+                for (int j = 0; j < 4; ++j) rotate((j >> 1) * 4 + (j & 1), (j >> 1) * 4 + (j & 1) + 2, (j & 1) * 16 + 4 * lq);
             }
         }
     }
@@ -601,20 +573,20 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
 //      single-pass kernel does.  For EPI_ROPE a thread owns the quad and its partner d/2 columns on.
 template <int NW>
 __global__ void __launch_bounds__(256) splitk_finish_kernel(GemmArgs a, int nM, int nN, int nfull) {
-    constexpr int MI = 16 / NW, WROWS = 32 * MI;
+    constexpr int MI = 32 / NW, WROWS = 16 * MI;
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int rt = (int)(g >> 14);                 // split tile (16384 quads per tile)
     const int v = (int)(g & 16383);
-    const int lane = v & 63, q = (v >> 6) & 3, j = (v >> 8) & 3, wi = v >> 10;
+    const int lane = v & 63, j = (v >> 6) & 7, wi = v >> 9;
     const int wave = wi / MI, i = wi % MI;
-    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lh = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lq = lane >> 4;
     int tm, tn;
     tile_of(nfull + rt, nM, nN, tm, tn);
-    const int64_t grow = (int64_t)tm * BM + wm * WROWS + i * 32 + l32;
+    const int64_t grow = (int64_t)tm * BM + wm * WROWS + i * 16 + l16;
     const int col0 = tn * 256;
     const float* P = a.part32 + (int64_t)rt * a.ksplit * (BM * 256);
     auto quad = [&](int jj) {
-        const float* p = P + ((((wave * MI + i) * 4 + jj) * 4 + q) * 64 + lane) * 4;
+        const float* p = P + (((wave * MI + i) * 8 + jj) * 64 + lane) * 4;
         f32x4 s = {0.f, 0.f, 0.f, 0.f};
         for (int sp = 0; sp < a.ksplit; ++sp) s += *reinterpret_cast<const f32x4*>(p + (int64_t)sp * (BM * 256));
         return s;
@@ -632,7 +604,7 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(GemmArgs a, int nM, 
     }
     if (epi == EPI_STORE) {
         const f32x4 s = quad(j);
-        const int col = col0 - colshift + wn * 128 + j * 32 + 4 * lh + 8 * q;
+        const int col = col0 - colshift + wn * 128 + j * 16 + 4 * lq;
         u32x2 o = {pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w)};
         if (rok) {
             if (a.c_slab) *reinterpret_cast<u32x2*>(Cb + ((int64_t)(col >> 5) * a.M + grow) * 32 + (col & 31)) = o;   // slab-major C
@@ -647,7 +619,7 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(GemmArgs a, int nM, 
     } else if (epi == EPI_RESIDUAL) {
         if (!rok) return;
         const f32x4 s = quad(j);
-        const int col = col0 + wn * 128 + j * 32 + 4 * lh + 8 * q;
+        const int col = col0 + wn * 128 + j * 16 + 4 * lq;
         u32x2* p = reinterpret_cast<u32x2*>(Cb + crow * a.ldc + col);
         const u32x2 old = *p;
         u32x2 o;
@@ -658,8 +630,8 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(GemmArgs a, int nM, 
         if (!rok) return;
         const int half = a.head_dim >> 1;
         int j1, j2, jj;   // accumulator blocks of the quad and of its partner; column inside the half head
-        if (half == 64) { if (j >= 2) return; j1 = j; j2 = j + 2; jj = j * 32 + 4 * lh + 8 * q; }
-        else { if (j & 1) return; j1 = j; j2 = j + 1; jj = 4 * lh + 8 * q; }
+        if (half == 64) { if (j >= 4) return; j1 = j; j2 = j + 4; jj = j * 16 + 4 * lq; }
+        else { if (j & 2) return; j1 = j; j2 = j + 2; jj = (j & 1) * 16 + 4 * lq; }
         const f32x4 x1 = quad(j1), x2 = quad(j2);
         const int64_t trow = a.rope_idx ? (int64_t)a.rope_idx[grow] : grow;
         const float2* tab = a.rope + trow * half + jj;
@@ -671,7 +643,7 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(GemmArgs a, int nM, 
             lo[t] = (x1[t] * cs.x - x2[t] * cs.y) * rs;
             hi[t] = (x2[t] * cs.x + x1[t] * cs.y) * rs;
         }
-        const int col = col0 + wn * 128 + (half == 64 ? 0 : (j >> 1) * 64) + jj;
+        const int col = col0 + wn * 128 + (half == 64 ? 0 : (j >> 2) * 64) + jj;
         u32x2 o1 = {pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
         u32x2 o2 = {pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3])};
         *reinterpret_cast<u32x2*>(Cb + crow * a.ldc + col) = o1;
