@@ -1,7 +1,7 @@
 // bf16 matrix-core GEMM for products that leave the 256x256 tiles of kernels_gemm_mfma.hip short of work: few rows (a short
 // prompt, the probe queries, one request's active rows) or few columns (K projection, proxy factors).
 //
-//  * TM x 128 output tile (TM = 64, 128 or 192), 4 wavefronts (2x2) of TM/2 x 64 = (TM/64) x 2 MFMA 32x32x16 blocks.  32 / 64 / 96
+//  * TM x 128 output tile (TM = 64, 128 or 192), 4 wavefronts (2x2) of TM/2 x 64 = (TM/32) x 4 MFMA 16x16x32 blocks.  32 / 64 / 96
 //    accumulators per lane and a ring of 48 / 80 / 80 KB let two or three workgroups share a CU, which hides one's barriers,
 //    fragment reads and epilogue behind the other's MFMAs; per flop it moves twice the operand bytes of the 256x256 tile, so it
 //    pays only where that one leaves CUs idle or multiplies padding (the rule: gemm_small_plan).
@@ -10,7 +10,7 @@
 //    Slab-major operands as in kernels_gemm_mfma.hip (whole lines per load instruction), same swizzle, same LDS image.
 //  * Split-K: `ksplit` workgroups share a tile, each leaves its raw fp32 accumulators (fragment order: every store is 1 KB),
 //    small_finish_kernel sums them in split order and applies the epilogue.
-//  * Column blocks of a wavefront: wavefront column wn, block j covers tile columns j * 64 + wn * 32 (or wn * 64 + j * 32 for
+//  * 32-wide column blocks of a wavefront: wavefront column wn, block j covers tile columns j * 64 + wn * 32 (or wn * 64 + j * 32 for
 //    rotary heads of 64), so that block 0 and block 1 are the two members of a rotary pair, or gate and up of a channel: the
 //    dual epilogues combine registers of one lane, also in the finish kernel.
 //
@@ -22,7 +22,6 @@
 namespace spts {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SBN = 128;        // tile columns (weight rows)
@@ -59,9 +58,9 @@ __device__ __forceinline__ void small_tile_of(int id, int nM, int nN, int& tm, i
     tn = in_g / gsz;
 }
 
-// the two finished quads (block j = 0, 1; columns tile_col(j) .. + 3) of output row grow -> bf16 pairs; returns how many quads
+// the two finished quads (block j = 0, 1; columns cq .. cq + 3 of the block) of output row grow -> bf16 pairs; returns how many quads
 // there are (dual epilogues: SiLU leaves one)
-__device__ __forceinline__ void small_epilogue(const GemmArgs& a, const SmallTile& t, int wn, int lh, int q, int64_t growc, int64_t crow,
+__device__ __forceinline__ void small_epilogue(const GemmArgs& a, const SmallTile& t, int wn, int cq, int64_t growc, int64_t crow,
                                                f32x4 v0, f32x4 v1, u32x2& o0, u32x2& o1) {
     if (a.epi == EPI_SILU_MUL) {
         float h[4];
@@ -72,7 +71,7 @@ __device__ __forceinline__ void small_epilogue(const GemmArgs& a, const SmallTil
     }
     if (t.rope) {
         const int64_t trow = a.rope_idx ? (int64_t)a.rope_idx[growc] : growc;
-        const int jj = (a.head_dim == 128 ? wn * 32 : 0) + 4 * lh + 8 * q;
+        const int jj = (a.head_dim == 128 ? wn * 32 : 0) + cq;
         const float2* tab = a.rope + trow * (a.head_dim >> 1) + jj;
         const float rs = a.rope_scale != 0.f ? a.rope_scale : 1.f;
         float lo[4], hi[4];
@@ -87,7 +86,7 @@ __device__ __forceinline__ void small_epilogue(const GemmArgs& a, const SmallTil
         return;
     }
     if (a.epi == EPI_RESIDUAL) {   // one rounding of old + sum
-        const bf16_t* c = (const bf16_t*)a.C + crow * a.ldc + t.col0 + wn * t.wstride + 4 * lh + 8 * q;
+        const bf16_t* c = (const bf16_t*)a.C + crow * a.ldc + t.col0 + wn * t.wstride + cq;
         const u32x2 p0 = *reinterpret_cast<const u32x2*>(c), p1 = *reinterpret_cast<const u32x2*>(c + t.jstride);
         v0 += f32x4{__uint_as_float(p0[0] << 16), __uint_as_float(p0[0] & 0xffff0000u), __uint_as_float(p0[1] << 16), __uint_as_float(p0[1] & 0xffff0000u)};
         v1 += f32x4{__uint_as_float(p1[0] << 16), __uint_as_float(p1[0] & 0xffff0000u), __uint_as_float(p1[1] << 16), __uint_as_float(p1[1] & 0xffff0000u)};
@@ -123,7 +122,7 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lh = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lq = lane >> 4;
     const int64_t row0 = (int64_t)tm * TM;
 
     // ---- load addresses: a wavefront-uniform base advanced along K plus a fixed 32-bit lane offset
@@ -167,13 +166,13 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
         for (int q = 0; q < LA; ++q) dma16s(oa[q], abase + ks * a_kstep, lds_a + stage * STAGE + q * 1024);
     };
 
-    f32x16 acc[MI][2];
+    f32x4 acc[MI][2][4];   // 32x32 block (i, j): quarter q = rows 16 * (q / 2), columns 16 * (q % 2)
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int npre = nk < NST - 1 ? nk : NST - 1;
     for (int t = 0; t < npre; ++t) issue(t, t);
@@ -186,17 +185,15 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
         if (ISSUE) issue((kt_) + NST - 1, ((st_) + NST - 1) % NST);                                                  \
         const char* sa_ = smem + (st_) * STAGE;                                                                      \
         const char* sb_ = sa_ + A_BYTES;                                                                             \
-        bf16x8 fa_[2][MI], fb_[2][2];                                                                                \
-        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {                                                           \
-            _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                           \
-                fa_[ks][i] = *reinterpret_cast<const bf16x8*>(sa_ + small_off(wm * (TM / 2) + i * 32 + l32, 2 * ks + lh)); \
-            _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                            \
-                fb_[ks][j] = *reinterpret_cast<const bf16x8*>(sb_ + small_off(j * st.jstride + wn * st.wstride + l32, 2 * ks + lh)); \
-        }                                                                                                            \
-        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                             \
-            _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                           \
-                _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                        \
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb_[ks][j], fa_[ks][i], acc[i][j], 0, 0, 0); \
+        bf16x8 fa_[2 * MI], fb_[4];                                                                                  \
+        _Pragma("unroll") for (int i = 0; i < 2 * MI; ++i)                                                           \
+            fa_[i] = *reinterpret_cast<const bf16x8*>(sa_ + small_off(wm * (TM / 2) + i * 16 + l16, lq));            \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                                \
+            fb_[j] = *reinterpret_cast<const bf16x8*>(sb_ + small_off((j >> 1) * st.jstride + wn * st.wstride + (j & 1) * 16 + l16, lq)); \
+        _Pragma("unroll") for (int i = 0; i < 2 * MI; ++i)                                                           \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                            \
+                acc[i >> 1][j >> 1][(i & 1) * 2 + (j & 1)] =                                                         \
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb_[j], fa_[i], acc[i >> 1][j >> 1][(i & 1) * 2 + (j & 1)], 0, 0, 0); \
     }
     int kt = 0;
     for (; kt + 2 * NST - 2 < nk; kt += NST) {   // ring stages are constants here
@@ -206,7 +203,7 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
     for (; kt + NST - 1 < nk; ++kt) SPTS_SMALL_SLAB(kt, kt % NST, NST - 2, true)
     for (; kt < nk; ++kt) SPTS_SMALL_SLAB(kt, kt % NST, 0, false)
 
-    // ---- lane: output row l32 of its block, columns 8 * q + 4 * lh + e of blocks j = 0, 1
+    // ---- lane: output row l16 of its quarter block, columns 4 * lq + e
     if (ksplit > 1) {
         float* P = a.part32 + ((int64_t)split * tiles + id) * (TM * SBN);
 #pragma unroll
@@ -214,10 +211,7 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    *reinterpret_cast<f32x4*>(P + ((((wave * MI + i) * 2 + j) * 4 + q) * 64 + lane) * 4) = v;
-                }
+                for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(P + ((((wave * MI + i) * 2 + j) * 4 + q) * 64 + lane) * 4) = acc[i][j][q];
         return;
     }
     // staged through LDS (the ring is free once every wavefront is past its last fragment read) so that the tile leaves in
@@ -226,20 +220,20 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
     const bool silu = silu_b;
     const int nch = silu ? 8 : 16;               // chunks per staged row
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-        const int tr = wm * (TM / 2) + i * 32 + l32;
+    for (int i = 0; i < 2 * MI; ++i) {
+        const int tr = wm * (TM / 2) + i * 16 + l16;
         const int64_t grow = row0 + tr;
         const int64_t growc = grow < a.M ? grow : a.M - 1;
         const int64_t crow = a.c_idx ? (int64_t)a.c_idx[growc] : growc;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int h = 0; h < 2; ++h) {
+            const int q = (i & 1) * 2 + h, cq = h * 16 + 4 * lq;
             u32x2 o[2];
-            small_epilogue(a, st, wn, lh, q, growc, crow, f32x4{acc[i][0][4 * q], acc[i][0][4 * q + 1], acc[i][0][4 * q + 2], acc[i][0][4 * q + 3]},
-                           f32x4{acc[i][1][4 * q], acc[i][1][4 * q + 1], acc[i][1][4 * q + 2], acc[i][1][4 * q + 3]}, o[0], o[1]);
+            small_epilogue(a, st, wn, cq, growc, crow, acc[i >> 1][0][q], acc[i >> 1][1][q], o[0], o[1]);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 if (silu && j == 1) continue;
-                const int tc = j * st.jstride + wn * st.wstride + 4 * lh + 8 * q;
+                const int tc = j * st.jstride + wn * st.wstride + cq;
                 *reinterpret_cast<u32x2*>(smem + tr * (nch * 16) + ((((tc >> 3) ^ tr) & (nch - 1)) << 4) + ((tc & 4) << 1)) = o[j];
                 if (a.Ct && !st.rope && grow < a.ldct) small_store_ct(a, st.col0 - (second ? a.n_split : 0) + tc, grow, o[j]);
             }
@@ -274,12 +268,13 @@ __global__ void __launch_bounds__(256) small_finish_kernel(GemmArgs a, int nM, i
     const int id = (int)(g / QPT), v = (int)(g % QPT);
     const int lane = v & 63, q = (v >> 6) & 3, wi = v >> 8;
     const int wave = wi / MI, i = wi % MI;
-    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lh = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lq = lane >> 4;
     const int tiles = nM * nN;
     int tm, tn;
     small_tile_of(id, nM, nN, tm, tn);
     const SmallTile st = small_tile(a, tn);
-    const int64_t grow = (int64_t)tm * TM + wm * (TM / 2) + i * 32 + l32;
+    const int64_t grow = (int64_t)tm * TM + wm * (TM / 2) + i * 32 + (q >> 1) * 16 + l16;
+    const int cq = (q & 1) * 16 + 4 * lq;
     const bool rok = grow < a.M;
     if (!rok && !(a.Ct && !st.rope && grow < a.ldct)) return;
     const float* P = a.part32 + (int64_t)id * (TM * SBN) + (((wave * MI + i) * 2 * 4 + q) * 64 + lane) * 4;
@@ -293,13 +288,13 @@ __global__ void __launch_bounds__(256) small_finish_kernel(GemmArgs a, int nM, i
     const int64_t growc = rok ? grow : a.M - 1;
     const int64_t crow = a.c_idx ? (int64_t)a.c_idx[growc] : growc;
     u32x2 o[2];
-    small_epilogue(a, st, wn, lh, q, growc, crow, s0, s1, o[0], o[1]);
+    small_epilogue(a, st, wn, cq, growc, crow, s0, s1, o[0], o[1]);
     bf16_t* Cb = (bf16_t*)(st.second ? a.C2 : a.C);
     const int64_t ldo = st.second ? a.ldc2 : a.ldc;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         if (a.epi == EPI_SILU_MUL && j == 1) continue;
-        const int col = st.col0 - (st.second ? a.n_split : 0) + j * st.jstride + wn * st.wstride + 4 * lh + 8 * q;
+        const int col = st.col0 - (st.second ? a.n_split : 0) + j * st.jstride + wn * st.wstride + cq;
         if (rok) {
             if (a.c_slab) *reinterpret_cast<u32x2*>(Cb + ((int64_t)(col >> 5) * a.M + grow) * 32 + (col & 31)) = o[j];
             else *reinterpret_cast<u32x2*>(Cb + crow * ldo + col) = o[j];

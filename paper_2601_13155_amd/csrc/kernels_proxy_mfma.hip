@@ -5,18 +5,16 @@
 // quarter-rate transcendentals per element) takes about as much vector time as the 8 slabs take matrix time, one after
 // the other.  This kernel turns the loops around:
 //  * A wavefront owns 32 rows and keeps their t_g / t_u fragments in registers for its whole life (B operand of
-//    h^T = V t^T: 16 k-steps x 2 x 4 registers = 128); a workgroup = 8 wavefronts = 256 rows.
+//    h^T = V t^T, 16x16x32: 2 row blocks x 8 k-steps x 2 x 4 registers = 128); a workgroup = 8 wavefronts = 256 rows.
 //  * The workgroup streams its share of the channels in tiles of 32 (Vg and Vu rows, 32 KB per tile for r = 256) through a
 //    4-stage direct-to-LDS ring shared by the 8 wavefronts (tiles are published in pairs: one barrier per two tiles); per
-//    tile a wavefront issues 32 MFMAs (one LDS fragment each).
+//    tile a wavefront issues 64 MFMAs (two per LDS fragment).
 //  * Two accumulator sets alternate: while the matrix pipe works on tile c, the vector ALU takes SiLU(gate) * up of tile
-//    c - 1, packs it to bf16 and stores it -- written as 16 steps of two MFMAs + one element's arithmetic, fenced for the
+//    c - 1, packs it to bf16 and stores it -- written as 16 steps of four MFMAs + one element's arithmetic, fenced for the
 //    scheduler, so the two kinds of work are offered to the SIMD side by side.
-//  * The rows of a weight tile are put into LDS with the two middle quads of every 16 swapped (vt_key_slot): the
-//    accumulator layout of the 32x32 MFMA then gives a lane 2 x 8 consecutive channels, and one exchange between the lane
-//    halves (v_permlane32_swap) makes that 16 consecutive channels = 32 contiguous bytes of its row, stored as two 16-byte
-//    pieces; the wavefront's 32 rows x 64 bytes are one contiguous 2 KB of the slab-major output.  (Passing the tile
-//    through LDS to store whole 1 KB runs per instruction measured 4 % slower: the round trip sits at the end of a tile.)
+//  * LDS row 16 * cb + 4 * q + t of a weight tile holds channel 8 * q + 4 * cb + t: the accumulators of the two channel blocks
+//    cb then give a lane 8 consecutive channels of its row, and the 16-byte pieces of a wavefront's 16 rows x 64 bytes are 1 KB of
+//    whole lines per store instruction.
 //  * Output: h slab-major [Dlow/32][N][32], the layout the following projection GEMM reads as whole lines.
 //  * Grid: (row tiles of 256) x (channel shares); the share count is chosen so that the workgroups fill whole rounds of the
 //    256 CUs.  Workgroups of one XCD take neighbouring ids, i.e. mostly the same channel share: its weights stay in that L2.
@@ -26,7 +24,7 @@
 namespace spts {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int PH_NSTG = 4;          // ring stages (tiles of 32 channels)
 constexpr int PH_WAVES = 8;
@@ -35,15 +33,14 @@ __device__ inline float ph_silu(float g) {
     return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
 }
 
-template <int KS>   // k-steps of 16: r = 16 * KS
+template <int KS>   // k-steps of 32: r = 32 * KS
 __global__ void __launch_bounds__(PH_WAVES * 64) proxy_hidden_kernel(ProxyHiddenArgs a, int RT, int SC) {
-    constexpr int NSL = KS / 2;                   // 32-wide K slabs
+    constexpr int NSL = KS;                       // 32-wide K slabs
     constexpr int MAT_BYTES = NSL * 2048;         // one matrix's tile: [NSL][32 channels][64 bytes]
     constexpr int STAGE = 2 * MAT_BYTES;          // Vg tile + Vu tile
     constexpr int LOADS = 2 * NSL * 2;            // 1 KB loads per tile
     constexpr int LPW = LOADS / PH_WAVES;         // per wavefront
-    constexpr int EPS = 16 / KS;                  // elements of the previous tile finished per k-step
-    static_assert(KS == 16, "r = 256");
+    static_assert(KS == 8, "r = 256");             // 2 * KS steps per tile, one element of the previous tile in each
     extern __shared__ __attribute__((aligned(16))) char smem[];   // the ring: PH_NSTG stages of (Vg tile, Vu tile)
 
     // ---- work unit: (row tile, channel share); ids of one XCD are consecutive
@@ -59,7 +56,7 @@ __global__ void __launch_bounds__(PH_WAVES * 64) proxy_hidden_kernel(ProxyHidden
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, lh = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4;
     const int64_t row0w = (int64_t)rt * 256 + wave * 32;
 
     // ---- direct-to-LDS loads of a weight tile: load q = (matrix X, slab s, 16-row half hf); lane -> (LDS row, chunk position)
@@ -68,7 +65,7 @@ __global__ void __launch_bounds__(PH_WAVES * 64) proxy_hidden_kernel(ProxyHidden
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
         const int m = hf * 16 + (lane >> 2);                 // LDS row of the tile
-        const int ch = (int)vt_key_slot(m);                  // channel (inside the tile) that belongs there
+        const int ch = ((m & 12) << 1) | ((m >> 4) << 2) | (m & 3);   // channel (inside the tile) that belongs there
         const int c = (lane & 3) ^ ((m >> 2) & 3);           // global chunk for this LDS chunk position
         goff[hf] = (uint32_t)(ch * 64 + c * 16);
     }
@@ -91,59 +88,62 @@ __global__ void __launch_bounds__(PH_WAVES * 64) proxy_hidden_kernel(ProxyHidden
         const int npre = ntiles < PH_NSTG ? ntiles : PH_NSTG;
         for (int t = 0; t < npre; ++t) SPTS_PH_DMA(t)
     }
-    bf16x8 tg[KS], tu[KS];
-    {
-        int64_t row = row0w + l32;
+    bf16x8 tg[2][KS], tu[2][KS];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+        int64_t row = row0w + rb * 16 + l16;
         if (row >= a.N) row = a.N - 1;
-        const char* pg = (const char*)a.tg + row * a.t_row_pitch + lh * 16;
-        const char* pu = (const char*)a.tu + row * a.t_row_pitch + lh * 16;
+        const char* pg = (const char*)a.tg + row * a.t_row_pitch + lq * 16;
+        const char* pu = (const char*)a.tu + row * a.t_row_pitch + lq * 16;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const int64_t o = (int64_t)(ks >> 1) * a.t_slab_pitch + (ks & 1) * 32;
-            tg[ks] = *reinterpret_cast<const bf16x8*>(pg + o);
-            tu[ks] = *reinterpret_cast<const bf16x8*>(pu + o);
+            tg[rb][ks] = *reinterpret_cast<const bf16x8*>(pg + ks * a.t_slab_pitch);
+            tu[rb][ks] = *reinterpret_cast<const bf16x8*>(pu + ks * a.t_slab_pitch);
         }
     }
-    // fragment read offsets inside a matrix tile for the two k-steps of a slab
-    uint32_t foff[2];
-#pragma unroll
-    for (int par = 0; par < 2; ++par) foff[par] = (uint32_t)(l32 * 64 + (((2 * par + lh) ^ ((l32 >> 2) & 3)) << 4));
+    // fragment read offset inside a slab of a matrix tile (channel block 1 is 1 KB on)
+    const uint32_t foff = (uint32_t)(l16 * 64 + ((lq ^ ((l16 >> 2) & 3)) << 4));
     char* hp = (char*)a.hp;
-    const int64_t out_off = (row0w + l32) * 64 + lh * 32;   // the lane's 32 bytes inside a slab of the output
-    const bool row_ok = row0w + l32 < a.N;
+    const int64_t out_off = (row0w + l16) * 64 + lq * 16;   // the lane's 16 bytes inside a slab of the output, row block 0
+    const bool row_ok[2] = {row0w + l16 < a.N, row0w + 16 + l16 < a.N};
 
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 Ga = zero16, Ua = zero16, Gb = zero16, Ub = zero16;
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    f32x4 Ga[2][2], Ua[2][2], Gb[2][2], Ub[2][2];   // [channel block][row block]
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) Ga[c][r] = Ua[c][r] = Gb[c][r] = Ub[c][r] = zero4;
 
-    // One tile: 2*KS MFMAs into (GC, UC) from the ring stage of tile tl_, interleaved with the arithmetic of the previous
-    // tile's accumulators (GP, UP), whose packed result is stored at the end (two 16-byte pieces per lane).
-    constexpr int FD = 3;   // fragment reads run FD k-steps ahead (2 and 4 measure the same)
-#define SPTS_PH_FRAG(X_, ks_) (*reinterpret_cast<const bf16x8*>(sT_ + (X_) * MAT_BYTES + ((ks_) >> 1) * 2048 + foff[(ks_) & 1]))
+    // One tile: 8*KS MFMAs into (GC, UC) from the ring stage of tile tl_, interleaved with the arithmetic of the previous
+    // tile's accumulators (GP, UP), whose packed result is stored at the end (one 16-byte piece per lane and row block).
+    // Step i: K piece i / 2, channel block i % 2.
+    constexpr int FD = 3;   // fragment reads run FD steps ahead
+#define SPTS_PH_FRAG(X_, i_) (*reinterpret_cast<const bf16x8*>(sT_ + (X_) * MAT_BYTES + ((i_) >> 1) * 2048 + ((i_) & 1) * 1024 + foff))
+#define SPTS_PH_STORE(tile_, h_)                                                                              \
+    {                                                                                                         \
+        _Pragma("unroll") for (int rb_ = 0; rb_ < 2; ++rb_) {                                                 \
+            u32x4 x_;                                                                                         \
+            _Pragma("unroll") for (int j_ = 0; j_ < 4; ++j_) x_[j_] = cvt_pk_bf16(h_[rb_ * 8 + 2 * j_], h_[rb_ * 8 + 2 * j_ + 1]); \
+            if (row_ok[rb_]) *reinterpret_cast<u32x4*>(hp + (int64_t)(tile_) * a.N * 64 + out_off + rb_ * 1024) = x_; \
+        }                                                                                                     \
+    }
 #define SPTS_PH_TILE(tl_, GC, UC, GP, UP)                                                                      \
     {                                                                                                         \
         const char* sT_ = smem + ((tl_) % PH_NSTG) * STAGE;                                                   \
         const bool prev_ = (tl_) > 0;                                                                         \
         bf16x8 fg_[FD + 1], fu_[FD + 1];                                                                      \
         _Pragma("unroll") for (int i_ = 0; i_ < FD; ++i_) { fg_[i_] = SPTS_PH_FRAG(0, i_); fu_[i_] = SPTS_PH_FRAG(1, i_); } \
-        float h_[16];                                                                                         \
-        _Pragma("unroll") for (int i_ = 0; i_ < KS; ++i_) {                                                   \
-            if (i_ + FD < KS) { fg_[(i_ + FD) % (FD + 1)] = SPTS_PH_FRAG(0, i_ + FD); fu_[(i_ + FD) % (FD + 1)] = SPTS_PH_FRAG(1, i_ + FD); } \
-            GC = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fg_[i_ % (FD + 1)], tg[i_], i_ == 0 ? zero16 : GC, 0, 0, 0); \
-            UC = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fu_[i_ % (FD + 1)], tu[i_], i_ == 0 ? zero16 : UC, 0, 0, 0); \
-            _Pragma("unroll") for (int e_ = i_ * EPS; e_ < (i_ + 1) * EPS; ++e_) h_[e_] = ph_silu(GP[e_]) * UP[e_]; \
+        float h_[16];   /* [row block][channel of the lane's 8] */                                            \
+        _Pragma("unroll") for (int i_ = 0; i_ < 2 * KS; ++i_) {                                               \
+            if (i_ + FD < 2 * KS) { fg_[(i_ + FD) % (FD + 1)] = SPTS_PH_FRAG(0, i_ + FD); fu_[(i_ + FD) % (FD + 1)] = SPTS_PH_FRAG(1, i_ + FD); } \
+            _Pragma("unroll") for (int rb_ = 0; rb_ < 2; ++rb_) {                                             \
+                GC[i_ & 1][rb_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fg_[i_ % (FD + 1)], tg[rb_][i_ >> 1], i_ < 2 ? zero4 : GC[i_ & 1][rb_], 0, 0, 0); \
+                UC[i_ & 1][rb_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fu_[i_ % (FD + 1)], tu[rb_][i_ >> 1], i_ < 2 ? zero4 : UC[i_ & 1][rb_], 0, 0, 0); \
+            }                                                                                                 \
+            h_[i_] = ph_silu(GP[(i_ >> 2) & 1][i_ >> 3][i_ & 3]) * UP[(i_ >> 2) & 1][i_ >> 3][i_ & 3];        \
             __builtin_amdgcn_sched_barrier(0);                                                                \
         }                                                                                                     \
-        if (prev_) {                                                                                          \
-            u32x4 x_, y_;                                                                                     \
-            _Pragma("unroll") for (int j_ = 0; j_ < 4; ++j_) {                                                \
-                const uint32_t lo_ = cvt_pk_bf16(h_[2 * j_], h_[2 * j_ + 1]);                                 \
-                const uint32_t hi_ = cvt_pk_bf16(h_[8 + 2 * j_], h_[8 + 2 * j_ + 1]);                         \
-                const auto sw_ = __builtin_amdgcn_permlane32_swap(lo_, hi_, false, false);                    \
-                x_[j_] = sw_[0]; y_[j_] = sw_[1];                                                             \
-            }                                                                                                 \
-            char* dst_ = hp + (int64_t)(tile_begin + (tl_) - 1) * a.N * 64 + out_off;                         \
-            if (row_ok) { *reinterpret_cast<u32x4*>(dst_) = x_; *reinterpret_cast<u32x4*>(dst_ + 16) = y_; }  \
-        }                                                                                                     \
+        if (prev_) SPTS_PH_STORE(tile_begin + (tl_) - 1, h_)                                                  \
     }
 
     // Everything in flight lands here (the t fragments included): the compiler does not see the direct-to-LDS loads, so
@@ -171,17 +171,11 @@ __global__ void __launch_bounds__(PH_WAVES * 64) proxy_hidden_kernel(ProxyHidden
         const bool odd = (ntiles & 1) != 0;   // last tile index is even -> it used (Ga, Ua)
         float h[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) h[e] = odd ? ph_silu(Ga[e]) * Ua[e] : ph_silu(Gb[e]) * Ub[e];
-        u32x4 x, y;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t lo = cvt_pk_bf16(h[2 * j], h[2 * j + 1]);
-            const uint32_t hi = cvt_pk_bf16(h[8 + 2 * j], h[8 + 2 * j + 1]);
-            const auto sw2 = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
-            x[j] = sw2[0]; y[j] = sw2[1];
+        for (int e = 0; e < 16; ++e) {
+            const int c = (e >> 2) & 1, r = e >> 3, t = e & 3;
+            h[e] = odd ? ph_silu(Ga[c][r][t]) * Ua[c][r][t] : ph_silu(Gb[c][r][t]) * Ub[c][r][t];
         }
-        char* dst = hp + (int64_t)(tile_end - 1) * a.N * 64 + out_off;
-        if (row_ok) { *reinterpret_cast<u32x4*>(dst) = x; *reinterpret_cast<u32x4*>(dst + 16) = y; }
+        SPTS_PH_STORE(tile_end - 1, h)
     }
 }
 
@@ -214,12 +208,12 @@ hipError_t launch_proxy_hidden(const ProxyHiddenArgs& a, hipStream_t s) {
     const int SC = pick_shares(RT, TT);
     const int total = RT * SC;
     const int grid = (total + 7) / 8 * 8;
-    const int ks = a.r / 16;
-    const size_t lds = (size_t)PH_NSTG * 2 * (ks / 2) * 2048;
-    if (ks != 16) return hipErrorInvalidValue;
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&proxy_hidden_kernel<16>), (int)lds);
+    const int ks = a.r / 32;
+    const size_t lds = (size_t)PH_NSTG * 2 * ks * 2048;
+    if (a.r != 256) return hipErrorInvalidValue;
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&proxy_hidden_kernel<8>), (int)lds);
     if (e != hipSuccess) return e;
-    proxy_hidden_kernel<16><<<dim3(grid), dim3(PH_WAVES * 64), lds, s>>>(a, RT, SC);
+    proxy_hidden_kernel<8><<<dim3(grid), dim3(PH_WAVES * 64), lds, s>>>(a, RT, SC);
     return hipGetLastError();
 }
 
