@@ -235,13 +235,14 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
         _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                        \
             bfr[half][j] = *reinterpret_cast<const bf16x8*>(sB_ + S::off(brow((half) * 4 + j) + l16, (ks) * 4 + lq)); \
     }
-    // MFMA m of a step
+    // MFMA m of a step: block row m / 4, block columns back and forth, so that each instruction shares an operand with the one before
+#define SPTS_MJ(m) (((m) / 4) & 1 ? 3 - (m) % 4 : (m) % 4)
 #define SPTS_MFMA(abuf, half, m)                                                                             \
     {                                                                                                        \
         if (DUAL_A && (half) == 1)                                                                           \
-            acc[(m) / 4][(half) * 4 + (m) % 4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[half][(m) % 4], af1[DUAL_A ? (m) / 4 : 0], acc[(m) / 4][(half) * 4 + (m) % 4], 0, 0, 0); \
+            acc[(m) / 4][(half) * 4 + SPTS_MJ(m)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[half][SPTS_MJ(m)], af1[DUAL_A ? (m) / 4 : 0], acc[(m) / 4][(half) * 4 + SPTS_MJ(m)], 0, 0, 0); \
         else                                                                                                 \
-            acc[(m) / 4][(half) * 4 + (m) % 4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[half][(m) % 4], af[abuf][(m) / 4], acc[(m) / 4][(half) * 4 + (m) % 4], 0, 0, 0); \
+            acc[(m) / 4][(half) * 4 + SPTS_MJ(m)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[half][SPTS_MJ(m)], af[abuf][(m) / 4], acc[(m) / 4][(half) * 4 + SPTS_MJ(m)], 0, 0, 0); \
     }
     constexpr int NM = 4 * MI;                            // MFMAs per step
     constexpr int HS = NM / 2;                            // MFMA slots per half step
