@@ -569,32 +569,39 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// ---- tail split-K second pass: one thread per accumulator-fragment quad (4 consecutive columns of one
-//      row) of a split tile; sums the splits in split order and applies the epilogue exactly as the
-//      single-pass kernel does.  For EPI_ROPE a thread owns the quad and its partner d/2 columns on.
+// ---- tail split-K second pass: one thread per FIN_U accumulator-fragment quads (4 consecutive columns of FIN_U rows 16 apart) of a
+//      split tile; sums the splits in split order and applies the epilogue exactly as the single-pass kernel does.  In a rotary
+//      product (not in one that also stores) a thread owns the quad and its partner d/2 columns on, and only the first halves of
+//      the heads have threads.  Bound: the memory-side cache, which the partial tiles were
+//      just written to; with one quad per thread, half of a rotary product's wavefronts had nothing to do and a thread waited for
+//      one load at a time: K projection of 8192 rows (256 shares) 26 -> 18 us, of 20011 rows 21 -> 15, stored products the same.
+constexpr int FIN_U = 2;
 template <int NW>
 __global__ void __launch_bounds__(256) splitk_finish_kernel(GemmArgs a, int nM, int nN, int nfull) {
-    constexpr int MI = 32 / NW, WROWS = 16 * MI;
+    constexpr int MI = 32 / NW, WROWS = 16 * MI, MG = MI / FIN_U;
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int rt = (int)(g >> 14);                 // split tile (16384 quads per tile)
-    const int v = (int)(g & 16383);
-    const int lane = v & 63, j = (v >> 6) & 7, wi = v >> 9;
-    const int wave = wi / MI, i = wi % MI;
+    const bool halves = a.epi == EPI_ROPE;         // 4 of the 8 column blocks have threads
+    const int jb = halves ? 2 : 3;
+    const int per_tile = 16384 / FIN_U >> (halves ? 1 : 0);
+    const int rt = (int)(g / per_tile);            // split tile
+    const int v = (int)(g % per_tile);
+    const int lane = v & 63, jx = (v >> 6) & ((1 << jb) - 1), wi = v >> (6 + jb);
+    const int wave = wi / MG, i0 = wi % MG * FIN_U;
+    const int j = halves && a.head_dim == 64 ? (jx >> 1) * 4 + (jx & 1) : jx;
     const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lq = lane >> 4;
     int tm, tn;
     tile_of(nfull + rt, nM, nN, tm, tn);
-    const int64_t grow = (int64_t)tm * BM + wm * WROWS + i * 16 + l16;
     const int col0 = tn * 256;
     const float* P = a.part32 + (int64_t)rt * a.ksplit * (BM * 256);
-    auto quad = [&](int jj) {
-        const float* p = P + (((wave * MI + i) * 8 + jj) * 64 + lane) * 4;
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};
-        for (int sp = 0; sp < a.ksplit; ++sp) s += *reinterpret_cast<const f32x4*>(p + (int64_t)sp * (BM * 256));
-        return s;
+    auto quads = [&](int jj, f32x4 (&s)[FIN_U]) {
+        const float* p = P + (((wave * MI + i0) * 8 + jj) * 64 + lane) * 4;
+#pragma unroll
+        for (int u = 0; u < FIN_U; ++u) s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+        for (int sp = 0; sp < a.ksplit; ++sp)
+#pragma unroll
+            for (int u = 0; u < FIN_U; ++u) s[u] += *reinterpret_cast<const f32x4*>(p + (int64_t)sp * (BM * 256) + u * 8 * 64 * 4);
     };
-    const bool rok = grow < a.M;
-    const int64_t growc = rok ? grow : a.M - 1;
-    const int64_t crow = a.c_idx ? (int64_t)a.c_idx[growc] : growc;
     bf16_t* Cb = (bf16_t*)a.C;
     // two products in one launch: a tile is either a rotary tile of the first or a stored tile of the second
     int epi = a.epi, colshift = 0;
@@ -603,52 +610,60 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(GemmArgs a, int nM, 
         if (col0 >= a.n_split) { epi = EPI_STORE; colshift = a.n_split; Cb = (bf16_t*)a.C2; ldo = a.ldc2; }
         else epi = EPI_ROPE;
     }
-    if (epi == EPI_STORE) {
-        const f32x4 s = quad(j);
-        const int col = col0 - colshift + wn * 128 + j * 16 + 4 * lq;
-        u32x2 o = {pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w)};
-        if (rok) {
-            if (a.c_slab) *reinterpret_cast<u32x2*>(Cb + ((int64_t)(col >> 5) * a.M + grow) * 32 + (col & 31)) = o;   // slab-major C
-            else *reinterpret_cast<u32x2*>(Cb + crow * ldo + col) = o;
-        }
-        if (a.Ct && grow < a.ldct) {
-            bf16_t* ct = (bf16_t*)a.Ct;
-            const uint16_t e[4] = {(uint16_t)(o.x & 0xffff), (uint16_t)(o.x >> 16), (uint16_t)(o.y & 0xffff), (uint16_t)(o.y >> 16)};
+    const int half = a.head_dim >> 1;
+    int j2 = j, jj = 0;   // rotary: block of the quad's partner; column inside the half head
+    if (epi == EPI_ROPE) {
+        if (half == 64) { if (j >= 4) return; j2 = j + 4; jj = j * 16 + 4 * lq; }
+        else { if (j & 2) return; j2 = j + 2; jj = (j & 1) * 16 + 4 * lq; }
+    }
+    f32x4 s1[FIN_U], s2[FIN_U];
+    quads(j, s1);
+    if (epi == EPI_ROPE) quads(j2, s2);
+    const int col = col0 - colshift + wn * 128 + (epi == EPI_ROPE ? (half == 64 ? 0 : (j >> 2) * 64) + jj : j * 16 + 4 * lq);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) ct[(int64_t)(col + t) * a.ldct + vt_key_slot(grow)].v = e[t];
-        }
-    } else if (epi == EPI_RESIDUAL) {
-        if (!rok) return;
-        const f32x4 s = quad(j);
-        const int col = col0 + wn * 128 + j * 16 + 4 * lq;
-        u32x2* p = reinterpret_cast<u32x2*>(Cb + crow * a.ldc + col);
-        const u32x2 old = *p;
-        u32x2 o;
-        o.x = pack_bf16x2(__uint_as_float(old.x << 16) + s.x, __uint_as_float(old.x & 0xffff0000u) + s.y);
-        o.y = pack_bf16x2(__uint_as_float(old.y << 16) + s.z, __uint_as_float(old.y & 0xffff0000u) + s.w);
-        *p = o;
-    } else {   // EPI_ROPE
-        if (!rok) return;
-        const int half = a.head_dim >> 1;
-        int j1, j2, jj;   // accumulator blocks of the quad and of its partner; column inside the half head
-        if (half == 64) { if (j >= 4) return; j1 = j; j2 = j + 4; jj = j * 16 + 4 * lq; }
-        else { if (j & 2) return; j1 = j; j2 = j + 2; jj = (j & 1) * 16 + 4 * lq; }
-        const f32x4 x1 = quad(j1), x2 = quad(j2);
-        const int64_t trow = a.rope_idx ? (int64_t)a.rope_idx[grow] : grow;
-        const float2* tab = a.rope + trow * half + jj;
-        const float rs = a.rope_scale != 0.f ? a.rope_scale : 1.f;
-        float lo[4], hi[4];
+    for (int u = 0; u < FIN_U; ++u) {
+        const f32x4 s = s1[u];
+        const int64_t grow = (int64_t)tm * BM + wm * WROWS + (i0 + u) * 16 + l16;
+        const bool rok = grow < a.M;
+        const int64_t growc = rok ? grow : a.M - 1;
+        const int64_t crow = a.c_idx ? (int64_t)a.c_idx[growc] : growc;
+        if (epi == EPI_STORE) {
+            u32x2 o = {pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w)};
+            if (rok) {
+                if (a.c_slab) *reinterpret_cast<u32x2*>(Cb + ((int64_t)(col >> 5) * a.M + grow) * 32 + (col & 31)) = o;   // slab-major C
+                else *reinterpret_cast<u32x2*>(Cb + crow * ldo + col) = o;
+            }
+            if (a.Ct && grow < a.ldct) {
+                bf16_t* ct = (bf16_t*)a.Ct;
+                const uint16_t e[4] = {(uint16_t)(o.x & 0xffff), (uint16_t)(o.x >> 16), (uint16_t)(o.y & 0xffff), (uint16_t)(o.y >> 16)};
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const float2 cs = tab[t];
-            lo[t] = (x1[t] * cs.x - x2[t] * cs.y) * rs;
-            hi[t] = (x2[t] * cs.x + x1[t] * cs.y) * rs;
+                for (int t = 0; t < 4; ++t) ct[(int64_t)(col + t) * a.ldct + vt_key_slot(grow)].v = e[t];
+            }
+        } else if (epi == EPI_RESIDUAL) {
+            if (!rok) continue;
+            u32x2* p = reinterpret_cast<u32x2*>(Cb + crow * a.ldc + col);
+            const u32x2 old = *p;
+            u32x2 o;
+            o.x = pack_bf16x2(__uint_as_float(old.x << 16) + s.x, __uint_as_float(old.x & 0xffff0000u) + s.y);
+            o.y = pack_bf16x2(__uint_as_float(old.y << 16) + s.z, __uint_as_float(old.y & 0xffff0000u) + s.w);
+            *p = o;
+        } else {   // EPI_ROPE
+            if (!rok) continue;
+            const int64_t trow = a.rope_idx ? (int64_t)a.rope_idx[grow] : grow;
+            const float2* tab = a.rope + trow * half + jj;
+            const float rs = a.rope_scale != 0.f ? a.rope_scale : 1.f;
+            float lo[4], hi[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float2 cs = tab[t];
+                lo[t] = (s[t] * cs.x - s2[u][t] * cs.y) * rs;
+                hi[t] = (s2[u][t] * cs.x + s[t] * cs.y) * rs;
+            }
+            u32x2 o1 = {pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
+            u32x2 o2 = {pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3])};
+            *reinterpret_cast<u32x2*>(Cb + crow * a.ldc + col) = o1;
+            *reinterpret_cast<u32x2*>(Cb + crow * a.ldc + col + half) = o2;
         }
-        const int col = col0 + wn * 128 + (half == 64 ? 0 : (j >> 2) * 64) + jj;
-        u32x2 o1 = {pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
-        u32x2 o2 = {pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3])};
-        *reinterpret_cast<u32x2*>(Cb + crow * a.ldc + col) = o1;
-        *reinterpret_cast<u32x2*>(Cb + crow * a.ldc + col + half) = o2;
     }
 }
 
@@ -700,9 +715,9 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
     }
     if (e != hipSuccess || a.ksplit <= 1) return e;
     const int nM = (int)((a.M + BM - 1) / BM), nN = a.N / 256;
-    const int64_t quads = (int64_t)(nM * nN - a.nfull) * 16384;
-    if (quads <= 0) return hipSuccess;
-    splitk_finish_kernel<NW><<<dim3((unsigned)(quads / 256)), dim3(256), 0, s>>>(a, nM, nN, a.nfull);
+    const int64_t threads = (int64_t)(nM * nN - a.nfull) * (16384 / FIN_U >> (a.epi == EPI_ROPE ? 1 : 0));
+    if (threads <= 0) return hipSuccess;
+    splitk_finish_kernel<NW><<<dim3((unsigned)(threads / 256)), dim3(256), 0, s>>>(a, nM, nN, a.nfull);
     return hipGetLastError();
 }
 
