@@ -211,3 +211,21 @@ def test_long_row_topk_patterns(torch, n):
             got = out.cpu().numpy()
             for b, name in enumerate(rows):
                 assert np.array_equal(got[b], orc.topk_select(s[b], k, protect)), (name, k, protect)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 333, 511, 512, 513, 1023, 1024, 1025])
+def test_short_row_topk(torch, n):
+    """Around the lengths where the wavefront kernel takes over from the workgroup kernel, and its two sizes."""
+    rng = np.random.default_rng(n)
+    rows = np.stack([np.exp(rng.standard_normal(n)), rng.standard_normal(n), np.full(n, 0.25), np.round(2 * rng.standard_normal(n)),
+                     np.where(rng.random(n) < 0.5, -0.0, 0.0), np.full(n, -np.inf)]).astype(np.float32)
+    sd = torch.from_numpy(rows).cuda()
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    for k in sorted({1, max(1, n // 3), max(1, n - 1), n}):
+        for protect in (0, 1):
+            out = torch.full((len(rows) * k + 1,), -7, dtype=torch.int32, device="cuda")
+            ctx.spts_select_topk_batched(sd, n, k, protect, len(rows), out)
+            got = out.cpu().numpy()
+            assert got[-1] == -7
+            for b in range(len(rows)):
+                assert np.array_equal(got[b * k:(b + 1) * k], orc.topk_select(rows[b], k, protect)), (b, k, protect)
