@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __
 // bracket misses or overflows (heavily tied scores, scores that depend strongly on the position) take the three-sweep route of
 // topk_long_rows.
 // Bound: HBM for one read of the scores and the index list (68 us for 512 rows of 131072, k = 52428, at 5.5 TB/s) and about 25
-// vector instructions per score and wavefront.  Measured there: 199 us with three sweeps -> 153 us, of which about 45 are
+// vector instructions per score and wavefront.  Measured there: 199 us with three sweeps -> 155-167 us, of which about 45 are
 // the sample, the barriers and the passes over the bracket (the same for every length).
 constexpr int LONG1_MAX_N = 131072;                               // one bit per score: 16 KB
 constexpr int LONG1_WORDS = LONG1_MAX_N / TOPK_WAVES / 64 / 32;  // 32-score words per lane
