@@ -95,8 +95,18 @@ __device__ inline void pick_bin(const int* hist, int lane, int shift, uint32_t p
 // fit its region (heavily tied scores) makes the caller fall back to 8-bit passes over all keys.
 constexpr int T13_BINS = 8192;
 constexpr int T13_LOW = 19;
-constexpr int T13_CW = 768;                                              // keys per wavefront region
-constexpr int T13_LDS_BYTES = T13_BINS * 4 + TOPK_WAVES * T13_CW * 4;    // 80 KB: two workgroups per CU
+constexpr int T13_CW = 736;                                              // keys per wavefront region
+constexpr int T13_LDS_BYTES = T13_BINS * 4 + TOPK_WAVES * T13_CW * 4;
+// The small arrays of those kernels.  With the regions they have to stay within half of a CU's 160 KB: at 768 keys per region they
+// did not, and every CU ran one workgroup where the registers allow two (512 rows of 131072, k = 52428: 140 us, now 119).
+struct TopkShared {
+    int64_t need;
+    int hist[256];
+    int wave_gt[TOPK_WAVES], wave_eq[TOPK_WAVES], wave_tot[TOPK_WAVES], wave_in[TOPK_WAVES];
+    uint32_t prefix, lo, hi;
+    int bin, over;
+};
+static_assert(T13_LDS_BYTES + sizeof(TopkShared) <= 80 * 1024, "two workgroups share a CU's LDS");
 
 // all 1024 lanes: from the 8192-bin histogram the bin that holds the k-th largest key (-> *sh_bin) and the rank wanted
 // inside it (-> *sh_need); ends with a barrier
@@ -218,11 +228,8 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_reg_kernel(const float* __r
     extern __shared__ __attribute__((aligned(16))) char lsm[];
     int* h13 = reinterpret_cast<int*>(lsm);                                                   // [T13_BINS]
     uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);   // [TOPK_WAVES][T13_CW]
-    __shared__ int hist[256];
-    __shared__ uint32_t sh_prefix;
-    __shared__ int64_t sh_need;
-    __shared__ int wave_gt[TOPK_WAVES], wave_eq[TOPK_WAVES], wave_tot[TOPK_WAVES];
-    __shared__ int sh_bin, sh_over;
+    __shared__ TopkShared sh;
+    int* const hist = sh.hist;
 
     // one independent problem per workgroup: equal rows, or the segment the descriptors give it
     if (seg.offsets) {
@@ -252,13 +259,13 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_reg_kernel(const float* __r
     uint32_t T = 0;
     int need_eq = 0;
     for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
-    if (tid == 0) { sh_over = 0; sh_bin = 0; sh_need = k; }
+    if (tid == 0) { sh.over = 0; sh.bin = 0; sh.need = k; }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < KPT; ++j) hist_add(h13, lo + 64 * j + lane < N, (int)(keys[j] >> T13_LOW));
     __syncthreads();
-    t13_pick(h13, k, wave_tot, &sh_bin, &sh_need);
-    const uint32_t bin = (uint32_t)sh_bin;
+    t13_pick(h13, k, sh.wave_tot, &sh.bin, &sh.need);
+    const uint32_t bin = (uint32_t)sh.bin;
     int cnt = 0, cgt = 0;
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
@@ -271,16 +278,16 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_reg_kernel(const float* __r
         if (in && at < T13_CW) cand[wave][at] = keys[j] & ((1u << T13_LOW) - 1u);
         cnt += (int)__popcll(m);
     }
-    if (lane == 0 && cnt > T13_CW) sh_over = 1;
+    if (lane == 0 && cnt > T13_CW) sh.over = 1;
     __syncthreads();
-    if (sh_over == 0) {
+    if (sh.over == 0) {
         int g, e;
-        const uint32_t low = t13_resolve(cand[wave], cnt, sh_need, hist, &sh_prefix, &sh_need, &need_eq, &g, &e);
+        const uint32_t low = t13_resolve(cand[wave], cnt, sh.need, hist, &sh.prefix, &sh.need, &need_eq, &g, &e);
         T = (bin << T13_LOW) | low;
-        if (lane == 0) { wave_gt[wave] = cgt + g; wave_eq[wave] = e; }
+        if (lane == 0) { sh.wave_gt[wave] = cgt + g; sh.wave_eq[wave] = e; }
     } else {
         // heavily tied keys: four 8-bit passes over the registers
-        if (tid == 0) { sh_prefix = 0; sh_need = k; }
+        if (tid == 0) { sh.prefix = 0; sh.need = k; }
         uint32_t prefix = 0;
         int64_t need = k;
         for (int pass = 0; pass < 4; ++pass) {
@@ -294,10 +301,10 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_reg_kernel(const float* __r
                 hist_add(hist, valid && (keys[j] & hi_mask) == prefix, (int)((keys[j] >> shift) & 0xFF));
             }
             __syncthreads();
-            if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh_prefix, &sh_need);
+            if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh.prefix, &sh.need);
             __syncthreads();
-            prefix = sh_prefix;
-            need = sh_need;
+            prefix = sh.prefix;
+            need = sh.need;
         }
         T = prefix;
         need_eq = (int)need;
@@ -309,11 +316,11 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_reg_kernel(const float* __r
             cgt += (int)__popcll(__ballot(valid && keys[j] > T));
             ceq += (int)__popcll(__ballot(valid && keys[j] == T));
         }
-        if (lane == 0) { wave_gt[wave] = cgt; wave_eq[wave] = ceq; }
+        if (lane == 0) { sh.wave_gt[wave] = cgt; sh.wave_eq[wave] = ceq; }
     }
     __syncthreads();
     int gt_before = 0, eq_before = 0;
-    for (int w = 0; w < wave; ++w) { gt_before += wave_gt[w]; eq_before += wave_eq[w]; }
+    for (int w = 0; w < wave; ++w) { gt_before += sh.wave_gt[w]; eq_before += sh.wave_eq[w]; }
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
         const int i = lo + 64 * j + lane;
@@ -422,15 +429,11 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 constexpr int LONG_U = 4;                       // 16-byte loads in flight per lane
 constexpr int LONG_STEP = 64 * 4 * LONG_U;      // scores a wavefront takes per iteration
 
-__device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores, int64_t N, int64_t k, int protect_last, int32_t* __restrict__ idx_out, char* lsm) {
+__device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores, int64_t N, int64_t k, int protect_last, int32_t* __restrict__ idx_out, char* lsm, TopkShared& sh) {
     int* h13 = reinterpret_cast<int*>(lsm);                                                     // [T13_BINS]
     uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);     // [TOPK_WAVES][T13_CW]
     int (*whist)[256] = reinterpret_cast<int (*)[256]>(lsm + T13_BINS * 4);                     // fallback only, same bytes
-    __shared__ int hist[256];
-    __shared__ uint32_t sh_prefix;
-    __shared__ int64_t sh_need;
-    __shared__ int wave_gt[TOPK_WAVES], wave_eq[TOPK_WAVES], wave_tot[TOPK_WAVES];
-    __shared__ int sh_b12, sh_over;
+    int* const hist = sh.hist;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)N;
     const int per_wave = ((n + TOPK_WAVES - 1) / TOPK_WAVES + LONG_STEP - 1) / LONG_STEP * LONG_STEP;
@@ -461,13 +464,13 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
     int need_eq = 0;
     // ---- sweep 1: top 13 bits
     for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
-    if (tid == 0) { sh_over = 0; sh_b12 = 0; sh_need = k; }
+    if (tid == 0) { sh.over = 0; sh.bin = 0; sh.need = k; }
     __syncthreads();
     SPTS_LONG_SWEEP({ hist_add(h13, valid, (int)(key >> T13_LOW)); })
     __syncthreads();
-    t13_pick(h13, k, wave_tot, &sh_b12, &sh_need);
-    const uint32_t b12 = (uint32_t)sh_b12;
-    int64_t need = sh_need;
+    t13_pick(h13, k, sh.wave_tot, &sh.bin, &sh.need);
+    const uint32_t b12 = (uint32_t)sh.bin;
+    int64_t need = sh.need;
     // ---- sweep 2: the wavefront's keys of that bin into its LDS region (low 19 bits), keys of higher bins counted
     int cnt = 0, cgt = 0;
     SPTS_LONG_SWEEP({
@@ -479,17 +482,17 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
         if (in && at < T13_CW) cand[wave][at] = key & ((1u << T13_LOW) - 1u);
         cnt += (int)__popcll(m);
     })
-    if (lane == 0 && cnt > T13_CW) sh_over = 1;
+    if (lane == 0 && cnt > T13_CW) sh.over = 1;
     __syncthreads();
-    if (sh_over == 0) {
+    if (sh.over == 0) {
         int g, e;
-        const uint32_t low = t13_resolve(cand[wave], cnt, need, hist, &sh_prefix, &sh_need, &need_eq, &g, &e);
+        const uint32_t low = t13_resolve(cand[wave], cnt, need, hist, &sh.prefix, &sh.need, &need_eq, &g, &e);
         T = (b12 << T13_LOW) | low;
-        if (lane == 0) { wave_gt[wave] = cgt + g; wave_eq[wave] = e; }
+        if (lane == 0) { sh.wave_gt[wave] = cgt + g; sh.wave_eq[wave] = e; }
     } else {
         // ---- fallback: four 8-bit passes over the row
-        __syncthreads();   // every wavefront has read sh_over before the regions are reused as histograms
-        if (tid == 0) { sh_prefix = 0; sh_need = k; }
+        __syncthreads();   // every wavefront has read sh.over before the regions are reused as histograms
+        if (tid == 0) { sh.prefix = 0; sh.need = k; }
         uint32_t prefix = 0;
         need = k;
         cgt = 0;   // last pass: keys of this wavefront's slice whose decided 24 bits exceed the prefix
@@ -510,10 +513,10 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
                 hist[tid] = t;
             }
             __syncthreads();
-            if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh_prefix, &sh_need);
+            if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh.prefix, &sh.need);
             __syncthreads();
-            prefix = sh_prefix;
-            need = sh_need;
+            prefix = sh.prefix;
+            need = sh.need;
         }
         T = prefix;
         need_eq = (int)need;
@@ -527,11 +530,11 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
         }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) above += __shfl_xor(above, off);
-        if (lane == 0) { wave_gt[wave] = above + cgt; wave_eq[wave] = whist[wave][digit]; }
+        if (lane == 0) { sh.wave_gt[wave] = above + cgt; sh.wave_eq[wave] = whist[wave][digit]; }
     }
     __syncthreads();
     int gt_before = 0, eq_before = 0;
-    for (int w = 0; w < wave; ++w) { gt_before += wave_gt[w]; eq_before += wave_eq[w]; }
+    for (int w = 0; w < wave; ++w) { gt_before += sh.wave_gt[w]; eq_before += sh.wave_eq[w]; }
     // ordered compaction of the slice: index order inside an iteration is (load u, lane, element e)
     for (int base = lo; base < hi; base += LONG_STEP) {
         f32x4v v[LONG_U];
@@ -572,7 +575,8 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
 __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
                                                                  int protect_last, int32_t* __restrict__ idx_out) {
     extern __shared__ __attribute__((aligned(16))) char lsm[];
-    topk_long_rows(scores + (int64_t)blockIdx.x * N, N, k, protect_last, idx_out + (int64_t)blockIdx.x * k, lsm);
+    __shared__ TopkShared sh;
+    topk_long_rows(scores + (int64_t)blockIdx.x * N, N, k, protect_last, idx_out + (int64_t)blockIdx.x * k, lsm, sh);
 }
 
 // The same rows read from memory once (32768 < N <= LONG1_MAX_N, N % 4 == 0).  A sample of 8192 scores spread over the row gives, through
@@ -629,10 +633,8 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     extern __shared__ __attribute__((aligned(16))) char lsm[];
     int* h13 = reinterpret_cast<int*>(lsm);                                                   // [T13_BINS], the sample's
     uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);   // [TOPK_WAVES][T13_CW]
-    __shared__ int hist[256];
-    __shared__ uint32_t sh_prefix, sh_lo, sh_hi;
-    __shared__ int64_t sh_need;
-    __shared__ int wave_gt[TOPK_WAVES], wave_in[TOPK_WAVES], wave_eq[TOPK_WAVES], wave_tot[TOPK_WAVES];
+    __shared__ TopkShared sh;
+    int* const hist = sh.hist;
     scores += (int64_t)blockIdx.x * N;
     idx_out += (int64_t)blockIdx.x * k;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -654,11 +656,11 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     __syncthreads();
     const float frac = (float)k / (float)n, r = frac * LONG1_SAMPLES, dev = 4.f * sqrtf(r * (1.f - frac)) + 4.f;
     const int r_hi = (int)(r - dev), r_lo = (int)(r + dev) + 1;
-    if (tid == 0) { sh_hi = 0xFFFFFFFFu; sh_lo = 0u; }
+    if (tid == 0) { sh.hi = 0xFFFFFFFFu; sh.lo = 0u; }
     __syncthreads();
-    if (r_hi >= 1) sample_key(h13, r_hi, wave_tot, &sh_hi);                   // else nothing lies above the bracket
-    if (r_lo <= LONG1_SAMPLES) sample_key(h13, r_lo, wave_tot, &sh_lo);       // else it has no lower end
-    const uint32_t hi_key = sh_hi, lo_key = sh_lo < sh_hi ? sh_lo : sh_hi, width = hi_key - lo_key;
+    if (r_hi >= 1) sample_key(h13, r_hi, sh.wave_tot, &sh.hi);                   // else nothing lies above the bracket
+    if (r_lo <= LONG1_SAMPLES) sample_key(h13, r_lo, sh.wave_tot, &sh.lo);       // else it has no lower end
+    const uint32_t hi_key = sh.hi, lo_key = sh.lo < sh.hi ? sh.lo : sh.hi, width = hi_key - lo_key;
 
     // ---- the one sweep: wavefront w owns a contiguous slice
     const int per_wave = ((n + TOPK_WAVES - 1) / TOPK_WAVES + LONG_STEP - 1) / LONG_STEP * LONG_STEP;
@@ -716,15 +718,15 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) cgt += __shfl_xor(cgt, off);
-    if (lane == 0) { wave_gt[wave] = cgt; wave_in[wave] = cnt; }
+    if (lane == 0) { sh.wave_gt[wave] = cgt; sh.wave_in[wave] = cnt; }
     __syncthreads();
     int above = 0, inside = 0;
     bool fits = width < (1u << 21);
 #pragma unroll
-    for (int w = 0; w < TOPK_WAVES; ++w) { above += wave_gt[w]; inside += wave_in[w]; fits &= wave_in[w] <= T13_CW; }
+    for (int w = 0; w < TOPK_WAVES; ++w) { above += sh.wave_gt[w]; inside += sh.wave_in[w]; fits &= sh.wave_in[w] <= T13_CW; }
     if (!fits || (int64_t)above >= k || (int64_t)above + inside < k) {
         __syncthreads();
-        topk_long_rows(scores, N, k, protect_last, idx_out, lsm);
+        topk_long_rows(scores, N, k, protect_last, idx_out, lsm, sh);
         return;
     }
     // ---- exact threshold among the keys of the bracket: 8 + 8 + 5 bits of their distance from its lower end
@@ -742,10 +744,10 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
             hist_add(hist, j < cnt && (c & hi_mask) == prefix, (int)((c >> shift) & (pass == 2 ? 0x1Fu : 0xFFu)));
         }
         __syncthreads();
-        if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh_prefix, &sh_need);
+        if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh.prefix, &sh.need);
         __syncthreads();
-        prefix = sh_prefix;
-        need = sh_need;
+        prefix = sh.prefix;
+        need = sh.need;
     }
     const uint32_t T = prefix >> 11;   // the threshold's distance from lo_key
     const int need_eq = (int)need;
@@ -755,11 +757,11 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
         g += (int)__popcll(__ballot(j < cnt && c > T));
         ne += (int)__popcll(__ballot(j < cnt && c == T));
     }
-    if (lane == 0) wave_eq[wave] = ne;
+    if (lane == 0) sh.wave_eq[wave] = ne;
     __syncthreads();
     int eq_before = 0, eq_all = 0;
 #pragma unroll
-    for (int w = 0; w < TOPK_WAVES; ++w) { eq_before += w < wave ? wave_eq[w] : 0; eq_all += wave_eq[w]; }
+    for (int w = 0; w < TOPK_WAVES; ++w) { eq_before += w < wave ? sh.wave_eq[w] : 0; eq_all += sh.wave_eq[w]; }
     // ---- the bracket's selected keys join the words.  Keys equal to the threshold go by index; they are ranked only where the
     //      selection ends between them.
     auto place = [&](uint32_t c, int j) {   // index order inside the wavefront: word, load, lane, element
@@ -788,10 +790,10 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
         if (take) atomicOr(&sel[at >> 11][wave * 64 + ((at >> 2) & 63u)], 1u << (31 - (((at >> 8) & 7u) * 4 + (at & 3u))));
     }
     const int eq_taken = need_eq - eq_before < 0 ? 0 : need_eq - eq_before < ne ? need_eq - eq_before : ne;
-    if (lane == 0) wave_in[wave] = cgt + g + eq_taken;   // selected scores of this slice
+    if (lane == 0) sh.wave_in[wave] = cgt + g + eq_taken;   // selected scores of this slice
     __syncthreads();
     int out = 0;
-    for (int w = 0; w < wave; ++w) out += wave_in[w];
+    for (int w = 0; w < wave; ++w) out += sh.wave_in[w];
 
     // ---- ordered index list from the words; index order inside a load is (lane, element e)
     for (int w = 0; w < words; ++w) {
