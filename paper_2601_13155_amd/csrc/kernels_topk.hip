@@ -63,25 +63,25 @@ __device__ inline void hist_add(int* hist, bool active, int bin) {
 }
 
 // wavefront 0: from the 256-bin histogram and the rank `need` still wanted, the bin that holds the
-// need-th largest element of the current bucket; updates (prefix, need) in LDS
-__device__ inline void pick_bin(const int* hist, int lane, int shift, uint32_t prefix, int64_t need, uint32_t* sh_prefix,
-                                int64_t* sh_need) {
+// need-th largest element of the current bucket; updates (prefix, need) in LDS.  I: int64_t, or int where ranks fit
+template <typename I>
+__device__ inline void pick_bin(const int* hist, int lane, int shift, uint32_t prefix, I need, uint32_t* sh_prefix, I* sh_need) {
     // bins in descending order: lane l owns bins 255-4l .. 252-4l
     int c0 = hist[255 - 4 * lane], c1 = hist[254 - 4 * lane], c2 = hist[253 - 4 * lane], c3 = hist[252 - 4 * lane];
-    int64_t tot = (int64_t)c0 + c1 + c2 + c3;
-    int64_t incl = tot;
+    I tot = (I)c0 + c1 + c2 + c3;
+    I incl = tot;
     for (int off = 1; off < 64; off <<= 1) {
-        int64_t o = __shfl_up(incl, off);
+        I o = __shfl_up(incl, off);
         if (lane >= off) incl += o;
     }
-    int64_t excl = incl - tot;  // elements in bins above this lane's bins
+    I excl = incl - tot;  // elements in bins above this lane's bins
     if (excl < need && need <= incl) {
-        int64_t rem = need - excl;
+        I rem = need - excl;
         int bin;
         if (rem <= c0) { bin = 255 - 4 * lane; }
-        else if (rem <= (int64_t)c0 + c1) { bin = 254 - 4 * lane; rem -= c0; }
-        else if (rem <= (int64_t)c0 + c1 + c2) { bin = 253 - 4 * lane; rem -= (int64_t)c0 + c1; }
-        else { bin = 252 - 4 * lane; rem -= (int64_t)c0 + c1 + c2; }
+        else if (rem <= (I)c0 + c1) { bin = 254 - 4 * lane; rem -= c0; }
+        else if (rem <= (I)c0 + c1 + c2) { bin = 253 - 4 * lane; rem -= (I)c0 + c1; }
+        else { bin = 252 - 4 * lane; rem -= (I)c0 + c1 + c2; }
         *sh_prefix = prefix | ((uint32_t)bin << shift);
         *sh_need = rem;
     }
@@ -104,7 +104,7 @@ struct TopkShared {
     int hist[256];
     int wave_gt[TOPK_WAVES], wave_eq[TOPK_WAVES], wave_tot[TOPK_WAVES], wave_in[TOPK_WAVES];
     uint32_t prefix, lo, hi;
-    int bin, over;
+    int bin, over, rank_lo, rank;
 };
 static_assert(T13_LDS_BYTES + sizeof(TopkShared) <= 80 * 1024, "two workgroups share a CU's LDS");
 
@@ -580,25 +580,31 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __
 }
 
 // The same rows read from memory once (32768 < N <= LONG1_MAX_N, N % 4 == 0).  A sample of 8192 scores spread over the row gives, through
-// the 8192-bin histogram and linear interpolation inside a bin, two keys that bracket the k-th largest with four standard
-// deviations of the sample's quantile on either side (about 4 % of the row lies between them).  One sweep over the row then
-// leaves, per score, a bit of the lane's own in LDS (above the bracket), and the keys inside the bracket, with their places, in the
-// wavefront's LDS region; counts tell whether the bracket holds the threshold.  The exact threshold is resolved among those keys,
-// the selected ones set their bits, and the index list is written from the bits: no score is read again.  Rows whose
-// bracket misses or overflows (heavily tied scores, scores that depend strongly on the position) take the three-sweep route of
-// topk_long_rows.
+// the 8192-bin histogram and 8 more bits of the keys in its bins, two keys that bracket the k-th largest with four standard
+// deviations of the sample's quantile on either side (about 4 % of the row lies between them, whatever the scores' spread).  One
+// sweep over the row then leaves, per score, a bit of the lane's own in LDS (above the bracket), and the keys inside the bracket, with
+// their places, in the wavefront's LDS region; counts tell whether the bracket holds the threshold.  The exact threshold is
+// resolved among those keys, the selected ones set their bits, and the index list is written from the bits.  A region keeps
+// 21 bits of a key's distance from the bracket's lower end; where the bracket is wider, the keys that share the threshold's 21 bits
+// (a handful) are read again for the rest.  Rows of which the sample says that a wavefront's share of the bracket does not fit its region
+// (a few equal values, scores ordered by position) take the three-sweep route of topk_long_rows at once, and so do the rare
+// ones (1 in 10^4 of ordinary rows) that turn out not to fit or not to hold the threshold after the sweep.
 // Bound: HBM for one read of the scores and the index list (68 us for 512 rows of 131072, k = 52428, at 5.5 TB/s) and about 25
-// vector instructions per score and wavefront.  Measured there: 199 us with three sweeps -> 155-167 us, of which about 45 are
-// the sample, the barriers and the passes over the bracket (the same for every length).
-constexpr int LONG1_MAX_N = 131072;                               // one bit per score: 16 KB
+// vector instructions per score and wavefront.  Measured there, three sweeps -> this kernel: 196 -> 116 us for scores within an
+// octave, 191 -> 121 for scores over many (log-spread 1.5 to 3), 189 -> 117 for signed normal ones; k = 5 % 182 -> 103, k = 95 % 225 -> 174; all
+// equal or sorted rows, which go back to the sweeps, no slower than those alone (410 -> 381, 349 -> 320: two workgroups per CU now).
+// 16 rows 86 -> 48-50, one of 33000 30 -> 24-27.
+constexpr int LONG1_MAX_N = 131072;                               // one bit per score: 16 KB; longer rows keep to the three sweeps
 constexpr int LONG1_WORDS = LONG1_MAX_N / TOPK_WAVES / 64 / 32;  // 32-score words per lane
 constexpr int LONG1_SAMPLES = 8192;
+constexpr int LONG1_BITS = LONG1_WORDS * TOPK_THREADS * 4;       // bytes of those bits; the regions take what is left of the LDS
+constexpr int LONG1_CW = (T13_LDS_BYTES - LONG1_BITS) / (TOPK_WAVES * 4);   // keys per wavefront region: 992, 12 % of the longest slice
 struct topk_true { static constexpr bool value = true; };
 struct topk_false { static constexpr bool value = false; };
 
-// all 1024 lanes: the key at rank `rank` (1 = largest; clamped to 1 .. LONG1_SAMPLES by the caller) of the sampled histogram,
-// interpolated inside its 13-bit bin -> *sh_key; ends with a barrier
-__device__ inline void sample_key(const int* h13, int rank, int* wave_tot, uint32_t* sh_key) {
+// all 1024 lanes: the 13-bit bins of the sampled histogram that hold ranks r_hi <= r_lo (1 = largest) and the ranks inside them ->
+// sh.hi / sh.rank and sh.lo / sh.rank_lo; ends with a barrier
+__device__ inline void sample_bins(const int* h13, int r_hi, int r_lo, TopkShared& sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int BPT = T13_BINS / TOPK_THREADS;
     int c[BPT], tot = 0;
@@ -609,21 +615,21 @@ __device__ inline void sample_key(const int* h13, int rank, int* wave_tot, uint3
         const int o = __shfl_up(incl, off);
         if (lane >= off) incl += o;
     }
-    if (lane == 63) wave_tot[wave] = incl;
+    if (lane == 63) sh.wave_tot[wave] = incl;
     __syncthreads();
     int excl = incl - tot;
-    for (int w = 0; w < wave; ++w) excl += wave_tot[w];
-    if (excl < rank && rank <= excl + tot) {
-        int rem = rank - excl, q = 0;
+    for (int w = 0; w < wave; ++w) excl += sh.wave_tot[w];
 #pragma unroll
-        for (int t = 0; t < BPT - 1; ++t)
-            if (q == t && rem > c[t]) { rem -= c[t]; q = t + 1; }
-        int cq = c[0];
+    for (int end = 0; end < 2; ++end) {
+        const int rank = end ? r_lo : r_hi;
+        if (excl < rank && rank <= excl + tot) {
+            int rem = rank - excl, q = 0;
 #pragma unroll
-        for (int t = 1; t < BPT; ++t) cq = q == t ? c[t] : cq;
-        const uint32_t width = 1u << T13_LOW, lo = (uint32_t)(T13_BINS - 1 - BPT * tid - q) << T13_LOW;
-        const uint32_t down = (uint32_t)((float)width * ((float)rem - 0.5f) / (float)cq);   // the rem-th of cq keys from the bin's top
-        *sh_key = lo + (width - 1u - (down < width ? down : width - 1u));
+            for (int t = 0; t < BPT - 1; ++t)
+                if (q == t && rem > c[t]) { rem -= c[t]; q = t + 1; }
+            *(end ? &sh.lo : &sh.hi) = (uint32_t)(T13_BINS - 1 - BPT * tid - q);
+            *(end ? &sh.rank_lo : &sh.rank) = rem;
+        }
     }
     __syncthreads();
 }
@@ -632,47 +638,72 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
                                                                  int protect_last, int32_t* __restrict__ idx_out) {
     extern __shared__ __attribute__((aligned(16))) char lsm[];
     int* h13 = reinterpret_cast<int*>(lsm);                                                   // [T13_BINS], the sample's
-    uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);   // [TOPK_WAVES][T13_CW]
+    uint32_t (*sel)[TOPK_THREADS] = reinterpret_cast<uint32_t (*)[TOPK_THREADS]>(lsm);        // [LONG1_WORDS][1024], after the sample
+    uint32_t (*cand)[LONG1_CW] = reinterpret_cast<uint32_t (*)[LONG1_CW]>(lsm + LONG1_BITS);  // [TOPK_WAVES][LONG1_CW], after the sample
     __shared__ TopkShared sh;
     int* const hist = sh.hist;
     scores += (int64_t)blockIdx.x * N;
     idx_out += (int64_t)blockIdx.x * k;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)N;
+    const int per_wave = ((n + TOPK_WAVES - 1) / TOPK_WAVES + LONG_STEP - 1) / LONG_STEP * LONG_STEP;   // a wavefront's slice
     // ---- bracket from the sample: two 16-byte pieces per lane, spread evenly
-    for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
-    __syncthreads();
+    int* const h8 = h13 + T13_BINS;   // two 256-bin histograms
+    uint32_t smp[8];
     {
         const int quads = n / 4;
         f32x4v v[2];
 #pragma unroll
         for (int p = 0; p < 2; ++p)
             v[p] = *reinterpret_cast<const f32x4v*>(scores + 4 * (int64_t)((int64_t)(2 * tid + p) * quads / (LONG1_SAMPLES / 4)));
+        for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
+        if (tid < 512) h8[tid] = 0;
+        __syncthreads();
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) hist_add(h13, true, (int)(order_key(v[p][e]) >> T13_LOW));
+        for (int e = 0; e < 8; ++e) {
+            smp[e] = order_key(v[e >> 2][e & 3]);
+            hist_add(h13, true, (int)(smp[e] >> T13_LOW));
+        }
     }
     __syncthreads();
+    // (the budgets that come here leave at least 79 ranks of the sample above the bracket and below it)
     const float frac = (float)k / (float)n, r = frac * LONG1_SAMPLES, dev = 4.f * sqrtf(r * (1.f - frac)) + 4.f;
-    const int r_hi = (int)(r - dev), r_lo = (int)(r + dev) + 1;
-    if (tid == 0) { sh.hi = 0xFFFFFFFFu; sh.lo = 0u; }
-    __syncthreads();
-    if (r_hi >= 1) sample_key(h13, r_hi, sh.wave_tot, &sh.hi);                   // else nothing lies above the bracket
-    if (r_lo <= LONG1_SAMPLES) sample_key(h13, r_lo, sh.wave_tot, &sh.lo);       // else it has no lower end
-    const uint32_t hi_key = sh.hi, lo_key = sh.lo < sh.hi ? sh.lo : sh.hi, width = hi_key - lo_key;
+    sample_bins(h13, (int)(r - dev), (int)(r + dev) + 1, sh);
+    {
+        const uint32_t bh = sh.hi, bl = sh.lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (smp[e] >> T13_LOW == bh) atomicAdd(&h8[smp[e] >> 11 & 0xFFu], 1);   // a few lanes at most, as a rule
+            if (smp[e] >> T13_LOW == bl) atomicAdd(&h8[256 + (smp[e] >> 11 & 0xFFu)], 1);
+        }
+        __syncthreads();
+        if (wave == 0) pick_bin(h8, lane, 11, bh << T13_LOW, sh.rank, &sh.hi, &sh.rank);
+        if (wave == 1) pick_bin(h8 + 256, lane, 11, bl << T13_LOW, sh.rank_lo, &sh.lo, &sh.rank_lo);
+        __syncthreads();
+    }
+    const uint32_t hi_key = __builtin_amdgcn_readfirstlane(sh.hi) | 0x7FFu, lo_key = __builtin_amdgcn_readfirstlane(sh.lo), width = hi_key - lo_key;
+    const int shift = width >> 21 ? 11 - __builtin_clz(width) : 0;   // lower bits of a distance that do not fit in 21
+    // A wavefront's samples lie in its own slice (or, where slices are rounded up, its neighbour's): the share of them that the
+    // bracket holds, times the slice, has to fit a region (scores in no order of position fill a third of it).
+    bool fits = true;
+    {
+        int in = 0, most = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) in += (int)__popcll(__ballot(smp[e] - lo_key <= width));
+        if (lane == 0) sh.wave_eq[wave] = in;   // (next written two barriers on)
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < TOPK_WAVES; ++w) most = sh.wave_eq[w] > most ? sh.wave_eq[w] : most;
+        fits = most * per_wave <= LONG1_CW * (LONG1_SAMPLES / TOPK_WAVES);
+    }
 
     // ---- the one sweep: wavefront w owns a contiguous slice
-    const int per_wave = ((n + TOPK_WAVES - 1) / TOPK_WAVES + LONG_STEP - 1) / LONG_STEP * LONG_STEP;
     const int lo = wave * per_wave;
     const int hi = lo + per_wave < n ? lo + per_wave : n;   // n % 4 == 0, so a 16-byte load that starts below hi ends below it
     const int last = protect_last ? n - 1 : -1;
-    // Bit 31 - (4 u + e) of word w: element e of the slice's load 8 w + u lies above the bracket (later: is selected).  The words lie
-    // where the sample's histogram was.  A key inside the bracket is kept as (key - lo_key) << 11 | (4 u + e) << 6 | lane; its word
-    // follows from the region's fill at the word's end.
-    uint32_t (*sel)[TOPK_THREADS] = reinterpret_cast<uint32_t (*)[TOPK_THREADS]>(lsm);
-    static_assert(LONG1_WORDS * TOPK_THREADS * 4 <= T13_BINS * 4, "the words fit the histogram's place");
-    const int words = (hi > lo ? hi - lo + 2 * LONG_STEP - 1 : 0) / (2 * LONG_STEP);   // of this wavefront
+    // Bit 31 - (4 u + e) of word w: element e of the slice's load 8 w + u lies above the bracket (later: is selected).  A key inside the bracket is kept as (key - lo_key) >> shift << 11 | (4 u + e) << 6 | lane;
+    // its word follows from the region's fill at the word's end.
+    const int words = (fits && hi > lo ? hi - lo + 2 * LONG_STEP - 1 : 0) / (2 * LONG_STEP);   // of this wavefront; none without a sweep
     int cnt = 0, cgt = 0, word_end[LONG1_WORDS];
 #pragma unroll
     for (int w = 0; w < LONG1_WORDS; ++w) {
@@ -700,7 +731,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
                         gw = (gw << 1) | ((ALL || i0 < hi) && key > hi_key ? 1u : 0u);
                         const uint64_t m = __ballot(in);
                         const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, cnt));
-                        if (in && at < T13_CW) cand[wave][at] = (delta << 11) | (uint32_t)((half * 16 + u * 4 + e) << 6) | (uint32_t)lane;
+                        if (in && at < LONG1_CW) cand[wave][at] = (delta >> shift << 11) | (uint32_t)((half * 16 + u * 4 + e) << 6) | (uint32_t)lane;
                         cnt += (int)__popcll(m);
                     }
                 }
@@ -721,17 +752,23 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     if (lane == 0) { sh.wave_gt[wave] = cgt; sh.wave_in[wave] = cnt; }
     __syncthreads();
     int above = 0, inside = 0;
-    bool fits = width < (1u << 21);
 #pragma unroll
-    for (int w = 0; w < TOPK_WAVES; ++w) { above += sh.wave_gt[w]; inside += sh.wave_in[w]; fits &= sh.wave_in[w] <= T13_CW; }
+    for (int w = 0; w < TOPK_WAVES; ++w) { above += sh.wave_gt[w]; inside += sh.wave_in[w]; fits &= sh.wave_in[w] <= LONG1_CW; }
     if (!fits || (int64_t)above >= k || (int64_t)above + inside < k) {
         __syncthreads();
         topk_long_rows(scores, N, k, protect_last, idx_out, lsm, sh);
         return;
     }
+    auto place = [&](uint32_t c, int j) {   // of region entry j = c, in index order inside the slice: word, load, lane, element
+        int w = 0;
+#pragma unroll
+        for (int q = 0; q < LONG1_WORDS - 1; ++q) w += j >= word_end[q] ? 1 : 0;
+        const uint32_t ue = (c >> 6) & 31u;
+        return ((uint32_t)w << 11) | ((ue >> 2) << 8) | ((c & 63u) << 2) | (ue & 3u);
+    };
     // ---- exact threshold among the keys of the bracket: 8 + 8 + 5 bits of their distance from its lower end
     uint32_t prefix = 0;
-    int64_t need = k - above;
+    int need = (int)(k - above);
     const int cnt64 = (cnt + 63) & ~63;
 #pragma unroll
     for (int pass = 0; pass < 3; ++pass) {
@@ -744,13 +781,44 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
             hist_add(hist, j < cnt && (c & hi_mask) == prefix, (int)((c >> shift) & (pass == 2 ? 0x1Fu : 0xFFu)));
         }
         __syncthreads();
-        if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh.prefix, &sh.need);
+        if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh.prefix, &sh.rank);
         __syncthreads();
         prefix = sh.prefix;
-        need = sh.need;
+        need = sh.rank;
     }
-    const uint32_t T = prefix >> 11;   // the threshold's distance from lo_key
-    const int need_eq = (int)need;
+    uint32_t T = prefix >> 11;   // the threshold's distance from lo_key, as far as the regions keep it
+    if (shift > 0) {
+        // 8 + 3 more bits among the keys that share those 21, then every entry's distance becomes 2 / 1 / 0: above / equal / below
+        auto low_bits = [&](uint32_t c, int j) { return (load_key(scores, lo + (int)place(c, j), N, protect_last) - lo_key) & ((1u << shift) - 1u); };
+        prefix = 0;
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            if (tid < 256) hist[tid] = 0;
+            __syncthreads();
+            for (int j = lane; j < cnt64; j += 64) {
+                const uint32_t c = j < cnt ? cand[wave][j] : 0u;
+                const bool in = j < cnt && c >> 11 == T;
+                const uint32_t d = in ? low_bits(c, j) : 0u;
+                hist_add(hist, in && (pass == 0 || (d & 0x7F8u) == prefix), (int)(pass == 0 ? d >> 3 : d & 7u));
+            }
+            __syncthreads();
+            if (wave == 0) pick_bin(hist, lane, pass == 0 ? 3 : 0, prefix, need, &sh.prefix, &sh.rank);
+            __syncthreads();
+            prefix = sh.prefix;
+            need = sh.rank;
+        }
+        for (int j = lane; j < cnt; j += 64) {
+            const uint32_t c = cand[wave][j];
+            uint32_t order = c >> 11 > T ? 2u : 0u;
+            if (c >> 11 == T) {
+                const uint32_t d = low_bits(c, j);
+                order = d > prefix ? 2u : d == prefix ? 1u : 0u;
+            }
+            cand[wave][j] = (order << 11) | (c & 0x7FFu);
+        }
+        T = 1;
+    }
+    const int need_eq = need;
     int g = 0, ne = 0;
     for (int j = lane; j < cnt64; j += 64) {
         const uint32_t c = j < cnt ? cand[wave][j] >> 11 : 0u;
@@ -764,13 +832,6 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     for (int w = 0; w < TOPK_WAVES; ++w) { eq_before += w < wave ? sh.wave_eq[w] : 0; eq_all += sh.wave_eq[w]; }
     // ---- the bracket's selected keys join the words.  Keys equal to the threshold go by index; they are ranked only where the
     //      selection ends between them.
-    auto place = [&](uint32_t c, int j) {   // index order inside the wavefront: word, load, lane, element
-        int w = 0;
-#pragma unroll
-        for (int q = 0; q < LONG1_WORDS - 1; ++q) w += j >= word_end[q] ? 1 : 0;
-        const uint32_t ue = (c >> 6) & 31u;
-        return ((uint32_t)w << 11) | ((ue >> 2) << 8) | ((c & 63u) << 2) | (ue & 3u);
-    };
     for (int j0 = 0; j0 < cnt64; j0 += 64) {
         const int j = j0 + lane;
         const uint32_t c = j < cnt ? cand[wave][j] : 0u;
@@ -1196,7 +1257,8 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
         }
     }
     else if (!seg.offsets && N % 4 == 0 && N < ((int64_t)1 << 30)) {
-        // the bracket needs sample ranks on both of its sides: budgets between 1/64 and 63/64 of the row
+        // the bracket needs sample ranks on both of its sides: budgets between 1/64 and 63/64 of the row (k = 0.5 % of 512 x 131072: three
+        // sweeps, 152 us)
         if (N <= LONG1_MAX_N && k * 64 >= N && (N - k) * 64 >= N) {
             hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&topk_once_kernel), T13_LDS_BYTES);
             if (e != hipSuccess) return e;

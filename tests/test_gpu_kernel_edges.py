@@ -229,3 +229,56 @@ def test_short_row_topk(torch, n):
             assert got[-1] == -7
             for b in range(len(rows)):
                 assert np.array_equal(got[b * k:(b + 1) * k], orc.topk_select(rows[b], k, protect)), (b, k, protect)
+
+
+def _best_us(torch, call, repeats=7, per=5):
+    """Shortest time of a call among `repeats` runs of `per` calls each."""
+    call()
+    best = float("inf")
+    for _ in range(repeats):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(per):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / per * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("share", [0.05, 0.4, 0.95])
+def test_long_row_topk_time_does_not_depend_on_the_spread(torch, share):
+    """Scores that spread over many octaves, and signed ones, cost what scores within an octave do: one sweep.  (A row that is sampled,
+    swept and then swept three more times takes 1.6 to 2.3 times as long; the bound lies between.)"""
+    rows, n = 512, 131072
+    k = int(share * n)
+    z = torch.randn((rows, n), generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    out = torch.zeros((rows, k), dtype=torch.int32, device="cuda")
+    us = {}
+    for name, s in (("narrow", torch.softmax(0.5 * z, 1)), ("1.5", torch.softmax(1.5 * z, 1)), ("3", torch.softmax(3.0 * z, 1)), ("signed", z)):
+        us[name] = _best_us(torch, lambda: ctx.spts_select_topk_batched(s, n, k, 1, rows, out))
+    assert max(us.values()) <= 1.35 * us["narrow"], us
+
+
+@pytest.mark.parametrize("n", [32772, 70000, 131072])
+def test_long_row_topk_threshold_among_neighbouring_values(torch, n):
+    """Signed scores whose bracket spans zero (its keys do not fit the 21 bits that are kept of them) with a threshold among values that
+    are a few units in the last place apart, single and repeated."""
+    rng = np.random.default_rng(n)
+    s = rng.standard_normal((4, n)).astype(np.float32)
+    for b, (centre, steps) in enumerate(((0.01, 4000), (-0.01, 4000), (0.003, 7), (-1e-30, 300))):
+        at = rng.choice(n, n // 70, replace=False)
+        s[b, at] = (np.float32(centre).view(np.int32) + rng.integers(0, steps, at.size).astype(np.int32)).view(np.float32)
+    sd = torch.from_numpy(s).cuda()
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    for b in range(4):
+        cluster = np.abs(s[b] - np.float32((0.01, -0.01, 0.003, -1e-30)[b])) < 1e-4 * abs((0.01, -0.01, 0.003, -1e-30)[b])
+        above = int((s[b] > s[b][cluster].max()).sum())
+        for inside in (1, n // 300, n // 140, int(cluster.sum())):
+            k = above + inside
+            out = torch.full((4, k), -7, dtype=torch.int32, device="cuda")
+            ctx.spts_select_topk_batched(sd, n, k, 0, 4, out)
+            got = out.cpu().numpy()
+            for row in range(4):
+                assert np.array_equal(got[row], orc.topk_select(s[row], k, 0)), (b, k, row)
