@@ -591,9 +591,9 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __
 // ones (1 in 10^4 of ordinary rows) that turn out not to fit or not to hold the threshold after the sweep.
 // Bound: HBM for one read of the scores and the index list (68 us for 512 rows of 131072, k = 52428, at 5.5 TB/s) and about 25
 // vector instructions per score and wavefront.  Measured there, three sweeps -> this kernel: 196 -> 116 us for scores within an
-// octave, 191 -> 121 for scores over many (log-spread 1.5 to 3), 189 -> 117 for signed normal ones; k = 5 % 182 -> 103, k = 95 % 225 -> 174; all
-// equal or sorted rows, which go back to the sweeps, no slower than those alone (410 -> 381, 349 -> 320: two workgroups per CU now).
-// 16 rows 86 -> 48-50, one of 33000 30 -> 24-27.
+// octave, 191 -> 115 for scores over many (log-spread 1.5 to 3), 189 -> 118 for signed normal ones, 194 -> 148 for fifty values; k = 5 %
+// 182 -> 97, k = 95 % 225 -> 170; all equal or sorted rows, which go back to the sweeps, no slower than those alone (410 -> 385,
+// 349 -> 322: two workgroups per CU now).  16 rows 86 -> 48-51, one of 33000 30 -> 24-27.
 constexpr int LONG1_MAX_N = 131072;                               // one bit per score: 16 KB; longer rows keep to the three sweeps
 constexpr int LONG1_WORDS = LONG1_MAX_N / TOPK_WAVES / 64 / 32;  // 32-score words per lane
 constexpr int LONG1_SAMPLES = 8192;
@@ -827,34 +827,54 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     }
     if (lane == 0) sh.wave_eq[wave] = ne;
     __syncthreads();
-    int eq_before = 0, eq_all = 0;
+    int eq_before = 0;
 #pragma unroll
-    for (int w = 0; w < TOPK_WAVES; ++w) { eq_before += w < wave ? sh.wave_eq[w] : 0; eq_all += sh.wave_eq[w]; }
-    // ---- the bracket's selected keys join the words.  Keys equal to the threshold go by index; they are ranked only where the
-    //      selection ends between them.
-    for (int j0 = 0; j0 < cnt64; j0 += 64) {
-        const int j = j0 + lane;
-        const uint32_t c = j < cnt ? cand[wave][j] : 0u;
-        const bool eq = j < cnt && (c >> 11) == T;
-        const uint32_t at = place(c, j);
-        bool take = j < cnt && (c >> 11) > T;
-        if (eq_all == need_eq) {
-            take |= eq;
-        } else if (__ballot(eq)) {
-            int rank = eq_before;
-            for (int q = 0; q < cnt; ++q) {
-                const uint32_t o = cand[wave][q];
-                if ((o >> 11) == T && place(o, q) < at) ++rank;
-            }
-            take |= eq && rank < need_eq;
-        }
-        if (take) atomicOr(&sel[at >> 11][wave * 64 + ((at >> 2) & 63u)], 1u << (31 - (((at >> 8) & 7u) * 4 + (at & 3u))));
-    }
+    for (int w = 0; w < TOPK_WAVES; ++w) eq_before += w < wave ? sh.wave_eq[w] : 0;
+    // ---- the bracket's selected keys join the words.  Of the keys equal to the threshold the first `eq_taken` of this slice are taken; in
+    //      the one wavefront where that is some but not all, they get words of their own (where the last histogram was) and are
+    //      counted off in index order.
     const int eq_taken = need_eq - eq_before < 0 ? 0 : need_eq - eq_before < ne ? need_eq - eq_before : ne;
+    const bool part = eq_taken > 0 && eq_taken < ne;
+    uint32_t* const eqw = reinterpret_cast<uint32_t*>(hist);   // [LONG1_WORDS][64]
+    static_assert(LONG1_WORDS * 64 <= 256, "the equal keys' words fit the histogram's place");
+    if (part) {
+#pragma unroll
+        for (int w = 0; w < LONG1_WORDS; ++w) eqw[w * 64 + lane] = 0;
+    }
+    for (int j = lane; j < cnt; j += 64) {
+        const uint32_t c = cand[wave][j], at = place(c, j), lane_at = (at >> 2) & 63u, bit = 1u << (31 - (((at >> 8) & 7u) * 4 + (at & 3u)));
+        const bool eq = (c >> 11) == T;
+        if (eq && part) atomicOr(&eqw[(at >> 11) * 64 + lane_at], bit);
+        else if ((c >> 11) > T || (eq && eq_taken > 0)) atomicOr(&sel[at >> 11][wave * 64 + lane_at], bit);
+    }
     if (lane == 0) sh.wave_in[wave] = cgt + g + eq_taken;   // selected scores of this slice
     __syncthreads();
     int out = 0;
     for (int w = 0; w < wave; ++w) out += sh.wave_in[w];
+    if (part) {
+        int seen = 0;
+        for (int w = 0; w < words; ++w) {
+            const uint32_t ew = eqw[w * 64 + lane];
+            uint32_t take = 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                int mine = seen;   // equal keys before this lane's first of load q
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint64_t m = __ballot((ew >> (31 - (q * 4 + e))) & 1u);
+                    mine += lane_prefix_popc(m);
+                    seen += (int)__popcll(m);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t bit = ew & (1u << (31 - (q * 4 + e)));
+                    if (bit && mine < eq_taken) take |= bit;
+                    mine += bit ? 1 : 0;
+                }
+            }
+            sel[w][tid] |= take;
+        }
+    }
 
     // ---- ordered index list from the words; index order inside a load is (lane, element e)
     for (int w = 0; w < words; ++w) {

@@ -282,3 +282,20 @@ def test_long_row_topk_threshold_among_neighbouring_values(torch, n):
             got = out.cpu().numpy()
             for row in range(4):
                 assert np.array_equal(got[row], orc.topk_select(s[row], k, 0)), (b, k, row)
+
+
+@pytest.mark.parametrize("share", [0.05, 0.4, 0.95])
+def test_long_row_topk_time_does_not_depend_on_ties(torch, share):
+    """Scores of fifty values, 2 % of the row each (the selection ends between equal ones), cost what distinct scores do (equal keys ranked
+    one by one took 3 to 7 times as long); and the lowest indices of the last value are the ones taken."""
+    rows, n = 512, 131072
+    k = int(share * n)
+    u = torch.rand((rows, n), generator=torch.Generator(device="cuda").manual_seed(4), device="cuda")
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    out = torch.zeros((rows, k), dtype=torch.int32, device="cuda")
+    distinct = _best_us(torch, lambda: ctx.spts_select_topk_batched(u, n, k, 1, rows, out))
+    s = torch.floor(50.0 * u)
+    tied = _best_us(torch, lambda: ctx.spts_select_topk_batched(s, n, k, 1, rows, out))
+    for row in (0, 7, rows - 1):
+        assert np.array_equal(out[row].cpu().numpy(), orc.topk_select(s[row].cpu().numpy(), k, 1)), row
+    assert tied <= 1.6 * distinct, (tied, distinct)
