@@ -251,14 +251,14 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(GemmArgs a) {
     }
 }
 
-// Rows of whole 16-byte chunks at 16-byte addresses; every epilogue but the merged rotary + store one, no stacked B.
+// Rows of whole 16-byte chunks at 16-byte addresses; every epilogue but the merged rotary + store and the channel-major one, no stacked B.
 bool gemm_tile32_supported(const GemmArgs& a, bool bf16) {
     const int epc = bf16 ? 8 : 4;
     auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     if (a.M <= 0 || a.N <= 0 || a.K <= 0 || a.K % epc != 0 || a.lda % epc != 0 || a.ldb % epc != 0) return false;
     if ((a.M + 31) / 32 > 65535) return false;   // grid y
     if (!al(a.A) || !al(a.B0) || (a.A1 && !al(a.A1)) || (a.B1 && !al(a.B1))) return false;
-    if (a.a_slab || a.b_slab || a.c_slab || a.epi == EPI_ROPE_STORE || (a.epi == EPI_STORE && a.B1)) return false;
+    if (a.a_slab || a.b_slab || a.c_slab || a.epi == EPI_ROPE_STORE || a.epi == EPI_SILU_MUL_T || (a.epi == EPI_STORE && a.B1)) return false;
     if (a.epi == EPI_ROPE && (a.head_dim <= 0 || a.head_dim % 2 != 0 || a.N % a.head_dim != 0 || a.c_is_f32 || a.Ct)) return false;
     if (a.c_is_f32 && a.epi != EPI_STORE) return false;
     return true;
@@ -281,7 +281,7 @@ hipError_t launch_gemm_generic(const GemmArgs& a, bool bf16, hipStream_t s) {
         if (bf16) launch_tile32_t<bf16_t>(a, s); else launch_tile32_t<float>(a, s);
         return hipGetLastError();
     }
-    if (a.epi == EPI_ROPE || a.epi == EPI_ROPE_STORE) return hipErrorInvalidValue;
+    if (a.epi == EPI_ROPE || a.epi == EPI_ROPE_STORE || a.epi == EPI_SILU_MUL_T) return hipErrorInvalidValue;
     dim3 grid((unsigned)((a.N + GT - 1) / GT), (unsigned)((a.M + GT - 1) / GT)), block(256);
     bool dual = a.epi == EPI_SILU_MUL;
     if (bf16) {

@@ -109,7 +109,7 @@ struct GemmArgs {
 // sets *nfull; needs (tiles - nfull) * ksplit * 65536 floats of part32.
 int gemm_pick_split(int64_t M, int32_t N, int32_t K, int epi, int32_t* nfull);
 
-// any shape; EPI_ROPE only where gemm_tile32_supported
+// any shape; EPI_ROPE only where gemm_tile32_supported, never EPI_ROPE_STORE or EPI_SILU_MUL_T (hipErrorInvalidValue)
 hipError_t launch_gemm_generic(const GemmArgs& a, bool bf16, hipStream_t s);
 bool gemm_tile32_supported(const GemmArgs& a, bool bf16);
 // true when the matrix-core kernel can serve these arguments (alignment / divisibility)
