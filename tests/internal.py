@@ -40,3 +40,31 @@ def mfma_supported(a):
 
 def launch_generic(a, bf16, stream=None):
     return _fn("_ZN4spts19launch_gemm_genericERKNS_8GemmArgsEbP12ihipStream_t", C.c_int, _ARGS, C.c_bool, C.c_void_p)(a, bf16, stream)
+
+
+def pick_split(M, N, K, epi):
+    """(ksplit, nfull) of the 256-wide kernel's plan."""
+    nfull = C.c_int32(0)
+    ks = _fn("_ZN4spts15gemm_pick_splitEliiiPi", C.c_int, C.c_int64, C.c_int32, C.c_int32, C.c_int, C.POINTER(C.c_int32))(M, N, K, epi, nfull)
+    return ks, nfull.value
+
+
+def small_pick(a, part_bytes):
+    """(tm, ksplit) of the short-product kernel where the dispatch prefers it to the 256-wide one, else None."""
+    ks, nfull = pick_split(a.M, a.N, a.K, a.epi)
+    plan = SmallPlan()
+    f = _fn("_ZN4spts15gemm_small_pickERKNS_8GemmArgsEiimPNS_13GemmSmallPlanE", C.c_bool, _ARGS, C.c_int, C.c_int, C.c_size_t, C.POINTER(SmallPlan))
+    return (plan.tm, plan.ksplit) if f(a, ks, nfull, part_bytes, plan) else None
+
+
+def small_part_bytes(a, tm, ksplit):
+    return _fn("_ZN4spts21gemm_small_part_bytesERKNS_8GemmArgsERKNS_13GemmSmallPlanE", C.c_size_t, _ARGS, C.POINTER(SmallPlan))(a, SmallPlan(tm, ksplit))
+
+
+def small_supported(a):
+    return _fn("_ZN4spts20gemm_small_supportedERKNS_8GemmArgsE", C.c_bool, _ARGS)(a)
+
+
+def launch_small(a, tm, ksplit, stream):
+    return _fn("_ZN4spts17launch_gemm_smallERKNS_8GemmArgsERKNS_13GemmSmallPlanEP12ihipStream_t", C.c_int, _ARGS, C.POINTER(SmallPlan),
+               C.c_void_p)(a, SmallPlan(tm, ksplit), stream)

@@ -40,3 +40,33 @@ def test_general_gemm_refuses_the_channel_major_epilogue(bf16):
         a = I.GemmArgs(A=A16, lda=K, B0=A16, B1=A16, ldb=K, C=A16, ldc=256, M=40, N=128, K=K, epi=I.EPI_SILU_MUL_T)
         assert not I.tile32_supported(a, bf16)
         assert I.launch_generic(a, bf16) == HIP_INVALID_VALUE
+
+
+def _layer_products(D, QD, KV, Dff, r, d, N, Ma, Mf, P):
+    """The products of one skip layer over N rows with Ma / Mf active ones, as the layer call sets them up (row-major weights)."""
+    def g(M, n, k, epi, **kw):
+        return I.GemmArgs(A=A16, lda=k, B0=A16, ldb=k, C=A16, ldc=n, M=M, N=n, K=k, epi=epi, head_dim=d, rope=A16, **kw)
+    return {"k": g(N, KV, D, I.EPI_ROPE), "probe_q": g(P, QD, D, I.EPI_ROPE),
+            "qv": g(Ma, QD + KV, D, I.EPI_ROPE_STORE, n_split=QD, B1=A16, C2=A16, ldc2=KV, Ct=A16, ldct=(Ma + 255) // 256 * 256, a_idx=A16, a_rows=N),
+            "o": g(Ma, D, QD, I.EPI_RESIDUAL, c_idx=A16), "proxy_in": g(N, 2 * r, D, I.EPI_STORE, B1=A16), "z": g(N, r, Dff, I.EPI_STORE),
+            "gate_up": g(Mf, Dff, D, I.EPI_SILU_MUL, B1=A16, a_idx=A16, a_rows=N), "down": g(Mf, D, Dff, I.EPI_RESIDUAL, c_idx=A16)}
+
+
+def test_short_prompts_reach_every_tile_height_and_both_splits():
+    """Plans of the products of short prompts (8B shape): each tile height is taken unsplit and split, the rotary, merged and
+    residual products are split; a product of many rows stays with the 256-wide tiles.  What the plans compute is in
+    test_gpu_short_products.py."""
+    seen = {}
+    for N in (65, 250, 333, 600, 1025, 2000):
+        for name, a in _layer_products(4096, 4096, 1024, 14336, 256, 128, N, int(0.4 * N), int(0.4 * N), 64).items():
+            assert I.small_supported(a), name
+            plan = I.small_pick(a, 64 << 20)
+            if plan:
+                tm, ks = plan
+                assert tm in (64, 128, 192) and 1 <= ks <= 16 and (ks == 1 or a.K // ks >= 1024) and I.small_part_bytes(a, tm, ks) <= 64 << 20
+                seen.setdefault((tm, ks > 1), set()).add(name)
+    assert {tm for tm, split in seen if not split} == {64, 128, 192} and {tm for tm, split in seen if split} == {64, 128, 192}, seen
+    assert {"k", "qv", "o", "down"} <= set.union(*(names for (_, split), names in seen.items() if split)), seen
+    for name, a in _layer_products(4096, 4096, 1024, 14336, 256, 128, 32768, 13107, 13107, 64).items():
+        if name in ("qv", "o", "gate_up", "down"):
+            assert I.small_pick(a, 64 << 20) is None, name

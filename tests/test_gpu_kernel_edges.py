@@ -95,9 +95,9 @@ def test_layer_of_any_head_dimension(torch, dtype, D, H_, Hkv, d, Dff):
 
 
 # ------------------------------------------------------------------------------------------ short products
-# row counts around the 64 / 128 / 192-row tiles of the short-product GEMM (one row tile, one row more, two tiles), every epilogue it
-# has (rotary d = 128 / 64, merged Q + V with the transposed copy, residual scatter, SiLU, stacked slab-major proxy input), with and
-# without slab-major weights
+# row counts around one and two of the short-product GEMM's tiles, through the layer, with and without slab-major weights.  Products
+# this small all take 64-row tiles, and only down and z are split; every tile height, split and epilogue is in
+# test_gpu_short_products.py
 @pytest.mark.parametrize("pack", [True, False], ids=["packed", "row_major"])
 @pytest.mark.parametrize("H_,Hkv,d", [(8, 2, 128), (8, 4, 64)], ids=["d128", "d64"])
 def test_layer_with_short_products(torch, H_, Hkv, d, pack):
@@ -215,7 +215,7 @@ def test_long_row_topk_patterns(torch, n):
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 333, 511, 512, 513, 1023, 1024, 1025])
 def test_short_row_topk(torch, n):
-    """Around the lengths where the wavefront kernel takes over from the workgroup kernel, and its two sizes."""
+    """Around the lengths where the wavefront kernel (up to 512 scores) and the workgroup kernel meet."""
     rng = np.random.default_rng(n)
     rows = np.stack([np.exp(rng.standard_normal(n)), rng.standard_normal(n), np.full(n, 0.25), np.round(2 * rng.standard_normal(n)),
                      np.where(rng.random(n) < 0.5, -0.0, 0.0), np.full(n, -np.inf)]).astype(np.float32)
