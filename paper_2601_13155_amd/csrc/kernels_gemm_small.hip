@@ -318,6 +318,17 @@ bool gemm_small_supported(const GemmArgs& a) {
 //    and its fp32 tiles written and read at 4 TB/s.
 //  * 256-wide tiles: 0.41 us per slab + up to 0.36 us as the chip fills, a round of 256 tiles after the other, a partly filled
 //    last round split over K as gemm_pick_split plans.
+//  * The fitted products have K >= 4096, so the times per slab carry the epilogues.  Products of fewer than EPI_SLABS slabs (K < 2048) do
+//    not, and get the rest: a start, and the epilogue per 128 rows of every workgroup that a CU runs, or per round of 256-wide
+//    tiles.  Without it short products with many tiles came here too often: of 1095 measured with K < 2048, 66 took more than 2 % longer
+//    than on the 256-wide tiles (up to 50 %; proxy z of 20011 rows on 512 channels 16.6 -> 18.4 us), with it none (0.73 of the
+//    256-wide time on the mean, 0.74 without).
+constexpr double EPI_SLABS = 64.0;
+struct EpilogueTimes { double store, rope, resid, silu; };
+static double short_share(const GemmArgs& a) { return a.K / SBK < EPI_SLABS ? 1.0 - a.K / SBK / EPI_SLABS : 0.0; }
+static double epilogue_time(const EpilogueTimes& e, int epi) {
+    return epi == EPI_SILU_MUL ? e.silu : epi == EPI_RESIDUAL ? e.resid : epi == EPI_STORE ? e.store : e.rope;
+}
 static double small_time(const GemmArgs& a, int tm, int ks) {
     const double lat = tm == 64 ? 0.18 : tm == 128 ? 0.31 : 0.38;
     const int64_t nM = (a.M + tm - 1) / tm, nN = a.N / (a.epi == EPI_SILU_MUL ? SBN / 2 : SBN), units = nM * nN * ks;
@@ -325,17 +336,18 @@ static double small_time(const GemmArgs& a, int tm, int ks) {
     const double rows = tm * (0.35 + 0.65 * (double)a.M / (double)(nM * tm));
     const double slab_kb = (rows + SBN) * SROW / 1024.0;
     const double per_slab = lat > per_cu * slab_kb / 47.0 ? lat : per_cu * slab_kb / 47.0;
-    double t = 2.6 + per_slab * (double)((a.K / SBK + ks - 1) / ks);
-    if (ks > 1) t += 2.5 + (double)units * tm * SBN * 8.0 / 4.0e6;
-    return t;
+    const double t = 2.6 + per_slab * (double)((a.K / SBK + ks - 1) / ks);
+    if (ks > 1) return t + 2.5 + (double)units * tm * SBN * 8.0 / 4.0e6;
+    return t + short_share(a) * (2.5 + per_cu * tm / 128.0 * epilogue_time(EpilogueTimes{5.0, 7.5, 5.5, 3.0}, a.epi));
 }
 static double wide_time(const GemmArgs& a, int ks, int nfull) {
     const int64_t tiles = (a.M + 255) / 256 * (a.N / (a.epi == EPI_SILU_MUL ? 128 : 256));
     const double slabs = a.K / SBK;
     auto per_slab = [](double busy) { return 0.41 + 0.36 * busy / 256.0; };
     const int64_t whole = ks > 1 ? nfull : tiles;
-    double t = 4.6 + (double)(whole / 256) * slabs * per_slab(256);
-    if (const int64_t rem = whole % 256) t += slabs * per_slab(whole > 256 && rem < 160 ? 160 : (double)rem);
+    const double epi = short_share(a) * epilogue_time(EpilogueTimes{9.0, 20.0, 15.0, 6.0}, a.epi);
+    double t = 4.6 + (double)(whole / 256) * (slabs * per_slab(256) + epi);
+    if (const int64_t rem = whole % 256) t += slabs * per_slab(whole > 256 && rem < 160 ? 160 : (double)rem) + epi * (0.3 + 0.7 * (double)rem / 256.0);
     if (ks > 1) {
         const int64_t units = (tiles - nfull) * ks;
         t += (double)((units + 255) / 256) * (double)((int)(slabs + ks - 1) / ks) * per_slab(units < 256 ? (double)units : 256.0) + 5.1 +

@@ -70,3 +70,18 @@ def test_short_prompts_reach_every_tile_height_and_both_splits():
     for name, a in _layer_products(4096, 4096, 1024, 14336, 256, 128, 32768, 13107, 13107, 64).items():
         if name in ("qv", "o", "gate_up", "down"):
             assert I.small_pick(a, 64 << 20) is None, name
+
+
+# products that were measured to be faster on the 256-wide tiles: us there / on the small tiles that a model without the epilogues chose
+@pytest.mark.parametrize("epi,M,N,K", [
+    pytest.param(I.EPI_STORE, 20011, 256, 512, id="16.6_18.4"), pytest.param(I.EPI_STORE, 2643, 4096, 128, id="11.5_16.4"),
+    pytest.param(I.EPI_STORE, 14414, 1280, 256, id="23.3_28.9"), pytest.param(I.EPI_RESIDUAL, 23422, 512, 256, id="20.1_23.7"),
+    pytest.param(I.EPI_RESIDUAL, 1620, 5120, 256, id="19.0_23.0"),
+    pytest.param(I.EPI_ROPE, 38805, 512, 128, id="31.6_37.6"), pytest.param(I.EPI_SILU_MUL, 10405, 512, 128, id="9.8_12.1"),
+    pytest.param(I.EPI_SILU_MUL, 2896, 2816, 128, id="16.5_19.0")])
+def test_products_that_the_wide_tiles_finish_sooner_stay_with_them(epi, M, N, K):
+    a = I.GemmArgs(A=A16, lda=K, B0=A16, ldb=K, C=A16, ldc=N, M=M, N=N, K=K, epi=epi, head_dim=128, rope=A16)
+    if epi == I.EPI_SILU_MUL:
+        a.B1 = A16
+    assert I.small_supported(a)
+    assert I.small_pick(a, 512 << 20) is None
