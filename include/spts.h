@@ -129,7 +129,9 @@ typedef struct spts_ctx spts_ctx;
 int spts_pack_slab32(spts_ctx *ctx, const void *W, int64_t rows, int64_t K, void *out);
 
 /* Bytes of device workspace a context needs to serve calls with N <= max_tokens,
- * probe_len <= max_probe, r <= max_r, Dlow <= max_dlow.  0 on invalid arguments. */
+ * probe_len <= max_probe, r <= max_r, Dlow <= max_dlow.  0 on invalid arguments.  A bf16 context holds at
+ * least 64 MB of it for the partial sums of products that are split over the chip, and any context transposed
+ * values for about 4300 key columns beyond max_tokens, however small its limits are. */
 size_t spts_workspace_bytes(const spts_model_desc *model, int64_t max_tokens, int32_t max_probe,
                             int32_t max_r, int32_t max_dlow);
 

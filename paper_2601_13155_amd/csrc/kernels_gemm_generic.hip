@@ -21,7 +21,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// SPLIT_NONE: one product.  SILU: a second product (A1 / B1).  ROPE: columns c and c + d/2 of a head (B rows d/2 apart).  WIDE:
+// ONE: one product.  SILU: a second product (A1 / B1).  ROPE: columns c and c + d/2 of a head (B rows d/2 apart).  WIDE:
 // columns c and c + 32 (the row sums of squares keep their 64-column blocks).
 enum Tile32Mode : int { T32_ONE, T32_SILU, T32_ROPE, T32_WIDE };
 

@@ -4,19 +4,20 @@
 //  * TM x 128 output tile (TM = 64, 128 or 192), 4 wavefronts (2x2) of TM/2 x 64 = (TM/32) x 4 MFMA 16x16x32 blocks.  32 / 64 / 96
 //    accumulators per lane and a ring of 48 / 80 / 80 KB let two or three workgroups share a CU, which hides one's barriers,
 //    fragment reads and epilogue behind the other's MFMAs; per flop it moves twice the operand bytes of the 256x256 tile, so it
-//    pays only where that one leaves CUs idle or multiplies padding (the rule: gemm_small_plan).
-//  * K in slabs of 32, travelling global memory -> LDS directly into a ring of NST stages: NST - 1 slabs are in flight (64 KB
-//    per workgroup and stage set), which is what keeps HBM busy when the product is bound by reading its weights once.
+//    pays only where that one leaves CUs idle or multiplies padding (the rule: gemm_small_pick).
+//  * K in slabs of 32, travelling global memory -> LDS directly into a ring of NST stages: NST - 1 slabs are in flight (36 / 64 /
+//    60 KB per workgroup), which is what keeps HBM busy when the product is bound by reading its weights once.
 //    Slab-major operands as in kernels_gemm_mfma.hip (whole lines per load instruction), same swizzle, same LDS image.
 //  * Split-K: `ksplit` workgroups share a tile, each leaves its raw fp32 accumulators (fragment order: every store is 1 KB),
 //    small_finish_kernel sums them in split order and applies the epilogue.
 //  * 32-wide column blocks of a wavefront: wavefront column wn, block j covers tile columns j * 64 + wn * 32 (or wn * 64 + j * 32 for
 //    rotary heads of 64), so that block 0 and block 1 are the two members of a rotary pair, or gate and up of a channel: the
-//    dual epilogues combine registers of one lane, also in the finish kernel.
+//    dual epilogues combine registers of one lane, also in the finish kernel.  The epilogue is chosen at run time; its finished
+//    quads pass through 32 bytes of scratch memory per lane, once per product.
 //
-// Measured (us, weights from HBM, 256-wide tiles with their split -> here): 64 rows x 4096 x 4096 27.5 -> 14.6, 133 rows of
-// gate/up 80 -> 60 and of down 46 -> 37 (the weights' HBM time: 39 and 20), K projection of 4096 rows 59 -> 44, proxy z of 512
-// rows 36 -> 16.
+// Measured (us from launch to launch, row-major weights from HBM, 256-wide tiles with their split -> here): 64 rows x 4096 x 4096
+// 30 -> 18 (4 shares of K), 133 rows of gate/up 100 -> 67 and of down 64 -> 41 (the weights' HBM time: 39 and 20), proxy z of 512
+// rows 55 -> 19.
 #include "spts_internal.h"
 
 namespace spts {
@@ -132,8 +133,7 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
     const int lr = lane >> 2;                   // row of the load's 16
     uint32_t oa[LA], ob[LB];
     const char* abase = (const char*)a.A + (a.a_idx ? (int64_t)0 : row0 * a_pitch);
-    // This wavefront's 32 weight rows: which matrix, and from which row of it.  Plain selects: written as an if / else chain this
-    // was compiled (ROCm 7.2) to a path that left the base register unset for the first half of a stacked B.
+    // This wavefront's 32 weight rows: which matrix, and from which row of it (one address for all epilogues, by selects)
     const int rw = wave * 32;
     const bool silu_b = a.epi == EPI_SILU_MUL;
     const bool upper = a.epi == EPI_STORE && a.B1 != nullptr && st.col0 >= a.N / 2;   // stacked B: columns [N/2, N) from B1
@@ -364,9 +364,10 @@ bool gemm_small_pick(const GemmArgs& a, int wide_ksplit, int wide_nfull, size_t 
     for (const int tm : {64, 128, 192})
         for (const int ks : {1, 2, 3, 4, 6, 8, 12, 16}) {
             const GemmSmallPlan p{tm, ks};
-            // Shares of at least 1024: shorter ones save 1-2 us a product (64 x 4096 x 4096: 16.8 us in 4 shares, 14.6 in 8), and
-            // a product with K <= 1024 is then summed the same way whatever its row count (a batched call and the calls one
-            // by one agree bit for bit there).
+            // Shares of at least 1024, at the price of 1-3 us a product (64 x 4096 x 4096: 18.1 us in 4 shares, 15.5 in 8).  A
+            // product with K < 1024 is then never split (gemm_pick_split's shares are 512 at least) and is summed the same way
+            // whatever its row count and whichever kernel takes it: a batched call and the calls one by one agree bit for bit.  From
+            // K = 1024 on the row count decides the shares.
             if (ks > 1 && (a.K / ks < 1024 || gemm_small_part_bytes(a, p) > part_bytes)) break;
             const double t = small_time(a, tm, ks);
             if (t < best) { best = t; *plan = p; found = true; }

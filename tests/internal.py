@@ -68,3 +68,7 @@ def small_supported(a):
 def launch_small(a, tm, ksplit, stream):
     return _fn("_ZN4spts17launch_gemm_smallERKNS_8GemmArgsERKNS_13GemmSmallPlanEP12ihipStream_t", C.c_int, _ARGS, C.POINTER(SmallPlan),
                C.c_void_p)(a, SmallPlan(tm, ksplit), stream)
+
+
+def launch_wide(a, stream):
+    return _fn("_ZN4spts16launch_gemm_mfmaERKNS_8GemmArgsEP12ihipStream_t", C.c_int, _ARGS, C.c_void_p)(a, stream)

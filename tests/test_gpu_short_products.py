@@ -160,3 +160,20 @@ def test_rotary_alone_and_beside_a_stored_product(torch, tm, ksplit, slab, d):
                 assert torch.isnan(v[M:]).all()
                 slots = torch.tensor([_key_slot(i) for i in range(M)], device="cuda")
                 assert torch.equal(vt[:, slots].t(), v[:M]) and torch.isfinite(vt[:, :(M + 63) // 64 * 64]).all()
+
+
+@pytest.mark.parametrize("k", [992, 1024, 4096])
+def test_unsplit_sums_are_those_of_the_256_wide_tiles(torch, k):
+    """Both kernels add a row's products in the same order when K is not split: which one takes a product does not show in its result."""
+    M, N = 300, 512
+    g = torch.Generator(device="cuda").manual_seed(k)
+    A, B = (torch.randn((n, k), generator=g, device="cuda").bfloat16() for n in (M, N))
+    want = torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
+    a = I.GemmArgs(A=A.data_ptr(), lda=k, B0=B.data_ptr(), ldb=k, ldc=N, M=M, N=N, K=k, C=want.data_ptr())
+    stream = torch.cuda.current_stream().cuda_stream
+    assert I.mfma_supported(a) and I.launch_wide(a, stream) == 0
+    for tm in (64, 128, 192):
+        got = torch.zeros_like(want)
+        a.C = got.data_ptr()
+        assert I.launch_small(a, tm, 1, stream) == 0
+        assert torch.equal(got, want), tm
