@@ -429,7 +429,11 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 constexpr int LONG_U = 4;                       // 16-byte loads in flight per lane
 constexpr int LONG_STEP = 64 * 4 * LONG_U;      // scores a wavefront takes per iteration
 
-__device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores, int64_t N, int64_t k, int protect_last, int32_t* __restrict__ idx_out, char* lsm, TopkShared& sh) {
+// HINT: a caller that has reason to believe that the k-th largest key begins with the 16 bits `top16` (>= 0) skips the sweeps and passes before
+// those that resolve the other 16; the counts of the first of them tell when it does not, and all four follow.
+template <bool HINT>
+__device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores, int64_t N, int64_t k, int protect_last, int32_t* __restrict__ idx_out, char* lsm, TopkShared& sh,
+                                               int top16 = -1) {
     int* h13 = reinterpret_cast<int*>(lsm);                                                     // [T13_BINS]
     uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);     // [TOPK_WAVES][T13_CW]
     int (*whist)[256] = reinterpret_cast<int (*)[256]>(lsm + T13_BINS * 4);                     // fallback only, same bytes
@@ -462,29 +466,35 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
 
     uint32_t T = 0;
     int need_eq = 0;
-    // ---- sweep 1: top 13 bits
-    for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
-    if (tid == 0) { sh.over = 0; sh.bin = 0; sh.need = k; }
-    __syncthreads();
-    SPTS_LONG_SWEEP({ hist_add(h13, valid, (int)(key >> T13_LOW)); })
-    __syncthreads();
-    t13_pick(h13, k, sh.wave_tot, &sh.bin, &sh.need);
-    const uint32_t b12 = (uint32_t)sh.bin;
-    int64_t need = sh.need;
-    // ---- sweep 2: the wavefront's keys of that bin into its LDS region (low 19 bits), keys of higher bins counted
+    uint32_t b12 = 0;
+    int64_t need = 0;
     int cnt = 0, cgt = 0;
-    SPTS_LONG_SWEEP({
-        const uint32_t top = key >> T13_LOW;
-        cgt += (int)__popcll(__ballot(valid && top > b12));
-        const bool in = valid && top == b12;
-        const uint64_t m = __ballot(in);
-        const int at = cnt + lane_prefix_popc(m);
-        if (in && at < T13_CW) cand[wave][at] = key & ((1u << T13_LOW) - 1u);
-        cnt += (int)__popcll(m);
-    })
-    if (lane == 0 && cnt > T13_CW) sh.over = 1;
-    __syncthreads();
-    if (sh.over == 0) {
+    bool over = HINT && top16 >= 0;
+    if (!over) {
+        // ---- sweep 1: top 13 bits
+        for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
+        if (tid == 0) { sh.over = 0; sh.bin = 0; sh.need = k; }
+        __syncthreads();
+        SPTS_LONG_SWEEP({ hist_add(h13, valid, (int)(key >> T13_LOW)); })
+        __syncthreads();
+        t13_pick(h13, k, sh.wave_tot, &sh.bin, &sh.need);
+        b12 = (uint32_t)sh.bin;
+        need = sh.need;
+        // ---- sweep 2: the wavefront's keys of that bin into its LDS region (low 19 bits), keys of higher bins counted
+        SPTS_LONG_SWEEP({
+            const uint32_t top = key >> T13_LOW;
+            cgt += (int)__popcll(__ballot(valid && top > b12));
+            const bool in = valid && top == b12;
+            const uint64_t m = __ballot(in);
+            const int at = cnt + lane_prefix_popc(m);
+            if (in && at < T13_CW) cand[wave][at] = key & ((1u << T13_LOW) - 1u);
+            cnt += (int)__popcll(m);
+        })
+        if (lane == 0 && cnt > T13_CW) sh.over = 1;
+        __syncthreads();
+        over = sh.over != 0;
+    }
+    if (!over) {
         int g, e;
         const uint32_t low = t13_resolve(cand[wave], cnt, need, hist, &sh.prefix, &sh.need, &need_eq, &g, &e);
         T = (b12 << T13_LOW) | low;
@@ -492,19 +502,22 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
     } else {
         // ---- fallback: four 8-bit passes over the row
         __syncthreads();   // every wavefront has read sh.over before the regions are reused as histograms
-        if (tid == 0) { sh.prefix = 0; sh.need = k; }
-        uint32_t prefix = 0;
+        uint32_t prefix = HINT && top16 >= 0 ? (uint32_t)top16 << 16 : 0u;
         need = k;
-        cgt = 0;   // last pass: keys of this wavefront's slice whose decided 24 bits exceed the prefix
-        for (int pass = 0; pass < 4; ++pass) {
+        cgt = 0;   // last pass, and the first one after a hint: keys of this wavefront's slice whose decided bits exceed the prefix
+        for (int pass = HINT && top16 >= 0 ? 2 : 0; pass < 4; ++pass) {
+            if (HINT) cgt = 0;
+            const bool hinted = HINT && top16 >= 0 && pass == 2;
             const int shift = 24 - 8 * pass;
             const uint32_t hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
             for (int i = lane; i < 256; i += 64) whist[wave][i] = 0;
             __syncthreads();
             SPTS_LONG_SWEEP({
                 hist_add(whist[wave], valid && (key & hi_mask) == prefix, (int)((key >> shift) & 0xFF));
-                if (pass == 3) cgt += (int)__popcll(__ballot(valid && (key & hi_mask) > prefix));
+                if (pass == 3 || hinted) cgt += (int)__popcll(__ballot(valid && (key & hi_mask) > prefix));
             })
+            if (hinted && lane == 0) sh.wave_gt[wave] = cgt;
+            if (HINT && tid == 0) sh.need = 0;
             __syncthreads();
             if (tid < 256) {
                 int t = 0;
@@ -512,11 +525,19 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
                 for (int w = 0; w < TOPK_WAVES; ++w) t += whist[w][tid];
                 hist[tid] = t;
             }
+            if (hinted) {
+                int above = 0;
+                for (int w = 0; w < TOPK_WAVES; ++w) above += sh.wave_gt[w];
+                need -= __builtin_amdgcn_readfirstlane(above);
+            }
             __syncthreads();
             if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh.prefix, &sh.need);
             __syncthreads();
-            prefix = sh.prefix;
-            need = sh.need;
+            prefix = HINT ? (uint32_t)__builtin_amdgcn_readfirstlane(sh.prefix) : sh.prefix;
+            need = HINT ? __builtin_amdgcn_readfirstlane((int)sh.need) : sh.need;
+            if (HINT && need == 0) {   // no bin holds that rank: not the key's first bits
+                prefix = 0; need = k; top16 = -1; pass = -1;
+            }
         }
         T = prefix;
         need_eq = (int)need;
@@ -576,7 +597,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __
                                                                  int protect_last, int32_t* __restrict__ idx_out) {
     extern __shared__ __attribute__((aligned(16))) char lsm[];
     __shared__ TopkShared sh;
-    topk_long_rows(scores + (int64_t)blockIdx.x * N, N, k, protect_last, idx_out + (int64_t)blockIdx.x * k, lsm, sh);
+    topk_long_rows<false>(scores + (int64_t)blockIdx.x * N, N, k, protect_last, idx_out + (int64_t)blockIdx.x * k, lsm, sh);
 }
 
 // The same rows read from memory once (32768 < N <= LONG1_MAX_N, N % 4 == 0).  A sample of 8192 scores spread over the row gives, through
@@ -587,13 +608,15 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __
 // resolved among those keys, the selected ones set their bits, and the index list is written from the bits.  A region keeps
 // 21 bits of a key's distance from the bracket's lower end; where the bracket is wider, the keys that share the threshold's 21 bits
 // (a handful) are read again for the rest.  Rows of which the sample says that a wavefront's share of the bracket does not fit its region
-// (a few equal values, scores ordered by position) take the three-sweep route of topk_long_rows at once, and so do the rare
-// ones (1 in 10^4 of ordinary rows) that turn out not to fit or not to hold the threshold after the sweep.
+// (a few equal values, scores ordered by position) take the route of topk_long_rows at once, and so do the rare ones (1 in 10^4 of
+// ordinary rows) that turn out not to fit or not to hold the threshold after the sweep; where the bracket's ends share 16 bits (equal
+// values, as a rule), only the last 16 are left to resolve there: two passes and the output instead of seven sweeps.
 // Bound: HBM for one read of the scores and the index list (68 us for 512 rows of 131072, k = 52428, at 5.5 TB/s) and about 25
 // vector instructions per score and wavefront.  Measured there, three sweeps -> this kernel: 196 -> 116 us for scores within an
-// octave, 191 -> 115 for scores over many (log-spread 1.5 to 3), 189 -> 118 for signed normal ones, 194 -> 148 for fifty values; k = 5 %
-// 182 -> 97, k = 95 % 225 -> 170; all equal or sorted rows, which go back to the sweeps, no slower than those alone (410 -> 385,
-// 349 -> 322: two workgroups per CU now).  16 rows 86 -> 48-51, one of 33000 30 -> 24-27.
+// octave, 191 -> 117 for scores over many (log-spread 1.5 to 3), 189 -> 116 for signed normal ones, 194 -> 148 for fifty values, 410 -> 192
+// for equal ones; k = 5 % 182 -> 97, k = 95 % 225 -> 168.  16 rows 86 -> 48-51, of equal values 186 -> 96; one row of 33000 30 -> 24-27.
+// Scores sorted by position pay the sample and the sweeps: 512 rows 349 -> 319 (two workgroups per CU now), 16 rows 160 -> 168, one of
+// 33000 36 -> 43.
 constexpr int LONG1_MAX_N = 131072;                               // one bit per score: 16 KB; longer rows keep to the three sweeps
 constexpr int LONG1_WORDS = LONG1_MAX_N / TOPK_WAVES / 64 / 32;  // 32-score words per lane
 constexpr int LONG1_SAMPLES = 8192;
@@ -603,7 +626,7 @@ struct topk_true { static constexpr bool value = true; };
 struct topk_false { static constexpr bool value = false; };
 
 // all 1024 lanes: the 13-bit bins of the sampled histogram that hold ranks r_hi <= r_lo (1 = largest) and the ranks inside them ->
-// sh.hi / sh.rank and sh.lo / sh.rank_lo; ends with a barrier
+// sh.hi / sh.rank and sh.lo / sh.rank_lo, samples in those bins and the seven around them -> sh.bin, sh.over; ends with a barrier
 __device__ inline void sample_bins(const int* h13, int r_hi, int r_lo, TopkShared& sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int BPT = T13_BINS / TOPK_THREADS;
@@ -629,6 +652,7 @@ __device__ inline void sample_bins(const int* h13, int r_hi, int r_lo, TopkShare
                 if (q == t && rem > c[t]) { rem -= c[t]; q = t + 1; }
             *(end ? &sh.lo : &sh.hi) = (uint32_t)(T13_BINS - 1 - BPT * tid - q);
             *(end ? &sh.rank_lo : &sh.rank) = rem;
+            *(end ? &sh.over : &sh.bin) = tot;
         }
     }
     __syncthreads();
@@ -671,10 +695,18 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     sample_bins(h13, (int)(r - dev), (int)(r + dev) + 1, sh);
     {
         const uint32_t bh = sh.hi, bl = sh.lo;
+        const bool many = sh.bin + sh.over > LONG1_SAMPLES / 2;   // else a few lanes of a wavefront, which need no grouping
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            if (smp[e] >> T13_LOW == bh) atomicAdd(&h8[smp[e] >> 11 & 0xFFu], 1);   // a few lanes at most, as a rule
-            if (smp[e] >> T13_LOW == bl) atomicAdd(&h8[256 + (smp[e] >> 11 & 0xFFu)], 1);
+            const bool eh = smp[e] >> T13_LOW == bh, el = smp[e] >> T13_LOW == bl;
+            const int b8 = (int)(smp[e] >> 11 & 0xFFu);
+            if (many) {
+                hist_add(h8, eh, b8);
+                hist_add(h8 + 256, el, b8);
+            } else {
+                if (eh) atomicAdd(&h8[b8], 1);
+                if (el) atomicAdd(&h8[256 + b8], 1);
+            }
         }
         __syncthreads();
         if (wave == 0) pick_bin(h8, lane, 11, bh << T13_LOW, sh.rank, &sh.hi, &sh.rank);
@@ -756,7 +788,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     for (int w = 0; w < TOPK_WAVES; ++w) { above += sh.wave_gt[w]; inside += sh.wave_in[w]; fits &= sh.wave_in[w] <= LONG1_CW; }
     if (!fits || (int64_t)above >= k || (int64_t)above + inside < k) {
         __syncthreads();
-        topk_long_rows(scores, N, k, protect_last, idx_out, lsm, sh);
+        topk_long_rows<true>(scores, N, k, protect_last, idx_out, lsm, sh, (hi_key ^ lo_key) >> 16 == 0 ? (int)(lo_key >> 16) : -1);
         return;
     }
     auto place = [&](uint32_t c, int j) {   // of region entry j = c, in index order inside the slice: word, load, lane, element

@@ -299,3 +299,40 @@ def test_long_row_topk_time_does_not_depend_on_ties(torch, share):
     for row in (0, 7, rows - 1):
         assert np.array_equal(out[row].cpu().numpy(), orc.topk_select(s[row].cpu().numpy(), k, 1)), row
     assert tied <= 1.6 * distinct, (tied, distinct)
+
+
+@pytest.mark.parametrize("n", [32772, 65536, 131072])
+def test_long_row_topk_of_rows_whose_sample_is_one_value(torch, n):
+    """Rows that look like a single value at the sample's places (two of every few quads): all equal, and with every other score larger,
+    smaller or on both sides, so that the threshold is that value or far from it."""
+    rng = np.random.default_rng(n)
+    quads = n // 4
+    seen = np.zeros(quads, bool)
+    seen[(np.arange(2048, dtype=np.int64) * quads) // 2048] = True
+    seen = np.repeat(seen, 4)[:n]
+    z = rng.standard_normal(n).astype(np.float32)
+    rows = np.stack([np.full(n, 0.25), np.where(seen, 0.25, 1.0 + np.abs(z)), np.where(seen, 0.25, -np.abs(z)), np.where(seen, 0.25, z),
+                     np.where(seen, -0.0, np.where(rng.random(n) < 0.5, 0.0, z))]).astype(np.float32)
+    sd = torch.from_numpy(rows).cuda()
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    for k in (n // 60, int(0.1 * n), int(0.4 * n), int(0.75 * n), n - n // 60):
+        for protect in (0, 1):
+            out = torch.full((len(rows), k), -7, dtype=torch.int32, device="cuda")
+            ctx.spts_select_topk_batched(sd, n, k, protect, len(rows), out)
+            got = out.cpu().numpy()
+            for b in range(len(rows)):
+                assert np.array_equal(got[b], orc.topk_select(rows[b], k, protect)), (b, k, protect)
+
+
+@pytest.mark.parametrize("rows", [16, 512])
+def test_long_row_topk_of_equal_scores_is_cheap(torch, rows):
+    """Rows of equal scores leave the one-sweep route by their sample and need three sweeps (1.7 to 2.0 times the time of distinct scores), not
+    the seven of a row about which nothing is known (3.3 to 4.3 times)."""
+    n, k = 131072, 52428
+    s = torch.full((rows, n), 0.25, device="cuda")
+    u = torch.rand((rows, n), generator=torch.Generator(device="cuda").manual_seed(4), device="cuda")
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    out = torch.zeros((rows, k), dtype=torch.int32, device="cuda")
+    distinct = _best_us(torch, lambda: ctx.spts_select_topk_batched(u, n, k, 1, rows, out))
+    equal = _best_us(torch, lambda: ctx.spts_select_topk_batched(s, n, k, 1, rows, out))
+    assert equal <= 2.5 * distinct, (equal, distinct)
