@@ -95,10 +95,11 @@ __device__ inline void pick_bin(const int* hist, int lane, int shift, uint32_t p
 // fit its region (heavily tied scores) makes the caller fall back to 8-bit passes over all keys.
 constexpr int T13_BINS = 8192;
 constexpr int T13_LOW = 19;
-constexpr int T13_CW = 736;                                              // keys per wavefront region
-constexpr int T13_LDS_BYTES = T13_BINS * 4 + TOPK_WAVES * T13_CW * 4;
-// The small arrays of those kernels.  With the regions they have to stay within half of a CU's 160 KB: at 768 keys per region they
-// did not, and every CU ran one workgroup where the registers allow two (512 rows of 131072, k = 52428: 140 us, now 119).
+// Half of a CU's 160 KB with the small arrays below, so that two workgroups share a CU where the registers allow it (at 80 KB without
+// the arrays they did not: 512 rows of 131072, k = 52428: 140 us, now 119).  The regions take the place of the histogram once the bin is
+// known.
+constexpr int T13_LDS_BYTES = 78 * 1024;
+constexpr int T13_CW = T13_LDS_BYTES / (TOPK_WAVES * 4);                 // keys per wavefront region: 1248
 struct TopkShared {
     int64_t need;
     int hist[256];
@@ -107,6 +108,7 @@ struct TopkShared {
     int bin, over, rank_lo, rank;
 };
 static_assert(T13_LDS_BYTES + sizeof(TopkShared) <= 80 * 1024, "two workgroups share a CU's LDS");
+static_assert(T13_BINS * 4 <= T13_LDS_BYTES && TOPK_WAVES * 256 * 4 <= T13_LDS_BYTES, "the histograms fit");
 
 // all 1024 lanes: from the 8192-bin histogram the bin that holds the k-th largest key (-> *sh_bin) and the rank wanted
 // inside it (-> *sh_need); ends with a barrier
@@ -227,7 +229,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_reg_kernel(const float* __r
                                                                 int protect_last, int32_t* __restrict__ idx_out, TopkSegments seg) {
     extern __shared__ __attribute__((aligned(16))) char lsm[];
     int* h13 = reinterpret_cast<int*>(lsm);                                                   // [T13_BINS]
-    uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);   // [TOPK_WAVES][T13_CW]
+    uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm);                   // [TOPK_WAVES][T13_CW], after the histogram
     __shared__ TopkShared sh;
     int* const hist = sh.hist;
 
@@ -435,8 +437,8 @@ template <bool HINT>
 __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores, int64_t N, int64_t k, int protect_last, int32_t* __restrict__ idx_out, char* lsm, TopkShared& sh,
                                                int top16 = -1) {
     int* h13 = reinterpret_cast<int*>(lsm);                                                     // [T13_BINS]
-    uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm + T13_BINS * 4);     // [TOPK_WAVES][T13_CW]
-    int (*whist)[256] = reinterpret_cast<int (*)[256]>(lsm + T13_BINS * 4);                     // fallback only, same bytes
+    uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm);                     // [TOPK_WAVES][T13_CW], after the histogram
+    int (*whist)[256] = reinterpret_cast<int (*)[256]>(lsm);                                    // 8-bit passes only, same bytes
     int* const hist = sh.hist;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)N;
@@ -615,8 +617,8 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __
 // vector instructions per score and wavefront.  Measured there, three sweeps -> this kernel: 196 -> 116 us for scores within an
 // octave, 191 -> 117 for scores over many (log-spread 1.5 to 3), 189 -> 116 for signed normal ones, 194 -> 148 for fifty values, 410 -> 192
 // for equal ones; k = 5 % 182 -> 97, k = 95 % 225 -> 168.  16 rows 86 -> 48-51, of equal values 186 -> 96; one row of 33000 30 -> 24-27.
-// Scores sorted by position pay the sample and the sweeps: 512 rows 349 -> 319 (two workgroups per CU now), 16 rows 160 -> 168, one of
-// 33000 36 -> 43.
+// Scores sorted by position pay the sample and the sweeps: 512 rows 349 -> 196 (their bin fits the regions now, and two workgroups share a CU), 16
+// rows 160 -> 98, but one of 33000 36 -> 43 and 256 of 65536 66 -> 76.
 constexpr int LONG1_MAX_N = 131072;                               // one bit per score: 16 KB; longer rows keep to the three sweeps
 constexpr int LONG1_WORDS = LONG1_MAX_N / TOPK_WAVES / 64 / 32;  // 32-score words per lane
 constexpr int LONG1_SAMPLES = 8192;

@@ -336,3 +336,17 @@ def test_long_row_topk_of_equal_scores_is_cheap(torch, rows):
     distinct = _best_us(torch, lambda: ctx.spts_select_topk_batched(u, n, k, 1, rows, out))
     equal = _best_us(torch, lambda: ctx.spts_select_topk_batched(s, n, k, 1, rows, out))
     assert equal <= 2.5 * distinct, (equal, distinct)
+
+
+def test_long_row_topk_of_sorted_scores_fits_its_regions(torch):
+    """Sorted normal scores: the threshold's 13-bit bin, about 790 scores, lies in one or two wavefronts' slices and has to fit their regions
+    (1.8 to 2 times the time of the same scores shuffled; 3.5 times by 8-bit passes over the whole row)."""
+    n, k = 131072, 52428
+    z = torch.randn((1, n), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    out = torch.zeros((1, k), dtype=torch.int32, device="cuda")
+    shuffled = _best_us(torch, lambda: ctx.spts_select_topk_batched(z, n, k, 1, 1, out))
+    for s in (torch.sort(z, 1)[0].contiguous(), torch.sort(z, 1, descending=True)[0].contiguous()):
+        us = _best_us(torch, lambda: ctx.spts_select_topk_batched(s, n, k, 1, 1, out))
+        assert np.array_equal(out[0].cpu().numpy(), orc.topk_select(s[0].cpu().numpy(), k, 1))
+        assert us <= 2.6 * shuffled, (us, shuffled)

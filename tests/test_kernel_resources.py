@@ -55,8 +55,7 @@ def _named(kernels, part):
 def test_long_row_topk_leaves_room_for_two_workgroups(kernels):
     """512 long rows are two workgroups per CU: each within half of its 160 KB of LDS and of its registers (8 wavefronts per SIMD)."""
     src = open(os.path.join(CSRC, "kernels_topk.hip")).read()
-    bins, region = (int(re.search(rf"constexpr int {n} = (\d+);", src).group(1)) for n in ("T13_BINS", "T13_CW"))
-    dynamic = bins * 4 + 16 * region * 4
+    dynamic = int(re.search(r"constexpr int T13_LDS_BYTES = (\d+) \* 1024;", src).group(1)) * 1024
     for part in ("topk_long_kernel", "topk_once_kernel"):
         for name, k in _named(kernels, part).items():
             assert k[".group_segment_fixed_size"] + dynamic <= 80 * 1024, name
