@@ -8,7 +8,7 @@
 //    16x16x32 blocks: 128 fp32 accumulators per lane, 32 MFMAs per 12 fragment reads, two wavefronts
 //    per SIMD so that one wavefront's LDS reads, waits and barriers hide behind the other's MFMAs.
 //    The same tile on 32x32x16 instructions has the same LDS traffic and rate on paper.  In a layer (8B shape, kernel
-//    times of one box, 32x32x16 in row order -> 16x16x32 back and forth): gate/up of 13107 rows 2399 -> 2304 us (1336 TFLOP/s), of
+//    times on one GPU, 32x32x16 in row order -> 16x16x32 back and forth): gate/up of 13107 rows 2399 -> 2304 us (1336 TFLOP/s), of
 //    3277 rows 627 -> 595; down 1131 -> 1125 and 325 -> 316; O 361 -> 350 and 109 -> 112; Q+V 470 -> 466 and 128 -> 127.  Products
 //    that power does not bound lose instead (proxy z of 32768 rows, which reads 0.94 GB, 247 -> 262; proxy input of 20011 rows, 158 tiles,
 //    110 -> 112); whole layers gain 2-5 %.
