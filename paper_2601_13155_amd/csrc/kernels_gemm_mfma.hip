@@ -12,13 +12,11 @@
 //    3277 rows 627 -> 595; down 1131 -> 1125 and 325 -> 316; O 361 -> 350 and 109 -> 112; Q+V 470 -> 466 and 128 -> 127.  Products
 //    that power does not bound lose instead (proxy z of 32768 rows, which reads 0.94 GB, 247 -> 262; proxy input of 20011 rows, 158 tiles,
 //    110 -> 112); whole layers gain 2-5 %.
-//  * K is consumed in slabs of 64 (32 when K is not a multiple of 64, or when a second A operand
-//    is staged).  Slabs travel global memory -> LDS directly (global_load_lds_dwordx4: no VGPR
-//    staging, no ds_write instructions) into a ring of 2 LDS stages of 64 KB (4 stages of 32 KB for
-//    slabs of 32, 3 with a second A operand): the loads of the next slab(s) are in flight while the
-//    current one is multiplied.  The wavefront counts its own outstanding slab loads with
-//    s_waitcnt vmcnt(n) and one workgroup barrier per slab publishes a landed slab and frees the
-//    stage consumed before it.
+//  * K is consumed in slabs of 32.  Operands travel global memory -> LDS directly (global_load_lds_dwordx4: no VGPR
+//    staging, no ds_write instructions) into a ring of stages (struct Ring): the loads of the next slabs are in flight while the
+//    current one is multiplied.  The wavefront counts its own outstanding loads with
+//    s_waitcnt vmcnt(n) and a workgroup barrier publishes a landed slab and frees the
+//    stages consumed before it.
 //  * The address of a load is a wavefront-uniform base in SGPRs, advanced along K by scalar adds, plus
 //    a 32-bit per-lane offset fixed for the whole tile, and the steady state is unrolled over the ring
 //    so that LDS stage offsets are immediates: the loop holds no vector address arithmetic (vector
@@ -29,14 +27,18 @@
 //  * A slab of 32 is two steps, one per half of the wavefront's columns.  Fragment reads of the next step are issued
 //    between the MFMAs of the current one (sched_group_barrier pins the interleaving); the barrier sits a few MFMAs
 //    into the last step so that the matrix pipe stays fed while wavefronts meet.
-//  * Slab-major operands.  With row-major operands and slabs of 32 a load instruction takes 64 bytes of each of 16
-//    rows, so every 128-byte line is requested twice (by the loads of two consecutive slabs) and the kernel is bound
-//    by L2 requests (measured: whole-line loads of the same data are 8-9 % faster, per operand).  An operand stored
-//    [K/32][rows][32] (64 bytes per row and slab, neighbouring rows adjacent) makes the same 16 rows 1 KB of whole
-//    lines; only the addresses differ (row pitch 64 bytes, slab pitch rows * 64 bytes), the LDS image and the order
-//    of the products do not.  B: slab-major weight copies (b_slab); A: activations that another kernel of this library
-//    wrote slab-major (a_slab; the SiLU and store epilogues and the split-K finish write such a C on request, c_slab).
-//    Calls with slab operands run the 32-wide, 4-stage instantiation whatever K is.
+//  * Whole cache lines.  A load instruction that takes 64 bytes of each of 16 rows of a row-major operand requests every 128-byte line
+//    twice (with the load of the next slab), and the kernel is bound by L2 requests.  Two ways round it:
+//    (a) slab-major operands, [K/32][rows][32] (64 bytes per row and slab, neighbouring rows adjacent): the same 16 rows are 1 KB of
+//    whole lines; only the addresses differ (row pitch 64 bytes, slab pitch rows * 64 bytes), the LDS image and the order of the
+//    products do not.  B: weight copies (b_slab); A: activations that another kernel of this library wrote that way (a_slab; the SiLU
+//    and store epilogues and the split-K finish write such a C on request, c_slab).
+//    (b) 64 of K at a time: a load takes whole lines of 8 rows.  That costs LDS (32 KB a stage), and with 2 stages of both operands the loads
+//    of the next stage arrive late.  So only the operands that are row-major are wide: A in 3 stages and a slab-major B in 4 stages of
+//    32 (LAY_WIDE_A), or A in 3 and B in 2 (LAY_WIDE_AB) - A, which few workgroups share, comes from far away and gets the depth.
+//    Measured alone (us, 32-wide slabs or 2 stages of 64 -> now): gate/up of 13107 gathered rows, slab-major weights 2294 -> 2140 (1440 TFLOP/s;
+//    slab-major A 2167), of 3276 rows 577 -> 540; K projection of 32768 rows 229 -> 210; the proxy's input of 32768 rows 118 -> 103, of 20011 rows
+//    100 -> 86; with row-major weights gate/up of 13107 rows 2504 -> 2358, down of 8192 rows 803 -> 718, K projection 252 -> 224.
 //  * Rows of A may be gathered through an index list (the active-token gather of Eq. (skip) is
 //    folded into the A loads: a row is 2*K contiguous bytes, so nothing is lost in coalescing),
 //    rows of C may be scattered through one (the residual update X[T] += ...).
@@ -65,14 +67,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 256, BN = 256;
-#ifndef SPTS_GEMM_UNROLL_RING
-#define SPTS_GEMM_UNROLL_RING 1
-#endif
 
-// K slab geometry.  A tile row holds BK bf16 = CPR 16-byte chunks; chunk c of row `row` is stored at
+// LDS image of an operand tile, BK of K wide.  A tile row holds BK bf16 = CPR 16-byte chunks; chunk c of row `row` is stored at
 // chunk position c ^ ((row / RP) % CPR) (RP = rows per 256 bytes), so the 16 lanes of a b128
 // fragment read (16 consecutive rows, same chunk) cover all 64 LDS banks exactly once.
-template <int BK> struct Slab {
+template <int BK> struct Image {
     static constexpr int ROW_BYTES = BK * 2;
     static constexpr int CPR = BK / 8;
     static constexpr int RP = 256 / ROW_BYTES;
@@ -80,6 +79,23 @@ template <int BK> struct Slab {
     static constexpr int ROWS_PER_LOAD = 64 / CPR;   // tile rows moved by one direct-to-LDS load
     __device__ static inline int swz(int row) { return (row / RP) % CPR; }
     __device__ static inline int off(int row, int c) { return row * ROW_BYTES + ((c ^ swz(row)) << 4); }
+};
+
+// How the operands travel.  The loop's unit is a slab of 32 of K; a WIDE operand is moved 64 of K at a time, i.e. whole cache lines of a
+// row-major matrix, and one of its stages serves two slabs.
+enum Layout : int {
+    LAY_SLABS = 0,   // both 32 wide, 4 stages each (3 with a second A operand): slab-major operands, K not a multiple of 64
+    LAY_WIDE_A = 1,  // row-major A 64 wide in 3 stages, slab-major B 32 wide in 4: 96 + 64 KB
+    LAY_WIDE_AB = 2, // both row-major and 64 wide, A in 3 stages and B in 2: 96 + 64 KB.  B, which many workgroups read, comes from L2
+};
+template <int LAY, bool DUAL_A> struct Ring {
+    static constexpr bool AW = LAY != LAY_SLABS, BW = LAY == LAY_WIDE_AB;
+    static constexpr int NSA = AW ? 3 : DUAL_A ? 3 : 4, NSB = BW ? 2 : DUAL_A ? 3 : 4;   // stages
+    using IA = Image<AW ? 64 : 32>;
+    using IB = Image<BW ? 64 : 32>;
+    static constexpr int B0 = NSA * IA::TILE_BYTES, A1 = B0 + NSB * IB::TILE_BYTES;      // where B's and the second A's stages begin
+    static constexpr int BYTES = A1 + (DUAL_A ? NSA * IA::TILE_BYTES : 0);
+    static constexpr int UNROLL = AW ? 12 : 4;                                           // slabs after which every stage number recurs
 };
 
 __device__ inline uint32_t pack_bf16x2(float a, float b) { return cvt_pk_bf16(a, b); }
@@ -105,22 +121,23 @@ __device__ __forceinline__ void tile_of(int id, int nM, int nN, int& tm, int& tn
 // NW wavefronts per workgroup: 4 (2x2 wavefronts of 128x128, one per SIMD) or 8 (4x2 wavefronts of
 // 64x128, two per SIMD: a wavefront's memory instructions, waits and barriers hide behind the other's
 // MFMAs at the price of 50 % more LDS fragment traffic).
-template <int EPI, int BK, bool DUAL_A, int NW>
+template <int EPI, int LAY, bool DUAL_A, int NW>
 __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, int nN, int nfull, int nunits) {
-    using S = Slab<BK>;
+    using R = Ring<LAY, DUAL_A>;
+    using IA = typename R::IA;
+    using IB = typename R::IB;
+    static_assert(!DUAL_A || LAY == LAY_SLABS, "a second A operand travels in slabs of 32");
+    constexpr bool AW = R::AW, BW = R::BW;
+    constexpr int NSA = R::NSA, NSB = R::NSB;
     constexpr int MI = 32 / NW;                   // 16-row blocks per wavefront (8 or 4)
     constexpr int WROWS = 16 * MI;                // output rows per wavefront
     constexpr int LROWS = 256 / NW;               // operand tile rows each wavefront loads
     constexpr bool DUAL = (EPI == EPI_SILU_MUL || EPI == EPI_SILU_MUL_T);
     constexpr bool SEG = (EPI == EPI_ROPE_STORE);   // two products side by side: rotary columns, then stored columns
     constexpr bool CAN_SPLIT = (EPI == EPI_STORE || EPI == EPI_RESIDUAL || EPI == EPI_ROPE || SEG);
-    constexpr int TILE_BYTES = S::TILE_BYTES;
-    constexpr int NOPS = DUAL_A ? 3 : 2;          // operand tiles per stage (A, B[, A1])
-    constexpr int NST = BK == 64 ? 2 : (DUAL_A ? 3 : 4);   // LDS ring stages
-    constexpr int STAGE = TILE_BYTES * NOPS;
-    constexpr int LPO = LROWS / S::ROWS_PER_LOAD; // loads per wavefront per operand tile
-    constexpr int PER = LPO * NOPS;               // direct-to-LDS loads per wavefront per slab
-    constexpr int STEPS = BK / 16;                // multiplication steps per slab: 32 of K times half of the wavefront's columns
+    constexpr int LPA = LROWS / IA::ROWS_PER_LOAD, LPB = LROWS / IB::ROWS_PER_LOAD;   // loads per wavefront per operand tile
+    constexpr int PER = LROWS / 16 * (DUAL_A ? 3 : 2);   // direct-to-LDS loads per wavefront per slab (on average, of a wide operand)
+    constexpr int STEPS = 2;                             // multiplication steps per slab: 32 of K times half of the wavefront's columns
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     // ---- work unit.  Workgroup b runs on XCD b % 8 as that XCD's (b / 8)-th workgroup.  Every XCD
@@ -153,8 +170,8 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     constexpr int OUT_COLS = DUAL ? 128 : 256;   // output columns covered by one tile
     const int col0 = tn * OUT_COLS;
 
-    // ---- direct-to-LDS assignment: wavefront w moves tile rows [64w, 64w+64) of every operand, 16
-    //      (BK=32) or 8 (BK=64) rows = 1 KB per load; lane -> (row, LDS chunk position), and fetches
+    // ---- direct-to-LDS assignment: wavefront w moves tile rows [LROWS * w, LROWS * (w + 1)) of every operand, 16
+    //      (32 wide) or 8 (64 wide) rows = 1 KB per load; lane -> (row, LDS chunk position), and fetches
     //      the global chunk that the swizzle maps to that LDS position.
     // A load's address is a wavefront-uniform base (SGPR pair, advanced along K with scalar adds) plus a
     // 32-bit per-lane byte offset that never changes: no vector instructions for addresses in the loop.
@@ -162,12 +179,12 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     // byte size must then fit 32 bits); the B rows this wavefront moves.
     // Slab-major operands (32-wide slabs): a row of a slab is 64 bytes and consecutive rows are adjacent, so the row
     // pitch is 64 bytes and one slab further on is rows * 64 bytes.
-    const bool a_slab = BK == 32 && a.a_slab, b_slab = BK == 32 && a.b_slab;
+    const bool a_slab = !AW && a.a_slab, b_slab = !BW && a.b_slab;
     const int64_t a_pitch = a_slab ? 64 : a.lda * 2, b_pitch = b_slab ? 64 : a.ldb * 2;      // bytes between rows
     const bool second = SEG && col0 >= a.n_split;   // this tile belongs to the second product (B1 -> C2)
-    const int64_t a_kstep = a_slab ? a.M * 64 : BK * 2;                                              // bytes per slab
-    const int64_t b_kstep = b_slab ? (second ? a.b_rows1 : a.b_rows) * 64 : BK * 2;
-    uint32_t oa[LPO], ob[LPO];
+    const int64_t a_kstep = a_slab ? a.M * 64 : IA::ROW_BYTES;                                       // bytes per tile along K
+    const int64_t b_kstep = b_slab ? (second ? a.b_rows1 : a.b_rows) * 64 : IB::ROW_BYTES;
+    uint32_t oa[LPA], ob[LPB];
     const char* abase = (const char*)a.A + (a.a_idx ? (int64_t)0 : row0 * a_pitch);
     const char* a1base = DUAL_A ? (const char*)a.A1 + (a.a_idx ? (int64_t)0 : row0 * a_pitch) : abase;
     const char* bbase;
@@ -181,29 +198,48 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
         else bbase = (const char*)a.B0 + (int64_t)(col0 + rw) * b_pitch;
     }
 #pragma unroll
-    for (int q = 0; q < LPO; ++q) {
-        const int rl = q * S::ROWS_PER_LOAD + lane / S::CPR;   // row inside the wavefront's share
-        const int r = wave * LROWS + rl;
-        const int c = (lane % S::CPR) ^ S::swz(r);
+    for (int q = 0; q < LPA; ++q) {
+        const int r = wave * LROWS + q * IA::ROWS_PER_LOAD + lane / IA::CPR;
+        const int c = (lane % IA::CPR) ^ IA::swz(r);
         int64_t grow = row0 + r;
         if (grow >= a.M) grow = a.M - 1;  // clamp: duplicates of the last row are never stored
         const int64_t srow = a.a_idx ? (int64_t)a.a_idx[grow] : grow - row0;
         oa[q] = (uint32_t)(srow * a_pitch + c * 16);
+    }
+#pragma unroll
+    for (int q = 0; q < LPB; ++q) {
+        const int rl = q * IB::ROWS_PER_LOAD + lane / IB::CPR;   // row inside the wavefront's share
+        const int c = (lane % IB::CPR) ^ IB::swz(wave * LROWS + rl);
         ob[q] = (uint32_t)((int64_t)rl * b_pitch + c * 16);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
-    const uint32_t lds_w = lds0 + wave * (LROWS * S::ROW_BYTES);   // this wavefront's rows inside an operand tile
-    // load number u (0 .. PER-1) of slab kt_: operand u % NOPS, 16-row group u / NOPS
-#define SPTS_DMA_ONE(kt_, u)                                                                   \
-    {                                                                                          \
-        const uint32_t sb_ = lds_w + ((kt_) % NST) * STAGE + ((u) / NOPS) * 1024;              \
-        const int64_t ks_ = kbeg + (kt_);                                                      \
-        if ((u) % NOPS == 0) dma16s(oa[(u) / NOPS], abase + ks_ * a_kstep, sb_);               \
-        else if ((u) % NOPS == 1) dma16s(ob[(u) / NOPS], bbase + ks_ * b_kstep, sb_ + TILE_BYTES); \
-        else dma16s(oa[(u) / NOPS], a1base + ks_ * a_kstep, sb_ + 2 * TILE_BYTES);             \
+    const uint32_t lds_a = lds0 + wave * (LROWS * IA::ROW_BYTES);           // this wavefront's rows inside an operand tile
+    const uint32_t lds_b = lds0 + R::B0 + wave * (LROWS * IB::ROW_BYTES);
+    // load q of operand tile t_ (counted from this workgroup's share of K): the tile goes to stage t_ % stages
+#define SPTS_DMA_A(t_, q) dma16s(oa[q], abase + (a_t0 + (t_)) * a_kstep, lds_a + ((t_) % NSA) * IA::TILE_BYTES + (q) * 1024);
+#define SPTS_DMA_B(t_, q) dma16s(ob[q], bbase + (b_t0 + (t_)) * b_kstep, lds_b + ((t_) % NSB) * IB::TILE_BYTES + (q) * 1024);
+#define SPTS_DMA_A1(t_, q) dma16s(oa[q], a1base + (a_t0 + (t_)) * a_kstep, lds_a + R::A1 + ((t_) % NSA) * IA::TILE_BYTES + (q) * 1024);
+    // Load number u_ of the PER or fewer that slab kt_ puts in flight.  LAY_SLABS: the slab NS - 1 further on, operands in turn.
+    // LAY_WIDE_A: half of the A tile two pairs of slabs on, and B's slab three on.  LAY_WIDE_AB: the even slab of a pair fetches B's
+    // next tile, the odd one A's next but one.  ISSUE: 1 = all, 2 = B only (A has no tile left).
+#define SPTS_ISSUE(kt_, ISSUE, u_)                                                                           \
+    {                                                                                                        \
+        if (LAY == LAY_SLABS) {                                                                              \
+            constexpr int OPS = DUAL_A ? 3 : 2;                                                              \
+            if ((u_) < PER) {                                                                                \
+                const int q_ = (u_) < PER ? (u_) / OPS : 0;                                                  \
+                if ((u_) % OPS == 0) { SPTS_DMA_A((kt_) + NSA - 1, q_) }                                     \
+                else if ((u_) % OPS == 1) { SPTS_DMA_B((kt_) + NSA - 1, q_) }                                \
+                else { SPTS_DMA_A1((kt_) + NSA - 1, q_) }                                                    \
+            }                                                                                                \
+        } else if (LAY == LAY_WIDE_A) {                                                                      \
+            if ((u_) < LPB) { SPTS_DMA_B((kt_) + 3, ((u_) < LPB ? (u_) : 0)) }                               \
+            else if ((ISSUE) == 1 && (u_) < LPB + LPA / 2) { SPTS_DMA_A(((kt_) >> 1) + 2, (((kt_) & 1) * (LPA / 2) + ((u_) < LPB + LPA / 2 ? (u_) - LPB : 0))) } \
+        } else {                                                                                             \
+            if (((kt_) & 1) == 0) { if ((u_) < LPB) { SPTS_DMA_B(((kt_) >> 1) + 1, ((u_) < LPB ? (u_) : 0)) } } \
+            else if ((ISSUE) == 1 && (u_) < LPA) { SPTS_DMA_A(((kt_) >> 1) + 2, ((u_) < LPA ? (u_) : 0)) }   \
+        }                                                                                                    \
     }
-#define SPTS_DMA_SLAB(kt_)                                                                     \
-    { _Pragma("unroll") for (int u_ = 0; u_ < PER; ++u_) SPTS_DMA_ONE(kt_, u_) }
 
     f32x4 acc[MI][8];
 #pragma unroll
@@ -216,26 +252,27 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     // B tile row of this wavefront's N block j (16 columns)
     auto brow = [&](int j) { return DUAL ? (j >> 2) * 128 + wn * 64 + (j & 3) * 16 : wn * 128 + j * 16; };
 
-    // A fragment is 16 rows of 32 K elements.  Step st of a slab multiplies the A fragments of its 32-wide piece st / 2 by the B
-    // fragments of columns 64 * (st % 2) .. + 63 of the wavefront's.
+    // A fragment is 16 rows of 32 K elements.  Step st of a slab multiplies its A fragments by the B fragments of columns
+    // 64 * st .. + 63 of the wavefront's.
     bf16x8 af[2][MI], af1[DUAL_A ? MI : 1], bfr[2][4];
-#define SPTS_LOAD_A(buf, stage, ks)                                                                          \
+    // The fragments of slab kt_ sit in the 32-wide piece kt_ % 2 of a wide operand's stage.
+#define SPTS_LOAD_A(buf, kt_)                                                                                \
     {                                                                                                        \
-        const char* sA_ = smem + (stage) * STAGE;                                                            \
+        const char* sA_ = smem + (AW ? ((kt_) >> 1) % NSA : (kt_) % NSA) * IA::TILE_BYTES;                   \
         _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                       \
-            af[buf][i] = *reinterpret_cast<const bf16x8*>(sA_ + S::off(wm * WROWS + i * 16 + l16, (ks) * 4 + lq)); \
+            af[buf][i] = *reinterpret_cast<const bf16x8*>(sA_ + IA::off(wm * WROWS + i * 16 + l16, (AW ? ((kt_) & 1) * 4 : 0) + lq)); \
     }
-#define SPTS_LOAD_A1(stage, ks)                                                                              \
+#define SPTS_LOAD_A1(kt_)                                                                                    \
     {                                                                                                        \
-        const char* sA1_ = smem + (stage) * STAGE + 2 * TILE_BYTES;                                          \
+        const char* sA1_ = smem + R::A1 + ((kt_) % NSA) * IA::TILE_BYTES;                                    \
         _Pragma("unroll") for (int i = 0; i < (DUAL_A ? MI : 0); ++i)                                        \
-            af1[i] = *reinterpret_cast<const bf16x8*>(sA1_ + S::off(wm * WROWS + i * 16 + l16, (ks) * 4 + lq)); \
+            af1[i] = *reinterpret_cast<const bf16x8*>(sA1_ + IA::off(wm * WROWS + i * 16 + l16, lq));        \
     }
-#define SPTS_LOAD_B(half, stage, ks)                                                                         \
+#define SPTS_LOAD_B(half, kt_)                                                                               \
     {                                                                                                        \
-        const char* sB_ = smem + (stage) * STAGE + TILE_BYTES;                                               \
+        const char* sB_ = smem + R::B0 + (BW ? ((kt_) >> 1) % NSB : (kt_) % NSB) * IB::TILE_BYTES;           \
         _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                        \
-            bfr[half][j] = *reinterpret_cast<const bf16x8*>(sB_ + S::off(brow((half) * 4 + j) + l16, (ks) * 4 + lq)); \
+            bfr[half][j] = *reinterpret_cast<const bf16x8*>(sB_ + IB::off(brow((half) * 4 + j) + l16, (BW ? ((kt_) & 1) * 4 : 0) + lq)); \
     }
     // MFMA m of a step: block row m / 4, block columns back and forth, so that each instruction shares an operand with the one before
 #define SPTS_MJ(m) (((m) / 4) & 1 ? 3 - (m) % 4 : (m) % 4)
@@ -248,99 +285,133 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_kernel(GemmArgs a, int nM, 
     }
     constexpr int NM = 4 * MI;                            // MFMAs per step
     constexpr int HS = NM / 2;                            // MFMA slots per half step
-    constexpr int NR_ODD = DUAL_A ? MI + 4 : 4;           // fragment reads for a step of the second columns / of the first
-    constexpr int NR_EVEN = MI + 4;
+    constexpr int NR_ODD = DUAL_A ? MI + 4 : 4;           // fragment reads for the step of the second columns
 
-    // K slabs of this workgroup: all of them, or the split's share (the first nk_all % ksplit splits
-    // take one slab more)
-    const int nk_all = a.K / BK;
-    const int nk = nk_all / ksplit + (split < nk_all % ksplit ? 1 : 0);
-    const int kbeg = split * (nk_all / ksplit) + (split < nk_all % ksplit ? split : nk_all % ksplit);
-    // ---- prologue: slabs 0 .. NST-2 are put in flight, slab 0 must have landed
-    {
-        const int npre = nk < NST - 1 ? nk : NST - 1;
-        for (int t = 0; t < npre; ++t) SPTS_DMA_SLAB(t)
-        if (npre == NST - 1) { SPTS_WAIT_VMCNT((NST - 2) * PER); } else { SPTS_WAIT_VMCNT(0); }   // slab 0 landed
+    // K tiles of this workgroup: all of them, or the split's share (the first `units % ksplit` splits take one more); a unit is a slab,
+    // or a pair of slabs where an operand is wide
+    const int units = a.K / (AW ? 64 : 32);
+    const int my_units = units / ksplit + (split < units % ksplit ? 1 : 0);
+    const int unit0 = split * (units / ksplit) + (split < units % ksplit ? split : units % ksplit);
+    const int nk = AW ? 2 * my_units : my_units;             // slabs
+    const int64_t a_t0 = unit0, b_t0 = AW && !BW ? 2 * (int64_t)unit0 : unit0;   // first tile of A, of B
+    // ---- prologue: what the ring holds ahead of slab 0, slab 0's operands first; they must have landed
+    if (LAY == LAY_SLABS) {
+        const int npre = nk < NSA - 1 ? nk : NSA - 1;
+        for (int t = 0; t < npre; ++t) {
+            _Pragma("unroll") for (int q = 0; q < LPA; ++q) {
+                SPTS_DMA_A(t, q)
+                SPTS_DMA_B(t, q)
+                if (DUAL_A) SPTS_DMA_A1(t, q)
+            }
+        }
+        if (npre == NSA - 1) { SPTS_WAIT_VMCNT((NSA - 2) * PER); } else { SPTS_WAIT_VMCNT(0); }
+    } else {
+        _Pragma("unroll") for (int q = 0; q < LPA; ++q) SPTS_DMA_A(0, q)
+        _Pragma("unroll") for (int q = 0; q < LPB; ++q) SPTS_DMA_B(0, q)
+        if (!BW) { _Pragma("unroll") for (int q = 0; q < LPB; ++q) SPTS_DMA_B(1, q) }
+        if (nk > 2) {
+            _Pragma("unroll") for (int q = 0; q < LPA; ++q) SPTS_DMA_A(1, q)
+            if (!BW) { _Pragma("unroll") for (int q = 0; q < LPB; ++q) SPTS_DMA_B(2, q) }
+            SPTS_WAIT_VMCNT(LPA + (BW ? 0 : 2 * LPB));
+        } else { SPTS_WAIT_VMCNT(0); }
     }
     __syncthreads();
-    SPTS_LOAD_A(0, 0, 0)
-    SPTS_LOAD_B(0, 0, 0)
+    SPTS_LOAD_A(0, 0)
+    SPTS_LOAD_B(0, 0)
 
-    // One K slab = STEPS steps of 16 MFMAs per wavefront.  Every memory instruction sits in the
-    // shadow of an MFMA (an MFMA occupies the matrix pipe for 16 cycles while the wavefront may
+    // One slab of 32 = two steps of 16 MFMAs per wavefront.  Every memory instruction sits in the
+    // shadow of an MFMA (an MFMA occupies the matrix pipe for 8 cycles while the wavefront may
     // issue other work):
-    //   step s < STEPS-1: the first half's MFMAs are interleaved with the fragment reads of step s+1,
-    //                     the second half's with direct-to-LDS loads of slab kt+NST-1 (ISSUE);
-    //   last step: a quarter of the MFMAs, then wait for this wavefront's share of slab kt+1 and meet the
-    //              workgroup (slab kt+1 is published, stage kt%NST is free for the next iteration),
-    //              then the other MFMAs, interleaved with the first fragment reads of slab kt+1.
-    // ISSUE / NEXT / PAR (buffer of the slab's first A fragments) / COPY (hand the next slab its A fragments in buffer 0) are
+    //   first step: the first half's MFMAs are interleaved with the fragment reads of the second step, the second half's with the
+    //               direct-to-LDS loads (ISSUE);
+    //   last step:  a quarter of the MFMAs, then (SYNC) wait for this wavefront's share of the next slab and meet the
+    //               workgroup (the next slab is published, the stages read last by this one are free from here on),
+    //               then the other MFMAs, interleaved with the first fragment reads of the next slab.
+    // The loads of the two slabs behind the one being published may still be in flight (WAITN).  The even slab of a pair of wide
+    // operands publishes and frees nothing (SYNC false).
+    // ISSUE / SYNC / NEXT / PAR (buffer of the slab's A fragments) / COPY (hand the next slab its A fragments in buffer 0) are
     // literal constants at every expansion.
-#define SPTS_SLAB(kt_, ISSUE, NEXT, WAITN, PAR, COPY)                                                        \
+#define SPTS_SLAB(kt_, ISSUE, SYNC, NEXT, WAITN, PAR, COPY)                                                  \
     {                                                                                                        \
-        const int st_ = (kt_) % NST;                                                                         \
-        _Pragma("unroll") for (int s_ = 0; s_ + 1 < STEPS; ++s_) {                                           \
-            const int ab_ = ((s_ >> 1) + (PAR)) & 1;                                                         \
-            if (s_ & 1) { SPTS_LOAD_A(ab_ ^ 1, st_, (s_ + 1) >> 1) SPTS_LOAD_B(0, st_, (s_ + 1) >> 1) }      \
-            else { SPTS_LOAD_B(1, st_, s_ >> 1) SPTS_LOAD_A1(st_, s_ >> 1) }                                 \
-            _Pragma("unroll") for (int m_ = 0; m_ < HS; ++m_) SPTS_MFMA(ab_, s_ & 1, m_)                     \
-            if (s_ & 1) {                                                                                    \
-                _Pragma("unroll") for (int g_ = 0; g_ < HS; ++g_) {                                          \
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
-                    __builtin_amdgcn_sched_group_barrier(0x100, (NR_EVEN + HS - 1) / HS, 0);                 \
-                }                                                                                            \
-            } else {                                                                                         \
-                _Pragma("unroll") for (int g_ = 0; g_ < HS; ++g_) {                                          \
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
-                    __builtin_amdgcn_sched_group_barrier(0x100, (NR_ODD + HS - 1) / HS, 0);                  \
-                }                                                                                            \
-            }                                                                                                \
-            __builtin_amdgcn_sched_barrier(0);                                                               \
-            _Pragma("unroll") for (int m_ = HS; m_ < NM; ++m_) {                                             \
-                SPTS_MFMA(ab_, s_ & 1, m_)                                                                   \
-                if (ISSUE) {                                                                                 \
-                    const int u_ = s_ * HS + m_ - HS;                                                        \
-                    __builtin_amdgcn_sched_barrier(0);                                                       \
-                    if (u_ < PER) SPTS_DMA_ONE((kt_) + NST - 1, (u_ < PER ? u_ : 0))                         \
-                    __builtin_amdgcn_sched_barrier(0);                                                       \
-                }                                                                                            \
+        constexpr int ab_ = (PAR);                                                                           \
+        SPTS_LOAD_B(1, kt_)                                                                                  \
+        SPTS_LOAD_A1(kt_)                                                                                    \
+        _Pragma("unroll") for (int m_ = 0; m_ < HS; ++m_) SPTS_MFMA(ab_, 0, m_)                              \
+        _Pragma("unroll") for (int g_ = 0; g_ < HS; ++g_) {                                                  \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                               \
+            __builtin_amdgcn_sched_group_barrier(0x100, (NR_ODD + HS - 1) / HS, 0);                          \
+        }                                                                                                    \
+        __builtin_amdgcn_sched_barrier(0);                                                                   \
+        _Pragma("unroll") for (int m_ = HS; m_ < NM; ++m_) {                                                 \
+            SPTS_MFMA(ab_, 0, m_)                                                                            \
+            if (ISSUE) {                                                                                     \
+                __builtin_amdgcn_sched_barrier(0);                                                           \
+                SPTS_ISSUE(kt_, ISSUE, m_ - HS)                                                              \
+                __builtin_amdgcn_sched_barrier(0);                                                           \
             }                                                                                                \
         }                                                                                                    \
-        {                                                                                                    \
-            const int ab_ = (((STEPS - 1) >> 1) + (PAR)) & 1;                                                \
-            _Pragma("unroll") for (int m_ = 0; m_ < NM / 4; ++m_) SPTS_MFMA(ab_, 1, m_)                      \
+        _Pragma("unroll") for (int m_ = 0; m_ < NM / 4; ++m_) SPTS_MFMA(ab_, 1, m_)                          \
+        if (SYNC) {                                                                                          \
             if (NEXT) { SPTS_WAIT_VMCNT(WAITN); }                                                            \
             __syncthreads();                                                                                 \
-            if (NEXT) { SPTS_LOAD_A(ab_ ^ 1, ((kt_) + 1) % NST, 0) SPTS_LOAD_B(0, ((kt_) + 1) % NST, 0) }    \
-            _Pragma("unroll") for (int m_ = NM / 4; m_ < NM; ++m_) SPTS_MFMA(ab_, 1, m_)                     \
-            if (NEXT) {                                                                                      \
-                _Pragma("unroll") for (int g_ = 0; g_ < NM - NM / 4; ++g_) {                                 \
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                       \
-                }                                                                                            \
+        }                                                                                                    \
+        if (NEXT) { SPTS_LOAD_A(ab_ ^ 1, (kt_) + 1) SPTS_LOAD_B(0, (kt_) + 1) }                              \
+        _Pragma("unroll") for (int m_ = NM / 4; m_ < NM; ++m_) SPTS_MFMA(ab_, 1, m_)                         \
+        if (NEXT) {                                                                                          \
+            _Pragma("unroll") for (int g_ = 0; g_ < NM - NM / 4; ++g_) {                                     \
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                           \
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                           \
             }                                                                                                \
-            __builtin_amdgcn_sched_barrier(0);                                                               \
-            if (NEXT && (COPY) && ab_ == 0) {                                                                \
-                _Pragma("unroll") for (int i = 0; i < MI; ++i) af[0][i] = af[1][i];                          \
-            }                                                                                                \
+        }                                                                                                    \
+        __builtin_amdgcn_sched_barrier(0);                                                                   \
+        if (NEXT && (COPY)) {                                                                                \
+            _Pragma("unroll") for (int i = 0; i < MI; ++i) af[0][i] = af[1][i];                              \
         }                                                                                                    \
     }
 
-    int kt = 0;
-    // steady state: slab kt+NST-1 exists; after its loads are issued the slabs behind kt+1 in flight
-    // are kt+2 .. kt+NST-1.  First in groups of NST slabs, where the ring stage of every slab is a
+    // Steady state, first in groups of UNROLL slabs, where the ring stage of every slab is a
     // compile-time constant and the LDS addresses of the fragment reads need no arithmetic in the loop.
-    if (SPTS_GEMM_UNROLL_RING && (NST & (NST - 1)) == 0) {
-        int kb = 0;
-        for (; kb * NST + 2 * NST - 2 < nk; ++kb) {
-            _Pragma("unroll") for (int u = 0; u < NST; ++u) SPTS_SLAB(kb * NST + u, true, true, (NST - 2) * PER, STEPS == 2 ? (u & 1) : 0, false)
+    int kt = 0;
+    if (LAY == LAY_SLABS) {
+        // after the loads of slab kt + NSA - 1 are issued the slabs behind kt + 1 in flight are kt + 2 .. kt + NSA - 1
+        if (NSA == 4) {
+            int kb = 0;
+            for (; kb * 4 + 6 < nk; ++kb) {
+                _Pragma("unroll") for (int u = 0; u < 4; ++u) {
+                    if (u & 1) SPTS_SLAB(kb * 4 + u, 1, true, true, (NSA - 2) * PER, 1, false)
+                    else SPTS_SLAB(kb * 4 + u, 1, true, true, (NSA - 2) * PER, 0, false)
+                }
+            }
+            kt = kb * 4;
         }
-        kt = kb * NST;
+        for (; kt + NSA - 1 < nk; ++kt) SPTS_SLAB(kt, 1, true, true, (NSA - 2) * PER, 0, true)
+        // drain: nothing left to issue; wait for everything that is still in flight
+        for (; kt + 1 < nk; ++kt) SPTS_SLAB(kt, 0, true, true, 0, 0, true)
+        SPTS_SLAB(kt, 0, true, false, 0, 0, false)
+    } else {
+        // a pair of slabs whose A tile two pairs on exists; LAY_WIDE_A: at the end of a slab the loads of it and of the one before may
+        // be in flight, LAY_WIDE_AB: at the end of a pair those of its odd slab
+        constexpr int W = BW ? LPA : 2 * PER;
+        int kb = 0;
+        for (; kb * R::UNROLL + R::UNROLL + 4 <= nk; ++kb) {
+            _Pragma("unroll") for (int u = 0; u < R::UNROLL; u += 2) {
+                SPTS_SLAB(kb * R::UNROLL + u, 1, !BW, true, W, 0, false)
+                SPTS_SLAB(kb * R::UNROLL + u + 1, 1, true, true, W, 1, false)
+            }
+        }
+        for (kt = kb * R::UNROLL; kt + 4 < nk; kt += 2) {
+            SPTS_SLAB(kt, 1, !BW, true, W, 0, false)
+            SPTS_SLAB(kt + 1, 1, true, true, W, 1, false)
+        }
+        // the last two pairs: A is all in flight or landed, B's last slab (last tile) is still to be fetched
+        if (nk > 2) {
+            SPTS_SLAB(kt, 2, !BW, true, PER + LPB, 0, false)
+            SPTS_SLAB(kt + 1, 0, true, true, BW ? 0 : LPB, 1, false)
+            kt += 2;
+        }
+        SPTS_SLAB(kt, 0, !BW, true, 0, 0, false)
+        SPTS_SLAB(kt + 1, 0, true, false, 0, 1, false)
     }
-    for (; kt + NST - 1 < nk; ++kt) SPTS_SLAB(kt, true, true, (NST - 2) * PER, 0, true)
-    // drain: nothing left to issue; wait for everything that is still in flight
-    for (; kt + 1 < nk; ++kt) SPTS_SLAB(kt, false, true, 0, 0, true)
-    SPTS_SLAB(kt, false, false, 0, 0, true)
 
     // ---- epilogue.  acc[i][j][r]: row = row0 + wm*WROWS + i*16 + l16, column (inside the wavefront's share) =
     //      16*j + 4*lq + r  -> 4 consecutive columns per block.
@@ -553,7 +624,7 @@ bool gemm_mfma_supported(const GemmArgs& a) {
     return true;
 }
 
-template <int EPI, int BK, bool DUAL_A, int NW>
+template <int EPI, int LAY, bool DUAL_A, int NW>
 static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
     const int ncols = EPI == EPI_SILU_MUL || EPI == EPI_SILU_MUL_T ? 128 : 256;
     const int nM = (int)((a.M + BM - 1) / BM), nN = a.N / ncols;
@@ -562,13 +633,23 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
     const int nfull = split ? a.nfull : tiles;
     const int nunits = split ? (tiles - nfull) * a.ksplit : 0;
     const int grid = 8 * ((nfull + 7) / 8 + (nunits + 7) / 8);
-    const size_t lds = (size_t)Slab<BK>::TILE_BYTES * (DUAL_A ? 3 : 2) * (BK == 64 ? 2 : (DUAL_A ? 3 : 4));
+    const size_t lds = Ring<LAY, DUAL_A>::BYTES;
     {
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_mfma_kernel<EPI, BK, DUAL_A, NW>), (int)lds);
+        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_mfma_kernel<EPI, LAY, DUAL_A, NW>), (int)lds);
         if (e != hipSuccess) return e;
     }
-    gemm_mfma_kernel<EPI, BK, DUAL_A, NW><<<dim3(grid), dim3(NW * 64), lds, s>>>(a, nM, nN, nfull, nunits);
+    gemm_mfma_kernel<EPI, LAY, DUAL_A, NW><<<dim3(grid), dim3(NW * 64), lds, s>>>(a, nM, nN, nfull, nunits);
     return hipGetLastError();
+}
+
+template <int EPI, int NW>
+static hipError_t launch_layout(const GemmArgs& a, hipStream_t s) {
+    constexpr bool B_SLABS = EPI != EPI_SUMSQ;   // which is refused with a slab-major B
+    if (a.a_slab || a.K % 64 != 0) return launch_t<EPI, LAY_SLABS, false, NW>(a, s);
+    if constexpr (B_SLABS) {
+        if (a.b_slab) return launch_t<EPI, LAY_WIDE_A, false, NW>(a, s);
+    }
+    return launch_t<EPI, LAY_WIDE_AB, false, NW>(a, s);
 }
 
 // ---- tail split-K second pass: one thread per FIN_U accumulator-fragment quads (4 consecutive columns of FIN_U rows 16 apart) of a
@@ -700,19 +781,15 @@ int gemm_pick_split(int64_t M, int32_t N, int32_t K, int epi, int32_t* nfull) {
 
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
     constexpr int NW = SPTS_GEMM_NW;
-    const bool slab = a.a_slab || a.b_slab;   // slab-major operands exist for 32-wide slabs only
     hipError_t e;
     switch (a.epi) {
-        case EPI_STORE: e = (a.K % 64 == 0 && !slab ? launch_t<EPI_STORE, 64, false, NW>(a, s) : launch_t<EPI_STORE, 32, false, NW>(a, s)); break;
-        case EPI_RESIDUAL: e = (a.K % 64 == 0 && !slab ? launch_t<EPI_RESIDUAL, 64, false, NW>(a, s) : launch_t<EPI_RESIDUAL, 32, false, NW>(a, s)); break;
-        case EPI_SUMSQ: e = (a.K % 64 == 0 ? launch_t<EPI_SUMSQ, 64, false, NW>(a, s) : launch_t<EPI_SUMSQ, 32, false, NW>(a, s)); break;
-        case EPI_ROPE: e = (a.K % 64 == 0 && !slab ? launch_t<EPI_ROPE, 64, false, NW>(a, s) : launch_t<EPI_ROPE, 32, false, NW>(a, s)); break;
-        case EPI_ROPE_STORE: e = (a.K % 64 == 0 && !slab ? launch_t<EPI_ROPE_STORE, 64, false, NW>(a, s) : launch_t<EPI_ROPE_STORE, 32, false, NW>(a, s)); break;
-        case EPI_SILU_MUL:
-            if (a.A1) e = launch_t<EPI_SILU_MUL, 32, true, NW>(a, s);
-            else e = launch_t<EPI_SILU_MUL, 32, false, NW>(a, s);   // 4 stages of 32 measured 2 % faster here than 2 of 64
-            break;
-        case EPI_SILU_MUL_T: e = launch_t<EPI_SILU_MUL_T, 32, false, NW>(a, s); break;
+        case EPI_STORE: e = launch_layout<EPI_STORE, NW>(a, s); break;
+        case EPI_RESIDUAL: e = launch_layout<EPI_RESIDUAL, NW>(a, s); break;
+        case EPI_SUMSQ: e = launch_layout<EPI_SUMSQ, NW>(a, s); break;
+        case EPI_ROPE: e = launch_layout<EPI_ROPE, NW>(a, s); break;
+        case EPI_ROPE_STORE: e = launch_layout<EPI_ROPE_STORE, NW>(a, s); break;
+        case EPI_SILU_MUL: e = a.A1 ? launch_t<EPI_SILU_MUL, LAY_SLABS, true, NW>(a, s) : launch_layout<EPI_SILU_MUL, NW>(a, s); break;
+        case EPI_SILU_MUL_T: e = launch_layout<EPI_SILU_MUL_T, NW>(a, s); break;
         default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess || a.ksplit <= 1) return e;
