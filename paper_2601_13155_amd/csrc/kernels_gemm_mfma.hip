@@ -38,7 +38,7 @@
 //    32 (LAY_WIDE_A), or A in 3 and B in 2 (LAY_WIDE_AB) - A, which few workgroups share, comes from far away and gets the depth.
 //    Measured alone (us, 32-wide slabs or 2 stages of 64 -> now): gate/up of 13107 gathered rows, slab-major weights 2294 -> 2140 (1440 TFLOP/s;
 //    slab-major A 2167), of 3276 rows 577 -> 540; K projection of 32768 rows 229 -> 210; the proxy's input of 32768 rows 118 -> 103, of 20011 rows
-//    100 -> 86; with row-major weights gate/up of 13107 rows 2504 -> 2358, down of 8192 rows 803 -> 718, K projection 252 -> 224.
+//    100 -> 86; with row-major weights gate/up of 13107 rows 2504 -> 2290, down of 8192 rows 803 -> 718, K projection 252 -> 224.
 //  * Rows of A may be gathered through an index list (the active-token gather of Eq. (skip) is
 //    folded into the A loads: a row is 2*K contiguous bytes, so nothing is lost in coalescing),
 //    rows of C may be scattered through one (the residual update X[T] += ...).
@@ -85,7 +85,7 @@ template <int BK> struct Image {
 // row-major matrix, and one of its stages serves two slabs.
 enum Layout : int {
     LAY_SLABS = 0,   // both 32 wide, 4 stages each (3 with a second A operand): slab-major operands, K not a multiple of 64
-    LAY_WIDE_A = 1,  // row-major A 64 wide in 3 stages, slab-major B 32 wide in 4: 96 + 64 KB
+    LAY_WIDE_A = 1,  // row-major A 64 wide in 3 stages, B (slab-major as a rule) 32 wide in 4: 96 + 64 KB
     LAY_WIDE_AB = 2, // both row-major and 64 wide, A in 3 stages and B in 2: 96 + 64 KB.  B, which many workgroups read, comes from L2
 };
 template <int LAY, bool DUAL_A> struct Ring {
@@ -644,12 +644,17 @@ static hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
 
 template <int EPI, int NW>
 static hipError_t launch_layout(const GemmArgs& a, hipStream_t s) {
-    constexpr bool B_SLABS = EPI != EPI_SUMSQ;   // which is refused with a slab-major B
+    constexpr bool silu = EPI == EPI_SILU_MUL || EPI == EPI_SILU_MUL_T;
     if (a.a_slab || a.K % 64 != 0) return launch_t<EPI, LAY_SLABS, false, NW>(a, s);
-    if constexpr (B_SLABS) {
-        if (a.b_slab) return launch_t<EPI, LAY_WIDE_A, false, NW>(a, s);
+    // row-major weights of the SiLU products: 32 wide as well, i.e. in halves of lines but three slabs ahead (gate/up of 13107 rows
+    // 2440 -> 2333 us, of 3276 rows 615 -> 591); the other products are faster in whole lines (down of 8192 rows 736 against 762)
+    if constexpr (silu) return launch_t<EPI, LAY_WIDE_A, false, NW>(a, s);
+    else {
+        if constexpr (EPI != EPI_SUMSQ) {   // which is refused with a slab-major B
+            if (a.b_slab) return launch_t<EPI, LAY_WIDE_A, false, NW>(a, s);
+        }
+        return launch_t<EPI, LAY_WIDE_AB, false, NW>(a, s);
     }
-    return launch_t<EPI, LAY_WIDE_AB, false, NW>(a, s);
 }
 
 // ---- tail split-K second pass: one thread per FIN_U accumulator-fragment quads (4 consecutive columns of FIN_U rows 16 apart) of a
