@@ -2,11 +2,16 @@
 // prompt, the probe queries, one request's active rows) or few columns (K projection, proxy factors).
 //
 //  * TM x 128 output tile (TM = 64, 128 or 192), 4 wavefronts (2x2) of TM/2 x 64 = (TM/32) x 4 MFMA 16x16x32 blocks.  32 / 64 / 96
-//    accumulators per lane and a ring of 48 / 80 / 80 KB let two or three workgroups share a CU, which hides one's barriers,
+//    accumulators per lane and a ring of 48 / 64 / 80 KB let two or three workgroups share a CU, which hides one's barriers,
 //    fragment reads and epilogue behind the other's MFMAs; per flop it moves twice the operand bytes of the 256x256 tile, so it
 //    pays only where that one leaves CUs idle or multiplies padding (the rule: gemm_small_pick).
-//  * K in slabs of 32, travelling global memory -> LDS directly into a ring of NST stages: NST - 1 slabs are in flight (36 / 64 /
-//    60 KB per workgroup), which is what keeps HBM busy when the product is bound by reading its weights once.
+//  * K in slabs of 32, travelling global memory -> LDS directly into a ring of 4 stages.  A slab's fragments are read between the matrix
+//    instructions of the slab before (with a workgroup or two per CU nothing else hides the reads), so its stage is free again before
+//    it is multiplied and 3 slabs (36 / 48 / 60 KB per workgroup) stay in flight, which is what keeps HBM busy when the product is
+//    bound by reading its weights once.  Against reading the fragments right before they are used: products at the plan that is best
+//    for them 0-14 % faster (800 rows of O 47.1 -> 40.7 us, 333 of down 58.6 -> 52.9, 133 of gate/up 65.0 -> 60.2, K projection of 1638 rows
+//    30.5 -> 26.7).  Rings of 8 to 12 stages where a CU has one workgroup anyway: no faster, and the longer code costs short
+//    products 1-2 us (16 slabs: 8.4 -> 10.3).
 //    Slab-major operands as in kernels_gemm_mfma.hip (whole lines per load instruction), same swizzle, same LDS image.
 //  * Split-K: `ksplit` workgroups share a tile, each leaves its raw fp32 accumulators (fragment order: every store is 1 KB),
 //    small_finish_kernel sums them in split order and applies the epilogue.
@@ -28,8 +33,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int SBN = 128;        // tile columns (weight rows)
 constexpr int SBK = 32;         // K slab
 constexpr int SROW = SBK * 2;   // bytes of a tile row in a slab
-template <int TM> constexpr int small_stages() { return TM == 128 ? 5 : 4; }   // 48 / 80 / 80 KB
 template <int TM> constexpr int small_stage_bytes() { return (TM + SBN) * SROW; }
+// ring stages: 48 / 64 / 80 KB (even, since the two fragment sets alternate)
+constexpr int SMALL_STAGES = 4;
 
 __device__ inline int small_off(int row, int c) { return row * SROW + ((c ^ ((row >> 2) & 3)) << 4); }
 __device__ inline float small_silu(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)); }
@@ -107,7 +113,7 @@ __device__ __forceinline__ void small_store_ct(const GemmArgs& a, int col, int64
 template <int TM>
 __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmArgs a, int nM, int nN, int ksplit) {
     constexpr int MI = TM / 64;                 // 32-row blocks per wavefront
-    constexpr int NST = small_stages<TM>(), STAGE = small_stage_bytes<TM>(), A_BYTES = TM * SROW;
+    constexpr int NST = SMALL_STAGES, STAGE = small_stage_bytes<TM>(), A_BYTES = TM * SROW;
     constexpr int LA = TM / 64, LB = 2, PER = LA + LB;   // direct-to-LDS loads per wavefront and slab: 16 rows each
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -174,34 +180,70 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int npre = nk < NST - 1 ? nk : NST - 1;
+    // All stages in flight; a slab's fragments are read while the slab before is multiplied, so its stage is free again when its
+    // multiplication begins.
+    const int npre = nk < NST ? nk : NST;
     for (int t = 0; t < npre; ++t) issue(t, t);
-    // one slab: its loads (this wavefront's) have landed when only `left` slabs' loads are outstanding; the barrier publishes
-    // everyone's and says that the stage of the slab before is free, which the next loads go to
-#define SPTS_SMALL_SLAB(kt_, st_, left_, ISSUE)                                                                      \
-    {                                                                                                                \
-        SPTS_WAIT_VMCNT((left_) * PER);                                                                              \
-        __syncthreads();                                                                                             \
-        if (ISSUE) issue((kt_) + NST - 1, ((st_) + NST - 1) % NST);                                                  \
-        const char* sa_ = smem + (st_) * STAGE;                                                                      \
-        const char* sb_ = sa_ + A_BYTES;                                                                             \
-        bf16x8 fa_[2 * MI], fb_[4];                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < 2 * MI; ++i)                                                           \
-            fa_[i] = *reinterpret_cast<const bf16x8*>(sa_ + small_off(wm * (TM / 2) + i * 16 + l16, lq));            \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                                \
-            fb_[j] = *reinterpret_cast<const bf16x8*>(sb_ + small_off((j >> 1) * st.jstride + wn * st.wstride + (j & 1) * 16 + l16, lq)); \
-        _Pragma("unroll") for (int i = 0; i < 2 * MI; ++i)                                                           \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                            \
-                acc[i >> 1][j >> 1][(i & 1) * 2 + (j & 1)] =                                                         \
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb_[j], fa_[i], acc[i >> 1][j >> 1][(i & 1) * 2 + (j & 1)], 0, 0, 0); \
-    }
-    int kt = 0;
-    for (; kt + 2 * NST - 2 < nk; kt += NST) {   // ring stages are constants here
+    bf16x8 fa[2][2 * MI], fb[2][4];
+    auto fragments = [&](int buf, int stage) {
+        const char* sa = smem + stage * STAGE;
+        const char* sb = sa + A_BYTES;
 #pragma unroll
-        for (int u = 0; u < NST; ++u) SPTS_SMALL_SLAB(kt + u, u, NST - 2, true)
+        for (int j = 0; j < 4; ++j)
+            fb[buf][j] = *reinterpret_cast<const bf16x8*>(sb + small_off((j >> 1) * st.jstride + wn * st.wstride + (j & 1) * 16 + l16, lq));
+#pragma unroll
+        for (int i = 0; i < 2 * MI; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(sa + small_off(wm * (TM / 2) + i * 16 + l16, lq));
+    };
+    if (npre == NST) { SPTS_WAIT_VMCNT((NST - 1) * PER); } else { SPTS_WAIT_VMCNT(0); }
+    __syncthreads();
+    fragments(0, 0);
+    auto multiply = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[i >> 1][j >> 1][(i & 1) * 2 + (j & 1)] =
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[buf][j], fa[buf][i], acc[i >> 1][j >> 1][(i & 1) * 2 + (j & 1)], 0, 0, 0);
+    };
+    // fragment reads between the matrix instructions
+    auto interleave = [&]() {
+#pragma unroll
+        for (int g = 0; g < 4 + 2 * MI; ++g) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // Slab kt from one fragment set while the other takes slab kt + 1: this wavefront's loads of that have landed when only the `left`
+    // slabs' behind it are outstanding; the barrier publishes everyone's and says that slab kt's stage has been read.
+    int kt = 0;
+    for (; kt + 2 * NST - 1 < nk; kt += NST) {   // ring stages are constants here
+#pragma unroll
+        for (int u = 0; u < NST; ++u) {
+            SPTS_WAIT_VMCNT((NST - 2) * PER);
+            __syncthreads();
+            issue(kt + u + NST, u);
+            fragments(~u & 1, (u + 1) % NST);
+            multiply(u & 1);
+            interleave();
+        }
     }
-    for (; kt + NST - 1 < nk; ++kt) SPTS_SMALL_SLAB(kt, kt % NST, NST - 2, true)
-    for (; kt < nk; ++kt) SPTS_SMALL_SLAB(kt, kt % NST, 0, false)
+    for (; kt + 1 < nk; ++kt) {
+        const int left = nk - 2 - kt;
+        if (left >= NST - 2) { SPTS_WAIT_VMCNT((NST - 2) * PER); }
+        else if (left == 1) { SPTS_WAIT_VMCNT(PER); }
+        else { SPTS_WAIT_VMCNT(0); }
+        __syncthreads();
+        if (kt + NST < nk) issue(kt + NST, kt % NST);
+        fragments(1, (kt + 1) % NST);
+        multiply(0);
+        interleave();
+#pragma unroll
+        for (int i = 0; i < 2 * MI; ++i) fa[0][i] = fa[1][i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) fb[0][j] = fb[1][j];
+    }
+    multiply(0);
 
     // ---- lane: output row l16 of its quarter block, columns 4 * lq + e
     if (ksplit > 1) {
@@ -385,7 +427,7 @@ static hipError_t launch_small_t(const GemmArgs& a, int ksplit, hipStream_t s) {
     const int nM = (int)((a.M + TM - 1) / TM), nN = a.N / (a.epi == EPI_SILU_MUL ? SBN / 2 : SBN);
     const int64_t units = (int64_t)nM * nN * ksplit;
     if (units > ((int64_t)1 << 30)) return hipErrorInvalidValue;
-    constexpr int lds = small_stages<TM>() * small_stage_bytes<TM>();
+    constexpr int lds = SMALL_STAGES * small_stage_bytes<TM>();
     static_assert(lds >= TM * SBN * 2, "the finished tile is staged in the ring");
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_small_kernel<TM>), lds);
     if (e != hipSuccess) return e;
