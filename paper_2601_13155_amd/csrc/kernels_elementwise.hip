@@ -27,26 +27,41 @@ hipError_t ensure_dynamic_lds(const void* kernel, int bytes) {
 // ---------------------------------------------------------------- rotary table
 // table[n, j] = (cos, sin)(pos[n] * base^(-2j/d)), j < d/2.  Angles are formed in fp64 so that
 // positions up to 2^17 and beyond keep full fp32 accuracy in the stored cos/sin.
-__global__ void rope_table_kernel(const int32_t* __restrict__ pos, int64_t N, int half, double neg2_over_d_log2base,
-                                  float2* __restrict__ table) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N * half) return;
-    int64_t n = i / half;
-    int j = (int)(i - n * half);
-    double theta = exp2((double)j * neg2_over_d_log2base);
-    double ang = (double)pos[n] * theta;
-    double s, c;
-    sincos(ang, &s, &c);
-    table[i] = make_float2((float)c, (float)s);
+// pos_out (may be null): pos_out[n] = pos[n], for a cache that keeps every candidate.
+struct RopeTable { const int32_t* pos; float2* table; int32_t* pos_out; double neg2_over_d_log2base; int half; };
+constexpr int ROPE_ROWS = 16;   // rows a workgroup of 256 threads makes
+
+// (cos, sin) of an fp64 angle below 2^32, to fp32.  The angle less the nearest multiple n of pi/2 (two fused steps with pi/2 in two parts:
+// exact to 2^-53 of the remainder and n * 2^-107), then the Taylor series up to the 13th / 14th power, whose first neglected term is below
+// 3e-14 on [-pi/4, pi/4]: the result is the rounded fp64 value but for one in some million halfway cases.  The library's sincos also
+// reduces angles of any size, which takes it 78 registers (this: 62) and the norm below two of its eight wavefronts per SIMD.
+__device__ __forceinline__ float2 cos_sin(double ang) {
+    constexpr double HALF_PI = 1.5707963267948966, HALF_PI_LOW = 6.123233995736766e-17;
+    const double n = rint(ang * 0.6366197723675814);
+    const double r = fma(-n, HALF_PI_LOW, fma(-n, HALF_PI, ang)), q = r * r;
+    double s = 1.0 / 6227020800.0, c = -1.0 / 87178291200.0;
+    s = fma(s, q, -1.0 / 39916800.0); c = fma(c, q, 1.0 / 479001600.0);
+    s = fma(s, q, 1.0 / 362880.0);    c = fma(c, q, -1.0 / 3628800.0);
+    s = fma(s, q, -1.0 / 5040.0);     c = fma(c, q, 1.0 / 40320.0);
+    s = fma(s, q, 1.0 / 120.0);       c = fma(c, q, -1.0 / 720.0);
+    s = fma(s, q, -1.0 / 6.0);        c = fma(c, q, 1.0 / 24.0);
+    s = fma(s * q, r, r);             c = fma(fma(c, q, -0.5), q, 1.0);
+    const int k = (int)((long long)n & 3);
+    const double a = k & 1 ? s : c, b = k & 1 ? c : s;
+    return make_float2((float)(k == 1 || k == 2 ? -a : a), (float)(k & 2 ? -b : b));
 }
 
-hipError_t launch_rope_table(const int32_t* pos, int64_t N, int d, float base, float2* table, hipStream_t s) {
-    if (N == 0) return hipSuccess;
-    int half = d / 2;
-    double k = -2.0 / (double)d * log2((double)base);
-    int64_t total = N * half;
-    rope_table_kernel<<<dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s>>>(pos, N, half, k, table);
-    return hipGetLastError();
+__device__ __forceinline__ void rope_rows(const RopeTable& r, int64_t row0, int64_t N) {
+    const int rows = N - row0 < ROPE_ROWS ? (int)(N - row0) : ROPE_ROWS;
+    if (r.pos_out && threadIdx.x < rows) r.pos_out[row0 + threadIdx.x] = r.pos[row0 + threadIdx.x];
+    int jt = -1;
+    double theta = 0.0;
+    for (int i = threadIdx.x; i < rows * r.half; i += 256) {
+        const int row = i / r.half, j = i - row * r.half;
+        if (j != jt) { theta = exp2((double)j * r.neg2_over_d_log2base); jt = j; }   // once a thread where 256 is a multiple of d/2
+        const double ang = (double)r.pos[row0 + row] * theta;
+        r.table[(row0 + row) * r.half + j] = cos_sin(ang);
+    }
 }
 
 // ---------------------------------------------------------------- RMSNorm
@@ -56,11 +71,9 @@ template <> struct Vec16<float> { static constexpr int n = 4; };
 template <> struct Vec16<bf16_t> { static constexpr int n = 8; };
 
 template <typename T>
-__global__ void __launch_bounds__(256) rmsnorm_kernel(const T* __restrict__ x, const T* __restrict__ gamma, float eps,
-                                                      T* __restrict__ out, int64_t N, int D) {
+__device__ __forceinline__ void rmsnorm_row(const T* __restrict__ x, const T* __restrict__ gamma, float eps, T* __restrict__ out, int64_t row, int D) {
     constexpr int VN = Vec16<T>::n;
     constexpr int MAXV = 4;  // up to 4 vectors of 16 bytes per thread
-    int64_t row = blockIdx.x;
     const T* xr = x + row * (int64_t)D;
     T* orow = out + row * (int64_t)D;
     float vals[MAXV * VN];
@@ -100,9 +113,7 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const T* __restrict__ x, c
 
 // generic fallback for any D (scalar accesses)
 template <typename T>
-__global__ void __launch_bounds__(256) rmsnorm_any_kernel(const T* __restrict__ x, const T* __restrict__ gamma, float eps,
-                                                          T* __restrict__ out, int64_t N, int D) {
-    int64_t row = blockIdx.x;
+__device__ __forceinline__ void rmsnorm_row_any(const T* __restrict__ x, const T* __restrict__ gamma, float eps, T* __restrict__ out, int64_t row, int D) {
     const T* xr = x + row * (int64_t)D;
     float ss = 0.f;
     for (int j = threadIdx.x; j < D; j += 256) { float f = to_f32(xr[j]); ss += f * f; }
@@ -115,19 +126,51 @@ __global__ void __launch_bounds__(256) rmsnorm_any_kernel(const T* __restrict__ 
     for (int j = threadIdx.x; j < D; j += 256) out[row * (int64_t)D + j] = from_f32<T>(to_f32(xr[j]) * inv * to_f32(gamma[j]));
 }
 
+template <typename T, bool VEC>
+__global__ void __launch_bounds__(256) rmsnorm_kernel(const T* __restrict__ x, const T* __restrict__ gamma, float eps,
+                                                      T* __restrict__ out, int D) {
+    if (VEC) rmsnorm_row(x, gamma, eps, out, blockIdx.x, D);
+    else rmsnorm_row_any(x, gamma, eps, out, blockIdx.x, D);
+}
+
+// The layer's first RMSNorm and its rotary table: both are functions of what the call is given, so they share a launch, a workgroup of
+// the table behind every 16 of the norm.  The norm is bound by HBM, the table by fp64 arithmetic.  Rows of 4096 bf16, 64 angles each: 8192 rows
+// 23.3 us + 5.1 for a table kernel -> 25.2, 32768 rows 94.6 + 13.4 -> 101.7, 333 rows 10.0 -> 5.6.
+template <typename T, bool VEC>
+__global__ void __launch_bounds__(256) rmsnorm_rope_kernel(const T* __restrict__ x, const T* __restrict__ gamma, float eps,
+                                                           T* __restrict__ out, int64_t N, int D, RopeTable r) {
+    const int64_t group = blockIdx.x / (ROPE_ROWS + 1);
+    const int in = (int)(blockIdx.x - group * (ROPE_ROWS + 1));
+    if (in == ROPE_ROWS) { rope_rows(r, group * ROPE_ROWS, N); return; }
+    const int64_t row = group * ROPE_ROWS + in;
+    if (row >= N) return;
+    if (VEC) rmsnorm_row(x, gamma, eps, out, row, D);
+    else rmsnorm_row_any(x, gamma, eps, out, row, D);
+}
+
 template <typename T>
-static hipError_t rmsnorm_t(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, hipStream_t s) {
+static hipError_t rmsnorm_t(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, const RopeTable* r, hipStream_t s) {
     constexpr int VN = Vec16<T>::n;
-    if (D % VN == 0 && D / VN <= 1024)
-        rmsnorm_kernel<T><<<dim3((unsigned)N), dim3(256), 0, s>>>((const T*)x, (const T*)gamma, eps, (T*)out, N, D);
-    else
-        rmsnorm_any_kernel<T><<<dim3((unsigned)N), dim3(256), 0, s>>>((const T*)x, (const T*)gamma, eps, (T*)out, N, D);
+    const bool vec = D % VN == 0 && D / VN <= 1024;
+    const dim3 grid((unsigned)(r ? cdiv(N, ROPE_ROWS) * (ROPE_ROWS + 1) : N)), block(256);
+    const T* xt = (const T*)x; const T* g = (const T*)gamma; T* o = (T*)out;
+    if (r && vec) rmsnorm_rope_kernel<T, true><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
+    else if (r) rmsnorm_rope_kernel<T, false><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
+    else if (vec) rmsnorm_kernel<T, true><<<grid, block, 0, s>>>(xt, g, eps, o, D);
+    else rmsnorm_kernel<T, false><<<grid, block, 0, s>>>(xt, g, eps, o, D);
     return hipGetLastError();
 }
 
 hipError_t launch_rmsnorm(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, bool bf16, hipStream_t s) {
     if (N == 0) return hipSuccess;
-    return bf16 ? rmsnorm_t<bf16_t>(x, gamma, eps, out, N, D, s) : rmsnorm_t<float>(x, gamma, eps, out, N, D, s);
+    return bf16 ? rmsnorm_t<bf16_t>(x, gamma, eps, out, N, D, nullptr, s) : rmsnorm_t<float>(x, gamma, eps, out, N, D, nullptr, s);
+}
+
+hipError_t launch_rmsnorm_rope(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, const int32_t* pos, int d, float base,
+                               float2* table, int32_t* pos_out, bool bf16, hipStream_t s) {
+    if (N == 0) return hipSuccess;
+    const RopeTable r{pos, table, pos_out, -2.0 / (double)d * log2((double)base), d / 2};
+    return bf16 ? rmsnorm_t<bf16_t>(x, gamma, eps, out, N, D, &r, s) : rmsnorm_t<float>(x, gamma, eps, out, N, D, &r, s);
 }
 
 // ---------------------------------------------------------------- rotary application
@@ -245,30 +288,6 @@ __global__ void gather_i32_kernel(const int32_t* __restrict__ in, const int32_t*
 hipError_t launch_gather_i32(const int32_t* in, const int32_t* idx, int32_t* out, int64_t n, hipStream_t s) {
     if (n == 0) return hipSuccess;
     gather_i32_kernel<<<dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s>>>(in, idx, out, n);
-    return hipGetLastError();
-}
-
-__global__ void copy16_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, int64_t nvec) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < nvec; i += stride) out[i] = in[i];
-}
-__global__ void copy4_kernel(const uint32_t* __restrict__ in, uint32_t* __restrict__ out, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) out[i] = in[i];
-}
-hipError_t launch_copy_bytes(const void* in, void* out, int64_t bytes, hipStream_t s) {
-    if (bytes == 0) return hipSuccess;
-    if (bytes % 16 == 0) {
-        int64_t nv = bytes / 16;
-        int64_t blocks = cdiv(nv, 256); if (blocks > 8192) blocks = 8192;
-        copy16_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>((const uint4*)in, (uint4*)out, nv);
-    } else {
-        int64_t nw = bytes / 4;
-        int64_t blocks = cdiv(nw, 256); if (blocks > 8192) blocks = 8192;
-        copy4_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>((const uint32_t*)in, (uint32_t*)out, nw);
-    }
     return hipGetLastError();
 }
 

@@ -103,14 +103,14 @@ struct spts_ctx {
 };
 
 enum PhaseId {
-    PH_ROPE_TABLE = 0, PH_RMSNORM, PH_K_PROJ, PH_PROBE_Q, PH_PROBE_ATTN, PH_TOPK, PH_GATHER, PH_Q_PROJ, PH_V_PROJ,
+    PH_RMSNORM = 0, PH_K_PROJ, PH_PROBE_Q, PH_PROBE_ATTN, PH_TOPK, PH_GATHER, PH_Q_PROJ, PH_V_PROJ,
     PH_ATTENTION, PH_O_PROJ, PH_PROXY_IN, PH_PROXY_MID, PH_PROXY_Z, PH_PROXY_OUT, PH_FFN_GATE_UP, PH_FFN_DOWN,
     PH_COMPACT, PH_DEC_NORM, PH_DEC_QKV, PH_DEC_ROPE_APPEND, PH_DEC_ATTN, PH_DEC_O, PH_DEC_GATE_UP, PH_DEC_DOWN, PH_DEC_HEAD,
     PH_BUILD_SALIENCY, PH_BUILD_TOPMEAN, PH_QV_PROJ,
     PH_COUNT
 };
 static const char* const kPhaseNames[PH_COUNT] = {
-    "rope_table", "rmsnorm", "k_proj", "probe_q", "probe_attn", "topk", "gather", "q_proj", "v_proj",
+    "rmsnorm", "k_proj", "probe_q", "probe_attn", "topk", "gather", "q_proj", "v_proj",
     "attention", "o_proj", "proxy_in", "proxy_mid", "proxy_z", "proxy_out", "ffn_gate_up", "ffn_down", "compact",
     "dec_rmsnorm", "dec_qkv", "dec_rope_append", "dec_attention", "dec_o_proj", "dec_gate_up", "dec_down", "dec_head",
     "build_saliency", "build_topmean", "qv_proj"};
@@ -279,13 +279,13 @@ int probe_scores_rows(spts_ctx* c, int64_t row0, int64_t n, const spts_layer_wei
     return SPTS_OK;
 }
 
-// leaves xn (normalised x) and the rotary table in the workspace for the caller
+// leaves xn (normalised x) and the rotary table in the workspace for the caller; pos_out (may be null) takes a copy of pos
 int probe_attn_impl(spts_ctx* c, const void* x, const int32_t* pos, int64_t N, const spts_layer_weights* w, int P,
-                    bool want_scores, void* k_out, float* s_out) {
+                    bool want_scores, void* k_out, float* s_out, int32_t* pos_out = nullptr) {
     const auto& m = c->m;
     c->dec_rope_pos = -1;   // the prefill's table overwrites the decode row
-    { PHASE(c, PH_ROPE_TABLE); SPTS_HIP(c, launch_rope_table(pos, N, m.d, m.rope_base, c->p<float2>(c->off.rope), c->stream)); }
-    { PHASE(c, PH_RMSNORM); SPTS_HIP(c, launch_rmsnorm(x, w->gamma1, m.rms_eps, c->p<void>(c->off.xn), N, m.D, c->bf16, c->stream)); }
+    { PHASE(c, PH_RMSNORM);
+      SPTS_HIP(c, launch_rmsnorm_rope(x, w->gamma1, m.rms_eps, c->p<void>(c->off.xn), N, m.D, pos, m.d, m.rope_base, c->p<float2>(c->off.rope), pos_out, c->bf16, c->stream)); }
     const int KV = m.Hkv * m.d;
     GemmArgs gk = gemm_args(c->p<void>(c->off.xn), m.D, nullptr, w->Wk, m.D, nullptr, KV, N, KV, m.D);
     { PHASE(c, PH_K_PROJ); SPTS_TRY(run_gemm_rope(c, gk, m.Hkv, nullptr, 0, k_out, w->Wk_s)); }
@@ -888,7 +888,8 @@ int spts_layer_prefill(spts_ctx* c, void* x, const int32_t* pos, int64_t N, cons
     float* S = s_mha ? s_mha : c->p<float>(c->off.S);
     int32_t* idxA = nullptr;
     void* kall = (kv && full_kv && Ma > 0) ? kv->k : c->p<void>(c->off.kall);
-    SPTS_TRY(probe_attn_impl(c, x, pos, N, w, skip ? cfg->probe_len : 0, skip, kall, S));
+    // a cache that keeps every candidate gets its positions with the first launch
+    SPTS_TRY(probe_attn_impl(c, x, pos, N, w, skip ? cfg->probe_len : 0, skip, kall, S, kv && full_kv && Ma > 0 ? kv->pos : nullptr));
     if (skip) {
         idxA = idx_attn ? idx_attn : c->p<int32_t>(c->off.idxA);
         PHASE(c, PH_TOPK);
@@ -912,7 +913,6 @@ int spts_layer_prefill(spts_ctx* c, void* x, const int32_t* pos, int64_t N, cons
             }
             qpos = posA;
         }
-        if (full_kv && kv) SPTS_HIP(c, launch_copy_bytes(pos, kv->pos, N * 4, st));
         vv = kv ? kv->v : c->p<void>(c->off.vhat);
         AttnArgs aa{};
         aa.q = c->p<void>(c->off.q); aa.k = kk; aa.v = vv; aa.qpos = qpos; aa.kpos = kpos; aa.out = c->p<void>(c->off.att);

@@ -143,8 +143,11 @@ hipError_t launch_proxy_hidden(const ProxyHiddenArgs& a, hipStream_t s);
 // ------------------------------------------------------------------ elementwise / data movement
 // slab-major copy of a row-major [rows, K] matrix of 2-byte elements: out[(s * rows + r) * 32 + j] = W[r * K + 32 * s + j]
 hipError_t launch_pack_slab32(const void* W, int64_t rows, int64_t K, void* out, hipStream_t s);
-hipError_t launch_rope_table(const int32_t* pos, int64_t N, int d, float base, float2* table, hipStream_t s);
 hipError_t launch_rmsnorm(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, bool bf16, hipStream_t s);
+// the same with the rotary table of positions pos[N] (table[n, j] = (cos, sin)(pos[n] * base^(-2j/d))) in the same launch, and pos_out[n] =
+// pos[n] when pos_out
+hipError_t launch_rmsnorm_rope(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, const int32_t* pos, int d, float base,
+                               float2* table, int32_t* pos_out, bool bf16, hipStream_t s);
 // out[n, h, :] = scale * rotary(in_f32[n, h, :]) with table row (idx ? idx[n] : n + row0)
 hipError_t launch_rope_apply(const float* in, const float2* table, const int32_t* idx, int64_t row0, void* out,
                              int64_t n, int heads, int d, bool bf16, hipStream_t s, float scale = 1.0f);
@@ -155,7 +158,6 @@ hipError_t launch_gather_rows(const void* in, const int32_t* idx, void* out, int
 hipError_t launch_gather_rows_maps(const void* in, const int32_t* idx, void* out, int64_t n, int64_t row_bytes,
                                    const int32_t* pos_in, int32_t* pos_out, int32_t* old2new, hipStream_t s);
 hipError_t launch_gather_i32(const int32_t* in, const int32_t* idx, int32_t* out, int64_t n, hipStream_t s);
-hipError_t launch_copy_bytes(const void* in, void* out, int64_t bytes, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_iota_i32(int32_t* p, int64_t n, hipStream_t s);
 // Per-sequence caches of a batch filled from rows laid back to back: sequence b's `rows[b]` rows from row0[b] on of k and v (row_bytes each,
