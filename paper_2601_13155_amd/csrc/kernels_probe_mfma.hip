@@ -4,9 +4,9 @@
 //
 // A softmax needs the full-row denominator before any probability can be averaged over rows, so
 // K is streamed twice:
-//   pass 1  per (kv head g, chunk of 256 keys): running (max, sum-exp) of every probe row of that
+//   pass 1  per (kv head g, chunk of keys): running (max, sum-exp) of every probe row of that
 //           head group over the chunk  ->  stats_part[chunk][g][row]
-//   combine per (g, row): global max M and 1/sum over the chunks
+//   combine per (g, row): global max M and 1/sum over the chunks; where those are few every workgroup of pass 2 does it for itself
 //   pass 2  per (g, chunk): logits again, p = exp2(s - M) / L summed over the rows of the group
 //           ->  part[g][n];   final: S[n] = sum_g part[g][n] / (P*H)   (fixed order: deterministic)
 // The R = P*H/Hkv probe rows of one KV head form a dense [R x d] operand that stays in registers
@@ -24,9 +24,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int PKV = 64;          // keys per tile
-constexpr int CHUNK_TILES = 4;   // tiles per workgroup
-constexpr int CHUNK = PKV * CHUNK_TILES;
-static_assert(CHUNK == PROBE_CHUNK, "the caller of the batched form counts chunks");
 
 // last b with pref[b] <= i (pref ascending, pref[0] = 0, i < pref[n])
 __device__ inline int segment_of(const int64_t* pref, int n, int64_t i) {
@@ -45,17 +42,21 @@ template <int D> struct ProbeLds {
     __device__ static inline int koff(int row, int c) { return row * (2 * D) + ((c ^ ((row / RPK) % CPRK)) << 4); }
 };
 
-// stats_part: [nchunks][Hkv][Rp][2]; stats: [Hkv][Rp][2] (M, 1/L); part: [Hkv][Np]
+// Offset that turns a logit's exponent into the probability's, log2(1 / L) - M; -inf for a row that weighs nothing
+__device__ inline float probe_offset(float M, float inv_l) { return inv_l > 0.f ? __builtin_amdgcn_logf(inv_l) - M : -INFINITY; }
+
+// stats_part: [nchunks][Hkv][Rp][2]; stats: [Hkv][Rp][2] (M, 1/L), or null where pass 2 combines stats_part itself; part: [Hkv][Np]
 // NWV wavefronts per workgroup, 32 * RB probe rows each.  Two wavefronts per SIMD are asked of the register allocator
-// where the rows fit (RB <= 2; left alone it used 270 registers for pass 2 and ran one).
+// where the rows fit (RB <= 2; left alone it used 270-280 registers and ran one).
 template <int D, int RB, int PASS, int NWV>
-__global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((PASS == 2 && RB <= 2) ? 2 : 1, 8))) probe_mfma_kernel(ProbeArgs a, int Rp, int64_t Np, float qmul,
+__global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(RB <= 2 ? 2 : 1, 8))) probe_mfma_kernel(ProbeArgs a, int Rp, int64_t Np, float qmul, int chunk_keys, int nchunks,
                                                          float* __restrict__ stats_part, const float* __restrict__ stats, ProbeSegments seg) {
     using L = ProbeLds<D>;
     constexpr int KS = D / 16;
     __shared__ __attribute__((aligned(16))) char sK[2][L::K_BYTES];
     constexpr int NT = 64 * NWV;
     __shared__ float sRed[NWV][PKV];
+    __shared__ float sOff[PASS == 2 ? 32 * RB * NWV : 1];
 
     // one sequence, or the sequence of a batch that this chunk belongs to
     int chunk = blockIdx.x;
@@ -68,15 +69,19 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
         seq_row0 = seg.off[b];
         a.N = seg.off[b + 1] - seq_row0;
         Q += (int64_t)b * a.P * a.H * D;
-        if (PASS == 2) stats += (int64_t)b * a.Hkv * Rp * 2;
+        if (PASS == 2) {
+            if (stats) stats += (int64_t)b * a.Hkv * Rp * 2;
+            nchunks = (int)(seg.chunk[b + 1] - seg.chunk[b]);
+            stats_part += seg.chunk[b] * a.Hkv * Rp * 2;
+        }
     }
     const int row_base = (int)blockIdx.z * (32 * RB * NWV);   // first probe row of this row group
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     const int grp = a.H / a.Hkv;
     const int R = a.P * grp;
-    const int64_t key_begin = (int64_t)chunk * CHUNK;
-    const int64_t key_end = key_begin + CHUNK < a.N ? key_begin + CHUNK : a.N;
+    const int64_t key_begin = (int64_t)chunk * chunk_keys;
+    const int64_t key_end = key_begin + chunk_keys < a.N ? key_begin + chunk_keys : a.N;
     const int n_tiles = (int)((key_end - key_begin + PKV - 1) / PKV);
 
     // ---- probe-row fragments: row rr = p * grp + hg  <->  qp[p, g*grp + hg, :]
@@ -112,13 +117,38 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
     // register: candidate N - P + j is hidden from the row when j >= p + 1 (0 for padded rows, whose offset is -inf anyway)
     uint32_t pvis[PASS == 2 ? RB : 1][8];
     if (PASS == 2) {
+        for (int i = tid; i < 32 * RB * NWV; i += NT) {
+            const int rr = row_base + i;
+            if (stats) {
+                const float2 st = *reinterpret_cast<const float2*>(stats + ((int64_t)g * Rp + rr) * 2);
+                sOff[i] = probe_offset(st.x, st.y);
+            } else {
+                const float* sp = stats_part + ((int64_t)g * Rp + rr) * 2;
+                const int64_t step = (int64_t)a.Hkv * Rp * 2;
+                float M = -INFINITY, l = 0.f;
+                for (int c0 = 0; c0 < nchunks; c0 += 8) {
+                    float2 st[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) st[u] = c0 + u < nchunks ? *reinterpret_cast<const float2*>(sp + (c0 + u) * step) : make_float2(-INFINITY, 0.f);
+                    float m = M;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) m = fmaxf(m, st[u].x);
+                    if (m == -INFINITY) continue;
+                    l *= __builtin_amdgcn_exp2f(M - m);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) l += st[u].y * __builtin_amdgcn_exp2f(st[u].x - m);
+                    M = m;
+                }
+                sOff[i] = rr < R && l > 0.f ? probe_offset(M, 1.0f / l) : -INFINITY;
+            }
+        }
+        __syncthreads();
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int rr = row_base + wave * 32 * RB + rb * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-                const float2 st = *reinterpret_cast<const float2*>(stats + ((int64_t)g * Rp + rr) * 2);
-                coff[rb][r] = st.y > 0.f ? __builtin_amdgcn_logf(st.y) - st.x : -INFINITY;
+                const int in = wave * 32 * RB + rb * 32 + 8 * (r >> 2) + 4 * lh + (r & 3), rr = row_base + in;
+                coff[rb][r] = sOff[in];
                 const uint32_t enc = rr < R ? (uint32_t)(rr / grp + 1) : 0u;
                 if (r & 1) pvis[rb][r >> 1] |= enc << 16; else pvis[rb][r >> 1] = enc;
             }
@@ -169,16 +199,14 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
                     }
                 }
                 // lane: probe row = column l32; keys = kb*32 + 8*(r/4) + 4*lh + r%4
+                const int vis_rel = vis_last[rb] - (int)key0 - 4 * lh;   // against literals: no thresholds in registers
                 float mx = -INFINITY;
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         float v = s[kb][r];
-                        if (need_mask) {
-                            int64_t key = key0 + kb * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-                            if (key > vis_last[rb]) v = -INFINITY;
-                        }
+                        if (need_mask && kb * 32 + 8 * (r >> 2) + (r & 3) > vis_rel) v = -INFINITY;
                         s[kb][r] = v;
                         mx = fmaxf(mx, v);
                     }
@@ -192,6 +220,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((
                     for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[kb][r] - m_use);
                 l_run[rb] = l_run[rb] * __builtin_amdgcn_exp2f(m_run[rb] - m_use) + sum;
                 m_run[rb] = m_new;
+                __builtin_amdgcn_sched_barrier(0);   // as in pass 2
             }
         } else {
             float ksum[2] = {0.f, 0.f};
@@ -300,13 +329,33 @@ static inline int probe_rp(int P, int H, int Hkv) {
 }
 static inline int probe_groups(int Rp) { return (Rp + PROBE_GROUP_ROWS - 1) / PROBE_GROUP_ROWS; }
 
+// Keys per chunk.  A workgroup fetches its probe rows (64 KB for 256 of 128 elements) and then works tile by tile, so long chunks are the
+// cheaper ones once every CU has one; below that the time is the chain of tiles.  64 probe rows, 8 kv heads, both passes: 333 candidates
+// 256 -> 64 keys 25 -> 15 us; 8192 candidates (256 workgroups) 256 and 64 keys the same.
+constexpr int CHUNK_MAX = 256;
+constexpr int64_t PROBE_FILL = 256;
+int probe_chunk_keys(int64_t N, int P, int H, int Hkv) {
+    const int64_t per_chunk = (int64_t)Hkv * probe_groups(probe_rp(P, H, Hkv));
+    int keys = CHUNK_MAX;
+    while (keys > PKV && (N + keys - 1) / keys * per_chunk < PROBE_FILL) keys >>= 1;
+    return keys;
+}
+
+// Chunks up to which pass 2 combines their statistics itself: every workgroup then reads 8 bytes per row and chunk once more, which is less
+// than a launch of its own.  Pass 2 with the combine before it -> with it inside: 32 chunks 19.4 -> 16.9 us, 24 sequences of at most
+// 6 chunks 23.3 -> 13.9; 64 chunks cost 33 (with two passes over the statistics).
+constexpr int FOLD_CHUNKS = 32;
+
 size_t probe_scratch_floats(int64_t N, int P, int H, int Hkv) {
     // generic path: stats [P*H, 2].  Matrix-core path: stats_part [nchunks][Hkv][Rp][2] + stats [Hkv][Rp][2]
-    // + part [groups][Hkv][Np]
+    // + part [groups][Hkv][Np].  It serves every call of up to N candidates and P rows: one whose chunks were shortened has fewer than
+    // twice PROBE_FILL workgroups, and one of 64-key chunks has no more of them than N gives.
     int64_t Np = (N + 255) / 256 * 256;
-    int64_t nchunks = (N + CHUNK - 1) / CHUNK;
+    const int64_t longest = (N + CHUNK_MAX - 1) / CHUNK_MAX * Hkv, all = (N + PKV - 1) / PKV * Hkv;
+    const int64_t filled = 2 * PROBE_FILL + Hkv < all ? 2 * PROBE_FILL + Hkv : all;
+    const int64_t chunks_hkv = longest > filled ? longest : filled;
     int64_t Rp = probe_rp(P, H, Hkv);
-    const size_t windowed = (size_t)(2 * (int64_t)P * H + 64) + (size_t)(nchunks * Hkv * Rp * 2 + Hkv * Rp * 2 + probe_groups((int)Rp) * Hkv * Np + 256);
+    const size_t windowed = (size_t)(2 * (int64_t)P * H + 64) + (size_t)(chunks_hkv * Rp * 2 + Hkv * Rp * 2 + probe_groups((int)Rp) * Hkv * Np + 256);
     const size_t single = probe_p1_scratch_floats(N, H);   // the single-row probe uses the same region from its start
     return windowed > single ? windowed : single;
 }
@@ -320,9 +369,13 @@ bool probe_mfma_supported(const ProbeArgs& a) {
 }
 
 // chunks, statistics rows and result rows of one sequence or of a batch
-struct ProbePlan { int64_t Np, chunks; int nseq; };
+struct ProbePlan { int64_t Np, chunks, max_chunks; int nseq, keys; };
 static ProbePlan probe_plan(const ProbeArgs& a, const ProbeSegments& seg) {
-    return ProbePlan{(a.N + 255) / 256 * 256, seg.n > 0 ? seg.chunks : (a.N + CHUNK - 1) / CHUNK, seg.n > 0 ? seg.n : 1};
+    const int64_t Np = (a.N + 255) / 256 * 256;
+    if (seg.n > 0) return ProbePlan{Np, seg.chunks, seg.max_chunks, seg.n, seg.chunk_keys};
+    const int keys = probe_chunk_keys(a.N, a.P, a.H, a.Hkv);
+    const int64_t chunks = (a.N + keys - 1) / keys;
+    return ProbePlan{Np, chunks, chunks, 1, keys};
 }
 
 template <int D, int RB, int NWV = 4>
@@ -339,9 +392,10 @@ static hipError_t launch_probe_t(const ProbeArgs& a, const ProbeSegments& seg, i
     const float qmul = (a.q_scale != 0.f) ? want / a.q_scale : want;   // exactly 1 when the producer applied `want`
     const int groups = probe_groups(Rp);
     dim3 grid(nchunks, a.Hkv, groups), block(256), pblock(64 * NWV);
-    probe_mfma_kernel<D, RB, 1, NWV><<<grid, pblock, 0, s>>>(b, Rp, pl.Np, qmul, stats_part, nullptr, seg);
-    probe_combine_kernel<<<dim3((unsigned)((pl.nseq * a.Hkv * Rp + 3) / 4)), block, 0, s>>>(stats_part, stats, nchunks, a.Hkv, Rp, R, seg);
-    probe_mfma_kernel<D, RB, 2, NWV><<<grid, pblock, 0, s>>>(b, Rp, pl.Np, qmul, nullptr, stats, seg);
+    probe_mfma_kernel<D, RB, 1, NWV><<<grid, pblock, 0, s>>>(b, Rp, pl.Np, qmul, pl.keys, nchunks, stats_part, nullptr, seg);
+    const bool fold = pl.max_chunks <= FOLD_CHUNKS;
+    if (!fold) probe_combine_kernel<<<dim3((unsigned)((pl.nseq * a.Hkv * Rp + 3) / 4)), block, 0, s>>>(stats_part, stats, nchunks, a.Hkv, Rp, R, seg);
+    probe_mfma_kernel<D, RB, 2, NWV><<<grid, pblock, 0, s>>>(b, Rp, pl.Np, qmul, pl.keys, nchunks, stats_part, fold ? nullptr : stats, seg);
     probe_final_kernel<<<dim3((unsigned)((a.N + 255) / 256)), block, 0, s>>>(part, a.S, a.N, pl.Np, groups * a.Hkv, 1.0f / (float)(a.P * a.H));
     return hipGetLastError();
 }
@@ -361,7 +415,7 @@ static hipError_t launch_probe_any(const ProbeArgs& a, const ProbeSegments& seg,
     return launch_probe_t<64, 2, 8>(a, seg, Rp, s);
 }
 
-hipError_t launch_probe_mfma(const ProbeArgs& a, hipStream_t s) { return launch_probe_any(a, ProbeSegments{nullptr, nullptr, 0, 0}, s); }
+hipError_t launch_probe_mfma(const ProbeArgs& a, hipStream_t s) { return launch_probe_any(a, ProbeSegments{nullptr, nullptr, 0, 0, 0, 0}, s); }
 
 size_t probe_batch_scratch_floats(const ProbeArgs& a, const ProbeSegments& seg) {
     const ProbePlan pl = probe_plan(a, seg);
@@ -370,7 +424,7 @@ size_t probe_batch_scratch_floats(const ProbeArgs& a, const ProbeSegments& seg) 
 }
 
 hipError_t launch_probe_mfma_batched(const ProbeArgs& a, const ProbeSegments& seg, hipStream_t s) {
-    if (seg.n < 1 || seg.chunks < 1 || seg.chunks > 0x7fffffff || (int64_t)seg.n * a.Hkv * probe_rp(a.P, a.H, a.Hkv) > 0x7fffffff) return hipErrorInvalidValue;
+    if (seg.n < 1 || seg.chunks < 1 || seg.chunk_keys < PKV || seg.chunk_keys % PKV != 0 || seg.chunks > 0x7fffffff || (int64_t)seg.n * a.Hkv * probe_rp(a.P, a.H, a.Hkv) > 0x7fffffff) return hipErrorInvalidValue;
     return launch_probe_any(a, seg, s);
 }
 

@@ -1028,6 +1028,7 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
     std::vector<int64_t> desc(SEG_ARRAYS * nb1, 0);
     int64_t *dOff = desc.data(), *ma = dOff + nb1, *oa = ma + nb1, *mf = oa + nb1, *of = mf + nb1, *dChunk = of + nb1, *dCol = dChunk + nb1, *dTile = dCol + nb1;
     const int qt = attention_query_tile(m.H, m.Hkv);
+    const int probe_keys = skip ? probe_chunk_keys(N, probe_len, m.H, m.Hkv) : 1;
     int64_t max_len = 0;
     for (int b = 0; b < batch; ++b) {
         const int64_t nb = seq_offsets[b + 1] - seq_offsets[b];
@@ -1038,7 +1039,7 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
         dOff[b] = seq_offsets[b];
         oa[b + 1] = oa[b] + ma[b];
         of[b + 1] = of[b] + mf[b];
-        dChunk[b + 1] = dChunk[b] + (nb + PROBE_CHUNK - 1) / PROBE_CHUNK;
+        dChunk[b + 1] = dChunk[b] + (nb + probe_keys - 1) / probe_keys;
         dCol[b + 1] = dCol[b] + (ma[b] + BATCH_VT_ALIGN - 1) / BATCH_VT_ALIGN * BATCH_VT_ALIGN;
         dTile[b + 1] = dTile[b] + (ma[b] + qt - 1) / qt;
         max_len = std::max(max_len, nb);
@@ -1076,7 +1077,7 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
         ProbeArgs pa{};
         pa.qp = c->p<void>(c->off.q); pa.k = kall; pa.S = S; pa.partial = c->p<float>(c->off.tmp32); pa.q_scale = q_scale;
         pa.N = N; pa.P = probe_len; pa.H = m.H; pa.Hkv = m.Hkv; pa.d = m.d;
-        const ProbeSegments ps{dev(dOff), dev(dChunk), batch, dChunk[batch]};
+        const ProbeSegments ps{dev(dOff), dev(dChunk), batch, dChunk[batch], (max_len + probe_keys - 1) / probe_keys, probe_keys};
         if (c->bf16 && probe_mfma_supported(pa) && probe_batch_scratch_floats(pa, ps) * sizeof(float) <= split_scratch_bytes(m, c->lim.max_tokens)) {
             int32_t* rows = c->p<int32_t>(c->off.idxF);   // free until the FFN's selection
             {

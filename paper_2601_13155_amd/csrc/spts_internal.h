@@ -242,9 +242,10 @@ hipError_t launch_probe_generic(const ProbeArgs& a, bool bf16, hipStream_t s);
 bool probe_mfma_supported(const ProbeArgs& a);
 hipError_t launch_probe_mfma(const ProbeArgs& a, hipStream_t s);
 // Every sequence of a batch in the same four launches: rows [off[b], off[b+1]) of k and S, probe queries [n, P, H, d], chunks of
-// PROBE_CHUNK keys from chunk[b] (device arrays [n + 1]; `chunks` = chunk[n]); a.N = off[n]; a.partial: probe_batch_scratch_floats
-struct ProbeSegments { const int64_t* off; const int64_t* chunk; int n; int64_t chunks; };
-constexpr int PROBE_CHUNK = 256;
+// chunk_keys keys from chunk[b] (device arrays [n + 1]; `chunks` = chunk[n], max_chunks = those of the longest sequence); a.N = off[n];
+// a.partial: probe_batch_scratch_floats
+struct ProbeSegments { const int64_t* off; const int64_t* chunk; int n; int64_t chunks; int64_t max_chunks; int chunk_keys; };
+int probe_chunk_keys(int64_t N, int P, int H, int Hkv);   // for N candidates in all
 size_t probe_batch_scratch_floats(const ProbeArgs& a, const ProbeSegments& seg);
 hipError_t launch_probe_mfma_batched(const ProbeArgs& a, const ProbeSegments& seg, hipStream_t s);
 // idx[b * P + p] = off[b + 1] - P + p: the probe rows of every sequence
