@@ -51,6 +51,10 @@ __device__ inline void dma16(const void* gptr, uint32_t lds_base) {
 __device__ inline void dma16s(uint32_t voff, const void* sbase, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\t" ::"v"(voff), "s"(sbase), "s"(lds_base) : "memory");
 }
+// ... of data that is read once: not to be kept in the caches
+__device__ inline void dma16s_nt(uint32_t voff, const void* sbase, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt\n\t" ::"v"(voff), "s"(sbase), "s"(lds_base) : "memory");
+}
 // s_waitcnt vmcnt(n) only (expcnt / lgkmcnt fields left at "no wait")
 #define SPTS_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 0xF) | (((n) >> 4) << 14))
 
