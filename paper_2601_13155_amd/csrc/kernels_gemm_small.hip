@@ -164,10 +164,16 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
     const int nk_all = a.K / SBK;
     const int nk = nk_all / ksplit + (split < nk_all % ksplit ? 1 : 0);
     const int kbeg = split * (nk_all / ksplit) + (split < nk_all % ksplit ? split : nk_all % ksplit);
+    // With one row tile no other workgroup reads these weights: they are loaded as such and leave the caches to the rows, which all do
+    // (133 rows, in a layer: gate/up 67.5 -> 64.6 us, down 34 -> 29, O 14.6 -> 14; 333 rows, all products 338 -> 314)
+    const bool once = nM == 1;
     auto issue = [&](int kt, int stage) {
         const int64_t ks = kbeg + kt;
 #pragma unroll
-        for (int q = 0; q < LB; ++q) dma16s(ob[q], bbase + ks * b_kstep, lds_b + stage * STAGE + q * 1024);
+        for (int q = 0; q < LB; ++q) {
+            if (once) dma16s_nt(ob[q], bbase + ks * b_kstep, lds_b + stage * STAGE + q * 1024);
+            else dma16s(ob[q], bbase + ks * b_kstep, lds_b + stage * STAGE + q * 1024);
+        }
 #pragma unroll
         for (int q = 0; q < LA; ++q) dma16s(oa[q], abase + ks * a_kstep, lds_a + stage * STAGE + q * 1024);
     };
