@@ -34,17 +34,17 @@ __device__ inline f32x16 tile32_mfma(u32x4 b, u32x4 a, f32x16 c, bf16_t) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
 }
 
+// tile (bx, by) of a product
 template <typename T, int MODE>
-__global__ void __launch_bounds__(256) gemm_tile32_kernel(GemmArgs a) {
+__device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by, float (*red)[4][32][36]) {
     constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
     constexpr int KS = 2 * EPC;                // k per step: one chunk for each half of the wavefront
     constexpr int U = 4;                       // steps per group: 128 consecutive bytes of a row
     constexpr int NP = MODE == T32_ONE ? 1 : 2;
-    __shared__ __attribute__((aligned(16))) float red[NP][4][32][36];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
-    const int64_t row0 = (int64_t)blockIdx.y * 32;
-    const int col0 = (int)blockIdx.x * (MODE == T32_WIDE ? 64 : 32);
+    const int64_t row0 = (int64_t)by * 32;
+    const int col0 = bx * (MODE == T32_WIDE ? 64 : 32);
     const int ncols = MODE == T32_ROPE ? a.N / 2 : a.N;   // rotary: a column stands for its pair
     const int half = MODE == T32_ROPE ? a.head_dim >> 1 : 1;
 
@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(256) gemm_tile32_kernel(GemmArgs a) {
             if (col0 + 32 + c4 + e < a.N) ss += v[NP - 1][e] * v[NP - 1][e];
         }
         ss += __shfl_xor(ss, 1); ss += __shfl_xor(ss, 2); ss += __shfl_xor(ss, 4);
-        if ((tid & 7) == 0 && grow < a.M) a.part[grow * a.part_ld + blockIdx.x] = ss;
+        if ((tid & 7) == 0 && grow < a.M) a.part[grow * a.part_ld + bx] = ss;
         return;
     }
     if (grow >= a.M) return;
@@ -143,6 +143,25 @@ __global__ void __launch_bounds__(256) gemm_tile32_kernel(GemmArgs a) {
             if (a.Ct) ((T*)a.Ct)[(int64_t)col * a.ldct + vt_key_slot(grow)] = o;
         }
     }
+}
+
+template <typename T, int MODE>
+__global__ void __launch_bounds__(256) gemm_tile32_kernel(GemmArgs a) {
+    __shared__ __attribute__((aligned(16))) float red[MODE == T32_ONE ? 1 : 2][4][32][36];
+    tile32_product<T, MODE>(a, blockIdx.x, blockIdx.y, red);
+}
+
+// independent products, rotary or plain, in one launch: product i has the blocks from first[i] on, nx[i] of them to a row of tiles
+struct Tile32Group { GemmArgs a[GEMM_GROUP_MAX]; int first[GEMM_GROUP_MAX], nx[GEMM_GROUP_MAX]; };
+template <typename T>
+__global__ void __launch_bounds__(256) gemm_tile32_group_kernel(Tile32Group g) {
+    __shared__ __attribute__((aligned(16))) float red[2][4][32][36];
+    int i = 0;
+#pragma unroll
+    for (int q = 1; q < GEMM_GROUP_MAX; ++q) i += (int)blockIdx.x >= g.first[q] ? 1 : 0;
+    const int b = blockIdx.x - g.first[i], by = b / g.nx[i], bx = b - by * g.nx[i];
+    if (g.a[i].epi == EPI_ROPE) tile32_product<T, T32_ROPE>(g.a[i], bx, by, red);
+    else tile32_product<T, T32_ONE>(g.a[i], bx, by, red);
 }
 
 constexpr int GT = 64;   // tile edge
@@ -291,6 +310,32 @@ hipError_t launch_gemm_generic(const GemmArgs& a, bool bf16, hipStream_t s) {
         if (dual) gemm_generic_kernel<float, true><<<grid, block, 0, s>>>(a);
         else gemm_generic_kernel<float, false><<<grid, block, 0, s>>>(a);
     }
+    return hipGetLastError();
+}
+
+bool gemm_tile32_group_supported(const GemmArgs* a, int n, bool bf16) {
+    if (n < 1 || n > GEMM_GROUP_MAX) return false;
+    for (int i = 0; i < n; ++i)
+        if (!gemm_tile32_supported(a[i], bf16) || (a[i].epi != EPI_ROPE && a[i].epi != EPI_STORE && a[i].epi != EPI_RESIDUAL)) return false;
+    return true;
+}
+
+hipError_t launch_gemm_tile32_group(const GemmArgs* a, int n, bool bf16, hipStream_t s) {
+    if (!gemm_tile32_group_supported(a, n, bf16)) return hipErrorInvalidValue;
+    Tile32Group g{};
+    int64_t blocks = 0;
+    for (int i = 0; i < GEMM_GROUP_MAX; ++i) {
+        g.first[i] = 0x7fffffff;
+        g.nx[i] = 1;
+        if (i >= n) continue;
+        g.a[i] = a[i];
+        g.first[i] = (int)blocks;
+        g.nx[i] = ((a[i].epi == EPI_ROPE ? a[i].N / 2 : a[i].N) + 31) / 32;
+        blocks += (int64_t)g.nx[i] * ((a[i].M + 31) / 32);
+        if (blocks > 1 << 23) return hipErrorInvalidValue;
+    }
+    if (bf16) gemm_tile32_group_kernel<bf16_t><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);
+    else gemm_tile32_group_kernel<float><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);
     return hipGetLastError();
 }
 

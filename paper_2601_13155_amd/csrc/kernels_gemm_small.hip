@@ -110,8 +110,9 @@ __device__ __forceinline__ void small_store_ct(const GemmArgs& a, int col, int64
     for (int t = 0; t < 4; ++t) ct[(int64_t)(col + t) * a.ldct + vt_key_slot(grow)].v = e[t];
 }
 
+// workgroup `block` of a product
 template <int TM>
-__global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmArgs a, int nM, int nN, int ksplit) {
+__device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN, int ksplit, int block) {
     constexpr int MI = TM / 64;                 // 32-row blocks per wavefront
     constexpr int NST = SMALL_STAGES, STAGE = small_stage_bytes<TM>(), A_BYTES = TM * SROW;
     constexpr int LA = TM / 64, LB = 2, PER = LA + LB;   // direct-to-LDS loads per wavefront and slab: 16 rows each
@@ -120,8 +121,8 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
     // XCD b % 8 takes a contiguous range of the units (split outermost): neighbouring units share operand panels in its L2
     const int tiles = nM * nN, units = tiles * ksplit;
     const int per_xcd = (units + 7) / 8;
-    const int unit = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-    if ((int)(blockIdx.x / 8) >= per_xcd || unit >= units) return;
+    const int unit = block % 8 * per_xcd + block / 8;
+    if (block / 8 >= per_xcd || unit >= units) return;
     const int split = unit / tiles, id = unit - split * tiles;
     int tm, tn;
     small_tile_of(id, nM, nN, tm, tn);
@@ -308,11 +309,28 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmA
     }
 }
 
+template <int TM>
+__global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmArgs a, int nM, int nN, int ksplit) {
+    small_product<TM>(a, nM, nN, ksplit, blockIdx.x);
+}
+
+// Independent products of one tile height in one launch: product i has the blocks from first[i] on (multiples of 8: a block's XCD stays what
+// it is in a launch of its own), and those from finish[i] on of the second pass.
+struct SmallGroup { GemmArgs a[GEMM_GROUP_MAX]; int nM[GEMM_GROUP_MAX], nN[GEMM_GROUP_MAX], ksplit[GEMM_GROUP_MAX], first[GEMM_GROUP_MAX], finish[GEMM_GROUP_MAX]; };
+
+template <int TM>
+__global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_group_kernel(SmallGroup g) {
+    int i = 0;
+#pragma unroll
+    for (int q = 1; q < GEMM_GROUP_MAX; ++q) i += (int)blockIdx.x >= g.first[q] ? 1 : 0;
+    small_product<TM>(g.a[i], g.nM[i], g.nN[i], g.ksplit[i], blockIdx.x - g.first[i]);
+}
+
 // Second pass of a split product: one thread per fragment quad pair (j = 0, 1), splits summed in order.
 template <int TM>
-__global__ void __launch_bounds__(256) small_finish_kernel(GemmArgs a, int nM, int nN, int ksplit) {
+__device__ __forceinline__ void small_finish(const GemmArgs& a, int nM, int nN, int ksplit, int block) {
     constexpr int MI = TM / 64, QPT = TM * SBN / 8;      // quad pairs per tile
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t g = (int64_t)block * 256 + threadIdx.x;
     const int id = (int)(g / QPT), v = (int)(g % QPT);
     const int lane = v & 63, q = (v >> 6) & 3, wi = v >> 8;
     const int wave = wi / MI, i = wi % MI;
@@ -349,6 +367,17 @@ __global__ void __launch_bounds__(256) small_finish_kernel(GemmArgs a, int nM, i
         }
         if (a.Ct && !st.rope && grow < a.ldct) small_store_ct(a, col, grow, o[j]);
     }
+}
+
+template <int TM>
+__global__ void __launch_bounds__(256) small_finish_kernel(GemmArgs a, int nM, int nN, int ksplit) { small_finish<TM>(a, nM, nN, ksplit, blockIdx.x); }
+
+template <int TM>
+__global__ void __launch_bounds__(256) small_finish_group_kernel(SmallGroup g) {
+    int i = 0;
+#pragma unroll
+    for (int q = 1; q < GEMM_GROUP_MAX; ++q) i += (int)blockIdx.x >= g.finish[q] ? 1 : 0;
+    small_finish<TM>(g.a[i], g.nM[i], g.nN[i], g.ksplit[i], blockIdx.x - g.finish[i]);
 }
 
 bool gemm_small_supported(const GemmArgs& a) {
@@ -447,6 +476,39 @@ static hipError_t launch_small_t(const GemmArgs& a, int ksplit, hipStream_t s) {
 hipError_t launch_gemm_small(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s) {
     if (p.ksplit < 1 || p.ksplit > a.K / SBK || (p.ksplit > 1 && !a.part32)) return hipErrorInvalidValue;
     return p.tm == 192 ? launch_small_t<192>(a, p.ksplit, s) : p.tm == 128 ? launch_small_t<128>(a, p.ksplit, s) : launch_small_t<64>(a, p.ksplit, s);
+}
+
+template <int TM>
+static hipError_t launch_small_group_t(const GemmArgs* a, const GemmSmallPlan* p, int n, hipStream_t s) {
+    SmallGroup g{};
+    int64_t blocks = 0, finish = 0;
+    for (int i = 0; i < GEMM_GROUP_MAX; ++i) {
+        g.first[i] = g.finish[i] = 0x7fffffff;
+        if (i >= n) continue;
+        g.a[i] = a[i];
+        g.nM[i] = (int)((a[i].M + TM - 1) / TM);
+        g.nN[i] = a[i].N / (a[i].epi == EPI_SILU_MUL ? SBN / 2 : SBN);
+        g.ksplit[i] = p[i].ksplit;
+        g.first[i] = (int)blocks;
+        blocks += ((int64_t)g.nM[i] * g.nN[i] * p[i].ksplit + 7) / 8 * 8;
+        g.finish[i] = (int)finish;
+        if (p[i].ksplit > 1) finish += (int64_t)g.nM[i] * g.nN[i] * (TM * SBN / 8 / 256);
+        if (blocks > 1 << 30 || finish > 1 << 30) return hipErrorInvalidValue;
+    }
+    constexpr int lds = SMALL_STAGES * small_stage_bytes<TM>();
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_small_group_kernel<TM>), lds);
+    if (e != hipSuccess) return e;
+    gemm_small_group_kernel<TM><<<dim3((unsigned)blocks), dim3(256), lds, s>>>(g);
+    if ((e = hipGetLastError()) != hipSuccess || finish == 0) return e;
+    small_finish_group_kernel<TM><<<dim3((unsigned)finish), dim3(256), 0, s>>>(g);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_small_group(const GemmArgs* a, const GemmSmallPlan* p, int n, hipStream_t s) {
+    if (n < 1 || n > GEMM_GROUP_MAX) return hipErrorInvalidValue;
+    for (int i = 0; i < n; ++i)
+        if (p[i].tm != p[0].tm || p[i].ksplit < 1 || p[i].ksplit > a[i].K / SBK || (p[i].ksplit > 1 && !a[i].part32)) return hipErrorInvalidValue;
+    return p[0].tm == 192 ? launch_small_group_t<192>(a, p, n, s) : p[0].tm == 128 ? launch_small_group_t<128>(a, p, n, s) : launch_small_group_t<64>(a, p, n, s);
 }
 
 }  // namespace spts

@@ -151,19 +151,25 @@ struct PhaseScope {
 namespace {
 
 // ---- dispatch helpers -------------------------------------------------------------------------
+// how the matrix-core products are split and tiled: true when the short-product kernel takes it (*plan), else the 256-wide tiles with (*ks, *nfull);
+// at most `have` bytes of split scratch
+bool plan_gemm_mfma(const GemmArgs& a, size_t have, int* ks, int32_t* nfull, GemmSmallPlan* plan) {
+    *ks = gemm_pick_split(a.M, a.N, a.K, a.epi, nfull);
+    if (*ks > 1) {
+        const int64_t tiles = (a.M + 255) / 256 * (a.N / 256);
+        if ((size_t)(tiles - *nfull) * *ks * 65536 * sizeof(float) > have) *ks = 1;
+    }
+    return gemm_small_pick(a, *ks, *nfull, have, plan);
+}
+
 // matrix-core launch: 256-wide tiles, their partly filled last round split over K through the fp32 staging buffer, or the smaller
 // tiles where those leave the chip short of work
 int run_gemm_mfma(spts_ctx* c, GemmArgs a) {
-    const size_t have = split_scratch_bytes(c->m, c->lim.max_tokens);
+    int ks;
     int32_t nfull = 0;
-    int ks = gemm_pick_split(a.M, a.N, a.K, a.epi, &nfull);
-    if (ks > 1) {
-        const int64_t tiles = (a.M + 255) / 256 * (a.N / 256);
-        if ((size_t)(tiles - nfull) * ks * 65536 * sizeof(float) > have) ks = 1;
-    }
-    a.part32 = c->p<float>(c->off.tmp32);
     GemmSmallPlan small{};
-    if (gemm_small_pick(a, ks, nfull, have, &small)) {
+    a.part32 = c->p<float>(c->off.tmp32);
+    if (plan_gemm_mfma(a, split_scratch_bytes(c->m, c->lim.max_tokens), &ks, &nfull, &small)) {
         SPTS_HIP(c, launch_gemm_small(a, small, c->stream));
         return SPTS_OK;
     }
@@ -175,6 +181,37 @@ int run_gemm_mfma(spts_ctx* c, GemmArgs a) {
 int run_gemm(spts_ctx* c, const GemmArgs& a) {
     if (c->bf16 && gemm_mfma_supported(a)) return run_gemm_mfma(c, a);
     SPTS_HIP(c, launch_gemm_generic(a, c->bf16, c->stream));
+    return SPTS_OK;
+}
+
+// Products that do not depend on one another in one launch, where all are short products of one tile height or all run on the 32x32 tiles
+// (*done; nothing is launched otherwise).  A short prompt's products are 10-15 us each, a third of it the launch and the second pass
+// of its split (333 rows of the 8B shape: K, V and the probe queries 49 -> 23 us, the layer 321 -> 301; fp32 layer of 512 rows 155 -> 139).
+int try_gemm_group(spts_ctx* c, GemmArgs* a, int n, bool* done) {
+    *done = false;
+    if (n < 2 || n > GEMM_GROUP_MAX) return SPTS_OK;
+    bool mfma = c->bf16;
+    for (int i = 0; i < n; ++i) mfma = mfma && gemm_mfma_supported(a[i]);
+    if (!mfma) {
+        if (!gemm_tile32_group_supported(a, n, c->bf16)) return SPTS_OK;
+        SPTS_HIP(c, launch_gemm_tile32_group(a, n, c->bf16, c->stream));
+        *done = true;
+        return SPTS_OK;
+    }
+    GemmSmallPlan plan[GEMM_GROUP_MAX];
+    char* part = c->p<char>(c->off.tmp32);
+    size_t have = split_scratch_bytes(c->m, c->lim.max_tokens);
+    for (int i = 0; i < n; ++i) {
+        int ks;
+        int32_t nfull = 0;
+        if (!plan_gemm_mfma(a[i], have, &ks, &nfull, &plan[i]) || plan[i].tm != plan[0].tm) return SPTS_OK;
+        const size_t bytes = align_up(gemm_small_part_bytes(a[i], plan[i]));   // at most `have`, but for the alignment
+        a[i].part32 = reinterpret_cast<float*>(part);
+        part += bytes;
+        have = have > bytes ? have - bytes : 0;
+    }
+    SPTS_HIP(c, launch_gemm_small_group(a, plan, n, c->stream));
+    *done = true;
     return SPTS_OK;
 }
 
@@ -211,18 +248,19 @@ float query_store_scale(const spts_ctx* c) { return c->bf16 ? attention_mfma_q_s
 
 // out[rows, heads*d] = out_scale * rotary(A * B^T); table row of output row i is (tidx ? tidx[i] : i + row0); b_slab:
 // optional slab-major copy of B (heads*d rows)
+// -- as one product (*f): false where no kernel has that epilogue for the shape
+bool rope_args(const spts_ctx* c, const GemmArgs& g, const int32_t* tidx, int64_t row0, void* out, const void* b_slab, float out_scale, GemmArgs* f) {
+    *f = g;
+    f->epi = EPI_ROPE; f->C = out; f->rope = c->p<float2>(c->off.rope) + row0 * (c->m.d / 2); f->rope_idx = tidx; f->head_dim = c->m.d;
+    f->rope_scale = out_scale;
+    prefer_slab(c, *f, b_slab, nullptr, g.N);
+    return (c->bf16 && gemm_mfma_supported(*f)) || gemm_tile32_supported(*f, c->bf16);
+}
 int run_gemm_rope(spts_ctx* c, GemmArgs g, int heads, const int32_t* tidx, int64_t row0, void* out, const void* b_slab = nullptr,
                   float out_scale = 1.0f) {
     const float2* table = c->p<float2>(c->off.rope);
-    GemmArgs f = g;
-    f.epi = EPI_ROPE; f.C = out; f.rope = table + row0 * (c->m.d / 2); f.rope_idx = tidx; f.head_dim = c->m.d;
-    f.rope_scale = out_scale;
-    prefer_slab(c, f, b_slab, nullptr, g.N);
-    if (c->bf16 && gemm_mfma_supported(f)) return run_gemm_mfma(c, f);
-    if (gemm_tile32_supported(f, c->bf16)) {
-        SPTS_HIP(c, launch_gemm_generic(f, c->bf16, c->stream));
-        return SPTS_OK;
-    }
+    GemmArgs f;
+    if (rope_args(c, g, tidx, row0, out, b_slab, out_scale, &f)) return run_gemm(c, f);
     g.C = c->p<float>(c->off.tmp32); g.c_is_f32 = 1; g.epi = EPI_STORE;
     SPTS_TRY(run_gemm(c, g));
     SPTS_HIP(c, launch_rope_apply(c->p<float>(c->off.tmp32), table, tidx, row0, out, g.M, heads, c->m.d, c->bf16, c->stream, out_scale));
@@ -255,11 +293,14 @@ int check_weights_full(const spts_ctx* c, const spts_layer_weights* w, bool need
 // ---- PAP probe: norm, keys, probe queries, scores ----------------------------------------------
 // scores of the candidates [row0, row0 + n) of the rows that norm_keys_impl prepared: the last P of them
 // are the probe queries, k_rows points at the keys of row row0
-int probe_scores_rows(spts_ctx* c, int64_t row0, int64_t n, const spts_layer_weights* w, int P, const void* k_rows, float* s_out) {
+GemmArgs probe_query_args(const spts_ctx* c, int64_t row_end, const spts_layer_weights* w, int P) {
     const auto& m = c->m;
     const int QD = m.H * m.d;
-    const size_t eb = c->bf16 ? 2 : 4;
-    const char* xn_probe = c->p<char>(c->off.xn) + (size_t)(row0 + n - P) * m.D * eb;
+    return gemm_args(c->p<char>(c->off.xn) + (size_t)(row_end - P) * m.D * (c->bf16 ? 2 : 4), m.D, nullptr, w->Wq, m.D, nullptr, QD, P, QD, m.D);
+}
+// (have_queries: they are in the workspace already)
+int probe_scores_rows(spts_ctx* c, int64_t row0, int64_t n, const spts_layer_weights* w, int P, const void* k_rows, float* s_out, bool have_queries = false) {
+    const auto& m = c->m;
     ProbeArgs pa{};
     pa.qp = c->p<void>(c->off.qp); pa.k = k_rows; pa.S = s_out;
     pa.stats = c->p<float>(c->off.probe);
@@ -270,8 +311,10 @@ int probe_scores_rows(spts_ctx* c, int64_t row0, int64_t n, const spts_layer_wei
     // bf16: the queries leave the projection already multiplied by log2(e)/sqrt(d), before their one rounding (the
     // matrix-core kernels then get exponents of 2 straight from the MFMA; the other kernels divide their scale by it)
     pa.q_scale = query_store_scale(c);
-    GemmArgs gq = gemm_args(xn_probe, m.D, nullptr, w->Wq, m.D, nullptr, QD, P, QD, m.D);
-    { PHASE(c, PH_PROBE_Q); SPTS_TRY(run_gemm_rope(c, gq, m.H, nullptr, row0 + n - P, c->p<void>(c->off.qp), w->Wq_s, pa.q_scale)); }
+    if (!have_queries) {
+        PHASE(c, PH_PROBE_Q);
+        SPTS_TRY(run_gemm_rope(c, probe_query_args(c, row0 + n, w, P), m.H, nullptr, row0 + n - P, c->p<void>(c->off.qp), w->Wq_s, pa.q_scale));
+    }
     PHASE(c, PH_PROBE_ATTN);
     if (p1) SPTS_HIP(c, launch_probe_p1(pa, c->p<float>(c->off.probe), c->bf16, c->stream));
     else if (pmf) SPTS_HIP(c, launch_probe_mfma(pa, c->stream));
@@ -279,18 +322,30 @@ int probe_scores_rows(spts_ctx* c, int64_t row0, int64_t n, const spts_layer_wei
     return SPTS_OK;
 }
 
-// leaves xn (normalised x) and the rotary table in the workspace for the caller; pos_out (may be null) takes a copy of pos
+// leaves xn (normalised x) and the rotary table in the workspace for the caller; pos_out (may be null) takes a copy of pos.  `more`: products
+// of xn that wait for no selection (values of all candidates, a dense layer's queries), launched with the keys' and the probe
+// queries' where they can be (*more_done)
 int probe_attn_impl(spts_ctx* c, const void* x, const int32_t* pos, int64_t N, const spts_layer_weights* w, int P,
-                    bool want_scores, void* k_out, float* s_out, int32_t* pos_out = nullptr) {
+                    bool want_scores, void* k_out, float* s_out, int32_t* pos_out = nullptr, const GemmArgs* more = nullptr, int n_more = 0, bool* more_done = nullptr) {
     const auto& m = c->m;
     c->dec_rope_pos = -1;   // the prefill's table overwrites the decode row
     { PHASE(c, PH_RMSNORM);
       SPTS_HIP(c, launch_rmsnorm_rope(x, w->gamma1, m.rms_eps, c->p<void>(c->off.xn), N, m.D, pos, m.d, m.rope_base, c->p<float2>(c->off.rope), pos_out, c->bf16, c->stream)); }
     const int KV = m.Hkv * m.d;
     GemmArgs gk = gemm_args(c->p<void>(c->off.xn), m.D, nullptr, w->Wk, m.D, nullptr, KV, N, KV, m.D);
-    { PHASE(c, PH_K_PROJ); SPTS_TRY(run_gemm_rope(c, gk, m.Hkv, nullptr, 0, k_out, w->Wk_s)); }
+    GemmArgs group[GEMM_GROUP_MAX];
+    int n = 1;
+    bool done = rope_args(c, gk, nullptr, 0, k_out, w->Wk_s, 1.0f, &group[0]);
+    if (want_scores && done) done = rope_args(c, probe_query_args(c, N, w, P), nullptr, N - P, c->p<void>(c->off.qp), w->Wq_s, query_store_scale(c), &group[n++]);
+    if (done) {
+        for (int i = 0; i < n_more && n < GEMM_GROUP_MAX; ++i) group[n++] = more[i];
+        PHASE(c, PH_K_PROJ);
+        SPTS_TRY(try_gemm_group(c, group, n, &done));
+    }
+    if (more_done) *more_done = done;
+    if (!done) { PHASE(c, PH_K_PROJ); SPTS_TRY(run_gemm_rope(c, gk, m.Hkv, nullptr, 0, k_out, w->Wk_s)); }
     if (!want_scores) return SPTS_OK;
-    return probe_scores_rows(c, 0, N, w, P, k_out, s_out);
+    return probe_scores_rows(c, 0, N, w, P, k_out, s_out, done);
 }
 
 // ---- LTP probe on an already normalised xn2 [N, D] ---------------------------------------------
@@ -322,10 +377,11 @@ int proxy_scores_impl(spts_ctx* c, const void* xn2, int64_t N, const spts_layer_
             if (r % 32 == 0 && gemm_mfma_supported(s12) && gemm_mfma_supported(s3)) { g12 = s12; g3 = s3; }
             SPTS_TRY(run_gemm_mfma(c, g12));
         } else {
-            GemmArgs g1 = gemm_args(xn2, m.D, nullptr, w->Ug, m.D, t, 2 * r, N, r, m.D);
-            SPTS_TRY(run_gemm(c, g1));
-            GemmArgs g2 = gemm_args(xn2, m.D, nullptr, w->Uu, m.D, t + (size_t)r * eb, 2 * r, N, r, m.D);
-            SPTS_TRY(run_gemm(c, g2));
+            GemmArgs both[2] = {gemm_args(xn2, m.D, nullptr, w->Ug, m.D, t, 2 * r, N, r, m.D),
+                                gemm_args(xn2, m.D, nullptr, w->Uu, m.D, t + (size_t)r * eb, 2 * r, N, r, m.D)};
+            bool done;
+            SPTS_TRY(try_gemm_group(c, both, 2, &done));
+            for (int i = 0; i < 2 && !done; ++i) SPTS_TRY(run_gemm(c, both[i]));
         }
     }
     {
@@ -885,75 +941,72 @@ int spts_layer_prefill(spts_ctx* c, void* x, const int32_t* pos, int64_t N, cons
     void* xn = c->p<void>(c->off.xn);
 
     // ------------------------------------------------ attention block (Alg. 1, PAP block / dense branch)
+    // Every buffer is known before the selection is: K-hat = K[T_a] and the active positions go straight into the cache when there is one
     float* S = s_mha ? s_mha : c->p<float>(c->off.S);
-    int32_t* idxA = nullptr;
+    int32_t* idxA = !skip ? nullptr : idx_attn ? idx_attn : c->p<int32_t>(c->off.idxA);
+    int32_t* posA = (kv && !full_kv) ? kv->pos : c->p<int32_t>(c->off.posA);
     void* kall = (kv && full_kv && Ma > 0) ? kv->k : c->p<void>(c->off.kall);
+    void* kk = full_kv ? kall : kv ? kv->k : c->p<void>(c->off.khat);
+    void* vv = kv ? kv->v : c->p<void>(c->off.vhat);
+    AttnArgs aa{};
+    aa.q = c->p<void>(c->off.q); aa.k = kk; aa.v = vv; aa.qpos = skip ? posA : pos; aa.kpos = full_kv ? pos : posA; aa.out = c->p<void>(c->off.att);
+    aa.Mq = Ma; aa.Mk = Mk; aa.H = m.H; aa.Hkv = m.Hkv; aa.d = m.d;
+    aa.ldvt = (Mk + 255) / 256 * 256; aa.vt = c->p<void>(c->off.vt);
+    const bool amf = c->bf16 && Ma > 0 && attention_mfma_supported(aa);
+    // queries of the active rows (rows gathered through idxA inside the GEMM's A loads), stored with the factor of
+    // query_store_scale()
+    aa.q_scale = query_store_scale(c);
+    GemmArgs gq = gemm_args(xn, m.D, idxA, w->Wq, m.D, nullptr, QD, Ma, QD, m.D);
+    gq.a_rows = N;
+    GemmArgs gv = gemm_args(xn, m.D, full_kv ? nullptr : idxA, w->Wv, m.D, vv, KV, Mk, KV, m.D);
+    gv.a_rows = N;
+    // Queries and values of the same rows (active queries against their own keys, or the dense branch) leave one
+    // launch when the matrix-core kernels take everything: columns [0, H*d) rotary queries, [H*d, H*d + Hkv*d)
+    // values with their transposed copy.  One grid of (H + Hkv) * d / 256 column tiles instead of two, one tail.
+    GemmArgs qv = gq;
+    qv.epi = EPI_ROPE_STORE; qv.N = QD + KV; qv.n_split = QD; qv.B1 = w->Wv;
+    qv.C = c->p<void>(c->off.q); qv.ldc = QD; qv.C2 = vv; qv.ldc2 = KV;
+    qv.rope = c->p<float2>(c->off.rope); qv.rope_idx = idxA; qv.head_dim = m.d; qv.rope_scale = aa.q_scale;
+    qv.Ct = c->p<void>(c->off.vt); qv.ldct = aa.ldvt;
+    prefer_slab(c, qv, w->Wq_s, w->Wv_s, QD, KV);
+    const bool merged = amf && Mk == Ma && gv.a_idx == gq.a_idx && gemm_mfma_supported(qv);
+    prefer_slab(c, gv, w->Wv_s, nullptr, KV);
+    bool vt_done = false;
+    if (amf) {
+        // the matrix-core projection writes the transposed copy (keys contiguous) in its epilogue
+        GemmArgs gvt = gv; gvt.Ct = c->p<void>(c->off.vt); gvt.ldct = aa.ldvt;
+        if (gemm_mfma_supported(gvt)) { gv = gvt; vt_done = true; }
+    }
+    // what waits for no selection: the values of all candidates, and a dense layer's queries
+    GemmArgs more[2];
+    int n_more = 0;
+    if (full_kv && Ma > 0) {
+        if (merged) { if (!skip) more[n_more++] = qv; }
+        else {
+            more[n_more++] = gv;
+            if (!skip && rope_args(c, gq, nullptr, 0, c->p<void>(c->off.q), w->Wq_s, aa.q_scale, &more[1])) n_more = 2;
+        }
+    }
+    bool early = false;
     // a cache that keeps every candidate gets its positions with the first launch
-    SPTS_TRY(probe_attn_impl(c, x, pos, N, w, skip ? cfg->probe_len : 0, skip, kall, S, kv && full_kv && Ma > 0 ? kv->pos : nullptr));
+    SPTS_TRY(probe_attn_impl(c, x, pos, N, w, skip ? cfg->probe_len : 0, skip, kall, S, kv && full_kv && Ma > 0 ? kv->pos : nullptr, more, n_more, &early));
     if (skip) {
-        idxA = idx_attn ? idx_attn : c->p<int32_t>(c->off.idxA);
         PHASE(c, PH_TOPK);
         SPTS_TRY(run_topk(c, S, N, Ma, cfg->protect_last, idxA));
     }
     if (Ma > 0) {
-        const int32_t* qpos = pos;
-        const int32_t* kpos = pos;
-        void* kk = kall;
-        void* vv;
         if (skip) {
-            // K-hat = K[T_a] and the active positions, straight into the cache when there is one: one launch
-            int32_t* posA = (kv && !full_kv) ? kv->pos : c->p<int32_t>(c->off.posA);
             PHASE(c, PH_GATHER);
-            if (!full_kv) {
-                kk = kv ? kv->k : c->p<void>(c->off.khat);
-                SPTS_TRY(gather_rows_maps(c, kall, idxA, kk, Ma, (int64_t)KV * eb, pos, posA, nullptr));
-                kpos = posA;
-            } else {
-                SPTS_HIP(c, launch_gather_i32(pos, idxA, posA, Ma, st));
-            }
-            qpos = posA;
+            if (!full_kv) SPTS_TRY(gather_rows_maps(c, kall, idxA, kk, Ma, (int64_t)KV * eb, pos, posA, nullptr));
+            else SPTS_HIP(c, launch_gather_i32(pos, idxA, posA, Ma, st));
         }
-        vv = kv ? kv->v : c->p<void>(c->off.vhat);
-        AttnArgs aa{};
-        aa.q = c->p<void>(c->off.q); aa.k = kk; aa.v = vv; aa.qpos = qpos; aa.kpos = kpos; aa.out = c->p<void>(c->off.att);
-        aa.Mq = Ma; aa.Mk = Mk; aa.H = m.H; aa.Hkv = m.Hkv; aa.d = m.d;
-        aa.ldvt = (Mk + 255) / 256 * 256; aa.vt = c->p<void>(c->off.vt);
-        const bool amf = c->bf16 && attention_mfma_supported(aa);
-        // queries of the active rows (rows gathered through idxA inside the GEMM's A loads), stored with the factor of
-        // query_store_scale()
-        aa.q_scale = query_store_scale(c);
-        GemmArgs gq = gemm_args(xn, m.D, idxA, w->Wq, m.D, nullptr, QD, Ma, QD, m.D);
-        gq.a_rows = N;
-        GemmArgs gv = gemm_args(xn, m.D, full_kv ? nullptr : idxA, w->Wv, m.D, vv, KV, Mk, KV, m.D);
-        gv.a_rows = N;
-        // Queries and values of the same rows (active queries against their own keys, or the dense branch) leave one
-        // launch when the matrix-core kernels take everything: columns [0, H*d) rotary queries, [H*d, H*d + Hkv*d)
-        // values with their transposed copy.  One grid of (H + Hkv) * d / 256 column tiles instead of two, one tail.
-        bool merged = false;
-        if (amf && Mk == Ma && gv.a_idx == gq.a_idx) {
-            GemmArgs f = gq;
-            f.epi = EPI_ROPE_STORE; f.N = QD + KV; f.n_split = QD; f.B1 = w->Wv;
-            f.C = c->p<void>(c->off.q); f.ldc = QD; f.C2 = vv; f.ldc2 = KV;
-            f.rope = c->p<float2>(c->off.rope); f.rope_idx = idxA; f.head_dim = m.d; f.rope_scale = aa.q_scale;
-            f.Ct = c->p<void>(c->off.vt); f.ldct = aa.ldvt;
-            prefer_slab(c, f, w->Wq_s, w->Wv_s, QD, KV);
-            if (gemm_mfma_supported(f)) {
-                PHASE(c, PH_QV_PROJ);
-                SPTS_TRY(run_gemm_mfma(c, f));
-                merged = true;
-            }
-        }
-        if (!merged) {
-            { PHASE(c, PH_Q_PROJ); SPTS_TRY(run_gemm_rope(c, gq, m.H, idxA, 0, c->p<void>(c->off.q), w->Wq_s, aa.q_scale)); }
-            prefer_slab(c, gv, w->Wv_s, nullptr, KV);
-            bool vt_done = false;
-            if (amf) {
-                // the matrix-core projection writes the transposed copy (keys contiguous) in its epilogue
-                GemmArgs gvt = gv; gvt.Ct = c->p<void>(c->off.vt); gvt.ldct = aa.ldvt;
-                if (gemm_mfma_supported(gvt)) { gv = gvt; vt_done = true; }
-            }
+        const bool q_done = early && !skip && (merged || n_more == 2), v_done = early && n_more > 0 && (!merged || q_done);
+        if (merged) {
+            if (!q_done) { PHASE(c, PH_QV_PROJ); SPTS_TRY(run_gemm_mfma(c, qv)); }
+        } else {
+            if (!q_done) { PHASE(c, PH_Q_PROJ); SPTS_TRY(run_gemm_rope(c, gq, m.H, idxA, 0, c->p<void>(c->off.q), w->Wq_s, aa.q_scale)); }
             PHASE(c, PH_V_PROJ);
-            SPTS_TRY(run_gemm(c, gv));
+            if (!v_done) SPTS_TRY(run_gemm(c, gv));
             if (amf && !vt_done) SPTS_HIP(c, launch_transpose_pad(vv, c->p<void>(c->off.vt), Mk, KV, aa.ldvt, c->bf16, st));
         }
         if (kv) kv->count = Mk;

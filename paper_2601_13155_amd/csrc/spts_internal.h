@@ -128,6 +128,12 @@ size_t gemm_small_part_bytes(const GemmArgs& a, const GemmSmallPlan& p);
 // of split scratch are used
 bool gemm_small_pick(const GemmArgs& a, int wide_ksplit, int wide_nfull, size_t part_bytes, GemmSmallPlan* plan);
 hipError_t launch_gemm_small(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s);
+// Up to GEMM_GROUP_MAX products that do not depend on one another in one launch (and one second pass): of the short-product kernel, where
+// all plans have the same tile height (part32 regions of their own), and of the 32x32 tiles (epilogues ROPE, STORE, RESIDUAL)
+constexpr int GEMM_GROUP_MAX = 3;
+hipError_t launch_gemm_small_group(const GemmArgs* a, const GemmSmallPlan* p, int n, hipStream_t s);
+bool gemm_tile32_group_supported(const GemmArgs* a, int n, bool bf16);
+hipError_t launch_gemm_tile32_group(const GemmArgs* a, int n, bool bf16, hipStream_t s);
 // number of column blocks a EPI_SUMSQ launch writes per row
 int gemm_sumsq_blocks(int32_t N, bool mfma);
 
