@@ -784,7 +784,7 @@ int gemm_pick_split(int64_t M, int32_t N, int32_t K, int epi, int32_t* nfull) {
 #define SPTS_GEMM_NW 8
 #endif
 
-hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
+static hipError_t launch_products(const GemmArgs& a, hipStream_t s) {
     constexpr int NW = SPTS_GEMM_NW;
     hipError_t e;
     switch (a.epi) {
@@ -797,11 +797,72 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
         case EPI_SILU_MUL_T: e = launch_layout<EPI_SILU_MUL_T, NW>(a, s); break;
         default: return hipErrorInvalidValue;
     }
+    return e;
+}
+
+hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
+    constexpr int NW = SPTS_GEMM_NW;
+    const hipError_t e = launch_products(a, s);
     if (e != hipSuccess || a.ksplit <= 1) return e;
     const int nM = (int)((a.M + BM - 1) / BM), nN = a.N / 256;
     const int64_t threads = (int64_t)(nM * nN - a.nfull) * (16384 / FIN_U >> (a.epi == EPI_ROPE ? 1 : 0));
     if (threads <= 0) return hipSuccess;
     splitk_finish_kernel<NW><<<dim3((unsigned)(threads / 256)), dim3(256), 0, s>>>(a, nM, nN, a.nfull);
+    return hipGetLastError();
+}
+
+// Second pass of a split product of 256 columns whose rows are wanted only for their norms (the proxy's z): c[n] = ||z[n, :]||, with z rounded to
+// bf16 as the stored one would be, s[n] = c[n] * s_mha[n].  A workgroup takes 16 rows, which are 16 chunks of 1 KB in every share
+// (fragment order: a chunk is 16 rows x 16 columns); wavefront w sums the shares of chunks 4 w .. 4 w + 3, squares, and the 16 row sums meet in
+// LDS.  z is neither written nor read: 8192 rows in 8 shares 18.7 -> 13.4 us, 32768 in 2 22 -> 12, 11159 in 2 17 -> 10.3.
+struct NormTiles { int tm, nM, nN; };   // tm: rows of a tile (64 / 128 / 192 x 128 of the short products, 256 x 256)
+__global__ void __launch_bounds__(256) norm_finish_kernel(const float* __restrict__ part, NormTiles t, int ksplit, const float* __restrict__ s_mha,
+                                                          float* __restrict__ c_ffn, float* __restrict__ s_ffn, int64_t M) {
+    __shared__ float red[4][16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15;
+    const int per_tile = t.tm / 16, tm = blockIdx.x / per_tile, gi = blockIdx.x - tm * per_tile;
+    const int64_t row = (int64_t)tm * t.tm + gi * 16 + l16;
+    const int64_t tiles = (int64_t)t.nM * t.nN, stride = t.tm == 256 ? 65536 : tiles * t.tm * 128;
+    float sq = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int c = wave * 4 + u;
+        const float* p;
+        if (t.tm == 256) p = part + (int64_t)tm * ksplit * 65536 + (((gi >> 2) * 2 + (c >> 3)) * 4 + (gi & 3)) * 2048 + (c & 7) * 256;
+        else {
+            const int half = t.tm / 32, wm = gi / half, in = gi - wm * half;        // row groups of a wavefront
+            const int group = tm / 8 * 8, gsz = t.nM - group < 8 ? t.nM - group : 8;
+            const int64_t id = (int64_t)group * t.nN + (c >> 3) * gsz + (tm - group);   // as small_tile_of numbers the tiles
+            p = part + id * t.tm * 128 + (((((wm * 2 + ((c >> 2) & 1)) * (t.tm / 64) + (in >> 1)) * 2 + ((c >> 1) & 1)) * 4 + (in & 1) * 2 + (c & 1)) * 64) * 4;
+        }
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int sp = 0; sp < ksplit; ++sp) z += *reinterpret_cast<const f32x4*>(p + sp * stride + lane * 4);
+        const uint32_t lo = pack_bf16x2(z[0], z[1]), hi = pack_bf16x2(z[2], z[3]);
+        const float v[4] = {__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xffff0000u)};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq += v[e] * v[e];
+    }
+    sq += __shfl_xor(sq, 16);
+    sq += __shfl_xor(sq, 32);
+    if (lane < 16) red[wave][l16] = sq;
+    __syncthreads();
+    if (threadIdx.x < 16 && row < M) {
+        const float c = sqrtf(red[0][l16] + red[1][l16] + red[2][l16] + red[3][l16]);
+        if (c_ffn) c_ffn[row] = c;
+        if (s_ffn) s_ffn[row] = s_mha ? c * s_mha[row] : c;
+    }
+}
+
+bool gemm_norm_supported(const GemmArgs& a, int wide_ksplit, int wide_nfull, const GemmSmallPlan* small) {
+    if (a.epi != EPI_STORE || a.N != 256 || a.B1 || a.Ct || !gemm_mfma_supported(a)) return false;
+    return small ? small->ksplit > 1 : wide_ksplit > 1 && wide_nfull == 0;
+}
+hipError_t launch_gemm_norm(const GemmArgs& a, const GemmSmallPlan* small, const float* s_mha, float* c_ffn, float* s_ffn, hipStream_t s) {
+    const NormTiles t = small ? NormTiles{small->tm, (int)((a.M + small->tm - 1) / small->tm), 2} : NormTiles{256, (int)((a.M + BM - 1) / BM), 1};
+    const hipError_t e = small ? launch_gemm_small_shares(a, *small, s) : launch_products(a, s);
+    if (e != hipSuccess) return e;
+    norm_finish_kernel<<<dim3((unsigned)(t.nM * (t.tm / 16))), dim3(256), 0, s>>>(a.part32, t, small ? small->ksplit : a.ksplit, s_mha, c_ffn, s_ffn, a.M);
     return hipGetLastError();
 }
 

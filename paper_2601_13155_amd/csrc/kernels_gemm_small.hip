@@ -458,7 +458,7 @@ size_t gemm_small_part_bytes(const GemmArgs& a, const GemmSmallPlan& p) {
 }
 
 template <int TM>
-static hipError_t launch_small_t(const GemmArgs& a, int ksplit, hipStream_t s) {
+static hipError_t launch_small_t(const GemmArgs& a, int ksplit, bool finish, hipStream_t s) {
     const int nM = (int)((a.M + TM - 1) / TM), nN = a.N / (a.epi == EPI_SILU_MUL ? SBN / 2 : SBN);
     const int64_t units = (int64_t)nM * nN * ksplit;
     if (units > ((int64_t)1 << 30)) return hipErrorInvalidValue;
@@ -467,16 +467,18 @@ static hipError_t launch_small_t(const GemmArgs& a, int ksplit, hipStream_t s) {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_small_kernel<TM>), lds);
     if (e != hipSuccess) return e;
     gemm_small_kernel<TM><<<dim3((unsigned)((units + 7) / 8 * 8)), dim3(256), lds, s>>>(a, nM, nN, ksplit);
-    if ((e = hipGetLastError()) != hipSuccess || ksplit <= 1) return e;
+    if ((e = hipGetLastError()) != hipSuccess || ksplit <= 1 || !finish) return e;
     const int64_t pairs = (int64_t)nM * nN * (TM * SBN / 8);
     small_finish_kernel<TM><<<dim3((unsigned)(pairs / 256)), dim3(256), 0, s>>>(a, nM, nN, ksplit);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_small(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s) {
+static hipError_t launch_small(const GemmArgs& a, const GemmSmallPlan& p, bool finish, hipStream_t s) {
     if (p.ksplit < 1 || p.ksplit > a.K / SBK || (p.ksplit > 1 && !a.part32)) return hipErrorInvalidValue;
-    return p.tm == 192 ? launch_small_t<192>(a, p.ksplit, s) : p.tm == 128 ? launch_small_t<128>(a, p.ksplit, s) : launch_small_t<64>(a, p.ksplit, s);
+    return p.tm == 192 ? launch_small_t<192>(a, p.ksplit, finish, s) : p.tm == 128 ? launch_small_t<128>(a, p.ksplit, finish, s) : launch_small_t<64>(a, p.ksplit, finish, s);
 }
+hipError_t launch_gemm_small(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s) { return launch_small(a, p, true, s); }
+hipError_t launch_gemm_small_shares(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s) { return launch_small(a, p, false, s); }
 
 template <int TM>
 static hipError_t launch_small_group_t(const GemmArgs* a, const GemmSmallPlan* p, int n, hipStream_t s) {

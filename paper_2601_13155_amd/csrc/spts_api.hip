@@ -395,6 +395,20 @@ int proxy_scores_impl(spts_ctx* c, const void* xn2, int64_t N, const spts_layer_
         if (c->bf16 && g4.a_slab && proxy_hidden_supported(ph)) SPTS_HIP(c, launch_proxy_hidden(ph, c->stream));
         else SPTS_TRY(run_gemm(c, g3));
     }
+    if (w->Ud_orthonormal && c->bf16 && gemm_mfma_supported(g4)) {
+        // only the norms of z's rows are wanted: from the shares of a split product directly
+        int ks;
+        int32_t nfull = 0;
+        GemmSmallPlan plan{};
+        g4.part32 = c->p<float>(c->off.tmp32);
+        const bool small = plan_gemm_mfma(g4, split_scratch_bytes(m, c->lim.max_tokens), &ks, &nfull, &plan);
+        if (gemm_norm_supported(g4, ks, nfull, small ? &plan : nullptr)) {
+            if (!small) { g4.ksplit = ks; g4.nfull = nfull; }
+            PHASE(c, PH_PROXY_Z);
+            SPTS_HIP(c, launch_gemm_norm(g4, small ? &plan : nullptr, s_mha, c_ffn, s_ffn, c->stream));
+            return SPTS_OK;
+        }
+    }
     { PHASE(c, PH_PROXY_Z); SPTS_TRY(run_gemm(c, g4)); }
     if (w->Ud_orthonormal) {
         // ||z Ud^T|| = ||z|| when the columns of Ud are orthonormal (what a truncated SVD with Sigma folded into V

@@ -128,6 +128,11 @@ size_t gemm_small_part_bytes(const GemmArgs& a, const GemmSmallPlan& p);
 // of split scratch are used
 bool gemm_small_pick(const GemmArgs& a, int wide_ksplit, int wide_nfull, size_t part_bytes, GemmSmallPlan* plan);
 hipError_t launch_gemm_small(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s);
+hipError_t launch_gemm_small_shares(const GemmArgs& a, const GemmSmallPlan& p, hipStream_t s);   // without the second pass
+// A stored product of 256 columns that is split (as a whole), with a second pass that leaves the rows' norms and no product: c_ffn[n] =
+// ||C[n, :]||, s_ffn[n] = c_ffn[n] * s_mha[n] (each may be null).  small: the short-product plan, null for the 256-wide tiles (a.ksplit)
+bool gemm_norm_supported(const GemmArgs& a, int wide_ksplit, int wide_nfull, const GemmSmallPlan* small);
+hipError_t launch_gemm_norm(const GemmArgs& a, const GemmSmallPlan* small, const float* s_mha, float* c_ffn, float* s_ffn, hipStream_t s);
 // Up to GEMM_GROUP_MAX products that do not depend on one another in one launch (and one second pass): of the short-product kernel, where
 // all plans have the same tile height (part32 regions of their own), and of the 32x32 tiles (epilogues ROPE, STORE, RESIDUAL)
 constexpr int GEMM_GROUP_MAX = 3;
