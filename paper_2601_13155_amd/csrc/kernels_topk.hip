@@ -1207,9 +1207,10 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_mean_kernel(const T* __rest
 // Rows of at most 64 * KPT values: one wavefront per row, the row read once into registers.  The key of the k-th largest |value|
 // (15 significant bits in bf16, 31 in fp32) is built from its top bit down: a bit stays set when at least k keys reach it.
 // Counting is one compare per key whose lane mask is summed on the scalar unit, so there are no histograms, no LDS and no
-// barrier, and the wavefronts of a SIMD hide each other's scalar work.  Bound: 15 compares per key on the vector unit (26 us
-// for 14336 rows of 4096) and one read of the row (20 us).  Measured there: 283 us with the workgroup-per-row kernel above
-// (two histogram passes over 1024-lane strides), 93 us here.
+// barrier.  The scalar unit is what that runs out of (two instructions a key against one), so every third key is counted on the
+// vector unit instead (one more), lane by lane.  Bound: 15 compares per key (26 us for 14336 rows of 4096) and one read of the row (20
+// us).  Measured there: 283 us with the workgroup-per-row kernel above (two histogram passes over 1024-lane strides), 84 with all
+// keys on the scalar unit, 76 here.
 template <typename T, int KPT>
 __global__ void __launch_bounds__(256) topk_mean_wave_kernel(const T* __restrict__ vals, int64_t ld, int64_t rows, int n, int k, int wide,
                                                              float* __restrict__ out) {
@@ -1246,10 +1247,15 @@ __global__ void __launch_bounds__(256) topk_mean_wave_kernel(const T* __restrict
     uint32_t t = 0;
     for (int b = BITS - 1; b >= 0; --b) {
         const uint32_t cand = t | (1u << b);
-        int cnt = 0;
+        int cnt = 0, mine = 0;
 #pragma unroll
-        for (int j = 0; j < KPT; ++j) cnt += (int)__popcll(__ballot(key[j] >= cand));
-        if (cnt >= k) t = cand;
+        for (int j = 0; j < KPT; ++j) {
+            if (j % 3 == 2) mine += key[j] >= cand ? 1 : 0;
+            else cnt += (int)__popcll(__ballot(key[j] >= cand));
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
+        if (cnt + mine >= k) t = cand;
     }
     auto value = [](uint32_t q) { return __uint_as_float(sizeof(T) == 2 ? q << 16 : q); };
     float s = 0.f;
