@@ -240,9 +240,6 @@ __global__ void __launch_bounds__(256) gather_rows_maps_kernel(const u32x4* __re
                                                                int32_t* __restrict__ old2new) {
     const int64_t row0 = (int64_t)blockIdx.x * rows_per_wg;
     const int total = rows_per_wg * row_vec;      // vectors of this workgroup (<= 1024, or one row of any length)
-    // A copy beyond what the L2 caches hold (32 MB in all) leaves past them (nt): 16384 rows of 8 KB 45.7 -> 39 us, 6.9 TB/s both ways (with nt
-    // loads as well 48)
-    const bool stream = n * row_vec > (int64_t)2 << 20;
     for (int base = 0; base < total; base += 1024) {
         u32x4 v[4];
         int64_t dst[4];
@@ -259,10 +256,7 @@ __global__ void __launch_bounds__(256) gather_rows_maps_kernel(const u32x4* __re
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (dst[u] >= 0) {
-                if (stream) __builtin_nontemporal_store(v[u], out + dst[u]);
-                else out[dst[u]] = v[u];
-            }
+            if (dst[u] >= 0) out[dst[u]] = v[u];
     }
     if ((int)threadIdx.x < rows_per_wg) {
         const int64_t row = row0 + threadIdx.x;
