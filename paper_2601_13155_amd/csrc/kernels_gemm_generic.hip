@@ -313,11 +313,16 @@ hipError_t launch_gemm_generic(const GemmArgs& a, bool bf16, hipStream_t s) {
     return hipGetLastError();
 }
 
+static int tile32_columns(const GemmArgs& a) { return ((a.epi == EPI_ROPE ? a.N / 2 : a.N) + 31) / 32; }   // tiles of a plain or rotary product
+
 bool gemm_tile32_group_supported(const GemmArgs* a, int n, bool bf16) {
     if (n < 1 || n > GEMM_GROUP_MAX) return false;
-    for (int i = 0; i < n; ++i)
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
         if (!gemm_tile32_supported(a[i], bf16) || (a[i].epi != EPI_ROPE && a[i].epi != EPI_STORE && a[i].epi != EPI_RESIDUAL)) return false;
-    return true;
+        blocks += (int64_t)tile32_columns(a[i]) * ((a[i].M + 31) / 32);
+    }
+    return blocks <= 1 << 23;   // one grid dimension of 256 threads each
 }
 
 hipError_t launch_gemm_tile32_group(const GemmArgs* a, int n, bool bf16, hipStream_t s) {
@@ -330,9 +335,8 @@ hipError_t launch_gemm_tile32_group(const GemmArgs* a, int n, bool bf16, hipStre
         if (i >= n) continue;
         g.a[i] = a[i];
         g.first[i] = (int)blocks;
-        g.nx[i] = ((a[i].epi == EPI_ROPE ? a[i].N / 2 : a[i].N) + 31) / 32;
+        g.nx[i] = tile32_columns(a[i]);
         blocks += (int64_t)g.nx[i] * ((a[i].M + 31) / 32);
-        if (blocks > 1 << 23) return hipErrorInvalidValue;
     }
     if (bf16) gemm_tile32_group_kernel<bf16_t><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);
     else gemm_tile32_group_kernel<float><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);

@@ -190,9 +190,10 @@ int run_gemm(spts_ctx* c, const GemmArgs& a) {
 int try_gemm_group(spts_ctx* c, GemmArgs* a, int n, bool* done) {
     *done = false;
     if (n < 2 || n > GEMM_GROUP_MAX) return SPTS_OK;
-    bool mfma = c->bf16;
-    for (int i = 0; i < n; ++i) mfma = mfma && gemm_mfma_supported(a[i]);
-    if (!mfma) {
+    int mfma = 0;
+    for (int i = 0; i < n; ++i) mfma += c->bf16 && gemm_mfma_supported(a[i]) ? 1 : 0;
+    if (mfma != 0 && mfma != n) return SPTS_OK;   // each keeps the kernel that run_gemm gives it
+    if (mfma == 0) {
         if (!gemm_tile32_group_supported(a, n, c->bf16)) return SPTS_OK;
         SPTS_HIP(c, launch_gemm_tile32_group(a, n, c->bf16, c->stream));
         *done = true;

@@ -42,6 +42,17 @@ def test_general_gemm_refuses_the_channel_major_epilogue(bf16):
         assert I.launch_generic(a, bf16) == HIP_INVALID_VALUE
 
 
+def test_groups_of_32x32_tiles_are_no_larger_than_a_launch():
+    """2^23 workgroups of 256 threads: larger products keep their own launches instead of failing in one."""
+    f = getattr(binding.load(), "_ZN4spts27gemm_tile32_group_supportedEPKNS_8GemmArgsEib")
+    f.restype, f.argtypes = C.c_bool, [C.POINTER(I.GemmArgs), C.c_int, C.c_bool]
+    for M, fits in ((32 << 15, True), ((32 << 15) + 1, False)):   # 128 and 128 column tiles: plain, and rotary pairs of twice the columns
+        two = [I.GemmArgs(A=A16, lda=64, B0=A16, ldb=64, C=A16, ldc=n, M=M, N=n, K=64, epi=epi, head_dim=64, rope=A16)
+               for n, epi in ((4096, I.EPI_STORE), (8192, I.EPI_ROPE))]
+        assert all(I.tile32_supported(a, False) for a in two)
+        assert f((I.GemmArgs * 2)(*two), 2, False) == fits
+
+
 def _layer_products(D, QD, KV, Dff, r, d, N, Ma, Mf, P):
     """The products of one skip layer over N rows with Ma / Mf active ones, as the layer call sets them up (row-major weights)."""
     def g(M, n, k, epi, **kw):

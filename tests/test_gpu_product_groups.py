@@ -3,7 +3,7 @@ import ctypes as C
 
 import pytest
 
-from paper_2601_13155_amd import binding
+from paper_2601_13155_amd import binding, runtime, synth
 from tests import internal as I
 
 pytestmark = pytest.mark.gpu
@@ -97,3 +97,14 @@ def test_32x32_tiles(torch, n, dtype):
         assert torch.equal(torch.nan_to_num(x, nan=7.0), torch.nan_to_num(y, nan=7.0))
     for (M, N, epi), c in zip(shapes, got[0][::2]):
         assert torch.isfinite(c[:M]).all() and torch.isnan(c[M:]).all()
+
+
+def test_products_of_different_kernels_stay_apart(torch):
+    """A dense layer with 128 key columns, which the 256-wide tiles do not take, and 512 query columns, which they do: the queries do not
+    follow the keys into the 32x32 tiles' launch."""
+    shape = synth.ModelShape(D=256, H=4, Hkv=1, d=128, Dff=256, dtype="bf16")
+    ctx = runtime.make_context(shape, 300, 1, 16, shape.Dff)
+    dw = runtime.upload_layer(synth.make_layer(3, 0, shape, 16), shape, 16)
+    ctx.spts_profile_begin()
+    runtime.run_layer(ctx, synth.hidden_states(3, 300, shape.D, "bf16"), synth.positions(300), dw, shape, skip=0, probe_len=1, m_attn=300, m_ffn=300)
+    assert ctx.spts_profile_end()["q_proj"][1] == 1
