@@ -653,14 +653,14 @@ constexpr int GRP_MAX = 8;
 // G: query heads per KV head the register arrays are sized for (>= H / Hkv)
 template <typename T, int D, int G>
 __device__ __forceinline__ void decode_attn_body(const T* __restrict__ q, const T* __restrict__ K, const T* __restrict__ V,
-                                                 int64_t M, int split, int nsplit, int H, int Hkv, float scale_log2e, float* __restrict__ part) {
+                                                 int64_t M, int H, int Hkv, float scale_log2e, float* __restrict__ part) {
     constexpr int EPC = 16 / (int)sizeof(T);
     constexpr int LPK = D / EPC;          // lanes that hold one key row
     constexpr int KPW = 64 / LPK;         // keys per wavefront step
     __shared__ float sm[4][G][2];
     __shared__ float sacc[4][G][D];
 
-    const int g = blockIdx.y;
+    const int split = blockIdx.x, nsplit = gridDim.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = lane % LPK, kslot = lane / LPK;
     const int grp = H / Hkv;
@@ -776,34 +776,30 @@ template <typename T, int D, int G>
 __global__ void __launch_bounds__(256) decode_attn_kernel(const T* __restrict__ q, const T* __restrict__ K,
                                                           const T* __restrict__ V, int64_t M, int H, int Hkv, float scale_log2e,
                                                           float* __restrict__ part) {
-    decode_attn_body<T, D, G>(q, K, V, M, blockIdx.x, gridDim.x, H, Hkv, scale_log2e, part);
+    decode_attn_body<T, D, G>(q, K, V, M, H, Hkv, scale_log2e, part);
 }
-// Splits of a batch: sequence b has those from first[b] on of the launch's first dimension
-struct DecodeSplits { int first[DECODE_MAX_BATCH + 1]; };
-// a sequence's query [H, D], its cache (count[b] + 1 pairs: the new pair is already appended) and its share of the partial buffer
+// blockIdx.z = sequence: its query [H, D], its cache (count[b] + 1 pairs: the new pair is already appended) and its
+// share of the partial buffer
 template <typename T, int D, int G>
-__global__ void __launch_bounds__(256) decode_attn_batched_kernel(const T* __restrict__ q, DecodeBatch db, DecodeSplits sp, int H, int Hkv,
-                                                                  float scale_log2e, float* __restrict__ part) {
-    int b = 0;
-    while (b + 1 < db.n && (int)blockIdx.x >= sp.first[b + 1]) ++b;
-    const int first = sp.first[b];
-    decode_attn_body<T, D, G>(q + (int64_t)b * H * D, (const T*)db.cache_k[b], (const T*)db.cache_v[b], db.count[b] + 1, (int)blockIdx.x - first,
-                              sp.first[b + 1] - first, H, Hkv, scale_log2e, part + (int64_t)first * Hkv * GRP_MAX * (D + 2));
+__global__ void __launch_bounds__(256) decode_attn_batched_kernel(const T* __restrict__ q, DecodeBatch db, int H, int Hkv,
+                                                                  float scale_log2e, float* __restrict__ part, int64_t part_stride) {
+    const int b = blockIdx.z;
+    decode_attn_body<T, D, G>(q + (int64_t)b * H * D, (const T*)db.cache_k[b], (const T*)db.cache_v[b], db.count[b] + 1, H, Hkv,
+                              scale_log2e, part + (int64_t)b * part_stride);
 }
 
 // out[h, e] = sum over splits of the weighted values / sum of sums.  One workgroup of 1024 threads per
 // query head: thread s < 256 takes split s for the (max, sum) part; the weighted values are summed by
 // 1024 / D thread groups that each walk a strided subset of the splits with independent loads.
 template <typename T>
-__global__ void __launch_bounds__(1024) decode_attn_merge_kernel(const float* __restrict__ part, DecodeSplits sp, int H, int Hkv, int D,
-                                                                 T* __restrict__ out) {
+__global__ void __launch_bounds__(1024) decode_attn_merge_kernel(const float* __restrict__ part, int nsplit, int H, int Hkv, int D,
+                                                                 T* __restrict__ out, int64_t part_stride) {
     __shared__ float sa[256];
     __shared__ float sw[16], sl[16];
     __shared__ float so[1024];
     const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int grp = H / Hkv, g = h / grp, hg = h % grp;
-    const int first = sp.first[blockIdx.y], nsplit = sp.first[blockIdx.y + 1] - first;   // blockIdx.y = sequence of a batched step
-    part += (int64_t)first * Hkv * GRP_MAX * (D + 2);
+    part += (int64_t)blockIdx.y * part_stride;      // blockIdx.y = sequence of a batched step
     out += (int64_t)blockIdx.y * H * D;
     const float* base = part + ((int64_t)g * nsplit * GRP_MAX + hg) * (D + 2);
     const int64_t stride = (int64_t)GRP_MAX * (D + 2);
@@ -837,34 +833,18 @@ __global__ void __launch_bounds__(1024) decode_attn_merge_kernel(const float* __
     }
 }
 
-// Number of key splits of one sequence: two workgroups per CU over the launch (measured best on 4.6K-13K cached pairs: 32 / 64 / 128 / 256 splits
-// of 8 KV heads take 14.6 / 11.7 / 12.8 / 14.3 us), at least 64 keys each, and no more than the scratch buffer holds
-static int64_t split_cap(int Hkv, int d, size_t scratch_floats) { return (int64_t)(scratch_floats / ((size_t)Hkv * GRP_MAX * (d + 2))); }
-static int decode_attn_splits(int64_t M, int Hkv, int d, size_t scratch_floats) {
-    return (int)std::max<int64_t>(1, std::min({(int64_t)512 / Hkv, (M + 63) / 64, split_cap(Hkv, d, scratch_floats), (int64_t)256}));
-}
-// Splits of a batch: the same two workgroups per CU (8 sequences of 8.3K pairs: 8 / 16 / 32 / 64 splits each take 61 / 62 / 65 / 69 us, 4 splits
-// 89 us), dealt out so that the longest split is as short as it can be: they run side by side, so with as many splits for each sequence the
-// launch took as long as the longest one's: 8 sequences of 6001 .. 2851 pairs (8 KV heads) 40.2 -> 37.9 us, a step of two layers and the head 433 -> 426.
-DecodeSplits decode_attn_batch_splits(const int64_t* pairs, int n, int Hkv, int d, size_t scratch_floats) {
-    const int64_t total = std::max<int64_t>(n, std::min((int64_t)512 / Hkv, split_cap(Hkv, d, scratch_floats)));
-    int ns[DECODE_MAX_BATCH];
-    int64_t used = 0;
-    // every sequence has a split; the next one goes to the sequence whose splits are the longest
-    for (int b = 0; b < n; ++b) { ns[b] = 1; ++used; }
-    for (; used < total; ++used) {
-        int64_t longest = 0;
-        int at = -1;
-        for (int b = 0; b < n; ++b) {
-            const int64_t len = (pairs[b] + ns[b] - 1) / ns[b];
-            if (ns[b] < 256 && len > longest) { longest = len; at = b; }
-        }
-        if (at < 0 || longest <= 64) break;
-        ++ns[at];
-    }
-    DecodeSplits sp{};
-    for (int b = 0; b < n; ++b) sp.first[b + 1] = sp.first[b] + ns[b];
-    return sp;
+// number of key splits per sequence: two workgroups per CU over the whole launch (measured best on 4.6K-13K cached
+// pairs, one sequence: 32 / 64 / 128 / 256 splits of 8 KV heads take 14.6 / 11.7 / 12.8 / 14.3 us; 8 sequences of
+// 8.3K pairs: 8 / 16 / 32 / 64 splits take 61 / 62 / 65 / 69 us, 4 splits 89 us), at least 64 keys each, and no
+// more than the scratch buffer (scratch_floats, per sequence) holds
+int decode_attn_splits(int64_t M, int Hkv, int d, size_t scratch_floats, int nseq) {
+    int64_t s = 512 / ((int64_t)(Hkv > 0 ? Hkv : 1) * (nseq > 0 ? nseq : 1));
+    if (s > (M + 63) / 64) s = (M + 63) / 64;
+    const int64_t cap = (int64_t)(scratch_floats / ((size_t)Hkv * GRP_MAX * (d + 2)));
+    if (s > cap) s = cap;
+    if (s > 256) s = 256;
+    if (s < 1) s = 1;
+    return (int)s;
 }
 size_t decode_attn_min_scratch_floats(int Hkv, int d) { return (size_t)Hkv * GRP_MAX * (d + 2); }
 
@@ -877,7 +857,7 @@ bool decode_attn_supported(int H, int Hkv, int d, bool bf16) {
 template <typename T>
 static hipError_t launch_decode_attn_t(const T* q, const T* K, const T* V, int64_t M, int H, int Hkv, int d, float* part,
                                        size_t part_floats, T* out, hipStream_t s) {
-    const int nsplit = decode_attn_splits(M, Hkv, d, part_floats);
+    const int nsplit = decode_attn_splits(M, Hkv, d, part_floats, 1);
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)d);
     const dim3 g((unsigned)nsplit, (unsigned)Hkv), b(256);
     const int grp = H / Hkv;
@@ -896,7 +876,7 @@ static hipError_t launch_decode_attn_t(const T* q, const T* K, const T* V, int64
 #undef SPTS_DEC_ATTN
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    decode_attn_merge_kernel<T><<<dim3((unsigned)H), dim3(1024), 0, s>>>(part, DecodeSplits{{0, nsplit}}, H, Hkv, d, out);
+    decode_attn_merge_kernel<T><<<dim3((unsigned)H), dim3(1024), 0, s>>>(part, nsplit, H, Hkv, d, out, 0);
     return hipGetLastError();
 }
 
@@ -909,21 +889,23 @@ hipError_t launch_decode_attn(const void* q, const void* K, const void* V, int64
     return launch_decode_attn_t<float>((const float*)q, (const float*)K, (const float*)V, M, H, Hkv, d, part, part_floats, (float*)out, s);
 }
 
-// the same for a batch of sequences in one launch; out [B, H, d]
+// the same for a batch of sequences in one launch (grid z = sequence); every sequence takes the same number of
+// splits, chosen for the longest cache; out [B, H, d]
 template <typename T>
 static hipError_t launch_decode_attn_batched_t(const T* q, const DecodeBatch& db, int H, int Hkv, int d, float* part,
                                                size_t part_floats, T* out, hipStream_t s) {
-    int64_t pairs[DECODE_MAX_BATCH];
-    for (int b = 0; b < db.n; ++b) pairs[b] = db.count[b] + 1;
-    const DecodeSplits sp = decode_attn_batch_splits(pairs, db.n, Hkv, d, part_floats);
+    int64_t mmax = 1;
+    for (int b = 0; b < db.n; ++b) mmax = db.count[b] + 1 > mmax ? db.count[b] + 1 : mmax;
+    const int nsplit = decode_attn_splits(mmax, Hkv, d, part_floats / (size_t)db.n, db.n);
+    const int64_t stride = (int64_t)Hkv * nsplit * GRP_MAX * (d + 2);
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)d);
-    const dim3 g((unsigned)sp.first[db.n], (unsigned)Hkv), b(256);
+    const dim3 g((unsigned)nsplit, (unsigned)Hkv, (unsigned)db.n), b(256);
     const int grp = H / Hkv;
 #define SPTS_DEC_ATTN_B(D_)                                                                                                 \
-    if (grp <= 1) decode_attn_batched_kernel<T, D_, 1><<<g, b, 0, s>>>(q, db, sp, H, Hkv, scale_log2e, part);           \
-    else if (grp <= 2) decode_attn_batched_kernel<T, D_, 2><<<g, b, 0, s>>>(q, db, sp, H, Hkv, scale_log2e, part);      \
-    else if (grp <= 4) decode_attn_batched_kernel<T, D_, 4><<<g, b, 0, s>>>(q, db, sp, H, Hkv, scale_log2e, part);      \
-    else decode_attn_batched_kernel<T, D_, GRP_MAX><<<g, b, 0, s>>>(q, db, sp, H, Hkv, scale_log2e, part);
+    if (grp <= 1) decode_attn_batched_kernel<T, D_, 1><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);           \
+    else if (grp <= 2) decode_attn_batched_kernel<T, D_, 2><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);      \
+    else if (grp <= 4) decode_attn_batched_kernel<T, D_, 4><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);      \
+    else decode_attn_batched_kernel<T, D_, GRP_MAX><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);
     switch (d) {
         case 128: SPTS_DEC_ATTN_B(128) break;
         case 64: SPTS_DEC_ATTN_B(64) break;
@@ -934,7 +916,7 @@ static hipError_t launch_decode_attn_batched_t(const T* q, const DecodeBatch& db
 #undef SPTS_DEC_ATTN_B
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    decode_attn_merge_kernel<T><<<dim3((unsigned)H, (unsigned)db.n), dim3(1024), 0, s>>>(part, sp, H, Hkv, d, out);
+    decode_attn_merge_kernel<T><<<dim3((unsigned)H, (unsigned)db.n), dim3(1024), 0, s>>>(part, nsplit, H, Hkv, d, out, stride);
     return hipGetLastError();
 }
 
