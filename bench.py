@@ -23,7 +23,7 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA (published)
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E (published)
 # Kernel behind the roofline figure (phase ffn_gate_up of the library's event timer) as rocprofv3 names it.
-DOMINANT_KERNEL = "gemm_mfma_kernel<1, 32, false, 8>"
+DOMINANT_KERNEL = "gemm_mfma_kernel<1, 1, false, 8>"
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "c2_ffn_gate_up_hbm_traffic.txt")
 
 
