@@ -31,10 +31,14 @@ hipError_t ensure_dynamic_lds(const void* kernel, int bytes) {
 struct RopeTable { const int32_t* pos; float2* table; int32_t* pos_out; double neg2_over_d_log2base; int half; };
 constexpr int ROPE_ROWS = 16;   // rows a workgroup of 256 threads makes
 
-// (cos, sin) of an fp64 angle below 2^32, to fp32.  The angle less the nearest multiple n of pi/2 (two fused steps with pi/2 in two parts:
+// (cos, sin) of an fp64 angle below 2^50, to fp32.  The angle less the nearest multiple n of pi/2 (two fused steps with pi/2 in two parts:
 // exact to 2^-53 of the remainder and n * 2^-107), then the Taylor series up to the 13th / 14th power, whose first neglected term is below
-// 3e-14 on [-pi/4, pi/4]: the result is the rounded fp64 value but for one in some million halfway cases.  The library's sincos also
-// reduces angles of any size, which takes it 78 registers (this: 62) and the norm below two of its eight wavefronts per SIMD.
+// 3e-14 on [-pi/4, pi/4]: the result is the rounded fp64 value but for one in some million halfway cases (200000 angles in each octave
+// from 2^20 to 2^50 against 64-bit mantissas: none differs; from 2^53 on n is no integer any more and the remainder leaves the series' interval).
+// The library's sincos also reduces angles of any size, which takes it 78 registers (this: 62) and the norm below two of its eight
+// wavefronts per SIMD.  It serves the bases whose angles may be larger: positions are below 2^31 and frequencies below 1 / base, so
+// those below 2^-19.
+constexpr float NEAR_BASE = 1.0f / (1 << 19);
 __device__ __forceinline__ float2 cos_sin(double ang) {
     constexpr double HALF_PI = 1.5707963267948966, HALF_PI_LOW = 6.123233995736766e-17;
     const double n = rint(ang * 0.6366197723675814);
@@ -51,6 +55,7 @@ __device__ __forceinline__ float2 cos_sin(double ang) {
     return make_float2((float)(k == 1 || k == 2 ? -a : a), (float)(k & 2 ? -b : b));
 }
 
+template <bool FAR>
 __device__ __forceinline__ void rope_rows(const RopeTable& r, int64_t row0, int64_t N) {
     const int rows = N - row0 < ROPE_ROWS ? (int)(N - row0) : ROPE_ROWS;
     if (r.pos_out && threadIdx.x < rows) r.pos_out[row0 + threadIdx.x] = r.pos[row0 + threadIdx.x];
@@ -60,7 +65,11 @@ __device__ __forceinline__ void rope_rows(const RopeTable& r, int64_t row0, int6
         const int row = i / r.half, j = i - row * r.half;
         if (j != jt) { theta = exp2((double)j * r.neg2_over_d_log2base); jt = j; }   // once a thread where 256 is a multiple of d/2
         const double ang = (double)r.pos[row0 + row] * theta;
-        r.table[(row0 + row) * r.half + j] = cos_sin(ang);
+        if (FAR) {
+            double s, c;
+            sincos(ang, &s, &c);
+            r.table[(row0 + row) * r.half + j] = make_float2((float)c, (float)s);
+        } else r.table[(row0 + row) * r.half + j] = cos_sin(ang);
     }
 }
 
@@ -136,12 +145,12 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const T* __restrict__ x, c
 // The layer's first RMSNorm and its rotary table: both are functions of what the call is given, so they share a launch, a workgroup of
 // the table behind every 16 of the norm.  The norm is bound by HBM, the table by fp64 arithmetic.  Rows of 4096 bf16, 64 angles each: 8192 rows
 // 23.3 us + 5.1 for a table kernel -> 25.2, 32768 rows 94.6 + 13.4 -> 101.7, 333 rows 10.0 -> 5.6.
-template <typename T, bool VEC>
+template <typename T, bool VEC, bool FAR>
 __global__ void __launch_bounds__(256) rmsnorm_rope_kernel(const T* __restrict__ x, const T* __restrict__ gamma, float eps,
                                                            T* __restrict__ out, int64_t N, int D, RopeTable r) {
     const int64_t group = blockIdx.x / (ROPE_ROWS + 1);
     const int in = (int)(blockIdx.x - group * (ROPE_ROWS + 1));
-    if (in == ROPE_ROWS) { rope_rows(r, group * ROPE_ROWS, N); return; }
+    if (in == ROPE_ROWS) { rope_rows<FAR>(r, group * ROPE_ROWS, N); return; }
     const int64_t row = group * ROPE_ROWS + in;
     if (row >= N) return;
     if (VEC) rmsnorm_row(x, gamma, eps, out, row, D);
@@ -149,13 +158,15 @@ __global__ void __launch_bounds__(256) rmsnorm_rope_kernel(const T* __restrict__
 }
 
 template <typename T>
-static hipError_t rmsnorm_t(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, const RopeTable* r, hipStream_t s) {
+static hipError_t rmsnorm_t(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, const RopeTable* r, bool far, hipStream_t s) {
     constexpr int VN = Vec16<T>::n;
     const bool vec = D % VN == 0 && D / VN <= 1024;
     const dim3 grid((unsigned)(r ? cdiv(N, ROPE_ROWS) * (ROPE_ROWS + 1) : N)), block(256);
     const T* xt = (const T*)x; const T* g = (const T*)gamma; T* o = (T*)out;
-    if (r && vec) rmsnorm_rope_kernel<T, true><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
-    else if (r) rmsnorm_rope_kernel<T, false><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
+    if (r && far && vec) rmsnorm_rope_kernel<T, true, true><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
+    else if (r && far) rmsnorm_rope_kernel<T, false, true><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
+    else if (r && vec) rmsnorm_rope_kernel<T, true, false><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
+    else if (r) rmsnorm_rope_kernel<T, false, false><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
     else if (vec) rmsnorm_kernel<T, true><<<grid, block, 0, s>>>(xt, g, eps, o, D);
     else rmsnorm_kernel<T, false><<<grid, block, 0, s>>>(xt, g, eps, o, D);
     return hipGetLastError();
@@ -163,14 +174,14 @@ static hipError_t rmsnorm_t(const void* x, const void* gamma, float eps, void* o
 
 hipError_t launch_rmsnorm(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, bool bf16, hipStream_t s) {
     if (N == 0) return hipSuccess;
-    return bf16 ? rmsnorm_t<bf16_t>(x, gamma, eps, out, N, D, nullptr, s) : rmsnorm_t<float>(x, gamma, eps, out, N, D, nullptr, s);
+    return bf16 ? rmsnorm_t<bf16_t>(x, gamma, eps, out, N, D, nullptr, false, s) : rmsnorm_t<float>(x, gamma, eps, out, N, D, nullptr, false, s);
 }
 
 hipError_t launch_rmsnorm_rope(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, const int32_t* pos, int d, float base,
                                float2* table, int32_t* pos_out, bool bf16, hipStream_t s) {
     if (N == 0) return hipSuccess;
     const RopeTable r{pos, table, pos_out, -2.0 / (double)d * log2((double)base), d / 2};
-    return bf16 ? rmsnorm_t<bf16_t>(x, gamma, eps, out, N, D, &r, s) : rmsnorm_t<float>(x, gamma, eps, out, N, D, &r, s);
+    return bf16 ? rmsnorm_t<bf16_t>(x, gamma, eps, out, N, D, &r, base < NEAR_BASE, s) : rmsnorm_t<float>(x, gamma, eps, out, N, D, &r, base < NEAR_BASE, s);
 }
 
 // ---------------------------------------------------------------- rotary application
