@@ -157,19 +157,36 @@ __global__ void __launch_bounds__(256) rmsnorm_rope_kernel(const T* __restrict__
     else rmsnorm_row_any(x, gamma, eps, out, row, D);
 }
 
+// A launch has fewer than 2^32 threads, and a larger one is not refused but cut short (15.8 million rows of the norm with its table came
+// out partly unwritten): rows go 2^22 at a time.
+constexpr int64_t NORM_ROWS = 1 << 22;
+static_assert(NORM_ROWS % ROPE_ROWS == 0 && NORM_ROWS / ROPE_ROWS * (ROPE_ROWS + 1) * 256 < (int64_t)1 << 32, "one launch");
+
 template <typename T>
-static hipError_t rmsnorm_t(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, const RopeTable* r, bool far, hipStream_t s) {
+static hipError_t rmsnorm_t(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, const RopeTable* rope, bool far, hipStream_t s) {
     constexpr int VN = Vec16<T>::n;
     const bool vec = D % VN == 0 && D / VN <= 1024;
-    const dim3 grid((unsigned)(r ? cdiv(N, ROPE_ROWS) * (ROPE_ROWS + 1) : N)), block(256);
-    const T* xt = (const T*)x; const T* g = (const T*)gamma; T* o = (T*)out;
-    if (r && far && vec) rmsnorm_rope_kernel<T, true, true><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
-    else if (r && far) rmsnorm_rope_kernel<T, false, true><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
-    else if (r && vec) rmsnorm_rope_kernel<T, true, false><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
-    else if (r) rmsnorm_rope_kernel<T, false, false><<<grid, block, 0, s>>>(xt, g, eps, o, N, D, *r);
-    else if (vec) rmsnorm_kernel<T, true><<<grid, block, 0, s>>>(xt, g, eps, o, D);
-    else rmsnorm_kernel<T, false><<<grid, block, 0, s>>>(xt, g, eps, o, D);
-    return hipGetLastError();
+    const T* g = (const T*)gamma;
+    RopeTable r{};
+    if (rope) r = *rope;
+    for (int64_t n0 = 0; n0 < N; n0 += NORM_ROWS) {
+        const int64_t n = N - n0 < NORM_ROWS ? N - n0 : NORM_ROWS;
+        const dim3 grid((unsigned)(rope ? cdiv(n, ROPE_ROWS) * (ROPE_ROWS + 1) : n)), block(256);
+        const T* xt = (const T*)x + n0 * D; T* o = (T*)out + n0 * D;
+        if (rope && far && vec) rmsnorm_rope_kernel<T, true, true><<<grid, block, 0, s>>>(xt, g, eps, o, n, D, r);
+        else if (rope && far) rmsnorm_rope_kernel<T, false, true><<<grid, block, 0, s>>>(xt, g, eps, o, n, D, r);
+        else if (rope && vec) rmsnorm_rope_kernel<T, true, false><<<grid, block, 0, s>>>(xt, g, eps, o, n, D, r);
+        else if (rope) rmsnorm_rope_kernel<T, false, false><<<grid, block, 0, s>>>(xt, g, eps, o, n, D, r);
+        else if (vec) rmsnorm_kernel<T, true><<<grid, block, 0, s>>>(xt, g, eps, o, D);
+        else rmsnorm_kernel<T, false><<<grid, block, 0, s>>>(xt, g, eps, o, D);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        if (!rope) continue;
+        r.pos += NORM_ROWS;
+        r.table += NORM_ROWS * r.half;
+        if (r.pos_out) r.pos_out += NORM_ROWS;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_rmsnorm(const void* x, const void* gamma, float eps, void* out, int64_t N, int D, bool bf16, hipStream_t s) {

@@ -60,3 +60,13 @@ def test_rows_are_rotations_and_those_of_a_decode_step(torch, d, base):
     want = np.stack([np.cos(ang), np.sin(ang)], -1)
     bound = 2.0 ** -25 + 2.0 ** -48 * np.abs(ang)[..., None]
     assert (np.abs(t.cpu().numpy() - want) <= bound)[known].all()
+
+
+def test_more_rows_than_a_launch_has_threads_for(torch):
+    """15.8 million rows: with a workgroup of 256 threads a row and one of the table behind every 16, more than 2^32 threads."""
+    N, d = 15_800_000, 2
+    pos = torch.arange(N, dtype=torch.int32, device="cuda")
+    table, copy, out = _table(torch, pos, d, 10000.0, D=4)
+    assert torch.equal(copy, pos) and bool((out - 1.0).abs().max() <= 2.0 ** -20)
+    want = torch.stack([torch.cos(pos.double()), torch.sin(pos.double())], -1)[:, None]
+    assert bool((table.double() - want).abs().max() <= 2.0 ** -24)
