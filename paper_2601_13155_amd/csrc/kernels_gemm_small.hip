@@ -443,8 +443,9 @@ bool gemm_small_pick(const GemmArgs& a, int wide_ksplit, int wide_nfull, size_t 
             const GemmSmallPlan p{tm, ks};
             // Shares of at least 1024, at the price of 1-3 us a product (64 x 4096 x 4096: 18.1 us in 4 shares, 15.5 in 8).  A
             // product with K < 1024 is then never split (gemm_pick_split's shares are 512 at least) and is summed the same way
-            // whatever its row count and whichever kernel takes it: a batched call and the calls one by one agree bit for bit.  From
-            // K = 1024 on the row count decides the shares.
+            // whatever its row count and whichever kernel takes it: a batched call and the calls one by one have the same sums (the
+            // kernels' rotary epilogues still round a few values in a million differently).  From K = 1024 on the row count decides
+            // the shares.
             if (ks > 1 && (a.K / ks < 1024 || gemm_small_part_bytes(a, p) > part_bytes)) break;
             const double t = small_time(a, tm, ks);
             if (t < best) { best = t; *plan = p; found = true; }

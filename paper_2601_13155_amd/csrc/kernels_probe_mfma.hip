@@ -4,19 +4,23 @@
 //
 // A softmax needs the full-row denominator before any probability can be averaged over rows, so
 // K is streamed twice:
-//   pass 1  per (kv head g, chunk of keys): running (max, sum-exp) of every probe row of that
+//   pass 1  per (kv head g, chunk of keys): (max, sum-exp) of every probe row of that
 //           head group over the chunk  ->  stats_part[chunk][g][row]
 //   combine per (g, row): global max M and 1/sum over the chunks; where those are few every workgroup of pass 2 does it for itself
 //   pass 2  per (g, chunk): logits again, p = exp2(s - M) / L summed over the rows of the group
 //           ->  part[g][n];   final: S[n] = sum_g part[g][n] / (P*H)   (fixed order: deterministic)
 // The R = P*H/Hkv probe rows of one KV head form a dense [R x d] operand that stays in registers
 // (32*RB rows per wavefront); K tiles of 64 keys go through LDS (swizzled, shared by the 4
-// wavefronts).  Pass 1 computes S^T = K Q^T (one probe row per lane column: row max in-lane),
+// wavefronts).  The scores of a sequence are the same bits alone and inside any batch, although both the chunk length and who combines
+// depend on the whole call: the statistics of 64-key tiles always meet in the same tree (pairs, groups of 256 keys, the
+// groups over JOIN_LANES lanes).  Pass 1 computes S^T = K Q^T (one probe row per lane column: row max in-lane),
 // pass 2 computes S = Q K^T (one key per lane column: the sum over rows is in-lane).
 // Up to 512 rows per kv head are one workgroup's; more (7 query heads per kv head x 128 probe rows = 896, say) are dealt to
 // row groups of 512 (grid z), each of which streams K for itself and leaves its own part[group][g][n].  (They used to take the
 // fp32 kernels: a layer of 8192 tokens with 896 probe rows per kv head, 64.4 -> 2.03 ms.)
 #include "spts_internal.h"
+
+#include <type_traits>
 
 namespace spts {
 
@@ -24,6 +28,62 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int PKV = 64;          // keys per tile
+constexpr int CHUNK_MAX = 256;   // keys of the longest chunk: a group of tiles
+// Chunks up to which pass 2 combines their statistics itself: every workgroup then reads 8 bytes per row and chunk once more, which is less
+// than a launch of its own.  Pass 2 with the combine before it -> with it inside: 32 chunks 19.4 -> 16.9 us, 24 sequences of at most
+// 6 chunks 23.3 -> 13.9; 64 chunks cost 33 (with two passes over the statistics).
+constexpr int FOLD_CHUNKS = 32;
+
+// Statistics of a probe row over some keys: the largest exponent, and the sum of 2^(exponent - m).  join() is the same roundings
+// wherever two halves of a group meet, and joining nothing changes no bit.  Both passes with one tree for every chunk length, against
+// running sums in the chunk and whatever order suited each of the two combines: 333 candidates 20.2 -> 20.3 us, 1000 21.3 -> 21.7,
+// 8192 37.4 -> 38.1, 20000 71 -> 66, 32768 87.5 -> 84, 24 ragged sequences 35.0 -> 34.6.
+struct RowStats { float m, l; };
+__device__ constexpr RowStats NO_KEYS{-INFINITY, 0.f};
+__device__ __forceinline__ RowStats join(RowStats a, RowStats b) {
+    const bool up = a.m >= b.m;
+    const float hi = fmaxf(a.m, b.m), lo = fminf(a.m, b.m);
+    const float e = lo == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(lo - hi);
+    return RowStats{hi, fmaf(up ? b.l : a.l, e, up ? a.l : b.l)};
+}
+
+// a group from the PG chunks it was cut into
+template <int PG>
+__device__ __forceinline__ RowStats group_of(const RowStats* c) {
+    if constexpr (PG == 1) return c[0];
+    else if constexpr (PG == 2) return join(c[0], c[1]);
+    else return join(join(c[0], c[1]), join(c[2], c[3]));
+}
+// The groups of a row meet in JOIN_LANES lanes: lane i joins groups i, i + JOIN_LANES, ... in turn, then the lanes meet in halves.
+// Here by one thread, for a row of at most FOLD_CHUNKS chunks, PG to a group; sp: the row's first chunk, `step` floats to the next.
+constexpr int JOIN_LANES = 8;
+template <int PG>
+__device__ __forceinline__ RowStats join_chunks(const float* sp, int64_t step, int nchunks) {
+    RowStats acc[JOIN_LANES];
+#pragma unroll
+    for (int u = 0; u < JOIN_LANES; ++u) acc[u] = NO_KEYS;
+#pragma unroll
+    for (int c0 = 0; c0 < FOLD_CHUNKS; c0 += 8) {
+        if (c0 >= nchunks) break;
+        RowStats cs[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float2 v = *reinterpret_cast<const float2*>(sp + (c0 + u < nchunks ? c0 + u : nchunks - 1) * step);
+            cs[u] = c0 + u < nchunks ? RowStats{v.x, v.y} : NO_KEYS;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; u += PG) {
+            const RowStats g = group_of<PG>(cs + u);
+            const int q = (c0 + u) / PG;
+            acc[q % JOIN_LANES] = q < JOIN_LANES ? g : join(acc[q % JOIN_LANES], g);
+        }
+    }
+#pragma unroll
+    for (int off = JOIN_LANES / 2; off > 0; off >>= 1)
+#pragma unroll
+        for (int u = 0; u < off; ++u) acc[u] = join(acc[u], acc[u + off]);
+    return acc[0];
+}
 
 // last b with pref[b] <= i (pref ascending, pref[0] = 0, i < pref[n])
 __device__ inline int segment_of(const int64_t* pref, int n, int64_t i) {
@@ -71,7 +131,7 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(R
         Q += (int64_t)b * a.P * a.H * D;
         if (PASS == 2) {
             if (stats) stats += (int64_t)b * a.Hkv * Rp * 2;
-            nchunks = (int)(seg.chunk[b + 1] - seg.chunk[b]);
+            nchunks = __builtin_amdgcn_readfirstlane((int)(seg.chunk[b + 1] - seg.chunk[b]));
             stats_part += seg.chunk[b] * a.Hkv * Rp * 2;
         }
     }
@@ -125,21 +185,9 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(R
             } else {
                 const float* sp = stats_part + ((int64_t)g * Rp + rr) * 2;
                 const int64_t step = (int64_t)a.Hkv * Rp * 2;
-                float M = -INFINITY, l = 0.f;
-                for (int c0 = 0; c0 < nchunks; c0 += 8) {
-                    float2 st[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) st[u] = c0 + u < nchunks ? *reinterpret_cast<const float2*>(sp + (c0 + u) * step) : make_float2(-INFINITY, 0.f);
-                    float m = M;
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) m = fmaxf(m, st[u].x);
-                    if (m == -INFINITY) continue;
-                    l *= __builtin_amdgcn_exp2f(M - m);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) l += st[u].y * __builtin_amdgcn_exp2f(st[u].x - m);
-                    M = m;
-                }
-                sOff[i] = rr < R && l > 0.f ? probe_offset(M, 1.0f / l) : -INFINITY;
+                const RowStats all = chunk_keys == CHUNK_MAX ? join_chunks<1>(sp, step, nchunks)
+                                     : chunk_keys == CHUNK_MAX / 2 ? join_chunks<2>(sp, step, nchunks) : join_chunks<4>(sp, step, nchunks);
+                sOff[i] = rr < R && all.l > 0.f ? probe_offset(all.m, 1.0f / all.l) : -INFINITY;
             }
         }
         __syncthreads();
@@ -172,9 +220,9 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(R
         for (int i = 0; i < KCH; ++i) *reinterpret_cast<u32x4*>(sK[stage] + L::koff(kr + (NT / L::CPRK) * i, kc)) = rk[i];
     };
 
-    float m_run[RB], l_run[RB];
+    RowStats first[RB], pair[RB];   // pass 1: the chunk's first two tiles, the two in hand
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) { m_run[rb] = -INFINITY; l_run[rb] = 0.f; }
+    for (int rb = 0; rb < RB; ++rb) first[rb] = pair[rb] = NO_KEYS;
 
     const int64_t first_masked = a.N - a.P + 1;   // candidates from here on are hidden from some probe row
     if (n_tiles > 0) { load_tile(0); store_tile(0); }
@@ -185,6 +233,10 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(R
         const int64_t key0 = key_begin + (int64_t)t * PKV;
         const bool need_mask = key0 + PKV > first_masked || key0 + PKV > a.N;
         if (PASS == 1) {
+            if (t == 2) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) first[rb] = pair[rb];
+            }
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 f32x16 s[2];
@@ -210,16 +262,17 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(R
                         s[kb][r] = v;
                         mx = fmaxf(mx, v);
                     }
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float m_new = fmaxf(m_run[rb], mx);
-                const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+                const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);   // both halves' values
+                mx = fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1]));
+                const float ref = mx == -INFINITY ? 0.f : mx;
                 float sum = 0.f;
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[kb][r] - m_use);
-                l_run[rb] = l_run[rb] * __builtin_amdgcn_exp2f(m_run[rb] - m_use) + sum;
-                m_run[rb] = m_new;
+                    for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[kb][r] - ref);
+                const auto sh = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+                const RowStats tile{mx, __uint_as_float(sh[0]) + __uint_as_float(sh[1])};
+                pair[rb] = t & 1 ? join(pair[rb], tile) : tile;
                 __builtin_amdgcn_sched_barrier(0);   // as in pass 2
             }
         } else {
@@ -268,24 +321,25 @@ __global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(R
     if (PASS == 1) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            float l = l_run[rb] + __shfl_xor(l_run[rb], 32);
+            const RowStats all = n_tiles > 2 ? join(first[rb], pair[rb]) : pair[rb];
             int rr = row_base + wave * 32 * RB + rb * 32 + l32;
             if (lh == 0) {
                 float* o = stats_part + (((int64_t)blockIdx.x * a.Hkv + g) * Rp + rr) * 2;
-                o[0] = m_run[rb];
-                o[1] = l;
+                o[0] = all.m;
+                o[1] = all.l;
             }
         }
     }
 }
 
-// stats[g][rr] = (M, 1/L) over the chunks; padded rows rr >= R get (huge, 0).  One wavefront per (g, rr):
-// lane c takes chunks c, c + 64, ...; maximum and sum are reduced over a fixed shuffle tree (deterministic).
+// stats[g][rr] = (M, 1/L) over the chunks; padded rows rr >= R get (huge, 0).  JOIN_LANES lanes per (g, rr), neighbouring lanes
+// neighbouring rows (fixed order: deterministic).
 __global__ void __launch_bounds__(256) probe_combine_kernel(const float* __restrict__ stats_part, float* __restrict__ stats,
-                                                            int nchunks, int Hkv, int Rp, int R, ProbeSegments seg) {
-    const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int per_seq = Hkv * Rp, b = i / per_seq;
+                                                            int nchunks, int chunk_keys, int Hkv, int Rp, int R, ProbeSegments seg) {
+    constexpr int ROWS = 64 / JOIN_LANES;   // per wavefront
+    const int lane = threadIdx.x & 63, part = lane / ROWS;
+    const int i = (blockIdx.x * 4 + (threadIdx.x >> 6)) * ROWS + lane % ROWS;
+    const int per_seq = Hkv * Rp, b = i / per_seq;   // Rp is a multiple of ROWS: a wavefront's rows are one sequence's
     if (b >= (seg.n > 0 ? seg.n : 1)) return;
     const int g = (i - b * per_seq) / Rp, rr = i % Rp;
     if (seg.n > 0) {
@@ -293,22 +347,35 @@ __global__ void __launch_bounds__(256) probe_combine_kernel(const float* __restr
         nchunks = (int)(seg.chunk[b + 1] - c0);
         stats_part += c0 * per_seq * 2;
     }
-    if (rr >= R) {   // padded rows weigh nothing
-        if (lane == 0) { stats[2 * i] = 1e30f; stats[2 * i + 1] = 0.f; }
-        return;
+    const float* sp = stats_part + ((int64_t)g * Rp + rr) * 2;
+    const int64_t step = (int64_t)per_seq * 2;
+    auto chunk = [&](int c) {
+        const float2 v = *reinterpret_cast<const float2*>(sp + (c < nchunks ? c : nchunks - 1) * step);
+        return c < nchunks ? RowStats{v.x, v.y} : NO_KEYS;
+    };
+    auto join_groups = [&](auto pg) {
+        constexpr int PG = decltype(pg)::value, AHEAD = 8;   // groups whose loads are in flight together
+        RowStats acc = NO_KEYS;
+        for (int q = part; q * PG < nchunks; q += AHEAD * JOIN_LANES) {
+            RowStats gs[AHEAD][PG];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+                for (int e = 0; e < PG; ++e) gs[u][e] = chunk((q + u * JOIN_LANES) * PG + e);   // beyond the last: no keys
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) acc = join(acc, group_of<PG>(gs[u]));
+        }
+        return acc;
+    };
+    RowStats acc = chunk_keys == CHUNK_MAX ? join_groups(std::integral_constant<int, 1>{})
+                   : chunk_keys == CHUNK_MAX / 2 ? join_groups(std::integral_constant<int, 2>{}) : join_groups(std::integral_constant<int, 4>{});
+    for (int off = JOIN_LANES / 2; off > 0; off >>= 1) {
+        const RowStats other{__shfl_xor(acc.m, off * ROWS), __shfl_xor(acc.l, off * ROWS)};
+        acc = join(acc, other);
     }
-    float M = -INFINITY;
-    for (int c = lane; c < nchunks; c += 64) M = fmaxf(M, stats_part[(((int64_t)c * Hkv + g) * Rp + rr) * 2]);
-    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-    float Lsum = 0.f;
-    for (int c = lane; c < nchunks; c += 64) {
-        const float* s = stats_part + (((int64_t)c * Hkv + g) * Rp + rr) * 2;
-        if (s[0] != -INFINITY) Lsum += s[1] * __builtin_amdgcn_exp2f(s[0] - M);
-    }
-    for (int off = 32; off > 0; off >>= 1) Lsum += __shfl_xor(Lsum, off);
-    if (lane == 0) {
-        stats[2 * i] = M;
-        stats[2 * i + 1] = Lsum > 0.f ? 1.0f / Lsum : 0.f;
+    if (part == 0) {   // padded rows weigh nothing
+        stats[2 * i] = rr < R ? acc.m : 1e30f;
+        stats[2 * i + 1] = rr < R && acc.l > 0.f ? 1.0f / acc.l : 0.f;
     }
 }
 
@@ -332,7 +399,6 @@ static inline int probe_groups(int Rp) { return (Rp + PROBE_GROUP_ROWS - 1) / PR
 // Keys per chunk.  A workgroup fetches its probe rows (64 KB for 256 of 128 elements) and then works tile by tile, so long chunks are the
 // cheaper ones once every CU has one; below that the time is the chain of tiles.  64 probe rows, 8 kv heads, both passes: 333 candidates
 // 256 -> 64 keys 25 -> 15 us; 8192 candidates (256 workgroups) 256 and 64 keys the same.
-constexpr int CHUNK_MAX = 256;
 constexpr int64_t PROBE_FILL = 256;
 int probe_chunk_keys(int64_t N, int P, int H, int Hkv) {
     const int64_t per_chunk = (int64_t)Hkv * probe_groups(probe_rp(P, H, Hkv));
@@ -340,11 +406,6 @@ int probe_chunk_keys(int64_t N, int P, int H, int Hkv) {
     while (keys > PKV && (N + keys - 1) / keys * per_chunk < PROBE_FILL) keys >>= 1;
     return keys;
 }
-
-// Chunks up to which pass 2 combines their statistics itself: every workgroup then reads 8 bytes per row and chunk once more, which is less
-// than a launch of its own.  Pass 2 with the combine before it -> with it inside: 32 chunks 19.4 -> 16.9 us, 24 sequences of at most
-// 6 chunks 23.3 -> 13.9; 64 chunks cost 33 (with two passes over the statistics).
-constexpr int FOLD_CHUNKS = 32;
 
 size_t probe_scratch_floats(int64_t N, int P, int H, int Hkv) {
     // generic path: stats [P*H, 2].  Matrix-core path: stats_part [nchunks][Hkv][Rp][2] + stats [Hkv][Rp][2]
@@ -394,7 +455,7 @@ static hipError_t launch_probe_t(const ProbeArgs& a, const ProbeSegments& seg, i
     dim3 grid(nchunks, a.Hkv, groups), block(256), pblock(64 * NWV);
     probe_mfma_kernel<D, RB, 1, NWV><<<grid, pblock, 0, s>>>(b, Rp, pl.Np, qmul, pl.keys, nchunks, stats_part, nullptr, seg);
     const bool fold = pl.max_chunks <= FOLD_CHUNKS;
-    if (!fold) probe_combine_kernel<<<dim3((unsigned)((pl.nseq * a.Hkv * Rp + 3) / 4)), block, 0, s>>>(stats_part, stats, nchunks, a.Hkv, Rp, R, seg);
+    if (!fold) probe_combine_kernel<<<dim3((unsigned)(pl.nseq * a.Hkv * Rp / 32)), block, 0, s>>>(stats_part, stats, nchunks, pl.keys, a.Hkv, Rp, R, seg);
     probe_mfma_kernel<D, RB, 2, NWV><<<grid, pblock, 0, s>>>(b, Rp, pl.Np, qmul, pl.keys, nchunks, stats_part, fold ? nullptr : stats, seg);
     probe_final_kernel<<<dim3((unsigned)((a.N + 255) / 256)), block, 0, s>>>(part, a.S, a.N, pl.Np, groups * a.Hkv, 1.0f / (float)(a.P * a.H));
     return hipGetLastError();
@@ -424,7 +485,7 @@ size_t probe_batch_scratch_floats(const ProbeArgs& a, const ProbeSegments& seg) 
 }
 
 hipError_t launch_probe_mfma_batched(const ProbeArgs& a, const ProbeSegments& seg, hipStream_t s) {
-    if (seg.n < 1 || seg.chunks < 1 || seg.chunk_keys < PKV || seg.chunk_keys % PKV != 0 || seg.chunks > 0x7fffffff || (int64_t)seg.n * a.Hkv * probe_rp(a.P, a.H, a.Hkv) > 0x7fffffff) return hipErrorInvalidValue;
+    if (seg.n < 1 || seg.chunks < 1 || (seg.chunk_keys != PKV && seg.chunk_keys != 2 * PKV && seg.chunk_keys != CHUNK_MAX) || seg.chunks > 0x7fffffff || (int64_t)seg.n * a.Hkv * probe_rp(a.P, a.H, a.Hkv) > 0x7fffffff) return hipErrorInvalidValue;
     return launch_probe_any(a, seg, s);
 }
 
