@@ -271,6 +271,8 @@ def main():
                        "qv_proj": flops_by["qv_proj"],
                        "q_proj": flops_by["qv_proj"] * shape.H / (shape.H + shape.Hkv),
                        "v_proj": flops_by["qv_proj"] * shape.Hkv / (shape.H + shape.Hkv)}
+        if "kqv_proj" in phase_out:   # some layers' projections shared a launch: the separate phases are the other layers' only
+            phase_flops = {k: v for k, v in phase_flops.items() if k not in ("k_proj", "probe_q", "qv_proj", "q_proj", "v_proj")}
         proxy_ms = sum(phase_out[k]["ms_per_step"] for k in ("proxy_in", "proxy_mid", "proxy_z", "proxy_out") if k in phase_out)
         for k, fl in phase_flops.items():
             if k in phase_out and phase_out[k]["ms_per_step"] > 0:

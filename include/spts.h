@@ -293,7 +293,9 @@ int spts_msdp_compact_batched(spts_ctx *ctx, const void *x_in, const int32_t *po
 
 /* Per-phase timing for benchmarks.  Between spts_profile_begin and spts_profile_end every phase of
  * every call on this context (k_proj, probe_attn, topk, attention, ffn_gate_up, ...) is bracketed
- * by two HIP events on the context's stream.  spts_profile_end synchronises the stream (the only
+ * by two HIP events on the context's stream.  Products that share a launch are one phase (qv_proj:
+ * queries and values; kqv_proj: keys with the probe's queries, the values or a dense layer's queries,
+ * which then have no phase of their own).  spts_profile_end synchronises the stream (the only
  * call of this library that does) and accumulates the elapsed milliseconds and the number of
  * bracketed launches per phase; spts_profile_get reads phase i in [0, spts_profile_count). */
 int spts_profile_begin(spts_ctx *ctx);

@@ -106,20 +106,20 @@ enum PhaseId {
     PH_RMSNORM = 0, PH_K_PROJ, PH_PROBE_Q, PH_PROBE_ATTN, PH_TOPK, PH_GATHER, PH_Q_PROJ, PH_V_PROJ,
     PH_ATTENTION, PH_O_PROJ, PH_PROXY_IN, PH_PROXY_MID, PH_PROXY_Z, PH_PROXY_OUT, PH_FFN_GATE_UP, PH_FFN_DOWN,
     PH_COMPACT, PH_DEC_NORM, PH_DEC_QKV, PH_DEC_ROPE_APPEND, PH_DEC_ATTN, PH_DEC_O, PH_DEC_GATE_UP, PH_DEC_DOWN, PH_DEC_HEAD,
-    PH_BUILD_SALIENCY, PH_BUILD_TOPMEAN, PH_QV_PROJ,
+    PH_BUILD_SALIENCY, PH_BUILD_TOPMEAN, PH_QV_PROJ, PH_KQV_PROJ,
     PH_COUNT
 };
 static const char* const kPhaseNames[PH_COUNT] = {
     "rmsnorm", "k_proj", "probe_q", "probe_attn", "topk", "gather", "q_proj", "v_proj",
     "attention", "o_proj", "proxy_in", "proxy_mid", "proxy_z", "proxy_out", "ffn_gate_up", "ffn_down", "compact",
     "dec_rmsnorm", "dec_qkv", "dec_rope_append", "dec_attention", "dec_o_proj", "dec_gate_up", "dec_down", "dec_head",
-    "build_saliency", "build_topmean", "qv_proj"};
+    "build_saliency", "build_topmean", "qv_proj", "kqv_proj"};
 
 // Brackets the launches issued during its lifetime with two events when profiling is on.
 struct PhaseScope {
     spts_ctx* c; int rec = -1;
     PhaseScope(spts_ctx* ctx, int phase) : c(ctx) {
-        if (!c->prof_on) return;
+        if (!c->prof_on || phase == PH_COUNT) return;
         hipEvent_t e[2];
         for (int i = 0; i < 2; ++i) {
             if (c->ev_used == c->ev_pool.size()) {
@@ -187,7 +187,8 @@ int run_gemm(spts_ctx* c, const GemmArgs& a) {
 // Products that do not depend on one another in one launch, where all are short products of one tile height or all run on the 32x32 tiles
 // (*done; nothing is launched otherwise).  A short prompt's products are 10-15 us each, a third of it the launch and the second pass
 // of its split (333 rows of the 8B shape: K, V and the probe queries 49 -> 23 us, the layer 321 -> 301; fp32 layer of 512 rows 155 -> 139).
-int try_gemm_group(spts_ctx* c, GemmArgs* a, int n, bool* done) {
+// phase: what the launch is timed as, PH_COUNT where the caller's phase has it.
+int try_gemm_group(spts_ctx* c, GemmArgs* a, int n, int phase, bool* done) {
     *done = false;
     if (n < 2 || n > GEMM_GROUP_MAX) return SPTS_OK;
     int mfma = 0;
@@ -195,6 +196,7 @@ int try_gemm_group(spts_ctx* c, GemmArgs* a, int n, bool* done) {
     if (mfma != 0 && mfma != n) return SPTS_OK;   // each keeps the kernel that run_gemm gives it
     if (mfma == 0) {
         if (!gemm_tile32_group_supported(a, n, c->bf16)) return SPTS_OK;
+        PHASE(c, phase);
         SPTS_HIP(c, launch_gemm_tile32_group(a, n, c->bf16, c->stream));
         *done = true;
         return SPTS_OK;
@@ -211,6 +213,7 @@ int try_gemm_group(spts_ctx* c, GemmArgs* a, int n, bool* done) {
         part += bytes;
         have = have > bytes ? have - bytes : 0;
     }
+    PHASE(c, phase);
     SPTS_HIP(c, launch_gemm_small_group(a, plan, n, c->stream));
     *done = true;
     return SPTS_OK;
@@ -340,8 +343,7 @@ int probe_attn_impl(spts_ctx* c, const void* x, const int32_t* pos, int64_t N, c
     if (want_scores && done) done = rope_args(c, probe_query_args(c, N, w, P), nullptr, N - P, c->p<void>(c->off.qp), w->Wq_s, query_store_scale(c), &group[n++]);
     if (done) {
         for (int i = 0; i < n_more && n < GEMM_GROUP_MAX; ++i) group[n++] = more[i];
-        PHASE(c, PH_K_PROJ);
-        SPTS_TRY(try_gemm_group(c, group, n, &done));
+        SPTS_TRY(try_gemm_group(c, group, n, PH_KQV_PROJ, &done));
     }
     if (more_done) *more_done = done;
     if (!done) { PHASE(c, PH_K_PROJ); SPTS_TRY(run_gemm_rope(c, gk, m.Hkv, nullptr, 0, k_out, w->Wk_s)); }
@@ -381,7 +383,7 @@ int proxy_scores_impl(spts_ctx* c, const void* xn2, int64_t N, const spts_layer_
             GemmArgs both[2] = {gemm_args(xn2, m.D, nullptr, w->Ug, m.D, t, 2 * r, N, r, m.D),
                                 gemm_args(xn2, m.D, nullptr, w->Uu, m.D, t + (size_t)r * eb, 2 * r, N, r, m.D)};
             bool done;
-            SPTS_TRY(try_gemm_group(c, both, 2, &done));
+            SPTS_TRY(try_gemm_group(c, both, 2, PH_COUNT, &done));
             for (int i = 0; i < 2 && !done; ++i) SPTS_TRY(run_gemm(c, both[i]));
         }
     }
@@ -1020,9 +1022,12 @@ int spts_layer_prefill(spts_ctx* c, void* x, const int32_t* pos, int64_t N, cons
             if (!q_done) { PHASE(c, PH_QV_PROJ); SPTS_TRY(run_gemm_mfma(c, qv)); }
         } else {
             if (!q_done) { PHASE(c, PH_Q_PROJ); SPTS_TRY(run_gemm_rope(c, gq, m.H, idxA, 0, c->p<void>(c->off.q), w->Wq_s, aa.q_scale)); }
-            PHASE(c, PH_V_PROJ);
-            if (!v_done) SPTS_TRY(run_gemm(c, gv));
-            if (amf && !vt_done) SPTS_HIP(c, launch_transpose_pad(vv, c->p<void>(c->off.vt), Mk, KV, aa.ldvt, c->bf16, st));
+            const bool transpose = amf && !vt_done;
+            if (!v_done || transpose) {
+                PHASE(c, PH_V_PROJ);
+                if (!v_done) SPTS_TRY(run_gemm(c, gv));
+                if (transpose) SPTS_HIP(c, launch_transpose_pad(vv, c->p<void>(c->off.vt), Mk, KV, aa.ldvt, c->bf16, st));
+            }
         }
         if (kv) kv->count = Mk;
         // x[T_a] += att * Wo^T; the attention output (a buffer of the library's own) goes slab-major when the matrix-core
