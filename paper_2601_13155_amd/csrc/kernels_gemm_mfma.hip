@@ -779,13 +779,11 @@ int gemm_pick_split(int64_t M, int32_t N, int32_t K, int epi, int32_t* nfull) {
     return best_ks;
 }
 
-// wavefronts per workgroup used by launch_gemm_mfma (4 or 8)
-#ifndef SPTS_GEMM_NW
-#define SPTS_GEMM_NW 8
-#endif
+// wavefronts per workgroup: the order of a split tile's shares follows it, in the launches and in both second passes
+constexpr int GEMM_NW = 8;
 
 static hipError_t launch_products(const GemmArgs& a, hipStream_t s) {
-    constexpr int NW = SPTS_GEMM_NW;
+    constexpr int NW = GEMM_NW;
     hipError_t e;
     switch (a.epi) {
         case EPI_STORE: e = launch_layout<EPI_STORE, NW>(a, s); break;
@@ -801,7 +799,7 @@ static hipError_t launch_products(const GemmArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
-    constexpr int NW = SPTS_GEMM_NW;
+    constexpr int NW = GEMM_NW;
     const hipError_t e = launch_products(a, s);
     if (e != hipSuccess || a.ksplit <= 1) return e;
     const int nM = (int)((a.M + BM - 1) / BM), nN = a.N / 256;
@@ -828,7 +826,10 @@ __global__ void __launch_bounds__(256) norm_finish_kernel(const float* __restric
     for (int u = 0; u < 4; ++u) {
         const int c = wave * 4 + u;
         const float* p;
-        if (t.tm == 256) p = part + (int64_t)tm * ksplit * 65536 + (((gi >> 2) * 2 + (c >> 3)) * 4 + (gi & 3)) * 2048 + (c & 7) * 256;
+        if (t.tm == 256) {   // wavefront (gi / MI, c / 8) of the product, its block row gi % MI
+            constexpr int MI = 32 / GEMM_NW;
+            p = part + (int64_t)tm * ksplit * 65536 + ((gi / MI * 2 + (c >> 3)) * MI + gi % MI) * 2048 + (c & 7) * 256;
+        }
         else {
             const int half = t.tm / 32, wm = gi / half, in = gi - wm * half;        // row groups of a wavefront
             const int group = tm / 8 * 8, gsz = t.nM - group < 8 ? t.nM - group : 8;
