@@ -354,6 +354,10 @@ static hipError_t launch_gemv_nb_t(const GemvArgs& a, hipStream_t s) {
 // in LDS.  Needs K % 256 == 0 and row counts that are multiples of 16.
 // The weights are read once and are loaded as such (nt): kept in the caches they push out the input vectors, which every strip reads.
 // 8 vectors: table of 128256 x 4096 178 -> 155 us (6.8 TB/s), gate/up 41 -> 36.5, down 22.2 -> 20.5; a step of two layers and the head 467 -> 432.
+// Models that the 256 MB memory-side cache holds from step to step pay for it, the others gain, and a call sees one product only.  Steps of 8
+// vectors, 32000 words, cached -> nt: hidden size 512, 16 layers 598 -> 604 us; 1024, 2 / 8 / 24 layers 95.6 -> 99.4 / 338.7 -> 331.1 /
+// 1005 -> 954; 2048, 1 / 2 / 8 layers 75.4 -> 81.5 / 139.1 -> 131.6 / 462.6 -> 440.  By the product's bytes instead (cached below 4, 16 or 32 MB) the
+// cached products' weights push out the rest: 1024 x 24 layers 954 (4 MB), 1030 (16), 1030 (32); 2048 x 8 layers 448 (4), 442 (16), 465 (32).
 // (8 instead of 16 rows of input vectors in a stage, which makes room for three workgroups per CU or six stages: no faster.)
 typedef __bf16 mfma_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));

@@ -34,6 +34,7 @@ constexpr int SBN = 128;        // tile columns (weight rows)
 constexpr int SBK = 32;         // K slab
 constexpr int SROW = SBK * 2;   // bytes of a tile row in a slab
 template <int TM> constexpr int small_stage_bytes() { return (TM + SBN) * SROW; }
+constexpr int64_t ONCE_BYTES = 4 << 20;   // weights of a product from which on one row tile loads them as data that is read once
 // ring stages: 48 / 64 / 80 KB (even, since the two fragment sets alternate)
 constexpr int SMALL_STAGES = 4;
 
@@ -166,8 +167,11 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
     const int nk = nk_all / ksplit + (split < nk_all % ksplit ? 1 : 0);
     const int kbeg = split * (nk_all / ksplit) + (split < nk_all % ksplit ? split : nk_all % ksplit);
     // With one row tile no other workgroup reads these weights: they are loaded as such and leave the caches to the rows, which all do
-    // (133 rows, in a layer: gate/up 67.5 -> 64.6 us, down 34 -> 29, O 14.6 -> 14; 333 rows, all products 338 -> 314)
-    const bool once = nM == 1;
+    // (133 rows, in a layer: gate/up 67.5 -> 64.6 us, down 34 -> 29, O 14.6 -> 14; 333 rows, all products 338 -> 314).  Not products
+    // below ONCE_BYTES, whose weights the caches keep from call to call at no cost to the rest (us a layer
+    // of 130 rows, with these loads / without / from ONCE_BYTES on: hidden size 512, 16 layers 139.0 / 136.0 / 136.2; 1024, 24 layers
+    // 152.0 / 156.4 / 151.2, 4 layers 151.0 / 144.7 / 148.3; 2048, 8 layers 171.9 / 178.2 / 172.1, 1 layer 172.1 / 164.8 / 171.5).
+    const bool once = nM == 1 && (int64_t)a.N * a.K * (a.epi == EPI_SILU_MUL ? 4 : 2) >= ONCE_BYTES;
     auto issue = [&](int kt, int stage) {
         const int64_t ks = kbeg + kt;
 #pragma unroll
