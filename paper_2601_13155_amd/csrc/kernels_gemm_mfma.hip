@@ -756,7 +756,8 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(GemmArgs a, int nM, 
 }
 
 // Cost model behind the split plan (one workgroup per CU, 256 CUs): a whole tile takes
-// t_tile = 2*256*256*K flops at the sustained per-CU rate; the tail of `rem` tiles costs one t_tile
+// t_tile = 2*256*256*K flops at 4.2 TFLOP/s a CU (a chip of them reaches 1.3 times that now; the splits are as good as measured, see
+// the time models of kernels_gemm_small.hip); the tail of `rem` tiles costs one t_tile
 // unsplit, or ceil(rem*ks/256)/ks of it plus the partial-tile traffic (rem*ks tiles of 256 KB, written
 // and read back) plus one more launch when split ks ways.
 int gemm_pick_split(int64_t M, int32_t N, int32_t K, int epi, int32_t* nfull) {

@@ -20,9 +20,9 @@
 //    dual epilogues combine registers of one lane, also in the finish kernel.  The epilogue is chosen at run time; its finished
 //    quads pass through 32 bytes of scratch memory per lane, once per product.
 //
-// Measured (us from launch to launch, row-major weights from HBM, 256-wide tiles with their split -> here): 64 rows x 4096 x 4096
-// 30 -> 18 (4 shares of K), 133 rows of gate/up 100 -> 67 and of down 64 -> 41 (the weights' HBM time: 39 and 20), proxy z of 512
-// rows 55 -> 19.
+// Measured (us from launch to launch, weights from HBM, 256-wide tiles with their split -> here; slab-major weights, then row-major):
+// 64 rows x 4096 x 4096 26.7 -> 17.0 and 30.0 -> 19.4 (4 shares of K), 133 rows of gate/up 67.2 -> 58.3 and 93.0 -> 79.9, of down
+// 46.2 -> 38.1 and 60.4 -> 46.1 (the weights' HBM time: 39 and 20), proxy z of 512 rows 37.2 -> 16.8 and 39.6 -> 17.0.
 #include "spts_internal.h"
 
 namespace spts {
@@ -392,8 +392,11 @@ bool gemm_small_supported(const GemmArgs& a) {
 }
 
 // Time models (us) behind the choice between the two kernels and among this one's tiles and splits, fitted to 170 measured
-// (product, rows) pairs x 24 (tile, split) pairs: rows 1 .. 16000 of the 8B shape's projections, FFN and proxy products.  Over
-// those the choice costs 2 % on the mean against the best of everything measured.
+// (product, rows) pairs x 24 (tile, split) pairs: rows 1 .. 16000 of the 8B shape's projections, FFN and proxy products, with kernels
+// that read their fragments later and row-major operands in half lines.  The constants were not fitted again since; what counts is the
+// choice, and that was measured with the present kernels, weights from HBM, 7 products x 18 row counts: against the best of everything
+// tried it costs 0.2 % on the mean and 7 % at most (K projection of 800 rows) with slab-major weights, 0.4 % and 12 % (of 5003 rows)
+// with row-major ones.
 //  * this kernel: a K slab takes the load latency (0.18 / 0.31 / 0.38 us at TM = 64 / 128 / 192) or, with more workgroups, the
 //    47 KB/us that a CU's slab loads reach together (rows past M repeat a line and cost a third); a split adds the finish launch
 //    and its fp32 tiles written and read at 4 TB/s.

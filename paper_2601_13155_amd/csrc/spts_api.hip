@@ -187,6 +187,9 @@ int run_gemm(spts_ctx* c, const GemmArgs& a) {
 // Products that do not depend on one another in one launch, where all are short products of one tile height or all run on the 32x32 tiles
 // (*done; nothing is launched otherwise).  A short prompt's products are 10-15 us each, a third of it the launch and the second pass
 // of its split (333 rows of the 8B shape: K, V and the probe queries 49 -> 23 us, the layer 321 -> 301; fp32 layer of 512 rows 155 -> 139).
+// The 32x32 tiles share a launch at any size, although its plain products then have the rotary ones' LDS and half the wavefronts: no size
+// was found where that costs (fp32, hidden size 256, skip layer with all keys of 64 / 1024 / 4096 / 24000 rows 129 -> 112, 192 -> 175, 358 -> 345,
+// 2664 -> 2649 us, dense layer of 12000 rows 1447 -> 1441; 16 heads of 32 and bf16 with 88-wide heads alike).
 // phase: what the launch is timed as, PH_COUNT where the caller's phase has it.
 int try_gemm_group(spts_ctx* c, GemmArgs* a, int n, int phase, bool* done) {
     *done = false;

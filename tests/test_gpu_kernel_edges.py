@@ -124,8 +124,8 @@ def test_layer_with_short_products(torch, H_, Hkv, d, pack):
     ("d128_g7", synth.ModelShape(D=512, H=7, Hkv=1, d=128, Dff=1024, dtype="bf16"), 80),
 ], ids=lambda v: v if isinstance(v, str) else None)
 def test_batch_with_sequences_around_chunks_and_tiles(torch, name, shape, P):
-    """50 sequences (more than one launch of the cache fill takes) whose lengths and budgets lie around the probe's 256-key chunks and
-    the attention's 64-key / 64 .. 256-query tiles, budgets of zero among them; skip and dense branch, every sequence
+    """50 sequences (more than one launch of the cache fill takes) whose lengths and budgets lie around the probe's 64-key tiles (and
+    chunks, which so few candidates leave at 64 keys; longer ones: test_gpu_probe_batches.py) and the attention's 64-key / 64 .. 256-query tiles, budgets of zero among them; skip and dense branch, every sequence
     lock-step against the oracle, caches included."""
     r, mdl = 64, H.oracle_model(shape)
     rng = np.random.default_rng(3)
