@@ -15,10 +15,10 @@
 //      LDS prefix gives each wavefront its output offsets, a second sweep ranks every element inside
 //      the wavefront with ballot + mbcnt (lane prefix popcount) and writes
 //      out[gt_before + min(eq_before, need_eq)].
-// Up to 512 scores a single wavefront decides the threshold bit by bit instead (topk_wave_kernel).
 // Up to 32768 scores the keys are read once and stay in registers (KPT per lane, wavefront w holding
-// the contiguous slice [64*KPT*w, 64*KPT*(w+1))); longer inputs re-read the scores in every sweep.
-// Shortcut for step 1 (register-resident and long-row kernels): one pass builds an 8192-bin histogram
+// the contiguous slice [64*KPT*w, 64*KPT*(w+1))), and the threshold is found by halving the range of keys
+// (topk_reg_kernel); longer inputs re-read the scores in every sweep.
+// Shortcut for step 1 (long-row kernels): one pass builds an 8192-bin histogram
 // of the top 13 key bits, the keys of the bin that holds the k-th largest go to LDS and the remaining
 // 19 bits are resolved there; the four 8-bit passes over all keys remain as the route for rows whose
 // threshold bin does not fit (heavily tied scores).  Both routes yield the same exact threshold.
@@ -87,7 +87,7 @@ __device__ inline void pick_bin(const int* hist, int lane, int shift, uint32_t p
     }
 }
 
-// ---- the threshold bin resolved in LDS (used by the register-resident and the long-row kernels) -------------------
+// ---- the threshold bin resolved in LDS (long-row kernels) -------------------
 // A first histogram over the keys' top 13 bits (sign, exponent, four mantissa bits: a bin is 4.4 % wide in value) finds the
 // bin of the k-th largest key; every wavefront then copies the low 19 bits of ITS keys of that bin into its own LDS
 // region, and three radix passes over those few keys (8 + 8 + 3 bits) give the exact threshold, the number of keys equal
@@ -175,63 +175,40 @@ __device__ inline uint32_t t13_resolve(const uint32_t* cand, int cnt, int64_t ne
     return prefix;
 }
 
-// Short rows (N <= 64 * KPT): one wavefront per problem, KPT keys per lane.  The threshold comes bit by bit, from the top: a bit
-// stays when at least k keys reach the value with it.  No LDS and no barrier, which is what bounds the workgroup kernel below at
-// these lengths: one row of 512 scores 9.0 -> 5.8 us (a launch alone takes 4.5), 512 rows 17.9 -> 6.3.
-constexpr int WAVE_KPT = 8;
-template <int KPT>
-__global__ void __launch_bounds__(64) topk_wave_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
-                                                       int protect_last, int32_t* __restrict__ idx_out, TopkSegments seg) {
-    if (seg.offsets) {
-        const int64_t b0 = seg.offsets[blockIdx.x];
-        N = seg.offsets[blockIdx.x + 1] - b0;
-        k = seg.k[blockIdx.x];
-        scores += b0;
-        idx_out += seg.out_offsets[blockIdx.x];
-        if (k > N) k = N;
-        if (k <= 0 || N <= 0) return;
-    } else {
-        scores += (int64_t)blockIdx.x * N;
-        idx_out += (int64_t)blockIdx.x * k;
-    }
-    const int lane = threadIdx.x, n = (int)N, kk = (int)k;
-    uint32_t keys[KPT];   // element 64 * j + lane; slots past the row hold 0 and are never written out
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) keys[j] = 64 * j + lane < n ? load_key(scores, 64 * j + lane, N, protect_last) : 0u;
-    uint32_t T = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-        const uint32_t t = T | (1u << bit);
-        int c = 0;
-#pragma unroll
-        for (int j = 0; j < KPT; ++j) c += (int)__popcll(__ballot(keys[j] >= t));   // t > 0: no empty slot counts
-        if (c >= kk) T = t;
-    }
-    int need_eq = kk;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) need_eq -= (int)__popcll(__ballot(keys[j] > T));
-    int gt = 0, eq = 0;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        const int i = 64 * j + lane;
-        const bool g_ = keys[j] > T, e_ = i < n && keys[j] == T;
-        const uint64_t mg = __ballot(g_), me = __ballot(e_);
-        const int my_gt = gt + lane_prefix_popc(mg), my_eq = eq + lane_prefix_popc(me);
-        if (g_ || (e_ && my_eq < need_eq)) idx_out[my_gt + (my_eq < need_eq ? my_eq : need_eq)] = i;
-        gt += (int)__popcll(mg);
-        eq += (int)__popcll(me);
-    }
+// sums / minima / maxima over the wavefront's 64 lanes in six DPP steps, the result uniform.  (A lane-crossing shuffle goes through
+// the LDS crossbar: about a hundred cycles a step.)
+template <typename F>
+__device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t v, uint32_t identity, F f) {
+    auto step = [&](auto dpp) { v = f(v, dpp()); };
+    step([&] { return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, 0x111, 0xF, 0xF, false); });   // row_shr 1
+    step([&] { return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, 0x112, 0xF, 0xF, false); });   // row_shr 2
+    step([&] { return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, 0x114, 0xF, 0xF, false); });   // row_shr 4
+    step([&] { return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, 0x118, 0xF, 0xF, false); });   // row_shr 8
+    step([&] { return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, 0x142, 0xA, 0xF, false); });   // row_bcast 15
+    step([&] { return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, 0x143, 0xC, 0xF, false); });   // row_bcast 31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Register-resident variant: N <= 1024 * KPT.  Lane keeps keys[j] = key of element lo + 64*j + lane,
-// lo = 64*KPT*wave; slots at or beyond N hold key 0 and are never written out.
-template <int KPT>
-__global__ void __launch_bounds__(TOPK_THREADS) topk_reg_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
-                                                                int protect_last, int32_t* __restrict__ idx_out, TopkSegments seg) {
-    extern __shared__ __attribute__((aligned(16))) char lsm[];
-    int* h13 = reinterpret_cast<int*>(lsm);                                                   // [T13_BINS]
-    uint32_t (*cand)[T13_CW] = reinterpret_cast<uint32_t (*)[T13_CW]>(lsm);                   // [TOPK_WAVES][T13_CW], after the histogram
-    __shared__ TopkShared sh;
-    int* const hist = sh.hist;
+// Register-resident variant: N <= 64 * KPT * W, one workgroup of W wavefronts per problem.  Lane keeps keys[j] = key of element
+// lo + 64*j + lane, lo = 64*KPT*wave; slots at or beyond N hold key 0, which no
+// threshold reaches (scores have keys from 1 on).
+// The threshold is searched for between the row's smallest and largest key: a round counts the keys that reach the middle (a
+// compare per key, summed on the scalar unit -- of 12 and more keys every third on the vector unit, since the scalar one runs out --, one LDS
+// atomic per wavefront, one barrier) and keeps one half, until that holds at most 64 keys or a single value.  Those keys go to LDS, and
+// every wavefront decides the rest of the threshold for itself, bit by bit, one key per lane, without a barrier.  A round that leaves
+// every key in has met few values: the range then shrinks to the outermost of them, so ties need no route of their own.
+// Bound: latency (a launch that does nothing takes 4.3 us; a round 0.25 us at 8 keys per lane, 10 of them), from 16 keys per
+// lane on also the compares and the output's ranks.  With a histogram of the keys' top 13 bits (LDS atomics that meet in few bins, 8192 bins
+// cleared and scanned, three more passes for the other bits) in the place of the rounds a row of 700 scores took 8.9 us, now 4.5; 2048 9.1, now
+// 5.2; 8192 10.6, now 9.1; 20001 24.7, now 14.4; 32768 27.1, now 20.1; 512 rows of them 17.9, 18.4, 21.6, 64.7, 70.9, now 5.5, 7.7, 15.3, 27.5, 49.4.
+// Up to 512 scores: one wavefront that decided all 32 bits 5.9, now 4.4 (512 rows 6.5, now 4.9).  Three thresholds a round: 10.5 us at 8192.
+template <int KPT, int W>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 8))) topk_reg_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
+                                                            int protect_last, int32_t* __restrict__ idx_out, TopkSegments seg) {
+    constexpr int ROUNDS = 33;   // a round leaves at most half of a 32-bit range
+    __shared__ int count[ROUNDS];
+    __shared__ uint32_t cand[64], wave_min[W], wave_max[W];
+    __shared__ int cands, wave_ge[W], wave_gt[W];
 
     // one independent problem per workgroup: equal rows, or the segment the descriptors give it
     if (seg.offsets) {
@@ -246,92 +223,155 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_reg_kernel(const float* __r
         scores += (int64_t)blockIdx.x * N;
         idx_out += (int64_t)blockIdx.x * k;
     }
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = (int)N, kk = (int)k, last = protect_last ? n - 1 : -1;   // the protected score is above all others: left out of the search
     const int lo = wave * (64 * KPT);
 
+    auto umin = [](uint32_t a, uint32_t b) { return min(a, b); };
+    auto umax = [](uint32_t a, uint32_t b) { return max(a, b); };
+    auto uadd = [](uint32_t a, uint32_t b) { return a + b; };
+    // sum of the first `m` wavefronts' entries
+    auto sum_of = [&](const int* per_wave, int m) { return (int)wave_reduce_u32(lane < m ? (uint32_t)per_wave[lane & (W - 1)] : 0u, 0u, uadd); };
     uint32_t keys[KPT];
+    if (tid < ROUNDS) count[tid] = 0;
+    if (tid == 0) cands = 0;
+    {
+        float v[KPT];
+        uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+        if (lo + 64 * KPT <= n && !(last >= lo && last < lo + 64 * KPT)) {   // every slot has a key that is searched
+            const float* p = scores + lo + lane;
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        const int64_t i = lo + 64 * j + lane;
-        keys[j] = i < N ? load_key(scores, i, N, protect_last) : 0u;
-    }
-
-    // one pass over the keys for their top 13 bits, the rest of the threshold from the bin's keys in LDS
-    uint32_t T = 0;
-    int need_eq = 0;
-    for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
-    if (tid == 0) { sh.over = 0; sh.bin = 0; sh.need = k; }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) hist_add(h13, lo + 64 * j + lane < N, (int)(keys[j] >> T13_LOW));
-    __syncthreads();
-    t13_pick(h13, k, sh.wave_tot, &sh.bin, &sh.need);
-    const uint32_t bin = (uint32_t)sh.bin;
-    int cnt = 0, cgt = 0;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        const bool valid = lo + 64 * j + lane < N;
-        const uint32_t top = keys[j] >> T13_LOW;
-        cgt += (int)__popcll(__ballot(valid && top > bin));
-        const bool in = valid && top == bin;
-        const uint64_t m = __ballot(in);
-        const int at = cnt + lane_prefix_popc(m);
-        if (in && at < T13_CW) cand[wave][at] = keys[j] & ((1u << T13_LOW) - 1u);
-        cnt += (int)__popcll(m);
-    }
-    if (lane == 0 && cnt > T13_CW) sh.over = 1;
-    __syncthreads();
-    if (sh.over == 0) {
-        int g, e;
-        const uint32_t low = t13_resolve(cand[wave], cnt, sh.need, hist, &sh.prefix, &sh.need, &need_eq, &g, &e);
-        T = (bin << T13_LOW) | low;
-        if (lane == 0) { sh.wave_gt[wave] = cgt + g; sh.wave_eq[wave] = e; }
-    } else {
-        // heavily tied keys: four 8-bit passes over the registers
-        if (tid == 0) { sh.prefix = 0; sh.need = k; }
-        uint32_t prefix = 0;
-        int64_t need = k;
-        for (int pass = 0; pass < 4; ++pass) {
-            const int shift = 24 - 8 * pass;
-            const uint32_t hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-            if (tid < 256) hist[tid] = 0;
-            __syncthreads();
+            for (int j = 0; j < KPT; ++j) v[j] = p[64 * j];
 #pragma unroll
             for (int j = 0; j < KPT; ++j) {
-                const bool valid = lo + 64 * j + lane < N;
-                hist_add(hist, valid && (keys[j] & hi_mask) == prefix, (int)((keys[j] >> shift) & 0xFF));
+                keys[j] = max(order_key(v[j]), 1u);
+                mn = min(mn, keys[j]);
+                mx = max(mx, keys[j]);
             }
-            __syncthreads();
-            if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh.prefix, &sh.need);
-            __syncthreads();
-            prefix = sh.prefix;
-            need = sh.need;
-        }
-        T = prefix;
-        need_eq = (int)need;
-        int ceq = 0;
-        cgt = 0;
+        } else {
 #pragma unroll
-        for (int j = 0; j < KPT; ++j) {
-            const bool valid = lo + 64 * j + lane < N;
-            cgt += (int)__popcll(__ballot(valid && keys[j] > T));
-            ceq += (int)__popcll(__ballot(valid && keys[j] == T));
+            for (int j = 0; j < KPT; ++j) {
+                v[j] = 0.f;
+                if (lo + 64 * j < n) v[j] = scores[min(lo + 64 * j + lane, n - 1)];
+            }
+#pragma unroll
+            for (int j = 0; j < KPT; ++j) {
+                const int i = lo + 64 * j + lane;
+                const uint32_t key = max(order_key(v[j]), 1u);
+                const bool in = i < n && i != last;
+                keys[j] = in ? key : 0u;
+                mn = min(mn, in ? key : 0xFFFFFFFFu);
+                mx = max(mx, keys[j]);
+            }
         }
-        if (lane == 0) { sh.wave_gt[wave] = cgt; sh.wave_eq[wave] = ceq; }
+        mn = wave_reduce_u32(mn, 0xFFFFFFFFu, umin);
+        mx = wave_reduce_u32(mx, 0u, umax);
+        if (lane == 0) { wave_min[wave] = mn; wave_max[wave] = mx; }
     }
     __syncthreads();
-    int gt_before = 0, eq_before = 0;
-    for (int w = 0; w < wave; ++w) { gt_before += sh.wave_gt[w]; eq_before += sh.wave_eq[w]; }
+    const int want = protect_last ? kk - 1 : kk;   // rank of the threshold among the searched keys
+    uint32_t T = 0xFFFFFFFFu;
+    if (want > 0) {
+        // the threshold lies in [lo_key, lo_key + width]: c_lo >= want keys reach the lower end, c_hi < want are above the upper one
+        uint32_t lo_key = wave_reduce_u32(wave_min[lane & (W - 1)], 0xFFFFFFFFu, umin);
+        uint32_t width = wave_reduce_u32(wave_max[lane & (W - 1)], 0u, umax) - lo_key;
+        int c_lo = protect_last ? n - 1 : n, c_hi = 0, held = 0;
+        for (int round = 0; c_lo - c_hi > 64 && width > 0; ++round) {
+            const uint32_t off = (width >> 1) + 1, t = lo_key + off;   // > 0: no empty slot counts
+            int c = 0, mine = 0;
+#pragma unroll
+            for (int j = 0; j < KPT; ++j) {
+                if (KPT >= 12 && j % 3 == 2) mine += keys[j] >= t ? 1 : 0;
+                else c += (int)__popcll(__ballot(keys[j] >= t));
+            }
+            if (KPT >= 12) c += (int)wave_reduce_u32((uint32_t)mine, 0u, uadd);
+            if (lane == 0) atomicAdd(&count[round], c);
+            __syncthreads();
+            c = __builtin_amdgcn_readfirstlane(count[round]);
+            if (c >= want) { lo_key = t; width -= off; c_lo = c; }
+            else { width = off - 1; c_hi = c; }
+            const int inside = c_lo - c_hi;
+            if (inside == held && inside > 64) {
+                // a round that left every key in: the part's keys are few values, and its ends move to the outermost of them
+                uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+#pragma unroll
+                for (int j = 0; j < KPT; ++j) {
+                    const uint32_t d = keys[j] - lo_key;
+                    mn = min(mn, d <= width ? d : 0xFFFFFFFFu);
+                    mx = max(mx, d <= width ? d : 0u);
+                }
+                mn = wave_reduce_u32(mn, 0xFFFFFFFFu, umin);
+                mx = wave_reduce_u32(mx, 0u, umax);
+                if (lane == 0) { wave_min[wave] = mn; wave_max[wave] = mx; }
+                __syncthreads();
+                mn = wave_reduce_u32(wave_min[lane & (W - 1)], 0xFFFFFFFFu, umin);
+                mx = wave_reduce_u32(wave_max[lane & (W - 1)], 0u, umax);
+                lo_key += mn;
+                width = mx - mn;
+            }
+            held = inside;
+        }
+        T = lo_key;
+        if (width > 0) {
+            const uint32_t first = lo_key;
+#pragma unroll
+            for (int j = 0; j < KPT; ++j)
+                if (keys[j] - first <= width) cand[atomicAdd(&cands, 1) & 63] = keys[j] - first;
+            __syncthreads();
+            const uint32_t d = lane < c_lo - c_hi ? cand[lane] : 0u;
+            const int rank = want - c_hi;
+            uint32_t t = 0;
+            for (int bit = 31 - __builtin_clz(width); bit >= 0; --bit) {
+                const uint32_t at = t | (1u << bit);
+                if ((int)__popcll(__ballot(d >= at)) >= rank) t = at;
+            }
+            T = first + t;
+        }
+    }
+    if (last >= lo && last < lo + 64 * KPT) {
+#pragma unroll
+        for (int j = 0; j < KPT; ++j)
+            if (lo + 64 * j + lane == last) keys[j] = 0xFFFFFFFFu;
+    }
+
+    int ge = 0;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) ge += (int)__popcll(__ballot(keys[j] >= T));
+    if (lane == 0) wave_ge[wave] = ge;
+    __syncthreads();
+    const int total = sum_of(wave_ge, W);
+    int before = sum_of(wave_ge, wave);
+    if (total == kk) {   // every key that reaches the threshold is selected
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) {
+            const bool sel = keys[j] >= T;
+            const uint64_t m = __ballot(sel);
+            const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, before));
+            if (sel) idx_out[(uint32_t)at] = lo + 64 * j + lane;
+            before += (int)__popcll(m);
+        }
+        return;
+    }
+    // of the keys equal to the threshold only the first need_eq are taken
+    int gt = 0, eq = 0;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        gt += (int)__popcll(__ballot(keys[j] > T));
+        eq += (int)__popcll(__ballot(keys[j] == T));
+    }
+    __syncthreads();
+    if (lane == 0) { wave_gt[wave] = gt; wave_ge[wave] = eq; }
+    __syncthreads();
+    const int need_eq = kk - sum_of(wave_gt, W);
+    int gt_before = sum_of(wave_gt, wave), eq_before = sum_of(wave_ge, wave);
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
         const int i = lo + 64 * j + lane;
-        const bool valid = i < N;
-        const bool gt = valid && keys[j] > T, eq = valid && keys[j] == T;
-        const uint64_t mgt = __ballot(gt), meq = __ballot(eq);
+        const bool g_ = keys[j] > T, e_ = keys[j] == T;
+        const uint64_t mgt = __ballot(g_), meq = __ballot(e_);
         const int my_gt = gt_before + lane_prefix_popc(mgt);
         const int my_eq = eq_before + lane_prefix_popc(meq);
-        if (gt || (eq && my_eq < need_eq)) idx_out[my_gt + (my_eq < need_eq ? my_eq : need_eq)] = i;
+        if (g_ || (e_ && my_eq < need_eq)) idx_out[my_gt + (my_eq < need_eq ? my_eq : need_eq)] = i;
         gt_before += (int)__popcll(mgt);
         eq_before += (int)__popcll(meq);
     }
@@ -1300,21 +1340,22 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
     // with segments N is the longest segment (it picks the kernel variant) and k is ignored
     if ((k <= 0 && !seg.offsets) || N <= 0 || batch <= 0) return hipSuccess;
     const dim3 g((unsigned)batch), b(TOPK_THREADS);
-    // 16 keys per lane (1024 scores) would be a longer serial chain than the workgroup kernel's barriers: 10.3 against 9.0 us a row
-    if (N <= 64 * WAVE_KPT) {
-        topk_wave_kernel<WAVE_KPT><<<g, dim3(64), 0, s>>>(scores, N, k, protect_last, idx_out, seg);
-    } else if (N <= 1024 * 32) {
-        hipError_t e;
-        if (N <= 1024 * 8) {
-            if ((e = ensure_dynamic_lds(reinterpret_cast<const void*>(&topk_reg_kernel<8>), T13_LDS_BYTES)) != hipSuccess) return e;
-            topk_reg_kernel<8><<<g, b, T13_LDS_BYTES, s>>>(scores, N, k, protect_last, idx_out, seg);
-        } else if (N <= 1024 * 16) {
-            if ((e = ensure_dynamic_lds(reinterpret_cast<const void*>(&topk_reg_kernel<16>), T13_LDS_BYTES)) != hipSuccess) return e;
-            topk_reg_kernel<16><<<g, b, T13_LDS_BYTES, s>>>(scores, N, k, protect_last, idx_out, seg);
-        } else {
-            if ((e = ensure_dynamic_lds(reinterpret_cast<const void*>(&topk_reg_kernel<32>), T13_LDS_BYTES)) != hipSuccess) return e;
-            topk_reg_kernel<32><<<g, b, T13_LDS_BYTES, s>>>(scores, N, k, protect_last, idx_out, seg);
-        }
+    if (N <= TOPK_REG_MAX_N) {
+        // The smallest of these workgroups that holds the row: a round costs a compare per slot, empty or not, and 16 wavefronts wait
+        // longer for one another than 8 (4000 scores: 6.6 us with 8 x 8 slots, 7.3 with 4 x 16; 6000: 8.2 with 6 x 16, 8.6 with 12 x 8).
+#define SPTS_TOPK_REG(KPT, W) topk_reg_kernel<KPT, W><<<g, dim3(64 * W), 0, s>>>(scores, N, k, protect_last, idx_out, seg)
+        if (N <= 512) SPTS_TOPK_REG(2, 4);
+        else if (N <= 1024) SPTS_TOPK_REG(4, 4);
+        else if (N <= 2048) SPTS_TOPK_REG(4, 8);
+        else if (N <= 3072) SPTS_TOPK_REG(6, 8);
+        else if (N <= 4096) SPTS_TOPK_REG(8, 8);
+        else if (N <= 6144) SPTS_TOPK_REG(6, 16);
+        else if (N <= 8192) SPTS_TOPK_REG(8, 16);
+        else if (N <= 12288) SPTS_TOPK_REG(12, 16);
+        else if (N <= 16384) SPTS_TOPK_REG(16, 16);
+        else if (N <= 24576) SPTS_TOPK_REG(24, 16);
+        else SPTS_TOPK_REG(32, 16);
+#undef SPTS_TOPK_REG
     }
     else if (!seg.offsets && N % 4 == 0 && N < ((int64_t)1 << 30)) {
         // the bracket needs sample ranks on both of its sides: budgets between 1/64 and 63/64 of the row (k = 0.5 % of 512 x 131072: three

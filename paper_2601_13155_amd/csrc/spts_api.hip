@@ -450,7 +450,7 @@ int gather_rows_maps(spts_ctx* c, const void* in, const int32_t* idx, void* out,
 
 // TopK of one score row: longer rows are spread over the chip (a launch per radix pass), short ones stay in one workgroup
 int run_topk(spts_ctx* c, const float* scores, int64_t N, int64_t k, int protect_last, int32_t* idx_out) {
-    if (N >= TOPK_MULTI_MIN_N && N <= TOPK_MULTI_MAX_N)
+    if (N > TOPK_REG_MAX_N && N <= TOPK_MULTI_MAX_N)
         SPTS_HIP(c, launch_topk_multi(scores, N, k, protect_last, idx_out, c->p<void>(c->off.topk), c->stream));
     else
         SPTS_HIP(c, launch_topk(scores, N, k, protect_last, idx_out, 1, c->stream));

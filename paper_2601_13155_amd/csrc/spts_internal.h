@@ -211,7 +211,7 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
 // read was written earlier in the same call); calls sharing a scratch must not overlap.  N <= TOPK_MULTI_MAX_N.
 constexpr int TOPK_MULTI_MAX_WG = 128;
 constexpr int64_t TOPK_MULTI_MAX_N = (int64_t)TOPK_MULTI_MAX_WG * 8192;
-constexpr int64_t TOPK_MULTI_MIN_N = 20000;   // shorter rows: one workgroup with the keys in registers is as fast (measured crossover)
+constexpr int64_t TOPK_REG_MAX_N = 32768;     // one workgroup with the keys in registers; one row of 32768 20.1 us, over the chip 22 (20001: 14.4 and 20.5)
 constexpr size_t TOPK_MULTI_SCRATCH_BYTES = 2 * (size_t)TOPK_MULTI_MAX_WG * 256 * 4 + (size_t)TOPK_MULTI_MAX_WG * 4 + 64;
 // device address of this GPU's file-scope scratch array of TOPK_MULTI_SCRATCH_BYTES (looked up once per device, then cached)
 hipError_t topk_static_scratch(void** out);

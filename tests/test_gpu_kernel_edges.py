@@ -215,13 +215,35 @@ def test_long_row_topk_patterns(torch, n):
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 333, 511, 512, 513, 1023, 1024, 1025])
 def test_short_row_topk(torch, n):
-    """Around the lengths where the wavefront kernel (up to 512 scores) and the workgroup kernel meet."""
+    """Rows of up to a thousand scores, down to one."""
     rng = np.random.default_rng(n)
     rows = np.stack([np.exp(rng.standard_normal(n)), rng.standard_normal(n), np.full(n, 0.25), np.round(2 * rng.standard_normal(n)),
                      np.where(rng.random(n) < 0.5, -0.0, 0.0), np.full(n, -np.inf)]).astype(np.float32)
     sd = torch.from_numpy(rows).cuda()
     ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
     for k in sorted({1, max(1, n // 3), max(1, n - 1), n}):
+        for protect in (0, 1):
+            out = torch.full((len(rows) * k + 1,), -7, dtype=torch.int32, device="cuda")
+            ctx.spts_select_topk_batched(sd, n, k, protect, len(rows), out)
+            got = out.cpu().numpy()
+            assert got[-1] == -7
+            for b in range(len(rows)):
+                assert np.array_equal(got[b * k:(b + 1) * k], orc.topk_select(rows[b], k, protect)), (b, k, protect)
+
+
+@pytest.mark.parametrize("n", [256, 257, 512, 513, 1024, 1025, 2048, 2049, 3072, 3073, 4096, 4097, 6144, 6145, 8192, 8193, 12288, 12289, 16384, 16385, 24576, 24577,
+                               32767, 32768])
+def test_register_topk_edges(torch, n):
+    """The largest and smallest rows of every workgroup size of the register-resident kernel: thresholds among more than 64 neighbouring
+    keys, among equal ones at the ends and in the middle of the range, and scores of both signs, the largest and minus infinity."""
+    rng = np.random.default_rng(n)
+    z = rng.standard_normal(n).astype(np.float32)
+    near = (np.float32(0.5).view(np.int32) + rng.integers(0, max(2, n // 3), n).astype(np.int32)).view(np.float32)
+    inf = z.copy(); inf[rng.random(n) < 0.3] = 3e38; inf[rng.random(n) < 0.3] = -np.inf
+    rows = np.stack([z, near, inf, np.where(z > 0, 1.0, -1.0), np.where(np.arange(n) == n // 2, 3.0, 0.0), np.exp(15 * z), np.sort(z)]).astype(np.float32)
+    sd = torch.from_numpy(rows).cuda()
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    for k in sorted({1, 2, n // 7, n // 2, n - 1, n}):
         for protect in (0, 1):
             out = torch.full((len(rows) * k + 1,), -7, dtype=torch.int32, device="cuda")
             ctx.spts_select_topk_batched(sd, n, k, protect, len(rows), out)
