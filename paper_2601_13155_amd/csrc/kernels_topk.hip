@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float* __restr
     }
 }
 
-// Long rows of a batch (N > 32768, N % 4 == 0, equal rows): one workgroup per row as above, but written for streaming.
+// Long rows of a batch (N > 32768, equal rows): one workgroup per row as above, but written for streaming.
 // Every wavefront owns one contiguous slice in all sweeps and reads it as 16-byte loads, four per lane in flight (64 KB per
 // workgroup).
 // Three sweeps over the row in the usual case: (1) an 8192-bin histogram of the keys' top 13 bits (sign, exponent, four
@@ -467,9 +467,22 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float* __restr
 // over LDS, which also leave each wavefront's (greater, equal) counts; (3) the ordered compaction.  If a wavefront's
 // keys of the bin do not fit its region (heavily tied scores), the kernel falls back to four 8-bit passes over the row with
 // histograms private to the wavefront, six sweeps in all; both routes end in the same exact (threshold, rank) pair.
+// A length that is no multiple of 4 leaves rows at 4-byte addresses, which 16-byte loads take (512 rows of 131071: 112 us, of 131072
+// 113; one row 46 and 46, where scores read one by one in six sweeps took 477 and 231), and a last piece of one to three scores, which is loaded from the row's end, moved into place and padded with minus
+// infinity: no score is smaller and none comes later, so a padded place is never among the k <= N selected.
 typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int LONG_U = 4;                       // 16-byte loads in flight per lane
 constexpr int LONG_STEP = 64 * 4 * LONG_U;      // scores a wavefront takes per iteration
+
+// the piece [i0, i0 + 4) of a row of n scores, minus infinity in the places past it, from the four scores at min(i0, n - 4); for i0 >= n any of these
+__device__ __forceinline__ f32x4v end_piece(f32x4v v, int i0, int n) {
+    const int by = i0 - min(i0, n - 4);
+    const float none = -__builtin_inff();
+    if (by & 1) v = f32x4v{v[1], v[2], v[3], none};
+    if (by & 2) v = f32x4v{v[2], v[3], none, none};
+    return v;
+}
 
 // HINT: a caller that has reason to believe that the k-th largest key begins with the 16 bits `top16` (>= 0) skips the sweeps and passes before
 // those that resolve the other 16; the counts of the first of them tell when it does not, and all four follow.
@@ -483,18 +496,23 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)N;
     const int per_wave = ((n + TOPK_WAVES - 1) / TOPK_WAVES + LONG_STEP - 1) / LONG_STEP * LONG_STEP;
-    const int lo = wave * per_wave;
-    const int hi = lo + per_wave < n ? lo + per_wave : n;   // n % 4 == 0, so a 16-byte load that starts below hi ends below it
+    const int lo = __builtin_amdgcn_readfirstlane(wave * per_wave);
+    const int hi = lo + per_wave < n ? lo + per_wave : n;   // of a piece that starts below hi, places past it are minus infinity
+    auto load_step = [&](int base, f32x4v (&v)[LONG_U]) {   // the pieces of one iteration
+#pragma unroll
+        for (int u = 0; u < LONG_U; ++u) v[u] = *reinterpret_cast<const f32x4u*>(scores + (uint32_t)min(base + u * 256 + lane * 4, n - 4));
+        if (base + LONG_STEP > n) {
+#pragma unroll
+            for (int u = 0; u < LONG_U; ++u) v[u] = end_piece(v[u], base + u * 256 + lane * 4, n);
+        }
+    };
     const uint32_t last_key_at = protect_last ? (uint32_t)(n - 1) : 0xFFFFFFFFu;
 
     // one iteration of a sweep over the wavefront's slice: the keys of load u, element e (index i0 + e) go to BODY
 #define SPTS_LONG_SWEEP(BODY)                                                                              \
     for (int base = lo; base < hi; base += LONG_STEP) {                                                    \
         f32x4v v[LONG_U];                                                                                  \
-        _Pragma("unroll") for (int u = 0; u < LONG_U; ++u) {                                               \
-            const int i0 = base + u * 256 + lane * 4;                                                      \
-            v[u] = i0 < hi ? *reinterpret_cast<const f32x4v*>(scores + i0) : f32x4v{0.f, 0.f, 0.f, 0.f};   \
-        }                                                                                                  \
+        load_step(base, v);                                                                                \
         _Pragma("unroll") for (int u = 0; u < LONG_U; ++u) {                                               \
             const int i0 = base + u * 256 + lane * 4;                                                      \
             const bool valid = i0 < hi;                                                                    \
@@ -520,8 +538,8 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
         SPTS_LONG_SWEEP({ hist_add(h13, valid, (int)(key >> T13_LOW)); })
         __syncthreads();
         t13_pick(h13, k, sh.wave_tot, &sh.bin, &sh.need);
-        b12 = (uint32_t)sh.bin;
-        need = sh.need;
+        b12 = (uint32_t)__builtin_amdgcn_readfirstlane(sh.bin);
+        need = __builtin_amdgcn_readfirstlane((int)sh.need);
         // ---- sweep 2: the wavefront's keys of that bin into its LDS region (low 19 bits), keys of higher bins counted
         SPTS_LONG_SWEEP({
             const uint32_t top = key >> T13_LOW;
@@ -575,8 +593,8 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
             __syncthreads();
             if (wave == 0) pick_bin(hist, lane, shift, prefix, need, &sh.prefix, &sh.need);
             __syncthreads();
-            prefix = HINT ? (uint32_t)__builtin_amdgcn_readfirstlane(sh.prefix) : sh.prefix;
-            need = HINT ? __builtin_amdgcn_readfirstlane((int)sh.need) : sh.need;
+            prefix = (uint32_t)__builtin_amdgcn_readfirstlane(sh.prefix);
+            need = __builtin_amdgcn_readfirstlane((int)sh.need);
             if (HINT && need == 0) {   // no bin holds that rank: not the key's first bits
                 prefix = 0; need = k; top16 = -1; pass = -1;
             }
@@ -601,11 +619,7 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
     // ordered compaction of the slice: index order inside an iteration is (load u, lane, element e)
     for (int base = lo; base < hi; base += LONG_STEP) {
         f32x4v v[LONG_U];
-#pragma unroll
-        for (int u = 0; u < LONG_U; ++u) {
-            const int i0 = base + u * 256 + lane * 4;
-            v[u] = i0 < hi ? *reinterpret_cast<const f32x4v*>(scores + i0) : f32x4v{0.f, 0.f, 0.f, 0.f};
-        }
+        load_step(base, v);
 #pragma unroll
         for (int u = 0; u < LONG_U; ++u) {
             const int i0 = base + u * 256 + lane * 4;
@@ -635,14 +649,14 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
     }
 }
 
-__global__ void __launch_bounds__(TOPK_THREADS) topk_long_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
+__global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) topk_long_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
                                                                  int protect_last, int32_t* __restrict__ idx_out) {
     extern __shared__ __attribute__((aligned(16))) char lsm[];
     __shared__ TopkShared sh;
     topk_long_rows<false>(scores + (int64_t)blockIdx.x * N, N, k, protect_last, idx_out + (int64_t)blockIdx.x * k, lsm, sh);
 }
 
-// The same rows read from memory once (32768 < N <= LONG1_MAX_N, N % 4 == 0).  A sample of 8192 scores spread over the row gives, through
+// The same rows read from memory once (32768 < N <= LONG1_MAX_N).  A sample of 8192 scores spread over the row gives, through
 // the 8192-bin histogram and 8 more bits of the keys in its bins, two keys that bracket the k-th largest with four standard
 // deviations of the sample's quantile on either side (about 4 % of the row lies between them, whatever the scores' spread).  One
 // sweep over the row then leaves, per score, a bit of the lane's own in LDS (above the bracket), and the keys inside the bracket, with
@@ -721,7 +735,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
         f32x4v v[2];
 #pragma unroll
         for (int p = 0; p < 2; ++p)
-            v[p] = *reinterpret_cast<const f32x4v*>(scores + 4 * (int64_t)((int64_t)(2 * tid + p) * quads / (LONG1_SAMPLES / 4)));
+            v[p] = *reinterpret_cast<const f32x4u*>(scores + 4 * (int64_t)((int64_t)(2 * tid + p) * quads / (LONG1_SAMPLES / 4)));
         for (int i = tid; i < T13_BINS; i += TOPK_THREADS) h13[i] = 0;
         if (tid < 512) h8[tid] = 0;
         __syncthreads();
@@ -773,7 +787,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
 
     // ---- the one sweep: wavefront w owns a contiguous slice
     const int lo = wave * per_wave;
-    const int hi = lo + per_wave < n ? lo + per_wave : n;   // n % 4 == 0, so a 16-byte load that starts below hi ends below it
+    const int hi = lo + per_wave < n ? lo + per_wave : n;   // of a piece that starts below hi, places past it are minus infinity
     const int last = protect_last ? n - 1 : -1;
     // Bit 31 - (4 u + e) of word w: element e of the slice's load 8 w + u lies above the bracket (later: is selected).  A key inside the bracket is kept as (key - lo_key) >> shift << 11 | (4 u + e) << 6 | lane;
     // its word follows from the region's fill at the word's end.
@@ -791,7 +805,8 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
 #pragma unroll
                 for (int u = 0; u < LONG_U; ++u) {
                     const int i0 = base + u * 256 + lane * 4;
-                    v[u] = *reinterpret_cast<const f32x4v*>(scores + (ALL || i0 < hi ? i0 : n - 4));   // past the slice: any place of the row
+                    v[u] = *reinterpret_cast<const f32x4u*>(scores + (ALL ? (uint32_t)i0 : (uint32_t)min(i0, n - 4)));
+                    if (!ALL) v[u] = end_piece(v[u], i0, n);
                 }
 #pragma unroll
                 for (int u = 0; u < LONG_U; ++u) {
@@ -863,7 +878,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     uint32_t T = prefix >> 11;   // the threshold's distance from lo_key, as far as the regions keep it
     if (shift > 0) {
         // 8 + 3 more bits among the keys that share those 21, then every entry's distance becomes 2 / 1 / 0: above / equal / below
-        auto low_bits = [&](uint32_t c, int j) { return (load_key(scores, lo + (int)place(c, j), N, protect_last) - lo_key) & ((1u << shift) - 1u); };
+        auto low_bits = [&](uint32_t c, int j) { return (load_key(scores, min(lo + (int)place(c, j), n - 1), N, protect_last) - lo_key) & ((1u << shift) - 1u); };
         prefix = 0;
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {
@@ -1357,7 +1372,7 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
         else SPTS_TOPK_REG(32, 16);
 #undef SPTS_TOPK_REG
     }
-    else if (!seg.offsets && N % 4 == 0 && N < ((int64_t)1 << 30)) {
+    else if (!seg.offsets && N < ((int64_t)1 << 30)) {
         // the bracket needs sample ranks on both of its sides: budgets between 1/64 and 63/64 of the row (k = 0.5 % of 512 x 131072: three
         // sweeps, 152 us)
         if (N <= LONG1_MAX_N && k * 64 >= N && (N - k) * 64 >= N) {

@@ -231,6 +231,27 @@ def test_short_row_topk(torch, n):
                 assert np.array_equal(got[b * k:(b + 1) * k], orc.topk_select(rows[b], k, protect)), (b, k, protect)
 
 
+@pytest.mark.parametrize("n", [32769, 32770, 32771, 65537, 98305, 100003, 131069, 131071, 131073, 262147])
+def test_long_row_topk_of_rows_at_odd_addresses(torch, n):
+    """Lengths that are no multiple of 4: rows at any 4-byte address, a last piece of one to three scores, one that begins a wavefront's slice;
+    with the row's end among the largest, the smallest (minus infinity, so that padding ties with it) and the equal scores."""
+    rng = np.random.default_rng(n)
+    base = np.exp(0.5 * rng.standard_normal(n)).astype(np.float32) / n
+    end = base.copy(); end[-3:] = (5.0, 4.0, 6.0)
+    low = base.copy(); low[-5:] = -np.inf; low[rng.random(n) < 0.3] = -np.inf
+    rows = np.stack([base, end, low, np.full(n, 0.25), np.full(n, -np.inf), np.sort(base), np.round(2 * rng.standard_normal(n)), rng.standard_normal(n)]).astype(np.float32)
+    sd = torch.from_numpy(rows).cuda()
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    for k in (1, n // 100, int(0.4 * n), n - n // 20, n - 1, n):
+        for protect in (0, 1):
+            out = torch.full((len(rows) * k + 1,), -7, dtype=torch.int32, device="cuda")
+            ctx.spts_select_topk_batched(sd, n, k, protect, len(rows), out)
+            got = out.cpu().numpy()
+            assert got[-1] == -7
+            for b in range(len(rows)):
+                assert np.array_equal(got[b * k:(b + 1) * k], orc.topk_select(rows[b], k, protect)), (b, k, protect)
+
+
 @pytest.mark.parametrize("n", [256, 257, 512, 513, 1024, 1025, 2048, 2049, 3072, 3073, 4096, 4097, 6144, 6145, 8192, 8193, 12288, 12289, 16384, 16385, 24576, 24577,
                                32767, 32768])
 def test_register_topk_edges(torch, n):
