@@ -5,8 +5,8 @@
 //
 // One token means every contraction is a matrix-vector product whose cost is reading the weights
 // once, so the whole step is HBM-bound (8B-shaped model: 13.9 GB of bf16 weights per token):
-//   * gemv_kernel: y = W x with W [R, K] row-major.  A workgroup of 4 wavefronts owns 2 rows (a gate
-//     and an up row for the SwiGLU variant; 4 rows for Q/K/V) and splits K across its 256 lanes in
+//   * gemv_kernel: y = W x with W [R, K] row-major.  A workgroup of 4 wavefronts owns 2 rows (8, four gate
+//     and four up rows, for SwiGLU; 4 for Q/K/V) and splits K across its 256 lanes in
 //     16-byte chunks, with several independent 16-byte weight loads per lane in flight before the first use; bf16
 //     pairs are multiplied with v_dot2c_f32_bf16 (fp32 accumulate, no conversion instructions).
 //     Lanes reduce by shuffles, wavefronts through LDS.  Up to three matrices that share x run as
@@ -56,17 +56,29 @@ __device__ inline float chunk_sumsq(u32x4 v, float) {
     return s;
 }
 
-template <typename T, int MODE, bool NORM>
+// the sum over the wavefront's lanes, in every lane: six DPP steps (a shuffle through the LDS crossbar takes about a hundred cycles)
+__device__ __forceinline__ float wave_total(float v) {
+    auto bits = [](float f) { return __builtin_bit_cast(int, f); };
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, bits(v), 0x111, 0xF, 0xF, false));   // row_shr 1
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, bits(v), 0x112, 0xF, 0xF, false));   // row_shr 2
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, bits(v), 0x114, 0xF, 0xF, false));   // row_shr 4
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, bits(v), 0x118, 0xF, 0xF, false));   // row_shr 8
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, bits(v), 0x142, 0xA, 0xF, false));   // row_bcast 15
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, bits(v), 0x143, 0xC, 0xF, false));   // row_bcast 31
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(bits(v), 63));
+}
+
+// NORM: x is normalised on the way in (NCH chunks of it and of every row per lane, all in registers).  ROWS: dot products per workgroup.
+template <typename T, int MODE, bool NORM, int ROWS, int NCH>
 __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
     constexpr int EPC = 16 / (int)sizeof(T);          // elements per 16-byte chunk
-    constexpr int ROWS = (MODE == GEMV_RESID) ? 2 : (MODE == GEMV_SILU) ? 2 : 4;   // dot products per workgroup
-    constexpr int NCH = 4;                            // chunks of x a lane may hold (fused norm)
+    static_assert(MODE != GEMV_QKV_ROPE || ROWS == 4, "two rotary pairs");
     __shared__ float sred[4][ROWS];
     __shared__ float snorm[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-    // rows of this workgroup: ROWS consecutive rows of one matrix, or (SiLU) a gate row and the same up row.
-    // Two rows per workgroup measured best where the epilogue allows it (O-proj 8.0 -> 7.5 us, down 19.7 -> 19.3 us,
+    // rows of this workgroup: ROWS consecutive rows of one matrix, or (SiLU) ROWS / 2 gate rows and the same up rows.
+    // Without a norm two rows per workgroup measured best where the epilogue allows it (O-proj 8.0 -> 7.5 us, down 19.7 -> 19.3 us,
     // gate/up 36.9 -> 35.3 us against four; one row and eight rows are slower); Q/K/V keep the four rows of two
     // rotary pairs
     const T* wrow[ROWS];
@@ -122,7 +134,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
 #pragma unroll
         for (int i = 0; i < NCH; ++i)
             if (tid + 256 * i < nchunks) ss += chunk_sumsq(xc[i], T{});
-        ss = wave_sum(ss);
+        ss = wave_total(ss);
         if (lane == 0) snorm[wave] = ss;
         __syncthreads();
         const float inv = 1.0f / sqrtf((snorm[0] + snorm[1] + snorm[2] + snorm[3]) / (float)a.K + a.eps);
@@ -148,7 +160,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
     }
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-        acc[r] = wave_sum(acc[r]);
+        acc[r] = wave_total(acc[r]);
         if (lane == 0) sred[wave][r] = acc[r];
     }
     __syncthreads();
@@ -196,21 +208,40 @@ bool gemv_supported(const GemvArgs& a, bool bf16) {
     return true;
 }
 
+// With the norm inside, a workgroup of gate/up rows takes four of each, so that normalising x (a barrier and a round trip to the L2) comes once per
+// 64 KB of weights that are in flight meanwhile: 1 / 2 / 4 row pairs 345.7 / 339.3 / 341.0 us for two layers of the 8B shape and a head of 128256 rows, Qwen
+// shape 339.3 / 333.4 / 335.4 (one box; between runs +-1), without it and with a launch for each norm 344.2 and 338.6.  The head with four rows 336.1 and 330.2,
+// with eight 341.9 and 330.6.  Half as many registers where a lane holds two chunks (Q/K/V: 1536 workgroups, six per CU, at once instead of in two rounds).
 template <typename T>
 static hipError_t launch_gemv_t(const GemvArgs& a, hipStream_t s) {
     const int64_t rows = (int64_t)a.R[0] + a.R[1] + a.R[2];
     if (rows == 0) return hipSuccess;
     const dim3 b(256);
-    const dim3 g((unsigned)(a.mode == GEMV_SILU ? a.R[0] : a.mode == GEMV_RESID ? rows / 2 : rows / 4));
     const bool n = a.gamma != nullptr;
+    const bool two = a.K / (16 / (int)sizeof(T)) <= 512;   // chunks of x per lane, with the norm: 2, or 4
+    auto grid = [&](int per) { return dim3((unsigned)(rows / per)); };
     switch (a.mode) {
-        case GEMV_STORE: if (n) gemv_kernel<T, GEMV_STORE, true><<<g, b, 0, s>>>(a); else gemv_kernel<T, GEMV_STORE, false><<<g, b, 0, s>>>(a); break;
-        case GEMV_SILU: if (n) gemv_kernel<T, GEMV_SILU, true><<<g, b, 0, s>>>(a); else gemv_kernel<T, GEMV_SILU, false><<<g, b, 0, s>>>(a); break;
-        case GEMV_RESID: if (n) return hipErrorInvalidValue; gemv_kernel<T, GEMV_RESID, false><<<g, b, 0, s>>>(a); break;
-        case GEMV_F32: if (n) gemv_kernel<T, GEMV_F32, true><<<g, b, 0, s>>>(a); else gemv_kernel<T, GEMV_F32, false><<<g, b, 0, s>>>(a); break;
+        case GEMV_STORE:
+            if (!n) gemv_kernel<T, GEMV_STORE, false, 4, 1><<<grid(4), b, 0, s>>>(a);
+            else if (two) gemv_kernel<T, GEMV_STORE, true, 4, 2><<<grid(4), b, 0, s>>>(a);
+            else gemv_kernel<T, GEMV_STORE, true, 4, 4><<<grid(4), b, 0, s>>>(a);
+            break;
+        case GEMV_SILU:
+            if (!n) gemv_kernel<T, GEMV_SILU, false, 2, 1><<<grid(1), b, 0, s>>>(a);
+            else if (two) gemv_kernel<T, GEMV_SILU, true, 8, 2><<<grid(4), b, 0, s>>>(a);
+            else gemv_kernel<T, GEMV_SILU, true, 4, 4><<<grid(2), b, 0, s>>>(a);
+            break;
+        case GEMV_RESID: if (n) return hipErrorInvalidValue; gemv_kernel<T, GEMV_RESID, false, 2, 1><<<grid(2), b, 0, s>>>(a); break;
+        case GEMV_F32:
+            if (!n) gemv_kernel<T, GEMV_F32, false, 4, 1><<<grid(4), b, 0, s>>>(a);
+            else if (two) gemv_kernel<T, GEMV_F32, true, 4, 2><<<grid(4), b, 0, s>>>(a);
+            else gemv_kernel<T, GEMV_F32, true, 4, 4><<<grid(4), b, 0, s>>>(a);
+            break;
         case GEMV_QKV_ROPE:
             if (!a.rope || a.head_dim % 4 != 0 || a.R[0] % a.head_dim != 0 || a.R[1] % a.head_dim != 0) return hipErrorInvalidValue;
-            if (n) gemv_kernel<T, GEMV_QKV_ROPE, true><<<g, b, 0, s>>>(a); else gemv_kernel<T, GEMV_QKV_ROPE, false><<<g, b, 0, s>>>(a);
+            if (!n) gemv_kernel<T, GEMV_QKV_ROPE, false, 4, 1><<<grid(4), b, 0, s>>>(a);
+            else if (two) gemv_kernel<T, GEMV_QKV_ROPE, true, 4, 2><<<grid(4), b, 0, s>>>(a);
+            else gemv_kernel<T, GEMV_QKV_ROPE, true, 4, 4><<<grid(4), b, 0, s>>>(a);
             break;
         default: return hipErrorInvalidValue;
     }

@@ -659,7 +659,7 @@ int spts_decode_layer(spts_ctx* c, void* x, int32_t pos, const spts_layer_weight
         GemvArgs t = qkv; t.x = x; t.gamma = w->gamma1; t.eps = m.rms_eps;
         fuse_norm = gemv_supported(t, c->bf16);
     }
-    if (fuse_norm) {   // pays for Q/K/V (one launch less); the gate/up product is faster with the leaner plain kernel
+    if (fuse_norm) {
         qkv.x = x; qkv.gamma = w->gamma1; qkv.eps = m.rms_eps;
     } else {
         PHASE(c, PH_DEC_NORM); SPTS_HIP(c, launch_rmsnorm(x, w->gamma1, m.rms_eps, xn, 1, m.D, c->bf16, st));
@@ -687,7 +687,11 @@ int spts_decode_layer(spts_ctx* c, void* x, int32_t pos, const spts_layer_weight
     { PHASE(c, PH_DEC_ATTN);
       SPTS_HIP(c, launch_decode_attn(q, cache->k, cache->v, row + 1, m.H, m.Hkv, m.d, part, part_floats, att, c->bf16, st)); }
     { PHASE(c, PH_DEC_O); SPTS_HIP(c, launch_gemv(o, c->bf16, st)); }
-    { PHASE(c, PH_DEC_NORM); SPTS_HIP(c, launch_rmsnorm(x, w->gamma2, m.rms_eps, xn, 1, m.D, c->bf16, st)); }
+    if (fuse_norm) {
+        gu.x = x; gu.gamma = w->gamma2; gu.eps = m.rms_eps;
+    } else {
+        PHASE(c, PH_DEC_NORM); SPTS_HIP(c, launch_rmsnorm(x, w->gamma2, m.rms_eps, xn, 1, m.D, c->bf16, st));
+    }
     { PHASE(c, PH_DEC_GATE_UP); SPTS_HIP(c, launch_gemv(gu, c->bf16, st)); }
     { PHASE(c, PH_DEC_DOWN); SPTS_HIP(c, launch_gemv(dn, c->bf16, st)); }
     cache->count = row + 1;
@@ -710,8 +714,10 @@ int spts_greedy_token(spts_ctx* c, const void* x, const void* gamma_f, const voi
     GemvArgs g{}; g.mode = GEMV_F32; g.x = xn; g.K = m.D; g.W[0] = table; g.R[0] = V; g.y[0] = logits;
     if (!gemv_supported(g, c->bf16)) return SPTS_ESHAPE;
     PHASE(c, PH_DEC_HEAD);
-    // separate norm: over a table of this size the plain kernel streams faster than the fused one
-    SPTS_HIP(c, launch_rmsnorm(x, gamma_f, m.rms_eps, xn, 1, m.D, c->bf16, c->stream));
+    GemvArgs gn = g;
+    gn.x = x; gn.gamma = gamma_f; gn.eps = m.rms_eps;
+    if (gemv_supported(gn, c->bf16)) g = gn;
+    else SPTS_HIP(c, launch_rmsnorm(x, gamma_f, m.rms_eps, xn, 1, m.D, c->bf16, c->stream));
     SPTS_HIP(c, launch_gemv(g, c->bf16, c->stream));
     SPTS_HIP(c, launch_argmax_rows(logits, V, 1, token_out, table, m.D, x_next, c->bf16, c->p<void>(c->off.misc), c->stream));
     return SPTS_OK;

@@ -301,3 +301,42 @@ def test_decode_is_deterministic_and_consistent_with_dense_prefill(torch):
     a = runtime.to_host(outs[0][0]).astype(np.float64)[None, :]
     b = runtime.to_host(full[N]).astype(np.float64)[None, :]
     assert H.row_rel_err(a, b) <= H.TOL[dtype]["hidden"]
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 2048), ("bf16", 4096), ("bf16", 4104), ("bf16", 8192), ("bf16", 8200),
+                                     ("f32", 64), ("f32", 2048), ("f32", 2052), ("f32", 4096), ("f32", 4100)])
+def test_decode_norms_inside_the_products(torch, dtype, D):
+    """Widths around the limits of the products that normalise their input (two 16-byte chunks of a row per lane, four, a launch of its own for
+    the norm), hidden sizes and vocabularies that divide by 4 only; the RMSNorm's gammas differ from one."""
+    shape = synth.ModelShape(D=D, H=4, Hkv=2, d=64, Dff=72, dtype=dtype)
+    mdl, rnd, tol = H.oracle_model(shape), H.rnd_for(dtype), H.TOL[dtype]["hidden"]
+    w = synth.make_layer(51, 0, shape, 16)
+    rng = np.random.default_rng(D)
+    for g in ("gamma1", "gamma2"):
+        w[g] = rnd(rng.uniform(0.5, 1.5, D)).astype(np.float32)
+    dw = runtime.upload_layer(w, shape, 16)
+    ctx = ctx_for(shape, 64)
+    cache = runtime.KVCache(shape, 3)
+    new = synth.hidden_states(52, 3, D, dtype)
+    for t in range(3):
+        kh, vh, ph = cache.host()
+        xt = runtime.to_device(new[t:t + 1].copy(), dtype).reshape(-1)
+        x_in = runtime.to_host(xt).astype(np.float64)
+        ctx.spts_decode_layer(xt, t, dw, cache.struct)
+        torch.cuda.synchronize()
+        ref_x, _ = orc.decode_layer(x_in, t, w, mdl, orc.LayerCache(kh, vh, ph), rnd)
+        got = runtime.to_host(xt).astype(np.float64)
+        assert H.row_rel_err(got[None, :], ref_x[None, :]) <= tol, t
+    V = 300
+    table = synth.vocab_table(7, V, D, dtype)
+    gamma_f = rnd(rng.uniform(0.5, 1.5, D)).astype(np.float32)
+    tok = torch.zeros(1, dtype=torch.int32, device="cuda")
+    logits = torch.zeros(V, dtype=torch.float32, device="cuda")
+    x_next = torch.zeros_like(xt)
+    td = runtime.to_device(table, dtype)
+    ctx.spts_greedy_token(xt, runtime.to_device(gamma_f, dtype), td, V, tok, logits, x_next)
+    torch.cuda.synchronize()
+    lg = logits.cpu().numpy()
+    _, ref = orc.greedy_token(got, gamma_f, table, mdl, rnd)
+    assert np.max(np.abs(lg - ref)) <= tol * np.max(np.abs(ref))
+    assert int(tok[0]) == int(np.flatnonzero(lg == lg.max())[0]) and torch.equal(x_next, td[int(tok[0])])
