@@ -76,7 +76,7 @@ __device__ inline uint32_t pk2(float a, float b) { return cvt_pk_bf16(a, b); }
 // tiles, so a tile that is loaded once serves HPW heads.
 // SEG: the query tiles of every sequence of a batch (seg.qtile counts them), each over its own rows of q, k, v and out.
 template <int D, int HPW, int NW, bool SEG>
-__global__ void __launch_bounds__(NW * 64) attn_mfma_kernel(AttnArgs a, int nQ, int total, int xpg, float qmul, AttnSegments seg) {
+__global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnArgs a, int nQ, int total, int xpg, float qmul, AttnSegments seg) {
     using L = AttnLds<D>;
     constexpr int QB = 1;                // 32-query blocks per wavefront
     constexpr int WPH = NW / HPW;        // wavefronts per head
@@ -143,24 +143,40 @@ __global__ void __launch_bounds__(NW * 64) attn_mfma_kernel(AttnArgs a, int nQ, 
 
     // ---- visible key ranges.  Positions are strictly ascending, so "keys visible to position p" is a
     //      prefix; its length is an upper bound search (or the index itself when both sets coincide).
-    const bool same_set = a.qpos == a.kpos;
-    auto visible_count = [&](int64_t qi) -> int64_t {
-        if (same_set) return qi + 1;
-        const int p = a.qpos[qi];
-        int64_t lo = 0, hi = a.Mk;
-        while (lo < hi) {
-            int64_t mid = (lo + hi) >> 1;
-            if (a.kpos[mid] <= p) lo = mid + 1; else hi = mid;
-        }
-        return lo;
-    };
+    //      The 64 lanes search together, 64 places a step, for the workgroup's last query and the wavefront's first and last at once: two or
+    //      three dependent loads (133 queries over 333 keys, one place a step and one query after the other: 19.9 us, now 16.6).
     const int64_t q_last = (q0 + BQ < a.Mq ? q0 + BQ : a.Mq) - 1;
-    const int n_tiles = (int)((visible_count(q_last) + BKV - 1) / BKV);            // workgroup
     const int64_t qw_first = q0w < a.Mq ? q0w : a.Mq - 1;
     int64_t qw_last = (q0w + QB * 32 < a.Mq ? q0w + QB * 32 : a.Mq) - 1;
     if (qw_last < qw_first) qw_last = qw_first;
-    const int nbw = (int)((visible_count(qw_last) + 31) / 32);     // 32-key blocks this wavefront works on
-    const int nbfull = (int)(visible_count(qw_first) / 32);        // blocks it sees entirely (no mask)
+    int64_t seen[3] = {q_last + 1, qw_first + 1, qw_last + 1};   // keys visible to the three queries
+    if (a.qpos != a.kpos) {
+        const int p[3] = {a.qpos[q_last], a.qpos[qw_first], a.qpos[qw_last]};
+        int64_t hi[3] = {a.Mk, a.Mk, a.Mk};   // the keys before seen[i] are visible, those from hi[i] on are not
+        seen[0] = seen[1] = seen[2] = 0;
+        while (seen[0] < hi[0] || seen[1] < hi[1] || seen[2] < hi[2]) {
+            int64_t step[3];
+            int kp[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                step[i] = (hi[i] - seen[i] + 63) >> 6;
+                const int64_t at = seen[i] + (lane + 1) * step[i] - 1;
+                kp[i] = a.kpos[at < hi[i] ? at : a.Mk - 1];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const int64_t at = seen[i] + (lane + 1) * step[i] - 1;
+                const int n = (int)__popcll(__ballot(at < hi[i] && kp[i] <= p[i]));
+                if (seen[i] < hi[i]) {
+                    seen[i] += n * step[i];
+                    hi[i] = seen[i] + step[i] - 1 < hi[i] ? seen[i] + step[i] - 1 : hi[i];
+                }
+            }
+        }
+    }
+    const int n_tiles = (int)((seen[0] + BKV - 1) / BKV);   // workgroup
+    const int nbw = (int)((seen[2] + 31) / 32);             // 32-key blocks this wavefront works on
+    const int nbfull = (int)(seen[1] / 32);                 // blocks it sees entirely (no mask)
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane holds q[query = l32][16*ks + 8*lh .. +7]
     bf16x8 qf[QB][KS];
@@ -484,27 +500,36 @@ static int heads_per_workgroup(int H, int Hkv) {
     return SPTS_ATT_HPW_MAX >= 4 && grp % 4 == 0 ? 4 : SPTS_ATT_HPW_MAX >= 2 && grp % 2 == 0 ? 2 : 1;
 }
 
-template <int D, bool SEG>
+// Wavefronts per workgroup.  Where workgroups of eight are at most one per CU, workgroups of four spread the same tiles over twice as many
+// CUs (one wavefront per SIMD then has a CU's LDS and loads to itself): whole layers of 700, 1500 and 2000 rows of the 8B shape 370.9 -> 368.8, 536.7 -> 534.1, 607.5 ->
+// 600.0 us (40, 72 and 128 workgroups), dense 1200 and skip 3100 rows of the Qwen shape 578.9 -> 572.0, 856.7 -> 849.2 (144 both); 8000 rows of it, 336
+// workgroups, 1434.7 -> 1451.2.  The same sums in the same order.
+constexpr int64_t ATT_CUS = 256;
+static bool few_tiles(const AttnArgs& a) {
+    const int hpw = heads_per_workgroup(a.H, a.Hkv), bq = 8 / hpw * 32;
+    return (a.Mq + bq - 1) / bq * (a.H / hpw) <= ATT_CUS;
+}
+
+template <int D, int NW, bool SEG>
 static hipError_t launch_attn_d(const AttnArgs& a, const AttnSegments& seg, hipStream_t s) {
     switch (heads_per_workgroup(a.H, a.Hkv)) {
-        case 4: return launch_attn_t<D, 4, 8, SEG>(a, seg, s);
-        case 2: return launch_attn_t<D, 2, 8, SEG>(a, seg, s);
-        default: return launch_attn_t<D, 1, 8, SEG>(a, seg, s);
+        case 4: return launch_attn_t<D, 4, NW, SEG>(a, seg, s);
+        case 2: return launch_attn_t<D, 2, NW, SEG>(a, seg, s);
+        default: return launch_attn_t<D, 1, NW, SEG>(a, seg, s);
     }
 }
 
 hipError_t launch_attention_mfma(const AttnArgs& a, hipStream_t s) {
     const AttnSegments none{nullptr, nullptr, nullptr, 0, 0};
-    if (a.d == 128) return launch_attn_d<128, false>(a, none, s);
-    return launch_attn_d<64, false>(a, none, s);
+    if (few_tiles(a)) return a.d == 128 ? launch_attn_d<128, 4, false>(a, none, s) : launch_attn_d<64, 4, false>(a, none, s);
+    return a.d == 128 ? launch_attn_d<128, 8, false>(a, none, s) : launch_attn_d<64, 8, false>(a, none, s);
 }
 
 int attention_query_tile(int H, int Hkv) { return 8 / heads_per_workgroup(H, Hkv) * 32; }
 
 hipError_t launch_attention_mfma_batched(const AttnArgs& a, const AttnSegments& seg, hipStream_t s) {
     if (seg.n < 1 || seg.tiles < 1 || seg.tiles * a.H > 0x7fffffff || a.qpos != a.kpos || a.Mq != a.Mk) return hipErrorInvalidValue;
-    if (a.d == 128) return launch_attn_d<128, true>(a, seg, s);
-    return launch_attn_d<64, true>(a, seg, s);
+    return a.d == 128 ? launch_attn_d<128, 8, true>(a, seg, s) : launch_attn_d<64, 8, true>(a, seg, s);
 }
 
 }  // namespace spts

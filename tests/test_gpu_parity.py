@@ -464,6 +464,35 @@ def test_matrix_core_layer_at_edge_sizes(torch, name, shape):
             H.lockstep_layer(skip, x, pos, w, mdl, orc.LayerCfg(1, P, ma, mf, 1, 0), shape.dtype)
 
 
+@pytest.mark.parametrize("N", [2, 63, 64, 65, 128, 129, 4096, 4097])
+def test_active_queries_search_their_visible_keys(torch, N):
+    """Active queries against the keys of all candidates: 64 places of the key positions are compared at a time, so lengths around 64 and its
+    square; positions with gaps, and sharp attention, so that one key more or less shows."""
+    shape = synth.ModelShape(D=256, H=4, Hkv=2, d=64, Dff=256, dtype="bf16")
+    ctx = ctx_for(shape, 4200, max_probe=64, max_r=64)
+    w = dict(synth.make_layer(45, 0, shape, 64))
+    w["Wk"] = (4.0 * np.asarray(w["Wk"], dtype=np.float32)).astype(np.float32)
+    w["Wv"] = (8.0 * np.asarray(w["Wv"], dtype=np.float32)).astype(np.float32)
+    dw = runtime.upload_layer(w, shape, 64)
+    x = synth.hidden_states(45 + N, N, shape.D, shape.dtype)
+    pos = np.cumsum(np.random.default_rng(N).integers(1, 9, N)).astype(np.int32)
+    ma, P = max(1, N // 5), min(8, N)
+    got = runtime.run_layer(ctx, x, pos, dw, shape, skip=1, probe_len=P, m_attn=ma, m_ffn=N, kv_mode=1)
+    H.lockstep_layer(got, x, pos, w, H.oracle_model(shape), orc.LayerCfg(1, P, ma, N, 1, 1), shape.dtype)
+
+
+@pytest.mark.parametrize("N", [2048, 2049])
+def test_attention_workgroups_of_four_and_eight(torch, N):
+    """256 workgroups of eight wavefronts run as twice as many of four, 264 as they are; the same layer on both sides."""
+    shape = synth.ModelShape(D=256, H=32, Hkv=8, d=64, Dff=256, dtype="bf16")
+    ctx = ctx_for(shape, 4200, max_probe=64, max_r=64)
+    w = synth.make_layer(46, 0, shape, 64)
+    x = synth.hidden_states(46, N, shape.D, shape.dtype)
+    pos = synth.positions(N)
+    got = runtime.run_layer(ctx, x, pos, runtime.upload_layer(w, shape, 64), shape, skip=0, probe_len=8, m_attn=0, m_ffn=0)
+    H.lockstep_layer(got, x, pos, w, H.oracle_model(shape), orc.LayerCfg(0, 8, N, N, 1, 0), shape.dtype)
+
+
 def test_attention_under_steep_logits(torch):
     """Wk scaled by 16 and by 160: logits spread over tens to hundreds of log2 units, so a query's reference maximum
     in the matrix-core attention moves many times along the keys (and at 160 an exponential taken against a stale
