@@ -5,8 +5,9 @@
 // What bounds these kernels at the fp32 configuration's sizes (256-2048 rows, d = 64) is the latency of dependent loads, so
 // operand fragments come straight from global memory, a lane's whole row piece at once (element j of a lane's 4-element
 // piece is the operand of product j: which k an instruction multiplies is free as long as both operands agree), and the
-// wavefronts of a workgroup split the keys (attention, statistics) or the probe rows (scores) and meet in LDS.
-// Measured at N = 512, 4 heads, d = 64: attention of 256 queries 50 -> 24 us against one wavefront per query row; probe of 32
+// wavefronts of a workgroup split the keys (attention, statistics) or the probe rows (scores) and meet in LDS, all at once (the
+// attention's one after the other: 24.3 us for 256 queries over 512 keys, 53.0 for 750 over 1500; now 21.0 and 47.2).
+// Measured at N = 512, 4 heads, d = 64: attention of 256 queries 50 -> 21 us against one wavefront per query row; probe of 32
 // rows 1001 -> 22 us (two launches) against one lane per candidate that walked all P * H rows.  Dense fp32 layers of 6000 rows (D = 512,
 // H d = 512) against the same: d = 16 9.2 -> 1.85 ms, 32 7.1 -> 1.24, 64 6.6 -> 1.21, 128 6.7 -> 1.42, 256 7.4 -> 1.70.
 #include "spts_internal.h"
@@ -16,7 +17,7 @@ namespace spts {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Wavefronts per workgroup: eight up to d = 64, four beyond (up to 512 registers each).  At d = 64 the attention then keeps 24 registers in
+// Wavefronts per workgroup: eight up to d = 64, four beyond (up to 512 registers each).  At d = 64 the attention then keeps 3 registers in
 // scratch memory and reloads them in the key loop; four wavefronts without spills are slower (attention of 256 queries over 512 keys
 // 23.9 -> 26.6 us, dense layer of 6000 rows 1.21 -> 1.41 ms).  At d = 256 a lane's row pieces exceed 512 registers: 1.3 KB of scratch per lane
 // in the attention, 0.45 KB in the two probe kernels.
@@ -73,7 +74,7 @@ template <typename T, int D>
 __global__ void __launch_bounds__(64 * f32_waves<D>()) attention_f32_kernel(AttnArgs a) {
     constexpr int NS = D / 8, DB = D / 32, GW = f32_waves<D>();
     __shared__ float sm[GW][32], sl[GW][32];
-    __shared__ __attribute__((aligned(16))) float so[32][D + 4];
+    __shared__ __attribute__((aligned(16))) float so[GW][32][D + 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     const int h = blockIdx.y, g = h / (a.H / a.Hkv), d = a.d;
@@ -100,7 +101,7 @@ __global__ void __launch_bounds__(64 * f32_waves<D>()) attention_f32_kernel(Attn
         for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
 
     for (int64_t j0 = wave * 32; j0 < a.Mk; j0 += 32 * GW) {
-        if (a.kpos[j0] > qp_last) break;   // ascending positions: nothing visible from here on
+        const int first = a.kpos[j0];
         const int64_t jk = j0 + l32 < a.Mk ? j0 + l32 : a.Mk - 1;
         f32x4 kf[NS];
 #pragma unroll
@@ -111,6 +112,7 @@ __global__ void __launch_bounds__(64 * f32_waves<D>()) attention_f32_kernel(Attn
             const int64_t j = j0 + acc_row(r, lh);
             kp[r] = a.kpos[j < a.Mk ? j : a.Mk - 1];
         }
+        if (first > qp_last) break;   // ascending positions: nothing visible from here on
         const f32x16 s = mma_rows<NS>(kf, qf);
         float p[16], mx = m;
 #pragma unroll
@@ -151,22 +153,18 @@ __global__ void __launch_bounds__(64 * f32_waves<D>()) attention_f32_kernel(Attn
 #pragma unroll
     for (int w = 0; w < GW; ++w) lg += sl[w][l32] * __builtin_amdgcn_exp2f(sm[w][l32] - mu);
     const float f = __builtin_amdgcn_exp2f(m - mu) * (lg > 0.f ? 1.0f / lg : 0.f);
-    for (int w = 0; w < GW; ++w) {   // one wavefront after the other: a fixed order of the sums
-        if (wave == w) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    f32x4* dst = reinterpret_cast<f32x4*>(&so[l32][db * 32 + 8 * q + 4 * lh]);
-                    const f32x4 v = {o[db][4 * q] * f, o[db][4 * q + 1] * f, o[db][4 * q + 2] * f, o[db][4 * q + 3] * f};
-                    *dst = w == 0 ? v : *dst + v;
-                }
-        }
-        __syncthreads();
-    }
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(&so[wave][l32][db * 32 + 8 * q + 4 * lh]) = f32x4{o[db][4 * q] * f, o[db][4 * q + 1] * f, o[db][4 * q + 2] * f, o[db][4 * q + 3] * f};
+    __syncthreads();
     for (int t = tid; t < 32 * d; t += 64 * GW) {
         const int r = t / d, c = t - r * d;
-        if (q0 + r < a.Mq) ((T*)a.out)[((q0 + r) * a.H + h) * (int64_t)d + c] = from_f32<T>(so[r][c]);
+        float v = so[0][r][c];
+#pragma unroll
+        for (int w = 1; w < GW; ++w) v += so[w][r][c];   // fixed order
+        if (q0 + r < a.Mq) ((T*)a.out)[((q0 + r) * a.H + h) * (int64_t)d + c] = from_f32<T>(v);
     }
 }
 

@@ -1,7 +1,7 @@
 // C = A * B^T (A [M,K] rows optionally gathered, B [N,K]) with fp32 accumulation and the SPTS epilogues for whatever the
 // 256-wide matrix-core kernel does not take: fp32, and bf16 with dimensions that are not tile multiples.
 //
-//  * gemm_tile32_kernel (rows of whole 16-byte chunks): 32x32 output tile per workgroup, the four wavefronts split K and
+//  * gemm_tile32_kernel (rows of whole 16-byte chunks): 32x32 output tile per workgroup, its four or eight wavefronts split K and
 //    meet in LDS.  fp32 runs on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: fp32 products and sums, 157 TFLOP/s,
 //    twice what the vector ALU has without packed instructions), bf16 on the 32x32x16 one.  What bounds it: latency.  The
 //    products of the fp32 configuration (M <= 512, K <= 688) are 1-200 MFLOP; with small tiles there are enough workgroups for
@@ -34,9 +34,15 @@ __device__ inline f32x16 tile32_mfma(u32x4 b, u32x4 a, f32x16 c, bf16_t) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
 }
 
+// Wavefronts per tile: four; eight for a plain fp32 product of K > 256, whose groups are then three to a wavefront instead of six at K = 704 (proxy z
+// of 512 rows 12.7 -> 9.9 us, down of 256 13.6 -> 10.9; of 1500 and 750 rows 11.8 -> 8.7 and 13.6 -> 11.1; at K = 256, two groups to a wavefront of
+// four, 6.5 -> 6.1).  Two products to a tile (SiLU, rotary) have registers for one workgroup of eight per CU (gate/up of 750 rows 16.4 -> 23.4 us).
+// The rule knows nothing of the launch: a product has the same sums alone and in a group.
+template <typename T> __host__ __device__ constexpr int tile32_waves(int mode, int K) { return sizeof(T) == 4 && mode == T32_ONE && K > 256 ? 8 : 4; }
+
 // tile (bx, by) of a product
-template <typename T, int MODE>
-__device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by, float (*red)[4][32][36]) {
+template <typename T, int MODE, int W>
+__device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by, float (*red)[W][32][36]) {
     constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
     constexpr int KS = 2 * EPC;                // k per step: one chunk for each half of the wavefront
     constexpr int U = 4;                       // steps per group: 128 consecutive bytes of a row
@@ -73,19 +79,36 @@ __device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by
         for (int e = 0; e < 4; ++e) v[e] = in ? v[e] : 0u;
         return v;
     };
-    for (int k0 = wave * (U * KS); k0 < a.K; k0 += 4 * U * KS) {
-        u32x4 fa[U], fb[U], fa1[U], fb1[U];
+    constexpr int SETS = W == 8 ? 2 : 1;   // plain fp32 products: a group's loads are in flight while the group before is multiplied
+    u32x4 fa[SETS][U], fb[SETS][U], fa1[U], fb1[U];
+    auto load_group = [&](int set, int k0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            fa[u] = load(pa, k0 + u * KS);
-            fb[u] = load(pb, k0 + u * KS);
+            fa[set][u] = load(pa, k0 + u * KS);
+            fb[set][u] = load(pb, k0 + u * KS);
             if (NP == 2) fb1[u] = load(pb1, k0 + u * KS);
             if (MODE == T32_SILU) fa1[u] = load(pa1, k0 + u * KS);
         }
+    };
+    auto multiply_group = [&](int set) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            acc[0] = tile32_mfma(fb[u], fa[u], acc[0], T{});
-            if (NP == 2) acc[NP - 1] = tile32_mfma(fb1[u], MODE == T32_SILU ? fa1[u] : fa[u], acc[NP - 1], T{});
+            acc[0] = tile32_mfma(fb[set][u], fa[set][u], acc[0], T{});
+            if (NP == 2) acc[NP - 1] = tile32_mfma(fb1[u], MODE == T32_SILU ? fa1[u] : fa[set][u], acc[NP - 1], T{});
+        }
+    };
+    constexpr int STEP = W * U * KS;
+    if (SETS == 1) {
+        for (int k0 = wave * (U * KS); k0 < a.K; k0 += STEP) { load_group(0, k0); multiply_group(0); }
+    } else {
+        int k0 = wave * (U * KS);
+        if (k0 < a.K) load_group(0, k0);
+        for (; k0 < a.K; k0 += 2 * STEP) {
+            if (k0 + STEP < a.K) load_group(SETS - 1, k0 + STEP);
+            multiply_group(0);
+            if (k0 + STEP >= a.K) break;
+            if (k0 + 2 * STEP < a.K) load_group(0, k0 + 2 * STEP);
+            multiply_group(SETS - 1);
         }
     }
     // lane: output row l32, columns 8 * (r / 4) + 4 * lh + r % 4
@@ -95,13 +118,14 @@ __device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by
         for (int q = 0; q < 4; ++q)
             *reinterpret_cast<f32x4*>(&red[p][wave][l32][8 * q + 4 * lh]) = f32x4{acc[p][4 * q], acc[p][4 * q + 1], acc[p][4 * q + 2], acc[p][4 * q + 3]};
     __syncthreads();
+    if (tid >= 256) return;
     const int r = tid >> 3, c4 = (tid & 7) * 4;
     f32x4 v[2];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         v[p] = *reinterpret_cast<const f32x4*>(&red[p][0][r][c4]);
 #pragma unroll
-        for (int w = 1; w < 4; ++w) v[p] += *reinterpret_cast<const f32x4*>(&red[p][w][r][c4]);   // fixed order
+        for (int w = 1; w < W; ++w) v[p] += *reinterpret_cast<const f32x4*>(&red[p][w][r][c4]);   // fixed order
     }
     const int64_t grow = row0 + r;
     if (MODE == T32_WIDE) {   // EPI_SUMSQ
@@ -145,23 +169,31 @@ __device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by
     }
 }
 
-template <typename T, int MODE>
-__global__ void __launch_bounds__(256) gemm_tile32_kernel(GemmArgs a) {
-    __shared__ __attribute__((aligned(16))) float red[MODE == T32_ONE ? 1 : 2][4][32][36];
-    tile32_product<T, MODE>(a, blockIdx.x, blockIdx.y, red);
+template <typename T, int MODE, int W>
+__global__ void __launch_bounds__(64 * W) gemm_tile32_kernel(GemmArgs a) {
+    __shared__ __attribute__((aligned(16))) float red[MODE == T32_ONE ? 1 : 2][W][32][36];
+    tile32_product<T, MODE, W>(a, blockIdx.x, blockIdx.y, red);
 }
 
 // independent products, rotary or plain, in one launch: product i has the blocks from first[i] on, nx[i] of them to a row of tiles
 struct Tile32Group { GemmArgs a[GEMM_GROUP_MAX]; int first[GEMM_GROUP_MAX], nx[GEMM_GROUP_MAX]; };
-template <typename T>
-__global__ void __launch_bounds__(256) gemm_tile32_group_kernel(Tile32Group g) {
-    __shared__ __attribute__((aligned(16))) float red[2][4][32][36];
+template <typename T, int WG>
+__global__ void __launch_bounds__(64 * WG) gemm_tile32_group_kernel(Tile32Group g) {
+    __shared__ __attribute__((aligned(16))) float red[2 * 4 * 32 * 36];
+    static_assert(sizeof(red) >= sizeof(float) * WG * 32 * 36, "one product of WG wavefronts or two of four");
     int i = 0;
 #pragma unroll
     for (int q = 1; q < GEMM_GROUP_MAX; ++q) i += (int)blockIdx.x >= g.first[q] ? 1 : 0;
     const int b = blockIdx.x - g.first[i], by = b / g.nx[i], bx = b - by * g.nx[i];
-    if (g.a[i].epi == EPI_ROPE) tile32_product<T, T32_ROPE>(g.a[i], bx, by, red);
-    else tile32_product<T, T32_ONE>(g.a[i], bx, by, red);
+    const bool rope = g.a[i].epi == EPI_ROPE;
+    if (WG == 8 && tile32_waves<T>(rope ? T32_ROPE : T32_ONE, g.a[i].K) == 8) {
+        tile32_product<T, T32_ONE, WG>(g.a[i], bx, by, reinterpret_cast<float (*)[WG][32][36]>(red));
+        return;
+    }
+    if (threadIdx.x >= 256) return;
+    auto* red4 = reinterpret_cast<float (*)[4][32][36]>(red);
+    if (rope) tile32_product<T, T32_ROPE, 4>(g.a[i], bx, by, red4);
+    else tile32_product<T, T32_ONE, 4>(g.a[i], bx, by, red4);
 }
 
 constexpr int GT = 64;   // tile edge
@@ -285,12 +317,20 @@ bool gemm_tile32_supported(const GemmArgs& a, bool bf16) {
 
 template <typename T>
 static void launch_tile32_t(const GemmArgs& a, hipStream_t s) {
-    const unsigned ny = (unsigned)((a.M + 31) / 32);
+    const unsigned ny = (unsigned)((a.M + 31) / 32), nx = (unsigned)((a.N + 31) / 32);
+    const dim3 b4(256);
     switch (a.epi) {
-        case EPI_SILU_MUL: gemm_tile32_kernel<T, T32_SILU><<<dim3((unsigned)((a.N + 31) / 32), ny), dim3(256), 0, s>>>(a); break;
-        case EPI_ROPE: gemm_tile32_kernel<T, T32_ROPE><<<dim3((unsigned)((a.N / 2 + 31) / 32), ny), dim3(256), 0, s>>>(a); break;
-        case EPI_SUMSQ: gemm_tile32_kernel<T, T32_WIDE><<<dim3((unsigned)((a.N + 63) / 64), ny), dim3(256), 0, s>>>(a); break;
-        default: gemm_tile32_kernel<T, T32_ONE><<<dim3((unsigned)((a.N + 31) / 32), ny), dim3(256), 0, s>>>(a); break;
+        case EPI_SILU_MUL: gemm_tile32_kernel<T, T32_SILU, 4><<<dim3(nx, ny), b4, 0, s>>>(a); break;
+        case EPI_ROPE: gemm_tile32_kernel<T, T32_ROPE, 4><<<dim3((unsigned)((a.N / 2 + 31) / 32), ny), b4, 0, s>>>(a); break;
+        case EPI_SUMSQ: gemm_tile32_kernel<T, T32_WIDE, 4><<<dim3((unsigned)((a.N + 63) / 64), ny), b4, 0, s>>>(a); break;
+        default:
+            if constexpr (sizeof(T) == 4)
+                if (tile32_waves<T>(T32_ONE, a.K) == 8) {
+                    gemm_tile32_kernel<T, T32_ONE, 8><<<dim3(nx, ny), dim3(512), 0, s>>>(a);
+                    break;
+                }
+            gemm_tile32_kernel<T, T32_ONE, 4><<<dim3(nx, ny), b4, 0, s>>>(a);
+            break;
     }
 }
 
@@ -318,11 +358,13 @@ static int tile32_columns(const GemmArgs& a) { return ((a.epi == EPI_ROPE ? a.N 
 bool gemm_tile32_group_supported(const GemmArgs* a, int n, bool bf16) {
     if (n < 1 || n > GEMM_GROUP_MAX) return false;
     int64_t blocks = 0;
+    bool eight = false;
     for (int i = 0; i < n; ++i) {
+        eight |= !bf16 && tile32_waves<float>(a[i].epi == EPI_ROPE ? T32_ROPE : T32_ONE, a[i].K) == 8;
         if (!gemm_tile32_supported(a[i], bf16) || (a[i].epi != EPI_ROPE && a[i].epi != EPI_STORE && a[i].epi != EPI_RESIDUAL)) return false;
         blocks += (int64_t)tile32_columns(a[i]) * ((a[i].M + 31) / 32);
     }
-    return blocks <= 1 << 23;   // one grid dimension of 256 threads each
+    return eight ? blocks < 1 << 23 : blocks <= 1 << 23;   // one grid dimension of 256 or 512 threads each, 2^32 in all at most
 }
 
 hipError_t launch_gemm_tile32_group(const GemmArgs* a, int n, bool bf16, hipStream_t s) {
@@ -338,8 +380,12 @@ hipError_t launch_gemm_tile32_group(const GemmArgs* a, int n, bool bf16, hipStre
         g.nx[i] = tile32_columns(a[i]);
         blocks += (int64_t)g.nx[i] * ((a[i].M + 31) / 32);
     }
-    if (bf16) gemm_tile32_group_kernel<bf16_t><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);
-    else gemm_tile32_group_kernel<float><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);
+    bool eight = false;
+    for (int i = 0; i < n; ++i) eight |= !bf16 && tile32_waves<float>(a[i].epi == EPI_ROPE ? T32_ROPE : T32_ONE, a[i].K) == 8;
+    const dim3 grid((unsigned)blocks);
+    if (bf16) gemm_tile32_group_kernel<bf16_t, 4><<<grid, dim3(256), 0, s>>>(g);
+    else if (eight) gemm_tile32_group_kernel<float, 8><<<grid, dim3(512), 0, s>>>(g);
+    else gemm_tile32_group_kernel<float, 4><<<grid, dim3(256), 0, s>>>(g);
     return hipGetLastError();
 }
 
