@@ -202,19 +202,22 @@ __device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t v, uint32_t identit
 // cleared and scanned, three more passes for the other bits) in the place of the rounds a row of 700 scores took 8.9 us, now 4.5; 2048 9.1, now
 // 5.2; 8192 10.6, now 9.1; 20001 24.7, now 14.4; 32768 27.1, now 20.1; 512 rows of them 17.9, 18.4, 21.6, 64.7, 70.9, now 5.5, 7.7, 15.3, 27.5, 49.4.
 // Up to 512 scores: one wavefront that decided all 32 bits 5.9, now 4.4 (512 rows 6.5, now 4.9).  Three thresholds a round: 10.5 us at 8192.
-template <int KPT, int W>
+// MAP: map.in[i] goes where i goes.  (An instantiation of its own: a test in the place where indices are written costs the others 0.7 us.)
+template <int KPT, int W, bool MAP>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 8))) topk_reg_kernel(const float* __restrict__ scores, int64_t N, int64_t k,
-                                                            int protect_last, int32_t* __restrict__ idx_out, TopkSegments seg) {
+                                                            int protect_last, int32_t* __restrict__ idx_out, TopkSegments seg, TopkMap map) {
     constexpr int ROUNDS = 33;   // a round leaves at most half of a 32-bit range
     __shared__ int count[ROUNDS];
     __shared__ uint32_t cand[64], wave_min[W], wave_max[W];
     __shared__ int cands, wave_ge[W], wave_gt[W];
 
+    int base = 0;   // what the written indices count from
     // one independent problem per workgroup: equal rows, or the segment the descriptors give it
     if (seg.offsets) {
         const int64_t b0 = seg.offsets[blockIdx.x];
         N = seg.offsets[blockIdx.x + 1] - b0;
         k = seg.k[blockIdx.x];
+        if (seg.whole) base = (int)b0;
         scores += b0;
         idx_out += seg.out_offsets[blockIdx.x];
         if (k > N) k = N;
@@ -222,7 +225,12 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 
     } else {
         scores += (int64_t)blockIdx.x * N;
         idx_out += (int64_t)blockIdx.x * k;
+        if (MAP) map.out += (int64_t)blockIdx.x * k;
     }
+    auto put = [&](int at, int i) {
+        idx_out[(uint32_t)at] = base + i;
+        if (MAP) map.out[(uint32_t)at] = map.in[i];
+    };
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = (int)N, kk = (int)k, last = protect_last ? n - 1 : -1;   // the protected score is above all others: left out of the search
     const int lo = wave * (64 * KPT);
@@ -347,7 +355,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 
             const bool sel = keys[j] >= T;
             const uint64_t m = __ballot(sel);
             const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, before));
-            if (sel) idx_out[(uint32_t)at] = lo + 64 * j + lane;
+            if (sel) put(at, lo + 64 * j + lane);
             before += (int)__popcll(m);
         }
         return;
@@ -371,7 +379,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 
         const uint64_t mgt = __ballot(g_), meq = __ballot(e_);
         const int my_gt = gt_before + lane_prefix_popc(mgt);
         const int my_eq = eq_before + lane_prefix_popc(meq);
-        if (g_ || (e_ && my_eq < need_eq)) idx_out[my_gt + (my_eq < need_eq ? my_eq : need_eq)] = i;
+        if (g_ || (e_ && my_eq < need_eq)) put(my_gt + (my_eq < need_eq ? my_eq : need_eq), i);
         gt_before += (int)__popcll(mgt);
         eq_before += (int)__popcll(meq);
     }
@@ -384,11 +392,13 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float* __restr
     __shared__ int64_t sh_need;        // how many elements are still to be taken inside the current bucket
     __shared__ int64_t wave_gt[TOPK_WAVES], wave_eq[TOPK_WAVES];
 
+    int base = 0;   // what the written indices count from
     // one independent problem per workgroup: equal rows, or the segment the descriptors give it
     if (seg.offsets) {
         const int64_t b0 = seg.offsets[blockIdx.x];
         N = seg.offsets[blockIdx.x + 1] - b0;
         k = seg.k[blockIdx.x];
+        if (seg.whole) base = (int)b0;
         scores += b0;
         idx_out += seg.out_offsets[blockIdx.x];
         if (k > N) k = N;
@@ -411,8 +421,8 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float* __restr
         if (tid < 256) hist[tid] = 0;
         __syncthreads();
         // every lane runs the same number of rounds (hist_add uses wavefront-wide ballots)
-        for (int64_t base = 0; base < N; base += TOPK_THREADS) {
-            const int64_t i = base + tid;
+        for (int64_t at0 = 0; at0 < N; at0 += TOPK_THREADS) {
+            const int64_t i = at0 + tid;
             uint32_t key = i < N ? load_key(scores, i, N, protect_last) : 0u;
             hist_add(hist, i < N && (key & hi_mask) == prefix, (int)((key >> shift) & 0xFF));
         }
@@ -430,8 +440,8 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float* __restr
     int64_t lo = (int64_t)wave * per_wave;
     int64_t hi = lo + per_wave < N ? lo + per_wave : N;
     int64_t cgt = 0, ceq = 0;
-    for (int64_t base = lo; base < hi; base += 64) {
-        int64_t i = base + lane;
+    for (int64_t at0 = lo; at0 < hi; at0 += 64) {
+        int64_t i = at0 + lane;
         bool gt = false, eq = false;
         if (i < hi) { uint32_t key = load_key(scores, i, N, protect_last); gt = key > T; eq = key == T; }
         cgt += __popcll(__ballot(gt));
@@ -441,8 +451,8 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float* __restr
     __syncthreads();
     int64_t gt_before = 0, eq_before = 0;
     for (int w = 0; w < wave; ++w) { gt_before += wave_gt[w]; eq_before += wave_eq[w]; }
-    for (int64_t base = lo; base < hi; base += 64) {
-        int64_t i = base + lane;
+    for (int64_t at0 = lo; at0 < hi; at0 += 64) {
+        int64_t i = at0 + lane;
         bool gt = false, eq = false;
         if (i < hi) { uint32_t key = load_key(scores, i, N, protect_last); gt = key > T; eq = key == T; }
         uint64_t mgt = __ballot(gt), meq = __ballot(eq);
@@ -450,7 +460,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float* __restr
         int64_t my_eq = eq_before + lane_prefix_popc(meq);
         if (gt || (eq && my_eq < need_eq)) {
             int64_t o = my_gt + (my_eq < need_eq ? my_eq : need_eq);
-            idx_out[o] = (int32_t)i;
+            idx_out[o] = base + (int32_t)i;
         }
         gt_before += __popcll(mgt);
         eq_before += __popcll(meq);
@@ -806,7 +816,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
                 for (int u = 0; u < LONG_U; ++u) {
                     const int i0 = base + u * 256 + lane * 4;
                     v[u] = *reinterpret_cast<const f32x4u*>(scores + (ALL ? (uint32_t)i0 : (uint32_t)min(i0, n - 4)));
-                    if (!ALL) v[u] = end_piece(v[u], i0, n);
+                    if (!ALL && (n & 3) != 0) v[u] = end_piece(v[u], i0, n);
                 }
 #pragma unroll
                 for (int u = 0; u < LONG_U; ++u) {
@@ -1351,14 +1361,19 @@ hipError_t launch_topk_mean(const void* vals, int64_t ld, int64_t rows, int64_t 
 }
 
 hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_last, int32_t* idx_out, int batch,
-                       hipStream_t s, TopkSegments seg) {
+                       hipStream_t s, TopkSegments seg, TopkMap map) {
     // with segments N is the longest segment (it picks the kernel variant) and k is ignored
     if ((k <= 0 && !seg.offsets) || N <= 0 || batch <= 0) return hipSuccess;
+    if (map.out && (seg.offsets || N > TOPK_REG_MAX_N)) return hipErrorInvalidValue;
     const dim3 g((unsigned)batch), b(TOPK_THREADS);
     if (N <= TOPK_REG_MAX_N) {
         // The smallest of these workgroups that holds the row: a round costs a compare per slot, empty or not, and 16 wavefronts wait
         // longer for one another than 8 (4000 scores: 6.6 us with 8 x 8 slots, 7.3 with 4 x 16; 6000: 8.2 with 6 x 16, 8.6 with 12 x 8).
-#define SPTS_TOPK_REG(KPT, W) topk_reg_kernel<KPT, W><<<g, dim3(64 * W), 0, s>>>(scores, N, k, protect_last, idx_out, seg)
+#define SPTS_TOPK_REG(KPT, W)                                                                                              \
+    do {                                                                                                                   \
+        if (map.out) topk_reg_kernel<KPT, W, true><<<g, dim3(64 * W), 0, s>>>(scores, N, k, protect_last, idx_out, seg, map); \
+        else topk_reg_kernel<KPT, W, false><<<g, dim3(64 * W), 0, s>>>(scores, N, k, protect_last, idx_out, seg, map);        \
+    } while (0)
         if (N <= 512) SPTS_TOPK_REG(2, 4);
         else if (N <= 1024) SPTS_TOPK_REG(4, 4);
         else if (N <= 2048) SPTS_TOPK_REG(4, 8);

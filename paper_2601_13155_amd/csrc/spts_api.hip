@@ -449,11 +449,18 @@ int gather_rows_maps(spts_ctx* c, const void* in, const int32_t* idx, void* out,
 }
 
 // TopK of one score row: longer rows are spread over the chip (a launch per radix pass), short ones stay in one workgroup
-int run_topk(spts_ctx* c, const float* scores, int64_t N, int64_t k, int protect_last, int32_t* idx_out) {
-    if (N > TOPK_REG_MAX_N && N <= TOPK_MULTI_MAX_N)
+// (map_out[j] = map_in[idx_out[j]] with it where asked for)
+int run_topk(spts_ctx* c, const float* scores, int64_t N, int64_t k, int protect_last, int32_t* idx_out, const int32_t* map_in = nullptr,
+             int32_t* map_out = nullptr) {
+    if (N <= TOPK_REG_MAX_N) {
+        SPTS_HIP(c, launch_topk(scores, N, k, protect_last, idx_out, 1, c->stream, TopkSegments{nullptr, nullptr, nullptr, 0}, TopkMap{map_in, map_out}));
+        return SPTS_OK;
+    }
+    if (N <= TOPK_MULTI_MAX_N)
         SPTS_HIP(c, launch_topk_multi(scores, N, k, protect_last, idx_out, c->p<void>(c->off.topk), c->stream));
     else
         SPTS_HIP(c, launch_topk(scores, N, k, protect_last, idx_out, 1, c->stream));
+    if (map_out) SPTS_HIP(c, launch_gather_i32(map_in, idx_out, map_out, k, c->stream));
     return SPTS_OK;
 }
 
@@ -826,7 +833,7 @@ int spts_select_topk_segmented(spts_ctx* c, const float* scores, const int64_t* 
         return SPTS_EALIGN;
     PHASE(c, PH_TOPK);
     SPTS_HIP(c, launch_topk(scores, max_len, 0, protect_last, idx_out, batch, c->stream,
-                            TopkSegments{seg_offsets, seg_k, out_offsets}));
+                            TopkSegments{seg_offsets, seg_k, out_offsets, 0}));
     return SPTS_OK;
 }
 
@@ -925,9 +932,8 @@ int spts_msdp_compact_batched(spts_ctx* c, const void* x_in, const int32_t* pos_
     // the descriptors travel by value as kernel arguments: no staging copy of a host array that dies with this call
     int64_t* seg = c->p<int64_t>(c->off.seg);
     SPTS_HIP(c, launch_write_i64(desc.data(), (int64_t)desc.size(), seg, c->stream));
-    const TopkSegments segs{seg, seg + (batch + 1), seg + 2 * (batch + 1)};
+    const TopkSegments segs{seg, seg + (batch + 1), seg + 2 * (batch + 1), 1};
     SPTS_HIP(c, launch_topk(s_mha, max_len, 0, protect_last, map_new2old, batch, c->stream, segs));
-    SPTS_HIP(c, launch_add_segment_base(map_new2old, segs.out_offsets, segs.offsets, batch, keep, c->stream));
     const int64_t row_bytes = (int64_t)c->m.D * (c->bf16 ? 2 : 4);
     return gather_rows_maps(c, x_in, map_new2old, x_out, keep, row_bytes, pos_in, pos_out, map_old2new);
 }
@@ -1018,13 +1024,13 @@ int spts_layer_prefill(spts_ctx* c, void* x, const int32_t* pos, int64_t N, cons
     SPTS_TRY(probe_attn_impl(c, x, pos, N, w, skip ? cfg->probe_len : 0, skip, kall, S, kv && full_kv && Ma > 0 ? kv->pos : nullptr, more, n_more, &early));
     if (skip) {
         PHASE(c, PH_TOPK);
-        SPTS_TRY(run_topk(c, S, N, Ma, cfg->protect_last, idxA));
+        // with all keys in place the active positions are all there is to gather
+        SPTS_TRY(run_topk(c, S, N, Ma, cfg->protect_last, idxA, full_kv ? pos : nullptr, full_kv ? posA : nullptr));
     }
     if (Ma > 0) {
-        if (skip) {
+        if (skip && !full_kv) {
             PHASE(c, PH_GATHER);
-            if (!full_kv) SPTS_TRY(gather_rows_maps(c, kall, idxA, kk, Ma, (int64_t)KV * eb, pos, posA, nullptr));
-            else SPTS_HIP(c, launch_gather_i32(pos, idxA, posA, Ma, st));
+            SPTS_TRY(gather_rows_maps(c, kall, idxA, kk, Ma, (int64_t)KV * eb, pos, posA, nullptr));
         }
         const bool q_done = early && !skip && (merged || n_more == 2), v_done = early && n_more > 0 && (!merged || q_done);
         if (merged) {
@@ -1144,7 +1150,7 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
     int64_t* seg = c->p<int64_t>(c->off.seg);
     SPTS_HIP(c, launch_write_i64(desc.data(), (int64_t)desc.size(), seg, st));
     auto dev = [&](const int64_t* host) { return (const int64_t*)seg + (host - dOff); };
-    const TopkSegments seg_a{dev(dOff), dev(ma), dev(oa)}, seg_f{dev(dOff), dev(mf), dev(of)};
+    const TopkSegments seg_a{dev(dOff), dev(ma), dev(oa), 1}, seg_f{dev(dOff), dev(mf), dev(of), 1};
     const float q_scale = query_store_scale(c);
 
     // ------------------------------------------------ attention block: PAP per sequence, projections over the batch
@@ -1181,7 +1187,6 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
     if (skip) {
         PHASE(c, PH_TOPK);
         SPTS_HIP(c, launch_topk(S, max_len, 0, protect_last, idxA, batch, st, seg_a));
-        SPTS_HIP(c, launch_add_segment_base(idxA, seg_a.out_offsets, seg_a.offsets, batch, MaT, st));
     }
     if (MaT > 0) {
         const int32_t* posA = pos;
@@ -1274,7 +1279,6 @@ int spts_layer_prefill_batched(spts_ctx* c, void* x, const int32_t* pos, const i
     if (skip) {
         PHASE(c, PH_TOPK);
         SPTS_HIP(c, launch_topk(SF, max_len, 0, protect_last, idxF, batch, st, seg_f));
-        SPTS_HIP(c, launch_add_segment_base(idxF, seg_f.out_offsets, seg_f.offsets, batch, MfT, st));
     }
     GemmArgs gh = gemm_args(xn, m.D, idxF, w->Wgate, m.D, c->p<void>(c->off.big), m.Dff, MfT, m.Dff, m.D, EPI_SILU_MUL);
     gh.a_rows = N;

@@ -183,9 +183,6 @@ hipError_t launch_fill_caches(const CacheChunk& c, int n, const void* k, const v
 // synchronisation, safe under stream capture)
 struct I64Chunk { static constexpr int CAP = 256; int64_t v[CAP]; int32_t n; };
 hipError_t launch_write_i64(const int64_t* host_vals, int64_t n, int64_t* dst, hipStream_t s);
-// idx[i] += seg_offsets[b] for i in [out_offsets[b], out_offsets[b+1]); device descriptor arrays
-hipError_t launch_add_segment_base(int32_t* idx, const int64_t* out_offsets, const int64_t* seg_offsets, int nseg, int64_t total,
-                                   hipStream_t s);
 // old2new[idx[i]] = i
 hipError_t launch_scatter_iota(const int32_t* idx, int32_t* old2new, int64_t n, hipStream_t s);
 // c = sqrt(sum_j part[n, j]); s_ffn = c * (s_mha ? s_mha[n] : 1)
@@ -200,11 +197,13 @@ hipError_t launch_transpose_pad(const void* v, void* vt, int64_t M, int C, int64
 // ------------------------------------------------------------------ TopK
 // `batch` independent problems: scores [batch, N] -> idx_out [batch, k], every row ascending.
 // With segment descriptors (device arrays) problem b is scores[offsets[b] .. offsets[b+1]) with budget
-// min(k[b], length), written to idx_out + out_offsets[b] as indices local to the segment; N is then the
+// min(k[b], length), written to idx_out + out_offsets[b] as indices local to the segment, or (whole) as indices into `scores`; N is then the
 // longest segment.
-struct TopkSegments { const int64_t* offsets; const int64_t* k; const int64_t* out_offsets; };
+struct TopkSegments { const int64_t* offsets; const int64_t* k; const int64_t* out_offsets; int whole; };
+// With a map, map_out[j] = map_in[idx_out[j]] too (N <= TOPK_REG_MAX_N, no segments).
+struct TopkMap { const int32_t* in; int32_t* out; };
 hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_last, int32_t* idx_out,
-                       int batch, hipStream_t s, TopkSegments seg = TopkSegments{nullptr, nullptr, nullptr});
+                       int batch, hipStream_t s, TopkSegments seg = TopkSegments{nullptr, nullptr, nullptr, 0}, TopkMap map = TopkMap{nullptr, nullptr});
 
 // One problem spread over many workgroups (a launch per radix pass + one for the ordered compaction); `scratch`:
 // TOPK_MULTI_SCRATCH_BYTES of device memory, 256-byte aligned, contents irrelevant on entry (every word that is
