@@ -478,17 +478,18 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float* __restr
 // keys of the bin do not fit its region (heavily tied scores), the kernel falls back to four 8-bit passes over the row with
 // histograms private to the wavefront, six sweeps in all; both routes end in the same exact (threshold, rank) pair.
 // A length that is no multiple of 4 leaves rows at 4-byte addresses, which 16-byte loads take (512 rows of 131071: 112 us, of 131072
-// 113; one row 46 and 46, where scores read one by one in six sweeps took 477 and 231), and a last piece of one to three scores, which is loaded from the row's end, moved into place and padded with minus
-// infinity: no score is smaller and none comes later, so a padded place is never among the k <= N selected.
+// 113; one row 46 and 46, where scores read one by one in six sweeps took 477 and 231), and a last piece of one to three scores, which is loaded from the row's end, moved into place and padded with the NaN
+// whose key is 0: no score's key is smaller and none comes later, so a padded place is never among the k <= N selected.  (Minus infinity is
+// not enough: NaNs with the sign bit set come below it.)
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int LONG_U = 4;                       // 16-byte loads in flight per lane
 constexpr int LONG_STEP = 64 * 4 * LONG_U;      // scores a wavefront takes per iteration
 
-// the piece [i0, i0 + 4) of a row of n scores, minus infinity in the places past it, from the four scores at min(i0, n - 4); for i0 >= n any of these
+// the piece [i0, i0 + 4) of a row of n scores, key 0 in the places past it, from the four scores at min(i0, n - 4); for i0 >= n any of these
 __device__ __forceinline__ f32x4v end_piece(f32x4v v, int i0, int n) {
     const int by = i0 - min(i0, n - 4);
-    const float none = -__builtin_inff();
+    const float none = __uint_as_float(0xFFFFFFFFu);
     if (by & 1) v = f32x4v{v[1], v[2], v[3], none};
     if (by & 2) v = f32x4v{v[2], v[3], none, none};
     return v;
@@ -507,7 +508,7 @@ __device__ __forceinline__ void topk_long_rows(const float* __restrict__ scores,
     const int n = (int)N;
     const int per_wave = ((n + TOPK_WAVES - 1) / TOPK_WAVES + LONG_STEP - 1) / LONG_STEP * LONG_STEP;
     const int lo = __builtin_amdgcn_readfirstlane(wave * per_wave);
-    const int hi = lo + per_wave < n ? lo + per_wave : n;   // of a piece that starts below hi, places past it are minus infinity
+    const int hi = lo + per_wave < n ? lo + per_wave : n;   // of a piece that starts below hi, places past it have key 0
     auto load_step = [&](int base, f32x4v (&v)[LONG_U]) {   // the pieces of one iteration
 #pragma unroll
         for (int u = 0; u < LONG_U; ++u) v[u] = *reinterpret_cast<const f32x4u*>(scores + (uint32_t)min(base + u * 256 + lane * 4, n - 4));
@@ -797,7 +798,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
 
     // ---- the one sweep: wavefront w owns a contiguous slice
     const int lo = wave * per_wave;
-    const int hi = lo + per_wave < n ? lo + per_wave : n;   // of a piece that starts below hi, places past it are minus infinity
+    const int hi = lo + per_wave < n ? lo + per_wave : n;   // of a piece that starts below hi, places past it have key 0
     const int last = protect_last ? n - 1 : -1;
     // Bit 31 - (4 u + e) of word w: element e of the slice's load 8 w + u lies above the bracket (later: is selected).  A key inside the bracket is kept as (key - lo_key) >> shift << 11 | (4 u + e) << 6 | lane;
     // its word follows from the region's fill at the word's end.
@@ -888,7 +889,10 @@ __global__ void __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_
     uint32_t T = prefix >> 11;   // the threshold's distance from lo_key, as far as the regions keep it
     if (shift > 0) {
         // 8 + 3 more bits among the keys that share those 21, then every entry's distance becomes 2 / 1 / 0: above / equal / below
-        auto low_bits = [&](uint32_t c, int j) { return (load_key(scores, min(lo + (int)place(c, j), n - 1), N, protect_last) - lo_key) & ((1u << shift) - 1u); };
+        auto low_bits = [&](uint32_t c, int j) {
+            const int at = lo + (int)place(c, j);
+            return ((at < n ? load_key(scores, at, N, protect_last) : 0u) - lo_key) & ((1u << shift) - 1u);
+        };
         prefix = 0;
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {

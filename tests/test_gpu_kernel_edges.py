@@ -252,6 +252,36 @@ def test_long_row_topk_of_rows_at_odd_addresses(torch, n):
                 assert np.array_equal(got[b * k:(b + 1) * k], orc.topk_select(rows[b], k, protect)), (b, k, protect)
 
 
+@pytest.mark.parametrize("n", [32769, 65538, 131071, 131073])
+def test_long_row_topk_padding_is_below_every_score(torch, n):
+    """Lengths that are no multiple of 4 with NaNs of either sign (a set sign bit comes below minus infinity), and with as many infinite scores as
+    put the threshold's bracket across them and the finite ones: the places that fill the last piece up are never selected."""
+    rng = np.random.default_rng(n)
+    base = np.exp(0.5 * rng.standard_normal(n)).astype(np.float32) / n
+    negative = np.array([0xFFC00000, 0xFF800001, 0xFFFFFFFF], dtype=np.uint32).view(np.float32)
+    some = base.copy(); some[rng.random(n) < 0.3] = negative[0]; some[-1] = 1.0
+    most = np.where(rng.random(n) < 0.98, rng.choice(negative, n), base); most[-2:] = (negative[1], 2.0)
+    positive = base.copy(); positive[rng.random(n) < 0.1] = np.nan
+    low = base.copy(); low[rng.random(n) < 0.3] = -np.inf; low[-1] = 1.0
+    rows = np.stack([some, most, np.full(n, negative[0]), np.full(n, negative[2]), positive, low]).astype(np.float32)
+    sd = torch.from_numpy(rows.view(np.int32)).cuda().view(torch.float32)
+    ctx = runtime.make_context(synth.TINY, n, 1, 1, synth.TINY.Dff)
+    for k in (1, n // 50, int(0.7 * n), n - n // 50, n - 1, n):
+        for protect in (0, 1):
+            out = torch.full((len(rows) * k + 4,), -7, dtype=torch.int32, device="cuda")
+            ctx.spts_select_topk_batched(sd, n, k, protect, len(rows), out)
+            got = out.cpu().numpy()
+            assert (got[-4:] == -7).all()
+            for b in range(len(rows)):
+                bits = rows[b].view(np.uint32)
+                bits = np.where(np.isnan(rows[b]), bits | np.uint32(0x400000), bits)   # quiet NaNs, as the sum with +0 leaves them
+                key = np.where(bits >> 31, ~bits, bits | np.uint32(0x80000000)).astype(np.int64)
+                if protect:
+                    key[-1] = 0xFFFFFFFF
+                ref = np.sort(np.argsort(-key, kind="stable")[:k])
+                assert np.array_equal(got[b * k:(b + 1) * k], ref), (b, k, protect)
+
+
 @pytest.mark.parametrize("n", [256, 257, 512, 513, 1024, 1025, 2048, 2049, 3072, 3073, 4096, 4097, 6144, 6145, 8192, 8193, 12288, 12289, 16384, 16385, 24576, 24577,
                                32767, 32768])
 def test_register_topk_edges(torch, n):
