@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnArgs a, int n
             int kp[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                step[i] = (hi[i] - seen[i] + 63) >> 6;
+                step[i] = (hi[i] - seen[i] + 64) >> 6;   // at least one place: a query that sees no key ends at 0
                 const int64_t at = seen[i] + (lane + 1) * step[i] - 1;
                 kp[i] = a.kpos[at < hi[i] ? at : a.Mk - 1];
             }
