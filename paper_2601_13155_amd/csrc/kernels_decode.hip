@@ -395,9 +395,24 @@ typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int GEMV_MFMA_WAVES = 4;
 
-template <int MODE, int XI>
-__global__ void __launch_bounds__(GEMV_MFMA_WAVES * 64) gemv_mfma_kernel(GemvArgs a, int nb) {
+constexpr int GEMV_NORM_K = 4096;   // longest norm inside a product: the ring and gamma are 80 KB, two workgroups per CU
+// GEMV_QKV_ROPE of several sequences: where the new pairs go, and the rotation's exponent per channel pair
+struct GemvRopeBatch { DecodeBatch db; double neg2_over_d_log2base; };
+struct GemvNoRope {};
+template <int MODE> struct GemvRopeOf { typedef GemvNoRope type; };
+template <> struct GemvRopeOf<GEMV_QKV_ROPE> { typedef GemvRopeBatch type; };
+
+// NORM: x is normalised on the way in.  The product that wrote x (GEMV_RESID with ssq) has left the sum of squares of each strip of 16 rows; every workgroup
+// adds them up while its ring fills, gamma stands in LDS, and fragments are normalised and rounded as rmsnorm_kernel does it.  (From x itself, which is
+// then read twice per strip, gate/up of eight vectors took 45.6 us instead of 41.5: no less than the norm's launch.)
+// GEMV_QKV_ROPE: a strip of Q or K has the rows j .. j + 7 and j + d/2 .. j + d/2 + 7 of one head, both members of eight rotary pairs, and the epilogue
+// rotates them and writes keys and values into the caches, which was a launch of its own.
+// Both are the work of four more wavefronts: one that waits for loads of its own waits for its whole ring.
+template <int MODE, bool NORM> constexpr int gemv_mfma_threads() { return GEMV_MFMA_WAVES * (NORM || MODE == GEMV_QKV_ROPE ? 128 : 64); }
+template <int MODE, int XI, bool NORM>
+__global__ void __launch_bounds__((gemv_mfma_threads<MODE, NORM>()), 2) gemv_mfma_kernel(GemvArgs a, int nb, typename GemvRopeOf<MODE>::type rb) {
     constexpr int NW = GEMV_MFMA_WAVES;
+    constexpr bool HELP = NORM || MODE == GEMV_QKV_ROPE;
     constexpr int NS = MODE == GEMV_SILU ? 2 : 1;          // weight strips per workgroup (gate, up)
     constexpr int DEPTH = NS == 2 ? 3 : 4;                 // ring stages per wavefront (64 / 72 KB: two workgroups per CU)
     constexpr int NI = NS * 2 + XI;                        // direct-to-LDS loads per stage
@@ -405,10 +420,12 @@ __global__ void __launch_bounds__(GEMV_MFMA_WAVES * 64) gemv_mfma_kernel(GemvArg
     static_assert((DEPTH - 1) * NI <= 63, "vmcnt field");
     static_assert(NW * 64 >= 256 && (size_t)NW * WAVE_B >= (size_t)NW * NS * 16 * 17 * 4, "the partial tiles reuse the ring");
     extern __shared__ __attribute__((aligned(16))) char gsm[];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave_ = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_ & (NW - 1);
+    const bool helper = HELP && wave_ >= NW;
     const int l16 = lane & 15, kg = lane >> 4;
     int64_t row0 = (int64_t)blockIdx.x * 16;
     int which = 0;
+    int64_t upper = 8;                                      // strip row 8 + i is `upper` rows after row i
     const int nstage = a.K / (NW * 64);
     const int64_t kw = (int64_t)wave * nstage * 64;         // first k of this wavefront's contiguous share
     const char* wb[NS];
@@ -417,6 +434,11 @@ __global__ void __launch_bounds__(GEMV_MFMA_WAVES * 64) gemv_mfma_kernel(GemvArg
         wb[NS - 1] = (const char*)((const bf16_t*)a.W[1] + row0 * a.K + kw);
     } else {
         if (row0 >= a.R[0]) { row0 -= a.R[0]; which = 1; if (row0 >= a.R[1]) { row0 -= a.R[1]; which = 2; } }
+        if (MODE == GEMV_QKV_ROPE && which < 2) {
+            const int64_t head = row0 / a.head_dim;
+            row0 = head * a.head_dim + (row0 - head * a.head_dim) / 2;
+            upper = a.head_dim / 2;
+        }
         wb[0] = (const char*)((const bf16_t*)a.W[which] + row0 * a.K + kw);
     }
     const char* xb = (const char*)((const bf16_t*)a.x + kw);
@@ -426,7 +448,7 @@ __global__ void __launch_bounds__(GEMV_MFMA_WAVES * 64) gemv_mfma_kernel(GemvArg
     for (int j = 0; j < 2; ++j) {
         const int r = 8 * j + (lane >> 3), chunk = (lane & 7) ^ (r >> 1);
         const int xr = r < nb ? r : nb - 1;                 // rows beyond the batch: any valid row (their lanes feed zeros)
-        voff_w[j] = (uint32_t)(((int64_t)r * a.K + chunk * 8) * 2);
+        voff_w[j] = (uint32_t)(((j * upper + (r & 7)) * a.K + chunk * 8) * 2);
         voff_x[j] = (uint32_t)(((int64_t)xr * a.K + chunk * 8) * 2);
     }
     const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)gsm + (uint32_t)wave * WAVE_B;
@@ -441,7 +463,53 @@ __global__ void __launch_bounds__(GEMV_MFMA_WAVES * 64) gemv_mfma_kernel(GemvArg
         for (int j = 0; j < XI; ++j) dma16s(voff_x[j], xb + koff, slot + NS * STRIP_B + j * 1024);
     };
     const int npre = nstage < DEPTH ? nstage : DEPTH;
-    for (int st = 0; st < npre; ++st) issue(st);
+    if (!helper)
+        for (int st = 0; st < npre; ++st) issue(st);
+    // the helpers: 1 / rms of the vectors, gamma; for the epilogue, which is theirs (strip row t / 16, vector t % 16 of their t = 0 .. 255), rotation and cache row
+    const int t = (int)threadIdx.x - (HELP ? NW * 64 : 0);
+    float cs = 1.f, sn = 0.f, inv = 0.f;
+    bf16_t* out = nullptr;
+    const bf16_t* const gam = reinterpret_cast<const bf16_t*>(gsm + NW * WAVE_B);   // [K], with NORM
+    if constexpr (NORM) {
+        float* const sums = reinterpret_cast<float*>(gsm + NW * WAVE_B);   // [NW][16], in gamma's place until everyone has them
+        constexpr int GC = GEMV_NORM_K / 8 / (NW * 64);
+        u32x4 g[GC];
+        if (helper) {
+#pragma unroll
+            for (int i = 0; i < GC; ++i) g[i] = reinterpret_cast<const u32x4*>(a.gamma)[min(t + i * NW * 64, a.K / 8 - 1)];
+            float ss = 0.f;
+#pragma unroll 8
+            for (int i = t; i < a.K; i += NW * 64) ss += a.ssq[i];   // [K / 16][16]: lane's vector t % 16
+            ss += __shfl_xor(ss, 16);
+            ss += __shfl_xor(ss, 32);
+            if (lane < 16) sums[wave * 16 + lane] = ss;
+        }
+        __syncthreads();
+        float ss = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) ss += sums[w * 16 + l16];
+        inv = 1.0f / sqrtf(ss / (float)a.K + a.eps);
+        __syncthreads();
+        if (helper) {
+#pragma unroll
+            for (int i = 0; i < GC; ++i)
+                if (t + i * NW * 64 < a.K / 8) reinterpret_cast<u32x4*>(gsm + NW * WAVE_B)[t + i * NW * 64] = g[i];
+        }
+        __syncthreads();
+    }
+    if constexpr (MODE == GEMV_QKV_ROPE) {
+        if (helper) {
+            const int er = t >> 4, eb = (t & 15) < nb ? t & 15 : nb - 1;
+            if (which < 2) {
+                const int j = (int)(row0 % a.head_dim) + (er & 7);
+                double dc, ds;
+                sincos((double)rb.db.pos[eb] * exp2((double)j * rb.neg2_over_d_log2base), &ds, &dc);
+                cs = (float)dc; sn = (float)ds;
+            }
+            out = which == 0 ? (bf16_t*)a.y[0] + (int64_t)eb * a.R[0] : (bf16_t*)(which == 1 ? rb.db.cache_k[eb] : rb.db.cache_v[eb]) + rb.db.count[eb] * a.R[which];
+            if (blockIdx.x == 0 && t < nb) rb.db.cache_pos[t][rb.db.count[t]] = rb.db.pos[t];
+        }
+    }
     // fragment reads: lane (row l16, k group kg), half h of the stage -> chunk 4h + kg of its row
     const char* myring = gsm + (size_t)wave * WAVE_B;
     uint32_t foff[2];
@@ -451,22 +519,33 @@ __global__ void __launch_bounds__(GEMV_MFMA_WAVES * 64) gemv_mfma_kernel(GemvArg
     mfma_f32x4 acc[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) acc[s] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int st = 0; st < nstage; ++st) {
+    for (int st = 0; st < (helper ? 0 : nstage); ++st) {
         // stages issued so far: min(nstage, st + DEPTH); all but the DEPTH - 1 youngest must have landed
         if (st + DEPTH <= nstage) SPTS_WAIT_VMCNT((DEPTH - 1) * NI); else SPTS_WAIT_VMCNT(0);
         asm volatile("" ::: "memory");
         const char* slot = myring + (size_t)(st % DEPTH) * STAGE_B;
-        u32x4 wv[NS][2], xv[2];
+        u32x4 wv[NS][2], xv[2], gv[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) wv[s][h] = *reinterpret_cast<const u32x4*>(slot + s * STRIP_B + foff[h]);
             xv[h] = *reinterpret_cast<const u32x4*>(slot + NS * STRIP_B + foff[h]);
-            if (!tok) xv[h] = u32x4{0u, 0u, 0u, 0u};
+            if (NORM) gv[h] = *reinterpret_cast<const u32x4*>(gam + kw + st * 64 + (4 * h + kg) * 8);
+            if (!NORM && !tok) xv[h] = u32x4{0u, 0u, 0u, 0u};
         }
         // the slot is refilled only after its fragments have arrived in registers
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (st + DEPTH < nstage) issue(st + DEPTH);
+        if (NORM) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float x0 = __uint_as_float(xv[h][i] << 16), x1 = __uint_as_float(xv[h][i] & 0xffff0000u);
+                    const float g0 = __uint_as_float(gv[h][i] << 16), g1 = __uint_as_float(gv[h][i] & 0xffff0000u);
+                    xv[h][i] = tok ? cvt_pk_bf16(x0 * inv * g0, x1 * inv * g1) : 0u;
+                }
+        }
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -478,19 +557,48 @@ __global__ void __launch_bounds__(GEMV_MFMA_WAVES * 64) gemv_mfma_kernel(GemvArg
     // tiles take its place.  Lane (token l16, row group kg) holds rows 4*kg .. 4*kg+3 of its tile.
     __syncthreads();
     float (*sred)[NS][16][17] = reinterpret_cast<float (*)[NS][16][17]>(gsm);
+    if (!helper) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
+        for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sred[wave][s][4 * kg + r][l16] = acc[s][r];
+            for (int r = 0; r < 4; ++r) sred[wave][s][4 * kg + r][l16] = acc[s][r];
+    }
     __syncthreads();
-    const int t = threadIdx.x;
-    if (t >= 256) return;
+    if (t < 0) return;
     const int r = t >> 4, b = t & 15;
+    if (MODE == GEMV_RESID && a.ssq) {   // + the strip's sum of squares of each vector, as stored
+        float v = 0.f, y = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += sred[w][0][r][b];
+        if (b < nb) {
+            bf16_t* p = (bf16_t*)a.y[which] + (int64_t)b * a.R[which] + row0 + r;
+            const bf16_t s = f32_to_bf16(bf16_to_f32(*p) + v);
+            *p = s;
+            y = bf16_to_f32(s);
+        }
+        float ss = y * y;
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        __syncthreads();
+        float* const sums = reinterpret_cast<float*>(gsm);
+        if (lane < 16) sums[wave * 16 + lane] = ss;
+        __syncthreads();
+        if (t < 16) a.ssq[blockIdx.x * 16 + t] = sums[t] + sums[16 + t] + sums[32 + t] + sums[48 + t];
+        return;
+    }
     if (b >= nb) return;
     float v = 0.f, u = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) { v += sred[w][0][r][b]; if (NS == 2) u += sred[w][NS - 1][r][b]; }
-    if (MODE == GEMV_SILU) {
+    if constexpr (MODE == GEMV_QKV_ROPE) {
+        if (which < 2) {
+            float other = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) other += sred[w][0][r ^ 8][b];
+            v = r < 8 ? v * cs - other * sn : v * cs + other * sn;
+        }
+        out[row0 + (r >> 3) * upper + (r & 7)] = f32_to_bf16(v);
+    } else if (MODE == GEMV_SILU) {
         ((bf16_t*)a.y[0])[(int64_t)b * a.R[0] + row0 + r] = f32_to_bf16(v / (1.0f + __expf(-v)) * u);
     } else if (MODE == GEMV_RESID) {
         bf16_t* y = (bf16_t*)a.y[which] + (int64_t)b * a.R[which] + row0 + r;
@@ -502,52 +610,65 @@ __global__ void __launch_bounds__(GEMV_MFMA_WAVES * 64) gemv_mfma_kernel(GemvArg
     }
 }
 
+static int gemv_mfma_lds(const GemvArgs& a) {   // the ring, and gamma behind it
+    const int ns = a.mode == GEMV_SILU ? 2 : 1, depth = ns == 2 ? 3 : 4;
+    return GEMV_MFMA_WAVES * depth * (ns + 1) * 2048 + (a.gamma ? a.K * 2 : 0);
+}
+
 bool gemv_mfma_supported(const GemvArgs& a, int nb) {
-    if (nb < 1 || nb > 16 || a.gamma || a.K <= 0 || a.K % 256 != 0) return false;
-    if (a.mode != GEMV_STORE && a.mode != GEMV_SILU && a.mode != GEMV_RESID && a.mode != GEMV_F32) return false;
+    if (nb < 1 || nb > 16 || a.K <= 0 || a.K % 256 != 0) return false;
+    if (a.mode != GEMV_STORE && a.mode != GEMV_SILU && a.mode != GEMV_RESID && a.mode != GEMV_F32 && a.mode != GEMV_QKV_ROPE) return false;
+    if (a.gamma && (a.mode != GEMV_SILU || !a.ssq || a.K > GEMV_NORM_K)) return false;
+    if (a.mode == GEMV_QKV_ROPE && (a.head_dim <= 0 || a.head_dim % 16 != 0 || a.R[0] % a.head_dim != 0 || a.R[1] % a.head_dim != 0)) return false;
     for (int i = 0; i < 3; ++i)
         if (a.R[i] < 0 || a.R[i] % 16 != 0) return false;
-    // per-lane byte offsets are 32-bit: 16 rows of K elements
-    if ((int64_t)16 * a.K * 2 >= ((int64_t)1 << 32)) return false;
+    // per-lane byte offsets are 32-bit: 16 rows of K elements, or half a head's
+    const int64_t rows = a.mode == GEMV_QKV_ROPE && a.head_dim > 16 ? a.head_dim : 16;
+    if (rows * a.K * 2 >= ((int64_t)1 << 32)) return false;
     return true;
 }
 
-template <int MODE, int XI>
-static hipError_t launch_gemv_mfma_t(const GemvArgs& a, int nb, unsigned grid, hipStream_t s) {
-    constexpr int NS = MODE == GEMV_SILU ? 2 : 1, DEPTH = NS == 2 ? 3 : 4, NW = GEMV_MFMA_WAVES;
-    const size_t lds = (size_t)NW * DEPTH * (NS + 1) * 2048;
-    {
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemv_mfma_kernel<MODE, XI>), (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    gemv_mfma_kernel<MODE, XI><<<dim3(grid), dim3(NW * 64), lds, s>>>(a, nb);
+template <int MODE, int XI, bool NORM>
+static hipError_t launch_gemv_mfma_t(const GemvArgs& a, int nb, const typename GemvRopeOf<MODE>::type& rb, unsigned grid, hipStream_t s) {
+    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemv_mfma_kernel<MODE, XI, NORM>), NORM ? 80 * 1024 : gemv_mfma_lds(a));   // (NORM: the longest gamma)
+    if (e != hipSuccess) return e;
+    gemv_mfma_kernel<MODE, XI, NORM><<<dim3(grid), dim3(gemv_mfma_threads<MODE, NORM>()), gemv_mfma_lds(a), s>>>(a, nb, rb);
     return hipGetLastError();
 }
 
-template <int MODE>
-static hipError_t launch_gemv_mfma_m(const GemvArgs& a, int nb, hipStream_t s) {
+template <int MODE, bool NORM>
+static hipError_t launch_gemv_mfma_m(const GemvArgs& a, int nb, const typename GemvRopeOf<MODE>::type& rb, hipStream_t s) {
     const int64_t rows = MODE == GEMV_SILU ? (int64_t)a.R[0] : (int64_t)a.R[0] + a.R[1] + a.R[2];
     if (rows == 0) return hipSuccess;
     const unsigned grid = (unsigned)(rows / 16);
-    return nb > 8 ? launch_gemv_mfma_t<MODE, 2>(a, nb, grid, s) : launch_gemv_mfma_t<MODE, 1>(a, nb, grid, s);
+    return nb > 8 ? launch_gemv_mfma_t<MODE, 2, NORM>(a, nb, rb, grid, s) : launch_gemv_mfma_t<MODE, 1, NORM>(a, nb, rb, grid, s);
 }
 
 hipError_t launch_gemv_mfma(const GemvArgs& a, int nb, hipStream_t s) {
+    if (!gemv_mfma_supported(a, nb)) return hipErrorInvalidValue;
+    const GemvNoRope none{};
     switch (a.mode) {
-        case GEMV_STORE: return launch_gemv_mfma_m<GEMV_STORE>(a, nb, s);
-        case GEMV_SILU: return launch_gemv_mfma_m<GEMV_SILU>(a, nb, s);
-        case GEMV_RESID: return launch_gemv_mfma_m<GEMV_RESID>(a, nb, s);
-        case GEMV_F32: return launch_gemv_mfma_m<GEMV_F32>(a, nb, s);
+        case GEMV_STORE: return launch_gemv_mfma_m<GEMV_STORE, false>(a, nb, none, s);
+        case GEMV_SILU: return a.gamma ? launch_gemv_mfma_m<GEMV_SILU, true>(a, nb, none, s) : launch_gemv_mfma_m<GEMV_SILU, false>(a, nb, none, s);
+        case GEMV_RESID: return launch_gemv_mfma_m<GEMV_RESID, false>(a, nb, none, s);
+        case GEMV_F32: return launch_gemv_mfma_m<GEMV_F32, false>(a, nb, none, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_gemv_qkv_batched(const GemvArgs& a, const DecodeBatch& db, float base, hipStream_t s) {
+    if (a.mode != GEMV_QKV_ROPE || db.n < 1 || db.n > DECODE_MAX_BATCH || !gemv_mfma_supported(a, db.n)) return hipErrorInvalidValue;
+    const GemvRopeBatch rb{db, -2.0 / (double)a.head_dim * log2((double)base)};
+    return launch_gemv_mfma_m<GEMV_QKV_ROPE, false>(a, db.n, rb, s);
 }
 
 // nb input vectors (1 <= nb <= 16).  bf16 with tile-friendly shapes runs on the matrix cores; otherwise the
 // dot-product kernel, instantiated for 2, 4 and 8 vectors: other counts run as a sum of those (rows of X and Y are
 // contiguous, so a group of vectors is the same call on shifted pointers)
 hipError_t launch_gemv_nb(const GemvArgs& a, int nb, bool bf16, hipStream_t s) {
-    if (nb < 1 || nb > DECODE_MAX_BATCH || a.gamma || a.mode == GEMV_QKV_ROPE) return hipErrorInvalidValue;
+    if (nb < 1 || nb > DECODE_MAX_BATCH || a.mode == GEMV_QKV_ROPE) return hipErrorInvalidValue;
     if (bf16 && nb > 1 && gemv_mfma_supported(a, nb)) return launch_gemv_mfma(a, nb, s);
+    if (a.gamma) return hipErrorInvalidValue;
     const size_t eb = bf16 ? 2 : 4;
     int done = 0;
     while (done < nb) {

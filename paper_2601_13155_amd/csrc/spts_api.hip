@@ -775,13 +775,25 @@ int spts_decode_layer_batched(spts_ctx* c, void* x, const int32_t* pos, int32_t 
     if (part_floats / (size_t)batch < decode_attn_min_scratch_floats(m.Hkv, m.d)) return SPTS_EWORKSPACE;
     hipStream_t st = c->stream;
     c->dec_rope_pos = -1;
+    const bool mfma = c->bf16 && batch > 1;
+    GemvArgs qr = qkv; qr.mode = GEMV_QKV_ROPE; qr.head_dim = m.d; qr.y[0] = q; qr.y[1] = qr.y[2] = nullptr;
     { PHASE(c, PH_DEC_NORM); SPTS_HIP(c, launch_rmsnorm(x, w->gamma1, m.rms_eps, xn, batch, m.D, c->bf16, st)); }
-    { PHASE(c, PH_DEC_QKV); SPTS_HIP(c, launch_gemv_nb(qkv, batch, c->bf16, st)); }
-    { PHASE(c, PH_DEC_ROPE_APPEND);
-      SPTS_HIP(c, launch_decode_rope_append_batched(q32, k32, v32, q, m.H, m.Hkv, m.d, m.rope_base, db, c->bf16, st)); }
+    if (mfma && gemv_mfma_supported(qr, batch)) {
+        PHASE(c, PH_DEC_QKV);
+        SPTS_HIP(c, launch_gemv_qkv_batched(qr, db, m.rope_base, st));
+    } else {
+        { PHASE(c, PH_DEC_QKV); SPTS_HIP(c, launch_gemv_nb(qkv, batch, c->bf16, st)); }
+        PHASE(c, PH_DEC_ROPE_APPEND);
+        SPTS_HIP(c, launch_decode_rope_append_batched(q32, k32, v32, q, m.H, m.Hkv, m.d, m.rope_base, db, c->bf16, st));
+    }
     { PHASE(c, PH_DEC_ATTN); SPTS_HIP(c, launch_decode_attn_batched(q, db, m.H, m.Hkv, m.d, part, part_floats, att, c->bf16, st)); }
+    // the second norm inside gate/up, from sums of squares that the O projection leaves (4 D bytes in the place of the normalised rows)
+    GemvArgs os = o, gn = gu;
+    os.ssq = gn.ssq = (float*)xn; gn.x = x; gn.gamma = w->gamma2; gn.eps = m.rms_eps;
+    const bool norm_inside = mfma && gemv_mfma_supported(os, batch) && gemv_mfma_supported(gn, batch);
+    if (norm_inside) { o = os; gu = gn; }
     { PHASE(c, PH_DEC_O); SPTS_HIP(c, launch_gemv_nb(o, batch, c->bf16, st)); }
-    { PHASE(c, PH_DEC_NORM); SPTS_HIP(c, launch_rmsnorm(x, w->gamma2, m.rms_eps, xn, batch, m.D, c->bf16, st)); }
+    if (!norm_inside) { PHASE(c, PH_DEC_NORM); SPTS_HIP(c, launch_rmsnorm(x, w->gamma2, m.rms_eps, xn, batch, m.D, c->bf16, st)); }
     { PHASE(c, PH_DEC_GATE_UP); SPTS_HIP(c, launch_gemv_nb(gu, batch, c->bf16, st)); }
     { PHASE(c, PH_DEC_DOWN); SPTS_HIP(c, launch_gemv_nb(dn, batch, c->bf16, st)); }
     for (int b = 0; b < batch; ++b) caches[b].count += 1;

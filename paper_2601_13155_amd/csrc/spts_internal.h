@@ -290,6 +290,7 @@ struct GemvArgs {
     const void* W[3]; void* y[3]; int32_t R[3];
     const void* x; int32_t K; int mode;
     const void* gamma; float eps;
+    float* ssq;                             // gemv_mfma_kernel, [rows / 16][16]: RESID leaves the sums of squares of y by strips, SILU with gamma has x's
     const float2* rope; int32_t head_dim;   // GEMV_QKV_ROPE: (cos, sin)[head_dim / 2] of the token's position
     int32_t* pos_out; int32_t pos_val;      // GEMV_QKV_ROPE: *pos_out = pos_val (the cache row's position), when not NULL
 };
@@ -313,8 +314,11 @@ struct DecodeBatch {
     int64_t count[DECODE_MAX_BATCH]; int32_t pos[DECODE_MAX_BATCH]; int32_t n;
 };
 // Y[b, r] = W[r, :] . X[b, :] for nb <= DECODE_MAX_BATCH input vectors (X [nb, K], Y[i] [nb, R[i]] contiguous); modes STORE, SILU,
-// RESID, F32; no fused norm
+// RESID, F32; with gamma (a norm of X inside) or ssq only what gemv_mfma_supported takes
+bool gemv_mfma_supported(const GemvArgs& a, int nb);
 hipError_t launch_gemv_nb(const GemvArgs& a, int nb, bool bf16, hipStream_t s);
+// bf16, mode QKV_ROPE, gemv_mfma_supported: y[0] [n, H, d] = rotated queries, rotated keys and values into row count[b] of sequence b's cache
+hipError_t launch_gemv_qkv_batched(const GemvArgs& a, const DecodeBatch& db, float base, hipStream_t s);
 // fp32 projection sums q32 [n, H, d], k32 / v32 [n, Hkv, d] -> q [n, H, d] rotated, k rotated / v copied into row count[b] of
 // sequence b's cache; one rounding to the element type, after the rotation
 hipError_t launch_decode_rope_append_batched(const float* q32, const float* k32, const float* v32, void* q, int H, int Hkv, int d,

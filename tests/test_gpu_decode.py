@@ -340,3 +340,37 @@ def test_decode_norms_inside_the_products(torch, dtype, D):
     _, ref = orc.greedy_token(got, gamma_f, table, mdl, rnd)
     assert np.max(np.abs(lg - ref)) <= tol * np.max(np.abs(ref))
     assert int(tok[0]) == int(np.flatnonzero(lg == lg.max())[0]) and torch.equal(x_next, td[int(tok[0])])
+
+
+@pytest.mark.parametrize("D,H_,Hkv,d,nseq", [(256, 4, 2, 16, 2), (768, 3, 1, 32, 8), (3584, 4, 2, 64, 9), (4096, 2, 1, 128, 16), (4352, 2, 2, 128, 5),
+                                             (8192, 2, 1, 64, 16), (8448, 2, 1, 64, 3)])
+def test_batched_decode_norms_and_rotary_inside_the_products(torch, D, H_, Hkv, d, nseq):
+    """bf16, widths around the limit of the products that normalise their input (4096 elements) and are split over a workgroup's wavefronts (K = 256, one stage each), every head dimension, gammas that differ from one, batches of one and two loads of vectors."""
+    dtype = "bf16"
+    shape = synth.ModelShape(D=D, H=H_, Hkv=Hkv, d=d, Dff=256, dtype=dtype)
+    assert D % 256 == 0 and (H_ * d) % 16 == 0
+    mdl, rnd, tol = H.oracle_model(shape), H.rnd_for(dtype), H.TOL[dtype]["hidden"]
+    w = synth.make_layer(53, 0, shape, 16)
+    rng = np.random.default_rng(D + nseq)
+    for g in ("gamma1", "gamma2"):
+        w[g] = rnd(rng.uniform(0.5, 1.5, D)).astype(np.float32)
+    dw = runtime.upload_layer(w, shape, 16)
+    ctx = ctx_for(shape, 64)
+    caches = [runtime.KVCache(shape, 4) for _ in range(nseq)]
+    new = synth.hidden_states(54, 2 * nseq, D, dtype).reshape(2, nseq, D)
+    for t in range(2):
+        before = [c.host() for c in caches]
+        pos = [1000 * b + 7 * t for b in range(nseq)]
+        xt = runtime.to_device(new[t].copy(), dtype)
+        x_in = runtime.to_host(xt).astype(np.float64)
+        ctx.spts_decode_layer_batched(xt, pos, dw, [c.struct for c in caches])
+        torch.cuda.synchronize()
+        got = runtime.to_host(xt).astype(np.float64)
+        for b in range(nseq):
+            kh, vh, ph = before[b]
+            ref_x, ref_c = orc.decode_layer(x_in[b], pos[b], w, mdl, orc.LayerCache(kh, vh, ph), rnd)
+            assert H.row_rel_err(got[b][None, :], ref_x.reshape(1, -1)) <= tol, (t, b)
+            k2, v2, p2 = caches[b].host()
+            assert k2.shape[0] == kh.shape[0] + 1 and p2[-1] == pos[b] and np.array_equal(k2[:-1], kh) and np.array_equal(v2[:-1], vh)
+            for mine, ref in ((k2[-1], ref_c.k[-1]), (v2[-1], ref_c.v[-1])):
+                assert H.row_rel_err(mine.reshape(1, -1), np.asarray(ref).reshape(1, -1)) <= tol, (t, b)
