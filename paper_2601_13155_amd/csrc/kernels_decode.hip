@@ -13,7 +13,7 @@
 //     one launch (Q, K, V).  Epilogues: store, SiLU(gate)*up, residual add, fp32 store (logits).
 //   * decode_attn_kernel: flash-decoding.  Grid = (key splits, KV heads); 64/LPK keys per wavefront
 //     step (LPK lanes hold one key row as 16-byte pieces), every lane group keeps its own running
-//     (max, sum, weighted values) for all query heads of the KV head; groups, wavefronts and splits
+//     (max, sum, weighted values) for all query heads of the KV head, a lane the maximum and sum of one head; groups, wavefronts and splits
 //     are merged with the usual (max, sum) algebra in a fixed order (deterministic).
 //   * small kernels: rotary embedding of q / k for the new position + cache append, merge of the
 //     splits, argmax with ties to the lowest token id, table row gather.
@@ -806,13 +806,77 @@ hipError_t launch_decode_rope_append_batched(const float* q32, const float* k32,
 // partial layout: part[((g * nsplit + split) * GRP_MAX + hg) * (d + 2)] = (max, sum, weighted values[d])
 constexpr int GRP_MAX = 8;
 
+// ---- the lanes of a key (LPK of them, each with a piece of the row) and the query heads: every lane owns one of GL heads, number lane % GL
+template <int CTRL> __device__ __forceinline__ float dpp(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;   // (quad permutes, lane 7 - i of 8, rotations of 16)
+
+// p[h]: this lane's part of head h's sum -> the whole sum of the lane's own head.  As many heads as there are left are halved with the lanes, one
+// partner keeping either half, so that all heads together take GL - 1 additions and a few more, not GL log2(LPK).
+template <int LPK, int GL>
+__device__ __forceinline__ float sum_own_head(float (&p)[GL], int lane) {
+    if (GL == 8) {
+#pragma unroll
+        for (int h = 0; h < GL / 2; ++h) {
+            const float keep = lane & 4 ? p[GL / 2 + h] : p[h], send = lane & 4 ? p[h] : p[GL / 2 + h];
+            p[h] = keep + dpp<DPP_HALF_MIRROR>(send);
+        }
+    } else if (LPK == 8) {
+#pragma unroll
+        for (int h = 0; h < GL; ++h) p[h] += dpp<DPP_HALF_MIRROR>(p[h]);
+    }
+    if (GL >= 4) {
+        constexpr int H2 = GL >= 4 ? 2 : 0;
+#pragma unroll
+        for (int h = 0; h < H2; ++h) {
+            const float keep = lane & 2 ? p[H2 + h] : p[h], send = lane & 2 ? p[h] : p[H2 + h];
+            p[h] = keep + dpp<DPP_XOR2>(send);
+        }
+    }
+    if (GL >= 2) {
+        constexpr int H1 = GL >= 2 ? 1 : 0;
+        const float keep = lane & 1 ? p[H1] : p[0], send = lane & 1 ? p[0] : p[H1];
+        p[0] = keep + dpp<DPP_XOR1>(send);
+    }
+    float v = p[0];
+    if (GL == 1 && LPK >= 2) v += dpp<DPP_XOR1>(v);
+    if (GL <= 2 && LPK >= 4) v += dpp<DPP_XOR2>(v);
+    if (LPK >= 16) {
+        v += dpp<DPP_ROR8>(v);
+        if (GL < 8) v += dpp<DPP_ROR4>(v);
+    }
+    if (LPK >= 32) v += __shfl_xor(v, 16);
+    return v;
+}
+
+// v: a value of the lane's own head -> every head's, in every lane of the key
+template <int GL>
+__device__ __forceinline__ void all_heads(float v, int lane, float (&out)[GL]) {
+    if (GL == 1) out[0] = v;
+    if (GL == 2) { out[0] = dpp<0xA0>(v); out[GL / 2] = dpp<0xF5>(v); }   // quad_perm [0,0,2,2], [1,1,3,3]
+    if (GL >= 4) {
+        const float q[4] = {dpp<0x00>(v), dpp<0x55>(v), dpp<0xAA>(v), dpp<0xFF>(v)};
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const float other = GL == 8 ? dpp<DPP_HALF_MIRROR>(q[h]) : 0.f;
+            out[h & (GL - 1)] = GL == 8 && (lane & 4) ? other : q[h];
+            if (GL == 8) out[(4 + h) & (GL - 1)] = lane & 4 ? q[h] : other;
+        }
+    }
+}
+
 // G: query heads per KV head the register arrays are sized for (>= H / Hkv)
-template <typename T, int D, int G>
+// What bounds it besides the caches' bytes is instructions: per key and head a reduction over the key's lanes, a maximum, an exponential and the test for a
+// new maximum.  The lanes of a key hold the same sums, so each does that for one head only.
+// U: keys that a lane takes at a time (see decode_attn_pairs).
+template <typename T, int D, int G, int U>
 __device__ __forceinline__ void decode_attn_body(const T* __restrict__ q, const T* __restrict__ K, const T* __restrict__ V,
                                                  int64_t M, int H, int Hkv, float scale_log2e, float* __restrict__ part) {
     constexpr int EPC = 16 / (int)sizeof(T);
     constexpr int LPK = D / EPC;          // lanes that hold one key row
     constexpr int KPW = 64 / LPK;         // keys per wavefront step
+    constexpr int GL = G < LPK ? G : LPK, R = G / GL;   // heads that share the lanes, heads per lane
     __shared__ float sm[4][G][2];
     __shared__ float sacc[4][G][D];
 
@@ -831,81 +895,110 @@ __device__ __forceinline__ void decode_attn_body(const T* __restrict__ q, const 
         const int h = g * grp + (hg < grp ? hg : 0);
         qv[hg] = *reinterpret_cast<const u32x4*>(q + (int64_t)h * D + sub * EPC);
     }
-    float mrun[G], lrun[G], acc[G][EPC];
+    float mrun[R], lrun[R], acc[G][EPC];
 #pragma unroll
-    for (int hg = 0; hg < G; ++hg) {
-        mrun[hg] = -INFINITY; lrun[hg] = 0.f;
+    for (int r = 0; r < R; ++r) { mrun[r] = -INFINITY; lrun[r] = 0.f; }
+#pragma unroll
+    for (int hg = 0; hg < G; ++hg)
 #pragma unroll
         for (int e = 0; e < EPC; ++e) acc[hg][e] = 0.f;
-    }
 
-    // keys of this lane: m_begin + wave*KPW + kslot + it * 4*KPW; the next pair is loaded before the
-    // current one is used (rings of two or three more pairs in flight measured 25 % slower, at equal
-    // occupancy)
-    const T* Kg = K + (int64_t)g * D + sub * EPC;
-    const T* Vg = V + (int64_t)g * D + sub * EPC;
+    // keys of this lane: m_begin + wave*KPW + kslot + it * 4*KPW, U of them at a time; the next U are loaded before the
+    // current ones are used
+    const T* Kg = K + m_begin * Hkv * D + (int64_t)g * D + sub * EPC;
+    const T* Vg = V + m_begin * Hkv * D + (int64_t)g * D + sub * EPC;
     const int64_t rstride = (int64_t)Hkv * D;
-    int64_t m = m_begin + wave * KPW + kslot;
-    u32x4 kv = {0, 0, 0, 0}, vv = {0, 0, 0, 0};
-    if (m_begin < m_end) {
-        const int64_t mc = m < m_end ? m : m_end - 1;
-        kv = *reinterpret_cast<const u32x4*>(Kg + mc * rstride);
-        vv = *reinterpret_cast<const u32x4*>(Vg + mc * rstride);
-    }
-    for (int64_t m0 = m_begin + wave * KPW; m0 < m_end; m0 += 4 * KPW, m += 4 * KPW) {
-        const bool valid = m < m_end;
-        const int64_t mn_ = m + 4 * KPW;
-        const int64_t mnc = mn_ < m_end ? mn_ : m_end - 1;
-        const u32x4 kvn = *reinterpret_cast<const u32x4*>(Kg + mnc * rstride);
-        const u32x4 vvn = *reinterpret_cast<const u32x4*>(Vg + mnc * rstride);
-        float vf[EPC];
+    const int n = m_begin < m_end ? (int)(m_end - m_begin) : 0;
+    u32x4 kn[U], vn[U];
+    auto load = [&](int i0) {
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) vf[e] = chunk_elem(vv, e, T{});
+        for (int u = 0; u < U; ++u) {
+            const int64_t at = min(i0 + u * 4 * KPW, n - 1) * rstride;
+            kn[u] = *reinterpret_cast<const u32x4*>(Kg + at);
+            vn[u] = *reinterpret_cast<const u32x4*>(Vg + at);
+        }
+    };
+    if (n > 0) load(wave * KPW + kslot);
+    for (int i0 = wave * KPW; i0 < n; i0 += U * 4 * KPW) {
+        const int i = i0 + kslot;
+        u32x4 kv[U], vv[U];
 #pragma unroll
-        for (int hg = 0; hg < G; ++hg) {
-            if (hg < grp) {
-                float s = group_sum<LPK>(dot16(kv, qv[hg], 0.f, T{}));
-                s = valid ? s * scale_log2e : -INFINITY;
-                const float mn = fmaxf(mrun[hg], s);
-                const float mu = mn == -INFINITY ? 0.f : mn;
-                // the running maximum rarely moves after the first keys: rescale only when it did for some lane
-                if (__ballot(mn != mrun[hg]) != 0) {
-                    const float alpha = __builtin_amdgcn_exp2f(mrun[hg] - mu);
-                    lrun[hg] *= alpha;
+        for (int u = 0; u < U; ++u) { kv[u] = kn[u]; vv[u] = vn[u]; }
+        load(i + U * 4 * KPW);
+        float s[U][R];
 #pragma unroll
-                    for (int e = 0; e < EPC; ++e) acc[hg][e] *= alpha;
-                    mrun[hg] = mn;
-                }
-                const float p = __builtin_amdgcn_exp2f(s - mu);
-                lrun[hg] += p;
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int e = 0; e < EPC; ++e) acc[hg][e] = __builtin_fmaf(p, vf[e], acc[hg][e]);
+            for (int r = 0; r < R; ++r) {
+                float p[GL];
+#pragma unroll
+                for (int h = 0; h < GL; ++h) p[h] = r * GL + h < grp ? dot16(kv[u], qv[r * GL + h], 0.f, T{}) : 0.f;
+                const float t = sum_own_head<LPK, GL>(p, lane);
+                s[u][r] = i + u * 4 * KPW < n ? t * scale_log2e : -INFINITY;
+            }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float mn = mrun[r];
+#pragma unroll
+            for (int u = 0; u < U; ++u) mn = fmaxf(mn, s[u][r]);
+            const float mu = mn == -INFINITY ? 0.f : mn;
+            // the running maximum rarely moves after the first keys: rescale only when it did for some lane
+            if (__ballot(mn != mrun[r]) != 0) {
+                const float alpha = __builtin_amdgcn_exp2f(mrun[r] - mu);
+                lrun[r] *= alpha;
+                mrun[r] = mn;
+                float ah[GL];
+                all_heads<GL>(alpha, lane, ah);
+#pragma unroll
+                for (int h = 0; h < GL; ++h)
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) acc[r * GL + h][e] *= ah[h];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float p = __builtin_amdgcn_exp2f(s[u][r] - mu);
+                lrun[r] += p;
+                float ph[GL];
+                all_heads<GL>(p, lane, ph);
+#pragma unroll
+                for (int h = 0; h < GL; ++h)
+                    if (r * GL + h < grp) {
+#pragma unroll
+                        for (int e = 0; e < EPC; ++e) acc[r * GL + h][e] = __builtin_fmaf(ph[h], chunk_elem(vv[u], e, T{}), acc[r * GL + h][e]);
+                    }
             }
         }
-        kv = kvn;
-        vv = vvn;
     }
     // merge the KPW lane groups of the wavefront (lanes with equal `sub`)
 #pragma unroll
-    for (int hg = 0; hg < G; ++hg) {
-        if (hg < grp) {
+    for (int r = 0; r < R; ++r) {
 #pragma unroll
-            for (int off = LPK; off < 64; off <<= 1) {
-                const float mo = __shfl_xor(mrun[hg], off), lo = __shfl_xor(lrun[hg], off);
-                const float mn = fmaxf(mrun[hg], mo);
-                const float mu = mn == -INFINITY ? 0.f : mn;
-                const float a0 = __builtin_amdgcn_exp2f(mrun[hg] - mu), a1 = __builtin_amdgcn_exp2f(mo - mu);
-                lrun[hg] = lrun[hg] * a0 + lo * a1;
+        for (int off = LPK; off < 64; off <<= 1) {
+            const float mo = __shfl_xor(mrun[r], off), lo = __shfl_xor(lrun[r], off);
+            const float mn = fmaxf(mrun[r], mo);
+            const float mu = mn == -INFINITY ? 0.f : mn;
+            const float a0 = __builtin_amdgcn_exp2f(mrun[r] - mu), a1 = __builtin_amdgcn_exp2f(mo - mu);
+            lrun[r] = lrun[r] * a0 + lo * a1;
+            mrun[r] = mn;
+            float h0[GL], h1[GL];
+            all_heads<GL>(a0, lane, h0);
+            all_heads<GL>(a1, lane, h1);
 #pragma unroll
-                for (int e = 0; e < EPC; ++e) acc[hg][e] = acc[hg][e] * a0 + __shfl_xor(acc[hg][e], off) * a1;
-                mrun[hg] = mn;
-            }
-            if (kslot == 0) {
-                if (sub == 0) { sm[wave][hg][0] = mrun[hg]; sm[wave][hg][1] = lrun[hg]; }
+            for (int h = 0; h < GL; ++h)
+                if (r * GL + h < grp) {
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) acc[r * GL + h][e] = acc[r * GL + h][e] * h0[h] + __shfl_xor(acc[r * GL + h][e], off) * h1[h];
+                }
+        }
+        if (lane < GL) { sm[wave][r * GL + lane][0] = mrun[r]; sm[wave][r * GL + lane][1] = lrun[r]; }
+    }
+    if (kslot == 0) {
+#pragma unroll
+        for (int hg = 0; hg < G; ++hg)
+            if (hg < grp) {
 #pragma unroll
                 for (int e = 0; e < EPC; ++e) sacc[wave][hg][sub * EPC + e] = acc[hg][e];
             }
-        }
     }
     __syncthreads();
     // merge the 4 wavefronts: thread t < grp * D handles (hg, element)
@@ -928,19 +1021,19 @@ __device__ __forceinline__ void decode_attn_body(const T* __restrict__ q, const 
     }
 }
 
-template <typename T, int D, int G>
+template <typename T, int D, int G, int U>
 __global__ void __launch_bounds__(256) decode_attn_kernel(const T* __restrict__ q, const T* __restrict__ K,
                                                           const T* __restrict__ V, int64_t M, int H, int Hkv, float scale_log2e,
                                                           float* __restrict__ part) {
-    decode_attn_body<T, D, G>(q, K, V, M, H, Hkv, scale_log2e, part);
+    decode_attn_body<T, D, G, U>(q, K, V, M, H, Hkv, scale_log2e, part);
 }
 // blockIdx.z = sequence: its query [H, D], its cache (count[b] + 1 pairs: the new pair is already appended) and its
 // share of the partial buffer
-template <typename T, int D, int G>
+template <typename T, int D, int G, int U>
 __global__ void __launch_bounds__(256) decode_attn_batched_kernel(const T* __restrict__ q, DecodeBatch db, int H, int Hkv,
                                                                   float scale_log2e, float* __restrict__ part, int64_t part_stride) {
     const int b = blockIdx.z;
-    decode_attn_body<T, D, G>(q + (int64_t)b * H * D, (const T*)db.cache_k[b], (const T*)db.cache_v[b], db.count[b] + 1, H, Hkv,
+    decode_attn_body<T, D, G, U>(q + (int64_t)b * H * D, (const T*)db.cache_k[b], (const T*)db.cache_v[b], db.count[b] + 1, H, Hkv,
                               scale_log2e, part + (int64_t)b * part_stride);
 }
 
@@ -1002,6 +1095,11 @@ int decode_attn_splits(int64_t M, int Hkv, int d, size_t scratch_floats, int nse
     if (s < 1) s = 1;
     return (int)s;
 }
+// Two keys at a time per lane, four loads in flight instead of two and one test for a new maximum, where a split has keys enough to fill the
+// longer pipeline: attention of two layers with 750 keys to a split (8 sequences of 6001 .. 2851 pairs, 16 of 3000 .. 1313) 79.9 -> 68.5 us and 80.6 -> 69.6, with
+// 375 (2 of 12000 and 8400) 46.1 -> 48.5, with 205 (one of 13107) 37.0 -> 39.4.  (One head per lane instead of all heads in every lane came to 80.3, 80.4, 51.2 and
+// 41.0 -> the first figures.  Three keys: 69.8, 70.6, 50.7, 41.5.)
+static bool decode_attn_pairs(int64_t M, int nsplit) { return (M + nsplit - 1) / nsplit >= 512; }
 size_t decode_attn_min_scratch_floats(int Hkv, int d) { return (size_t)Hkv * GRP_MAX * (d + 2); }
 
 bool decode_attn_supported(int H, int Hkv, int d, bool bf16) {
@@ -1017,11 +1115,15 @@ static hipError_t launch_decode_attn_t(const T* q, const T* K, const T* V, int64
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)d);
     const dim3 g((unsigned)nsplit, (unsigned)Hkv), b(256);
     const int grp = H / Hkv;
-#define SPTS_DEC_ATTN(D_)                                                                                      \
-    if (grp <= 1) decode_attn_kernel<T, D_, 1><<<g, b, 0, s>>>(q, K, V, M, H, Hkv, scale_log2e, part);         \
-    else if (grp <= 2) decode_attn_kernel<T, D_, 2><<<g, b, 0, s>>>(q, K, V, M, H, Hkv, scale_log2e, part);    \
-    else if (grp <= 4) decode_attn_kernel<T, D_, 4><<<g, b, 0, s>>>(q, K, V, M, H, Hkv, scale_log2e, part);    \
-    else decode_attn_kernel<T, D_, GRP_MAX><<<g, b, 0, s>>>(q, K, V, M, H, Hkv, scale_log2e, part);
+    const bool two = decode_attn_pairs(M, nsplit);
+#define SPTS_DEC_ATTN_U(D_, G_)                                                                             \
+    if (two) decode_attn_kernel<T, D_, G_, 2><<<g, b, 0, s>>>(q, K, V, M, H, Hkv, scale_log2e, part);       \
+    else decode_attn_kernel<T, D_, G_, 1><<<g, b, 0, s>>>(q, K, V, M, H, Hkv, scale_log2e, part);
+#define SPTS_DEC_ATTN(D_)                                                                                   \
+    if (grp <= 1) { SPTS_DEC_ATTN_U(D_, 1) }                                                                \
+    else if (grp <= 2) { SPTS_DEC_ATTN_U(D_, 2) }                                                           \
+    else if (grp <= 4) { SPTS_DEC_ATTN_U(D_, 4) }                                                           \
+    else { SPTS_DEC_ATTN_U(D_, GRP_MAX) }
     switch (d) {
         case 128: SPTS_DEC_ATTN(128) break;
         case 64: SPTS_DEC_ATTN(64) break;
@@ -1030,6 +1132,7 @@ static hipError_t launch_decode_attn_t(const T* q, const T* K, const T* V, int64
         default: return hipErrorInvalidValue;
     }
 #undef SPTS_DEC_ATTN
+#undef SPTS_DEC_ATTN_U
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     decode_attn_merge_kernel<T><<<dim3((unsigned)H), dim3(1024), 0, s>>>(part, nsplit, H, Hkv, d, out, 0);
@@ -1057,11 +1160,15 @@ static hipError_t launch_decode_attn_batched_t(const T* q, const DecodeBatch& db
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)d);
     const dim3 g((unsigned)nsplit, (unsigned)Hkv, (unsigned)db.n), b(256);
     const int grp = H / Hkv;
-#define SPTS_DEC_ATTN_B(D_)                                                                                                 \
-    if (grp <= 1) decode_attn_batched_kernel<T, D_, 1><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);           \
-    else if (grp <= 2) decode_attn_batched_kernel<T, D_, 2><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);      \
-    else if (grp <= 4) decode_attn_batched_kernel<T, D_, 4><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);      \
-    else decode_attn_batched_kernel<T, D_, GRP_MAX><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);
+    const bool two = decode_attn_pairs(mmax, nsplit);
+#define SPTS_DEC_ATTN_BU(D_, G_)                                                                                          \
+    if (two) decode_attn_batched_kernel<T, D_, G_, 2><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);          \
+    else decode_attn_batched_kernel<T, D_, G_, 1><<<g, b, 0, s>>>(q, db, H, Hkv, scale_log2e, part, stride);
+#define SPTS_DEC_ATTN_B(D_)                                                                                               \
+    if (grp <= 1) { SPTS_DEC_ATTN_BU(D_, 1) }                                                                             \
+    else if (grp <= 2) { SPTS_DEC_ATTN_BU(D_, 2) }                                                                        \
+    else if (grp <= 4) { SPTS_DEC_ATTN_BU(D_, 4) }                                                                        \
+    else { SPTS_DEC_ATTN_BU(D_, GRP_MAX) }
     switch (d) {
         case 128: SPTS_DEC_ATTN_B(128) break;
         case 64: SPTS_DEC_ATTN_B(64) break;
@@ -1070,6 +1177,7 @@ static hipError_t launch_decode_attn_batched_t(const T* q, const DecodeBatch& db
         default: return hipErrorInvalidValue;
     }
 #undef SPTS_DEC_ATTN_B
+#undef SPTS_DEC_ATTN_BU
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     decode_attn_merge_kernel<T><<<dim3((unsigned)H, (unsigned)db.n), dim3(1024), 0, s>>>(part, nsplit, H, Hkv, d, out, stride);

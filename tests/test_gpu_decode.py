@@ -374,3 +374,37 @@ def test_batched_decode_norms_and_rotary_inside_the_products(torch, D, H_, Hkv, 
             assert k2.shape[0] == kh.shape[0] + 1 and p2[-1] == pos[b] and np.array_equal(k2[:-1], kh) and np.array_equal(v2[:-1], vh)
             for mine, ref in ((k2[-1], ref_c.k[-1]), (v2[-1], ref_c.v[-1])):
                 assert H.row_rel_err(mine.reshape(1, -1), np.asarray(ref).reshape(1, -1)) <= tol, (t, b)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("H_,Hkv,d", [(8, 8, 128), (8, 4, 64), (32, 8, 128), (14, 2, 128), (8, 1, 32), (16, 4, 16), (16, 2, 16), (6, 1, 64)])
+def test_decode_attention_keys_per_split(torch, dtype, H_, Hkv, d):
+    """Every way heads share a key's lanes (1 / 2 / 4 / 8 heads over 2 .. 32 lanes), with few and with many keys to a split: one sequence alone, then
+    16 at once, whose longest cache has just under and just over 512 keys to each of the launch's splits; a split's last keys are one short, whole, one more."""
+    shape = synth.ModelShape(D=256, H=H_, Hkv=Hkv, d=d, Dff=256, dtype=dtype)
+    mdl, rnd, tol = H.oracle_model(shape), H.rnd_for(dtype), H.TOL[dtype]["hidden"]
+    w = synth.make_layer(57, 0, shape, 16)
+    dw = runtime.upload_layer(w, shape, 16)
+    ctx = ctx_for(shape, 4096)
+    splits = max(1, 512 // (Hkv * 16))
+    for longest in (511 * splits - 1, 512 * splits + 1):
+        lens = [longest, longest - 7, longest // 2, 70, 1, 0, 64, 63, 5, 33, 17, 15, 16, 31, 2, 3]
+        caches = [runtime.KVCache(shape, n + 2) for n in lens]
+        for b, (c, n) in enumerate(zip(caches, lens)):
+            _fill_cache(torch, c, shape, n, 700 + b)
+        new = synth.hidden_states(58, 2 * len(lens), shape.D, dtype).reshape(2, len(lens), shape.D)
+        for batched in (False, True):
+            before = [c.host() for c in caches]
+            xt = runtime.to_device(new[int(batched)].copy(), dtype)
+            x_in = runtime.to_host(xt).astype(np.float64)
+            pos = [n + int(batched) for n in lens]
+            if batched:
+                ctx.spts_decode_layer_batched(xt, pos, dw, [c.struct for c in caches])
+            else:
+                for b in (0, 3):
+                    ctx.spts_decode_layer(xt[b], pos[b], dw, caches[b].struct)
+            torch.cuda.synchronize()
+            got = runtime.to_host(xt).astype(np.float64)
+            for b in range(len(lens)) if batched else (0, 3):
+                ref_x, _ = orc.decode_layer(x_in[b], pos[b], w, mdl, orc.LayerCache(*before[b]), rnd)
+                assert H.row_rel_err(got[b][None, :], ref_x.reshape(1, -1)) <= tol, (longest, batched, b)
