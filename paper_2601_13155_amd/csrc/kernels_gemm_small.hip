@@ -111,12 +111,14 @@ __device__ __forceinline__ void small_store_ct(const GemmArgs& a, int col, int64
     for (int t = 0; t < 4; ++t) ct[(int64_t)(col + t) * a.ldct + vt_key_slot(grow)].v = e[t];
 }
 
-// workgroup `block` of a product
-template <int TM>
+// workgroup `block` of a product.  PAIRS (row-major A): two slabs of A travel together, so that a load takes whole 128-byte lines of 8 rows and not
+// halves of 16, which come twice.  The same LDS: two slots of a pair each, then the four stages of B.
+template <int TM, bool PAIRS>
 __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN, int ksplit, int block) {
     constexpr int MI = TM / 64;                 // 32-row blocks per wavefront
     constexpr int NST = SMALL_STAGES, STAGE = small_stage_bytes<TM>(), A_BYTES = TM * SROW;
-    constexpr int LA = TM / 64, LB = 2, PER = LA + LB;   // direct-to-LDS loads per wavefront and slab: 16 rows each
+    constexpr int LA = TM / 64, LB = 2, PER = LA + LB;   // direct-to-LDS loads per wavefront and slab: 16 rows each (row-major A: 2 LA of 8 rows per two slabs)
+    constexpr int PAIR = TM * 2 * SROW, B_RING = 2 * PAIR, LQ = PAIRS ? 2 * LA : LA;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     // XCD b % 8 takes a contiguous range of the units (split outermost): neighbouring units share operand panels in its L2
@@ -139,7 +141,7 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
     const int64_t a_pitch = a.a_slab ? 64 : a.lda * 2, b_pitch = a.b_slab ? 64 : a.ldb * 2;
     const int64_t a_kstep = a.a_slab ? a.M * 64 : SROW, b_kstep = a.b_slab ? (second ? a.b_rows1 : a.b_rows) * 64 : SROW;
     const int lr = lane >> 2;                   // row of the load's 16
-    uint32_t oa[LA], ob[LB];
+    uint32_t oa[LQ], ob[LB];
     const char* abase = (const char*)a.A + (a.a_idx ? (int64_t)0 : row0 * a_pitch);
     // This wavefront's 32 weight rows: which matrix, and from which row of it (one address for all epilogues, by selects)
     const int rw = wave * 32;
@@ -149,20 +151,21 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
     const int brow0 = (silu_b ? (rw & 63) : rw) + st.col0 - (second ? a.n_split : 0) - (upper ? a.N / 2 : 0);
     const char* bbase = (const char*)(from_b1 ? a.B1 : a.B0) + (int64_t)brow0 * b_pitch;
 #pragma unroll
-    for (int q = 0; q < LA; ++q) {
-        const int r = wave * (TM / 4) + q * 16 + lr;
+    for (int q = 0; q < LQ; ++q) {
+        const int r = PAIRS ? wave * (TM / 4) + q * 8 + (lane >> 3) : wave * (TM / 4) + q * 16 + lr;
         int64_t grow = row0 + r;
         if (grow >= a.M) grow = a.M - 1;        // duplicates of the last row are never stored
         const int64_t srow = a.a_idx ? (int64_t)a.a_idx[grow] : grow - row0;
-        oa[q] = (uint32_t)(srow * a_pitch + (((lane & 3) ^ ((r >> 2) & 3)) << 4));
+        oa[q] = (uint32_t)(srow * a_pitch + (PAIRS ? ((lane & 7) ^ (lane >> 3)) << 4 : ((lane & 3) ^ ((r >> 2) & 3)) << 4));
     }
+    const uint32_t second_half = ((lane & 7) ^ (lane >> 3)) >= 4 ? SROW : 0;   // this lane's piece of a pair of slabs lies in the second one
 #pragma unroll
     for (int q = 0; q < LB; ++q) {
         const int r = wave * 32 + q * 16 + lr;
         ob[q] = (uint32_t)((int64_t)(q * 16 + lr) * b_pitch + (((lane & 3) ^ ((r >> 2) & 3)) << 4));
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
-    const uint32_t lds_a = lds0 + wave * (TM / 4) * SROW, lds_b = lds0 + A_BYTES + wave * 32 * SROW;
+    const uint32_t lds_a = lds0 + wave * (TM / 4) * (PAIRS ? 2 * SROW : SROW), lds_b = lds0 + (PAIRS ? B_RING : A_BYTES) + wave * 32 * SROW;
     const int nk_all = a.K / SBK;
     const int nk = nk_all / ksplit + (split < nk_all % ksplit ? 1 : 0);
     const int kbeg = split * (nk_all / ksplit) + (split < nk_all % ksplit ? split : nk_all % ksplit);
@@ -172,13 +175,17 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
     // of 130 rows, with these loads / without / from ONCE_BYTES on: hidden size 512, 16 layers 139.0 / 136.0 / 136.2; 1024, 24 layers
     // 152.0 / 156.4 / 151.2, 4 layers 151.0 / 144.7 / 148.3; 2048, 8 layers 171.9 / 178.2 / 172.1, 1 layer 172.1 / 164.8 / 171.5).
     const bool once = nM == 1 && (int64_t)a.N * a.K * (a.epi == EPI_SILU_MUL ? 4 : 2) >= ONCE_BYTES;
-    auto issue = [&](int kt, int stage) {
+    auto issue_b = [&](int kt, uint32_t at) {
         const int64_t ks = kbeg + kt;
 #pragma unroll
         for (int q = 0; q < LB; ++q) {
-            if (once) dma16s_nt(ob[q], bbase + ks * b_kstep, lds_b + stage * STAGE + q * 1024);
-            else dma16s(ob[q], bbase + ks * b_kstep, lds_b + stage * STAGE + q * 1024);
+            if (once) dma16s_nt(ob[q], bbase + ks * b_kstep, lds_b + at + q * 1024);
+            else dma16s(ob[q], bbase + ks * b_kstep, lds_b + at + q * 1024);
         }
+    };
+    auto issue = [&](int kt, int stage) {
+        const int64_t ks = kbeg + kt;
+        issue_b(kt, stage * STAGE);
 #pragma unroll
         for (int q = 0; q < LA; ++q) dma16s(oa[q], abase + ks * a_kstep, lds_a + stage * STAGE + q * 1024);
     };
@@ -191,23 +198,7 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // All stages in flight; a slab's fragments are read while the slab before is multiplied, so its stage is free again when its
-    // multiplication begins.
-    const int npre = nk < NST ? nk : NST;
-    for (int t = 0; t < npre; ++t) issue(t, t);
     bf16x8 fa[2][2 * MI], fb[2][4];
-    auto fragments = [&](int buf, int stage) {
-        const char* sa = smem + stage * STAGE;
-        const char* sb = sa + A_BYTES;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            fb[buf][j] = *reinterpret_cast<const bf16x8*>(sb + small_off((j >> 1) * st.jstride + wn * st.wstride + (j & 1) * 16 + l16, lq));
-#pragma unroll
-        for (int i = 0; i < 2 * MI; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(sa + small_off(wm * (TM / 2) + i * 16 + l16, lq));
-    };
-    if (npre == NST) { SPTS_WAIT_VMCNT((NST - 1) * PER); } else { SPTS_WAIT_VMCNT(0); }
-    __syncthreads();
-    fragments(0, 0);
     auto multiply = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < 2 * MI; ++i)
@@ -225,6 +216,80 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
         }
         __builtin_amdgcn_sched_barrier(0);
     };
+    if constexpr (PAIRS) {
+        const int npairs = (nk + 1) >> 1;
+        auto issue_a = [&](int p, uint32_t at) {
+            const uint32_t back = 2 * p + 1 < nk ? 0 : second_half;   // a pair whose second slab is not there: the first one twice
+#pragma unroll
+            for (int q = 0; q < LQ; ++q) dma16s(oa[q] - back, abase + (int64_t)(kbeg + 2 * p) * SROW, lds_a + at + q * 1024);
+        };
+        // slot / stage of the next pair and slab to load and of the slab whose fragments are next, in bytes
+        uint32_t a_in = 0, b_in = 0, a_out = 0, b_out = 0;
+        auto next_b = [](uint32_t& at) { at = (at + SBN * SROW) & (SMALL_STAGES * SBN * SROW - 1); };
+        for (int t = 0; t < NST && t < nk + 1; ++t) {   // pair p is loaded before B's slab 2 p + 1 (t = nk: the pair of an odd last slab)
+            if ((t & 1) && t / 2 < npairs) issue_a(t / 2, t / 2 * PAIR);
+            if (t < nk) issue_b(t, t * SBN * SROW);
+        }
+        int pair = 2;   // the next pair to load: its slot is free after its predecessor's second slab
+        const uint32_t fa0 = (wm * (TM / 2) + l16) * 2 * SROW + ((lq ^ (l16 & 7)) << 4);
+        const uint32_t fb0 = B_RING + (uint32_t)small_off(wn * st.wstride + l16, lq);
+        const uint32_t fbj = st.jstride * SROW;
+        auto fragments = [&](int buf, int odd) {   // of slab `odd` of the pair at a_out, and of b_out
+            const char* sb = smem + fb0 + b_out;
+            const char* sa = smem + a_out + (odd ? fa0 ^ 64u : fa0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) fb[buf][j] = *reinterpret_cast<const bf16x8*>(sb + (j >> 1) * fbj + (j & 1) * 16 * SROW);
+#pragma unroll
+            for (int i = 0; i < 2 * MI; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(sa + i * 16 * 2 * SROW);
+            next_b(b_out);
+            if (odd) a_out ^= PAIR;
+        };
+        if (nk >= NST) { SPTS_WAIT_VMCNT(3 * LB + LQ); } else { SPTS_WAIT_VMCNT(0); }
+        __syncthreads();
+        fragments(0, 0);
+        // Slab kt from one fragment set while the other takes kt + 1.  Loads that may be outstanding before that, as they were issued after those of kt + 1: B of
+        // kt + 2 and kt + 3 and, with kt even, the pair of kt + 2.
+        int kt = 0;
+        auto step = [&](int odd, bool end) {
+            if (!end && !odd) { SPTS_WAIT_VMCNT(2 * LB + LQ); }
+            else if (!end || kt + 3 < nk) { SPTS_WAIT_VMCNT(2 * LB); }
+            else if (kt + 2 < nk) { SPTS_WAIT_VMCNT(LB); }
+            else { SPTS_WAIT_VMCNT(0); }
+            __syncthreads();
+            if (odd && pair < npairs) { issue_a(pair++, a_in); a_in ^= PAIR; }
+            if (kt + NST < nk) { issue_b(kt + NST, b_in); next_b(b_in); }
+            fragments(odd ^ 1, odd ^ 1);
+            multiply(odd);
+            interleave();
+            ++kt;
+        };
+        while (kt + 4 < nk) {   // in here every load that the counts allow for has been issued
+            step(0, false);
+            step(1, false);
+        }
+        while (kt + 1 < nk) {
+            step(0, true);
+            if (kt + 1 < nk) step(1, true);
+        }
+        if (nk & 1) multiply(0);
+        else multiply(1);
+    } else {
+    // All stages in flight; a slab's fragments are read while the slab before is multiplied, so its stage is free again when its
+    // multiplication begins.
+    const int npre = nk < NST ? nk : NST;
+    for (int t = 0; t < npre; ++t) issue(t, t);
+    auto fragments = [&](int buf, int stage) {
+        const char* sa = smem + stage * STAGE;
+        const char* sb = sa + A_BYTES;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            fb[buf][j] = *reinterpret_cast<const bf16x8*>(sb + small_off((j >> 1) * st.jstride + wn * st.wstride + (j & 1) * 16 + l16, lq));
+#pragma unroll
+        for (int i = 0; i < 2 * MI; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(sa + small_off(wm * (TM / 2) + i * 16 + l16, lq));
+    };
+    if (npre == NST) { SPTS_WAIT_VMCNT((NST - 1) * PER); } else { SPTS_WAIT_VMCNT(0); }
+    __syncthreads();
+    fragments(0, 0);
     // Slab kt from one fragment set while the other takes slab kt + 1: this wavefront's loads of that have landed when only the `left`
     // slabs' behind it are outstanding; the barrier publishes everyone's and says that slab kt's stage has been read.
     int kt = 0;
@@ -255,6 +320,7 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
         for (int j = 0; j < 4; ++j) fb[0][j] = fb[1][j];
     }
     multiply(0);
+    }
 
     // ---- lane: output row l16 of its quarter block, columns 4 * lq + e
     if (ksplit > 1) {
@@ -313,9 +379,17 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
     }
 }
 
-template <int TM>
+// Pairs are for products that move more than they wait: shares of at least 96 slabs, tiles of 64 or 192 rows.  Gate/up of 64 / 133 / 333 / 700 rows
+// of the 8B shape (128 slabs, slab-major weights) 44.4 -> 41.5, 60.2 -> 57.7, 108.9 -> 91.9, 190.2 -> 175.2 us.  A shorter share's first loads and last slabs
+// cost what the lines save (4096 x 4096, 133 rows, 32 slabs 20.0 -> 21.3; 700 rows, 64 slabs 39.8 -> 40.8), and so it is with tiles of 128
+// rows, where a slot has two iterations for its loads but half the work (gate/up of 133 rows 65.7 -> 69.6, 700 of 4096 x 4096 40.4 -> 44.2).
+template <int TM> __host__ __device__ constexpr bool small_pairs(const GemmArgs& a, int ksplit) {
+    return TM != 128 && !a.a_slab && a.K / SBK / ksplit >= 96;
+}
+
+template <int TM, bool PAIRS>
 __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_kernel(GemmArgs a, int nM, int nN, int ksplit) {
-    small_product<TM>(a, nM, nN, ksplit, blockIdx.x);
+    small_product<TM, PAIRS>(a, nM, nN, ksplit, blockIdx.x);
 }
 
 // Independent products of one tile height in one launch: product i has the blocks from first[i] on (multiples of 8: a block's XCD stays what
@@ -327,7 +401,13 @@ __global__ void __launch_bounds__(256, TM == 64 ? 3 : 2) gemm_small_group_kernel
     int i = 0;
 #pragma unroll
     for (int q = 1; q < GEMM_GROUP_MAX; ++q) i += (int)blockIdx.x >= g.first[q] ? 1 : 0;
-    small_product<TM>(g.a[i], g.nM[i], g.nN[i], g.ksplit[i], blockIdx.x - g.first[i]);
+    if constexpr (TM != 128) {
+        if (small_pairs<TM>(g.a[i], g.ksplit[i])) {
+            small_product<TM, true>(g.a[i], g.nM[i], g.nN[i], g.ksplit[i], blockIdx.x - g.first[i]);
+            return;
+        }
+    }
+    small_product<TM, false>(g.a[i], g.nM[i], g.nN[i], g.ksplit[i], blockIdx.x - g.first[i]);
 }
 
 // Second pass of a split product: one thread per fragment quad pair (j = 0, 1), splits summed in order.
@@ -472,9 +552,18 @@ static hipError_t launch_small_t(const GemmArgs& a, int ksplit, bool finish, hip
     if (units > ((int64_t)1 << 30)) return hipErrorInvalidValue;
     constexpr int lds = SMALL_STAGES * small_stage_bytes<TM>();
     static_assert(lds >= TM * SBN * 2, "the finished tile is staged in the ring");
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_small_kernel<TM>), lds);
-    if (e != hipSuccess) return e;
-    gemm_small_kernel<TM><<<dim3((unsigned)((units + 7) / 8 * 8)), dim3(256), lds, s>>>(a, nM, nN, ksplit);
+    const dim3 grid((unsigned)((units + 7) / 8 * 8));
+    hipError_t e;
+    if constexpr (TM != 128) {
+        if (small_pairs<TM>(a, ksplit)) {
+            if ((e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_small_kernel<TM, true>), lds)) != hipSuccess) return e;
+            gemm_small_kernel<TM, true><<<grid, dim3(256), lds, s>>>(a, nM, nN, ksplit);
+        }
+    }
+    if (!small_pairs<TM>(a, ksplit)) {
+        if ((e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_small_kernel<TM, false>), lds)) != hipSuccess) return e;
+        gemm_small_kernel<TM, false><<<grid, dim3(256), lds, s>>>(a, nM, nN, ksplit);
+    }
     if ((e = hipGetLastError()) != hipSuccess || ksplit <= 1 || !finish) return e;
     const int64_t pairs = (int64_t)nM * nN * (TM * SBN / 8);
     small_finish_kernel<TM><<<dim3((unsigned)(pairs / 256)), dim3(256), 0, s>>>(a, nM, nN, ksplit);

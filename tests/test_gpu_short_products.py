@@ -177,3 +177,27 @@ def test_unsplit_sums_are_those_of_the_256_wide_tiles(torch, k):
         a.C = got.data_ptr()
         assert I.launch_small(a, tm, 1, stream) == 0
         assert torch.equal(got, want), tm
+
+
+@pytest.mark.parametrize("gather", [True, False])
+@pytest.mark.parametrize("slabs,ksplit", [(95, 1), (96, 1), (97, 1), (98, 1), (99, 1), (101, 1), (193, 2), (195, 2), (292, 3)])
+@pytest.mark.parametrize("tm", [64, 192])
+def test_long_shares_of_row_major_rows(torch, monkeypatch, tm, slabs, ksplit, gather):
+    """Two slabs of A at a time: shares just below and from the length on that takes them, even and odd (a last pair of one slab, the end of the last
+    row at the end of the operand), shares that begin in the middle of a line."""
+    monkeypatch.setitem(globals(), "K", 32 * slabs)
+    for M in _rows(tm):
+        p = Product(torch, M, 384, M, gather, False, True, second=384)
+        c = p.out(M, 384)
+        p.args.epi, p.args.C, p.args.ldc = I.EPI_SILU_MUL, c.data_ptr(), 384
+        p.run(tm, ksplit)
+        (g, u), (dg, du) = p.sums, p.slack
+        silu = g * torch.sigmoid(g)
+        _close(torch, c[:M], silu * u, 1.1 * dg * u.abs() + du * silu.abs() + dg * du + 2.0 ** -20 * (silu * u).abs())
+        assert torch.isnan(c[M:]).all()
+        p = Product(torch, M, 256, M + 1, gather, False, False)
+        c = p.out(M, 256)
+        p.args.C, p.args.ldc = c.data_ptr(), 256
+        p.run(tm, ksplit)
+        _close(torch, c[:M], p.sums[0], p.slack[0])
+        assert torch.isnan(c[M:]).all()
