@@ -1273,13 +1273,14 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_mean_kernel(const T* __rest
     }
 }
 
-// Rows of at most 64 * KPT values: one wavefront per row, the row read once into registers.  The key of the k-th largest |value|
-// (15 significant bits in bf16, 31 in fp32) is built from its top bit down: a bit stays set when at least k keys reach it.
+// Rows of at most 64 * KPT values: one wavefront per row, the row read once into registers.  The key of the k-th largest |value| lies between a key that k keys
+// reach and one that fewer do, and the two close in: first to either side of the same quantile of 256 of the keys, as far as its error and the usual slope of such
+// a row suggest and then twice as far each time, after that to their middle.  What is found does not depend on the guesses.
 // Counting is one compare per key whose lane mask is summed on the scalar unit, so there are no histograms, no LDS and no
 // barrier.  The scalar unit is what that runs out of (two instructions a key against one), so every third key is counted on the
-// vector unit instead (one more), lane by lane.  Bound: 15 compares per key (26 us for 14336 rows of 4096) and one read of the row (20
-// us).  Measured there: 283 us with the workgroup-per-row kernel above (two histogram passes over 1024-lane strides), 84 with all
-// keys on the scalar unit, 76 here.
+// vector unit instead (one more), lane by lane.  Bound: the counts, and one read of the row (20 us for 14336 rows of 4096).  Measured there: 283 us with
+// the workgroup-per-row kernel above (two histogram passes over 1024-lane strides), 72 with a count for each of a key's 15 bits, 45 here (1000
+// values to a row of 18944: 26).
 template <typename T, int KPT>
 __global__ void __launch_bounds__(256) topk_mean_wave_kernel(const T* __restrict__ vals, int64_t ld, int64_t rows, int n, int k, int wide,
                                                              float* __restrict__ out) {
@@ -1313,18 +1314,47 @@ __global__ void __launch_bounds__(256) topk_mean_wave_kernel(const T* __restrict
             key[j] = i < n ? key_of(sizeof(T) == 2 ? (uint32_t)reinterpret_cast<const uint16_t*>(row)[i] : reinterpret_cast<const uint32_t*>(row)[i]) : 0u;
         }
     }
-    uint32_t t = 0;
-    for (int b = BITS - 1; b >= 0; --b) {
-        const uint32_t cand = t | (1u << b);
+    auto reach = [&](uint32_t c) {   // keys that reach c
         int cnt = 0, mine = 0;
 #pragma unroll
         for (int j = 0; j < KPT; ++j) {
-            if (j % 3 == 2) mine += key[j] >= cand ? 1 : 0;
-            else cnt += (int)__popcll(__ballot(key[j] >= cand));
+            if (j % 3 == 2) mine += key[j] >= c ? 1 : 0;
+            else cnt += (int)__popcll(__ballot(key[j] >= c));
         }
+        return cnt + (int)wave_reduce_u32((uint32_t)mine, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+    };
+    uint32_t guess = 0;
+    {
+        const int rank = (int)(((int64_t)k * 4 + KPT - 1) / KPT);   // of 256 keys out of 64 KPT
+        for (int b = BITS - 1; b > BITS - 16; --b) {
+            const uint32_t c = guess | (1u << b);
+            int cnt = 0;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
-        if (cnt + mine >= k) t = cand;
+            for (int q = 0; q < 4; ++q) cnt += (int)__popcll(__ballot(key[KPT / 4 * q] >= c));
+            if (cnt >= rank) guess = c;
+        }
+    }
+    uint32_t t = 0, end = 1u << BITS, c = guess > 0 ? guess : 1u, step = 0;   // k keys or more reach t, fewer end
+    int at_t = 64 * KPT + 1;   // keys that reach t (0: all)
+    bool up = false, closing = false;
+    while (end - t > 1 && at_t != k) {
+        const int cnt = reach(c);
+        const bool enough = cnt >= k;
+        if (enough) { t = c; at_t = cnt; } else end = c;
+        if (step == 0) {   // twice as far as it is where keys thin out to a third within an octave
+            const float octaves = fminf((float)(enough ? cnt - k : k - cnt) / (float)k, 64.f);
+            step = (uint32_t)(octaves * (float)(2 << (BITS - 8))) + (2u << (BITS - 15));   // (0.7 / 1 / 1.4 octaves for that: 46 / 47 / 46 us, two 45)
+            up = enough;
+        } else closing = closing || up != enough;
+        const uint32_t room = end - t;
+        if (closing || step >= room) { c = t + room / 2; closing = true; }
+        else { c = up ? t + step : end - step; step *= 2; }
+    }
+    if (at_t == k && end - t > 1) {   // exactly k keys reach t: the smallest of them
+        uint32_t mn = 0xFFFFFFFFu;
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) mn = min(mn, key[j] >= t ? key[j] : 0xFFFFFFFFu);
+        t = wave_reduce_u32(mn, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return min(a, b); });
     }
     auto value = [](uint32_t q) { return __uint_as_float(sizeof(T) == 2 ? q << 16 : q); };
     float s = 0.f;

@@ -72,3 +72,8 @@ def launch_small(a, tm, ksplit, stream):
 
 def launch_wide(a, stream):
     return _fn("_ZN4spts16launch_gemm_mfmaERKNS_8GemmArgsEP12ihipStream_t", C.c_int, _ARGS, C.c_void_p)(a, stream)
+
+
+def topk_mean(vals, ld, rows, n, k, out, bf16, stream):
+    return _fn("_ZN4spts16launch_topk_meanEPKvllllPfbP12ihipStream_t", C.c_int, C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_int64, C.c_void_p, C.c_bool,
+               C.c_void_p)(vals, ld, rows, n, k, out, bf16, stream)

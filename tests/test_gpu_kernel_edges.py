@@ -183,6 +183,25 @@ def test_channel_importance_lengths(torch, dtype, T):
         assert np.max(np.abs(imp.cpu().numpy() - ref)) <= H.TOL[dtype]["score"] * np.max(np.abs(ref)), k
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 5, 64, 511, 513, 1500, 2048, 4096])
+def test_topk_mean_of_any_values(torch, dtype, n):
+    """Rows whose quantiles a sample of them tells well, badly and not at all: smooth, few values, steps, many octaves, ascending, all zero, infinite."""
+    from tests import internal as I
+    rng = np.random.default_rng(n)
+    z = rng.standard_normal(n)
+    rows = [z, np.abs(z) ** 8, np.zeros(n), np.full(n, -0.75), np.where(rng.random(n) < 0.3, 2.0, -1.0), np.sort(z), -np.sort(-np.abs(z)), np.exp(20 * z),
+            np.where(np.arange(n) % 64 == 5, 9.0, 1e-3 * z), np.where(np.arange(n) < n // 2, 0.0, z), np.round(3 * z), np.where(rng.random(n) < 0.01, np.inf, z)]
+    v = torch.from_numpy(np.stack(rows).astype(np.float32)).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32).contiguous()
+    host = np.sort(np.abs(v.float().cpu().numpy().astype(np.float64)), axis=1)[:, ::-1]
+    for k in sorted({1, 2, max(1, n // 50), max(1, n // 5), max(1, n // 2), max(1, n - 1), n} & set(range(1, n + 1))):
+        out = torch.full((len(rows),), -1.0, dtype=torch.float32, device="cuda")
+        assert I.topk_mean(v.data_ptr(), n, len(rows), n, k, out.data_ptr(), dtype == "bf16", torch.cuda.current_stream().cuda_stream) == 0
+        ref = host[:, :k].mean(1)
+        # a sum of k fp32 terms of one sign in any order, a product and a quotient
+        assert np.allclose(out.cpu().numpy(), ref, rtol=(k + 4) * 2.0 ** -24, atol=0), k
+
+
 # ------------------------------------------------------------------------------------------ TopK of long rows of a batch
 @pytest.mark.parametrize("n", [32772, 65536, 100004, 131068, 131072, 131076])
 def test_long_row_topk_patterns(torch, n):
