@@ -452,7 +452,7 @@ int gather_rows_maps(spts_ctx* c, const void* in, const int32_t* idx, void* out,
 // (map_out[j] = map_in[idx_out[j]] with it where asked for)
 int run_topk(spts_ctx* c, const float* scores, int64_t N, int64_t k, int protect_last, int32_t* idx_out, const int32_t* map_in = nullptr,
              int32_t* map_out = nullptr) {
-    if (N <= TOPK_REG_MAX_N) {
+    if (N <= TOPK_ONE_MAX_N) {
         SPTS_HIP(c, launch_topk(scores, N, k, protect_last, idx_out, 1, c->stream, TopkSegments{nullptr, nullptr, nullptr, 0}, TopkMap{map_in, map_out}));
         return SPTS_OK;
     }

@@ -210,7 +210,10 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
 // read was written earlier in the same call); calls sharing a scratch must not overlap.  N <= TOPK_MULTI_MAX_N.
 constexpr int TOPK_MULTI_MAX_WG = 128;
 constexpr int64_t TOPK_MULTI_MAX_N = (int64_t)TOPK_MULTI_MAX_WG * 8192;
-constexpr int64_t TOPK_REG_MAX_N = 32768;     // one workgroup with the keys in registers; one row of 32768 20.1 us, over the chip 22 (20001: 14.4 and 20.5)
+constexpr int64_t TOPK_REG_MAX_N = 32768;     // one workgroup with the keys in registers
+// A single row of up to this many scores takes one workgroup, longer ones the chip: compaction of 22937 rows 69 us both, of 30000 85 over the chip and 90; layers of 20011
+// and 32768 rows 1930 and 6850 us with one workgroup, 1950 and 6830 over the chip.  (Calls by themselves wait for five launches on the host and say 17 and 25 us at 22937.)
+constexpr int64_t TOPK_ONE_MAX_N = 24576;
 constexpr size_t TOPK_MULTI_SCRATCH_BYTES = 2 * (size_t)TOPK_MULTI_MAX_WG * 256 * 4 + (size_t)TOPK_MULTI_MAX_WG * 4 + 64;
 // device address of this GPU's file-scope scratch array of TOPK_MULTI_SCRATCH_BYTES (looked up once per device, then cached)
 hipError_t topk_static_scratch(void** out);
