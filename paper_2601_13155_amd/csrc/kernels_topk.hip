@@ -1417,6 +1417,7 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
         else if (N <= 8192) SPTS_TOPK_REG(8, 16);
         else if (N <= 12288) SPTS_TOPK_REG(12, 16);
         else if (N <= 16384) SPTS_TOPK_REG(16, 16);
+        else if (N <= 20480) SPTS_TOPK_REG(20, 16);
         else if (N <= 24576) SPTS_TOPK_REG(24, 16);
         else SPTS_TOPK_REG(32, 16);
 #undef SPTS_TOPK_REG

@@ -211,9 +211,10 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
 constexpr int TOPK_MULTI_MAX_WG = 128;
 constexpr int64_t TOPK_MULTI_MAX_N = (int64_t)TOPK_MULTI_MAX_WG * 8192;
 constexpr int64_t TOPK_REG_MAX_N = 32768;     // one workgroup with the keys in registers
-// A single row of up to this many scores takes one workgroup, longer ones the chip: compaction of 22937 rows 69 us both, of 30000 85 over the chip and 90; layers of 20011
-// and 32768 rows 1930 and 6850 us with one workgroup, 1950 and 6830 over the chip.  (Calls by themselves wait for five launches on the host and say 17 and 25 us at 22937.)
-constexpr int64_t TOPK_ONE_MAX_N = 24576;
+// A single row of up to this many scores (20 to a lane of 16 wavefronts) takes one workgroup, longer ones the chip.  The two TopK of a layer with one workgroup / over the
+// chip: 20011 rows (one probe row) 40 / 50 us, 18001 (64) 52 / 52, 23000 57 / 54, 32768 71 / 55; compaction of 18000 rows 48 / 51, 30000 90 / 85.  (Calls by
+// themselves wait for five launches on the host and say 17 and 25 us at 22937.)
+constexpr int64_t TOPK_ONE_MAX_N = 20480;
 constexpr size_t TOPK_MULTI_SCRATCH_BYTES = 2 * (size_t)TOPK_MULTI_MAX_WG * 256 * 4 + (size_t)TOPK_MULTI_MAX_WG * 4 + 64;
 // device address of this GPU's file-scope scratch array of TOPK_MULTI_SCRATCH_BYTES (looked up once per device, then cached)
 hipError_t topk_static_scratch(void** out);

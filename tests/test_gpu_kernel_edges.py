@@ -301,7 +301,7 @@ def test_long_row_topk_padding_is_below_every_score(torch, n):
                 assert np.array_equal(got[b * k:(b + 1) * k], ref), (b, k, protect)
 
 
-@pytest.mark.parametrize("n", [256, 257, 512, 513, 1024, 1025, 2048, 2049, 3072, 3073, 4096, 4097, 6144, 6145, 8192, 8193, 12288, 12289, 16384, 16385, 24576, 24577,
+@pytest.mark.parametrize("n", [256, 257, 512, 513, 1024, 1025, 2048, 2049, 3072, 3073, 4096, 4097, 6144, 6145, 8192, 8193, 12288, 12289, 16384, 16385, 20480, 20481, 24576, 24577,
                                32767, 32768])
 def test_register_topk_edges(torch, n):
     """The largest and smallest rows of every workgroup size of the register-resident kernel: thresholds among more than 64 neighbouring
