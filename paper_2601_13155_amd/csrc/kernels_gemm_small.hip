@@ -380,7 +380,7 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
 }
 
 // Pairs are for products that move more than they wait: shares of at least 96 slabs, tiles of 64 or 192 rows.  Gate/up of 64 / 133 / 333 / 700 rows
-// of the 8B shape (128 slabs, slab-major weights) 44.4 -> 41.5, 60.2 -> 57.7, 108.9 -> 91.9, 190.2 -> 175.2 us.  A shorter share's first loads and last slabs
+// of the 8B shape (128 slabs, slab-major weights) 44.4 -> 41.5, 60.2 -> 54.8, 108.9 -> 90.9, 190.2 -> 171.1 us.  A shorter share's first loads and last slabs
 // cost what the lines save (4096 x 4096, 133 rows, 32 slabs 20.0 -> 21.3; 700 rows, 64 slabs 39.8 -> 40.8), and so it is with tiles of 128
 // rows, where a slot has two iterations for its loads but half the work (gate/up of 133 rows 65.7 -> 69.6, 700 of 4096 x 4096 40.4 -> 44.2).
 template <int TM> __host__ __device__ constexpr bool small_pairs(const GemmArgs& a, int ksplit) {
