@@ -190,8 +190,8 @@ __device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t v, uint32_t identit
 }
 
 // Register-resident variant: N <= 64 * KPT * W, one workgroup of W wavefronts per problem.  Lane keeps keys[j] = key of element
-// lo + 64*j + lane, lo = 64*KPT*wave; slots at or beyond N hold key 0, which no
-// threshold reaches (scores have keys from 1 on).
+// lo + 64*j + lane, lo = 64*KPT*wave; slots at or beyond N hold key 0.  So does a score that is the NaN with every bit set: the search counts keys that
+// reach a value above 0 only, and where the threshold itself is 0 an empty slot is the last of the equal keys, behind the k <= N selected.
 // The threshold is searched for between the row's smallest and largest key: a round counts the keys that reach the middle (a
 // compare per key, summed on the scalar unit -- of 12 and more keys every third on the vector unit, since the scalar one runs out --, one LDS
 // atomic per wavefront, one barrier) and keeps one half, until that holds at most 64 keys or a single value.  Those keys go to LDS, and
@@ -243,6 +243,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 
     uint32_t keys[KPT];
     if (tid < ROUNDS) count[tid] = 0;
     if (tid == 0) cands = 0;
+    if (tid < 64) cand[tid] = 0;
     {
         float v[KPT];
         uint32_t mn = 0xFFFFFFFFu, mx = 0u;
@@ -252,7 +253,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 
             for (int j = 0; j < KPT; ++j) v[j] = p[64 * j];
 #pragma unroll
             for (int j = 0; j < KPT; ++j) {
-                keys[j] = max(order_key(v[j]), 1u);
+                keys[j] = order_key(v[j]);
                 mn = min(mn, keys[j]);
                 mx = max(mx, keys[j]);
             }
@@ -265,7 +266,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 
 #pragma unroll
             for (int j = 0; j < KPT; ++j) {
                 const int i = lo + 64 * j + lane;
-                const uint32_t key = max(order_key(v[j]), 1u);
+                const uint32_t key = order_key(v[j]);
                 const bool in = i < n && i != last;
                 keys[j] = in ? key : 0u;
                 mn = min(mn, in ? key : 0xFFFFFFFFu);
@@ -321,12 +322,12 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8, 
         }
         T = lo_key;
         if (width > 0) {
-            const uint32_t first = lo_key;
+            const uint32_t first = lo_key, above = max(first, 1u), span = width - (above - first);   // (distance 0 from key 0 is in cand already)
 #pragma unroll
             for (int j = 0; j < KPT; ++j)
-                if (keys[j] - first <= width) cand[atomicAdd(&cands, 1) & 63] = keys[j] - first;
+                if (keys[j] - above <= span) cand[atomicAdd(&cands, 1) & 63] = keys[j] - first;
             __syncthreads();
-            const uint32_t d = lane < c_lo - c_hi ? cand[lane] : 0u;
+            const uint32_t d = cand[lane];
             const int rank = want - c_hi;
             uint32_t t = 0;
             for (int bit = 31 - __builtin_clz(width); bit >= 0; --bit) {

@@ -323,6 +323,50 @@ def test_register_topk_edges(torch, n):
                 assert np.array_equal(got[b * k:(b + 1) * k], orc.topk_select(rows[b], k, protect)), (b, k, protect)
 
 
+@pytest.mark.parametrize("n", [2, 64, 300, 512, 1000, 2049, 6144, 20001, 32768])
+def test_register_topk_orders_the_smallest_keys(torch, n):
+    """NaNs with the sign bit and all or nearly all other bits set have the keys 0, 1 and 2, the same as empty slots or next to them: they are
+    told apart, and an empty slot is never selected.  Whole rows of them, a few and many among scores, equal rows and segments of all lengths."""
+    rng = np.random.default_rng(n)
+    nans = np.array([0xFFFFFFFF, 0xFFFFFFFE, 0xFFFFFFFD], dtype=np.uint32)
+    z = rng.standard_normal(n).astype(np.float32).view(np.uint32)
+    low = np.where(rng.random(n) < 0.5, nans[0], nans[1])
+    few = z.copy(); few[rng.permutation(n)[:min(n, 40)]] = rng.choice(nans, min(n, 40))
+    rows = np.stack([low, low[::-1], np.full(n, nans[0]), rng.choice(nans, n), few, np.where(rng.random(n) < 0.7, rng.choice(nans, n), z),
+                     np.where(np.arange(n) % 7 == 3, nans[1], nans[0])]).astype(np.uint32)
+    keys = np.where(rows >> 31, ~rows, rows | np.uint32(0x80000000)).astype(np.int64)
+
+    def expected(key, k, protect):
+        key = key.copy()
+        if protect:
+            key[-1] = 0xFFFFFFFF
+        return np.sort(np.argsort(-key, kind="stable")[:k])
+
+    sd = torch.from_numpy(rows.view(np.int32)).cuda().view(torch.float32)
+    ctx = runtime.make_context(synth.TINY, len(rows) * n, 1, 1, synth.TINY.Dff)
+    for k in sorted({1, 2, max(1, n // 3), n - n // 5, n - 1, n} & set(range(1, n + 1))):
+        for protect in (0, 1):
+            out = torch.full((len(rows) * k + 4,), -7, dtype=torch.int32, device="cuda")
+            ctx.spts_select_topk_batched(sd, n, k, protect, len(rows), out)
+            got = out.cpu().numpy()
+            assert (got[-4:] == -7).all()
+            for b in range(len(rows)):
+                assert np.array_equal(got[b * k:(b + 1) * k], expected(keys[b], k, protect)), (b, k, protect)
+    lens = [n, 1, n - n // 3, n // 2 + 1, min(n, 65), min(n, 3), n - 1 or 1]   # segment b: a beginning of row b
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    flat = np.concatenate([rows[b, :m] for b, m in enumerate(lens)])
+    for part in (0.3, 1.0):
+        ks = np.array([max(1, int(part * m)) for m in lens], dtype=np.int64)
+        to = np.concatenate([[0], np.cumsum(ks)]).astype(np.int64)
+        out = torch.full((int(to[-1]) + 4,), -7, dtype=torch.int32, device="cuda")
+        dev = [torch.from_numpy(a).cuda() for a in (offs, ks, to)]
+        ctx.spts_select_topk_segmented(torch.from_numpy(flat.view(np.int32)).cuda().view(torch.float32), dev[0], dev[1], dev[2], len(lens), n, 1, out)
+        got = out.cpu().numpy()
+        assert (got[-4:] == -7).all()
+        for b, m in enumerate(lens):
+            assert np.array_equal(got[to[b]:to[b + 1]], expected(keys[b, :m], int(ks[b]), 1)), (part, b)
+
+
 def _best_us(torch, call, repeats=7, per=5):
     """Shortest time of a call among `repeats` runs of `per` calls each."""
     call()
