@@ -20,7 +20,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Wavefronts per workgroup: eight up to d = 64, four beyond (up to 512 registers each).  At d = 64 the attention then keeps 3 registers in
 // scratch memory and reloads them in the key loop; four wavefronts without spills are slower (attention of 256 queries over 512 keys
 // 23.9 -> 26.6 us, dense layer of 6000 rows 1.21 -> 1.41 ms).  At d = 256 a lane's row pieces exceed 512 registers: 1.3 KB of scratch per lane
-// in the attention, 0.45 KB in the two probe kernels.
+// in the attention, 0.45 KB in the two probe kernels (the attention's 134 KB of LDS cost nothing: registers allow one workgroup per CU).
 template <int D> constexpr int f32_waves() { return D <= 64 ? 8 : 4; }
 constexpr float LOG2E = 1.4426950408889634f;
 
@@ -100,8 +100,13 @@ __global__ void __launch_bounds__(64 * f32_waves<D>()) attention_f32_kernel(Attn
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
 
+    // The block's loads go out beside the one that says whether it is visible at all, where they leave registers: beyond d = 64 that costs more
+    // spills (d = 256) and a worse schedule than the wait (attention of 6000 rows, d = 16 / 64 / 128 / 256, waiting and not: 1282 -> 1230, 626 -> 580,
+    // 924 -> 931, 1145 -> 2180 us).
+    constexpr bool LOAD_FIRST = D <= 64;
     for (int64_t j0 = wave * 32; j0 < a.Mk; j0 += 32 * GW) {
         const int first = a.kpos[j0];
+        if (!LOAD_FIRST && first > qp_last) break;   // ascending positions: nothing visible from here on
         const int64_t jk = j0 + l32 < a.Mk ? j0 + l32 : a.Mk - 1;
         f32x4 kf[NS];
 #pragma unroll
@@ -112,7 +117,7 @@ __global__ void __launch_bounds__(64 * f32_waves<D>()) attention_f32_kernel(Attn
             const int64_t j = j0 + acc_row(r, lh);
             kp[r] = a.kpos[j < a.Mk ? j : a.Mk - 1];
         }
-        if (first > qp_last) break;   // ascending positions: nothing visible from here on
+        if (LOAD_FIRST && first > qp_last) break;
         const f32x16 s = mma_rows<NS>(kf, qf);
         float p[16], mx = m;
 #pragma unroll
