@@ -11,7 +11,7 @@
 //    product's; which k an instruction multiplies is free as long as both operands agree.  256 x 256 x 256 fp32: 34 us (64x64
 //    tiles, 16-wide K steps through LDS, two barriers each) -> 7 us; 256 x 256 x 688 with the residual: 101 -> 10 us; the whole
 //    fp32 layer of 512 tokens with the probe and attention of kernels_attn_generic.hip 1590 -> 172 us, its error against 64
-//    bits 2.9e-7 -> 1.6e-7 (four partial sums instead of one chain).
+//    bits 2.9e-7 -> 1.6e-7 (four or eight partial sums instead of one chain).
 //  * gemm_generic_kernel: element-wise loads, any K and any leading dimension.
 #include "spts_internal.h"
 
@@ -34,14 +34,23 @@ __device__ inline f32x16 tile32_mfma(u32x4 b, u32x4 a, f32x16 c, bf16_t) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
 }
 
-// Wavefronts per tile: four; eight for a plain fp32 product of K > 256, whose groups are then three to a wavefront instead of six at K = 704 (proxy z
-// of 512 rows 12.7 -> 9.9 us, down of 256 13.6 -> 10.9; of 1500 and 750 rows 11.8 -> 8.7 and 13.6 -> 11.1; at K = 256, two groups to a wavefront of
-// four, 6.5 -> 6.1).  Two products to a tile (SiLU, rotary) have registers for one workgroup of eight per CU (gate/up of 750 rows 16.4 -> 23.4 us).
-// The rule knows nothing of the launch: a product has the same sums alone and in a group.
-template <typename T> __host__ __device__ constexpr int tile32_waves(int mode, int K) { return sizeof(T) == 4 && mode == T32_ONE && K > 256 ? 8 : 4; }
+// Partial sums of an element: one per wavefront, four; eight for a plain fp32 product of K > 256 (partial c: every eighth group of 32 from the c-th on),
+// which are added in order.  Who computes them is the launch's choice: eight wavefronts one each, or four two each.  The rule
+// for the number knows nothing of the launch or the row count: a product has the same sums alone, in a group and for any rows beside its own.
+template <typename T> __host__ __device__ constexpr int tile32_partials(int mode, int K) { return sizeof(T) == 4 && mode == T32_ONE && K > 256 ? 8 : 4; }
+
+// Eight wavefronts while every tile has a CU for itself: with their second set of loads they take 122 registers against 72 and twice the LDS.  K = 512,
+// N = 512, M = 512 / 768 / 1500 / 6000 (256, 384, 752, 3008 tiles) with eight 7.6 / 13.2 / 18.3 / 62 us, with four 7.8 / 10.8 / 14.4 / 52; K = 688, N = 256, M = 256 /
+// 1024 / 1500 / 6000 8.7 / 9.2 / 16.7 / 46, with four 9.7 / 10.0 / 16.1 / 43.5.  (Two products to a tile, SiLU and rotary, have registers for one workgroup of eight
+// per CU: gate/up of 750 rows 16.4 -> 23.4 us.)  And for long sums of very many rows to few columns: K = 1376, N = 128 / 256, 24000 rows 170 / 333, with four 185 / 351; K = 2752,
+// N = 64, 24000 rows 180 / 219, N = 256, 6000 rows 173 / 233; not at K = 1024 (N = 256, 6000 / 24000 rows 65 / 239, with four 59 / 234) or fewer tiles (K = 1376,
+// N = 128, 6000 rows, 752 of them, 47 / 42.5).
+// (A group: the first of the two, over all its tiles.)
+constexpr int64_t TILE32_EIGHT_TILES = 256;
+static bool tile32_eight_waves(int64_t tiles, int N, int K) { return tiles <= TILE32_EIGHT_TILES || (tiles > 4 * TILE32_EIGHT_TILES && N <= 256 && K > 1024); }
 
 // tile (bx, by) of a product
-template <typename T, int MODE, int W>
+template <typename T, int MODE, int W, int CH = 1>   // CH: partial sums per wavefront
 __device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by, float (*red)[W][32][36]) {
     constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
     constexpr int KS = 2 * EPC;                // k per step: one chunk for each half of the wavefront
@@ -65,9 +74,11 @@ __device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by
     const T* pb = (const T*)a.B0 + brow * a.ldb + lh * EPC;
     const T* pb1 = (const T*)(MODE == T32_SILU ? a.B1 : a.B0) + brow1 * a.ldb + lh * EPC;
 
-    f32x16 acc[NP];
+    static_assert(CH == 1 || (CH == 2 && W == 4 && NP == 1), "eight partial sums");
+    constexpr int NA = NP * CH;
+    f32x16 acc[NA];   // of either product, or either partial sum
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
+    for (int p = 0; p < NA; ++p)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[p][r] = 0.f;
     // K % EPC == 0: a chunk is inside or outside as a whole.  Loads past K read the last chunk instead and count as zeros: a load
@@ -90,15 +101,21 @@ __device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by
             if (MODE == T32_SILU) fa1[u] = load(pa1, k0 + u * KS);
         }
     };
-    auto multiply_group = [&](int set) {
+    auto multiply_group = [&](int set, int to = 0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            acc[0] = tile32_mfma(fb[set][u], fa[set][u], acc[0], T{});
+            acc[to] = tile32_mfma(fb[set][u], fa[set][u], acc[to], T{});
             if (NP == 2) acc[NP - 1] = tile32_mfma(fb1[u], MODE == T32_SILU ? fa1[u] : fa[set][u], acc[NP - 1], T{});
         }
     };
     constexpr int STEP = W * U * KS;
-    if (SETS == 1) {
+    if (CH == 2) {
+        for (int k0 = wave * (U * KS); k0 < a.K; k0 += 2 * STEP) {
+            load_group(0, k0);
+            multiply_group(0);
+            if (k0 + STEP < a.K) { load_group(0, k0 + STEP); multiply_group(0, NA - 1); }
+        }
+    } else if (SETS == 1) {
         for (int k0 = wave * (U * KS); k0 < a.K; k0 += STEP) { load_group(0, k0); multiply_group(0); }
     } else {
         int k0 = wave * (U * KS);
@@ -112,20 +129,27 @@ __device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by
         }
     }
     // lane: output row l32, columns 8 * (r / 4) + 4 * lh + r % 4
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<f32x4*>(&red[p][wave][l32][8 * q + 4 * lh]) = f32x4{acc[p][4 * q], acc[p][4 * q + 1], acc[p][4 * q + 2], acc[p][4 * q + 3]};
-    __syncthreads();
-    if (tid >= 256) return;
     const int r = tid >> 3, c4 = (tid & 7) * 4;
     f32x4 v[2];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        v[p] = *reinterpret_cast<const f32x4*>(&red[p][0][r][c4]);
+    for (int ch = 0; ch < CH; ++ch) {
+        if (ch > 0) __syncthreads();
 #pragma unroll
-        for (int w = 1; w < W; ++w) v[p] += *reinterpret_cast<const f32x4*>(&red[p][w][r][c4]);   // fixed order
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x16& s = acc[p + ch];
+                *reinterpret_cast<f32x4*>(&red[p][wave][l32][8 * q + 4 * lh]) = f32x4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
+            }
+        __syncthreads();
+        if (tid >= 256) return;   // (of eight wavefronts, which have one partial sum each)
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int w = 0; w < W; ++w) {   // fixed order
+                const f32x4 s = *reinterpret_cast<const f32x4*>(&red[p][w][r][c4]);
+                v[p] = ch == 0 && w == 0 ? s : v[p] + s;
+            }
     }
     const int64_t grow = row0 + r;
     if (MODE == T32_WIDE) {   // EPI_SUMSQ
@@ -169,15 +193,16 @@ __device__ __forceinline__ void tile32_product(const GemmArgs& a, int bx, int by
     }
 }
 
-template <typename T, int MODE, int W>
+template <typename T, int MODE, int W, int CH = 1>
 __global__ void __launch_bounds__(64 * W) gemm_tile32_kernel(GemmArgs a) {
     __shared__ __attribute__((aligned(16))) float red[MODE == T32_ONE ? 1 : 2][W][32][36];
-    tile32_product<T, MODE, W>(a, blockIdx.x, blockIdx.y, red);
+    tile32_product<T, MODE, W, CH>(a, blockIdx.x, blockIdx.y, red);
 }
 
 // independent products, rotary or plain, in one launch: product i has the blocks from first[i] on, nx[i] of them to a row of tiles
 struct Tile32Group { GemmArgs a[GEMM_GROUP_MAX]; int first[GEMM_GROUP_MAX], nx[GEMM_GROUP_MAX]; };
-template <typename T, int WG>
+// EIGHT: there are products of eight partial sums among them
+template <typename T, int WG, bool EIGHT>
 __global__ void __launch_bounds__(64 * WG) gemm_tile32_group_kernel(Tile32Group g) {
     __shared__ __attribute__((aligned(16))) float red[2 * 4 * 32 * 36];
     static_assert(sizeof(red) >= sizeof(float) * WG * 32 * 36, "one product of WG wavefronts or two of four");
@@ -185,13 +210,18 @@ __global__ void __launch_bounds__(64 * WG) gemm_tile32_group_kernel(Tile32Group 
 #pragma unroll
     for (int q = 1; q < GEMM_GROUP_MAX; ++q) i += (int)blockIdx.x >= g.first[q] ? 1 : 0;
     const int b = blockIdx.x - g.first[i], by = b / g.nx[i], bx = b - by * g.nx[i];
-    const bool rope = g.a[i].epi == EPI_ROPE;
-    if (WG == 8 && tile32_waves<T>(rope ? T32_ROPE : T32_ONE, g.a[i].K) == 8) {
+    const bool rope = g.a[i].epi == EPI_ROPE, eight = EIGHT && tile32_partials<T>(rope ? T32_ROPE : T32_ONE, g.a[i].K) == 8;
+    if (WG == 8 && eight) {
         tile32_product<T, T32_ONE, WG>(g.a[i], bx, by, reinterpret_cast<float (*)[WG][32][36]>(red));
         return;
     }
     if (threadIdx.x >= 256) return;
     auto* red4 = reinterpret_cast<float (*)[4][32][36]>(red);
+    if constexpr (WG == 4 && EIGHT)
+        if (eight) {
+            tile32_product<T, T32_ONE, 4, 2>(g.a[i], bx, by, red4);
+            return;
+        }
     if (rope) tile32_product<T, T32_ROPE, 4>(g.a[i], bx, by, red4);
     else tile32_product<T, T32_ONE, 4>(g.a[i], bx, by, red4);
 }
@@ -315,6 +345,12 @@ bool gemm_tile32_supported(const GemmArgs& a, bool bf16) {
     return true;
 }
 
+// wavefronts of a product in a launch of its own
+int gemm_tile32_waves(const GemmArgs& a, bool bf16) {
+    if (bf16 || (a.epi != EPI_STORE && a.epi != EPI_RESIDUAL) || tile32_partials<float>(T32_ONE, a.K) != 8) return 4;
+    return tile32_eight_waves((a.M + 31) / 32 * ((a.N + 31) / 32), a.N, a.K) ? 8 : 4;
+}
+
 template <typename T>
 static void launch_tile32_t(const GemmArgs& a, hipStream_t s) {
     const unsigned ny = (unsigned)((a.M + 31) / 32), nx = (unsigned)((a.N + 31) / 32);
@@ -325,8 +361,9 @@ static void launch_tile32_t(const GemmArgs& a, hipStream_t s) {
         case EPI_SUMSQ: gemm_tile32_kernel<T, T32_WIDE, 4><<<dim3((unsigned)((a.N + 63) / 64), ny), b4, 0, s>>>(a); break;
         default:
             if constexpr (sizeof(T) == 4)
-                if (tile32_waves<T>(T32_ONE, a.K) == 8) {
-                    gemm_tile32_kernel<T, T32_ONE, 8><<<dim3(nx, ny), dim3(512), 0, s>>>(a);
+                if (tile32_partials<T>(T32_ONE, a.K) == 8) {
+                    if (gemm_tile32_waves(a, false) == 8) gemm_tile32_kernel<T, T32_ONE, 8><<<dim3(nx, ny), dim3(512), 0, s>>>(a);
+                    else gemm_tile32_kernel<T, T32_ONE, 4, 2><<<dim3(nx, ny), b4, 0, s>>>(a);
                     break;
                 }
             gemm_tile32_kernel<T, T32_ONE, 4><<<dim3(nx, ny), b4, 0, s>>>(a);
@@ -358,13 +395,11 @@ static int tile32_columns(const GemmArgs& a) { return ((a.epi == EPI_ROPE ? a.N 
 bool gemm_tile32_group_supported(const GemmArgs* a, int n, bool bf16) {
     if (n < 1 || n > GEMM_GROUP_MAX) return false;
     int64_t blocks = 0;
-    bool eight = false;
     for (int i = 0; i < n; ++i) {
-        eight |= !bf16 && tile32_waves<float>(a[i].epi == EPI_ROPE ? T32_ROPE : T32_ONE, a[i].K) == 8;
         if (!gemm_tile32_supported(a[i], bf16) || (a[i].epi != EPI_ROPE && a[i].epi != EPI_STORE && a[i].epi != EPI_RESIDUAL)) return false;
         blocks += (int64_t)tile32_columns(a[i]) * ((a[i].M + 31) / 32);
     }
-    return eight ? blocks < 1 << 23 : blocks <= 1 << 23;   // one grid dimension of 256 or 512 threads each, 2^32 in all at most
+    return blocks <= 1 << 23;   // one grid dimension of 256 threads each
 }
 
 hipError_t launch_gemm_tile32_group(const GemmArgs* a, int n, bool bf16, hipStream_t s) {
@@ -381,11 +416,12 @@ hipError_t launch_gemm_tile32_group(const GemmArgs* a, int n, bool bf16, hipStre
         blocks += (int64_t)g.nx[i] * ((a[i].M + 31) / 32);
     }
     bool eight = false;
-    for (int i = 0; i < n; ++i) eight |= !bf16 && tile32_waves<float>(a[i].epi == EPI_ROPE ? T32_ROPE : T32_ONE, a[i].K) == 8;
+    for (int i = 0; i < n; ++i) eight |= !bf16 && tile32_partials<float>(a[i].epi == EPI_ROPE ? T32_ROPE : T32_ONE, a[i].K) == 8;
     const dim3 grid((unsigned)blocks);
-    if (bf16) gemm_tile32_group_kernel<bf16_t, 4><<<grid, dim3(256), 0, s>>>(g);
-    else if (eight) gemm_tile32_group_kernel<float, 8><<<grid, dim3(512), 0, s>>>(g);
-    else gemm_tile32_group_kernel<float, 4><<<grid, dim3(256), 0, s>>>(g);
+    if (bf16) gemm_tile32_group_kernel<bf16_t, 4, false><<<grid, dim3(256), 0, s>>>(g);
+    else if (!eight) gemm_tile32_group_kernel<float, 4, false><<<grid, dim3(256), 0, s>>>(g);
+    else if (blocks <= TILE32_EIGHT_TILES) gemm_tile32_group_kernel<float, 8, true><<<grid, dim3(512), 0, s>>>(g);
+    else gemm_tile32_group_kernel<float, 4, true><<<grid, dim3(256), 0, s>>>(g);
     return hipGetLastError();
 }
 

@@ -53,6 +53,19 @@ def test_groups_of_32x32_tiles_are_no_larger_than_a_launch():
         assert f((I.GemmArgs * 2)(*two), 2, False) == fits
 
 
+@pytest.mark.parametrize("M,N,K,waves", [(256, 1024, 512, 8), (257, 1024, 512, 4), (1500, 512, 688, 4), (6000, 256, 1376, 8), (6000, 256, 1024, 4), (6000, 260, 2052, 4),
+                                         (3000, 256, 2752, 4), (64, 64, 260, 8), (64, 64, 256, 4)])
+def test_plain_fp32_products_of_many_tiles_keep_four_wavefronts(M, N, K, waves):
+    """Eight where every tile has a CU for itself (256 tiles), and for very long sums of many rows to few columns."""
+    f = getattr(binding.load(), "_ZN4spts17gemm_tile32_wavesERKNS_8GemmArgsEb")
+    f.restype, f.argtypes = C.c_int, [C.POINTER(I.GemmArgs), C.c_bool]
+    for epi in (I.EPI_STORE, I.EPI_RESIDUAL):
+        a = I.GemmArgs(A=A16, lda=K, B0=A16, ldb=K, C=A16, ldc=N, M=M, N=N, K=K, epi=epi)
+        assert f(a, False) == waves and f(a, True) == 4
+    a.epi, a.head_dim, a.rope = I.EPI_ROPE, 4, A16
+    assert f(a, False) == 4
+
+
 def _layer_products(D, QD, KV, Dff, r, d, N, Ma, Mf, P):
     """The products of one skip layer over N rows with Ma / Mf active ones, as the layer call sets them up (row-major weights)."""
     def g(M, n, k, epi, **kw):

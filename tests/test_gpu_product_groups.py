@@ -99,6 +99,41 @@ def test_32x32_tiles(torch, n, dtype):
         assert torch.isfinite(c[:M]).all() and torch.isnan(c[M:]).all()
 
 
+@pytest.mark.parametrize("K", [256, 260, 512, 516, 772, 1028, 2052])
+@pytest.mark.parametrize("rows", [(65, 31, 100), (1500, 900, 64)], ids=["eight_wavefronts", "four_wavefronts"])
+def test_32x32_tiles_of_long_fp32_sums(torch, rows, K):
+    """Plain products of K > 256, eight partial sums, with a rotary product of four between them: K at and just beyond a group of every wavefront and of
+    half of them, few tiles (eight wavefronts) and many (four).  In one launch, in launches of their own and for 33 of the rows alone the same bits."""
+    stream = torch.cuda.current_stream().cuda_stream
+    shapes = [(rows[0], 512, I.EPI_STORE), (rows[1], 128, I.EPI_ROPE), (rows[2], 200, I.EPI_STORE)]
+    got = []
+    for together in (True, False):
+        made = [_product(torch, M, N, K, epi, torch.float32, i, d=32) for i, (M, N, epi) in enumerate(shapes)]
+        if together:
+            assert _tile32_group([m[0] for m in made], False, stream) == 0
+        else:
+            for m in made:
+                assert I.launch_generic(m[0], False, stream) == 0
+        torch.cuda.synchronize()
+        got.append([x for m in made for x in m[1:3]])
+    for x, y in zip(*got):
+        assert torch.equal(torch.nan_to_num(x, nan=7.0), torch.nan_to_num(y, nan=7.0))
+    for (M, N, epi), (a, c, ct, (A, B, _)) in zip(shapes, made):
+        assert torch.isnan(c[M:]).all()
+        if epi != I.EPI_STORE:
+            assert torch.isfinite(c[:M]).all()
+            continue
+        ref = A.double() @ B.double().t()
+        bound = A.double().abs() @ B.double().abs().t()
+        assert bool(((c[:M].double() - ref).abs() <= (K / 8 + 8) * 2.0 ** -24 * bound).all())   # eight chains of K / 8 fused terms, their sum
+        whole = c[:M].clone()
+        few = min(33, M)
+        a.M, a.Ct = few, None
+        c.fill_(float("nan"))
+        assert I.launch_generic(a, False, stream) == 0
+        assert torch.equal(c[:few], whole[:few]) and torch.isnan(c[few:]).all()
+
+
 def test_products_of_different_kernels_stay_apart(torch):
     """A dense layer with 128 key columns, which the 256-wide tiles do not take, and 512 query columns, which they do: the queries do not
     follow the keys into the 32x32 tiles' launch."""
