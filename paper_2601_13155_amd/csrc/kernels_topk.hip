@@ -1276,12 +1276,14 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_mean_kernel(const T* __rest
 
 // Rows of at most 64 * KPT values: one wavefront per row, the row read once into registers.  The key of the k-th largest |value| lies between a key that k keys
 // reach and one that fewer do, and the two close in: first to either side of the same quantile of 256 of the keys, as far as its error and the usual slope of such
-// a row suggest and then twice as far each time, after that to their middle.  What is found does not depend on the guesses.
+// a row suggest and then eight times as far each time, after that to their middle.  What is found does not depend on the guesses.  Up to 1024 values in bf16 the
+// key's 15 bits are decided one by one instead.
 // Counting is one compare per key whose lane mask is summed on the scalar unit, so there are no histograms, no LDS and no
 // barrier.  The scalar unit is what that runs out of (two instructions a key against one), so every third key is counted on the
 // vector unit instead (one more), lane by lane.  Bound: the counts, and one read of the row (20 us for 14336 rows of 4096).  Measured there: 283 us with
 // the workgroup-per-row kernel above (two histogram passes over 1024-lane strides), 72 with a count for each of a key's 15 bits, 45 here (1000
-// values to a row of 18944: 26).
+// values to a row of 18944: 26).  14336 rows of 256 / 1000 / 2048 / 4096 products of two normal values, k a fifth: bf16 bit by bit 11.9 / 18.8 / 31.0 / 58, from
+// the sample 15.2 / 18.9 / 26 / 42; fp32 31 / 35 / 55 / 108 and 17 / 24 / 36 / 63.  Rows that are one value repeated end later than those: 2048 in bf16 36.6, in fp32 50.
 template <typename T, int KPT>
 __global__ void __launch_bounds__(256) topk_mean_wave_kernel(const T* __restrict__ vals, int64_t ld, int64_t rows, int n, int k, int wide,
                                                              float* __restrict__ out) {
@@ -1324,8 +1326,14 @@ __global__ void __launch_bounds__(256) topk_mean_wave_kernel(const T* __restrict
         }
         return cnt + (int)wave_reduce_u32((uint32_t)mine, 0u, [](uint32_t a, uint32_t b) { return a + b; });
     };
-    uint32_t guess = 0;
-    {
+    uint32_t t = 0;
+    if constexpr (BITS == 15 && KPT <= 16) {   // bit by bit: a count costs no more than the sample's share of the other way
+        for (int b = BITS - 1; b >= 0; --b) {
+            const uint32_t c = t | (1u << b);
+            if (reach(c) >= k) t = c;
+        }
+    } else {
+        uint32_t guess = 0;
         const int rank = (int)(((int64_t)k * 4 + KPT - 1) / KPT);   // of 256 keys out of 64 KPT
         for (int b = BITS - 1; b > BITS - 16; --b) {
             const uint32_t c = guess | (1u << b);
@@ -1334,28 +1342,50 @@ __global__ void __launch_bounds__(256) topk_mean_wave_kernel(const T* __restrict
             for (int q = 0; q < 4; ++q) cnt += (int)__popcll(__ballot(key[KPT / 4 * q] >= c));
             if (cnt >= rank) guess = c;
         }
-    }
-    uint32_t t = 0, end = 1u << BITS, c = guess > 0 ? guess : 1u, step = 0;   // k keys or more reach t, fewer end
-    int at_t = 64 * KPT + 1;   // keys that reach t (0: all)
-    bool up = false, closing = false;
-    while (end - t > 1 && at_t != k) {
-        const int cnt = reach(c);
-        const bool enough = cnt >= k;
-        if (enough) { t = c; at_t = cnt; } else end = c;
-        if (step == 0) {   // twice as far as it is where keys thin out to a third within an octave
-            const float octaves = fminf((float)(enough ? cnt - k : k - cnt) / (float)k, 64.f);
-            step = (uint32_t)(octaves * (float)(2 << (BITS - 8))) + (2u << (BITS - 15));   // (0.7 / 1 / 1.4 octaves for that: 46 / 47 / 46 us, two 45)
-            up = enough;
-        } else closing = closing || up != enough;
-        const uint32_t room = end - t;
-        if (closing || step >= room) { c = t + room / 2; closing = true; }
-        else { c = up ? t + step : end - step; step *= 2; }
-    }
-    if (at_t == k && end - t > 1) {   // exactly k keys reach t: the smallest of them
-        uint32_t mn = 0xFFFFFFFFu;
+        uint32_t end = 1u << BITS, c = guess > 0 ? guess : 1u, step = 0;   // k keys or more reach t, fewer end
+        int at_t = 64 * KPT + 1;   // keys that reach t (0: all)
+        bool up = false, closing = false;
+        for (int left = 16; (BITS == 15 || left > 0) && end - t > 1 && at_t != k; --left) {
+            const int cnt = reach(c);
+            const bool enough = cnt >= k;
+            if (enough) { t = c; at_t = cnt; } else end = c;
+            if (step == 0) {   // twice as far as it is where keys thin out to a third within an octave
+                const float octaves = fminf((float)(enough ? cnt - k : k - cnt) / (float)k, 64.f);
+                step = (uint32_t)(octaves * (float)(2 << (BITS - 8))) + (2u << (BITS - 15));   // (0.7 / 1 / 1.4 octaves for that: 46 / 47 / 46 us, two 45)
+                up = enough;
+            } else closing = closing || up != enough;
+            const uint32_t room = end - t;
+            if (closing || step >= room) { c = t + room / 2; closing = true; }
+            else { c = up ? t + step : end - step; step *= 8; }
+        }
+        // fp32, and not there yet: few values, or rare ones, and up to 30 bits between them.  The ends move to the outermost keys, and then to their
+        // middle for some rounds.  (In bf16 there are 15 bits in all.)
+        while (BITS == 31 && end - t > 1 && at_t != k) {
+            uint32_t mn = 0xFFFFFFFFu, mx = 0u;
 #pragma unroll
-        for (int j = 0; j < KPT; ++j) mn = min(mn, key[j] >= t ? key[j] : 0xFFFFFFFFu);
-        t = wave_reduce_u32(mn, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return min(a, b); });
+            for (int j = 0; j < KPT; ++j) {
+                const uint32_t d = key[j] - t;
+                const bool in = d < end - t;
+                mn = min(mn, in ? d : 0xFFFFFFFFu);
+                mx = max(mx, in ? d : 0u);
+            }
+            mn = wave_reduce_u32(mn, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return min(a, b); });
+            mx = wave_reduce_u32(mx, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
+            end = t + mx + 1;
+            t += mn;
+            if (mn == mx) break;
+            for (int left = 6; left > 0 && end - t > 1 && at_t != k; --left) {
+                c = t + (end - t) / 2;
+                const int cnt = reach(c);
+                if (cnt >= k) { t = c; at_t = cnt; } else end = c;
+            }
+        }
+        if (at_t == k && end - t > 1) {   // exactly k keys reach t: the smallest of them
+            uint32_t mn = 0xFFFFFFFFu;
+#pragma unroll
+            for (int j = 0; j < KPT; ++j) mn = min(mn, key[j] >= t ? key[j] : 0xFFFFFFFFu);
+            t = wave_reduce_u32(mn, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return min(a, b); });
+        }
     }
     auto value = [](uint32_t q) { return __uint_as_float(sizeof(T) == 2 ? q << 16 : q); };
     float s = 0.f;

@@ -202,6 +202,45 @@ def test_topk_mean_of_any_values(torch, dtype, n):
         assert np.allclose(out.cpu().numpy(), ref, rtol=(k + 4) * 2.0 ** -24, atol=0), k
 
 
+def _topk_mean(torch, v, k, out):
+    from tests import internal as I
+    assert I.topk_mean(v.data_ptr(), v.shape[1], v.shape[0], v.shape[1], k, out.data_ptr(), v.dtype == torch.bfloat16, torch.cuda.current_stream().cuda_stream) == 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [64, 512, 513, 1024, 1025, 2048, 3000, 4096])
+def test_topk_mean_of_few_values(torch, dtype, n):
+    """Rows whose threshold lies among many equal or nearly equal values: one value, two, steps, values a few units of the last place apart, a tie below
+    smooth values, a tie that the sample misses (every 64th value is another)."""
+    rng = np.random.default_rng(100 + n)
+    z = rng.standard_normal(n)
+    u = rng.random(n)
+    rows = [np.full(n, -0.3), np.full(n, 1e-30), np.where(u < 0.19, 2.0, 1.0), np.where(u < 0.5, 1.0 + 1e-6 * z, 1e-20), np.round(2 * z), 0.3 * np.round(2 * z),
+            np.where(u < 0.15, 1.0 + np.abs(z), 0.7), np.where(u < 0.25, 1.0 + np.abs(z), 0.7), np.where(u < 0.6, 0.7, 0.7 * (1 - 1e-3 * u)), np.where(np.arange(n) % 64 < 13, 5.0, 4.0),
+            np.where(u < 0.5, np.inf, 1.0), np.where(u < 0.3, 1e38, 1e-38 * u)]
+    v = torch.from_numpy(np.stack(rows).astype(np.float32)).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32).contiguous()
+    host = np.sort(np.abs(v.float().cpu().numpy().astype(np.float64)), axis=1)[:, ::-1]
+    for k in sorted({1, max(1, n // 50), n // 5, n // 3, n // 2, n - 1, n}):
+        out = torch.full((len(rows),), -1.0, dtype=torch.float32, device="cuda")
+        _topk_mean(torch, v, k, out)
+        ref = host[:, :k].mean(1)
+        # a sum of k fp32 terms of one sign in any order, a product and a quotient; sums beyond the largest fp32 number are infinite
+        got = out.cpu().numpy().astype(np.float64)
+        over = host[:, :k].sum(1) > 3.4e38
+        assert np.allclose(got[~over], ref[~over], rtol=(k + 4) * 2.0 ** -24, atol=1e-45) and np.isinf(got[over]).all(), k
+
+
+@pytest.mark.parametrize("n", [1000, 2048])
+def test_topk_mean_of_equal_values_takes_little_longer(torch, n):
+    """The search for the threshold of 14336 rows closes in on it from both sides; of equal fp32 values it does not go through all bits below the first that
+    the sample tells (then 1.9 and 2 times the time of smooth rows, now 1.4 and 1.5)."""
+    out = torch.empty(14336, device="cuda")
+    smooth = torch.randn((14336, n), device="cuda") * torch.randn((14336, n), device="cuda")
+    same = torch.full((14336, n), 0.25, device="cuda")
+    times = [_best_us(torch, lambda v=v: _topk_mean(torch, v, n // 5, out)) for v in (smooth, same)]
+    assert times[1] <= 1.7 * times[0], times
+
+
 # ------------------------------------------------------------------------------------------ TopK of long rows of a batch
 @pytest.mark.parametrize("n", [32772, 65536, 100004, 131068, 131072, 131076])
 def test_long_row_topk_patterns(torch, n):
