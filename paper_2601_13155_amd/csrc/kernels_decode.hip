@@ -5,8 +5,8 @@
 //
 // One token means every contraction is a matrix-vector product whose cost is reading the weights
 // once, so the whole step is HBM-bound (8B-shaped model: 13.9 GB of bf16 weights per token):
-//   * gemv_kernel: y = W x with W [R, K] row-major.  A workgroup of 4 wavefronts owns 2 rows (8, four gate
-//     and four up rows, for SwiGLU; 4 for Q/K/V) and splits K across its 256 lanes in
+//   * gemv_kernel: y = W x with W [R, K] row-major.  A workgroup of 4 wavefronts owns 2 rows (4 where it
+//     normalises x itself, for Q/K/V and for the head) and splits K across its 256 lanes in
 //     16-byte chunks, with several independent 16-byte weight loads per lane in flight before the first use; bf16
 //     pairs are multiplied with v_dot2c_f32_bf16 (fp32 accumulate, no conversion instructions).
 //     Lanes reduce by shuffles, wavefronts through LDS.  Up to three matrices that share x run as
@@ -208,10 +208,12 @@ bool gemv_supported(const GemvArgs& a, bool bf16) {
     return true;
 }
 
-// With the norm inside, a workgroup of gate/up rows takes four of each, so that normalising x (a barrier and a round trip to the L2) comes once per
-// 64 KB of weights that are in flight meanwhile: 1 / 2 / 4 row pairs 345.7 / 339.3 / 341.0 us for two layers of the 8B shape and a head of 128256 rows, Qwen
-// shape 339.3 / 333.4 / 335.4 (one box; between runs +-1), without it and with a launch for each norm 344.2 and 338.6.  The head with four rows 336.1 and 330.2,
-// with eight 341.9 and 330.6.  Half as many registers where a lane holds two chunks (Q/K/V: 1536 workgroups, six per CU, at once instead of in two rounds).
+// With the norm inside, a workgroup of gate/up rows takes two of each, so that normalising x (a barrier and a round trip to the L2) comes once per
+// 32 KB of weights that are in flight meanwhile: 1 / 2 / 4 row pairs 338.9 / 331.8 / 333.3 us for two layers of the 8B shape, 13107 cached pairs, and a head of 128256 rows,
+// Qwen shape 335.4 / 329.6 / 330.3, hidden size 2048, 8 layers 352 / 349 / 351, fp32, 4 layers 236 / 232 / 234.  The head with four rows 336.1 and 330.2 (8B, Qwen), with eight
+// 341.9 and 330.6.  Half as many registers where a lane holds two chunks (Q/K/V: 1536 workgroups, six per CU, at once instead of in two rounds).
+// Against a launch for each norm (the head of 32000 rows, 500 cached pairs): hidden size 1024, 16 layers 479 -> 414; 2048, 8 layers 344 -> 299; 4096, 2 layers 226 -> 210; with
+// four chunks to a lane 5120 / 6144 / 8192, 2 layers 275 -> 256, 350 -> 327, 628 -> 612; fp32 1024, 8 layers 283 -> 249, 3072 / 4096, 2 layers 238 -> 224, 347 -> 331.
 template <typename T>
 static hipError_t launch_gemv_t(const GemvArgs& a, hipStream_t s) {
     const int64_t rows = (int64_t)a.R[0] + a.R[1] + a.R[2];
@@ -228,7 +230,7 @@ static hipError_t launch_gemv_t(const GemvArgs& a, hipStream_t s) {
             break;
         case GEMV_SILU:
             if (!n) gemv_kernel<T, GEMV_SILU, false, 2, 1><<<grid(1), b, 0, s>>>(a);
-            else if (two) gemv_kernel<T, GEMV_SILU, true, 8, 2><<<grid(4), b, 0, s>>>(a);
+            else if (two) gemv_kernel<T, GEMV_SILU, true, 4, 2><<<grid(2), b, 0, s>>>(a);
             else gemv_kernel<T, GEMV_SILU, true, 4, 4><<<grid(2), b, 0, s>>>(a);
             break;
         case GEMV_RESID: if (n) return hipErrorInvalidValue; gemv_kernel<T, GEMV_RESID, false, 2, 1><<<grid(2), b, 0, s>>>(a); break;
