@@ -189,10 +189,8 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a) {
     } else if (MODE == GEMV_RESID) {
         T* y = (T*)a.y[which] + out_row + tid;
         *y = from_f32<T>(to_f32(*y) + v);
-    } else if (MODE == GEMV_F32) {
+    } else {   // GEMV_F32
         ((float*)a.y[which])[out_row + tid] = v;
-    } else {
-        ((T*)a.y[which])[out_row + tid] = from_f32<T>(v);
     }
 }
 
@@ -223,11 +221,6 @@ static hipError_t launch_gemv_t(const GemvArgs& a, hipStream_t s) {
     const bool two = a.K / (16 / (int)sizeof(T)) <= 512;   // chunks of x per lane, with the norm: 2, or 4
     auto grid = [&](int per) { return dim3((unsigned)(rows / per)); };
     switch (a.mode) {
-        case GEMV_STORE:
-            if (!n) gemv_kernel<T, GEMV_STORE, false, 4, 1><<<grid(4), b, 0, s>>>(a);
-            else if (two) gemv_kernel<T, GEMV_STORE, true, 4, 2><<<grid(4), b, 0, s>>>(a);
-            else gemv_kernel<T, GEMV_STORE, true, 4, 4><<<grid(4), b, 0, s>>>(a);
-            break;
         case GEMV_SILU:
             if (!n) gemv_kernel<T, GEMV_SILU, false, 2, 1><<<grid(1), b, 0, s>>>(a);
             else if (two) gemv_kernel<T, GEMV_SILU, true, 4, 2><<<grid(2), b, 0, s>>>(a);
@@ -332,10 +325,8 @@ __global__ void __launch_bounds__(256) gemv_nb_kernel(GemvArgs a) {
     } else if (MODE == GEMV_RESID) {
         T* y = (T*)a.y[which] + (int64_t)b * a.R[which] + out_row + r;
         *y = from_f32<T>(to_f32(*y) + v);
-    } else if (MODE == GEMV_F32) {
+    } else {   // GEMV_F32
         ((float*)a.y[which])[(int64_t)b * a.R[which] + out_row + r] = v;
-    } else {
-        ((T*)a.y[which])[(int64_t)b * a.R[which] + out_row + r] = from_f32<T>(v);
     }
 }
 
@@ -345,7 +336,6 @@ static hipError_t launch_gemv_nb_tr(const GemvArgs& a, hipStream_t s) {
     const dim3 b(256);
     const dim3 g((unsigned)(a.mode == GEMV_SILU ? a.R[0] / (4 * (RW / 2)) : rows / (4 * RW)));
     switch (a.mode) {
-        case GEMV_STORE: gemv_nb_kernel<T, GEMV_STORE, NB, RW><<<g, b, 0, s>>>(a); break;
         case GEMV_SILU: gemv_nb_kernel<T, GEMV_SILU, NB, RW><<<g, b, 0, s>>>(a); break;
         case GEMV_RESID: gemv_nb_kernel<T, GEMV_RESID, NB, RW><<<g, b, 0, s>>>(a); break;
         case GEMV_F32: gemv_nb_kernel<T, GEMV_F32, NB, RW><<<g, b, 0, s>>>(a); break;
@@ -605,10 +595,8 @@ __global__ void __launch_bounds__((gemv_mfma_threads<MODE, NORM>()), 2) gemv_mfm
     } else if (MODE == GEMV_RESID) {
         bf16_t* y = (bf16_t*)a.y[which] + (int64_t)b * a.R[which] + row0 + r;
         *y = f32_to_bf16(bf16_to_f32(*y) + v);
-    } else if (MODE == GEMV_F32) {
+    } else {   // GEMV_F32
         ((float*)a.y[which])[(int64_t)b * a.R[which] + row0 + r] = v;
-    } else {
-        ((bf16_t*)a.y[which])[(int64_t)b * a.R[which] + row0 + r] = f32_to_bf16(v);
     }
 }
 
@@ -619,7 +607,7 @@ static int gemv_mfma_lds(const GemvArgs& a) {   // the ring, and gamma behind it
 
 bool gemv_mfma_supported(const GemvArgs& a, int nb) {
     if (nb < 1 || nb > 16 || a.K <= 0 || a.K % 256 != 0) return false;
-    if (a.mode != GEMV_STORE && a.mode != GEMV_SILU && a.mode != GEMV_RESID && a.mode != GEMV_F32 && a.mode != GEMV_QKV_ROPE) return false;
+    if (a.mode != GEMV_SILU && a.mode != GEMV_RESID && a.mode != GEMV_F32 && a.mode != GEMV_QKV_ROPE) return false;
     if (a.gamma && (a.mode != GEMV_SILU || !a.ssq || a.K > GEMV_NORM_K)) return false;
     if (a.mode == GEMV_QKV_ROPE && (a.head_dim <= 0 || a.head_dim % 16 != 0 || a.R[0] % a.head_dim != 0 || a.R[1] % a.head_dim != 0)) return false;
     for (int i = 0; i < 3; ++i)
@@ -650,7 +638,6 @@ hipError_t launch_gemv_mfma(const GemvArgs& a, int nb, hipStream_t s) {
     if (!gemv_mfma_supported(a, nb)) return hipErrorInvalidValue;
     const GemvNoRope none{};
     switch (a.mode) {
-        case GEMV_STORE: return launch_gemv_mfma_m<GEMV_STORE, false>(a, nb, none, s);
         case GEMV_SILU: return a.gamma ? launch_gemv_mfma_m<GEMV_SILU, true>(a, nb, none, s) : launch_gemv_mfma_m<GEMV_SILU, false>(a, nb, none, s);
         case GEMV_RESID: return launch_gemv_mfma_m<GEMV_RESID, false>(a, nb, none, s);
         case GEMV_F32: return launch_gemv_mfma_m<GEMV_F32, false>(a, nb, none, s);
@@ -707,54 +694,7 @@ hipError_t launch_decode_rope_row(int pos, int d, float base, float2* table, hip
 }
 
 // ------------------------------------------------------------------- rotary + cache append
-// q [H, d] is rotated in place for position pos; k [Hkv, d] is rotated and written, with v, to row
-// `row` of the cache; cache_pos[row] = pos.  Angles in fp64 like the prefill's rotary table.
-template <typename T>
-__global__ void decode_rope_append_kernel(T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int pos,
-                                          int H, int Hkv, int d, double neg2_over_d_log2base, T* __restrict__ cache_k,
-                                          T* __restrict__ cache_v, int32_t* __restrict__ cache_pos, int64_t row) {
-    const int half = d / 2;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) cache_pos[row] = pos;
-    if (i >= (H + Hkv) * half) return;
-    const int head = i / half, j = i % half;
-    double sn, cs;
-    sincos((double)pos * exp2((double)j * neg2_over_d_log2base), &sn, &cs);
-    const float c = (float)cs, s = (float)sn;
-    if (head < H) {
-        T* p = q + (int64_t)head * d + j;
-        const float a = to_f32(p[0]), b = to_f32(p[half]);
-        p[0] = from_f32<T>(a * c - b * s);
-        p[half] = from_f32<T>(b * c + a * s);
-    } else {
-        const int g = head - H;
-        const T* p = k + (int64_t)g * d + j;
-        const float a = to_f32(p[0]), b = to_f32(p[half]);
-        T* o = cache_k + (row * Hkv + g) * (int64_t)d + j;
-        o[0] = from_f32<T>(a * c - b * s);
-        o[half] = from_f32<T>(b * c + a * s);
-        T* ov = cache_v + (row * Hkv + g) * (int64_t)d + j;
-        const T* pv = v + (int64_t)g * d + j;
-        ov[0] = pv[0];
-        ov[half] = pv[half];
-    }
-}
-
-hipError_t launch_decode_rope_append(void* q, const void* k, const void* v, int pos, int H, int Hkv, int d, float base,
-                                     void* cache_k, void* cache_v, int32_t* cache_pos, int64_t row, bool bf16, hipStream_t s) {
-    const int n = (H + Hkv) * (d / 2);
-    const double kk = -2.0 / (double)d * log2((double)base);
-    const dim3 g((unsigned)((n + 255) / 256)), b(256);
-    if (bf16)
-        decode_rope_append_kernel<bf16_t><<<g, b, 0, s>>>((bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, pos, H, Hkv, d, kk,
-                                                          (bf16_t*)cache_k, (bf16_t*)cache_v, cache_pos, row);
-    else
-        decode_rope_append_kernel<float><<<g, b, 0, s>>>((float*)q, (const float*)k, (const float*)v, pos, H, Hkv, d, kk,
-                                                        (float*)cache_k, (float*)cache_v, cache_pos, row);
-    return hipGetLastError();
-}
-
-// the same for a batch of sequences (blockIdx.y = sequence), from the fp32 sums of the projections: q32 [B, H, d],
+// Rotary embedding and cache append for a batch of sequences (blockIdx.y = sequence), from the fp32 sums of the projections: q32 [B, H, d],
 // k32 / v32 [B, Hkv, d] -> q [B, H, d] and the new cache rows, rounded to T once, after the rotation (as the
 // single-sequence GEMV's epilogue does); every sequence has its own cache, row and position (by-value descriptor: at
 // most DECODE_MAX_BATCH sequences)

@@ -1429,7 +1429,7 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
                        hipStream_t s, TopkSegments seg, TopkMap map) {
     // with segments N is the longest segment (it picks the kernel variant) and k is ignored
     if ((k <= 0 && !seg.offsets) || N <= 0 || batch <= 0) return hipSuccess;
-    if (map.out && (seg.offsets || N > TOPK_REG_MAX_N)) return hipErrorInvalidValue;
+    if (map.out && (seg.offsets || N > TOPK_ONE_MAX_N)) return hipErrorInvalidValue;
     const dim3 g((unsigned)batch), b(TOPK_THREADS);
     if (N <= TOPK_REG_MAX_N) {
         // The smallest of these workgroups that holds the row: a round costs a compare per slot, empty or not, and 16 wavefronts wait
@@ -1449,8 +1449,8 @@ hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_la
         else if (N <= 12288) SPTS_TOPK_REG(12, 16);
         else if (N <= 16384) SPTS_TOPK_REG(16, 16);
         else if (N <= 20480) SPTS_TOPK_REG(20, 16);
-        else if (N <= 24576) SPTS_TOPK_REG(24, 16);
-        else SPTS_TOPK_REG(32, 16);
+        else if (N <= 24576) topk_reg_kernel<24, 16, false><<<g, b, 0, s>>>(scores, N, k, protect_last, idx_out, seg, map);   // (no map)
+        else topk_reg_kernel<32, 16, false><<<g, b, 0, s>>>(scores, N, k, protect_last, idx_out, seg, map);
 #undef SPTS_TOPK_REG
     }
     else if (!seg.offsets && N < ((int64_t)1 << 30)) {

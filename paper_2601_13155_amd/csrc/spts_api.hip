@@ -637,17 +637,15 @@ int spts_decode_layer(spts_ctx* c, void* x, int32_t pos, const spts_layer_weight
     const int QD = m.H * m.d, KV = m.Hkv * m.d;
     void* xn = c->p<void>(c->off.xn);
     void* q = c->p<void>(c->off.q);
-    void* kx = c->p<void>(c->off.khat);
-    void* vx = c->p<void>(c->off.vhat);
     void* att = c->p<void>(c->off.att);
     void* hbuf = c->p<void>(c->off.big);
     float* part = c->p<float>(c->off.tmp32);
     const size_t part_floats = (c->off.qp - c->off.tmp32) / sizeof(float);
 
     // the two RMSNorms run inside the GEMVs that consume them when the row fits the kernel's registers
-    GemvArgs qkv{}; qkv.mode = GEMV_STORE; qkv.x = xn; qkv.K = m.D;
+    GemvArgs qkv{}; qkv.mode = GEMV_QKV_ROPE; qkv.x = xn; qkv.K = m.D;
     qkv.W[0] = w->Wq; qkv.W[1] = w->Wk; qkv.W[2] = w->Wv; qkv.R[0] = QD; qkv.R[1] = KV; qkv.R[2] = KV;
-    qkv.y[0] = q; qkv.y[1] = kx; qkv.y[2] = vx;
+    qkv.y[0] = q;
     GemvArgs o{}; o.mode = GEMV_RESID; o.x = att; o.K = QD; o.W[0] = w->Wo; o.R[0] = m.D; o.y[0] = x;
     GemvArgs gu{}; gu.mode = GEMV_SILU; gu.x = xn; gu.K = m.D; gu.W[0] = w->Wgate; gu.W[1] = w->Wup; gu.R[0] = m.Dff; gu.y[0] = hbuf;
     GemvArgs dn{}; dn.mode = GEMV_RESID; dn.x = hbuf; dn.K = m.Dff; dn.W[0] = w->Wdown; dn.R[0] = m.D; dn.y[0] = x;
@@ -671,26 +669,19 @@ int spts_decode_layer(spts_ctx* c, void* x, int32_t pos, const spts_layer_weight
     } else {
         PHASE(c, PH_DEC_NORM); SPTS_HIP(c, launch_rmsnorm(x, w->gamma1, m.rms_eps, xn, 1, m.D, c->bf16, st));
     }
+    // rotary embedding in the GEMV's epilogue: q goes to the workspace, the rotated key and the value straight into
+    // row `row` of the cache.  The (cos, sin) row of this position is shared by all layers of the token.
     const size_t eb = c->bf16 ? 2 : 4;
-    if (m.d % 4 == 0) {
-        // rotary embedding in the GEMV's epilogue: q goes to the workspace, the rotated key and the value straight into
-        // row `row` of the cache.  The (cos, sin) row of this position is shared by all layers of the token.
-        if (c->dec_rope_pos != pos) {
-            PHASE(c, PH_DEC_ROPE_APPEND);
-            SPTS_HIP(c, launch_decode_rope_row(pos, m.d, m.rope_base, c->p<float2>(c->off.rope), st));
-            c->dec_rope_pos = pos;
-        }
-        qkv.mode = GEMV_QKV_ROPE; qkv.rope = c->p<float2>(c->off.rope); qkv.head_dim = m.d;
-        qkv.y[1] = (char*)cache->k + (size_t)row * KV * eb;
-        qkv.y[2] = (char*)cache->v + (size_t)row * KV * eb;
-        qkv.pos_out = cache->pos + row; qkv.pos_val = pos;
-        PHASE(c, PH_DEC_QKV); SPTS_HIP(c, launch_gemv(qkv, c->bf16, st));
-    } else {
-        { PHASE(c, PH_DEC_QKV); SPTS_HIP(c, launch_gemv(qkv, c->bf16, st)); }
+    if (c->dec_rope_pos != pos) {
         PHASE(c, PH_DEC_ROPE_APPEND);
-        SPTS_HIP(c, launch_decode_rope_append(q, kx, vx, pos, m.H, m.Hkv, m.d, m.rope_base, cache->k, cache->v, cache->pos, row,
-                                              c->bf16, st));
+        SPTS_HIP(c, launch_decode_rope_row(pos, m.d, m.rope_base, c->p<float2>(c->off.rope), st));
+        c->dec_rope_pos = pos;
     }
+    qkv.rope = c->p<float2>(c->off.rope); qkv.head_dim = m.d;
+    qkv.y[1] = (char*)cache->k + (size_t)row * KV * eb;
+    qkv.y[2] = (char*)cache->v + (size_t)row * KV * eb;
+    qkv.pos_out = cache->pos + row; qkv.pos_val = pos;
+    { PHASE(c, PH_DEC_QKV); SPTS_HIP(c, launch_gemv(qkv, c->bf16, st)); }
     { PHASE(c, PH_DEC_ATTN);
       SPTS_HIP(c, launch_decode_attn(q, cache->k, cache->v, row + 1, m.H, m.Hkv, m.d, part, part_floats, att, c->bf16, st)); }
     { PHASE(c, PH_DEC_O); SPTS_HIP(c, launch_gemv(o, c->bf16, st)); }

@@ -200,7 +200,7 @@ hipError_t launch_transpose_pad(const void* v, void* vt, int64_t M, int C, int64
 // min(k[b], length), written to idx_out + out_offsets[b] as indices local to the segment, or (whole) as indices into `scores`; N is then the
 // longest segment.
 struct TopkSegments { const int64_t* offsets; const int64_t* k; const int64_t* out_offsets; int whole; };
-// With a map, map_out[j] = map_in[idx_out[j]] too (N <= TOPK_REG_MAX_N, no segments).
+// With a map, map_out[j] = map_in[idx_out[j]] too (N <= TOPK_ONE_MAX_N, no segments).
 struct TopkMap { const int32_t* in; int32_t* out; };
 hipError_t launch_topk(const float* scores, int64_t N, int64_t k, int protect_last, int32_t* idx_out,
                        int batch, hipStream_t s, TopkSegments seg = TopkSegments{nullptr, nullptr, nullptr, 0}, TopkMap map = TopkMap{nullptr, nullptr});
@@ -280,7 +280,6 @@ hipError_t launch_topk_mean(const void* vals, int64_t ld, int64_t rows, int64_t 
 
 // ------------------------------------------------------------------ decode phase (one new token)
 enum GemvMode : int {
-    GEMV_STORE = 0,   // y[r] = W[r,:].x                     (T)
     GEMV_SILU = 1,    // y[r] = silu(W0[r,:].x) * W1[r,:].x  (T; R[0] rows each)
     GEMV_RESID = 2,   // y[r] += W[r,:].x                    (T, read-modify-write)
     GEMV_F32 = 3,     // y[r] = W[r,:].x                     (fp32)
@@ -302,9 +301,6 @@ bool gemv_supported(const GemvArgs& a, bool bf16);
 hipError_t launch_gemv(const GemvArgs& a, bool bf16, hipStream_t s);
 // (cos, sin) of one position for the decode GEMV's rotary epilogue: table[j] = (cos, sin)(pos * base^(-2j/d))
 hipError_t launch_decode_rope_row(int pos, int d, float base, float2* table, hipStream_t s);
-// rotary embedding of q [H, d] in place and of k [Hkv, d] into cache row `row`, v copied to that row
-hipError_t launch_decode_rope_append(void* q, const void* k, const void* v, int pos, int H, int Hkv, int d, float base,
-                                     void* cache_k, void* cache_v, int32_t* cache_pos, int64_t row, bool bf16, hipStream_t s);
 // out [H, d] = softmax(q K^T / sqrt(d)) V over the M cached pairs K, V [M, Hkv, d]; part: fp32 scratch
 bool decode_attn_supported(int H, int Hkv, int d, bool bf16);
 size_t decode_attn_min_scratch_floats(int Hkv, int d);
@@ -317,7 +313,7 @@ struct DecodeBatch {
     void* cache_k[DECODE_MAX_BATCH]; void* cache_v[DECODE_MAX_BATCH]; int32_t* cache_pos[DECODE_MAX_BATCH];
     int64_t count[DECODE_MAX_BATCH]; int32_t pos[DECODE_MAX_BATCH]; int32_t n;
 };
-// Y[b, r] = W[r, :] . X[b, :] for nb <= DECODE_MAX_BATCH input vectors (X [nb, K], Y[i] [nb, R[i]] contiguous); modes STORE, SILU,
+// Y[b, r] = W[r, :] . X[b, :] for nb <= DECODE_MAX_BATCH input vectors (X [nb, K], Y[i] [nb, R[i]] contiguous); modes SILU,
 // RESID, F32; with gamma (a norm of X inside) or ssq only what gemv_mfma_supported takes
 bool gemv_mfma_supported(const GemvArgs& a, int nb);
 hipError_t launch_gemv_nb(const GemvArgs& a, int nb, bool bf16, hipStream_t s);
