@@ -379,7 +379,7 @@ def test_batched_decode_norms_and_rotary_inside_the_products(torch, D, H_, Hkv, 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("H_,Hkv,d", [(8, 8, 128), (8, 4, 64), (32, 8, 128), (14, 2, 128), (8, 1, 32), (16, 4, 16), (16, 2, 16), (6, 1, 64)])
 def test_decode_attention_keys_per_split(torch, dtype, H_, Hkv, d):
-    """Every way heads share a key's lanes (1 / 2 / 4 / 8 heads over 2 .. 32 lanes), with few and with many keys to a split: one sequence alone, then
+    """Every way heads share a key's lanes (1 / 2 / 4 / 8 heads over 2 .. 32 lanes), with few and with many keys to a split: one sequence alone (at most 64 to a split), then
     16 at once, whose longest cache has just under and just over 512 keys to each of the launch's splits; a split's last keys are one short, whole, one more."""
     shape = synth.ModelShape(D=256, H=H_, Hkv=Hkv, d=d, Dff=256, dtype=dtype)
     mdl, rnd, tol = H.oracle_model(shape), H.rnd_for(dtype), H.TOL[dtype]["hidden"]
@@ -408,3 +408,41 @@ def test_decode_attention_keys_per_split(torch, dtype, H_, Hkv, d):
             for b in range(len(lens)) if batched else (0, 3):
                 ref_x, _ = orc.decode_layer(x_in[b], pos[b], w, mdl, orc.LayerCache(*before[b]), rnd)
                 assert H.row_rel_err(got[b][None, :], ref_x.reshape(1, -1)) <= tol, (longest, batched, b)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("H_,Hkv", [(3, 3), (4, 2), (8, 2), (6, 2), (16, 2), (7, 1)])
+def test_decode_attention_of_one_sequence_takes_two_keys_at_a_time(torch, dtype, H_, Hkv, d):
+    """The single sequence's kernel on either side of 512 keys to a split (two keys of a lane at a time from there on): scratch for three splits,
+    whose last has fewer keys or as many, and one split of few and of many; against 64 bits."""
+    import ctypes as C
+    from paper_2601_13155_amd import binding
+    lib = binding.load()
+    splits, launch = lib._ZN4spts18decode_attn_splitsEliimi, lib._ZN4spts18launch_decode_attnEPKvS1_S1_liiiPfmPvbP12ihipStream_t
+    splits.restype, splits.argtypes = C.c_int, [C.c_int64, C.c_int, C.c_int, C.c_size_t, C.c_int]
+    launch.restype = C.c_int
+    launch.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p, C.c_bool, C.c_void_p]
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(H_ * 1000 + d)
+    grp = H_ // Hkv
+    for want, M in ((3, 1532), (3, 1533), (3, 1534), (3, 1536), (3, 1537), (3, 2050), (1, 511), (1, 512), (1, 513), (1, 1027)):
+        floats = want * Hkv * 8 * (d + 2)
+        assert splits(M, Hkv, d, floats, 1) == want
+        q = (2.0 * torch.randn((H_, d), generator=g, device="cuda")).to(t)
+        k, v = (torch.randn((M, Hkv, d), generator=g, device="cuda").to(t) for _ in range(2))
+        part = torch.full((floats + 8,), 7.0, device="cuda")
+        out = torch.full((H_ * d + 8,), -7.0, device="cuda", dtype=t)
+        assert launch(q.data_ptr(), k.data_ptr(), v.data_ptr(), M, H_, Hkv, d, part.data_ptr(), floats, out.data_ptr(), dtype == "bf16",
+                      torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        assert bool((part[floats:] == 7.0).all()) and bool((out[H_ * d:] == -7.0).all())
+        got = out[:H_ * d].double().reshape(H_, d)
+        for h in range(H_):
+            kh, vh, qh = k[:, h // grp].double(), v[:, h // grp].double(), q[h].double()
+            p = torch.softmax(kh @ qh / d ** 0.5, 0)
+            ref, size = p @ vh, p @ vh.abs()
+            # sums of d products in fp32 (and the scale) in the exponent of every weight, of M weights in numerator and denominator; one rounding
+            exponent = 2.0 * (d + 4) * 2.0 ** -24 * float((kh.abs() @ qh.abs()).max()) / d ** 0.5
+            bound = (exponent + (2 * M / 16 + 64) * 2.0 ** -24) * size + (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * ref.abs()
+            assert bool(((got[h] - ref).abs() <= bound).all()), (want, M, h, float(((got[h] - ref).abs() / bound).max()))

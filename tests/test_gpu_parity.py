@@ -66,13 +66,13 @@ def test_select_topk_bit_exact(torch):
                     assert int(out[0]) == -7
 
 def test_select_topk_chip_wide_bit_exact(torch):
-    """Rows longer than one workgroup's registers take the chip-wide radix select (a launch per pass over up to 128
-    workgroups): lengths around its slice sizes (1, 2, 4 and 8 keys per lane) up to its maximum of 2^20 scores, back
-    to back on one context (the scratch tables are reused from call to call), same adversarial value patterns."""
+    """Single rows of more than 20480 scores take the chip-wide radix select (a launch per pass over up to 128
+    workgroups), shorter ones a workgroup: lengths around that limit, around its slice sizes (1, 2, 4 and 8 keys per lane) and up to its maximum of 2^20
+    scores, back to back on one context (the scratch tables are reused from call to call), same adversarial value patterns."""
     rng = np.random.default_rng(1)
     shape = synth.ModelShape(D=32, H=1, Hkv=1, d=16, Dff=32, dtype="f32")
     ctx = runtime.make_context(shape, 1 << 20, 4, 4, 32)
-    for n in (20000, 20001, 32769, 131071, 131073, 262144, 262145, 300001, 524288, 524289, (1 << 20) - 5, 1 << 20):
+    for n in (20000, 20001, 20480, 20481, 24577, 32768, 32769, 131071, 131073, 262144, 262145, 300001, 524288, 524289, (1 << 20) - 5, 1 << 20):
         cases = {
             "uniform": rng.random(n).astype(np.float32),
             "all_equal": np.full(n, 0.25, dtype=np.float32),
@@ -481,6 +481,20 @@ def test_active_queries_search_their_visible_keys(torch, N):
     H.lockstep_layer(got, x, pos, w, H.oracle_model(shape), orc.LayerCfg(1, P, ma, N, 1, 1), shape.dtype)
 
 
+@pytest.mark.parametrize("N", [20480, 20481, 33000])
+def test_active_positions_of_long_rows(torch, N):
+    """All keys kept: the active rows' positions come with the selection up to 20480 candidates and from a launch of their own beyond.  Positions with gaps,
+    so that a row index in the place of a position shows in the rotation and in what is visible."""
+    shape = synth.ModelShape(D=64, H=2, Hkv=1, d=32, Dff=64, dtype="f32")
+    ctx = ctx_for(shape, 33000, max_probe=4, max_r=16)
+    w = dict(synth.make_layer(47, 0, shape, 16))
+    w["Wk"] = (4.0 * np.asarray(w["Wk"], dtype=np.float32)).astype(np.float32)
+    x = synth.hidden_states(47, N, shape.D, shape.dtype)
+    pos = np.cumsum(np.random.default_rng(N).integers(1, 4, N)).astype(np.int32)
+    got = runtime.run_layer(ctx, x, pos, runtime.upload_layer(w, shape, 16), shape, skip=1, probe_len=4, m_attn=300, m_ffn=N, kv_mode=1)
+    H.lockstep_layer(got, x, pos, w, H.oracle_model(shape), orc.LayerCfg(1, 4, 300, N, 1, 1), shape.dtype)
+
+
 @pytest.mark.parametrize("N", [2048, 2049])
 def test_attention_workgroups_of_four_and_eight(torch, N):
     """256 workgroups of eight wavefronts run as twice as many of four, 264 as they are; the same layer on both sides."""
@@ -771,13 +785,12 @@ def test_layer_prefill_batched_dense_branch(torch, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_msdp_compact_batched_bit_exact(torch, dtype):
+@pytest.mark.parametrize("lens,nnext", [((257, 3, 1000, 64, 1), (100, 5, 999, 0, 1)), ((5, 33000, 700, 40001, 32768), (4, 20000, 1, 40000, 9))], ids=["short", "long"])
+def test_msdp_compact_batched_bit_exact(torch, dtype, lens, nnext):
     """Stage-end pruning of a batch: per sequence the maps the oracle's compaction gives on the same fp32 scores
     (as rows of the batch), rows and positions copied bit for bit; ties inside a sequence, an empty target and a
-    target above the length included."""
+    target above the length included; sequences on either side of the 32768 scores that one workgroup's registers hold."""
     shape = H.small_shape(dtype=dtype)
-    lens = (257, 3, 1000, 64, 1)
-    nnext = (100, 5, 999, 0, 1)
     offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     Ntot = int(offs[-1])
     rng = np.random.default_rng(11)
@@ -785,7 +798,7 @@ def test_msdp_compact_batched_bit_exact(torch, dtype):
     sc[300:700] = np.float32(0.25)                       # a run of ties inside the third sequence
     x = synth.hidden_states(5, Ntot, shape.D, dtype)
     pos = np.concatenate([np.sort(rng.choice(4 * n + 3, size=n, replace=False)) for n in lens]).astype(np.int32)
-    ctx = ctx_for(shape, 2048)
+    ctx = ctx_for(shape, max(2048, Ntot))
     xd = runtime.to_device(x, dtype); pd = torch.from_numpy(pos).cuda(); sd = torch.from_numpy(sc).cuda()
     keep = [min(n, k) for n, k in zip(lens, nnext)]
     KT = sum(keep)
