@@ -380,7 +380,9 @@ __device__ __forceinline__ void small_product(const GemmArgs& a, int nM, int nN,
 }
 
 // Pairs are for products that move more than they wait: shares of at least 96 slabs, tiles of 64 or 192 rows.  Gate/up of 64 / 133 / 333 / 700 rows
-// of the 8B shape (128 slabs, slab-major weights) 44.4 -> 41.5, 60.2 -> 54.8, 108.9 -> 90.9, 190.2 -> 171.1 us.  A shorter share's first loads and last slabs
+// of the 8B shape (128 slabs, slab-major weights) 44.4 -> 41.5, 60.2 -> 54.8, 108.9 -> 90.9, 190.2 -> 171.1 us.  14336 columns, weights from HBM, 64 / 180 / 550 rows: 96 slabs
+// 33.4 -> 31.6, 57.0 -> 46.0, 123.8 -> 109.8; 104 36.1 -> 33.9, 61.9 -> 49.3, 136 -> 118; 112 39.1 -> 36.3, 67.3 -> 52.6, 146 -> 125 (Qwen layer of 384 rows 327 -> 295).  With all of
+// a layer's weights in the memory-side cache 96 slabs can lose: 3072 wide, 8192 columns, 333 rows 43.6 -> 46.9.  A shorter share's first loads and last slabs
 // cost what the lines save (4096 x 4096, 133 rows, 32 slabs 20.0 -> 21.3; 700 rows, 64 slabs 39.8 -> 40.8), and so it is with tiles of 128
 // rows, where a slot has two iterations for its loads but half the work (gate/up of 133 rows 65.7 -> 69.6, 700 of 4096 x 4096 40.4 -> 44.2).
 template <int TM> __host__ __device__ constexpr bool small_pairs(const GemmArgs& a, int ksplit) {
@@ -474,9 +476,9 @@ bool gemm_small_supported(const GemmArgs& a) {
 // Time models (us) behind the choice between the two kernels and among this one's tiles and splits, fitted to 170 measured
 // (product, rows) pairs x 24 (tile, split) pairs: rows 1 .. 16000 of the 8B shape's projections, FFN and proxy products, with kernels
 // that read their fragments later and row-major operands in half lines.  The constants were not fitted again since; what counts is the
-// choice, and that was measured with the present kernels, weights from HBM, 7 products x 18 row counts: against the best of everything
-// tried it costs 0.2 % on the mean and 7 % at most (K projection of 800 rows) with slab-major weights, 0.4 % and 12 % (of 5003 rows)
-// with row-major ones.
+// choice, and that was measured with the present kernels (long shares of row-major rows in pairs of slabs), weights from HBM, 7 products x 18 row counts: against the
+// best of everything tried it costs 0.5 % on the mean and 21 % at most (down of 100 rows, 8 shares for 6: 40.9 us, 33.9) with slab-major weights, 0.4 %
+// and 11 % (proxy z of 800 rows) with row-major ones.
 //  * this kernel: a K slab takes the load latency (0.18 / 0.31 / 0.38 us at TM = 64 / 128 / 192) or, with more workgroups, the
 //    47 KB/us that a CU's slab loads reach together (rows past M repeat a line and cost a third); a split adds the finish launch
 //    and its fp32 tiles written and read at 4 TB/s.

@@ -212,8 +212,9 @@ constexpr int TOPK_MULTI_MAX_WG = 128;
 constexpr int64_t TOPK_MULTI_MAX_N = (int64_t)TOPK_MULTI_MAX_WG * 8192;
 constexpr int64_t TOPK_REG_MAX_N = 32768;     // one workgroup with the keys in registers
 // A single row of up to this many scores (20 to a lane of 16 wavefronts) takes one workgroup, longer ones the chip.  The two TopK of a layer with one workgroup / over the
-// chip: 20011 rows (one probe row) 40 / 50 us, 18001 (64) 52 / 52, 23000 57 / 54, 32768 71 / 55; compaction of 18000 rows 48 / 51, 30000 90 / 85.  (Calls by
-// themselves wait for five launches on the host and say 17 and 25 us at 22937.)
+// chip, one probe row: 17000 rows 39 / 51 us, 18500 40 / 50, 20400 47 / 50, 21500 48 / 51, 23000 51 / 51, 24500 53 / 51; 64 probe rows: 17000 41 / 51, 18500 44 / 50, 20400
+// 48 / 52, 21500 54 / 51, 24500 56 / 52, 32768 71 / 55; compaction of 17000 rows 44.9 / 51.0, 20480 54.0 / 58.1, 22500 64.2 / 64.8, 24500 71.0 / 71.2, 30000 90 / 85: they meet
+// between 20480 and 23000.  (Calls by themselves wait for five launches on the host and say 17 and 25 us at 22937.)
 constexpr int64_t TOPK_ONE_MAX_N = 20480;
 constexpr size_t TOPK_MULTI_SCRATCH_BYTES = 2 * (size_t)TOPK_MULTI_MAX_WG * 256 * 4 + (size_t)TOPK_MULTI_MAX_WG * 4 + 64;
 // device address of this GPU's file-scope scratch array of TOPK_MULTI_SCRATCH_BYTES (looked up once per device, then cached)
