@@ -9,7 +9,7 @@
 // attention's one after the other: 24.3 us for 256 queries over 512 keys, 53.0 for 750 over 1500; now 21.0 and 47.2).
 // Measured at N = 512, 4 heads, d = 64: attention of 256 queries 50 -> 21 us against one wavefront per query row; probe of 32
 // rows 1001 -> 22 us (two launches) against one lane per candidate that walked all P * H rows.  Dense fp32 layers of 6000 rows (D = 512,
-// H d = 512) against the same: d = 16 9.2 -> 1.85 ms, 32 7.1 -> 1.24, 64 6.6 -> 1.21, 128 6.7 -> 1.42, 256 7.4 -> 1.70.
+// H d = 512, Dff = 512), 7-9 ms with those: d = 16 1.61 ms, 32 1.01, 64 0.95, 128 1.30, 256 1.52; the attention in them 1231, 634, 578, 925 and 1127 us.
 #include "spts_internal.h"
 
 namespace spts {
